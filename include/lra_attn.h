@@ -321,6 +321,9 @@ lra_status lra_attn_decode_static(const lra_shape* shape, const lra_cache* cache
  *   q    DEVICE [n_new][Hq][d]        out  DEVICE [n_new][Hq][d]
  *   seq_index in [0, n_seqs), adapter_index in [0, n_adapters)
  *   1 <= n_new <= max_seq_len; the device-side seq_lens[seq_index] must be >= n_new.
+ *   workspace  as for lra_attn_decode; with max_seq_len below 1024 and more new tokens than the
+ *              split-KV path takes a call without one (or with too small a one) is served too,
+ *              by one workgroup per 128 query rows of a kv head
  */
 lra_status lra_attn_prefill(const lra_shape* shape, const lra_cache* cache,
                             const lra_adapters* adapters, const void* q, int32_t seq_index,

@@ -126,6 +126,37 @@ lra_status check_common(const lra_shape* sh, const lra_cache* c) {
   return LRA_OK;
 }
 
+// Workgroups that share the key tiles of a q tile in the tile-walking prefill kernel: the count with the
+// smallest estimated time.  A compute unit takes two workgroups; a 64-key tile of head dimension 128 costs a
+// workgroup 1.3 us on a unit of its own and 2.1 us beside another one (so a last round of at most 256 workgroups
+// costs about half a round), a workgroup 4 us outside its tiles, and the partial states are written and read
+// back at 4.3 TB/s.  Measured on MI355X, group 4, rank 16 (us at 1 / 2 / 4 / 5 / 6 / 8 / 12 / 16 shares, chosen
+// one marked): 333 new tokens on 5333: 100 / 67 / 60 / 57* / 66 / 62 / 72 / 79; 700 on 9000: 157 / 154 / 140* /
+// 144 / 152 / 152 / 170 / 182; 1500 on 9000: 256* / 258 / 265 / 278 / 276 / 291 / 335 / 386.
+// One share, and no workspace, where q tiles of 128 tokens per q head would fill two workgroups per unit.
+static int64_t prefill_shares(const lra_shape* sh, int tokens, int max_seq_len) {
+  const int64_t slots = 2 * kCUs, tiles = (static_cast<int64_t>(max_seq_len) + 63) / 64;
+  if (static_cast<int64_t>((tokens + 127) / 128) * sh->n_q_heads >= slots) return 1;
+  const int64_t group_rows = static_cast<int64_t>(tokens) * (sh->n_q_heads / sh->n_kv_heads);
+  const int64_t wgs = (group_rows + 127) / 128 * sh->n_kv_heads;
+  const double width = (sh->head_dim + 32) / 160.0;  // (the tile's fixed part weighs like 32 columns)
+  const double alone = 1.3 * width, beside = 2.1 * width, fixed = 4.0, merge = 3.0;
+  const double per_share = static_cast<double>(tokens) * sh->n_q_heads * (sh->head_dim + sh->rank) * 8.0 / 4.3e6;
+  int64_t best = 1;
+  double best_us = 0.0;
+  for (int64_t ns = 1; ns <= 32 && ns <= tiles; ++ns) {
+    const int64_t w = wgs * ns, rest = w % slots, share = (tiles + ns - 1) / ns;
+    double us = (w / slots) * (fixed + beside * share);
+    if (rest > 0) us += fixed + (rest <= kCUs ? alone : beside) * share;
+    if (ns > 1) us += merge + per_share * ns;
+    if (ns == 1 || us < best_us) {
+      best = ns;
+      best_us = us;
+    }
+  }
+  return best;
+}
+
 Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_queries_per_seq, bool prefill,
                const Tuning& tune) {
   Plan pl{};
@@ -171,21 +202,16 @@ Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_quer
                      static_cast<int64_t>(tokens) * 4 <= c->max_seq_len;
   const bool rope_split = rope && pl.mfma && (!prefill || pl.short_prefill);  // rotary form of the split-KV kernel
   if (prefill && pl.mfma && !pl.short_prefill) {
-    // Tile-walking kernel: one workgroup per (128-row q tile, q head).  When that is fewer than
-    // two workgroups per CU, the key tiles of every q tile are divided among several workgroups
-    // (at least eight 64-key tiles each) and the merge kernel finishes the job; otherwise it is
-    // one kernel without a workspace.
+    // Tile-walking kernel: one workgroup per 128 query rows of a kv head (new tokens x the q heads that share
+    // it).  Where those do not fill the chip the key tiles of a q tile are divided among several workgroups and
+    // the merge kernel finishes the job; otherwise it is one kernel without a workspace.
     pl.rows = tokens * sh->n_q_heads;
     pl.group_pad = pl.row_tiles = pl.row_groups = 1;
     pl.split_keys = c->max_seq_len;
-    const int64_t wgs = static_cast<int64_t>((tokens + 127) / 128) * sh->n_q_heads;
-    int64_t ns = tune.prefill_splits;
-    if (ns <= 0) {  // automatic: two workgroups per CU, at least eight key tiles per share
-      ns = (2 * kCUs + wgs - 1) / wgs;
-      const int64_t max_ns = c->max_seq_len / (8 * 64);
-      ns = ns > max_ns ? max_ns : ns;
-    }
+    int64_t ns = tune.prefill_splits > 0 ? tune.prefill_splits : prefill_shares(sh, tokens, c->max_seq_len);
     ns = ns > 32 ? 32 : (ns < 1 ? 1 : ns);
+    // (sequences below sixteen tiles ran without a workspace always: a call that brings none still does)
+    pl.workspace_optional = ns > 1 && tune.prefill_splits <= 0 && c->max_seq_len < 1024;
     pl.n_splits = static_cast<int>(ns);
     pl.bytes = 0;
     if (pl.n_splits > 1) {

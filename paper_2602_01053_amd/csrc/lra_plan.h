@@ -36,6 +36,7 @@ struct Plan {
   int n_splits;    // splits per sequence at max_seq_len
   int group_pad, row_tiles, row_groups;  // MFMA decode row packing
   int l_block;     // split-KV MFMA kernels with per-adapter low-rank caches: padded rank of one slot's column block, else 0
+  bool workspace_optional;  // prefill: without room for the plan's workspace the call runs with one share per q tile
   bool launchable;  // false: a grid dimension would exceed the limit of 65535 in y or z (LRA_ERR_UNSUPPORTED)
   size_t off_ml, off_o, off_lr, off_adapter, off_qt, qt_bytes, bytes;
   // rotary prefill with the completed keys in the workspace: their offset and size (0: none), and

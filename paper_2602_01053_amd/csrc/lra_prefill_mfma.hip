@@ -9,8 +9,11 @@
 // and after the last tile O^T += B_V^T . Olr^T (one more MFMA k-step per 16 ranks),
 // O /= l.  Qt = Q B_K^T is formed once per wave before the loop (MFMA).
 //
-// A workgroup owns 128 query rows of one q head (4 waves x 32 rows) and walks the
-// key tiles up to its causal limit.  v_mfma_f32_32x32x16_bf16 throughout; the
+// A workgroup owns 128 query rows of one kv head (4 waves x 32 rows; a row is a new token of one
+// of the q heads that share the kv head, the q head fastest) and walks the key tiles up to its
+// causal limit.  Rows of all q heads in one tile: a tile of 128 tokens per q head was a quarter
+// full at 32 new tokens, and a call of few tokens took four workgroups to every key (333 tokens
+// on 5333, group 4: 76 -> 57 us with the shares planned for the packed tiles; 2048: unchanged).  v_mfma_f32_32x32x16_bf16 throughout; the
 // transposed score tile leaves P^T in the lanes that need it as the B operand of
 // the second product.  K_base / V_base / L tiles are shared by the four waves:
 // every wave requests its quarter of the next tile straight from HBM into the
@@ -19,7 +22,7 @@
 // ds_read_b128 feeds the K operand, ds_read_b64_tr_b16 the transposed V and L
 // operands, both scheduled several products ahead.  Two workgroups share a CU, so
 // the softmax arithmetic of one overlaps the matrix work of the other.
-// Workgroups are numbered so that all q heads of a kv head run on the same XCD and
+// Workgroups are numbered so that all q tiles of a kv head run on the same XCD and
 // share its L2.
 #include "lra_prefill_util.h"
 
@@ -78,19 +81,18 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(Params p) {
   const int l32 = lane & 31, g2 = lane >> 5;
   const int Hq = p.n_q_heads, Hkv = p.n_kv_heads, G = p.group, r = p.rank;
 
-  // workgroup -> (kv head, q head in group, q tile); consecutive ids go to consecutive XCDs
+  // workgroup -> (kv head, q tile); consecutive ids go to consecutive XCDs
   const int lin = blockIdx.x;
   const int hk = lin % Hkv;
-  const int rest = lin / Hkv;
-  const int gq = rest % G;
-  int qt = rest / G;
+  int qt = lin / Hkv;
+  const int n_rows = p.n_new * G;                  // query rows of a kv head: (new token, q head of the group), the q head fastest
   {
     // Causal q tiles differ in length (tile i walks the keys up to its diagonal).  The 256 compute units take
     // workgroups in rounds of 256; a unit that holds two workgroups holds number k and number k + 256.  Every other
     // round walks its q tiles backwards, so the long tiles of one round sit next to the short tiles of the next
     // and the units finish together.
-    const int q_tiles = (p.n_new + BM - 1) / BM;
-    const int tpr = max(1, 256 / Hq);              // q tiles per round
+    const int q_tiles = (n_rows + BM - 1) / BM;
+    const int tpr = max(1, 256 / Hkv);             // q tiles per round
     const int round = qt / tpr, pos = qt - round * tpr;
     const int cnt = min(tpr, q_tiles - round * tpr);
     if ((round & 1)) qt = round * tpr + (cnt - 1 - pos);
@@ -100,16 +102,37 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(Params p) {
   const int n_t = min(PF_CONST_I32(p.seq_lens)[t], p.max_seq_len);
   const int n_new = p.n_new;
   const int q0 = qt * BM;
-  if (q0 >= n_new) return;
+  if (q0 >= n_rows) return;
   const int base_vis = n_t - n_new;  // new token i sees keys 0 .. base_vis + i
-  const int row = q0 + wave * 32 + l32;           // this lane's query row (new-token index)
-  const int n_live = n_new;                       // live rows of the tile
-  const int row_c = min(row, n_live - 1);         // clamped for loads; rows past the end are never stored
-  // token and q head of this lane's row: where its q, out and workspace rows are
-  const int grow = row, grow_c = row_c;
-  const int head = hk * G + gq;
-  const int limit = base_vis + row_c;             // last visible key of this lane's row
-  const int wg_last = base_vis + min(q0 + BM, n_new) - 1;  // last key any row of the workgroup sees
+  // First new token of the tile, how many of its q heads lie in the tile before, and the live rows of the tile.  A
+  // lane's row is in_tile = 32 wave + l32 rows further: token tok0 + (head0 + in_tile) / G, the quotient (of at most
+  // 143 by at most 16) taken exactly by a multiplication, so that it is cheap to form again wherever it is needed:
+  // kept in registers through the loop it sent the rank-64 kernels to scratch memory (the three small numbers
+  // travel in one scalar register for the same reason).
+  const int tok0 = __builtin_amdgcn_readfirstlane(q0 / G);
+  const int row_map = (q0 - tok0 * G) | (min(BM, n_rows - q0) << 4) | (__builtin_amdgcn_readfirstlane((65535 + G) / G) << 12);
+  // (token - tok0, q head of the group) of a row of the tile; false (and the last live row) for one past the end
+  auto map_row = [&](int in_tile, int& tok, int& gq) __attribute__((always_inline)) -> bool {
+    int m = row_map;
+    asm volatile("" : "+s"(m), "+v"(in_tile));
+    const int at = (m & 15) + min(in_tile, ((m >> 4) & 255) - 1);
+    tok = (at * (m >> 12)) >> 16;
+    gq = at - tok * G;
+    return in_tile < ((m >> 4) & 255);
+  };
+  // index of this lane's row in q, out and the workspace; -1: a row past the end, never stored
+  auto global_row = [&](bool clamped) __attribute__((always_inline)) -> int {
+    int tok, gq;
+    const bool live = map_row(wave * 32 + (static_cast<int>(threadIdx.x) & 31), tok, gq);
+    return live || clamped ? (tok0 + tok) * Hq + hk * G + gq : -1;
+  };
+  auto token_of = [&](int in_tile) __attribute__((always_inline)) -> int {
+    int tok, gq;
+    map_row(in_tile, tok, gq);
+    return tok0 + tok;
+  };
+  const int wave_first = __builtin_amdgcn_readfirstlane(base_vis + token_of(wave * 32));  // the smallest limit of this wave
+  const int wg_last = __builtin_amdgcn_readfirstlane(base_vis + token_of(BM - 1));       // last key any row of the workgroup sees
   const int n_tiles = wg_last / BN + 1;
   // this workgroup's share of the q tile's key tiles: [tile_begin, tile_end)
   const int split = SPLIT ? blockIdx.y : 0;
@@ -118,11 +141,12 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(Params p) {
   if (SPLIT && tile_begin >= tile_end) {
     // more workgroups than key tiles: leave an empty state (zero row sum), all the merge
     // kernel looks at
-    if (row < n_live && g2 == 0) {
-      const int64_t slot = (static_cast<int64_t>(grow) * Hq + head) * p.n_splits + split;
+    const int out_row = global_row(false);
+    if (out_row >= 0 && g2 == 0) {
+      const int64_t slot = static_cast<int64_t>(out_row) * p.n_splits + split;
       p.part_ml[slot * 2 + 0] = -INFINITY;
       p.part_ml[slot * 2 + 1] = 0.f;
-      if (split == 0) p.part_adapter[static_cast<int64_t>(grow) * Hq + head] = a_idx;
+      if (split == 0) p.part_adapter[out_row] = a_idx;
     }
     return;
   }
@@ -182,7 +206,7 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(Params p) {
   // qb[ks]: B operand of S^T: lane (row l32, k = 16ks + 8g2 + e)
   pf_bf16x8 qb[KS];
   {
-    const bf16_t* qrow = static_cast<const bf16_t*>(p.q) + (static_cast<int64_t>(grow_c) * Hq + head) * D + g2 * 8;
+    const bf16_t* qrow = static_cast<const bf16_t*>(p.q) + static_cast<int64_t>(global_row(true)) * D + g2 * 8;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) qb[ks] = pf_as_bf16x8(*reinterpret_cast<const uint4*>(qrow + ks * 16));
   }
@@ -395,7 +419,8 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(Params p) {
     }
     // causal mask + online softmax.  Element (kt, i) of this lane is key
     // j + 32kt + 8(i/4) + 4g2 + i%4 of row l32.
-    if (j + BN - 1 > base_vis + q0 + wave * 32) {  // some row of this wave does not see the whole tile
+    if (j + BN - 1 > wave_first) {  // some row of this wave does not see the whole tile
+      const int limit = base_vis + token_of(wave * 32 + (static_cast<int>(threadIdx.x) & 31));  // last visible key of this lane's row
 #pragma unroll
       for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
@@ -491,6 +516,7 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(Params p) {
   }
 
   // ---------------- epilogue: O^T += B_V^T Olr^T, O /= l, store ----------------
+  const int out_row = global_row(false);
   if (ONES_ROW) {
     // row sums sit in register 8 (rho = 32(RB-1) + 16) of the lanes with g2 == 0
     const float mine = lr_acc[RB - 1][8];
@@ -502,12 +528,12 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(Params p) {
   if (SPLIT) {
     // this share's state for the merge kernel: m in natural-log units, l, O^T and Olr^T as
     // fp32 rows [slot][d] and [slot][rank]; registers 4q..4q+3 are d (rho) = 32b + 8q + 4g2 + 0..3
-    if (row < n_live) {
-      const int64_t slot = (static_cast<int64_t>(grow) * Hq + head) * p.n_splits + split;
+    if (out_row >= 0) {
+      const int64_t slot = static_cast<int64_t>(out_row) * p.n_splits + split;
       if (g2 == 0) {
         p.part_ml[slot * 2 + 0] = m_run * 0.69314718055994530942f;
         p.part_ml[slot * 2 + 1] = l_run;
-        if (split == 0) p.part_adapter[static_cast<int64_t>(grow) * Hq + head] = a_idx;
+        if (split == 0) p.part_adapter[out_row] = a_idx;
       }
 #pragma unroll
       for (int b = 0; b < DB; ++b)
@@ -553,9 +579,9 @@ __global__ __launch_bounds__(256, 2) void prefill_mfma_kernel(Params p) {
       }
     }
   }
-  if (row < n_live) {
+  if (out_row >= 0) {
     const float inv = 1.0f / l_run;
-    bf16_t* orow = static_cast<bf16_t*>(p.out) + (static_cast<int64_t>(grow) * Hq + head) * D;
+    bf16_t* orow = static_cast<bf16_t*>(p.out) + static_cast<int64_t>(out_row) * D;
 #pragma unroll
     for (int b = 0; b < DB; ++b)
 #pragma unroll
@@ -599,8 +625,8 @@ static hipError_t launch_pf(const Params& p, dim3 grid, hipStream_t s) {
 }
 
 hipError_t launch_prefill_mfma(const Params& p, hipStream_t s) {
-  const int q_tiles = (p.n_new + 127) / 128;
-  dim3 grid(q_tiles * p.n_q_heads, p.n_splits);
+  const int q_tiles = (p.n_new * p.group + 127) / 128;
+  dim3 grid(q_tiles * p.n_kv_heads, p.n_splits);
   const int rp = p.rank <= 16 ? 16 : (p.rank <= 32 ? 32 : 64);
   if (p.head_dim == 128) {
     if (rp == 16) return launch_pf<128, 16>(p, grid, s);

@@ -186,6 +186,49 @@ def test_prefill_key_tiles_shared_by_workgroups(case):
     _gate(got, oracle_prefill(w), label=str(case))
 
 
+PACKED_ROW_CASES = [
+    # n, n_new, Hq, Hkv, d, r: the rows of a q tile are (new token, q head of the group) pairs
+    (1300, 32, 8, 2, 128, 16),     # 128 rows: exactly one tile
+    (1300, 33, 8, 2, 128, 16),     # 132: four rows in the second
+    (97, 43, 9, 3, 128, 16),       # 129 rows in groups of 3: a token's heads lie in two tiles
+    (55, 55, 7, 1, 128, 24),       # 385 rows in groups of 7, no old context: limits differ inside a wave
+    (140, 129, 32, 2, 64, 8),      # group of 16
+    (300, 129, 4, 4, 128, 64),     # group of 1
+]
+
+
+@pytest.mark.parametrize("case", PACKED_ROW_CASES, ids=lambda c: "n%d_new%d_hq%d_hkv%d_d%d_r%d" % c)
+@pytest.mark.parametrize("splits", [1, 2])
+def test_prefill_rows_of_all_heads_of_a_group_in_one_tile(case, splits):
+    n, n_new, hq, hkv, d, r = case
+    w = W.make_contiguous("packed_prefill", "prefill", seed=4500 + n + n_new, n_agents=1, n_q_heads=hq,
+                          n_kv_heads=hkv, head_dim=d, rank=r, n=n, n_new=n_new, d_model=None, b_std=0.05)
+    old_s = lra.lra_set_prefill_splits(splits)
+    old_t = lra.lra_set_short_prefill(0)
+    try:
+        got = run_prefill(w, DEV)
+    finally:
+        lra.lra_set_prefill_splits(old_s)
+        lra.lra_set_short_prefill(old_t)
+    _gate(got, oracle_prefill(w), label=str(case))
+
+
+@pytest.mark.parametrize("n,n_new", [(417, 84), (1023, 300)])
+def test_short_sequence_prefill_with_and_without_a_workspace(n, n_new):
+    w = W.make_contiguous("short_sequence", "prefill", seed=4700 + n, n_agents=1, n_q_heads=8, n_kv_heads=2,
+                          head_dim=128, rank=16, n=n, n_new=n_new, d_model=None, b_std=0.05)
+    ref = oracle_prefill(w)
+    for with_workspace in (True, False):
+        dw = DeviceWorkload(w, DEV)
+        assert dw.alloc_workspace() > 0
+        if not with_workspace:
+            dw.workspace = None
+        dw.out.fill_(float("nan"))
+        dw.prefill()
+        torch.cuda.synchronize()
+        _gate(dw.out.to(torch.float64).cpu().numpy(), ref, label=f"workspace {with_workspace}")
+
+
 def test_short_prefill_on_paged_cache_value_only():
     """Split-KV prefill of 5 new tokens on a paged, ragged cache without B_K."""
     w = W.make_paged("paged_short_prefill", seed=92, seq_lens=[40, 333, 1500], agents_per_seq=1, n_adapters=3,
