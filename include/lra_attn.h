@@ -215,11 +215,12 @@ typedef struct {
  *                      to the kernel's key tile; 0 automatic
  *   short_prefill      bf16 prefill calls with at most this many new tokens (and a context at
  *                      least four times as long) run on the split-KV decode kernels, the new
- *                      tokens standing in for the agents; 0 automatic (32, the measured
- *                      crossover), negative: never
+ *                      tokens standing in for the agents, where their sizes make that the
+ *                      faster path; 0 automatic (32), above 32: whatever the sizes,
+ *                      negative: never
  *   prefill_splits     workgroups that share the key tiles of one q tile in the tile-walking
  *                      prefill kernel (1..32; more than one ends with the merge kernel);
- *                      0 automatic (two workgroups per CU, at least eight 64-key tiles each)
+ *                      0 automatic (the smallest estimated time)
  *   rope_key_prepass   prefill calls of the tile-walking kernel with the rotary key side
  *                      (key_rope_theta > 0 and a b_k): 0 automatic (the completed keys
  *                      K_base + RoPE(L B_K) of the call's adapter and sequence are written once

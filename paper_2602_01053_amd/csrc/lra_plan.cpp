@@ -157,6 +157,22 @@ static int64_t prefill_shares(const lra_shape* sh, int tokens, int max_seq_len) 
   return best;
 }
 
+// Whether a prefill of few new tokens (no rotary key side) runs on the tile-walking kernel rather than on the
+// split-KV decode kernels.  Those take 16 rows per tile and, beyond 32 rows of a kv head, read the keys once per row
+// group; the tile-walking kernel has one tile for 128 rows, at the price of 128 rows' matrix work per key.
+// Measured on MI355X, us split-KV / tile walk (group 4, 8 kv heads): contiguous, 4 new tokens (one row tile):
+// 10.2 / 10.7 after 2000, 31.4 / 39.5 after 33000; 8: 18.7 / 17.3 after 9001, 34.7 / 39.7 after 33000; 16: 13.9 /
+// 14.0, 21.5 / 19.0 and 45.0 / 43.3 after 2000, 9001 and 33000; 32: 15.6 / 17.2, 27.3 / 23.3 and 66.5 / 47.7.
+// Paged: 8: 14.9 / 12.4, 21.9 / 18.4 and 42.9 / 40.1; 32: 18.2 / 18.0, 31.5 / 24.9 and 89.9 / 47.4.
+static bool short_prefill_walks_tiles(const lra_shape* sh, const lra_cache* c, int tokens) {
+  const int G = sh->n_q_heads / sh->n_kv_heads;
+  const int rows = tokens * (G <= 4 ? 4 : (G <= 8 ? 8 : 16));  // rows of a kv head in the split-KV kernels
+  if (rows <= 16) return false;
+  if (c->block_size != 0) return true;
+  if (sh->n_kv_heads * ((rows + 31) / 32) <= 8) return c->max_seq_len <= 8192 + 1024;
+  return tokens * G <= 96 || c->max_seq_len >= 4096;
+}
+
 Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_queries_per_seq, bool prefill,
                const Tuning& tune) {
   Plan pl{};
@@ -194,12 +210,11 @@ Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_quer
     if (l_rows * l_pitch * 2 > lim) pl.mfma = false;
     if (c->block_size == 0 && static_cast<int64_t>(c->max_seq_len) * c->kv_token_stride * 2 > lim) pl.mfma = false;
   }
-  // A handful of new tokens after a long context gives the tile-walking prefill kernel one
-  // workgroup per q head and nothing to split; the split-KV decode kernel, with the new
-  // tokens in the place of the agents and a causal limit per row, spreads the context over
-  // the chip instead.  (Measured crossover on MI355X: see kShortPrefill.)
+  // A handful of new tokens after a long context: the split-KV decode kernel, with the new tokens in the place of
+  // the agents and a causal limit per row, or the tile-walking kernel with the key tiles shared.
   pl.short_prefill = prefill && pl.mfma && tokens <= tune.short_prefill &&
-                     static_cast<int64_t>(tokens) * 4 <= c->max_seq_len;
+                     static_cast<int64_t>(tokens) * 4 <= c->max_seq_len &&
+                     (tune.short_prefill > 32 || rope || !short_prefill_walks_tiles(sh, c, tokens));
   const bool rope_split = rope && pl.mfma && (!prefill || pl.short_prefill);  // rotary form of the split-KV kernel
   if (prefill && pl.mfma && !pl.short_prefill) {
     // Tile-walking kernel: one workgroup per 128 query rows of a kv head (new tokens x the q heads that share
@@ -210,8 +225,9 @@ Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_quer
     pl.split_keys = c->max_seq_len;
     int64_t ns = tune.prefill_splits > 0 ? tune.prefill_splits : prefill_shares(sh, tokens, c->max_seq_len);
     ns = ns > 32 ? 32 : (ns < 1 ? 1 : ns);
-    // (sequences below sixteen tiles ran without a workspace always: a call that brings none still does)
-    pl.workspace_optional = ns > 1 && tune.prefill_splits <= 0 && c->max_seq_len < 1024;
+    // (sequences below sixteen tiles run without a workspace too, where they are not short prefills)
+    pl.workspace_optional = ns > 1 && tune.prefill_splits <= 0 && c->max_seq_len < 1024 &&
+                            (tokens > tune.short_prefill || static_cast<int64_t>(tokens) * 4 > c->max_seq_len);
     pl.n_splits = static_cast<int>(ns);
     pl.bytes = 0;
     if (pl.n_splits > 1) {

@@ -94,6 +94,7 @@ typedef const __attribute__((address_space(4))) int32_t* pf_const_i32;
 #define PF_CONST_I32(p) ((pf_const_i32)(p))
 
 constexpr uint32_t kPfOob = 0x80000000u;  // beyond any resource this kernel builds
+constexpr uint32_t kPfPoolBytes = 0x7ffff000u;  // size of the resources over a whole paged pool
 
 // Rotary angles.  Pair dd of a head turns by pos * theta^(-2 dd / d) radians; the kernels keep
 // that rate in revolutions (divided by 2 pi) in double precision, so that the product with a
@@ -135,8 +136,10 @@ template <int LCH> __device__ __forceinline__ int pf_swz_l(int key) {
 // which the swizzle of its rows does not depend on q: one K, one V offset per lane.
 // Rows past the sequence (and chunks past the rank) lie outside the resource: they read as
 // zero and touch no memory; such keys are masked anyway.  A stage is laid out as
-// [K tile][V tile][L tile].
-template <int D, int RP, bool PAGED>
+// [K tile][V tile][L tile].  POOL: a paged cache whose K_base and V_base pools lie within 32-bit byte
+// offsets (prefill_pool_fits); larger pools take a resource per load, some thirty scalar
+// instructions each.
+template <int D, int RP, bool PAGED, bool POOL = false>
 struct PfTileLoader {
   static constexpr int BN = 64;
   static constexpr int KCH = D / 8;              // 16-byte chunks per K/V row
@@ -149,19 +152,26 @@ struct PfTileLoader {
 
   const Params& p;
   const bf16_t *kb, *vb;
-  pf_const_i32 bt;
   pf_u32x4 rs_k, rs_v, rs_l;
   uint32_t ts2, r2, lp2, lds0, k_voff, v_voff, l_voff[L_DMA];  // lp2: bytes between L rows
-  int wave, lane, hk, n_t, nb_last;
+  int wave, lane, hk, seq, n_t, nb_last;
+  // Paged cache: the block ids of an aligned group of 64 blocks (16 tiles), lane l holding that of block l of the
+  // group.  A tile takes its four by v_readlane.  (Looked up by scalar loads where the requests are formed, every
+  // tile began with a memory round trip: 1.29 against 1.07 us per tile on a unit of its own, that of contiguous rows.)
+  mutable int ids = 0;
+  // reads the ids of the group of block b (clamped to the sequence's last block)
+  __device__ __forceinline__ void fetch_ids(int b) const {
+    ids = p.block_table[static_cast<int64_t>(seq) * p.max_blocks_per_seq + min((b & ~63) + lane, nb_last)];
+  }
+  __device__ __forceinline__ int block_id(int b) const { return __builtin_amdgcn_readlane(ids, b & 63); }
 
   __device__ __forceinline__ PfTileLoader(const Params& p_, unsigned char* smem, int wave_, int lane_, int hk_, int t,
                                           int n_t_)
-      : p(p_), wave(wave_), lane(lane_), hk(hk_), n_t(n_t_) {
+      : p(p_), wave(wave_), lane(lane_), hk(hk_), seq(t), n_t(n_t_) {
     kb = static_cast<const bf16_t*>(p.k_base);
     vb = static_cast<const bf16_t*>(p.v_base);
     // the rows of the call's one adapter (BaseShared: its own low-rank cache), with their own stride
     const bf16_t* lr = static_cast<const bf16_t*>(p.l) + static_cast<int64_t>(p.adapter_index) * p.l_adapter_stride;
-    bt = PF_CONST_I32(p.block_table) + static_cast<int64_t>(t) * p.max_blocks_per_seq;
     const int r = p.rank;
     ts2 = static_cast<uint32_t>(p.kv_token_stride) * 2u;
     r2 = static_cast<uint32_t>(r) * 2u;
@@ -187,6 +197,12 @@ struct PfTileLoader {
         l_voff[q] = (lch * 8 < r) ? static_cast<uint32_t>(lane / LCH) * lp2 + (lch << 4) : kPfOob;
       }
     } else {
+      if (POOL) {
+        const int64_t hoff = static_cast<int64_t>(hk) * p.kv_head_stride;
+        // (every block lies below that size, kPfOob beyond it)
+        rs_k = pf_rsrc(kb + hoff, kPfPoolBytes);
+        rs_v = pf_rsrc(vb + hoff, kPfPoolBytes);
+      }
       // paged L: one resource over the whole array; the lane's physical row is chosen per tile
       rs_l = pf_rsrc(lr, (static_cast<uint32_t>(p.num_blocks) * 16u - 1u) * lp2 + r2);
     }
@@ -200,10 +216,22 @@ struct PfTileLoader {
       const uint32_t soff = static_cast<uint32_t>(j + i * KROWS) * ts2;
       pf_load16_to_lds(rs_k, dst, k_voff, soff);
       pf_load16_to_lds(rs_v, dst + K_BYTES, v_voff, soff);
+    } else if (POOL) {
+      // one resource per pool: a load is a multiplication and an addition away from its block id.  The rows of one
+      // load lie in one 16-token block; those past the end of the sequence are cut by the lane's offset.
+      const int tok = j + i * KROWS;
+      const bool ok = tok + lane / KCH < n_t;
+      const uint32_t bs2 = static_cast<uint32_t>(p.kv_block_stride) * 2u;
+      const uint32_t in_blk = static_cast<uint32_t>(tok & 15) * ts2;
+      const uint32_t soff = static_cast<uint32_t>(block_id(tok >> 4)) * bs2 + in_blk;
+      // (completed keys left by the pre-pass lie at the block's logical index)
+      const uint32_t soff_k = p.keys_f16 ? static_cast<uint32_t>(min(tok >> 4, nb_last)) * bs2 + in_blk : soff;
+      pf_load16_to_lds(rs_k, dst, ok ? k_voff : kPfOob, soff_k);
+      pf_load16_to_lds(rs_v, dst + K_BYTES, ok ? v_voff : kPfOob, soff);
     } else {
       // the KROWS rows of one load lie in one 16-token block
       const int tok = j + i * KROWS;
-      const int blk = bt[min(tok >> 4, nb_last)];
+      const int blk = block_id(tok >> 4);
       const int nv = max(0, min(KROWS, n_t - tok));  // rows of this load inside the sequence
       const uint32_t bytes = nv > 0 ? static_cast<uint32_t>(nv - 1) * ts2 + D * 2 : 0u;
       const int64_t off = static_cast<int64_t>(blk) * p.kv_block_stride + static_cast<int64_t>(hk) * p.kv_head_stride +
@@ -225,10 +253,10 @@ struct PfTileLoader {
         if (!PAGED) {
           pf_load16_to_lds(rs_l, dst, l_voff[q], static_cast<uint32_t>(j + i * LROWS) * lp2);
         } else {
-          // LROWS rows span at most two blocks; their ids are wave-uniform (scalar loads)
+          // LROWS rows span at most two blocks
           const int tok0 = j + i * LROWS;
-          const int blk_a = bt[min(tok0 >> 4, nb_last)];
-          const int blk_b = bt[min((tok0 >> 4) + 1, nb_last)];
+          const int blk_a = block_id(tok0 >> 4);
+          const int blk_b = LROWS > 16 ? block_id((tok0 >> 4) + 1) : blk_a;  // (16 rows or fewer lie in one block)
           const int lrow = i * LROWS + lane / LCH;
           const int tok = tok0 + lane / LCH;
           const int blk = ((tok >> 4) == (tok0 >> 4)) ? blk_a : blk_b;
@@ -247,6 +275,8 @@ struct PfTileLoader {
 #pragma unroll
     for (int q = 0; q < KV_DMA; ++q) issue_kv(j, stage_off, q);
     issue_l(j, stage_off);
+    // the ids of the next sixteen tiles travel behind the requests of the last of this sixteen
+    if (PAGED && (((j >> 4) + 4) & 63) == 0) fetch_ids((j >> 4) + 4);
   }
 };
 

@@ -284,6 +284,36 @@ def test_prefill_on_paged_cache(variant, seq, n_new):
     _gate(out.to(torch.float64).cpu().numpy(), ref, label=f"paged prefill seq {seq} n_new {n_new}")
 
 
+@pytest.mark.parametrize("n_new,splits", [(40, 1), (333, 3)])
+def test_prefill_on_a_pool_beyond_two_gigabytes(n_new, splits):
+    """Pools within 32-bit byte offsets and larger ones take different kernels: the same blocks, once dense and once
+    128 MiB apart (3.2 GB), give the same bits."""
+    w = W.make_paged("far_blocks", seed=95, seq_lens=[1, 333], agents_per_seq=1, n_adapters=2, n_q_heads=8,
+                     n_kv_heads=2, head_dim=128, rank=16, d_model=None, b_std=0.05)
+    dw = DeviceWorkload(w, DEV)
+    nb, hkv, bs, d = dw.k_base.shape
+    far = [torch.empty(nb << 26, dtype=torch.bfloat16, device=DEV).as_strided((nb, hkv, bs, d), (1 << 26, bs * d, d, 1))
+           for _ in range(2)]
+    far[0].copy_(dw.k_base)
+    far[1].copy_(dw.v_base)
+    assert nb << 27 > 1 << 31
+    far_cache = lra.make_cache(far[0], far[1], dw.l, dw.seq_lens, max(w.seq_lens), dw.block_table)
+    q = torch.randn(n_new, 8, 128, generator=torch.Generator().manual_seed(96)).to(torch.bfloat16).to(DEV)
+    old_s, old_t = lra.lra_set_prefill_splits(splits), lra.lra_set_short_prefill(0)
+    try:
+        outs = []
+        for cache in (dw.cache, far_cache):
+            out = torch.full_like(q, float("nan"))
+            ws = torch.empty(max(256, lra.lra_workspace_bytes(dw.shape, cache, 1, 1, n_new)), dtype=torch.uint8, device=DEV)
+            lra.lra_attn_prefill(dw.shape, cache, dw.b_k, dw.b_v, w.n_adapters, q, 1, 1, out, ws)
+            outs.append(out)
+        torch.cuda.synchronize()
+    finally:
+        lra.lra_set_prefill_splits(old_s)
+        lra.lra_set_short_prefill(old_t)
+    assert torch.isfinite(outs[0]).all() and torch.equal(outs[0], outs[1])
+
+
 def test_paged_small_ragged_distinct_adapters(variant):
     """Lengths that end inside a block, one adapter per query, NaN-poisoned free
     slots: nothing outside a sequence's own tokens may reach its output."""
