@@ -235,7 +235,8 @@ typedef struct {
  *   append_skinny      lra_cache_append calls with at most this many new tokens stream the
  *                      weights instead of tiling; 0 automatic (64), negative: never
  *   append_stages      LDS stages of lra_cache_append's tiled GEMM: 2, 3 or 4; 0 automatic
- *   append_tile        output tile of that GEMM: 64, 128 or 256; 0 automatic
+ *   append_tile        output tile of that GEMM: 64, 128 or 256 (where Hkv * d exceeds 256);
+ *                      0 automatic
  *   append_k_splits    parts d_model is divided into when lra_cache_append is given a workspace:
  *                      0 automatic (from the sizes), 1 never, 2..16 that many where d_model / 64
  *                      is a multiple of it

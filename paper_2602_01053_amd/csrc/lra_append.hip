@@ -298,22 +298,34 @@ __global__ __launch_bounds__(256, NS == 2 ? 2 : 1) void append_kernel(AppendPara
 }
 
 // ---------------------------------------------------------------------------------------
-// 256 features x 256 tokens per workgroup (for chunks whose tiles fill whole rounds of the chip).  At
-// 128 x 128 a step moves 32 KB into LDS for 2.1 MFLOP and every MFMA costs one 1 KB LDS read:
-// with two workgroups per compute unit the LDS is busier than the matrix pipes.  Here a wave
-// owns 128 x 128 of the output (sixteen 32 x 32 accumulators, kept in the accumulation
-// registers), reads eight operands for sixteen MFMAs, and a step moves 64 KB for 8.4 MFLOP.
-// Same LDS layout, DMA and epilogue as append_kernel; two stages of 64 KB, one workgroup per
-// compute unit.  The wave's four feature blocks are one head (d = 128: pairs (0,2), (1,3)) or
-// two (d = 64: pairs (0,1), (2,3)).  Measured: about 1.45 us per step against 0.9 us of MFMA
-// work; ahead of append_kernel when its tiles fill whole rounds of the chip (16384 tokens:
-// 277 us against 302 us), behind it otherwise (the grid of 256-wide tiles quantises worse).
+// 256 features x 256 tokens per workgroup of eight waves (for chunks whose tiles fill the chip).  At
+// 128 x 128 a step moves 32 KB into LDS for 2.1 MFLOP and every MFMA costs one 1 KB LDS read: with
+// two workgroups per compute unit the LDS is busier than the matrix pipes.  Here a wave owns 128
+// features x 64 tokens (eight 32 x 32 accumulators), reads six operands for eight MFMAs, and a step
+// moves 64 KB for 8.4 MFLOP; the two waves of a SIMD cover each other's reads and requests.  (Four
+// waves of 128 x 128 left a SIMD one wave, which had to interleave its requests with its products by
+// hand and had no registers left for the L features.)  Same LDS layout, DMA and epilogue as
+// append_kernel; two stages, one workgroup per compute unit.  The wave's four feature blocks are one
+// head (d = 128: pairs (0,2), (1,3)) or two (d = 64: pairs (0,1), (2,3)).
+//
+// The L features (at most 64) have no tiles of their own: as a column of tiles they cost a call a
+// place on every compute unit they touched (8192 tokens are 256 K/V tiles, one round of the chip,
+// and became two).  The feature tiles of a token tile share its eight 32-token blocks among them
+// (tile f takes blocks f and f + F: two at most with the host's F >= 4) and stage the L rows of w
+// beside their own; waves 0-3 take one k-slice of a step each for the first block, waves 4-7 for the
+// second, one or two MFMAs beside thirty-two.  The four slices are added through LDS at the end.
+//
+// Workgroup -> tile: an XCD takes every eighth token tile and all feature tiles of it, one after
+// the other, so that the 32 tiles it works on at a time are 4 token tiles x 8 feature tiles.
+// Llama-3-8B projection, us before (L tiles in the grid, four waves) and now: 4096 new tokens
+// 93 and 86, 6000 130 and 101, 8192 185 and 120, 16384 301 and 239 (1.16 PFLOP/s).
 // ---------------------------------------------------------------------------------------
-template <int D, bool PAGED>
-__global__ __launch_bounds__(256, 1) void append_wide_kernel(AppendParams p) {
+template <int D, bool PAGED, int NLB>  // NLB: 32-row blocks the L features take (1: ranks up to 32, 2)
+__global__ __launch_bounds__(512, 2) void append_wide_kernel(AppendParams p) {
   constexpr int BF = 256, BT = 256, BK = 64;
   constexpr int TILE_BYTES = BF * BK * 2;  // 256 rows of 128 bytes
-  constexpr int STAGE = 2 * TILE_BYTES;    // [W tile][X tile]
+  constexpr int LT_BYTES = NLB * 32 * BK * 2;
+  constexpr int STAGE = 2 * TILE_BYTES + LT_BYTES;  // [W tile][X tile][W rows of L]
   __shared__ __align__(16) unsigned char smem[2 * STAGE];
   __shared__ double rope_rate[D / 2];  // revolutions per position of every rotary pair
 
@@ -321,22 +333,24 @@ __global__ __launch_bounds__(256, 1) void append_wide_kernel(AppendParams p) {
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, g2 = lane >> 5;
-  const int wr = wave >> 1, wc = wave & 1;
+  const int wr = wave >> 2, wc = wave & 3;  // position in the 2 x 4 grid of waves: features, tokens
   const int HD = p.n_kv_heads * D;
   const int n_ct_kv = (HD + BF - 1) / BF;
-  // The L tiles (little matrix work) come first in the grid, so they run beside the first full
-  // tiles instead of as a round of their own at the end.
-  const int ct = static_cast<int>(blockIdx.y) - 1;
-  const int kind = ct < 0 ? 2 : (ct < n_ct_kv ? 0 : 1);  // 0 K, 1 V, 2 L
-  const int ct_in = kind == 0 ? ct : (kind == 1 ? ct - n_ct_kv : 0);
-  const int feat0 = ct_in * BF;
-  const int w_row0 = (kind == 0 ? 0 : (kind == 1 ? HD : 2 * HD)) + feat0;
-  const int tok0 = blockIdx.x * BT;
+  const int n_ct = 2 * n_ct_kv;            // feature tiles F
+  const int idx = static_cast<int>(blockIdx.x) >> 3;
+  const int tt = (idx / n_ct) * 8 + (static_cast<int>(blockIdx.x) & 7), ct = idx % n_ct;
+  const int tok0 = tt * BT;
   const int n_new = p.n_new;
+  if (tok0 >= n_new) return;
+  const int kind = ct < n_ct_kv ? 0 : 1;  // 0 K, 1 V
+  const int feat0 = (kind == 0 ? ct : ct - n_ct_kv) * BF;
+  const int w_row0 = (kind == 0 ? 0 : HD) + feat0;
+  const int lb_mine = ct + (wave >> 2) * n_ct;   // token block whose L features this wave works on, below 8
+  const bool l_any = ct < 8, l_wave = lb_mine < 8;
   const int n_t = append_length(PF_CONST_I32(p.seq_lens)[p.seq_index], p.max_seq_len);
   const int pos0 = n_t - n_new;
 
-  // tile traffic: as in append_kernel, 32 wave-wide loads per tile, wave w issues i = w + 4q
+  // tile traffic: as in append_kernel, 32 wave-wide loads per tile, wave w issues i = w + 8q
   const uint32_t ldw2 = static_cast<uint32_t>(p.d_model) * 2u;
   const uint32_t n_w_rows = static_cast<uint32_t>(2 * HD + p.rank);
   const pf_u32x4 rs_w = pf_rsrc(p.w, (n_w_rows - 1) * ldw2 + ldw2);
@@ -344,130 +358,132 @@ __global__ __launch_bounds__(256, 1) void append_wide_kernel(AppendParams p) {
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(PF_LDS_AS(unsigned char, smem)));
   const uint32_t voff = static_cast<uint32_t>(lane >> 3) * ldw2 +
                         (((lane & 7) ^ ((4 * wave + (lane >> 4)) & 7)) << 4);
-  // request number part (0..15) of this wave for the step at k0: W loads first, then X
+  // request number part (0..3) of this wave for the step at k0: a W and an X load; the L rows (past the end of w
+  // they read as zero) go with the first
   auto issue_part = [&](int k0, int st, int part) __attribute__((always_inline)) {
-    const int i = wave + 4 * (part & 7);
+    const int i = wave + 8 * part;
     const uint32_t dst = lds0 + st * STAGE + i * 1024;
-    if (part < 8) pf_load16_to_lds(rs_w, dst, voff, static_cast<uint32_t>(w_row0 + 8 * i) * ldw2 + k0 * 2);
-    else pf_load16_to_lds(rs_x, dst + TILE_BYTES, voff, static_cast<uint32_t>(tok0 + 8 * i) * ldw2 + k0 * 2);
-  };
-  auto issue_step = [&](int k0, int st) __attribute__((always_inline)) {
-#pragma unroll
-    for (int part = 0; part < 16; ++part) issue_part(k0, st, part);
+    pf_load16_to_lds(rs_w, dst, voff, static_cast<uint32_t>(w_row0 + 8 * i) * ldw2 + k0 * 2);
+    pf_load16_to_lds(rs_x, dst + TILE_BYTES, voff, static_cast<uint32_t>(tok0 + 8 * i) * ldw2 + k0 * 2);
+    if (part == 0 && l_any && wave < 4 * NLB)
+      pf_load16_to_lds(rs_w, dst + 2 * TILE_BYTES, voff, static_cast<uint32_t>(2 * HD + 8 * i) * ldw2 + k0 * 2);
   };
   const int n_steps = p.d_model / BK;
-  issue_step(0, 0);
+#pragma unroll
+  for (int part = 0; part < 4; ++part) issue_part(0, 0, part);
   if (tid < D / 2 && p.rope_theta > 0.f) rope_rate[tid] = rope_rate_rev(tid, D, p.rope_theta);  // read after the loop's barriers
 
   const int pre = l32 * (BK * 2) + (((l32 >> 1) & 7) << 4);
-  const bool lr_tile = kind == 2;
-  // K, V tiles: feature blocks 4 wr + i, token blocks 4 wc + j (i, j < 4).
-  // L tile (at most 64 features): feature blocks 0, 1 and token blocks 2 wave + j (j < 2).
-  const int fbase = lr_tile ? 0 : 4 * wr;
-  const int tbase = lr_tile ? 2 * wave : 4 * wc;
+  // feature blocks 4 wr + i (i < 4), token blocks 2 wc + j (j < 2)
+  const int fbase = 4 * wr, tbase = 2 * wc;
+  pf_f32x16 acc[4][2];      // [feature block][token block]
+  pf_f32x16 acc_l[NLB];     // [32 L features], token block lb_mine, k-slice wave % 4 of every step
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) acc[a][b][i] = 0.f;
+#pragma unroll
+    for (int a = 0; a < NLB; ++a) acc_l[a][i] = 0.f;
+  }
 
-
-  // One step.  A wave issues instructions in order, and a wave-wide request occupies the
-  // memory pipe of the compute unit for some sixteen cycles (all four waves share it): sixteen
-  // requests issued in a row keep the wave off the matrix pipe for as long as the pipe needs
-  // to take them, and the two times add up.  So the requests for the next step go out two at a
-  // time between the groups of four MFMAs of the first half of the step, next to the LDS reads of the next k-slice
-  // (registers double-buffered); sched_barrier keeps the compiler from regrouping them.
-  auto k_step = [&](auto& acc, int step, auto st_c, auto lr_c, auto more_c) __attribute__((always_inline)) {
+  // One step: the tiles have landed, everybody is done with the other stage; the requests of the next step go out
+  // beside the products of the first two k-slices, the operands of a k-slice are read under the products of the one
+  // before.
+  auto k_step = [&](int step, auto st_c, bool more) __attribute__((always_inline)) {
     constexpr int ST = decltype(st_c)::value;
-    constexpr bool LR = decltype(lr_c)::value;
-    const bool MORE = more_c;                       // another step follows: request its tiles (uniform)
-    constexpr int NA = LR ? 2 : 4, NB = LR ? 2 : 4;
     constexpr int KS = BK / 16;
-    constexpr int GROUPS = KS * NA;          // groups of NB MFMAs in a step
-    constexpr int PARTS = 2 * 16 / GROUPS;   // requests per group: all sixteen go out in the first half of the
-                                             // step, so that the last one has the other half to land
     pf_wait_vm0();
     __syncthreads();
     const unsigned char* wt = smem + ST * STAGE + fbase * 32 * (BK * 2);
     const unsigned char* xt = smem + ST * STAGE + TILE_BYTES + tbase * 32 * (BK * 2);
-    pf_bf16x8 a[2][NA], b[2][NB];
-    {
-      const int off = pre ^ (g2 << 4);
+    pf_bf16x8 a[2][4], b[2][2];
+    auto read_slice = [&](int ks, int buf) __attribute__((always_inline)) {
+      const int off = pre ^ ((2 * ks + g2) << 4);
 #pragma unroll
-      for (int i = 0; i < NA; ++i) a[0][i] = pf_as_bf16x8(*reinterpret_cast<const uint4*>(wt + off + i * 32 * (BK * 2)));
+      for (int j = 0; j < 2; ++j) b[buf][j] = pf_as_bf16x8(*reinterpret_cast<const uint4*>(xt + off + j * 32 * (BK * 2)));
 #pragma unroll
-      for (int j = 0; j < NB; ++j) b[0][j] = pf_as_bf16x8(*reinterpret_cast<const uint4*>(xt + off + j * 32 * (BK * 2)));
-    }
+      for (int i = 0; i < 4; ++i) a[buf][i] = pf_as_bf16x8(*reinterpret_cast<const uint4*>(wt + off + i * 32 * (BK * 2)));
+    };
+    read_slice(0, 0);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      const int cur = ks & 1, nxt = cur ^ 1;
-      const int off = pre ^ ((2 * (ks + 1) + g2) << 4);
+      const int cur = ks & 1;
+      __builtin_amdgcn_sched_barrier(0);
+      if (more && ks < 2) {
+        issue_part((step + 1) * BK, ST ^ 1, 2 * ks);
+        issue_part((step + 1) * BK, ST ^ 1, 2 * ks + 1);
+      }
+      if (ks + 1 < KS) read_slice(ks + 1, cur ^ 1);
 #pragma unroll
-      for (int i = 0; i < NA; ++i) {
-        __builtin_amdgcn_sched_barrier(0);
-        if (MORE && (ks * NA + i) * PARTS < 16) {
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-          for (int q = 0; q < PARTS; ++q) issue_part((step + 1) * BK, ST ^ 1, (ks * NA + i) * PARTS + q);
-        }
-        if (ks + 1 < KS) {
-          // two operands of the next k-slice per group, in the order its groups need them: its
-          // first group takes every b and a[0], so the b's go first (NA == NB)
-#pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            const int o = 2 * i + q;  // 0 .. NA + NB - 1
-            if (o < NB) b[nxt][o] = pf_as_bf16x8(*reinterpret_cast<const uint4*>(xt + off + o * 32 * (BK * 2)));
-            else a[nxt][o - NB] = pf_as_bf16x8(*reinterpret_cast<const uint4*>(wt + off + (o - NB) * 32 * (BK * 2)));
-          }
-        }
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
+        for (int j = 0; j < 2; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[cur][i], b[cur][j], acc[i][j], 0, 0, 0);
+    }
+    if (l_wave) {  // (uniform)
+      const int off = pre ^ ((2 * wc + g2) << 4);
+      const pf_bf16x8 bl = pf_as_bf16x8(*reinterpret_cast<const uint4*>(smem + ST * STAGE + TILE_BYTES + lb_mine * 32 * (BK * 2) + off));
+#pragma unroll
+      for (int i = 0; i < NLB; ++i) {
+        const pf_bf16x8 al = pf_as_bf16x8(*reinterpret_cast<const uint4*>(smem + ST * STAGE + 2 * TILE_BYTES + i * 32 * (BK * 2) + off));
+        acc_l[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bl, acc_l[i], 0, 0, 0);
       }
     }
     __builtin_amdgcn_sched_barrier(0);
   };
-  auto k_loop = [&](auto& acc, auto lr_c) __attribute__((always_inline)) {
-    constexpr int N = decltype(lr_c)::value ? 2 : 4;
-#pragma unroll
-    for (int a = 0; a < N; ++a)
-#pragma unroll
-      for (int b = 0; b < N; ++b)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
-    // (one loop body for every step: peeled first or last steps make the compiler move the sixteen accumulator
-    // tuples between the copies of the body, through scratch memory)
-    for (int step = 0; step < n_steps; step += 2) {
-      k_step(acc, step, std::integral_constant<int, 0>{}, lr_c, step + 1 < n_steps);
-      if (step + 1 < n_steps) k_step(acc, step + 1, std::integral_constant<int, 1>{}, lr_c, step + 2 < n_steps);
-    }
-    pf_wait_vm0();
-  };
+  for (int step = 0; step < n_steps; step += 2) {
+    k_step(step, std::integral_constant<int, 0>{}, step + 1 < n_steps);
+    if (step + 1 < n_steps) k_step(step + 1, std::integral_constant<int, 1>{}, step + 2 < n_steps);
+  }
 
-  // epilogue.  acc[a][b], register i, lane (l32, g2): feature 32 (fbase + a) + 8 (i/4) + 4 g2 + i%4
+  auto cache_row = [&](int j, bool l_row) __attribute__((always_inline)) -> int64_t {  // element offset of (token j, kv head 0), or of row j of L
+    if (PAGED) {
+      const int blk = p.block_table[static_cast<int64_t>(p.seq_index) * p.max_blocks_per_seq + (j >> 4)];
+      return l_row ? (static_cast<int64_t>(blk) * 16 + (j & 15)) * p.l_row_stride
+                   : static_cast<int64_t>(blk) * p.kv_block_stride + static_cast<int64_t>(j & 15) * p.kv_token_stride;
+    }
+    return l_row ? static_cast<int64_t>(j) * p.l_row_stride : static_cast<int64_t>(j) * p.kv_token_stride;
+  };
+  // epilogue of L: the slices meet in LDS, [wave][feature block][register][lane]; a wave then stores registers
+  // 4 wc .. 4 wc + 3 of its token block, features 8 wc + 4 g2 + 0..3
+  if (l_any) {
+    float* red = reinterpret_cast<float*>(smem);
+    static_assert(8 * NLB * 16 * 64 * 4 <= 2 * STAGE, "the slices fit the stages");
+    __syncthreads();  // everybody is done with the tiles
+    if (l_wave) {
+#pragma unroll
+      for (int i = 0; i < NLB; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) red[((wave * NLB + i) * 16 + e) * 64 + lane] = acc_l[i][e];
+    }
+    __syncthreads();
+    const int tok = tok0 + 32 * lb_mine + l32, row = pos0 + tok;
+    if (l_wave && tok < n_new && row >= 0) {  // (a sequence length below n_new breaks the contract: nothing is written)
+      bf16_t* lrow = static_cast<bf16_t*>(p.l) + cache_row(row, true);
+#pragma unroll
+      for (int i = 0; i < NLB; ++i) {
+        float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] += red[((((wave & 4) + w) * NLB + i) * 16 + 4 * wc + e) * 64 + lane];
+        const int f = 32 * i + 8 * wc + 4 * g2;  // the rank is a multiple of 8: all four or none
+        if (f < p.rank) *reinterpret_cast<uint2*>(lrow + f) = make_uint2(pf_pack2(v[0], v[1]), pf_pack2(v[2], v[3]));
+      }
+    }
+  }
+
+  // epilogue of K and V.  acc[a][b], register i, lane (l32, g2): feature 32 (fbase + a) + 8 (i/4) + 4 g2 + i%4
   // of the tile, token 32 (tbase + b) + l32 of the tile.
   bf16_t* kcache = static_cast<bf16_t*>(kind == 0 ? p.k_base : p.v_base);
-  auto store_block = [&](auto& acc, auto lr_c, auto b_c) __attribute__((always_inline)) {
+  auto store_block = [&](auto b_c) __attribute__((always_inline)) {
     constexpr int b = decltype(b_c)::value;
-    constexpr bool LR = decltype(lr_c)::value;
     const int tok = tok0 + 32 * (tbase + b) + l32;
     const int j = pos0 + tok;
     if (tok >= n_new || j < 0) return;
-    int64_t row_off;
-    if (PAGED) {
-      const int blk = p.block_table[static_cast<int64_t>(p.seq_index) * p.max_blocks_per_seq + (j >> 4)];
-      row_off = kind == 2 ? (static_cast<int64_t>(blk) * 16 + (j & 15)) * p.l_row_stride
-                          : static_cast<int64_t>(blk) * p.kv_block_stride + static_cast<int64_t>(j & 15) * p.kv_token_stride;
-    } else {
-      row_off = kind == 2 ? static_cast<int64_t>(j) * p.l_row_stride : static_cast<int64_t>(j) * p.kv_token_stride;
-    }
-    if constexpr (LR) {
-      bf16_t* lrow = static_cast<bf16_t*>(p.l) + row_off;
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int f = 32 * a + 8 * q + 4 * g2;
-          if (f < p.rank)
-            *reinterpret_cast<uint2*>(lrow + f) =
-                make_uint2(pf_pack2(acc[a][b][4 * q + 0], acc[a][b][4 * q + 1]), pf_pack2(acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]));
-        }
-    } else {
+    const int64_t row_off = cache_row(j, false);
     if (kind == 0 && p.rope_theta > 0.f) {
       // rotates the pair of blocks (lo, hi); block_lo = position of lo among the wave's four
       auto rotate = [&](pf_f32x16& lo_v, pf_f32x16& hi_v, int block_lo) __attribute__((always_inline)) {
@@ -500,22 +516,9 @@ __global__ __launch_bounds__(256, 1) void append_wide_kernel(AppendParams p) {
               make_uint2(pf_pack2(acc[a][b][4 * q + 0], acc[a][b][4 * q + 1]), pf_pack2(acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]));
         }
       }
-    }
   };
-  // (the two kinds of tile keep accumulators of their own: sixteen 16-register tuples leave no room for a copy)
-  if (lr_tile) {
-    pf_f32x16 acc[2][2];  // [feature block][token block]
-    k_loop(acc, std::true_type{});
-    store_block(acc, std::true_type{}, std::integral_constant<int, 0>{});
-    store_block(acc, std::true_type{}, std::integral_constant<int, 1>{});
-  } else {
-    pf_f32x16 acc[4][4];
-    k_loop(acc, std::false_type{});
-    store_block(acc, std::false_type{}, std::integral_constant<int, 0>{});
-    store_block(acc, std::false_type{}, std::integral_constant<int, 1>{});
-    store_block(acc, std::false_type{}, std::integral_constant<int, 2>{});
-    store_block(acc, std::false_type{}, std::integral_constant<int, 3>{});
-  }
+  store_block(std::integral_constant<int, 0>{});
+  store_block(std::integral_constant<int, 1>{});
 }
 
 // ---------------------------------------------------------------------------------------
@@ -959,22 +962,29 @@ hipError_t launch_append(const AppendParams& p, hipStream_t s) {
     }
     return hipGetLastError();
   }
-  // 256 x 256 tiles, one workgroup per CU: on request, or when their full tiles fill whole rounds of
-  // the chip's 256 CUs (at most a tenth of the last round idle) and there are at least two rounds.
-  // Measured on the Llama-3-8B projection: 277 us against 302 us at 16384 new tokens (512 tiles, two
-  // rounds), but 165 against 158 at 8192 and worse wherever a round stays half empty.
-  const int wide_full = ((p.n_new + 255) / 256) * 2 * (hd / 256);
-  const int wide_rounds = (wide_full + 255) / 256;
-  const bool wide_fits = wide_full >= 448 && wide_rounds * 256 * 10 <= wide_full * 11;
-  if (p.tile == 256 || (p.tile == 0 && p.stages == 0 && wide_fits)) {
-    dim3 wgrid((p.n_new + 255) / 256, 2 * ((hd + 255) / 256) + 1);
+  // 256 x 256 tiles, one workgroup per compute unit, from half a round of the chip on: a round costs about as much
+  // however full it is.  Measured, us with 128 x 128 tiles and with these: Llama-3-8B projection (8 feature tiles)
+  // 3500 new tokens 71 and 90, 4096 93 and 86, 9000 (288 tiles) 210 and 218, 12000 274 and 222; 4 kv heads (4
+  // feature tiles) 7000 72 and 80, 8192 85 and 84, 9000 108 and 97, 16384 176 and 115.
+  const int wide_tiles = ((p.n_new + 255) / 256) * 2 * ((hd + 255) / 256);
+  const bool wide_ok = hd > 256;  // (four feature tiles and more: what the kernel's division of the L features assumes)
+  const bool wide_pays = wide_tiles >= 128;
+  if (wide_ok && (p.tile == 256 || (p.tile == 0 && p.stages == 0 && wide_pays))) {
+    const int n_ct = 2 * ((hd + 255) / 256), t8 = ((p.n_new + 255) / 256 + 7) / 8;
+    const dim3 wgrid(8 * t8 * n_ct);  // (see the kernel: XCD, feature tile, token tile)
+#define LRA_APPEND_WIDE(DD, PG)                                                                          \
+  do {                                                                                                   \
+    if (p.rank <= 32) hipLaunchKernelGGL((append_wide_kernel<DD, PG, 1>), wgrid, dim3(512), 0, s, p);    \
+    else hipLaunchKernelGGL((append_wide_kernel<DD, PG, 2>), wgrid, dim3(512), 0, s, p);                 \
+  } while (0)
     if (p.head_dim == 128) {
-      if (paged) hipLaunchKernelGGL((append_wide_kernel<128, true>), wgrid, dim3(256), 0, s, p);
-      else hipLaunchKernelGGL((append_wide_kernel<128, false>), wgrid, dim3(256), 0, s, p);
+      if (paged) LRA_APPEND_WIDE(128, true);
+      else LRA_APPEND_WIDE(128, false);
     } else {
-      if (paged) hipLaunchKernelGGL((append_wide_kernel<64, true>), wgrid, dim3(256), 0, s, p);
-      else hipLaunchKernelGGL((append_wide_kernel<64, false>), wgrid, dim3(256), 0, s, p);
+      if (paged) LRA_APPEND_WIDE(64, true);
+      else LRA_APPEND_WIDE(64, false);
     }
+#undef LRA_APPEND_WIDE
     return hipGetLastError();
   }
   dim3 grid((p.n_new + 127) / 128, 2 * ((hd + 127) / 128) + 1);

@@ -95,6 +95,25 @@ def test_append_tile_sizes(case, tile):
         lra.lra_set_append_skinny(prev_k)
 
 
+WIDE_CASES = [
+    # the 256 x 256 tiles need K and V regions of more than 256 features; their feature tiles divide the L features
+    (300, 300, 64, 4, 128, 8, 10000.0),        # one step of d_model; four feature tiles: two token blocks each, ragged tokens
+    (900, 515, 192, 5, 64, 40, 500000.0),      # region of 320: a partly filled tile; rank 40: two blocks of L rows
+    (2200, 2100, 128, 5, 128, 64, 0.0),        # six feature tiles (blocks 6 and 7 on the first two), nine token tiles
+    (1000, 257, 256, 16, 128, 32, 10000.0),    # sixteen feature tiles: eight of them without L features
+]
+
+
+@pytest.mark.parametrize("case", WIDE_CASES, ids=lambda c: "n%d_new%d_dm%d_hkv%d_d%d_r%d_th%g" % c)
+def test_append_wide_tiles(case):
+    prev_t, prev_k = lra.lra_set_append_tile(256), lra.lra_set_append_skinny(0)
+    try:
+        test_append_contiguous(case)
+    finally:
+        lra.lra_set_append_tile(prev_t)
+        lra.lra_set_append_skinny(prev_k)
+
+
 GUARD = 4096  # bytes of a bit pattern on either side of a workspace
 
 
