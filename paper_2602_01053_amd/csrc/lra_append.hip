@@ -35,12 +35,12 @@ __device__ __forceinline__ int append_length(int len, int max_seq_len) { return 
 
 // BT = 64 halves the token side of the tile (a wave then owns 64 features x 32 tokens): twice the
 // workgroups and three quarters of the bytes per step for chunks too small to fill the chip.
-// SPLITK: blockIdx.z takes one of p.k_splits equal parts of d_model and leaves its fp32 sums in the
+// SPLITK: a workgroup takes one of p.k_splits equal parts of d_model and leaves its fp32 sums in the
 // workspace, [part][token][feature] (feature = row of w); append_finish_kernel adds the parts,
 // rotates, casts and stores.  For chunks whose output tiles would occupy a fraction of the chip
 // and walk all of d_model one step after the other.
 template <int D, bool PAGED, int NS, int BT = 128, bool SPLITK = false>
-__global__ __launch_bounds__(256, NS == 2 ? 2 : 1) void append_kernel(AppendParams p) {
+__global__ __launch_bounds__(NS == 2 ? 256 : 512, NS == 2 ? 2 : 1) void append_kernel(AppendParams p) {
   constexpr int BF = 128, BK = 64;  // features, d_model step (BT tokens)
   constexpr bool ONE_TB = BT == 64;  // one 32-token block per wave
   constexpr int REQ = ONE_TB ? 6 : 8;  // requests per step and wave
@@ -53,19 +53,32 @@ __global__ __launch_bounds__(256, NS == 2 ? 2 : 1) void append_kernel(AppendPara
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // waves 4-7 (deeper rings only) request the tiles and do nothing else
+  const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool requester = NS != 2 && wave8 >= 4;
+  const int wave = wave8 & 3;
   const int l32 = lane & 31, g2 = lane >> 5;
   const int wr = wave >> 1, wc = wave & 1;  // position in the 2 x 2 grid of waves: features, tokens
   const int HD = p.n_kv_heads * D;
   const int n_ct_kv = (HD + BF - 1) / BF;   // feature tiles of the K (and of the V) region
-  // The L tiles (little matrix work) come first in the grid, so they run beside the first full
-  // tiles instead of as a round of their own at the end.
-  const int ct = static_cast<int>(blockIdx.y) - 1;
+  // Workgroup -> (part of d_model, feature tile, token tile).  Workgroups go to the 8 XCDs in turn, and each XCD takes
+  // a stretch of the list of tiles with the smaller operand's index running fastest: the tiles an XCD works on at a
+  // time then share rows of the larger operand in its L2 instead of every XCD reading all of it.
+  // The L tiles (little matrix work) come first among the feature tiles.
+  const int n_tt = (p.n_new + BT - 1) / BT, n_ft = 2 * n_ct_kv + 1;
+  const int n_items = n_tt * n_ft * (SPLITK ? p.k_splits : 1);
+  const int item = (static_cast<int>(blockIdx.x) & 7) * ((n_items + 7) >> 3) + (static_cast<int>(blockIdx.x) >> 3);
+  if ((static_cast<int>(blockIdx.x) >> 3) >= (n_items + 7) >> 3 || item >= n_items) return;
+  const int part_z = SPLITK ? item / (n_tt * n_ft) : 0;
+  const int tile = item - part_z * (n_tt * n_ft);
+  const bool tokens_fast = p.n_new <= 2 * HD;
+  const int tile_hi = tile / (tokens_fast ? n_tt : n_ft), tile_lo = tile - tile_hi * (tokens_fast ? n_tt : n_ft);
+  const int ct = (tokens_fast ? tile_hi : tile_lo) - 1, tt = tokens_fast ? tile_lo : tile_hi;
   const int kind = ct < 0 ? 2 : (ct < n_ct_kv ? 0 : 1);  // 0 K, 1 V, 2 L
   const int ct_in = kind == 0 ? ct : (kind == 1 ? ct - n_ct_kv : 0);
   const int feat0 = ct_in * BF;                                 // first feature of the tile inside its region
   const int w_row0 = (kind == 0 ? 0 : (kind == 1 ? HD : 2 * HD)) + feat0;  // its row of w
-  const int tok0 = blockIdx.x * BT;
+  const int tok0 = tt * BT;
   const int n_new = p.n_new;
   const int n_t = append_length(PF_CONST_I32(p.seq_lens)[p.seq_index], p.max_seq_len);
   const int pos0 = n_t - n_new;  // cache row (= position) of new token 0
@@ -95,10 +108,12 @@ __global__ __launch_bounds__(256, NS == 2 ? 2 : 1) void append_kernel(AppendPara
     for (int part = 0; part < 8; ++part) issue_part(k0, st, part);
   };
   const int n_steps = SPLITK ? p.d_model / BK / p.k_splits : p.d_model / BK;
-  const int k_first = SPLITK ? static_cast<int>(blockIdx.z) * n_steps * BK : 0;  // first d_model index of this part
+  const int k_first = SPLITK ? part_z * n_steps * BK : 0;  // first d_model index of this part
+  if (NS == 2 || requester) {
 #pragma unroll
-  for (int st = 0; st < NS - 1; ++st)
-    if (st < n_steps) issue_step(k_first + st * BK, st);
+    for (int st = 0; st < NS - 1; ++st)
+      if (st < n_steps) issue_step(k_first + st * BK, st);
+  }
   if constexpr (!SPLITK)  // (the finishing kernel rotates)
     if (tid < D / 2 && p.rope_theta > 0.f) rope_rate[tid] = rope_rate_rev(tid, D, p.rope_theta);  // read after the loop's barriers
 
@@ -130,81 +145,56 @@ __global__ __launch_bounds__(256, NS == 2 ? 2 : 1) void append_kernel(AppendPara
   // (8 per step and wave) are outstanding, the barrier makes every wave's share visible and
   // retires stage (s - 1) % NS, which the new requests then overwrite.
   // A wave issues in order and a wave-wide request holds it for as long as the memory pipe of
-  // the compute unit (shared by the four waves) needs to take it.  With one workgroup per
-  // compute unit the eight requests therefore go out two per k-slice between the MFMAs, next
-  // to the LDS reads of the following slice (operand registers double-buffered; sched_barrier
-  // keeps the compiler from regrouping them).
+  // the compute unit needs to take it: the requests of a step and its products add up in a wave that
+  // issues both.  Two workgroups per compute unit (NS == 2) cover each other; with one (the deeper
+  // rings) four waves of their own issue the requests, and the other four only read and multiply:
+  // 0.36 -> 0.29 us per step at 64 tokens, 0.54 -> 0.38 at 128.
+  if (requester) {
+    for (int step = 0; step < n_steps; ++step) {
+      if (step + NS - 2 < n_steps) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(REQ * (NS - 2)));
+      else pf_wait_vm0();
+      __syncthreads();
+      if (step + NS - 1 < n_steps) issue_step(k_first + (step + NS - 1) * BK, (step + NS - 1) % NS);
+    }
+    return;
+  }
   auto k_step = [&](int step, auto st_c, auto lr_c) __attribute__((always_inline)) {
     constexpr int ST = decltype(st_c)::value;
     constexpr bool LR = decltype(lr_c)::value;
     constexpr int KS = BK / 16;
-    if (step + NS - 2 < n_steps) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(REQ * (NS - 2)));
-    else pf_wait_vm0();
+    if (NS == 2) pf_wait_vm0();
     __syncthreads();
-    const bool more = step + NS - 1 < n_steps;
-    const int k_next = k_first + (step + NS - 1) * BK;
     const unsigned char* wt = smem + ST * STAGE;
     const unsigned char* xt = wt + TILE_BYTES;
-    if (NS == 2) {
-      // Two workgroups per compute unit: the other one's MFMAs cover this one's requests, and
-      // what pays is reading far ahead.  All requests first, then the sixteen operand reads of
-      // the step ordered against its sixteen MFMAs: two k-slices of reads, one read per MFMA.
-      if (more) issue_step(k_next, (ST + NS - 1) % NS);
-      pf_bf16x8 a0[KS], a1[KS], b0[KS], b1[KS];
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const int off = pre ^ ((2 * ks + g2) << 4);
-        a0[ks] = pf_as_bf16x8(*reinterpret_cast<const uint4*>(wt + off + fb0 * 32 * (BK * 2)));
-        b0[ks] = pf_as_bf16x8(*reinterpret_cast<const uint4*>(xt + off + tb0 * 32 * (BK * 2)));
-        a1[ks] = pf_as_bf16x8(*reinterpret_cast<const uint4*>(wt + off + fb1 * 32 * (BK * 2)));
-        if (!LR) b1[ks] = pf_as_bf16x8(*reinterpret_cast<const uint4*>(xt + off + tb1 * 32 * (BK * 2)));
-      }
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[ks], b0[ks], acc[0][0], 0, 0, 0);
-        acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[ks], b0[ks], acc[1][0], 0, 0, 0);
-        if (!LR) {
-          acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[ks], b1[ks], acc[0][1], 0, 0, 0);
-          acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[ks], b1[ks], acc[1][1], 0, 0, 0);
-        }
-      }
-      constexpr int READS = LR ? 12 : 16, MFMAS = LR ? 8 : 16, AHEAD = READS / 2;
-      __builtin_amdgcn_sched_group_barrier(0x100, AHEAD, 0);
-#pragma unroll
-      for (int i = 0; i < READS - AHEAD; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x008, MFMAS - (READS - AHEAD), 0);
-      return;
-    }
-    // One workgroup per compute unit (the deeper rings): nothing else covers the requests.
-    pf_bf16x8 a0[2], a1[2], b0[2], b1[2];
-    auto read_slice = [&](int ks, int buf) __attribute__((always_inline)) {
-      const int off = pre ^ ((2 * ks + g2) << 4);
-      a0[buf] = pf_as_bf16x8(*reinterpret_cast<const uint4*>(wt + off + fb0 * 32 * (BK * 2)));
-      b0[buf] = pf_as_bf16x8(*reinterpret_cast<const uint4*>(xt + off + tb0 * 32 * (BK * 2)));
-      a1[buf] = pf_as_bf16x8(*reinterpret_cast<const uint4*>(wt + off + fb1 * 32 * (BK * 2)));
-      if (!LR) b1[buf] = pf_as_bf16x8(*reinterpret_cast<const uint4*>(xt + off + tb1 * 32 * (BK * 2)));
-    };
-    read_slice(0, 0);
+    if (NS == 2 && step + 1 < n_steps) issue_step(k_first + (step + 1) * BK, ST ^ 1);
+    // the sixteen operand reads of the step ordered against its sixteen MFMAs: two k-slices of reads, one read per
+    // MFMA from then on
+    pf_bf16x8 a0[KS], a1[KS], b0[KS], b1[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      const int cur = ks & 1;
-      __builtin_amdgcn_sched_barrier(0);
-      if (more) {
-        issue_part(k_next, (ST + NS - 1) % NS, 2 * ks);
-        issue_part(k_next, (ST + NS - 1) % NS, 2 * ks + 1);
-      }
-      if (ks + 1 < KS) read_slice(ks + 1, cur ^ 1);
-      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[cur], b0[cur], acc[0][0], 0, 0, 0);
-      acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[cur], b0[cur], acc[1][0], 0, 0, 0);
+      const int off = pre ^ ((2 * ks + g2) << 4);
+      a0[ks] = pf_as_bf16x8(*reinterpret_cast<const uint4*>(wt + off + fb0 * 32 * (BK * 2)));
+      b0[ks] = pf_as_bf16x8(*reinterpret_cast<const uint4*>(xt + off + tb0 * 32 * (BK * 2)));
+      a1[ks] = pf_as_bf16x8(*reinterpret_cast<const uint4*>(wt + off + fb1 * 32 * (BK * 2)));
+      if (!LR) b1[ks] = pf_as_bf16x8(*reinterpret_cast<const uint4*>(xt + off + tb1 * 32 * (BK * 2)));
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[ks], b0[ks], acc[0][0], 0, 0, 0);
+      acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[ks], b0[ks], acc[1][0], 0, 0, 0);
       if (!LR) {
-        acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[cur], b1[cur], acc[0][1], 0, 0, 0);
-        acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[cur], b1[cur], acc[1][1], 0, 0, 0);
+        acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0[ks], b1[ks], acc[0][1], 0, 0, 0);
+        acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1[ks], b1[ks], acc[1][1], 0, 0, 0);
       }
     }
-    __builtin_amdgcn_sched_barrier(0);
+    constexpr int READS = LR ? 12 : 16, MFMAS = LR ? 8 : 16, AHEAD = READS / 2;
+    __builtin_amdgcn_sched_group_barrier(0x100, AHEAD, 0);
+#pragma unroll
+    for (int i = 0; i < READS - AHEAD; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, MFMAS - (READS - AHEAD), 0);
   };
   auto k_loop = [&](auto lr_c) __attribute__((always_inline)) {
     for (int step = 0; step < n_steps; step += NS) {
@@ -224,7 +214,7 @@ __global__ __launch_bounds__(256, NS == 2 ? 2 : 1) void append_kernel(AppendPara
     // the sums of this part of d_model as they are, four consecutive features per 16-byte store
     const int n_feat = 2 * HD + p.rank;
     const int region = kind == 2 ? p.rank : HD;   // features of this tile's region
-    float* part = p.split_ws + static_cast<int64_t>(blockIdx.z) * p.n_new * n_feat;
+    float* part = p.split_ws + static_cast<int64_t>(part_z) * p.n_new * n_feat;
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       if ((b == 1 && (lr_tile || ONE_TB)) || !stores) continue;
@@ -917,11 +907,12 @@ hipError_t launch_append(const AppendParams& p, hipStream_t s) {
     // Split over d_model (chosen by the host from the sizes, with a workspace): tiles of 128 features
     // x 64 or 128 tokens, four LDS stages, p.k_splits parts in z, then the finishing kernel.
     const int bt = p.split_bt;
-    dim3 grid((p.n_new + bt - 1) / bt, 2 * ((hd + 127) / 128) + 1, p.k_splits);
+    const int64_t tiles = static_cast<int64_t>((p.n_new + bt - 1) / bt) * (2 * ((hd + 127) / 128) + 1) * p.k_splits;
+    const dim3 grid(static_cast<unsigned>((tiles + 7) / 8 * 8));  // (see append_kernel)
 #define LRA_APPEND_SPLIT(DD, PG)                                                                                        \
   do {                                                                                                                  \
-    if (bt == 64) hipLaunchKernelGGL((append_kernel<DD, PG, 4, 64, true>), grid, dim3(256), 0, s, p);                   \
-    else hipLaunchKernelGGL((append_kernel<DD, PG, 4, 128, true>), grid, dim3(256), 0, s, p);                           \
+    if (bt == 64) hipLaunchKernelGGL((append_kernel<DD, PG, 4, 64, true>), grid, dim3(512), 0, s, p);                   \
+    else hipLaunchKernelGGL((append_kernel<DD, PG, 4, 128, true>), grid, dim3(512), 0, s, p);                           \
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;                                                   \
     const dim3 fgrid(p.n_new, (hd / 8 + hd / 4 + p.rank / 4 + 255) / 256);                                              \
     if (p.k_splits <= 2) hipLaunchKernelGGL((append_finish_kernel<DD, PG, 2>), fgrid, dim3(256), 0, s, p);              \
@@ -987,25 +978,27 @@ hipError_t launch_append(const AppendParams& p, hipStream_t s) {
 #undef LRA_APPEND_WIDE
     return hipGetLastError();
   }
-  dim3 grid((p.n_new + 127) / 128, 2 * ((hd + 127) / 128) + 1);
+  const int n_ft = 2 * ((hd + 127) / 128) + 1;
+  const int64_t tiles128 = static_cast<int64_t>((p.n_new + 127) / 128) * n_ft;
+  const dim3 grid(static_cast<unsigned>((tiles128 + 7) / 8 * 8));
   // One workgroup per compute unit or fewer: nothing shares the LDS, so a deeper ring of
   // stages (more requests in flight per workgroup) is free; beyond that two workgroups per
   // unit with two stages each hide each other's waits.
-  const int stages = p.stages != 0 ? p.stages : (static_cast<int>(grid.x * grid.y) <= 256 ? 4 : 2);
+  const int stages = p.stages != 0 ? p.stages : (tiles128 <= 256 ? 4 : 2);
   // half-size token tiles while even those leave CUs idle, or when asked for (Llama-3-8B projection:
-  // 22-24 us against 33-34 us up to 512 new tokens, level at 1024)
-  if (p.tile == 64 || (p.tile == 0 && p.stages == 0 && static_cast<int>(grid.x * grid.y) <= 100)) {
-    dim3 g64((p.n_new + 63) / 64, grid.y);
+  // 19-21 us against 25-27 us up to 512 new tokens, 23 against 29 at 700)
+  if (p.tile == 64 || (p.tile == 0 && p.stages == 0 && tiles128 <= 100)) {
+    const dim3 g64(static_cast<unsigned>((static_cast<int64_t>((p.n_new + 63) / 64) * n_ft + 7) / 8 * 8));
     if (p.head_dim == 128) {
-      if (paged) hipLaunchKernelGGL((append_kernel<128, true, 4, 64>), g64, dim3(256), 0, s, p);
-      else hipLaunchKernelGGL((append_kernel<128, false, 4, 64>), g64, dim3(256), 0, s, p);
+      if (paged) hipLaunchKernelGGL((append_kernel<128, true, 4, 64>), g64, dim3(512), 0, s, p);
+      else hipLaunchKernelGGL((append_kernel<128, false, 4, 64>), g64, dim3(512), 0, s, p);
     } else {
-      if (paged) hipLaunchKernelGGL((append_kernel<64, true, 4, 64>), g64, dim3(256), 0, s, p);
-      else hipLaunchKernelGGL((append_kernel<64, false, 4, 64>), g64, dim3(256), 0, s, p);
+      if (paged) hipLaunchKernelGGL((append_kernel<64, true, 4, 64>), g64, dim3(512), 0, s, p);
+      else hipLaunchKernelGGL((append_kernel<64, false, 4, 64>), g64, dim3(512), 0, s, p);
     }
     return hipGetLastError();
   }
-#define LRA_APPEND_LAUNCH(DD, PG, NS_) hipLaunchKernelGGL((append_kernel<DD, PG, NS_>), grid, dim3(256), 0, s, p)
+#define LRA_APPEND_LAUNCH(DD, PG, NS_) hipLaunchKernelGGL((append_kernel<DD, PG, NS_>), grid, dim3(NS_ == 2 ? 256 : 512), 0, s, p)
 #define LRA_APPEND_STAGES(DD, PG)            \
   do {                                       \
     if (stages == 2) LRA_APPEND_LAUNCH(DD, PG, 2);      \
