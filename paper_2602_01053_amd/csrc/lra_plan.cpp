@@ -37,7 +37,7 @@ bool plan_sizes_fit(const lra_shape* sh, const lra_cache* c, int32_t tokens, int
 // each of them, one 64-wide step after the other, at what one compute unit can pull from L2.  Such
 // chunks divide d_model among several workgroups per tile (a power of two of parts, at least four
 // steps each, about one workgroup per compute unit in all) and add the parts in a second kernel.
-// Measured on the Llama-3-8B projection: 64 tokens 14 against 21 us, 128 tokens 13 against 23 us; up to
+// Measured on the Llama-3-8B projection: 64 tokens 10 against 18 us, 160 tokens 12 against 19 us; up to
 // 32 tokens the weight-streaming kernel is as fast and stays.  Forced tile or stage choices keep the
 // unsplit kernels.
 AppendSplit plan_append_split(int n_new, int n_kv_heads, int head_dim, int rank, int d_model, const Tuning& tune) {
@@ -308,6 +308,10 @@ Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_quer
     // as long as a share then still has 512 keys (32768 tokens x 8 kv heads: 35.7 against 38.6 us, 65536: 49.2
     // against 53.7; at 256 keys per share the doubling loses)
     if (!batch && !prefill && c->block_size != 0 && !rope && work * c->max_seq_len >= int64_t{2} * kCUs * 512) wgs = 2 * kCUs;
+    // ... and one sequence in the rotary form at ranks up to 32 likewise (20011 tokens, rank 8: 34.0 against 40.5 us,
+    // 60000: 72 against 97; rank 32: 35.2 against 45.8 and 82 against 110): its steps are a chain of dependent
+    // products and rotations that only a second wave per SIMD covers.  Above rank 32 a unit holds one workgroup.
+    if (!batch && rope_split && sh->rank <= 32) wgs = 2 * kCUs;
     if (work >= 2 * wgs) {
       split_keys = c->max_seq_len;  // more units than workgroups wanted: one share per sequence
     } else {
