@@ -310,8 +310,12 @@ Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_quer
     if (!batch && !prefill && c->block_size != 0 && !rope && work * c->max_seq_len >= int64_t{2} * kCUs * 512) wgs = 2 * kCUs;
     // ... and one sequence in the rotary form at ranks up to 32 likewise (20011 tokens, rank 8: 34.0 against 40.5 us,
     // 60000: 72 against 97; rank 32: 35.2 against 45.8 and 82 against 110): its steps are a chain of dependent
-    // products and rotations that only a second wave per SIMD covers.  Above rank 32 a unit holds one workgroup.
-    if (!batch && rope_split && sh->rank <= 32) wgs = 2 * kCUs;
+    // products and rotations that only a second wave per SIMD covers.  Above rank 32 a unit holds one workgroup.  Not
+    // where that makes more than 64 shares of fewer than 384 keys (4 kv heads, 20011 tokens: 27.0 against 25.0).
+    if (!batch && rope_split && sh->rank <= 32) {
+      const int64_t sk = (work * c->max_seq_len / (2 * kCUs) + tile) / tile * tile;
+      if (sk >= 384 || (c->max_seq_len + sk - 1) / sk <= 64) wgs = 2 * kCUs;
+    }
     if (work >= 2 * wgs) {
       split_keys = c->max_seq_len;  // more units than workgroups wanted: one share per sequence
     } else {
