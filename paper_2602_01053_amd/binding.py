@@ -61,6 +61,7 @@ class LraTuning(ctypes.Structure):
 # lra_set_* helpers below are conveniences for tests and benchmarks that edit this one struct
 # (process-wide on the Python side only) and return the previous value.
 _tuning = LraTuning()
+_tuning_ref = ctypes.byref(_tuning)
 
 
 class LraError(RuntimeError):
@@ -116,13 +117,16 @@ def lra_cache_append(shape: LraShape, cache: LraCache, w: torch.Tensor, rope_the
     """Project the new tokens x [n_new][d_model] with w [2*Hkv*d + r][d_model] and write their
     K_base / V_base / L rows into the cache (the last n_new rows of sequence seq_index).  `workspace`
     (optional, lra_append_workspace_bytes bytes) lets mid-sized chunks split d_model over the chip."""
-    if not (x.is_contiguous() and w.is_contiguous()) or x.shape[1] != w.shape[1]:
+    if not (x.is_contiguous() and w.is_contiguous()) or x.size(1) != w.size(1):
         raise LraError(2, "x and w must be dense and share d_model")
-    proj = LraProjection(_ptr(w), int(w.shape[1]), float(rope_theta))
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load_library().lra_cache_append(ctypes.byref(shape), ctypes.byref(cache), ctypes.byref(proj), _ptr(x),
-                                           int(seq_index), int(x.shape[0]), _ptr(workspace), ws_bytes,
-                                           ctypes.byref(_tuning), _stream_ptr(stream)))
+    proj = LraProjection(w.data_ptr(), w.size(1), float(rope_theta))
+    ws_ptr, ws_bytes = (None, 0) if workspace is None else (workspace.data_ptr(), workspace.nbytes)
+    byref = ctypes.byref
+    status = (_lib or load_library()).lra_cache_append(
+        byref(shape), byref(cache), byref(proj), _ptr(x), int(seq_index), x.size(0), ws_ptr, ws_bytes, _tuning_ref,
+        _stream_ptr(stream))
+    if status:
+        _check(status)
 
 
 def lra_append_workspace_bytes(shape: LraShape, cache: LraCache, w: torch.Tensor, rope_theta: float, n_new: int) -> int:
@@ -278,8 +282,16 @@ def lra_workspace_bytes(shape: LraShape, cache: LraCache, n_queries: int,
     return int(n)
 
 
+# The raw handle of the current stream, without the Stream object torch.cuda.current_stream() builds around it: a
+# call's time on the host is what a decode step of a short context waits for (see lra_attn_decode).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream_ptr(stream) -> Optional[int]:
     if stream is None:
+        if _raw_stream is not None and _current_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_current_device()) or None
         stream = torch.cuda.current_stream()
     return stream.cuda_stream or None
 
@@ -294,13 +306,16 @@ def lra_attn_decode(shape: LraShape, cache: LraCache, b_k: Optional[torch.Tensor
                     query_adapter: torch.Tensor, seq_query_start: torch.Tensor,
                     max_queries_per_seq: int, out: torch.Tensor, workspace: Optional[torch.Tensor],
                     stream=None) -> None:
+    # (marshalling is kept short: small calls issued one by one take as long on the host as on the GPU, 11.8 us per
+    # decode of a short context with two launches before, 10.0 so)
     ad = LraAdapters(_ptr(b_k), _ptr(b_v), int(n_adapters))
-    ws_ptr = _ptr(workspace)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load_library().lra_attn_decode(
-        ctypes.byref(shape), ctypes.byref(cache), ctypes.byref(ad), _ptr(q), _ptr(query_adapter),
-        _ptr(seq_query_start), int(q.shape[0]), int(max_queries_per_seq), _ptr(out), ws_ptr,
-        ws_bytes, ctypes.byref(_tuning), _stream_ptr(stream)))
+    ws_ptr, ws_bytes = (None, 0) if workspace is None else (workspace.data_ptr(), workspace.nbytes)
+    byref = ctypes.byref
+    status = (_lib or load_library()).lra_attn_decode(
+        byref(shape), byref(cache), byref(ad), _ptr(q), _ptr(query_adapter), _ptr(seq_query_start), q.size(0),
+        int(max_queries_per_seq), _ptr(out), ws_ptr, ws_bytes, _tuning_ref, _stream_ptr(stream))
+    if status:
+        _check(status)
 
 
 def lra_attn_decode_static(shape: LraShape, cache: LraCache, b_k: Optional[torch.Tensor],
@@ -320,8 +335,10 @@ def lra_attn_prefill(shape: LraShape, cache: LraCache, b_k: Optional[torch.Tenso
                      adapter_index: int, out: torch.Tensor, workspace: Optional[torch.Tensor],
                      stream=None) -> None:
     ad = LraAdapters(_ptr(b_k), _ptr(b_v), int(n_adapters))
-    ws_ptr = _ptr(workspace)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load_library().lra_attn_prefill(
-        ctypes.byref(shape), ctypes.byref(cache), ctypes.byref(ad), _ptr(q), int(seq_index),
-        int(adapter_index), int(q.shape[0]), _ptr(out), ws_ptr, ws_bytes, ctypes.byref(_tuning), _stream_ptr(stream)))
+    ws_ptr, ws_bytes = (None, 0) if workspace is None else (workspace.data_ptr(), workspace.nbytes)
+    byref = ctypes.byref
+    status = (_lib or load_library()).lra_attn_prefill(
+        byref(shape), byref(cache), byref(ad), _ptr(q), int(seq_index), int(adapter_index), q.size(0), _ptr(out),
+        ws_ptr, ws_bytes, _tuning_ref, _stream_ptr(stream))
+    if status:
+        _check(status)
