@@ -905,7 +905,7 @@ hipError_t launch_append(const AppendParams& p, hipStream_t s) {
   const bool paged = p.block_size != 0;
   if (p.k_splits > 1) {
     // Split over d_model (chosen by the host from the sizes, with a workspace): tiles of 128 features
-    // x 64 or 128 tokens, four LDS stages, p.k_splits parts in z, then the finishing kernel.
+    // x 64 or 128 tokens, four LDS stages, p.k_splits parts, then the finishing kernel.
     const int bt = p.split_bt;
     const int64_t tiles = static_cast<int64_t>((p.n_new + bt - 1) / bt) * (2 * ((hd + 127) / 128) + 1) * p.k_splits;
     const dim3 grid(static_cast<unsigned>((tiles + 7) / 8 * 8));  // (see append_kernel)
