@@ -123,15 +123,8 @@ static lra_status decode_call(const lra_shape* shape, const lra_cache* cache, co
     return LRA_ERR_SHAPE;
   if (!plan_sizes_fit(shape, cache, n_queries, max_queries_per_seq)) return LRA_ERR_UNSUPPORTED;
   const Tuning tune = resolve_tuning(tuning);
-  Plan pl = make_plan(shape, cache, n_queries, max_queries_per_seq, false, tune);
+  const Plan pl = make_plan(shape, cache, n_queries, max_queries_per_seq, false, tune, adapters->b_k != nullptr);
   if (!pl.launchable) return LRA_ERR_UNSUPPORTED;
-  if (shape->key_rope_theta > 0.f && adapters->b_k == nullptr && !use_static) {
-    // nothing to rotate: the plan of the plain call, where the workspace (sized without knowing) has room for it
-    lra_shape plain = *shape;
-    plain.key_rope_theta = 0.f;
-    const Plan alt = make_plan(&plain, cache, n_queries, max_queries_per_seq, false, tune);
-    if (alt.launchable && check_workspace(alt, workspace, workspace_bytes) == LRA_OK) pl = alt;
-  }
   if (use_static) {
     if (pl.bytes > LRA_STATIC_WORKSPACE_BYTES) return LRA_ERR_WORKSPACE;
     st = scratch_of_current_device(&workspace);

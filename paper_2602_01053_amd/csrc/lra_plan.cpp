@@ -174,7 +174,7 @@ static bool short_prefill_walks_tiles(const lra_shape* sh, const lra_cache* c, i
 }
 
 Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_queries_per_seq, bool prefill,
-               const Tuning& tune) {
+               const Tuning& tune, bool key_adapter) {
   Plan pl{};
   const int G = sh->n_q_heads / sh->n_kv_heads;
   // The MFMA kernels move L in 16-byte pieces: ranks that are not a multiple of 8 take the
@@ -311,8 +311,9 @@ Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_quer
     // ... and one sequence in the rotary form at ranks up to 32 likewise (20011 tokens, rank 8: 34.0 against 40.5 us,
     // 60000: 72 against 97; rank 32: 35.2 against 45.8 and 82 against 110): its steps are a chain of dependent
     // products and rotations that only a second wave per SIMD covers.  Above rank 32 a unit holds one workgroup.  Not
-    // where that makes more than 64 shares of fewer than 384 keys (4 kv heads, 20011 tokens: 27.0 against 25.0).
-    if (!batch && rope_split && sh->rank <= 32) {
+    // where that makes more than 64 shares of fewer than 384 keys (4 kv heads, 20011 tokens: 27.0 against 25.0).  Nor
+    // without a B_K: nothing is rotated then, and one workgroup per unit keeps the streaming form.
+    if (!batch && rope_split && key_adapter && sh->rank <= 32) {
       const int64_t sk = (work * c->max_seq_len / (2 * kCUs) + tile) / tile * tile;
       if (sk >= 384 || (c->max_seq_len + sk - 1) / sk <= 64) wgs = 2 * kCUs;
     }

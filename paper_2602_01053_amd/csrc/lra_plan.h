@@ -47,8 +47,10 @@ struct Plan {
 lra_status check_common(const lra_shape* sh, const lra_cache* c);
 // false: the call is too large for the planner's 32-bit row arithmetic (LRA_ERR_UNSUPPORTED)
 bool plan_sizes_fit(const lra_shape* sh, const lra_cache* c, int32_t tokens, int32_t max_queries_per_seq);
+// key_adapter: whether the call has a B_K.  lra_workspace_bytes cannot know and plans with one; the plan without one
+// never needs more workspace.
 Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_queries_per_seq, bool prefill,
-               const Tuning& tune);
+               const Tuning& tune, bool key_adapter = true);
 
 // lra_cache_append: parts of d_model the tiled GEMM is divided into (1: none), the token side of its
 // tile, and the fp32 workspace the parts need.

@@ -88,6 +88,12 @@ int main(int argc, char** argv) {
       CHECK(pl.off_ml % 256 == 0 && pl.off_o % 256 == 0 && pl.off_lr % 256 == 0 && pl.off_adapter % 256 == 0 && pl.off_qt % 256 == 0);
       CHECK(pl.bytes % 256 == 0);
       CHECK(pl.bytes == pl.bytes_without_kc + pl.kc_bytes && pl.off_kc % 256 == 0 && pl.kc_bytes % 256 == 0);
+      {
+        // a call without a B_K runs in a workspace that was sized without knowing that
+        const Plan pk = make_plan(&sh, &c, static_cast<int>(tokens), static_cast<int>(mq), prefill != 0, tune, false);
+        CHECK(pk.mfma == pl.mfma && pk.bytes <= pl.bytes && pk.bytes_without_kc <= pl.bytes_without_kc);
+        CHECK(pk.n_splits <= pl.n_splits && pk.split_keys >= pl.split_keys);
+      }
       if (pl.kc_bytes) {  // completed keys of a rotary prefill: a copy of the K_base extent behind everything else
         CHECK(prefill && pl.mfma && !pl.short_prefill && sh.key_rope_theta > 0.f);
         CHECK(pl.off_kc >= pl.bytes_without_kc);

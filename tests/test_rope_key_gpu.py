@@ -224,6 +224,35 @@ def test_rotary_key_side_without_key_adapter_is_the_plain_path():
     assert rel <= REL_L2_TOL
 
 
+@pytest.mark.parametrize("paged", [False, True], ids=["contiguous", "paged"])
+@pytest.mark.parametrize("n,agents", [(8192, 4), (20011, 4), (60000, 8)])
+def test_static_and_ordinary_decode_without_a_key_adapter_give_the_same_bits(n, agents, paged):
+    """One plan for both entry points, whatever the size of the workspace: the bytes asked for, and four times that."""
+    hq, hkv, d, r = 32, 8, 128, 16
+    gen = torch.Generator(device=DEV).manual_seed(1700 + n)
+    rn = lambda *sh: torch.randn(*sh, generator=gen, device=DEV, dtype=torch.bfloat16)
+    blocks = (n + 15) // 16
+    k, v = (rn(blocks, hkv, 16, d), rn(blocks, hkv, 16, d)) if paged else (rn(n, hkv, d), rn(n, hkv, d))
+    l = rn(blocks, 16, r) if paged else rn(n, r)
+    table = torch.randperm(blocks, generator=gen, device=DEV).to(torch.int32)[None] if paged else None
+    b_v, q = rn(agents, r, hkv * d).mul_(0.1), rn(agents, hq, d)
+    lens = torch.tensor([n], dtype=torch.int32, device=DEV)
+    ids = torch.arange(agents, dtype=torch.int32, device=DEV)
+    start = torch.tensor([0, agents], dtype=torch.int32, device=DEV)
+    shape, cache = lra.make_shape(q, hkv, r, 0.0, 500000.0), lra.make_cache(k, v, l, lens, n, table)
+    need = lra.lra_workspace_bytes(shape, cache, agents, agents)
+    outs = []
+    for size in (need, 4 * need):
+        outs.append(torch.full_like(q, float("nan")))
+        ws = torch.empty(size, dtype=torch.uint8, device=DEV)
+        lra.lra_attn_decode(shape, cache, None, b_v, agents, q, ids, start, agents, outs[-1], ws)
+    outs.append(torch.full_like(q, float("nan")))
+    lra.lra_attn_decode_static(shape, cache, None, b_v, agents, q, ids, start, agents, outs[-1])
+    torch.cuda.synchronize()
+    assert torch.isfinite(outs[0]).all()
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+
+
 def _prefill_cases():
     mk = W.make_contiguous
     yield "d128_r16_ragged", mk("rp1", "prefill", seed=311, n_agents=1, n_q_heads=8, n_kv_heads=2, head_dim=128, rank=16,
