@@ -521,9 +521,22 @@
       // B operand: Olr^T registers 8(ks&1)..+7 of block ks/2: element e <-> rho = 16ks + 8(e/4) + 4g2 + e%4
       const int o = (ks & 1) * 8;
       const pf_f32x16& src = lr_acc[ks >> 1];
-      const pf_bf16x8 bop =
-          pf_as_bf16x8(make_uint4(pf_pack2(src[o + 0], src[o + 1]), pf_pack2(src[o + 2], src[o + 3]),
-                                  pf_pack2(src[o + 4], src[o + 5]), pf_pack2(src[o + 6], src[o + 7])));
+      // O_lr as two bf16 terms, the second what the first left over: to 17 bits, against the 8 of the output's own
+      // rounding.  (One term cost up to 2^-9 of |O_lr| |B_V|, which calls with several shares, whose merge holds
+      // O_lr in fp32, do not pay; 32 to 64 cycles of matrix pipe per 16 ranks and 32 columns, once per q tile.)
+      pf_bf16x8 bop[2];
+      {
+        uint32_t w[2][4];
+#pragma unroll
+        for (int e2 = 0; e2 < 4; ++e2) {
+          const float x0 = src[o + 2 * e2], x1 = src[o + 2 * e2 + 1];
+          w[0][e2] = pf_pack2(x0, x1);
+          const float r0 = x0 - __uint_as_float(w[0][e2] << 16), r1 = x1 - __uint_as_float(w[0][e2] & 0xffff0000u);
+          w[1][e2] = pf_pack2(__builtin_isfinite(r0) ? r0 : 0.f, __builtin_isfinite(r1) ? r1 : 0.f);
+        }
+#pragma unroll
+        for (int term = 0; term < 2; ++term) bop[term] = pf_as_bf16x8(make_uint4(w[term][0], w[term][1], w[term][2], w[term][3]));
+      }
 #pragma unroll
       for (int b = 0; b < DB; ++b) {
         // A operand: B_V^T: lane (d = 32b + l32, element e <-> rho as above)
@@ -534,8 +547,9 @@
           const uint32_t val = rho < r ? static_cast<uint32_t>(bv[rho * ldb + 32 * b + l32]) : 0u;
           w[e >> 1] |= val << ((e & 1) * 16);
         }
-        o_acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pf_as_bf16x8(make_uint4(w[0], w[1], w[2], w[3])), bop,
-                                                           o_acc[b], 0, 0, 0);
+        const pf_bf16x8 bvt = pf_as_bf16x8(make_uint4(w[0], w[1], w[2], w[3]));
+        o_acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bvt, bop[1], o_acc[b], 0, 0, 0);
+        o_acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bvt, bop[0], o_acc[b], 0, 0, 0);
       }
     }
   }

@@ -229,6 +229,46 @@ def test_short_sequence_prefill_with_and_without_a_workspace(n, n_new):
         _gate(dw.out.to(torch.float64).cpu().numpy(), ref, label=f"workspace {with_workspace}")
 
 
+@pytest.mark.parametrize("splits", [1, 3])
+@pytest.mark.parametrize("paged", [False, True], ids=["contiguous", "paged"])
+@pytest.mark.parametrize("d,r", [(128, 16), (64, 24), (128, 64)])
+def test_prefill_holds_the_low_rank_sums_in_fp32_until_the_output(d, r, paged, splits):
+    """L rows of about 4 and B_V rows that cancel: what is left of P.L.B_V is a tenth of its terms, so a P.L rounded to
+    bf16 (2^-9 of 4 per rank) would show as several percent.  The probabilities' own rounding does not: it scales all
+    ranks alike up to a spread of 2^-9 / sqrt(keys) per rank, below 1e-2 of what is left."""
+    n, n_new = 900, 140
+    make = lambda **kw: W.make_contiguous("cancelling", "prefill", n=n, n_new=n_new, n_agents=1, **kw)
+    w = make(seed=4800 + r, n_q_heads=8, n_kv_heads=2, head_dim=d, rank=r, d_model=None, b_std=0.05)
+    w.l = (4.0 + w.l.float()).to(torch.bfloat16)
+    w.v_base.mul_(1e-3)
+    signs = torch.tensor([1.0, -1.0]).repeat(r // 2)[:, None]
+    w.b_v = (signs * torch.ones_like(w.b_v[0].float()))[None].to(torch.bfloat16)
+    ref = oracle_prefill(w)
+    table = None
+    k, v, l = w.k_base.to(DEV), w.v_base.to(DEV), w.l.to(DEV)
+    if paged:  # the same rows in blocks of 16, the last one partly filled
+        blocks = (n + 15) // 16
+        pad = lambda t: torch.cat([t, torch.full((blocks * 16 - n, *t.shape[1:]), float("nan"), dtype=t.dtype, device=DEV)])
+        k, v = (pad(t).view(blocks, 16, 2, d).permute(0, 2, 1, 3).contiguous() for t in (k, v))
+        l = pad(l).view(blocks, 16, r)
+        table = torch.arange(blocks, dtype=torch.int32, device=DEV)[None].contiguous()
+    q = w.q.to(DEV)
+    shape = lra.make_shape(q, 2, r, w.scale)
+    cache = lra.make_cache(k, v, l, torch.tensor([n], dtype=torch.int32, device=DEV), n, table)
+    out = torch.full_like(q, float("nan"))
+    old = lra.lra_set_prefill_splits(splits)
+    try:
+        ws = torch.empty(max(256, lra.lra_workspace_bytes(shape, cache, 1, 1, n_new)), dtype=torch.uint8, device=DEV)
+        lra.lra_attn_prefill(shape, cache, w.b_k.to(DEV), w.b_v.to(DEV), 1, q, 0, 0, out, ws)
+        torch.cuda.synchronize()
+    finally:
+        lra.lra_set_prefill_splits(old)
+    got = out.to(torch.float64).cpu().numpy()
+    rel = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    print(f"relL2 {rel:.3e}", flush=True)
+    assert rel <= 1e-2
+
+
 def test_short_prefill_on_paged_cache_value_only():
     """Split-KV prefill of 5 new tokens on a paged, ragged cache without B_K."""
     w = W.make_paged("paged_short_prefill", seed=92, seq_lens=[40, 333, 1500], agents_per_seq=1, n_adapters=3,
