@@ -59,29 +59,34 @@ __device__ __forceinline__ void unpack_piece(uint4 v, float (&x)[E]) {
   }
 }
 
-// One workgroup of four waves per (query row, share of the keys), 64 keys per step.  Calls of this kernel are small
-// (fp32, odd ranks) and cost round trips, not bytes, so a step is one round of requests: four lanes share a K row
-// (16-byte pieces dealt round robin) and reduce by two exchanges, a thread takes a column piece of V for PK keys and
-// an eighth to a sixteenth of the keys, and the V and L rows are requested with the K rows, before any score is
-// known.  A wave per share, one key per lane and a load per dot-product step, took a round trip per step instead:
-// two agents on 512 keys in fp32 17.6 us per call, 11.1 us so.  Every wave forms the softmax of the 64 scores by
+// One workgroup of four waves per (query row, share of the keys), 64 keys per step.  Calls of this kernel (fp32, odd
+// ranks) cost round trips, not bytes, so a step is one round of requests: four lanes share a K row (16-byte pieces
+// dealt round robin) and reduce by two exchanges, a thread takes a column piece of V for PK keys and an eighth to a
+// sixteenth of the keys.  The K and L rows of a step are requested under the sums of the one before, its V rows as
+// soon as those of the one before are used up, so that three workgroups fit the registers of a compute unit (fp32,
+// d = 128: 168; with V a whole step ahead 216 and two).  One wave per share, one key per lane and a load per
+// dot-product step, takes a round trip per step instead: two agents on 512 keys in fp32 17.6 us per call, 9.8 us so;
+// 1024 new tokens in fp32 at 32 heads of 128 1602 us, 1562 us so.  Every wave forms the softmax of the 64 scores by
 // itself (lane = key), which leaves one barrier between the scores and the sums.
 // K and V rows are 16-byte aligned (bases and strides are checked); L rows of a rank that is no multiple of four
 // are not, and go through LDS element by element.
 template <typename T, int D>
-__global__ __launch_bounds__(256) void generic_partial_kernel(Params p) {
+__global__ __launch_bounds__(256, sizeof(T) == 4 || D == 64 ? 3 : 1) void generic_partial_kernel(Params p) {
   constexpr int E = 16 / static_cast<int>(sizeof(T));  // elements per piece
   constexpr int CG = D / E;                            // pieces per row
   constexpr int PK = CG / 4;                           // pieces of a K row per thread; V rows per thread and step
   constexpr int KG = 256 / CG;                         // key groups of the V sums
-  const int row = blockIdx.x;
+  constexpr bool LANE_SUMS = sizeof(T) == 2;
   const int split = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int Hq = p.n_q_heads, r = p.rank;
-  const int tok = row / Hq;
-  const int g = row - tok * Hq;
-  const int h = g / p.group;
+  // workgroup -> row: the kv head runs fastest, so that with 8 kv heads an XCD takes the rows of one (200 new tokens
+  // on 1200 fp32 keys: 1206 -> 966 us); the longest rows of a prefill come first, so that no long one is left for
+  // the end (1024 new tokens, bf16, rank 12: 1140 -> 1103 us)
+  const int rest = static_cast<int>(blockIdx.x) / p.n_kv_heads, h = static_cast<int>(blockIdx.x) - rest * p.n_kv_heads;
+  const int tok_up = rest / p.group, tok = p.is_prefill ? p.n_new - 1 - tok_up : tok_up;
+  const int row = tok * Hq + h * p.group + (rest - tok_up * p.group);
 
   int t, a, n_vis;
   if (p.is_prefill) {
@@ -112,19 +117,25 @@ __global__ __launch_bounds__(256) void generic_partial_kernel(Params p) {
 
   uint4 kp[PK], vp[PK];
   T lv[16];
-  auto request = [&](int jb) __attribute__((always_inline)) {  // (rows past the end: the last one again, weighted zero)
-    const uint4* krow = reinterpret_cast<const uint4*>(kb + kv_offset(p, t, min(jb + key_k, j1 - 1), h));
-#pragma unroll
-    for (int i = 0; i < PK; ++i) kp[i] = krow[quarter + 4 * i];
+  // (rows past the end: the last one again, weighted zero)
+  auto request_v = [&](int jb) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < PK; ++i)
       vp[i] = reinterpret_cast<const uint4*>(vb + kv_offset(p, t, min(jb + kg + KG * i, j1 - 1), h))[cg];
+  };
+  auto request = [&](int jb) __attribute__((always_inline)) {
+    const uint4* krow = reinterpret_cast<const uint4*>(kb + kv_offset(p, t, min(jb + key_k, j1 - 1), h));
+#pragma unroll
+    for (int i = 0; i < PK; ++i) kp[i] = krow[quarter + 4 * i];
     const T* lrow = lr + l_offset(p, t, min(jb + key_k, j1 - 1), a);
 #pragma unroll
     for (int i = 0; i < 16; ++i)
       if (4 * i < r) lv[i] = lrow[min(4 * i + quarter, r - 1)];  // (uniform)
   };
-  if (j0 < j1) request(j0);
+  if (j0 < j1) {
+    request(j0);
+    request_v(j0);
+  }
 
   const T* q = static_cast<const T*>(p.q) + static_cast<int64_t>(row) * D;
   uint4 bp[PK];
@@ -174,16 +185,14 @@ __global__ __launch_bounds__(256) void generic_partial_kernel(Params p) {
       }
     part = p.scale * sum4(part);
     if (quarter == 0) s_s[key_k] = key_k < cnt ? part : -INFINITY;
-    uint4 vc[PK];
-#pragma unroll
-    for (int i = 0; i < PK; ++i) vc[i] = vp[i];
     __syncthreads();
     if (jb + kWave < j1) request(jb + kWave);
     const float s = s_s[lane];
     const float m_new = fmaxf(m, wave_max(s));  // finite: key 0 of the step is always valid
     const float alpha = (m == -INFINITY) ? 0.f : expf(m - m_new);
     const float pj = lane < cnt ? expf(s - m_new) : 0.f;
-    ell = alpha * ell + wave_sum(pj);
+    // (bf16: the sum of this lane's keys, added up after the last step; in fp32 it is the register too many)
+    ell = fmaf(alpha, ell, LANE_SUMS ? pj : wave_sum(pj));
     olr *= alpha;
 #pragma unroll
     for (int e = 0; e < E; ++e) o[e] *= alpha;
@@ -193,11 +202,12 @@ __global__ __launch_bounds__(256) void generic_partial_kernel(Params p) {
       const float pk = __shfl(pj, key, kWave);
       if (key < cnt) {
         float x[E];
-        unpack_piece<T, E>(vc[i], x);
+        unpack_piece<T, E>(vp[i], x);
 #pragma unroll
         for (int e = 0; e < E; ++e) o[e] = fmaf(pk, x[e], o[e]);
       }
     }
+    if (jb + kWave < j1) request_v(jb + kWave);
     // O_lr: lane = rho, wave w the keys 16 w .. 16 w + 15
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
@@ -211,6 +221,7 @@ __global__ __launch_bounds__(256) void generic_partial_kernel(Params p) {
 #pragma unroll
   for (int e = 0; e < E; ++e) o_s[kg * D + cg * E + e] = o[e];
   olr_s[wave * 64 + lane] = olr;
+  if (LANE_SUMS) ell = wave_sum(ell);
   __syncthreads();
   const int64_t slot = static_cast<int64_t>(row) * p.n_splits + split;
   if (tid < D) {

@@ -294,7 +294,10 @@ Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_quer
     want = kCUs;
   } else {
     work = pl.rows;
-    want = kCUs * 8;
+    // shares of a few steps each: the one-wave-per-row kernel of the rotary key side fills the chip with 8 per
+    // compute unit, the plain one, of four waves, with the 3 that are resident (32 fp32 rows on 4000 keys: 34.1 us
+    // with 63 shares, 24.2 with 21)
+    want = rope && key_adapter ? kCUs * 8 : kCUs * 3;
   }
   int split_keys = tune.split_keys;
   if (split_keys <= 0 && pl.mfma) {
