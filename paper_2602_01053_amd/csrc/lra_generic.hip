@@ -84,7 +84,9 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 || D == 64 ? 3 : 1) void generi
   // workgroup -> row: the kv head runs fastest, so that with 8 kv heads an XCD takes the rows of one (200 new tokens
   // on 1200 fp32 keys: 1206 -> 966 us); the longest rows of a prefill come first, so that no long one is left for
   // the end (1024 new tokens, bf16, rank 12: 1140 -> 1103 us)
-  const int rest = static_cast<int>(blockIdx.x) / p.n_kv_heads, h = static_cast<int>(blockIdx.x) - rest * p.n_kv_heads;
+  const int idx = static_cast<int>(blockIdx.z) * static_cast<int>(gridDim.x) + static_cast<int>(blockIdx.x);
+  if (idx >= (p.is_prefill ? p.n_new : p.n_queries) * Hq) return;
+  const int rest = idx / p.n_kv_heads, h = idx - rest * p.n_kv_heads;
   const int tok_up = rest / p.group, tok = p.is_prefill ? p.n_new - 1 - tok_up : tok_up;
   const int row = tok * Hq + h * p.group + (rest - tok_up * p.group);
 
@@ -760,12 +762,15 @@ hipError_t launch_generic_partials(const Params& p, bool is_bf16, int rows, hipS
     else hipLaunchKernelGGL(generic_partial_rope_kernel<float>, grid, block, 0, s, p);
     return hipGetLastError();
   }
+  // (a grid dimension holds fewer than 2^32 threads: rows beyond 2^23 go on in z)
+  const int x = rows < (1 << 23) ? rows : (1 << 23);
+  const dim3 rgrid(x, p.n_splits, (rows + x - 1) / x);
   if (p.head_dim == 128) {
-    if (is_bf16) hipLaunchKernelGGL((generic_partial_kernel<bf16_t, 128>), grid, dim3(256), 0, s, p);
-    else hipLaunchKernelGGL((generic_partial_kernel<float, 128>), grid, dim3(256), 0, s, p);
+    if (is_bf16) hipLaunchKernelGGL((generic_partial_kernel<bf16_t, 128>), rgrid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((generic_partial_kernel<float, 128>), rgrid, dim3(256), 0, s, p);
   } else {
-    if (is_bf16) hipLaunchKernelGGL((generic_partial_kernel<bf16_t, 64>), grid, dim3(256), 0, s, p);
-    else hipLaunchKernelGGL((generic_partial_kernel<float, 64>), grid, dim3(256), 0, s, p);
+    if (is_bf16) hipLaunchKernelGGL((generic_partial_kernel<bf16_t, 64>), rgrid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((generic_partial_kernel<float, 64>), rgrid, dim3(256), 0, s, p);
   }
   return hipGetLastError();
 }

@@ -537,6 +537,24 @@ def test_many_rows_fp32_and_vector_alu_partials():
         _gate(got, oracle_decode(w), fp32=fp32, label=f"{w.name} {dtype}")
 
 
+def test_vector_alu_kernel_beyond_2_to_24_rows():
+    """4100 queries of 4096 heads, all the same: 16.8 million rows of 256 threads each, more threads than one grid
+    dimension holds.  Every query's output equals the first one's, bit for bit, and that one the oracle's."""
+    nq, hq, hkv, d, r, n = 4100, 4096, 256, 64, 8, 40
+    w = W.make_contiguous("many_rows", "decode", seed=97, dtype=torch.float32, n_agents=1, n_q_heads=hq, n_kv_heads=hkv,
+                          head_dim=d, rank=r, n=n, n_new=1, d_model=None, b_std=0.05)
+    dw = DeviceWorkload(w, DEV)
+    q = dw.q.expand(nq, hq, d).contiguous()
+    out = torch.full_like(q, float("nan"))
+    ids = torch.zeros(nq, dtype=torch.int32, device=DEV)
+    start = torch.tensor([0, nq], dtype=torch.int32, device=DEV)
+    ws = torch.empty(lra.lra_workspace_bytes(dw.shape, dw.cache, nq, nq), dtype=torch.uint8, device=DEV)
+    lra.lra_attn_decode(dw.shape, dw.cache, dw.b_k, dw.b_v, 1, q, ids, start, nq, out, ws)
+    torch.cuda.synchronize()
+    _gate(out[:1].to(torch.float64).cpu().numpy(), oracle_decode(w), fp32=True, label="first query")
+    assert all(torch.equal(out[i:i + 100], out[:1].expand(100, hq, d)) for i in range(0, nq, 100))
+
+
 def test_prefill_with_shared_key_tiles_and_many_rows():
     """64 new tokens x 16 q heads = 1024 rows, key tiles shared by 4 workgroups: the wave-per-row merge after the
     tile-walking prefill kernel."""
