@@ -173,6 +173,24 @@ static bool short_prefill_walks_tiles(const lra_shape* sh, const lra_cache* c, i
   return tokens * G <= 96 || c->max_seq_len >= 4096;
 }
 
+// Whether one sequence in the rotary form of the split-KV kernel runs with two workgroups per compute unit rather
+// than one: its steps are a chain of dependent products and rotations that only a second wave per SIMD covers, but
+// the partial states double.  Measured on MI355X over 810 calls, the ratio of the times with one and with two:
+// up to 64 shares (which one merge kernel takes) 0.98 to 1.43 with shares of 256 keys and more, 0.90 to 1.18 with
+// 128, there at least 1.01 up to 2048 (row, share) states; beyond 64 shares 0.71 to 1.08 with 128 and 256 keys,
+// at least 1.02 with 384 where one workgroup per unit makes more than 64 too, and where it does not 0.94 to 1.22 with
+// 512 (rank 32 the lower) and at least 1.0 with 640.
+static bool rope_pays_two_per_unit(int max_seq_len, int64_t work, int tile, int64_t rows, int rank) {
+  auto share_keys = [&](int64_t wgs) {  // as the plan rounds them
+    const int64_t sk = (work * max_seq_len + wgs - 1) / wgs;
+    return work >= 2 * wgs || sk > max_seq_len ? (max_seq_len + int64_t{tile} - 1) / tile * tile : (sk + tile - 1) / tile * tile;
+  };
+  const int64_t one = (max_seq_len + share_keys(kCUs) - 1) / share_keys(kCUs);
+  const int64_t sk = share_keys(2 * kCUs), two = (max_seq_len + sk - 1) / sk;
+  if (two > 64) return sk >= (one > 64 ? 384 : (rank <= 16 ? 512 : 640));
+  return sk >= 256 || rows * two <= 2048;
+}
+
 Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_queries_per_seq, bool prefill,
                const Tuning& tune, bool key_adapter) {
   Plan pl{};
@@ -311,15 +329,11 @@ Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_quer
     // as long as a share then still has 512 keys (32768 tokens x 8 kv heads: 35.7 against 38.6 us, 65536: 49.2
     // against 53.7; at 256 keys per share the doubling loses)
     if (!batch && !prefill && c->block_size != 0 && !rope && work * c->max_seq_len >= int64_t{2} * kCUs * 512) wgs = 2 * kCUs;
-    // ... and one sequence in the rotary form at ranks up to 32 likewise (20011 tokens, rank 8: 34.0 against 40.5 us,
-    // 60000: 72 against 97; rank 32: 35.2 against 45.8 and 82 against 110): its steps are a chain of dependent
-    // products and rotations that only a second wave per SIMD covers.  Above rank 32 a unit holds one workgroup.  Not
-    // where that makes more than 64 shares of fewer than 384 keys (4 kv heads, 20011 tokens: 27.0 against 25.0).  Nor
-    // without a B_K: nothing is rotated then, and one workgroup per unit keeps the streaming form.
-    if (!batch && rope_split && key_adapter && sh->rank <= 32) {
-      const int64_t sk = (work * c->max_seq_len / (2 * kCUs) + tile) / tile * tile;
-      if (sk >= 384 || (c->max_seq_len + sk - 1) / sk <= 64) wgs = 2 * kCUs;
-    }
+    // ... and one sequence in the rotary form at ranks up to 32 likewise (see rope_pays_two_per_unit).  Above rank 32 a
+    // unit holds one workgroup.  Nor without a B_K: nothing is rotated then, and one workgroup per unit keeps the
+    // streaming form.
+    if (!batch && rope_split && key_adapter && sh->rank <= 32 && rope_pays_two_per_unit(c->max_seq_len, work, tile, pl.rows, sh->rank))
+      wgs = 2 * kCUs;
     if (work >= 2 * wgs) {
       split_keys = c->max_seq_len;  // more units than workgroups wanted: one share per sequence
     } else {
