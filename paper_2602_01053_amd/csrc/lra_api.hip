@@ -188,11 +188,11 @@ lra_status lra_attn_prefill(const lra_shape* shape, const lra_cache* cache, cons
     return LRA_ERR_SHAPE;
   if (!plan_sizes_fit(shape, cache, n_new, 1)) return LRA_ERR_UNSUPPORTED;
   Tuning tune = resolve_tuning(tuning);
-  Plan pl = make_plan(shape, cache, n_new, 1, true, tune);
+  Plan pl = make_plan(shape, cache, n_new, 1, true, tune, adapters->b_k != nullptr);
   if (pl.workspace_optional && (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) ||
                                 workspace_bytes < pl.bytes_without_kc)) {
     tune.prefill_splits = 1;
-    pl = make_plan(shape, cache, n_new, 1, true, tune);
+    pl = make_plan(shape, cache, n_new, 1, true, tune, adapters->b_k != nullptr);
   }
   if (!pl.launchable) return LRA_ERR_UNSUPPORTED;
   // Rotary key side: the completed keys go to the workspace when the call has a key-side adapter and

@@ -179,14 +179,17 @@ static bool short_prefill_walks_tiles(const lra_shape* sh, const lra_cache* c, i
 // up to 64 shares (which one merge kernel takes) 0.98 to 1.43 with shares of 256 keys and more, 0.90 to 1.18 with
 // 128, there at least 1.01 up to 2048 (row, share) states; beyond 64 shares 0.71 to 1.08 with 128 and 256 keys,
 // at least 1.02 with 384 where one workgroup per unit makes more than 64 too, and where it does not 0.94 to 1.22 with
-// 512 (rank 32 the lower) and at least 1.0 with 640.
-static bool rope_pays_two_per_unit(int max_seq_len, int64_t work, int tile, int64_t rows, int rank) {
+// 512 (rank 32 the lower) and at least 1.0 with 640.  Prefills of a few tokens gain 1.05 to 1.5 from shares of 384
+// keys on (8 kv heads, 16 after 9000: 30.1 -> 26.2 us) and lose up to 13 % below (4 kv heads, 4 after 16000: 18.5 and
+// 21.3 us).
+static bool rope_pays_two_per_unit(int max_seq_len, int64_t work, int tile, int64_t rows, int rank, bool prefill) {
   auto share_keys = [&](int64_t wgs) {  // as the plan rounds them
     const int64_t sk = (work * max_seq_len + wgs - 1) / wgs;
     return work >= 2 * wgs || sk > max_seq_len ? (max_seq_len + int64_t{tile} - 1) / tile * tile : (sk + tile - 1) / tile * tile;
   };
   const int64_t one = (max_seq_len + share_keys(kCUs) - 1) / share_keys(kCUs);
   const int64_t sk = share_keys(2 * kCUs), two = (max_seq_len + sk - 1) / sk;
+  if (prefill) return sk >= 384 && two <= 64;
   if (two > 64) return sk >= (one > 64 ? 384 : (rank <= 16 ? 512 : 640));
   return sk >= 256 || rows * two <= 2048;
 }
@@ -332,7 +335,7 @@ Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_quer
     // ... and one sequence in the rotary form at ranks up to 32 likewise (see rope_pays_two_per_unit).  Above rank 32 a
     // unit holds one workgroup.  Nor without a B_K: nothing is rotated then, and one workgroup per unit keeps the
     // streaming form.
-    if (!batch && rope_split && key_adapter && sh->rank <= 32 && rope_pays_two_per_unit(c->max_seq_len, work, tile, pl.rows, sh->rank))
+    if (!batch && rope_split && key_adapter && sh->rank <= 32 && rope_pays_two_per_unit(c->max_seq_len, work, tile, pl.rows, sh->rank, prefill))
       wgs = 2 * kCUs;
     if (work >= 2 * wgs) {
       split_keys = c->max_seq_len;  // more units than workgroups wanted: one share per sequence

@@ -174,6 +174,26 @@ int main(int argc, char** argv) {
     CHECK(two.n_splits <= 64 || two.split_keys >= 384);
     CHECK(two.split_keys >= 256 || static_cast<int64_t>(two.rows) * two.n_splits <= 2048);
   }
+  // ... and for rotary prefills of a few tokens: only where a share keeps 384 keys
+  for (int it = 0; it < cases; ++it) {
+    lra_shape sh{};
+    sh.n_kv_heads = static_cast<int32_t>(pick({1, 2, 4, 8, 16, 32}));
+    sh.n_q_heads = sh.n_kv_heads * static_cast<int32_t>(pick({1, 2, 4, 7, 8, 16}));
+    sh.head_dim = 64;
+    sh.rank = static_cast<int32_t>(pick({8, 16, 32, 64}));
+    sh.key_rope_theta = 500000.f;
+    lra_cache c{};
+    c.k_base = c.v_base = c.l = dummy;
+    c.seq_lens = reinterpret_cast<const int32_t*>(dummy);
+    c.n_seqs = 1;
+    c.max_seq_len = static_cast<int32_t>(pick({128, 1024, 4096, 8192, 16384, 20011, 32768, 50000, 65536})) + static_cast<int32_t>(pick({-1, 0, 1}));
+    c.kv_token_stride = sh.head_dim * sh.n_kv_heads;
+    c.kv_head_stride = sh.head_dim;
+    const int n_new = static_cast<int>(pick({1, 4, 8, 16, 31, 32}));
+    const Plan two = make_plan(&sh, &c, n_new, 1, true, Tuning{}), one = make_plan(&sh, &c, n_new, 1, true, Tuning{}, false);
+    if (two.split_keys == one.split_keys) continue;
+    CHECK(two.short_prefill && two.split_keys >= 384 && two.n_splits <= 64);
+  }
   // the split of lra_cache_append over d_model
   for (int it = 0; it < cases; ++it) {
     const int64_t n_new = pick({1, 16, 32, 33, 64, 100, 128, 129, 512, 1000, 1024, 4096, 1 << 20, (1 << 20) + 1, INT32_MAX});
