@@ -91,3 +91,12 @@ def test_headline_kernels(table):
         if re.search(r"append_kernelILi128ELb0E", name) or "append_gemv_kernel" in name or "append_finish_kernel" in name:
             assert row[SCRATCH] == 0, name
     assert seen == {"cfg2", "cfg3"}
+
+
+def test_prefill_at_d64_rank64_reads_its_operands_ahead(table):
+    """d = 64, rank 64, plain key side: two waves per SIMD either way, and 190 registers and more are the schedule
+    that reads LDS operands ahead of their products.  The one that stays near 168 is a quarter slower per tile."""
+    rows = [r for n, r in table.items() if "prefill_mfma_kernel" in n and _args(n)[:2] == [64, 64] and _args(n)[3]]
+    assert len(rows) == 4
+    for row in rows:
+        assert row["VGPRs"] >= 190 and row[SCRATCH] == 0, row
