@@ -49,6 +49,10 @@ static void fill_params(Params& p, const lra_shape* sh, const lra_cache* c, cons
   p.num_blocks = c->num_blocks;
   p.n_seqs = c->n_seqs;
   p.max_seq_len = c->max_seq_len;
+  p.tile_group = pl.tile_group;
+  p.tile_heads = p.group / pl.tile_group;
+  p.tiles_per_round = 256 / (sh->n_kv_heads * p.tile_heads) > 0 ? 256 / (sh->n_kv_heads * p.tile_heads) : 1;
+  p.row_mul = (65535 + pl.tile_group) / pl.tile_group;
   p.group_pad = pl.group_pad;
   p.row_groups = pl.row_groups;
   p.split_keys = pl.split_keys;
@@ -191,7 +195,7 @@ lra_status lra_attn_prefill(const lra_shape* shape, const lra_cache* cache, cons
   Plan pl = make_plan(shape, cache, n_new, 1, true, tune, adapters->b_k != nullptr);
   if (pl.workspace_optional && (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) ||
                                 workspace_bytes < pl.bytes_without_kc)) {
-    tune.prefill_splits = 1;
+    tune.prefill_splits = -1;
     pl = make_plan(shape, cache, n_new, 1, true, tune, adapters->b_k != nullptr);
   }
   if (!pl.launchable) return LRA_ERR_UNSUPPORTED;

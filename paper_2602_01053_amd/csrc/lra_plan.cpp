@@ -126,35 +126,61 @@ lra_status check_common(const lra_shape* sh, const lra_cache* c) {
   return LRA_OK;
 }
 
-// Workgroups that share the key tiles of a q tile in the tile-walking prefill kernel: the count with the
-// smallest estimated time.  A compute unit takes two workgroups; a 64-key tile of head dimension 128 costs a
-// workgroup 1.3 us on a unit of its own and 2.1 us beside another one (so a last round of at most 256 workgroups
-// costs about half a round), a workgroup 4 us outside its tiles, and the partial states are written and read
-// back at 4.3 TB/s.  Measured on MI355X, group 4, rank 16 (us at 1 / 2 / 4 / 5 / 6 / 8 / 12 / 16 shares, chosen
-// one marked): 333 new tokens on 5333: 100 / 67 / 60 / 57* / 66 / 62 / 72 / 79; 700 on 9000: 157 / 154 / 140* /
-// 144 / 152 / 152 / 170 / 182; 1500 on 9000: 256* / 258 / 265 / 278 / 276 / 291 / 335 / 386.
+// The q tiles of the tile-walking prefill kernel and the workgroups that share the key tiles of each.
+//
+// A q tile holds 128 rows (new token, q head) of all q heads of a kv head, or 128 tokens of one q head (tile_group 1).
+// The first has fewer tiles and reads a key once for the group, the second spreads the reading of q, the product with
+// B_V and the stores over more compute units, which counts in calls of a few tokens on few keys (us with tiles of
+// the group / of one head, group 4: 33 new tokens without context 9.8 / 8.0, 64 after 300 12.7 / 11.9, 33 after
+// 5000 21.9 / 20.6, 200 after 9000 63 / 68).
+//
+// Shares: the count with the smallest estimated time.  A compute unit takes two workgroups; a 64-key tile of head
+// dimension 128 and rank 16 costs a workgroup 1.2 us on a unit of its own and 1.9 us beside another one (2.4 where every
+// workgroup has keys of its own: the memory is the bound), a workgroup 1.3 us outside its tiles and up to 2.3 for its
+// live rows; the merge costs 5 us, the partial states are written and read back at 4.3 TB/s.  Fitted to 2700 measured
+// calls.  The even division (about two workgroups per compute unit, at least eight tiles each) stays unless the
+// estimate is 8 % below its own: within that the two are level, and where it was followed at less it lost as often as
+// it won.  us at 1 / 2 / 4 / 5 / 6 / 8 / 12 / 16 shares, chosen one marked: 333 new tokens on 5333: 100 / 67 / 60 /
+// 57* / 66 / 62 / 72 / 79; 700 on 9000: 157 / 154 / 140* / 144 / 152 / 152 / 170 / 182.
 // One share, and no workspace, where q tiles of 128 tokens per q head would fill two workgroups per unit.
-static int64_t prefill_shares(const lra_shape* sh, int tokens, int max_seq_len) {
+struct PrefillTiles {
+  int tile_group;
+  int64_t shares;
+};
+static PrefillTiles plan_prefill_tiles(const lra_shape* sh, int tokens, int max_seq_len, bool split_kv_sized) {
+  const int G = sh->n_q_heads / sh->n_kv_heads;
   const int64_t slots = 2 * kCUs, tiles = (static_cast<int64_t>(max_seq_len) + 63) / 64;
-  if (static_cast<int64_t>((tokens + 127) / 128) * sh->n_q_heads >= slots) return 1;
-  const int64_t group_rows = static_cast<int64_t>(tokens) * (sh->n_q_heads / sh->n_kv_heads);
-  const int64_t wgs = (group_rows + 127) / 128 * sh->n_kv_heads;
-  const double width = (sh->head_dim + 32) / 160.0;  // (the tile's fixed part weighs like 32 columns)
-  const double alone = 1.3 * width, beside = 2.1 * width, fixed = 4.0, merge = 3.0;
+  const int64_t head_tiles = static_cast<int64_t>((tokens + 127) / 128) * sh->n_q_heads;  // tiles of one q head each
+  if (head_tiles >= slots) return {G, 1};
+  const bool few = !split_kv_sized && (max_seq_len < 1024 || (tokens <= 64 && max_seq_len <= 4096));
+  const int tg = few ? 1 : G;
+  const int64_t q_tiles = (static_cast<int64_t>(tokens) * tg + 127) / 128;
+  const int64_t wgs = q_tiles * (sh->n_q_heads / tg);
+  const int live = tokens * tg < 128 ? tokens * tg : 128;
+  const int rank_pad = sh->rank <= 16 ? 16 : (sh->rank <= 32 ? 32 : 64);
+  const double width = (sh->head_dim + 0.6 * rank_pad + 36.0) / (128 + 0.6 * 16 + 36.0);
+  const double alone = 1.2 * width, beside = (q_tiles == 1 && tg == G ? 2.4 : 1.9) * width;
+  const double fixed = 1.3 + 2.3 * live / 128, merge = 5.0;
   const double per_share = static_cast<double>(tokens) * sh->n_q_heads * (sh->head_dim + sh->rank) * 8.0 / 4.3e6;
-  int64_t best = 1;
-  double best_us = 0.0;
-  for (int64_t ns = 1; ns <= 32 && ns <= tiles; ++ns) {
+  auto estimate = [&](int64_t ns) {
     const int64_t w = wgs * ns, rest = w % slots, share = (tiles + ns - 1) / ns;
-    double us = (w / slots) * (fixed + beside * share);
-    if (rest > 0) us += fixed + (rest <= kCUs ? alone : beside) * share;
-    if (ns > 1) us += merge + per_share * ns;
-    if (ns == 1 || us < best_us) {
+    double us = static_cast<double>(w / slots) * (fixed + beside * static_cast<double>(share));
+    if (rest > 0) us += fixed + (rest <= kCUs ? alone : beside) * static_cast<double>(share);
+    return ns > 1 ? us + merge + per_share * static_cast<double>(ns) : us;
+  };
+  int64_t even = (slots + head_tiles - 1) / head_tiles;
+  if (even > max_seq_len / (8 * 64)) even = max_seq_len / (8 * 64);
+  even = even < 1 ? 1 : (even > 32 ? 32 : even);
+  int64_t best = even;
+  double best_us = 0.92 * estimate(even);
+  for (int64_t ns = 1; ns <= 32 && ns <= tiles; ++ns) {
+    const double us = estimate(ns);
+    if (us < best_us) {
       best = ns;
       best_us = us;
     }
   }
-  return best;
+  return {tg, best};
 }
 
 // Whether a prefill of few new tokens (no rotary key side) runs on the tile-walking kernel rather than on the
@@ -198,6 +224,7 @@ Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_quer
                const Tuning& tune, bool key_adapter) {
   Plan pl{};
   const int G = sh->n_q_heads / sh->n_kv_heads;
+  pl.tile_group = G;
   // The MFMA kernels move L in 16-byte pieces: ranks that are not a multiple of 8 take the
   // vector-ALU kernels.
   // The rotary key side: prefill runs on the tile-walking MFMA kernel, which completes a key
@@ -238,17 +265,21 @@ Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_quer
                      (tune.short_prefill > 32 || rope || !short_prefill_walks_tiles(sh, c, tokens));
   const bool rope_split = rope && pl.mfma && (!prefill || pl.short_prefill);  // rotary form of the split-KV kernel
   if (prefill && pl.mfma && !pl.short_prefill) {
-    // Tile-walking kernel: one workgroup per 128 query rows of a kv head (new tokens x the q heads that share
-    // it).  Where those do not fill the chip the key tiles of a q tile are divided among several workgroups and
-    // the merge kernel finishes the job; otherwise it is one kernel without a workspace.
+    // Tile-walking kernel: one workgroup per q tile (see plan_prefill_tiles).  Where those do not fill the chip the
+    // key tiles of a q tile are divided among several workgroups and the merge kernel finishes the job; otherwise it
+    // is one kernel without a workspace.
     pl.rows = tokens * sh->n_q_heads;
     pl.group_pad = pl.row_tiles = pl.row_groups = 1;
     pl.split_keys = c->max_seq_len;
-    int64_t ns = tune.prefill_splits > 0 ? tune.prefill_splits : prefill_shares(sh, tokens, c->max_seq_len);
+    // (few tokens on a long context reach this place only where the packed tile was measured ahead of the split-KV path)
+    const bool split_kv_sized = tokens <= tune.short_prefill && static_cast<int64_t>(tokens) * 4 <= c->max_seq_len;
+    const PrefillTiles pt = plan_prefill_tiles(sh, tokens, c->max_seq_len, split_kv_sized);
+    pl.tile_group = tune.prefill_splits > 0 ? G : pt.tile_group;
+    int64_t ns = tune.prefill_splits > 0 ? tune.prefill_splits : (tune.prefill_splits < 0 ? 1 : pt.shares);
     ns = ns > 32 ? 32 : (ns < 1 ? 1 : ns);
     // (sequences below sixteen tiles run without a workspace too, where they are not short prefills)
-    pl.workspace_optional = ns > 1 && tune.prefill_splits <= 0 && c->max_seq_len < 1024 &&
-                            (tokens > tune.short_prefill || static_cast<int64_t>(tokens) * 4 > c->max_seq_len);
+    pl.workspace_optional = ns > 1 && tune.prefill_splits == 0 && c->max_seq_len < 1024 &&
+                            !split_kv_sized;
     pl.n_splits = static_cast<int>(ns);
     pl.bytes = 0;
     if (pl.n_splits > 1) {

@@ -18,7 +18,7 @@ struct Tuning {
   int variant = 0;          // 0 automatic, 1 vector-ALU kernels, 2 MFMA kernels without the streaming form
   int split_keys = 0;       // keys per workgroup in decode, 0 = automatic
   int short_prefill = 32;   // new tokens up to which a prefill takes the split-KV path (0 = never)
-  int prefill_splits = 0;   // workgroups sharing the key tiles of a q tile, 0 = automatic
+  int prefill_splits = 0;   // workgroups sharing the key tiles of a q tile, 0 = automatic, -1 = one, q tiles as automatic
   bool rope_key_prepass = true;  // rotary prefill on contiguous caches: completed keys by a pre-pass
   int append_skinny = 64;   // new tokens up to which lra_cache_append streams the weights (0 = never)
   int append_stages = 0;    // LDS stages of the tiled append GEMM, 0 = chosen from the grid
@@ -34,6 +34,7 @@ struct Plan {
   int rows;        // query rows = (queries | new tokens) x Hq
   int split_keys;  // keys per split
   int n_splits;    // splits per sequence at max_seq_len
+  int tile_group;  // tile-walking prefill: q heads whose rows share a q tile (all of a kv head's, or one)
   int group_pad, row_tiles, row_groups;  // MFMA decode row packing
   int l_block;     // split-KV MFMA kernels with per-adapter low-rank caches: padded rank of one slot's column block, else 0
   bool workspace_optional;  // prefill: without room for the plan's workspace the call runs with one share per q tile

@@ -38,23 +38,31 @@
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, g2 = lane >> 5;
-  const int Hq = p.n_q_heads, Hkv = p.n_kv_heads, G = p.group, r = p.rank;
+  const int Hq = p.n_q_heads, Hkv = p.n_kv_heads, r = p.rank;
+  const int G = p.tile_group;  // q heads whose rows share a q tile: all of a kv head's, or one
 
-  // workgroup -> (kv head, q tile); consecutive ids go to consecutive XCDs
+  // workgroup -> (kv head, first of the tile's q heads, q tile); consecutive ids go to consecutive XCDs
   const int lin = blockIdx.x;
-  const int hk = lin % Hkv;
-  int qt = lin / Hkv;
-  const int n_rows = p.n_new * G;                  // query rows of a kv head: (new token, q head of the group), the q head fastest
+  const int rest = lin / Hkv, hk = lin - rest * Hkv;
+  int qt = rest;
+  int head_first = hk * p.group;
+  if (p.tile_heads > 1) {  // (the quotient by one is not worth its instructions in a call of one tile per workgroup)
+    qt = rest / p.tile_heads;
+    head_first += (rest - qt * p.tile_heads) * G;
+  }
+  const int n_rows = p.n_new * G;                  // query rows of these heads: (new token, q head), the q head fastest
   {
     // Causal q tiles differ in length (tile i walks the keys up to its diagonal).  The 256 compute units take
     // workgroups in rounds of 256; a unit that holds two workgroups holds number k and number k + 256.  Every other
     // round walks its q tiles backwards, so the long tiles of one round sit next to the short tiles of the next
     // and the units finish together.
     const int q_tiles = (n_rows + BM - 1) / BM;
-    const int tpr = max(1, 256 / Hkv);             // q tiles per round
-    const int round = qt / tpr, pos = qt - round * tpr;
-    const int cnt = min(tpr, q_tiles - round * tpr);
-    if ((round & 1)) qt = round * tpr + (cnt - 1 - pos);
+    const int tpr = p.tiles_per_round;
+    if (q_tiles > tpr) {
+      const int round = qt / tpr, pos = qt - round * tpr;
+      const int cnt = min(tpr, q_tiles - round * tpr);
+      if ((round & 1)) qt = round * tpr + (cnt - 1 - pos);
+    }
   }
   const int t = p.seq_index;
   const int a_idx = p.adapter_index;
@@ -68,14 +76,14 @@
   // 143 by at most 16) taken exactly by a multiplication, so that it is cheap to form again wherever it is needed:
   // kept in registers through the loop it sent the rank-64 kernels to scratch memory (the three small numbers
   // travel in one scalar register for the same reason).
-  const int tok0 = __builtin_amdgcn_readfirstlane(q0 / G);
-  const int row_map = (q0 - tok0 * G) | (min(BM, n_rows - q0) << 4) | (__builtin_amdgcn_readfirstlane((65535 + G) / G) << 12);
+  const int tok0 = G > 1 ? __builtin_amdgcn_readfirstlane(q0 / G) : q0;
+  const int row_map = (q0 - tok0 * G) | (min(BM, n_rows - q0) << 4) | (p.row_mul << 12);
   // (token - tok0, q head of the group) of a row of the tile; false (and the last live row) for one past the end
   auto map_row = [&](int in_tile, int& tok, int& gq) __attribute__((always_inline)) -> bool {
     int m = row_map;
-    // (not at d = 64, rank 64, contiguous, where the kernel has registers left and, with this barrier to its scheduling,
-    // walked a tile alone on its unit in 1.25 times the time)
-    if constexpr (D != 64 || RP != 64) asm volatile("" : "+s"(m), "+v"(in_tile));
+    // (not at d = 64, rank 64 with a Qt term, where the kernel has registers left and, with this barrier to its
+    // scheduling, walked a tile alone on its unit in 1.25 times the time)
+    if constexpr (!(D == 64 && RP == 64 && HAS_BK)) asm volatile("" : "+s"(m), "+v"(in_tile));
     const int at = (m & 15) + min(in_tile, ((m >> 4) & 255) - 1);
     tok = (at * (m >> 12)) >> 16;
     gq = at - tok * G;
@@ -85,7 +93,7 @@
   auto global_row = [&](bool clamped) __attribute__((always_inline)) -> int {
     int tok, gq;
     const bool live = map_row(wave * 32 + (static_cast<int>(threadIdx.x) & 31), tok, gq);
-    return live || clamped ? (tok0 + tok) * Hq + hk * G + gq : -1;
+    return live || clamped ? (tok0 + tok) * Hq + head_first + gq : -1;
   };
   auto token_of = [&](int in_tile) __attribute__((always_inline)) -> int {
     int tok, gq;
@@ -539,6 +547,7 @@
 #pragma unroll
         for (int term = 0; term < 2; ++term) bop[term] = pf_as_bf16x8(make_uint4(w[term][0], w[term][1], w[term][2], w[term][3]));
       }
+      pf_bf16x8 bvt[DB];
 #pragma unroll
       for (int b = 0; b < DB; ++b) {
         // A operand: B_V^T: lane (d = 32b + l32, element e <-> rho as above)
@@ -549,10 +558,12 @@
           const uint32_t val = rho < r ? static_cast<uint32_t>(bv[rho * ldb + 32 * b + l32]) : 0u;
           w[e >> 1] |= val << ((e & 1) * 16);
         }
-        const pf_bf16x8 bvt = pf_as_bf16x8(make_uint4(w[0], w[1], w[2], w[3]));
-        o_acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bvt, bop[1], o_acc[b], 0, 0, 0);
-        o_acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bvt, bop[0], o_acc[b], 0, 0, 0);
+        bvt[b] = pf_as_bf16x8(make_uint4(w[0], w[1], w[2], w[3]));
       }
+#pragma unroll
+      for (int term = 1; term >= 0; --term)
+#pragma unroll
+        for (int b = 0; b < DB; ++b) o_acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bvt[b], bop[term], o_acc[b], 0, 0, 0);
     }
   }
   if (out_row >= 0) {

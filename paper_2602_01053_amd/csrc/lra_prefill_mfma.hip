@@ -103,8 +103,8 @@ static hipError_t launch_pf(const Params& p, dim3 grid, hipStream_t s) {
 }
 
 hipError_t launch_prefill_mfma(const Params& p, hipStream_t s) {
-  const int q_tiles = (p.n_new * p.group + 127) / 128;
-  dim3 grid(q_tiles * p.n_kv_heads, p.n_splits);
+  const int q_tiles = (p.n_new * p.tile_group + 127) / 128;
+  dim3 grid(q_tiles * p.n_kv_heads * (p.group / p.tile_group), p.n_splits);
   const int rp = p.rank <= 16 ? 16 : (p.rank <= 32 ? 32 : 64);
   if (p.head_dim == 128) {
     if (rp == 16) return launch_pf<128, 16>(p, grid, s);

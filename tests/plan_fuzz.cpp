@@ -94,6 +94,15 @@ int main(int argc, char** argv) {
         CHECK(pk.mfma == pl.mfma && pk.bytes <= pl.bytes && pk.bytes_without_kc <= pl.bytes_without_kc);
         CHECK(pk.n_splits <= pl.n_splits && pk.split_keys >= pl.split_keys);
       }
+      if (prefill && pl.mfma && !pl.short_prefill) {
+        CHECK(pl.tile_group == 1 || pl.tile_group == G);
+        Tuning alone = tune;  // what a call falls back to where the workspace is optional and missing
+        alone.prefill_splits = -1;
+        const Plan pa = make_plan(&sh, &c, static_cast<int>(tokens), 1, true, alone);
+        CHECK(pa.n_splits == 1 && pa.bytes_without_kc == 0 && !pa.workspace_optional && (tune.prefill_splits > 0 || pa.tile_group == pl.tile_group));
+        CHECK(!pl.workspace_optional || (c.max_seq_len < 1024 && pl.n_splits > 1));
+        if (tune.prefill_splits > 0) CHECK(pl.tile_group == G);
+      }
       if (pl.kc_bytes) {  // completed keys of a rotary prefill: a copy of the K_base extent behind everything else
         CHECK(prefill && pl.mfma && !pl.short_prefill && sh.key_rope_theta > 0.f);
         CHECK(pl.off_kc >= pl.bytes_without_kc);

@@ -213,6 +213,28 @@ def test_prefill_rows_of_all_heads_of_a_group_in_one_tile(case, splits):
     _gate(got, oracle_prefill(w), label=str(case))
 
 
+TILE_CASES = [
+    # n, n_new, Hq, Hkv, d, r: automatic plans on either side of the lengths and token counts where a q tile holds
+    # 128 tokens of one q head (up to 1023 keys, or 64 tokens on up to 4096) or the rows of all heads of a group
+    (1023, 300, 9, 3, 128, 16),
+    (1024, 300, 9, 3, 128, 16),
+    (1023, 64, 14, 2, 64, 64),
+    (4096, 64, 14, 2, 64, 8),
+    (4097, 64, 14, 2, 64, 8),
+    (4096, 65, 16, 1, 128, 40),
+    (130, 129, 16, 1, 128, 24),    # sixteen tile sets per kv head, one live row in the second tile of each
+    (2500, 1300, 5, 1, 64, 16),    # several rounds of q tiles per head set
+]
+
+
+@pytest.mark.parametrize("case", TILE_CASES, ids=lambda c: "n%d_new%d_hq%d_hkv%d_d%d_r%d" % c)
+def test_prefill_tiles_of_one_head_or_of_a_group(case):
+    n, n_new, hq, hkv, d, r = case
+    w = W.make_contiguous("head_tiles", "prefill", seed=4600 + n + n_new, n_agents=1, n_q_heads=hq, n_kv_heads=hkv,
+                          head_dim=d, rank=r, n=n, n_new=n_new, d_model=None, b_std=0.05)
+    _gate(run_prefill(w, DEV), oracle_prefill(w), label=str(case))
+
+
 @pytest.mark.parametrize("n,n_new", [(417, 84), (1023, 300)])
 def test_short_sequence_prefill_with_and_without_a_workspace(n, n_new):
     w = W.make_contiguous("short_sequence", "prefill", seed=4700 + n, n_agents=1, n_q_heads=8, n_kv_heads=2,
