@@ -185,18 +185,26 @@ static PrefillTiles plan_prefill_tiles(const lra_shape* sh, int tokens, int max_
 
 // Whether a prefill of few new tokens (no rotary key side) runs on the tile-walking kernel rather than on the
 // split-KV decode kernels.  Those take 16 rows per tile and, beyond 32 rows of a kv head, read the keys once per row
-// group; the tile-walking kernel has one tile for 128 rows, at the price of 128 rows' matrix work per key.
-// Measured on MI355X, us split-KV / tile walk (group 4, 8 kv heads): contiguous, 4 new tokens (one row tile):
-// 10.2 / 10.7 after 2000, 31.4 / 39.5 after 33000; 8: 18.7 / 17.3 after 9001, 34.7 / 39.7 after 33000; 16: 13.9 /
-// 14.0, 21.5 / 19.0 and 45.0 / 43.3 after 2000, 9001 and 33000; 32: 15.6 / 17.2, 27.3 / 23.3 and 66.5 / 47.7.
-// Paged: 8: 14.9 / 12.4, 21.9 / 18.4 and 42.9 / 40.1; 32: 18.2 / 18.0, 31.5 / 24.9 and 89.9 / 47.4.
+// group; the tile-walking kernel has one tile for 128 rows, at the price of 128 rows' matrix work per key, and at most
+// 32 shares of it: with few kv heads it cannot fill the chip on long contexts.  Measured on MI355X at 0.3 to 33
+// thousand keys (ratio of the times split-KV / tile walk; G = q heads per kv head):
+//   8 kv heads, G 4    5 and 8 tokens 1.2 at 2 k, 1.05 at 9 k, paged 1.1 to 1.4 throughout; 32 tokens 1.0 to 4 k, 1.15 at 9 k, 1.55 at 33 k
+//   8 kv heads, d 64   8 tokens 1.13 at 2 k, 1.0 at 9 k, 0.87 at 20 k
+//   4 kv heads, G 7    4 tokens 1.0 at 6 k, 0.97 at 9 k, paged 1.08 at 9 k, 0.95 at 14 k; 8 tokens 1.03 at 9 k, paged 1.02 at 33 k
+//   2 kv heads, G 8    8 tokens 1.08 at 2 k, 0.98 at 6 k, 0.94 at 9 k, paged 1.02 at 9 k, 0.92 at 14 k; 16 tokens 0.94 from 2 k
+//                      on, paged 1.0 at 14 k, 0.94 at 20 k; 32 tokens 0.96 at 6 k, 1.04 at 9 k
+//   32 kv heads, G 1   5 and 8 tokens 1.1 to 14 k, 0.81 to 0.93 at 20 k (one row group: both read the keys once)
 static bool short_prefill_walks_tiles(const lra_shape* sh, const lra_cache* c, int tokens) {
-  const int G = sh->n_q_heads / sh->n_kv_heads;
+  const int G = sh->n_q_heads / sh->n_kv_heads, n = c->max_seq_len;
   const int rows = tokens * (G <= 4 ? 4 : (G <= 8 ? 8 : 16));  // rows of a kv head in the split-KV kernels
   if (rows <= 16) return false;
-  if (c->block_size != 0) return true;
-  if (sh->n_kv_heads * ((rows + 31) / 32) <= 8) return c->max_seq_len <= 8192 + 1024;
-  return tokens * G <= 96 || c->max_seq_len >= 4096;
+  const int groups = (rows + 31) / 32;                                // times those read the keys
+  const int units = sh->n_kv_heads * groups;
+  const int walk = sh->n_kv_heads * ((tokens * G + 127) / 128);      // q tiles of the tile-walking kernel
+  if (groups == 1 && walk > 8 && n > 16384) return false;
+  if (c->block_size != 0) return n <= 12288 || !(groups == 1 ? walk < 8 : walk < 4 && groups <= 4);
+  if (units <= 8) return n <= (walk < 4 ? (tokens * G <= 96 ? 3072 : 0) : (units < 8 ? 6144 : 9216));
+  return tokens * G <= 96 || n >= (walk < 8 ? 8192 : 4096);
 }
 
 // Whether one sequence in the rotary form of the split-KV kernel runs with two workgroups per compute unit rather

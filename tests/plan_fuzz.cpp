@@ -203,6 +203,30 @@ int main(int argc, char** argv) {
     if (two.split_keys == one.split_keys) continue;
     CHECK(two.short_prefill && two.split_keys >= 384 && two.n_splits <= 64);
   }
+  // prefills of a few tokens: the path that was measured ahead on either side of each bound
+  struct ShortCase { int hkv, G, n_new, n; bool paged, split_kv; };
+  const ShortCase shorts[] = {
+      {8, 4, 4, 9004, false, true},   {8, 4, 8, 9009, false, false},  {8, 4, 8, 33008, false, true},  {8, 4, 8, 33008, true, false},
+      {8, 4, 32, 2032, false, true},  {8, 4, 32, 9032, false, false}, {4, 7, 4, 6004, false, false},  {4, 7, 4, 9004, false, true},
+      {4, 7, 4, 9004, true, false},   {4, 7, 4, 14004, true, true},   {4, 7, 8, 33008, true, false},  {2, 8, 8, 2008, false, false},
+      {2, 8, 8, 9008, false, true},   {2, 8, 8, 9008, true, false},   {2, 8, 8, 14008, true, true},   {2, 8, 16, 2016, false, true},
+      {2, 8, 32, 6032, false, true},  {2, 8, 32, 9032, false, false}, {32, 1, 8, 14008, false, false}, {32, 1, 8, 20008, true, true}};
+  for (int it = 0; it < static_cast<int>(sizeof(shorts) / sizeof(shorts[0])); ++it) {
+    const ShortCase& t = shorts[it];
+    lra_shape sh{};
+    sh.n_kv_heads = t.hkv;
+    sh.n_q_heads = t.hkv * t.G;
+    sh.head_dim = 128;
+    sh.rank = 16;
+    lra_cache c{};
+    c.n_seqs = 1;
+    c.max_seq_len = t.n;
+    c.kv_token_stride = c.kv_head_stride = 128;
+    c.block_size = t.paged ? 16 : 0;
+    c.kv_block_stride = t.paged ? 16 * 128 * t.hkv : 0;
+    c.max_blocks_per_seq = c.num_blocks = t.paged ? (t.n + 15) / 16 : 0;
+    CHECK(make_plan(&sh, &c, t.n_new, 1, true, Tuning{}).short_prefill == t.split_kv);
+  }
   // the split of lra_cache_append over d_model
   for (int it = 0; it < cases; ++it) {
     const int64_t n_new = pick({1, 16, 32, 33, 64, 100, 128, 129, 512, 1000, 1024, 4096, 1 << 20, (1 << 20) + 1, INT32_MAX});
