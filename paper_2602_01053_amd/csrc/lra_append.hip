@@ -9,7 +9,7 @@
 // Four kernels, chosen by the number of new tokens (launch_append at the end of the file): a
 // matrix-vector kernel (1-2 tokens), a weight-streaming MFMA kernel (up to 64), and two tiled
 // GEMM kernels (128 features x 128 or 64 tokens per workgroup; 256 x 256 for chunks whose tiles
-// fill whole rounds of the chip).
+// fill the chip, see wide_tiles_pay).
 //
 // The tiled GEMM takes the weights one output feature per row (the usual layout of a linear
 // layer) and computes transposed, Y^T[feature][token] = W[feature][:] . X[token][:], so
@@ -919,6 +919,24 @@ static void launch_skinny(const AppendParams& p, hipStream_t s) {
   else hipLaunchKernelGGL((append_skinny_kernel<D, NT, false>), grid, dim3(512), 0, s, p);
 }
 
+// Whether the 256 x 256 tiles, one workgroup per compute unit, are faster than the 128 x 128 tiles with two.  An XCD
+// takes every eighth token tile with all its feature tiles, 32 tiles at a time.  Estimated times of rounds, in units
+// of 1 / 64 of d_model = 4096: 64 for 512 tiles of 128, three more for every round before it, 31 for a rest of up to
+// 256 of them and 54 to 70 beyond; 110 for a full round of an XCD, 74 to 118 for a partial one, 6 % more with two
+// blocks of L rows to stage.  Fitted to 650 calls of thirteen layers.  us with 128 and with 256: Llama-3-8B projection
+// 3500 new tokens 64 and 96, 6000 127 and 101, 8192 171 and 117, 8700 161 and 192 (two of the XCDs go a second round),
+// 12000 252 and 201; 12 kv heads on d_model 2048, 4500 71 and 104; 32 kv heads, 2500 175 and 211, 7000 526 and 445.
+// A K and V region that is no multiple of 256 features fills its last feature tile in part and never gains.
+static bool wide_tiles_pay(const AppendParams& p, int hd, int64_t tiles128) {
+  if (hd % 256 != 0 || tiles128 <= 256) return false;
+  const int64_t per_xcd = static_cast<int64_t>(((p.n_new + 255) / 256 + 7) / 8) * 2 * (hd / 256);
+  const double rounds = static_cast<double>(tiles128 / 512), rest = static_cast<double>(tiles128 % 512);
+  const double part = static_cast<double>(per_xcd % 32) / 32;
+  const double t128 = 64.0 * rounds + 1.5 * rounds * (rounds - 1.0) + (rest == 0 ? 0.0 : (rest <= 256 ? 31.0 : 54.0 + 16.0 * (rest - 256) / 256));
+  const double t256 = 110.5 * static_cast<double>(per_xcd / 32) + (part == 0 ? 0.0 : 74.0 + 44.0 * part);
+  return t256 * (p.rank > 32 ? 1.06 : 1.0) < 0.95 * t128;
+}
+
 hipError_t launch_append(const AppendParams& p, hipStream_t s) {
   const int hd = p.n_kv_heads * p.head_dim;
   const bool paged = p.block_size != 0;
@@ -972,14 +990,10 @@ hipError_t launch_append(const AppendParams& p, hipStream_t s) {
     }
     return hipGetLastError();
   }
-  // 256 x 256 tiles, one workgroup per compute unit, from half a round of the chip on: a round costs about as much
-  // however full it is.  Measured, us with 128 x 128 tiles and with these: Llama-3-8B projection (8 feature tiles)
-  // 3500 new tokens 71 and 90, 4096 93 and 86, 9000 (288 tiles) 210 and 218, 12000 274 and 222; 4 kv heads (4
-  // feature tiles) 7000 72 and 80, 8192 85 and 84, 9000 108 and 97, 16384 176 and 115.
-  const int wide_tiles = ((p.n_new + 255) / 256) * 2 * ((hd + 255) / 256);
-  const bool wide_ok = hd > 256;  // (four feature tiles and more: what the kernel's division of the L features assumes)
-  const bool wide_pays = wide_tiles >= 128;
-  if (wide_ok && (p.tile == 256 || (p.tile == 0 && p.stages == 0 && wide_pays))) {
+  const int n_ft = 2 * ((hd + 127) / 128) + 1;
+  const int64_t tiles128 = static_cast<int64_t>((p.n_new + 127) / 128) * n_ft;
+  // (four feature tiles and more: what the kernel's division of the L features assumes)
+  if (hd > 256 && (p.tile == 256 || (p.tile == 0 && p.stages == 0 && wide_tiles_pay(p, hd, tiles128)))) {
     const int n_ct = 2 * ((hd + 255) / 256), t8 = ((p.n_new + 255) / 256 + 7) / 8;
     const dim3 wgrid(8 * t8 * n_ct);  // (see the kernel: XCD, feature tile, token tile)
 #define LRA_APPEND_WIDE(DD, PG)                                                                          \
@@ -997,17 +1011,19 @@ hipError_t launch_append(const AppendParams& p, hipStream_t s) {
 #undef LRA_APPEND_WIDE
     return hipGetLastError();
   }
-  const int n_ft = 2 * ((hd + 127) / 128) + 1;
-  const int64_t tiles128 = static_cast<int64_t>((p.n_new + 127) / 128) * n_ft;
   const dim3 grid(static_cast<unsigned>((tiles128 + 7) / 8 * 8));
   // One workgroup per compute unit or fewer: nothing shares the LDS, so a deeper ring of
   // stages (more requests in flight per workgroup) is free; beyond that two workgroups per
-  // unit with two stages each hide each other's waits.
-  const int stages = p.stages != 0 ? p.stages : (tiles128 <= 256 ? 4 : 2);
-  // half-size token tiles while even those leave CUs idle, or when asked for (Llama-3-8B projection:
-  // 19-21 us against 25-27 us up to 512 new tokens, 23 against 29 at 700)
-  if (p.tile == 64 || (p.tile == 0 && p.stages == 0 && tiles128 <= 100)) {
-    const dim3 g64(static_cast<unsigned>((static_cast<int64_t>((p.n_new + 63) / 64) * n_ft + 7) / 8 * 8));
+  // unit with two stages each hide each other's waits.  Not where those would be one round and a little
+  // (up to 700 tiles): three rounds of one workgroup per unit then take less than two of two (us with two
+  // and with three stages: 576 tiles 87 and 78, 612 105 and 95, 680 110 and 101, 700 62.5 and 62).
+  const int stages = p.stages != 0 ? p.stages : (tiles128 <= 256 ? 4 : (tiles128 > 512 && tiles128 <= 700 ? 3 : 2));
+  // half-size token tiles while one round of one workgroup per unit holds them, or when asked for (us with 64-token
+  // and with 128-token tiles: Llama-3-8B projection 512 new tokens 23 and 28, 700 22 and 28; 8 kv heads of 64 on
+  // 2048, 1500 new tokens 13 and 17)
+  const int64_t tiles64 = static_cast<int64_t>((p.n_new + 63) / 64) * n_ft;
+  if (p.tile == 64 || (p.tile == 0 && p.stages == 0 && tiles64 <= 256)) {
+    const dim3 g64(static_cast<unsigned>((tiles64 + 7) / 8 * 8));
     if (p.head_dim == 128) {
       if (paged) hipLaunchKernelGGL((append_kernel<128, true, 4, 64>), g64, dim3(512), 0, s, p);
       else hipLaunchKernelGGL((append_kernel<128, false, 4, 64>), g64, dim3(512), 0, s, p);

@@ -33,13 +33,13 @@ bool plan_sizes_fit(const lra_shape* sh, const lra_cache* c, int32_t tokens, int
   return true;
 }
 
-// A chunk whose 128-feature output tiles occupy about half of the chip or less walks all of d_model in
-// each of them, one 64-wide step after the other, at what one compute unit can pull from L2.  Such
-// chunks divide d_model among several workgroups per tile (a power of two of parts, at least four
-// steps each, about one workgroup per compute unit in all) and add the parts in a second kernel.
-// Measured on the Llama-3-8B projection: 64 tokens 10 against 18 us, 160 tokens 12 against 19 us; up to
-// 32 tokens the weight-streaming kernel is as fast and stays.  Forced tile or stage choices keep the
-// unsplit kernels.
+// A chunk whose output tiles of 128 features x 64 tokens occupy about half of the chip or less walks all of d_model
+// in each of them, one 64-wide step after the other, at what one compute unit can pull from L2.  Such chunks divide
+// d_model among several workgroups per tile (a power of two of parts, at least four steps each, about one workgroup
+// per compute unit in all) and add the parts in a second kernel.  Measured on the Llama-3-8B projection: 64 tokens 10
+// against 18 us, 160 tokens 12 against 19 us; up to 32 tokens the weight-streaming kernel is as fast and stays.  Chunks
+// of more than 100 tiles of 128 tokens fill the chip with tiles of 64 in one round, unsplit (8 kv heads of 64 on 2048,
+// 1500 new tokens: 13 us, divided in two 19).  Forced tile or stage choices keep the unsplit kernels.
 AppendSplit plan_append_split(int n_new, int n_kv_heads, int head_dim, int rank, int d_model, const Tuning& tune) {
   AppendSplit none{1, 128, 0};
   if (tune.append_k_splits == 1 || tune.append_tile != 0 || tune.append_stages != 0) return none;
@@ -48,7 +48,7 @@ AppendSplit plan_append_split(int n_new, int n_kv_heads, int head_dim, int rank,
   const int64_t hd = static_cast<int64_t>(n_kv_heads) * head_dim;
   const int64_t tile_rows = 2 * ((hd + 127) / 128) + 1;
   const int64_t tiles128 = (static_cast<int64_t>(n_new) + 127) / 128 * tile_rows;
-  if (tune.append_k_splits == 0 && (n_new <= 32 || tiles128 * 2 > kCUs))
+  if (tune.append_k_splits == 0 && (n_new <= 32 || tiles128 > 100))
     return none;
   AppendSplit sp{1, tiles128 <= 100 ? 64 : 128, 0};
   const int64_t tiles = (static_cast<int64_t>(n_new) + sp.bt - 1) / sp.bt * tile_rows;

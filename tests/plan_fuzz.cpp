@@ -249,7 +249,7 @@ int main(int argc, char** argv) {
       CHECK(tune.append_tile == 0 && tune.append_stages == 0 && tune.append_k_splits != 1);
       if (tune.append_k_splits == 0) {
         const int64_t tiles = (n_new + sp.bt - 1) / sp.bt * (2 * ((static_cast<int64_t>(hkv) * d + 127) / 128) + 1);
-        CHECK(tiles * sp.k_splits <= kCUs && dm / 64 / sp.k_splits >= 4 && n_new > 32);
+        CHECK(tiles * sp.k_splits <= kCUs && dm / 64 / sp.k_splits >= 4 && n_new > 32 && sp.bt == 64);
       }
     }
   }
