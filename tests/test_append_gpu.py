@@ -86,7 +86,8 @@ def test_append_tiled_stage_counts(case, stages):
 @pytest.mark.parametrize("tile", [64, 128, 256])
 def test_append_tile_sizes(case, tile):
     """Every tile size of the GEMM kernels, forced: ragged token tiles, feature regions of 64, 192 and 1024
-    (a tile that is partly filled, one that straddles the K and V rows of w), rank 8 to 64."""
+    (a tile that is partly filled, one that straddles the K and V rows of w), rank 8 to 64.  Regions of up to 256
+    features have no 256-wide form: asked for it, they run on the automatic choice."""
     prev_t, prev_k = lra.lra_set_append_tile(tile), lra.lra_set_append_skinny(0)
     try:
         test_append_contiguous(case)
@@ -111,6 +112,28 @@ def test_append_wide_tiles(case):
         test_append_contiguous(case)
     finally:
         lra.lra_set_append_tile(prev_t)
+        lra.lra_set_append_skinny(prev_k)
+
+
+ORDER_CASES = [
+    # 128-token tiles, two stages: the orders in which the tiles are dealt out (three feature tiles here)
+    (600, 512, 64, 1, 64, 8, 10000.0),          # four token tiles, one round: the plain order
+    (700, 513, 64, 1, 64, 16, 10000.0),         # five: a stretch per XCD, L tiles on five of them
+    (30000, 22528, 64, 1, 64, 8, 10000.0),      # 176 token tiles, above a round: the plain order (a multiple of 8)
+    (30000, 22529, 64, 1, 64, 8, 0.0),          # 177: stretches
+    (44100, 44032, 64, 1, 64, 8, 10000.0),      # 344 token tiles, above two rounds: stretches
+    (100, 100, 128, 5, 128, 24, 10000.0),       # fewer tokens than features
+]
+
+
+@pytest.mark.parametrize("case", ORDER_CASES, ids=lambda c: "n%d_new%d_dm%d_hkv%d_d%d_r%d_th%g" % c)
+def test_append_tile_orders(case):
+    prev_t, prev_s, prev_k = lra.lra_set_append_tile(128), lra.lra_set_append_stages(2), lra.lra_set_append_skinny(0)
+    try:
+        test_append_contiguous(case)
+    finally:
+        lra.lra_set_append_tile(prev_t)
+        lra.lra_set_append_stages(prev_s)
         lra.lra_set_append_skinny(prev_k)
 
 
@@ -217,19 +240,19 @@ def test_append_split_over_d_model_forced(case, parts):
 def test_append_paged_then_attend(skinny, tile, parts):
     prev, prev_t, prev_p = lra.lra_set_append_skinny(skinny), lra.lra_set_append_tile(tile), lra.lra_set_append_k_splits(parts)
     try:
-        _paged_then_attend(parts > 1)
+        _paged_then_attend(parts > 1, hkv=4 if tile == 256 else 2)  # (the 256-wide tiles need more than 256 features)
     finally:
         lra.lra_set_append_skinny(prev)
         lra.lra_set_append_tile(prev_t)
         lra.lra_set_append_k_splits(prev_p)
 
 
-def _paged_then_attend(with_workspace=False):
+def _paged_then_attend(with_workspace=False, hkv=2):
     """Appends to two sequences of a paged cache (a last block that is partly filled, blocks in
     permuted order), checks the written rows and that nothing else moved, then runs the
     attention prefill on the appended tokens and compares it with the oracle evaluated on
     the cache the producer wrote."""
-    hkv, hq, d, r, d_model, theta = 2, 8, 128, 16, 512, 500000.0
+    hq, d, r, d_model, theta = 8, 128, 16, 512, 500000.0
     seq_lens = [77, 300]
     n_new = [30, 130]
     bs, max_blocks = 16, 20
@@ -295,6 +318,56 @@ def _paged_then_attend(with_workspace=False):
     lr = oracle.lra_oracle.gather_paged_l(f(ld), ids, seq_lens[s])
     ref = oracle.prefill(f(q), kb, vb, lr, f(b_k[1]), f(b_v[1]), n=seq_lens[s], scale=1.0 / d ** 0.5)
     _gate(f(out), ref, "attention over the appended cache")
+
+
+PAGED_WIDE_CASES = [
+    # lengths and new tokens of two sequences, d_model, Hkv, d, r: 256 x 256 tiles on paged caches
+    ([300, 77], [300, 5], 64, 4, 128, 8),          # four feature tiles of one step: two token blocks of L each; a second tile of 44 tokens
+    ([70, 900], [1, 515], 192, 5, 64, 40),         # a feature tile filled in part, two blocks of L rows, three token tiles
+    ([257, 1100], [256, 1000], 128, 8, 64, 64),    # exactly one token tile; a ragged last block
+    ([513, 40], [511, 40], 256, 6, 128, 24),       # six feature tiles: the first two take token blocks 6 and 7 too
+]
+
+
+@pytest.mark.parametrize("case", PAGED_WIDE_CASES, ids=lambda c: "n%d_new%d_n%d_new%d_dm%d_hkv%d_d%d_r%d" % (c[0][0], c[1][0], c[0][1], c[1][1], *c[2:]))
+def test_append_wide_tiles_on_paged_caches(case):
+    """The rows of K, V and L land in their blocks, and every other byte of the pools stays what it was."""
+    lens, n_new, d_model, hkv, d, r = case
+    blocks = [(n + 15) // 16 for n in lens]
+    gen = torch.Generator().manual_seed(6500 + lens[0])
+    num_blocks = sum(blocks) + 3
+    perm = torch.randperm(num_blocks, generator=gen).to(torch.int32)
+    table = torch.full((2, max(blocks)), -1, dtype=torch.int32)
+    table[0, :blocks[0]], table[1, :blocks[1]] = perm[:blocks[0]], perm[blocks[0]:sum(blocks)]
+    pools = [torch.randn(num_blocks, hkv, 16, d, generator=gen).to(torch.bfloat16) for _ in range(2)]
+    pools.append(torch.randn(num_blocks, 16, r, generator=gen).to(torch.bfloat16))
+    kd, vd, ld = (t.to(DEV) for t in pools)
+    shape = lra.make_shape(torch.empty(1, hkv, d, dtype=torch.bfloat16, device=DEV), hkv, r, 0.0)
+    lens_d, table_d = torch.tensor(lens, dtype=torch.int32, device=DEV), table.to(DEV)  # (the cache holds addresses only)
+    cache = lra.make_cache(kd, vd, ld, lens_d, max(lens), table_d)
+    f = lambda t: t.to(torch.float64).cpu().numpy()
+    exp = [f(t).copy() for t in pools]
+    prev_t, prev_k = lra.lra_set_append_tile(256), lra.lra_set_append_skinny(0)
+    try:
+        for s in range(2):
+            x, w = _inputs(6600 + s, n_new[s], d_model, hkv, d, r)
+            lra.lra_cache_append(shape, cache, w.to(DEV), 10000.0, x.to(DEV), s)
+            torch.cuda.synchronize()
+            first = lens[s] - n_new[s]
+            refs = oracle.project_new_tokens(f(x), f(w), hkv, d, r, np.arange(first, lens[s]), 10000.0)
+            ids = table[s, :blocks[s]].numpy()
+            got = [oracle.gather_paged(f(kd), ids, lens[s])[first:], oracle.gather_paged(f(vd), ids, lens[s])[first:],
+                   oracle.lra_oracle.gather_paged_l(f(ld), ids, lens[s])[first:]]
+            for name, g, ref in zip("KVL", got, refs):
+                _gate(g, ref, f"paged {name} rows seq {s}")
+            oracle.scatter_paged(exp[0], ids, first, got[0])
+            oracle.scatter_paged(exp[1], ids, first, got[1])
+            oracle.scatter_paged_l(exp[2], ids, first, got[2])
+            for t, e in zip((kd, vd, ld), exp):
+                np.testing.assert_array_equal(f(t), e)
+    finally:
+        lra.lra_set_append_tile(prev_t)
+        lra.lra_set_append_skinny(prev_k)
 
 
 def test_append_rejects_what_it_cannot_do():

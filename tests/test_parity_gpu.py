@@ -276,7 +276,8 @@ def test_prefill_holds_the_low_rank_sums_in_fp32_until_the_output(d, r, paged, s
         table = torch.arange(blocks, dtype=torch.int32, device=DEV)[None].contiguous()
     q = w.q.to(DEV)
     shape = lra.make_shape(q, 2, r, w.scale)
-    cache = lra.make_cache(k, v, l, torch.tensor([n], dtype=torch.int32, device=DEV), n, table)
+    lens = torch.tensor([n], dtype=torch.int32, device=DEV)
+    cache = lra.make_cache(k, v, l, lens, n, table)
     out = torch.full_like(q, float("nan"))
     old = lra.lra_set_prefill_splits(splits)
     try:
@@ -291,31 +292,41 @@ def test_prefill_holds_the_low_rank_sums_in_fp32_until_the_output(d, r, paged, s
     assert rel <= 1e-2
 
 
-def test_short_prefill_on_paged_cache_value_only():
-    """Split-KV prefill of 5 new tokens on a paged, ragged cache without B_K."""
+@pytest.mark.parametrize("seq,n_new,path", [(0, 5, "split_kv"), (1, 16, "split_kv"), (2, 9, "split_kv"), (0, 1, "default"),
+                                            (1, 4, "default"), (2, 3, "default"), (1, 16, "default")])
+def test_short_prefill_on_paged_cache_value_only(seq, n_new, path):
+    """Prefill of a few new tokens on a paged, ragged cache without B_K: the split-KV kernel, asked for or (up to 4
+    tokens at a group of 4) by itself, and the tile walk that takes 16 tokens by itself."""
     w = W.make_paged("paged_short_prefill", seed=92, seq_lens=[40, 333, 1500], agents_per_seq=1, n_adapters=3,
                      n_q_heads=8, n_kv_heads=2, head_dim=128, rank=16, d_model=None, b_std=0.05)
     import oracle
     f = lambda t: t.to(torch.float64).numpy()
-    for seq, n_new in [(0, 5), (1, 16), (2, 9)]:
-        gen = torch.Generator().manual_seed(600 + seq)
-        q = torch.randn(n_new, 8, 128, generator=gen).to(torch.bfloat16)
-        adapter = seq % 3
-        dw = DeviceWorkload(w, DEV)
-        qd = q.to(DEV)
-        out = torch.full_like(qd, float("nan"))
-        ws_bytes = lra.lra_workspace_bytes(dw.shape, dw.cache, 1, 1, n_new)
-        assert ws_bytes > 0
-        ws = torch.empty(ws_bytes, dtype=torch.uint8, device=DEV)
+    gen = torch.Generator().manual_seed(600 + seq)
+    q = torch.randn(n_new, 8, 128, generator=gen).to(torch.bfloat16)
+    adapter = seq % 3
+    dw = DeviceWorkload(w, DEV)
+    qd = q.to(DEV)
+    out = torch.full_like(qd, float("nan"))
+    need = lambda: lra.lra_workspace_bytes(dw.shape, dw.cache, 1, 1, n_new)
+    old = lra.lra_set_short_prefill(64)
+    try:
+        split_kv = need()
+        lra.lra_set_short_prefill(0)
+        assert need() != split_kv  # (the two paths are told apart by the workspace they ask for)
+        lra.lra_set_short_prefill(64 if path == "split_kv" else old)
+        assert (need() == split_kv) == (n_new < 16 or path == "split_kv") and need() > 0
+        ws = torch.empty(need(), dtype=torch.uint8, device=DEV)
         lra.lra_attn_prefill(dw.shape, dw.cache, None, dw.b_v, w.n_adapters, qd, seq, adapter, out, ws)
         torch.cuda.synchronize()
-        n_t = w.seq_lens[seq]
-        ids = w.block_table[seq].numpy()
-        kb = oracle.gather_paged(f(w.k_base), ids, n_t)
-        vb = oracle.gather_paged(f(w.v_base), ids, n_t)
-        lr = oracle.lra_oracle.gather_paged_l(f(w.l), ids, n_t)
-        ref = oracle.prefill(f(q), kb, vb, lr, np.zeros_like(f(w.b_k[adapter])), f(w.b_v[adapter]), n=n_t, scale=w.scale)
-        _gate(out.to(torch.float64).cpu().numpy(), ref, label=f"paged short prefill seq {seq} n_new {n_new}")
+    finally:
+        lra.lra_set_short_prefill(old)
+    n_t = w.seq_lens[seq]
+    ids = w.block_table[seq].numpy()
+    kb = oracle.gather_paged(f(w.k_base), ids, n_t)
+    vb = oracle.gather_paged(f(w.v_base), ids, n_t)
+    lr = oracle.lra_oracle.gather_paged_l(f(w.l), ids, n_t)
+    ref = oracle.prefill(f(q), kb, vb, lr, np.zeros_like(f(w.b_k[adapter])), f(w.b_v[adapter]), n=n_t, scale=w.scale)
+    _gate(out.to(torch.float64).cpu().numpy(), ref, label=f"paged short prefill seq {seq} n_new {n_new}")
 
 
 @pytest.mark.parametrize("seq,n_new", [(0, 1), (1, 77), (2, 300), (3, 1027)])
@@ -346,28 +357,38 @@ def test_prefill_on_paged_cache(variant, seq, n_new):
     _gate(out.to(torch.float64).cpu().numpy(), ref, label=f"paged prefill seq {seq} n_new {n_new}")
 
 
-@pytest.mark.parametrize("n_new,splits", [(40, 1), (333, 3)])
-def test_prefill_on_a_pool_beyond_two_gigabytes(n_new, splits):
+FAR_POOL_CASES = [
+    # n_new, splits, d, r, key side: with a B_K, without, rotary with the completed keys in the workspace
+    (40, 1, 128, 16, "bk"), (333, 3, 128, 16, "bk"), (40, 3, 128, 16, "none"), (333, 1, 128, 64, "none"),
+    (100, 1, 128, 32, "rotary"), (333, 2, 128, 16, "rotary"), (129, 1, 64, 64, "bk"), (65, 2, 64, 32, "none"),
+    (200, 2, 64, 64, "rotary"), (333, 2, 128, 64, "bk"), (50, 1, 64, 16, "bk"),
+]
+
+
+@pytest.mark.parametrize("n_new,splits,d,r,key_side", FAR_POOL_CASES)
+def test_prefill_on_a_pool_beyond_two_gigabytes(n_new, splits, d, r, key_side):
     """Pools within 32-bit byte offsets and larger ones take different kernels: the same blocks, once dense and once
     128 MiB apart (3.2 GB), give the same bits."""
     w = W.make_paged("far_blocks", seed=95, seq_lens=[1, 333], agents_per_seq=1, n_adapters=2, n_q_heads=8,
-                     n_kv_heads=2, head_dim=128, rank=16, d_model=None, b_std=0.05)
-    dw = DeviceWorkload(w, DEV)
-    nb, hkv, bs, d = dw.k_base.shape
+                     n_kv_heads=2, head_dim=d, rank=r, d_model=None, b_std=0.05)
+    dw = DeviceWorkload(w, DEV, key_rope_theta=500000.0 if key_side == "rotary" else 0.0)
+    b_k = None if key_side == "none" else dw.b_k
+    nb, hkv, bs, _ = dw.k_base.shape
     far = [torch.empty(nb << 26, dtype=torch.bfloat16, device=DEV).as_strided((nb, hkv, bs, d), (1 << 26, bs * d, d, 1))
            for _ in range(2)]
     far[0].copy_(dw.k_base)
     far[1].copy_(dw.v_base)
     assert nb << 27 > 1 << 31
     far_cache = lra.make_cache(far[0], far[1], dw.l, dw.seq_lens, max(w.seq_lens), dw.block_table)
-    q = torch.randn(n_new, 8, 128, generator=torch.Generator().manual_seed(96)).to(torch.bfloat16).to(DEV)
+    q = torch.randn(n_new, 8, d, generator=torch.Generator().manual_seed(96)).to(torch.bfloat16).to(DEV)
     old_s, old_t = lra.lra_set_prefill_splits(splits), lra.lra_set_short_prefill(0)
     try:
         outs = []
         for cache in (dw.cache, far_cache):
             out = torch.full_like(q, float("nan"))
-            ws = torch.empty(max(256, lra.lra_workspace_bytes(dw.shape, cache, 1, 1, n_new)), dtype=torch.uint8, device=DEV)
-            lra.lra_attn_prefill(dw.shape, cache, dw.b_k, dw.b_v, w.n_adapters, q, 1, 1, out, ws)
+            need = lra.lra_workspace_bytes(dw.shape, cache, 1, 1, n_new)
+            ws = torch.empty(max(256, need), dtype=torch.uint8, device=DEV)
+            lra.lra_attn_prefill(dw.shape, cache, b_k, dw.b_v, w.n_adapters, q, 1, 1, out, ws)
             outs.append(out)
         torch.cuda.synchronize()
     finally:

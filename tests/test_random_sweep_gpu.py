@@ -225,7 +225,8 @@ def test_append_and_base_shared_calls(block):
 @pytest.mark.parametrize("block", range(2))
 def test_prefills_on_paged_caches(block):
     """Causal prefill of the last tokens of one sequence of a paged ragged cache (NaN in the free slots), plain and
-    rotary key side, every kernel choice, from one new token (split-KV form) to a few hundred (tile-walking form)."""
+    rotary key side, every kernel choice, from one new token to a few hundred (few tokens: the split-KV or the
+    tile-walking form, by the sizes)."""
     f = lambda t: t.to(torch.float64).numpy()
     for case in range(block * BLOCK, (block + 1) * BLOCK):
         rnd = random.Random(70_000 + case)
