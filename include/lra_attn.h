@@ -220,7 +220,8 @@ typedef struct {
  *                      negative: never
  *   prefill_splits     workgroups that share the key tiles of one q tile in the tile-walking
  *                      prefill kernel (1..32; more than one ends with the merge kernel);
- *                      0 automatic (the smallest estimated time)
+ *                      0 automatic (an even division over the chip, or the smallest estimated
+ *                      time where that is clearly below)
  *   rope_key_prepass   prefill calls of the tile-walking kernel with the rotary key side
  *                      (key_rope_theta > 0 and a b_k): 0 automatic (the completed keys
  *                      K_base + RoPE(L B_K) of the call's adapter and sequence are written once
@@ -325,7 +326,7 @@ lra_status lra_attn_decode_static(const lra_shape* shape, const lra_cache* cache
  *   1 <= n_new <= max_seq_len; the device-side seq_lens[seq_index] must be >= n_new.
  *   workspace  as for lra_attn_decode; with max_seq_len below 1024 and more new tokens than the
  *              split-KV path takes a call without one (or with too small a one) is served too,
- *              by one workgroup per 128 query rows of a kv head
+ *              by one workgroup per q tile (128 query rows)
  */
 lra_status lra_attn_prefill(const lra_shape* shape, const lra_cache* cache,
                             const lra_adapters* adapters, const void* q, int32_t seq_index,

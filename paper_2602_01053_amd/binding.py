@@ -306,8 +306,8 @@ def lra_attn_decode(shape: LraShape, cache: LraCache, b_k: Optional[torch.Tensor
                     query_adapter: torch.Tensor, seq_query_start: torch.Tensor,
                     max_queries_per_seq: int, out: torch.Tensor, workspace: Optional[torch.Tensor],
                     stream=None) -> None:
-    # (marshalling is kept short: small calls issued one by one take as long on the host as on the GPU, 11.8 us per
-    # decode of a short context with two launches before, 10.0 so)
+    # (marshalling is kept short: small calls issued one by one take as long on the host as on the GPU; a decode of a
+    # short context with two launches 10.0 us, with shape tuples, a stream object and the tuning reference made anew in each call 11.8)
     ad = LraAdapters(_ptr(b_k), _ptr(b_v), int(n_adapters))
     ws_ptr, ws_bytes = (None, 0) if workspace is None else (workspace.data_ptr(), workspace.nbytes)
     byref = ctypes.byref

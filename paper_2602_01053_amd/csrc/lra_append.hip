@@ -8,8 +8,8 @@
 //
 // Four kernels, chosen by the number of new tokens (launch_append at the end of the file): a
 // matrix-vector kernel (1-2 tokens), a weight-streaming MFMA kernel (up to 64), and two tiled
-// GEMM kernels (128 features x 128 or 64 tokens per workgroup; 256 x 256 for chunks whose tiles
-// fill the chip, see wide_tiles_pay).
+// GEMM kernels (128 features x 128 or 64 tokens per workgroup; 256 x 256 for large chunks,
+// see wide_tiles_pay).
 //
 // The tiled GEMM takes the weights one output feature per row (the usual layout of a linear
 // layer) and computes transposed, Y^T[feature][token] = W[feature][:] . X[token][:], so
@@ -307,8 +307,8 @@ __global__ __launch_bounds__(NS == 2 ? 256 : 512, NS == 2 ? 2 : 1) void append_k
 }
 
 // ---------------------------------------------------------------------------------------
-// 256 features x 256 tokens per workgroup of eight waves (for chunks whose tiles fill the chip).  At
-// 128 x 128 a step moves 32 KB into LDS for 2.1 MFLOP and every MFMA costs one 1 KB LDS read: with
+// 256 features x 256 tokens per workgroup of eight waves (for chunks it is faster on, see
+// wide_tiles_pay).  At 128 x 128 a step moves 32 KB into LDS for 2.1 MFLOP and every MFMA costs one 1 KB LDS read: with
 // two workgroups per compute unit the LDS is busier than the matrix pipes.  Here a wave owns 128
 // features x 64 tokens (eight 32 x 32 accumulators), reads six operands for eight MFMAs, and a step
 // moves 64 KB for 8.4 MFLOP; the two waves of a SIMD cover each other's reads and requests.  (Four
@@ -326,8 +326,8 @@ __global__ __launch_bounds__(NS == 2 ? 256 : 512, NS == 2 ? 2 : 1) void append_k
 //
 // Workgroup -> tile: an XCD takes every eighth token tile and all feature tiles of it, one after
 // the other, so that the 32 tiles it works on at a time are 4 token tiles x 8 feature tiles.
-// Llama-3-8B projection, us before (L tiles in the grid, four waves) and now: 4096 new tokens
-// 93 and 86, 6000 130 and 101, 8192 185 and 120, 16384 301 and 239 (1.16 PFLOP/s).
+// Llama-3-8B projection, us with the L tiles in the grid and four waves, and as it is: 6000 new
+// tokens 130 and 101, 8192 185 and 120, 16384 301 and 239 (1.16 PFLOP/s).
 // ---------------------------------------------------------------------------------------
 template <int D, bool PAGED, int NLB>  // NLB: 32-row blocks the L features take (1: ranks up to 32, 2)
 __global__ __launch_bounds__(512, 2) void append_wide_kernel(AppendParams p) {
@@ -673,7 +673,7 @@ __global__ __launch_bounds__(512) void append_skinny_kernel(AppendParams p) {
 }
 
 // ---------------------------------------------------------------------------------------
-// One to four new tokens (every decode step appends one): a matrix-vector product.  One wave
+// One or two new tokens (every decode step appends one): a matrix-vector product.  One wave
 // per weight row reads it in fully coalesced 1 KB pieces, all in flight at once, and forms
 // the dot products with v_dot2c_f32_bf16; the 2 * Hkv * d + r rows make several hundred
 // workgroups, enough outstanding loads to run at HBM speed.  A workgroup's four rows are two

@@ -6,16 +6,18 @@
 //   online softmax along keys, causal mask aligned to the end of the sequence
 //   O^T[d][row]   += V_base^T[d][key] . P^T[key][row]                      (MFMA)
 //   Olr^T[p][row] += L^T[p][key]      . P^T[key][row]                      (MFMA)
-// and after the last tile O^T += B_V^T . Olr^T (one more MFMA k-step per 16 ranks),
-// O /= l.  Qt = Q B_K^T is formed once per wave before the loop (MFMA).
+// and after the last tile O^T += B_V^T . Olr^T (two more MFMA k-steps per 16 ranks: Olr, an
+// fp32 sum over all keys, enters as two bf16 terms), O /= l.  Qt = Q B_K^T is formed once per
+// wave before the loop (MFMA).
 //
-// A workgroup owns 128 query rows of one kv head (4 waves x 32 rows; a row is a new token of one
-// of the q heads that share the kv head, the q head fastest) and walks the key tiles up to its
-// causal limit.  Rows of all q heads in one tile: a tile of 128 tokens per q head was a quarter
-// full at 32 new tokens, and a call of few tokens took four workgroups to every key (333 tokens
-// on 5333, group 4: 76 -> 57 us with the shares planned for the packed tiles; 2048: unchanged).  v_mfma_f32_32x32x16_bf16 throughout; the
-// transposed score tile leaves P^T in the lanes that need it as the B operand of
-// the second product.  K_base / V_base / L tiles are shared by the four waves:
+// A workgroup owns a q tile of 128 query rows (4 waves x 32 rows) and walks the key tiles up to
+// its causal limit.  A row is a new token of one of tile_group q heads of a kv head, the q head
+// fastest: of all that share the kv head where keys are the larger part of a call (a tile of 128
+// tokens of one q head is a quarter full at 32 new tokens, and four workgroups walk every key;
+// 333 tokens on 5333, group 4: 76 us with tiles of one head, 57 with tiles of the group), of one
+// where a few tokens meet few keys (see plan_prefill_tiles).  v_mfma_f32_32x32x16_bf16
+// throughout; the transposed score tile leaves P^T in the lanes that need it as the B operand
+// of the second product.  K_base / V_base / L tiles are shared by the four waves:
 // every wave requests its quarter of the next tile straight from HBM into the
 // other LDS stage (buffer_load ... lds, swizzled by choosing which chunk each lane
 // fetches) at the top of the current tile; one wait and one barrier per tile.
