@@ -1,7 +1,8 @@
 // Body of the tile-walking prefill kernels, included inside each of them (lra_prefill_mfma.hip) with the template
 // parameters and POOL in scope.  Text rather than a function: the register allocation of the rank-64 forms, which fill
-// the register file, comes out without scratch memory for prefill_mfma_kernel only when the body stands in the kernel
-// itself, for prefill_pool_kernel only when it comes through a function.
+// the register file, comes out without scratch memory for prefill_mfma_kernel on contiguous caches only when the body
+// stands in the kernel itself (12 to 16 bytes for far paged pools), for prefill_pool_kernel only when it comes through
+// a function.
   static_assert(!(ROPE_K && HAS_BK), "the rotary key side replaces the Qt term");
   // Completed keys K_base + RoPE(L B_K) are held as fp16, whether the key pre-pass left them in the workspace
   // (KC16) or this kernel completes the tiles in LDS (ROPE_K): rounding the sum to bf16 a second time costs
