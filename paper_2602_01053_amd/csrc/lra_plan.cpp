@@ -142,6 +142,11 @@ lra_status check_common(const lra_shape* sh, const lra_cache* c) {
 // estimate is 8 % below its own: within that the two are level, and where it was followed at less it lost as often as
 // it won.  us at 1 / 2 / 4 / 5 / 6 / 8 / 12 / 16 shares, chosen one marked: 333 new tokens on 5333: 100 / 67 / 60 /
 // 57* / 66 / 62 / 72 / 79; 700 on 9000: 157 / 154 / 140* / 144 / 152 / 152 / 170 / 182.
+// A few tokens behind a context (the sizes the split-KV path takes too): the merge of their few rows costs 1.5 us and
+// 1 us per 1000 rows, a tile of its own the product with B_V, one dependent round trip per 16 ranks, 1.6 us more at
+// rank 32 and 5 at 64, and the smallest estimate is taken as it is.  Over 3100 such calls 0.4 to 1 % from the best
+// count (with the figures above 13 and 5 %); 6 tokens after 300, 8 kv heads of 128 / 64, us at 1 / 2 / 3 / 4 shares:
+// rank 16 12.8 / 12.4 / 11.4 / 11.4, rank 64 21.8 / 15.3 / 14.0 / 14.0; after 500, 64 wide, 1 and 8 shares: 13.5 / 9.1.
 // One share, and no workspace, where q tiles of 128 tokens per q head would fill two workgroups per unit.
 struct PrefillTiles {
   int tile_group;
@@ -160,19 +165,21 @@ static PrefillTiles plan_prefill_tiles(const lra_shape* sh, int tokens, int max_
   const int rank_pad = sh->rank <= 16 ? 16 : (sh->rank <= 32 ? 32 : 64);
   const double width = (sh->head_dim + 0.6 * rank_pad + 36.0) / (128 + 0.6 * 16 + 36.0);
   const double alone = 1.2 * width, beside = (q_tiles == 1 && tg == G ? 2.4 : 1.9) * width;
-  const double fixed = 1.3 + 2.3 * live / 128, merge = 5.0;
+  const double fixed = 1.3 + 2.3 * live / 128;
+  const double merge = split_kv_sized ? 1.5 + 1e-3 * tokens * sh->n_q_heads : 5.0;
+  const double own_b_v = split_kv_sized ? (rank_pad - 16) * (0.018 + 6.5e-4 * sh->head_dim) : 0.0;
   const double per_share = static_cast<double>(tokens) * sh->n_q_heads * (sh->head_dim + sh->rank) * 8.0 / 4.3e6;
   auto estimate = [&](int64_t ns) {
     const int64_t w = wgs * ns, rest = w % slots, share = (tiles + ns - 1) / ns;
     double us = static_cast<double>(w / slots) * (fixed + beside * static_cast<double>(share));
     if (rest > 0) us += fixed + (rest <= kCUs ? alone : beside) * static_cast<double>(share);
-    return ns > 1 ? us + merge + per_share * static_cast<double>(ns) : us;
+    return ns > 1 ? us + merge + per_share * static_cast<double>(ns) : us + own_b_v;
   };
   int64_t even = (slots + head_tiles - 1) / head_tiles;
   if (even > max_seq_len / (8 * 64)) even = max_seq_len / (8 * 64);
   even = even < 1 ? 1 : (even > 32 ? 32 : even);
   int64_t best = even;
-  double best_us = 0.92 * estimate(even);
+  double best_us = (split_kv_sized ? 1.0 : 0.92) * estimate(even);
   for (int64_t ns = 1; ns <= 32 && ns <= tiles; ++ns) {
     const double us = estimate(ns);
     if (us < best_us) {

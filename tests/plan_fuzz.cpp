@@ -227,6 +227,27 @@ int main(int argc, char** argv) {
     c.max_blocks_per_seq = c.num_blocks = t.paged ? (t.n + 15) / 16 : 0;
     CHECK(make_plan(&sh, &c, t.n_new, 1, true, Tuning{}).short_prefill == t.split_kv);
   }
+  // shares of a tile-walking prefill of a few tokens: about as many as were measured fastest
+  struct ShareCase { int hkv, G, d, rank, n_new, n; bool paged; int least, most; };
+  const ShareCase share_cases[] = {{8, 4, 128, 64, 6, 306, false, 3, 5}, {8, 4, 128, 16, 6, 306, false, 3, 5}, {2, 8, 128, 64, 6, 206, true, 4, 4},
+                                   {8, 4, 64, 16, 6, 506, true, 6, 8},   {4, 7, 128, 32, 10, 224, false, 3, 4}, {8, 4, 128, 16, 24, 142, false, 1, 1}};
+  for (int it = 0; it < static_cast<int>(sizeof(share_cases) / sizeof(share_cases[0])); ++it) {
+    const ShareCase& t = share_cases[it];
+    lra_shape sh{};
+    sh.n_kv_heads = t.hkv;
+    sh.n_q_heads = t.hkv * t.G;
+    sh.head_dim = t.d;
+    sh.rank = t.rank;
+    lra_cache c{};
+    c.n_seqs = 1;
+    c.max_seq_len = t.n;
+    c.kv_token_stride = c.kv_head_stride = t.d;
+    c.block_size = t.paged ? 16 : 0;
+    c.kv_block_stride = t.paged ? 16 * t.d * t.hkv : 0;
+    c.max_blocks_per_seq = c.num_blocks = t.paged ? (t.n + 15) / 16 : 0;
+    const Plan pl = make_plan(&sh, &c, t.n_new, 1, true, Tuning{});
+    CHECK(!pl.short_prefill && pl.n_splits >= t.least && pl.n_splits <= t.most);
+  }
   // the split of lra_cache_append over d_model
   for (int it = 0; it < cases; ++it) {
     const int64_t n_new = pick({1, 16, 32, 33, 64, 100, 128, 129, 512, 1000, 1024, 4096, 1 << 20, (1 << 20) + 1, INT32_MAX});
