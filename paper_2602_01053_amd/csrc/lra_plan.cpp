@@ -214,25 +214,33 @@ static bool short_prefill_walks_tiles(const lra_shape* sh, const lra_cache* c, i
   return tokens * G <= 96 || n >= (walk < 8 ? 8192 : 4096);
 }
 
-// Whether one sequence in the rotary form of the split-KV kernel runs with two workgroups per compute unit rather
-// than one: its steps are a chain of dependent products and rotations that only a second wave per SIMD covers, but
-// the partial states double.  Measured on MI355X over 810 calls, the ratio of the times with one and with two:
-// up to 64 shares (which one merge kernel takes) 0.98 to 1.43 with shares of 256 keys and more, 0.90 to 1.18 with
-// 128, there at least 1.01 up to 2048 (row, share) states; beyond 64 shares 0.71 to 1.08 with 128 and 256 keys,
-// at least 1.02 with 384 where one workgroup per unit makes more than 64 too, and where it does not 0.94 to 1.22 with
-// 512 (rank 32 the lower) and at least 1.0 with 640.  Prefills of a few tokens gain 1.05 to 1.5 from shares of 384
-// keys on (8 kv heads, 16 after 9000: 30.1 -> 26.2 us) and lose up to 13 % below (4 kv heads, 4 after 16000: 18.5 and
-// 21.3 us).
-static bool rope_pays_two_per_unit(int max_seq_len, int64_t work, int tile, int64_t rows, int rank, bool prefill) {
+// Keys per share where one sequence in the rotary form of the split-KV kernel runs with two workgroups per compute
+// unit rather than one, else 0: its steps are a chain of dependent products and rotations that only a second wave per
+// SIMD covers, but the partial states double.  Measured on MI355X over 1500 decode calls, the ratio of the times with
+// one and with two: up to 64 shares (which one merge kernel takes) 1.0 to 1.5 with shares of 384 keys and more (0.92
+// for 72 rows of a kv head on 50000); with 256 at ranks up to 16 1.04 to 1.26 where one per unit has 512, 0.94 to
+// 1.08 where it has 384, at rank 32 0.92 to 1.01; with 128 at least 1.01 up to 2048 (row, share) states; beyond 64
+// shares 0.71 to 1.08 with 128 and 256 keys, at least 1.02 with 384 where one workgroup per unit makes more than 64
+// too, and where it does not 0.94 to 1.22 with 512 (rank 32 the lower) and at least 1.0 with 640.  Prefills of a few
+// tokens gain 1.03 to 1.6 from shares of 384 keys on (8 kv heads, 16 after 9000: 30.1 -> 26.2 us; 0.94 to 0.97 at
+// three of 720 calls) and lose up to 13 % below (4 kv heads, 4 after 16000: 18.5 and 21.3 us).
+// at_once: where units x shares, rounded up, pass two per compute unit the share grows by key tiles until they fit
+// (24 units, rank 32, us with 21 shares of 13009 keys 28.7, with 22 of 13463 38.6 and with one workgroup per unit
+// 35.7; 1440 calls 1.06 in the mean, up to 1.69).  Not in decode at d = 64, where units hold more than two: 0.91 to 1.
+static int64_t rope_two_per_unit_keys(int max_seq_len, int64_t work, int tile, int64_t rows, int rank, bool prefill,
+                                      bool at_once) {
   auto share_keys = [&](int64_t wgs) {  // as the plan rounds them
     const int64_t sk = (work * max_seq_len + wgs - 1) / wgs;
     return work >= 2 * wgs || sk > max_seq_len ? (max_seq_len + int64_t{tile} - 1) / tile * tile : (sk + tile - 1) / tile * tile;
   };
   const int64_t one = (max_seq_len + share_keys(kCUs) - 1) / share_keys(kCUs);
-  const int64_t sk = share_keys(2 * kCUs), two = (max_seq_len + sk - 1) / sk;
-  if (prefill) return sk >= 384 && two <= 64;
-  if (two > 64) return sk >= (one > 64 ? 384 : (rank <= 16 ? 512 : 640));
-  return sk >= 256 || rows * two <= 2048;
+  int64_t sk = share_keys(2 * kCUs);
+  while (at_once && sk < max_seq_len && work * ((max_seq_len + sk - 1) / sk) > 2 * kCUs) sk += tile;
+  const int64_t two = (max_seq_len + sk - 1) / sk;
+  bool pays = sk >= 384 || (sk >= 256 ? rank <= 16 && share_keys(kCUs) >= 512 : rows * two <= 2048);
+  if (two > 64) pays = sk >= (one > 64 ? 384 : (rank <= 16 ? 512 : 640));
+  if (prefill) pays = sk >= 384 && two <= 64;
+  return pays ? sk : 0;
 }
 
 Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_queries_per_seq, bool prefill,
@@ -378,12 +386,15 @@ Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_quer
     // as long as a share then still has 512 keys (32768 tokens x 8 kv heads: 35.7 against 38.6 us, 65536: 49.2
     // against 53.7; at 256 keys per share the doubling loses)
     if (!batch && !prefill && c->block_size != 0 && !rope && work * c->max_seq_len >= int64_t{2} * kCUs * 512) wgs = 2 * kCUs;
-    // ... and one sequence in the rotary form at ranks up to 32 likewise (see rope_pays_two_per_unit).  Above rank 32 a
+    // ... and one sequence in the rotary form at ranks up to 32 likewise (see rope_two_per_unit_keys).  Above rank 32 a
     // unit holds one workgroup.  Nor without a B_K: nothing is rotated then, and one workgroup per unit keeps the
     // streaming form.
-    if (!batch && rope_split && key_adapter && sh->rank <= 32 && rope_pays_two_per_unit(c->max_seq_len, work, tile, pl.rows, sh->rank, prefill))
-      wgs = 2 * kCUs;
-    if (work >= 2 * wgs) {
+    const int64_t two_per_unit = !batch && rope_split && key_adapter && sh->rank <= 32
+                                     ? rope_two_per_unit_keys(c->max_seq_len, work, tile, pl.rows, sh->rank, prefill,
+                                                              prefill || sh->head_dim == 128) : 0;
+    if (two_per_unit > 0) {
+      split_keys = static_cast<int>(two_per_unit < c->max_seq_len ? two_per_unit : c->max_seq_len);
+    } else if (work >= 2 * wgs) {
       split_keys = c->max_seq_len;  // more units than workgroups wanted: one share per sequence
     } else {
       const int64_t key_heads = work * c->max_seq_len / (batch ? 2 : 1);

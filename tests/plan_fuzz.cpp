@@ -203,6 +203,24 @@ int main(int argc, char** argv) {
     if (two.split_keys == one.split_keys) continue;
     CHECK(two.short_prefill && two.split_keys >= 384 && two.n_splits <= 64);
   }
+  // ... and every workgroup of theirs finds a place at once: 8 kv heads, 9 tokens of a group of 4, three row groups
+  {
+    lra_shape sh{};
+    sh.n_kv_heads = 8;
+    sh.n_q_heads = 32;
+    sh.head_dim = 128;
+    sh.rank = 32;
+    sh.key_rope_theta = 500000.f;
+    lra_cache c{};
+    c.n_seqs = 1;
+    c.kv_token_stride = 1024;
+    c.kv_head_stride = 128;
+    for (int it = 9000; it < 21000; it += 37) {
+      c.max_seq_len = it;
+      const Plan pl = make_plan(&sh, &c, 9, 1, true, Tuning{});
+      CHECK(pl.short_prefill && pl.row_groups == 3 && pl.n_splits * 24 > 256 && pl.n_splits * 24 <= 512);
+    }
+  }
   // prefills of a few tokens: the path that was measured ahead on either side of each bound
   struct ShortCase { int hkv, G, n_new, n; bool paged, split_kv; };
   const ShortCase shorts[] = {
