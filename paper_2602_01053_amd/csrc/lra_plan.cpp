@@ -199,8 +199,13 @@ static PrefillTiles plan_prefill_tiles(const lra_shape* sh, int tokens, int max_
 //   8 kv heads, d 64   8 tokens 1.13 at 2 k, 1.0 at 9 k, 0.87 at 20 k
 //   4 kv heads, G 7    4 tokens 1.0 at 6 k, 0.97 at 9 k, paged 1.08 at 9 k, 0.95 at 14 k; 8 tokens 1.03 at 9 k, paged 1.02 at 33 k
 //   2 kv heads, G 8    8 tokens 1.08 at 2 k, 0.98 at 6 k, 0.94 at 9 k, paged 1.02 at 9 k, 0.92 at 14 k; 16 tokens 0.94 from 2 k
-//                      on, paged 1.0 at 14 k, 0.94 at 20 k; 32 tokens 0.96 at 6 k, 1.04 at 9 k
+//                      on, paged 1.0 at 14 k, 0.94 at 20 k; 20 tokens 0.92 to 0.97 from 7 k on; 32 tokens 0.96 at 6 k, 1.04 at 9 k
 //   32 kv heads, G 1   5 and 8 tokens 1.1 to 14 k, 0.81 to 0.93 at 20 k (one row group: both read the keys once)
+// Ranks above 32 cost the tile walk more, on pages most of all:
+//   4 kv heads, G 7    paged 4 and 8 tokens 1.1 at 4 k, 0.92 and 0.95 at 7 k; 12 tokens 0.98 at 7 k, 0.90 at 33 k
+//   2 kv heads, G 8    paged 8 tokens 1.07 at 4 k, 0.92 at 7 k, 0.83 at 11 k; 20 tokens 0.98 at 4 k, 0.94 at 7 k, 0.80 at 33 k; 28 tokens 1.0 to 1.13
+//   32 kv heads, G 1   paged 8 tokens 1.03 at 2 k, 0.94 at 7 k, 0.75 at 33 k
+//   8 kv heads, d 64   10 to 16 tokens 1.0 at 11 k, 0.95 at 20 k, 0.92 at 33 k
 static bool short_prefill_walks_tiles(const lra_shape* sh, const lra_cache* c, int tokens) {
   const int G = sh->n_q_heads / sh->n_kv_heads, n = c->max_seq_len;
   const int rows = tokens * (G <= 4 ? 4 : (G <= 8 ? 8 : 16));  // rows of a kv head in the split-KV kernels
@@ -209,9 +214,14 @@ static bool short_prefill_walks_tiles(const lra_shape* sh, const lra_cache* c, i
   const int units = sh->n_kv_heads * groups;
   const int walk = sh->n_kv_heads * ((tokens * G + 127) / 128);      // q tiles of the tile-walking kernel
   if (groups == 1 && walk > 8 && n > 16384) return false;
+  if (sh->rank > 32 && c->block_size != 0) {
+    if (groups == 1 && walk > 8) return n <= 3072;
+    return walk >= 8 || groups > 6 || n <= (walk < 4 || groups <= 2 ? 5120 : 9216);
+  }
+  if (sh->rank > 32 && sh->head_dim == 64 && walk <= 8 && tokens * G <= 64 && n > 14336) return false;
   if (c->block_size != 0) return n <= 12288 || !(groups == 1 ? walk < 8 : walk < 4 && groups <= 4);
   if (units <= 8) return n <= (walk < 4 ? (tokens * G <= 96 ? 3072 : 0) : (units < 8 ? 6144 : 9216));
-  return tokens * G <= 96 || n >= (walk < 8 ? 8192 : 4096);
+  return tokens * G <= 96 || (walk < 8 ? units >= 12 && n >= 8192 : n >= 4096);
 }
 
 // Keys per share where one sequence in the rotary form of the split-KV kernel runs with two workgroups per compute

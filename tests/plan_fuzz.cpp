@@ -222,26 +222,30 @@ int main(int argc, char** argv) {
     }
   }
   // prefills of a few tokens: the path that was measured ahead on either side of each bound
-  struct ShortCase { int hkv, G, n_new, n; bool paged, split_kv; };
+  struct ShortCase { int hkv, G, n_new, n; bool paged, split_kv; int rank = 16, d = 128; };
   const ShortCase shorts[] = {
       {8, 4, 4, 9004, false, true},   {8, 4, 8, 9009, false, false},  {8, 4, 8, 33008, false, true},  {8, 4, 8, 33008, true, false},
       {8, 4, 32, 2032, false, true},  {8, 4, 32, 9032, false, false}, {4, 7, 4, 6004, false, false},  {4, 7, 4, 9004, false, true},
       {4, 7, 4, 9004, true, false},   {4, 7, 4, 14004, true, true},   {4, 7, 8, 33008, true, false},  {2, 8, 8, 2008, false, false},
       {2, 8, 8, 9008, false, true},   {2, 8, 8, 9008, true, false},   {2, 8, 8, 14008, true, true},   {2, 8, 16, 2016, false, true},
-      {2, 8, 32, 6032, false, true},  {2, 8, 32, 9032, false, false}, {32, 1, 8, 14008, false, false}, {32, 1, 8, 20008, true, true}};
+      {2, 8, 32, 6032, false, true},  {2, 8, 32, 9032, false, false}, {32, 1, 8, 14008, false, false}, {32, 1, 8, 20008, true, true},
+      {2, 8, 20, 11020, false, true}, {2, 8, 20, 11020, true, false}, {2, 8, 8, 4008, true, false, 64}, {2, 8, 8, 7008, true, true, 64},
+      {2, 8, 20, 11020, true, true, 64}, {2, 8, 28, 20028, true, false, 64}, {4, 7, 8, 4008, true, false, 64}, {4, 7, 8, 11008, true, true, 64},
+      {4, 7, 12, 7012, true, false, 64}, {4, 7, 12, 20012, true, true, 48}, {4, 7, 20, 20020, true, false, 64}, {32, 1, 8, 2008, true, false, 64},
+      {32, 1, 8, 7008, true, true, 64}, {8, 4, 8, 33008, true, false, 64}, {8, 4, 12, 11012, false, false, 64, 64}, {8, 4, 12, 33012, false, true, 64, 64}};
   for (int it = 0; it < static_cast<int>(sizeof(shorts) / sizeof(shorts[0])); ++it) {
     const ShortCase& t = shorts[it];
     lra_shape sh{};
     sh.n_kv_heads = t.hkv;
     sh.n_q_heads = t.hkv * t.G;
-    sh.head_dim = 128;
-    sh.rank = 16;
+    sh.head_dim = t.d;
+    sh.rank = t.rank;
     lra_cache c{};
     c.n_seqs = 1;
     c.max_seq_len = t.n;
-    c.kv_token_stride = c.kv_head_stride = 128;
+    c.kv_token_stride = c.kv_head_stride = t.d;
     c.block_size = t.paged ? 16 : 0;
-    c.kv_block_stride = t.paged ? 16 * 128 * t.hkv : 0;
+    c.kv_block_stride = t.paged ? 16 * t.d * t.hkv : 0;
     c.max_blocks_per_seq = c.num_blocks = t.paged ? (t.n + 15) / 16 : 0;
     CHECK(make_plan(&sh, &c, t.n_new, 1, true, Tuning{}).short_prefill == t.split_kv);
   }
