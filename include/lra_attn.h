@@ -209,8 +209,9 @@ typedef struct {
  *   kernel_variant     0 automatic (MFMA kernels for bf16, vector-ALU kernels for fp32; among the
  *                      MFMA kernels, decode calls on a contiguous cache that give every compute
  *                      unit at most one workgroup take the form with two tile stages per wave and
- *                      separate prologue waves); 1 vector-ALU kernels for every dtype; 2 automatic
- *                      without that form
+ *                      separate prologue waves, and prefills that leave most of the chip idle the
+ *                      kernel whose waves divide the keys of 32 rows); 1 vector-ALU kernels for
+ *                      every dtype; 2 automatic without those two
  *   decode_split_keys  keys per workgroup in decode (the flash-decoding split size), rounded up
  *                      to the kernel's key tile; 0 automatic
  *   short_prefill      bf16 prefill calls with at most this many new tokens (and a context at

@@ -253,6 +253,47 @@ static int64_t rope_two_per_unit_keys(int max_seq_len, int64_t work, int tile, i
   return pays ? sk : 0;
 }
 
+// Whether a prefill runs on the kernel whose waves divide the keys of a workgroup's 32 rows (prefill_rows_kernel): one
+// kernel without a workspace, workgroups a quarter the size of a q tile.  It reads ranks up to 32, and a cache within
+// 32-bit byte offsets of one resource; the completed keys of a rotary call (`keys_ready`: the call has room for them).
+//
+// A workgroup has a compute unit to itself and takes 256 keys per 1.35 us (the way from L2 into LDS), about 7 us
+// outside its loop; the tile walk it replaces takes 15 to 20 us for anything that small but walks a long context with
+// fewer reads.  The line, from 1000 measured calls (8, 4 and 2 kv heads of group 4, 7 and 8, 32 of group 1, d = 64 and
+// 128, ranks 8 to 32, with and without pages; ratio of the times before / here):
+//   one round of the chip (w <= 256 workgroups): steps of 256 keys up to w / 8; 1.0 to 2.0, on the line itself 0.9 to
+//     1.1 (llama shape, 62 tokens on 525 keys 17.2 -> 9.9 us, 104 on 627 21.8 -> 10.7, 198 on 2199 31.4 -> 20.4; beyond
+//     the line 78 on 4395 0.82, 43 on 5802 0.80).  Above 16 kv heads the keys come from memory rather than from L2: w / 12.
+//   two rounds: from 3 steps on 1.0 to 1.8, with up to 8 steps whatever w, up to 20 with a second round half full (399
+//     tokens on 1270: 1.27; 264 on 3762 with 264 workgroups 0.89); at 512 keys and less 0.92 to 1.2, below 1 at rank 16
+//     under 320 workgroups.
+//   three rounds and more: 0.7 to 1.2, mostly below 1.
+//   calls of the size the split-KV path takes, two launches and 8.5 to 9.5 us of GPU time there: 512 keys 0.95 to 1.4,
+//     768 with two and three row tiles per kv head 1.0 to 1.3, 1024 from four on 1.07 to 1.4.
+static bool prefill_waves_divide_keys(const lra_shape* sh, const lra_cache* c, int tokens, bool split_kv_sized, bool keys_ready) {
+  if (sh->rank > 32 || sh->rank % 8 != 0) return false;
+  const bool rope = sh->key_rope_theta > 0.f;
+  if (rope && (split_kv_sized || !keys_ready)) return false;
+  const int64_t lim = 0x7ffff000 / 2;  // elements
+  const int64_t l_pitch = c->l_row_stride ? c->l_row_stride : sh->rank;
+  if (c->block_size == 0) {
+    if (c->max_seq_len * c->kv_token_stride > lim || c->max_seq_len * l_pitch > lim) return false;
+  } else {
+    const int64_t blocks = c->num_blocks > c->max_blocks_per_seq ? c->num_blocks : c->max_blocks_per_seq;
+    if (c->kv_block_stride > lim / blocks || c->kv_head_stride > lim / sh->n_kv_heads ||
+        blocks * c->kv_block_stride + sh->n_kv_heads * c->kv_head_stride + 16 * c->kv_token_stride > lim ||
+        l_pitch > lim / (blocks * 16))
+      return false;
+  }
+  const int64_t G = sh->n_q_heads / sh->n_kv_heads, tiles = (tokens * G + 31) / 32;
+  const int64_t w = tiles * sh->n_kv_heads, steps = (static_cast<int64_t>(c->max_seq_len) + 255) / 256;
+  if (split_kv_sized) return steps <= (tiles == 1 ? 2 : (tiles <= 3 ? 3 : 4)) && w <= kCUs;
+  if (w <= kCUs) return steps <= 4 || steps * (sh->n_kv_heads > 16 ? 12 : 8) <= w;
+  if (w > 2 * kCUs) return false;
+  if (steps <= 2) return w >= 320 || sh->rank > 16;
+  return steps <= 8 || (w >= 384 && steps <= 20);
+}
+
 Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_queries_per_seq, bool prefill,
                const Tuning& tune, bool key_adapter) {
   Plan pl{};
@@ -296,6 +337,23 @@ Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_quer
   pl.short_prefill = prefill && pl.mfma && tokens <= tune.short_prefill &&
                      static_cast<int64_t>(tokens) * 4 <= c->max_seq_len &&
                      (tune.short_prefill > 32 || rope || !short_prefill_walks_tiles(sh, c, tokens));
+  // completed keys of a rotary prefill, in the layout of K_base (whether or not the call has a B_K); caches beyond 4 GB
+  // keep completing tiles inside the kernel.  Paged caches: the blocks of the call's sequence in logical order, with
+  // the strides of the pool.
+  int64_t kc_span = -1;  // elements; -1: no pre-pass
+  if (rope && tune.rope_key_prepass) {
+    if (c->block_size == 0)
+      kc_span = (static_cast<int64_t>(c->max_seq_len) - 1) * c->kv_token_stride +
+                (static_cast<int64_t>(sh->n_kv_heads) - 1) * c->kv_head_stride + sh->head_dim;
+    else if (c->kv_block_stride <= (int64_t{1} << 31))  // (keeps the product below inside int64)
+      kc_span = (static_cast<int64_t>(c->max_seq_len) - 1) / 16 * c->kv_block_stride +
+                (static_cast<int64_t>(sh->n_kv_heads) - 1) * c->kv_head_stride + 15 * c->kv_token_stride + sh->head_dim;
+    if (kc_span > (int64_t{1} << 31)) kc_span = -1;
+  }
+  const bool split_kv_sized = tokens <= tune.short_prefill && static_cast<int64_t>(tokens) * 4 <= c->max_seq_len;
+  // (The rest of the plan is that of the kernel which would run without it: a call needs the same workspace either way.)
+  pl.wave_rows = prefill && pl.mfma && tune.variant == 0 && tune.prefill_splits == 0 && tune.short_prefill <= 32 &&
+                 prefill_waves_divide_keys(sh, c, tokens, split_kv_sized, kc_span >= 0);
   const bool rope_split = rope && pl.mfma && (!prefill || pl.short_prefill);  // rotary form of the split-KV kernel
   if (prefill && pl.mfma && !pl.short_prefill) {
     // Tile-walking kernel: one workgroup per q tile (see plan_prefill_tiles).  Where those do not fill the chip the
@@ -305,7 +363,6 @@ Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_quer
     pl.group_pad = pl.row_tiles = pl.row_groups = 1;
     pl.split_keys = c->max_seq_len;
     // (few tokens on a long context reach this place only where the packed tile was measured ahead of the split-KV path)
-    const bool split_kv_sized = tokens <= tune.short_prefill && static_cast<int64_t>(tokens) * 4 <= c->max_seq_len;
     const PrefillTiles pt = plan_prefill_tiles(sh, tokens, c->max_seq_len, split_kv_sized);
     pl.tile_group = tune.prefill_splits > 0 ? G : pt.tile_group;
     int64_t ns = tune.prefill_splits > 0 ? tune.prefill_splits : (tune.prefill_splits < 0 ? 1 : pt.shares);
@@ -325,22 +382,10 @@ Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_quer
     }
     pl.off_qt = pl.bytes;
     pl.bytes_without_kc = pl.bytes;
-    if (rope && tune.rope_key_prepass) {
-      // room for the completed keys of the call's adapter, in the layout of K_base (whether or
-      // not the call has a B_K); caches beyond 4 GB keep completing tiles inside the kernel.
-      // Paged caches: the blocks of the call's sequence in logical order, with the strides of the pool.
-      int64_t span = -1;  // elements; -1: no pre-pass
-      if (c->block_size == 0)
-        span = (static_cast<int64_t>(c->max_seq_len) - 1) * c->kv_token_stride +
-               (static_cast<int64_t>(sh->n_kv_heads) - 1) * c->kv_head_stride + sh->head_dim;
-      else if (c->kv_block_stride <= (int64_t{1} << 31))  // (keeps the product below inside int64)
-        span = (static_cast<int64_t>(c->max_seq_len) - 1) / 16 * c->kv_block_stride +
-               (static_cast<int64_t>(sh->n_kv_heads) - 1) * c->kv_head_stride + 15 * c->kv_token_stride + sh->head_dim;
-      if (span >= 0 && span <= (int64_t{1} << 31)) {
-        pl.off_kc = pl.bytes;
-        pl.kc_bytes = align_up(static_cast<size_t>(span) * 2, 256);
-        pl.bytes += pl.kc_bytes;
-      }
+    if (kc_span >= 0) {
+      pl.off_kc = pl.bytes;
+      pl.kc_bytes = align_up(static_cast<size_t>(kc_span) * 2, 256);
+      pl.bytes += pl.kc_bytes;
     }
     pl.launchable = true;  // at most 32 shares in y
     return pl;

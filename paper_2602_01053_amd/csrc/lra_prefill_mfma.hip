@@ -60,13 +60,6 @@ __global__ __launch_bounds__(256, 2) void prefill_pool_kernel(Params p) {
   prefill_pool_tiles<D, RP, HAS_BK, SPLIT, KC16>(p);
 }
 
-// K_base and V_base pools (and completed keys at logical block indices) within 32-bit byte offsets of one resource.
-static bool prefill_pool_fits(const Params& p) {
-  const int64_t blocks = p.num_blocks > p.max_blocks_per_seq ? p.num_blocks : p.max_blocks_per_seq;
-  const int64_t limit = kPfPoolBytes / 2;  // elements
-  return p.kv_block_stride <= limit / blocks && blocks * p.kv_block_stride + p.n_kv_heads * p.kv_head_stride + 16 * p.kv_token_stride <= limit;
-}
-
 template <int D, int RP, bool SPLIT>
 static hipError_t launch_pf2(const Params& p, dim3 grid, hipStream_t s) {
   const bool paged = p.block_size != 0, has_bk = p.b_k != nullptr;

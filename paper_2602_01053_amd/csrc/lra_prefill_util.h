@@ -96,6 +96,13 @@ typedef const __attribute__((address_space(4))) int32_t* pf_const_i32;
 constexpr uint32_t kPfOob = 0x80000000u;  // beyond any resource this kernel builds
 constexpr uint32_t kPfPoolBytes = 0x7ffff000u;  // size of the resources over a whole paged pool
 
+// K_base and V_base pools (and completed keys at logical block indices) within 32-bit byte offsets of one resource.
+inline bool prefill_pool_fits(const Params& p) {
+  const int64_t blocks = p.num_blocks > p.max_blocks_per_seq ? p.num_blocks : p.max_blocks_per_seq;
+  const int64_t limit = kPfPoolBytes / 2;  // elements
+  return p.kv_block_stride <= limit / blocks && blocks * p.kv_block_stride + p.n_kv_heads * p.kv_head_stride + 16 * p.kv_token_stride <= limit;
+}
+
 // Rotary angles.  Pair dd of a head turns by pos * theta^(-2 dd / d) radians; the kernels keep
 // that rate in revolutions (divided by 2 pi) in double precision, so that the product with a
 // position in the tens of thousands can be reduced to its fractional part without loss, and

@@ -103,6 +103,13 @@ int main(int argc, char** argv) {
         CHECK(!pl.workspace_optional || (c.max_seq_len < 1024 && pl.n_splits > 1));
         if (tune.prefill_splits > 0) CHECK(pl.tile_group == G);
       }
+      if (pl.wave_rows) {  // 32-row workgroups in at most two rounds, every byte offset within 2 GB, completed keys where a B_K is rotated
+        CHECK(prefill && pl.mfma && sh.rank <= 32 && (tokens * G + 31) / 32 * sh.n_kv_heads <= 512);
+        CHECK(!(sh.key_rope_theta > 0.f) || pl.kc_bytes > 0);
+        const int64_t pitch = c.l_row_stride ? c.l_row_stride : sh.rank, top = 0x7ffff000;
+        if (c.block_size == 0) CHECK(int64_t{c.max_seq_len} * c.kv_token_stride * 2 <= top && int64_t{c.max_seq_len} * pitch * 2 <= top);
+        else CHECK(c.max_seq_len <= 8192 && int64_t{c.num_blocks} * c.kv_block_stride * 2 <= top && int64_t{c.num_blocks} * 16 * pitch * 2 <= top);
+      }
       if (pl.kc_bytes) {  // completed keys of a rotary prefill: a copy of the K_base extent behind everything else
         CHECK(prefill && pl.mfma && !pl.short_prefill && sh.key_rope_theta > 0.f);
         CHECK(pl.off_kc >= pl.bytes_without_kc);
@@ -269,6 +276,33 @@ int main(int argc, char** argv) {
     c.max_blocks_per_seq = c.num_blocks = t.paged ? (t.n + 15) / 16 : 0;
     const Plan pl = make_plan(&sh, &c, t.n_new, 1, true, Tuning{});
     CHECK(!pl.short_prefill && pl.n_splits >= t.least && pl.n_splits <= t.most);
+  }
+  // prefills whose waves divide the keys: either side of the measured lines
+  struct WaveCase { int hkv, G, rank, n_new, n; bool waves; float theta; };
+  const WaveCase wave_cases[] = {
+      {8, 4, 16, 62, 525, true, 0.f},    {8, 4, 16, 64, 2048, true, 0.f},   {8, 4, 16, 64, 2049, false, 0.f}, {8, 4, 16, 256, 8192, true, 0.f},
+      {8, 4, 16, 256, 8193, false, 0.f}, {8, 4, 16, 257, 512, false, 0.f},  {8, 4, 24, 257, 512, true, 0.f},  {8, 4, 16, 257, 2048, true, 0.f},
+      {8, 4, 16, 257, 2049, false, 0.f}, {8, 4, 16, 512, 5120, true, 0.f},  {8, 4, 16, 513, 2000, false, 0.f}, {8, 4, 16, 8, 512, true, 0.f},
+      {8, 4, 16, 8, 513, false, 0.f},    {8, 4, 16, 9, 768, true, 0.f},     {8, 4, 16, 32, 1024, true, 0.f},  {8, 4, 16, 32, 1025, false, 0.f},
+      {8, 4, 64, 62, 525, false, 0.f},   {8, 4, 16, 62, 525, true, 1e4f},   {8, 4, 16, 8, 512, false, 1e4f},  {32, 1, 16, 64, 1280, true, 0.f},
+      {32, 1, 16, 64, 1281, false, 0.f}};
+  for (int it = 0; it < static_cast<int>(sizeof(wave_cases) / sizeof(wave_cases[0])); ++it) {
+    const WaveCase& t = wave_cases[it];
+    lra_shape sh{};
+    sh.n_kv_heads = t.hkv;
+    sh.n_q_heads = t.hkv * t.G;
+    sh.head_dim = 128;
+    sh.rank = t.rank;
+    sh.key_rope_theta = t.theta;
+    lra_cache c{};
+    c.n_seqs = 1;
+    c.max_seq_len = t.n;
+    c.kv_token_stride = t.hkv * 128;
+    c.kv_head_stride = 128;
+    CHECK(make_plan(&sh, &c, t.n_new, 1, true, resolve_tuning(nullptr)).wave_rows == t.waves);
+    lra_tuning forced{};
+    forced.kernel_variant = 2;
+    CHECK(!make_plan(&sh, &c, t.n_new, 1, true, resolve_tuning(&forced)).wave_rows);
   }
   // the split of lra_cache_append over d_model
   for (int it = 0; it < cases; ++it) {

@@ -235,6 +235,71 @@ def test_prefill_tiles_of_one_head_or_of_a_group(case):
     _gate(run_prefill(w, DEV), oracle_prefill(w), label=str(case))
 
 
+WAVE_CASES = [
+    # n, n_new, Hq, Hkv, d, r, paged, key side: 32 rows per workgroup, 32-key tiles dealt to eight waves
+    (1, 1, 4, 4, 128, 16, False, "bk"),        # one key: seven waves without a tile
+    (31, 31, 4, 1, 64, 8, True, "bk"),         # one tile, no old context
+    (32, 8, 8, 2, 128, 24, False, "bk"),       # a full tile, exactly 32 rows
+    (33, 9, 8, 2, 128, 32, True, "none"),      # two tiles, 36 rows: four in the second workgroup
+    (255, 40, 14, 2, 128, 16, False, "none"),  # group of 7; the last tile one key short
+    (256, 33, 9, 3, 64, 32, True, "bk"),       # group of 3; a tile for every wave
+    (257, 65, 16, 1, 128, 8, True, "bk"),      # group of 16; one wave takes a second tile of one key
+    (513, 150, 3, 3, 128, 16, True, "rotary"),
+    (700, 64, 8, 2, 64, 16, False, "rotary"),
+    (1500, 90, 28, 4, 128, 32, False, "bk"),
+    (8192, 512, 16, 2, 64, 8, True, "none"),   # 32 tiles per wave, all that its block ids reach
+    (600, 500, 16, 4, 128, 24, False, "bk"),   # two rounds of workgroups
+]
+
+
+@pytest.mark.parametrize("case", WAVE_CASES, ids=lambda c: "n%d_new%d_hq%d_hkv%d_d%d_r%d_paged%d_%s" % c)
+def test_prefill_whose_waves_divide_the_keys(case):
+    """Against the oracle, twice with the same bits; the workspace, without completed keys in it, is left alone (partial
+    states would mean another kernel ran), and the kernels of variant 2 pass the same bar."""
+    n, n_new, hq, hkv, d, r, paged, side = case
+    theta = 500000.0 if side == "rotary" else 0.0
+    w = W.make_contiguous("waves", "prefill", seed=4700 + n + n_new, n_agents=1, n_q_heads=hq, n_kv_heads=hkv,
+                          head_dim=d, rank=r, n=n, n_new=n_new, d_model=None, b_std=0.05)
+    k, v, l, table = w.k_base.to(DEV), w.v_base.to(DEV), w.l.to(DEV), None
+    if paged:
+        blocks = (n + 15) // 16
+        order = torch.randperm(blocks + 3, generator=torch.Generator().manual_seed(n))[:blocks]
+        def pool(t, lead):  # [n][...] -> [blocks][lead][16][...], NaN in the free slots
+            out = torch.full((blocks + 3, 16, *t.shape[1:]), float("nan"), dtype=t.dtype)
+            pad = torch.full((blocks * 16, *t.shape[1:]), float("nan"), dtype=t.dtype)
+            pad[:n] = t
+            out[order] = pad.view(blocks, 16, *t.shape[1:])
+            return (out.transpose(1, 2).contiguous() if lead else out).to(DEV)
+        k, v, l = pool(w.k_base, True), pool(w.v_base, True), pool(w.l, False)
+        table = order.to(torch.int32).view(1, -1).to(DEV)
+    lens = torch.tensor([n], dtype=torch.int32, device=DEV)
+    cache = lra.make_cache(k, v, l, lens, n, table)
+    q = w.q.to(DEV)
+    shape = lra.make_shape(q, hkv, r, 0.0, theta)
+    b_k = None if side == "none" else w.b_k.to(DEV)
+    b_v = w.b_v.to(DEV)
+    outs = []
+    for variant in (0, 0, 2):
+        old = lra.lra_set_kernel_variant(variant)
+        try:
+            need = lra.lra_workspace_bytes(shape, cache, 1, 1, n_new)
+            ws = torch.full((max(need, 256),), 0xA5 + len(outs), dtype=torch.uint8, device=DEV)
+            out = torch.full_like(q, float("nan"))
+            lra.lra_attn_prefill(shape, cache, b_k, b_v, w.n_adapters, q, 0, 0, out, ws)
+            torch.cuda.synchronize()
+            assert variant != 0 or side == "rotary" or bool((ws == 0xA5 + len(outs)).all())
+            outs.append(out)
+        finally:
+            lra.lra_set_kernel_variant(old)
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+    import oracle
+    f = lambda t: t.to(torch.float64).numpy()
+    bk0 = np.zeros_like(f(w.b_k[0])) if side == "none" else f(w.b_k[0])
+    ref = oracle.prefill(f(w.q), f(w.k_base), f(w.v_base), f(w.l), bk0, f(w.b_v[0]), n=n, scale=w.scale, key_rope_theta=theta)
+    for out in outs[1:]:
+        _gate(out.to(torch.float64).cpu().numpy(), ref, label=str(case))
+
+
 @pytest.mark.parametrize("n,n_new", [(417, 84), (1023, 300)])
 def test_short_sequence_prefill_with_and_without_a_workspace(n, n_new):
     w = W.make_contiguous("short_sequence", "prefill", seed=4700 + n, n_agents=1, n_q_heads=8, n_kv_heads=2,
