@@ -174,9 +174,10 @@ typedef struct {
                                   believes seq_lens holds.  Read during the call, never after it
                                   returns, and used for launch planning only: the decode of a
                                   batch sizes its key shares so that the workgroups that find
-                                  keys fill the compute units once (sequences of about equal
-                                  length) or just under twice (ragged lengths); without it a
-                                  batch is taken to be half as long on average as max_seq_len.
+                                  keys fill the compute units once (or, beyond 64 sequences of
+                                  ragged lengths, just under twice); without it the shares of
+                                  up to 64 sequences are sized on the device, and a larger batch
+                                  is taken to be half as long on average as max_seq_len.
                                   The results do
                                   not depend on it; entries outside [0, max_seq_len] are clamped.
                                   Key shares only grow with it, so a workspace sized with NULL

@@ -12,7 +12,7 @@ LIB_PATH = os.path.join(PKG_DIR, "liblra_attn.so")
 # what the compiler reports per kernel (registers, scratch, LDS, occupancy), written by every build
 RESOURCES_PATH = os.path.join(PKG_DIR, "kernel_resources.json")
 
-SOURCES = ["lra_plan.cpp", "lra_api.hip", "lra_generic.hip", "lra_decode_mfma.hip", "lra_decode_stream.hip", "lra_prefill_mfma.hip", "lra_prefill_rows.hip", "lra_append.hip", "lra_probe.hip"]
+SOURCES = ["lra_plan.cpp", "lra_api.hip", "lra_generic.hip", "lra_decode_mfma.hip", "lra_decode_batch.hip", "lra_decode_stream.hip", "lra_prefill_mfma.hip", "lra_prefill_rows.hip", "lra_append.hip", "lra_probe.hip"]
 
 HIPCC_FLAGS = [
     "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",

@@ -150,7 +150,13 @@ static lra_status decode_call(const lra_shape* shape, const lra_cache* cache, co
   p.is_prefill = 0;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool bf16 = shape->dtype == LRA_BF16;
-  if (pl.mfma) {
+  if (pl.batch_wgs > 0) {
+    p.n_splits = pl.batch_splits;
+    p.batch_wgs = pl.batch_wgs;
+    p.batch_tiles = pl.batch_tiles;
+    p.batch_min_tiles = pl.batch_min_tiles;
+    if (launch_decode_batch(p, pl.row_tiles, s) != hipSuccess) return LRA_ERR_HIP;
+  } else if (pl.mfma) {
     if (launch_decode_mfma(p, pl.row_tiles, tune.variant != 2, tune.main_kernel_only, s) != hipSuccess) return LRA_ERR_HIP;
   } else {
     if (launch_generic_partials(p, bf16, pl.rows, s) != hipSuccess) return LRA_ERR_HIP;

@@ -53,6 +53,8 @@ struct Params {
   // round of 256 workgroups, and 65536 / tile_group rounded up.  (Last: among the fields above they moved the decode
   // kernels' scalar loads of the block apart, 0.11 us a call: 8192 tokens 11.30 and 11.41 us.)
   int32_t tile_group, tile_heads, tiles_per_round, row_mul;
+  // decode_batch_kernel: workgroups per (kv head, row group), 128-key tiles of a share (0: from the lengths), their least
+  int32_t batch_wgs, batch_tiles, batch_min_tiles;
 #ifdef LRA_TIMING
   unsigned long long* timing;  // instrumented test build only: per-wave phase stamps
 #endif
@@ -112,6 +114,7 @@ __device__ __forceinline__ int64_t l_offset(const Params& p, int t, int j, int a
 hipError_t launch_generic_partials(const Params& p, bool is_bf16, int rows, hipStream_t s);
 hipError_t launch_merge(const Params& p, bool is_bf16, int rows, hipStream_t s);
 hipError_t launch_decode_mfma(const Params& p, int row_tiles, bool allow_stream_form, bool main_kernel_only, hipStream_t s);
+hipError_t launch_decode_batch(const Params& p, int row_tiles, hipStream_t s);
 bool decode_stream_applies(const Params& p, int row_tiles, int n_cus);
 hipError_t launch_decode_stream(const Params& p, int row_tiles, bool main_kernel_only, hipStream_t s);
 hipError_t launch_prefill_mfma(const Params& p, hipStream_t s);

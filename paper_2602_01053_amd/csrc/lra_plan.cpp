@@ -294,6 +294,57 @@ static bool prefill_waves_divide_keys(const lra_shape* sh, const lra_cache* c, i
   return steps <= 8 || (w >= 384 && steps <= 20);
 }
 
+// Decode of a batch with the shares of all sequences in one row (decode_batch_kernel): two workgroups per compute unit
+// (one in the rotary form above rank 32), or the grid of decode_mfma_kernel where that already gives every place at most
+// one live workgroup.  Measured on 38 batches of 2 to 16 sequences, 2 k to 65 k tokens (us before / here): 16 of 4 k to 64 k,
+// 4 kv heads 176 / 162; 10 of 1 k to 6 k 41.9 / 30.0; 10 of 6 k to 8 k with a low-rank cache per adapter, two row groups
+// 67.7 / 45.6; 9 of 1 k to 4 k 30.7 / 25.1; the slowest, 4 of 4 k to 7 k with 650 workgroups before, 18.0 / 19.1.  With
+// equal lengths and 512 live workgroups the other grid is up to 4 % ahead (8 of 18 k to 21 k: 113.7 / 116.4), with several
+// row groups this one.  The rotary forms, whose steps are long against everything else, gain from three tiles on (13 of
+// 0.6 k to 2.7 k: 38.3 / 31.6) and lose up to 8 % at two.
+static void plan_batch(Plan& pl, const lra_shape* sh, const lra_cache* c, bool key_adapter) {
+  if (c->n_seqs > 64) return;
+  const bool rope = sh->key_rope_theta > 0.f && key_adapter;
+  if (rope && sh->head_dim == 128 && (sh->rank <= 16 || sh->rank > 32)) return;  // (built without: its registers go to scratch memory)
+  const int64_t units = static_cast<int64_t>(sh->n_kv_heads) * pl.row_groups;
+  const int64_t places = (rope && sh->rank > 32 ? kCUs : 2 * kCUs) / units;
+  if (places < c->n_seqs) return;
+  const int64_t longest = (static_cast<int64_t>(c->max_seq_len) + 127) / 128;
+  const int64_t least = (longest + pl.n_splits - 1) / pl.n_splits;
+  int64_t total = 0, live = 0;
+  auto length = [&](int t) {
+    int64_t len = c->seq_lens_host[t];
+    len = len < 0 ? 0 : (len > c->max_seq_len ? c->max_seq_len : len);
+    return len;
+  };
+  if (c->seq_lens_host != nullptr)
+    for (int t = 0; t < c->n_seqs; ++t) {
+      total += (length(t) + 127) / 128;
+      live += (length(t) + pl.split_keys - 1) / pl.split_keys;
+    }
+  int64_t size = 0;
+  if (total > 0) {
+    if (pl.row_groups == 1 && live * units <= 2 * kCUs) return;
+    size = (total + places - 1) / places;
+    size = size < least ? least : size;
+    auto shares = [&]() {
+      int64_t n = 0;
+      for (int t = 0; t < c->n_seqs; ++t) {
+        const int64_t tiles = (length(t) + 127) / 128;
+        n += tiles > 0 ? (tiles + size - 1) / size : 1;
+      }
+      return n;
+    };
+    while (shares() > places) ++size;  // (at most n_seqs <= places shares with size = longest)
+  }
+  if (rope && (total > 0 ? size : longest * c->n_seqs / (2 * places)) < 3) return;
+  pl.batch_wgs = static_cast<int>(places);
+  pl.batch_tiles = static_cast<int>(size);
+  pl.batch_min_tiles = static_cast<int>(least);
+  const int64_t states = size > 0 ? (longest + size - 1) / size : pl.n_splits;
+  pl.batch_splits = static_cast<int>(states < pl.n_splits ? states : pl.n_splits);
+}
+
 Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_queries_per_seq, bool prefill,
                const Tuning& tune, bool key_adapter) {
   Plan pl{};
@@ -541,6 +592,8 @@ Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_quer
   if (!pl.mfma) pl.l_block = 0;
   pl.split_keys = split_keys;
   pl.n_splits = static_cast<int>((static_cast<int64_t>(c->max_seq_len) + split_keys - 1) / split_keys);
+  if (pl.mfma && !prefill && c->block_size != 0 && c->n_seqs > 1 && tune.variant == 0 && tune.split_keys <= 0)
+    plan_batch(pl, sh, c, key_adapter);
   // grids: (kv head, share, sequence x row group) for the MFMA kernels, (row, share) otherwise
   pl.launchable = pl.n_splits <= 65535 &&
                   (!pl.mfma || static_cast<int64_t>(n_seqs_eff) * pl.row_groups <= 65535);

@@ -38,6 +38,9 @@ struct Plan {
   int tile_group;  // tile-walking prefill: q heads whose rows share a q tile (all of a kv head's, or one)
   int group_pad, row_tiles, row_groups;  // MFMA decode row packing
   int l_block;     // split-KV MFMA kernels with per-adapter low-rank caches: padded rank of one slot's column block, else 0
+  // decode of a batch by decode_batch_kernel (batch_wgs > 0, else decode_mfma_kernel): workgroups per (kv head, row group),
+  // 128-key tiles of a share to begin with (0: from the lengths on the device) and at least, partial states per row
+  int batch_wgs, batch_tiles, batch_min_tiles, batch_splits;
   bool workspace_optional;  // prefill: without room for the plan's workspace the call runs with one share per q tile
   bool launchable;  // false: a grid dimension would exceed the limit of 65535 in y or z (LRA_ERR_UNSUPPORTED)
   size_t off_ml, off_o, off_lr, off_adapter, off_qt, qt_bytes, bytes;

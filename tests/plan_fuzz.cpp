@@ -110,6 +110,13 @@ int main(int argc, char** argv) {
         if (c.block_size == 0) CHECK(int64_t{c.max_seq_len} * c.kv_token_stride * 2 <= top && int64_t{c.max_seq_len} * pitch * 2 <= top);
         else CHECK(c.max_seq_len <= 8192 && int64_t{c.num_blocks} * c.kv_block_stride * 2 <= top && int64_t{c.num_blocks} * 16 * pitch * 2 <= top);
       }
+      if (pl.batch_wgs) {  // a batch's shares in one row: a place for every sequence, every state inside the workspace's slots
+        CHECK(!prefill && pl.mfma && c.block_size != 0 && c.n_seqs > 1 && c.n_seqs <= 64 && pl.batch_wgs >= c.n_seqs);
+        CHECK(static_cast<int64_t>(pl.batch_wgs) * sh.n_kv_heads * pl.row_groups <= 512);
+        CHECK(pl.batch_splits >= 1 && pl.batch_splits <= pl.n_splits && pl.batch_min_tiles >= 1);
+        const int64_t size = pl.batch_tiles > 0 ? pl.batch_tiles : pl.batch_min_tiles;
+        CHECK(size >= pl.batch_min_tiles && size * 128 * pl.batch_splits >= c.max_seq_len);
+      }
       if (pl.kc_bytes) {  // completed keys of a rotary prefill: a copy of the K_base extent behind everything else
         CHECK(prefill && pl.mfma && !pl.short_prefill && sh.key_rope_theta > 0.f);
         CHECK(pl.off_kc >= pl.bytes_without_kc);
@@ -276,6 +283,44 @@ int main(int argc, char** argv) {
     c.max_blocks_per_seq = c.num_blocks = t.paged ? (t.n + 15) / 16 : 0;
     const Plan pl = make_plan(&sh, &c, t.n_new, 1, true, Tuning{});
     CHECK(!pl.short_prefill && pl.n_splits >= t.least && pl.n_splits <= t.most);
+  }
+  // batches with known lengths: shares in one row unless the other grid has a live workgroup per place
+  struct BatchCase { std::vector<int32_t> lens; int hkv, G, queries; bool row; float theta; };
+  const BatchCase batch_cases[] = {{{65536, 4096, 30000, 9000}, 4, 7, 4, true, 0.f},  {{20000, 20000, 20000, 20000}, 8, 4, 4, false, 0.f},
+                                   {{7000, 3000, 5000, 2000}, 8, 4, 4, true, 0.f},     {{900, 300}, 8, 4, 1, false, 0.f},
+                                   {{2048, 1100, 700}, 8, 4, 4, false, 1e4f},          {{20480, 11000, 7000}, 8, 4, 4, true, 1e4f}};
+  for (int it = 0; it < static_cast<int>(sizeof(batch_cases) / sizeof(batch_cases[0])); ++it) {
+    const BatchCase& t = batch_cases[it];
+    lra_shape sh{};
+    sh.n_kv_heads = t.hkv;
+    sh.n_q_heads = t.hkv * t.G;
+    sh.head_dim = 128;
+    sh.rank = 24;
+    sh.key_rope_theta = t.theta;
+    lra_cache c{};
+    c.n_seqs = static_cast<int32_t>(t.lens.size());
+    c.block_size = 16;
+    c.kv_token_stride = 128;
+    c.kv_head_stride = 16 * 128;
+    c.kv_block_stride = 16 * 128 * t.hkv;
+    c.seq_lens_host = t.lens.data();
+    for (int32_t n : t.lens) c.max_seq_len = n > c.max_seq_len ? n : c.max_seq_len;
+    c.num_blocks = c.max_blocks_per_seq = (c.max_seq_len + 15) / 16;
+    const Plan pl = make_plan(&sh, &c, t.queries * c.n_seqs, t.queries, false, Tuning{});
+    CHECK((pl.batch_wgs > 0) == t.row);
+    if (!t.row) continue;
+    int64_t shares = 0, fewer = 0;
+    for (int32_t n : t.lens) {
+      shares += ((n + 127) / 128 + pl.batch_tiles - 1) / pl.batch_tiles;
+      if (pl.batch_tiles > 1) fewer += ((n + 127) / 128 + pl.batch_tiles - 2) / (pl.batch_tiles - 1);
+    }
+    CHECK(shares <= pl.batch_wgs && (fewer == 0 || fewer > pl.batch_wgs || pl.batch_tiles == pl.batch_min_tiles));
+    c.seq_lens_host = nullptr;
+    const Plan blind = make_plan(&sh, &c, t.queries * c.n_seqs, t.queries, false, Tuning{});
+    CHECK(blind.batch_tiles == 0 && blind.bytes >= pl.bytes);
+    Tuning other;
+    other.variant = 2;
+    CHECK(make_plan(&sh, &c, t.queries * c.n_seqs, t.queries, false, other).batch_wgs == 0);
   }
   // prefills whose waves divide the keys: either side of the measured lines
   struct WaveCase { int hkv, G, rank, n_new, n; bool waves; float theta; };

@@ -502,6 +502,58 @@ def test_one_long_sequence_in_a_paged_cache():
     _gate(run_decode(w, DEV), oracle_decode(w), label=w.name)
 
 
+BATCH_CASES = [
+    # lengths, agents, Hq, Hkv, d, r, side: the key shares of all sequences in one row, dealt to 512 workgroups
+    ([3000, 129, 128, 1, 2500], 2, 8, 2, 128, 16, "bk"),        # a tile and a key, a tile, one key; up to 24 shares
+    ([6000, 700], 5, 28, 4, 128, 32, "bk"),                     # group of 7: 40 rows, two row groups of two row tiles
+    ([5000, 40, 1900], 3, 8, 8, 64, 24, "none"),
+    ([4100, 2100, 900, 3300], 4, 16, 4, 128, 16, "own"),        # a low-rank cache per adapter
+    ([9000, 2222, 333], 3, 28, 4, 128, 32, "own"),              # ... in two row groups
+    ([9000, 500, 4000], 4, 8, 2, 128, 24, "rotary"),
+    ([7000, 900], 2, 8, 4, 64, 64, "rotary"),                   # one workgroup per compute unit
+    ([40 * (i + 3) for i in range(64)], 1, 4, 1, 64, 8, "bk"),  # a sequence in every lane
+]
+
+
+@pytest.mark.parametrize("mirror", ["exact", "none", "half", "double"])
+@pytest.mark.parametrize("case", BATCH_CASES, ids=lambda c: "s%d_a%d_hq%d_hkv%d_d%d_r%d_%s" % (len(c[0]), *c[1:]))
+def test_batch_whose_shares_stand_in_one_row(case, mirror):
+    """Ragged batches against the oracle, with the right lengths on the host, with none, and with wrong ones (shares that
+    do not fit their places are enlarged on the device); NaN in the workspace, so that a state nobody wrote would show."""
+    lens, agents, hq, hkv, d, r, side = case
+    theta = 500000.0 if side == "rotary" else 0.0
+    w = W.make_paged("batch_row", seed=4800 + sum(lens), seq_lens=lens, agents_per_seq=agents, n_adapters=max(agents, 2),
+                     n_q_heads=hq, n_kv_heads=hkv, head_dim=d, rank=r, d_model=None, b_std=0.05)
+    dev = lambda t: t.to(DEV)
+    f = lambda t: t.to(torch.float64).numpy()
+    l = w.l
+    if side == "own":  # adapter a attends over a low-rank cache of its own
+        l = torch.stack([w.l.roll(a, dims=-1) * (1 + a) for a in range(w.n_adapters)])
+    q = dev(w.q)
+    b_k = None if side == "none" else dev(w.b_k)
+    host = {"exact": lens, "none": None, "half": [n // 2 for n in lens], "double": [2 * n for n in lens]}[mirror]
+    cache_t = [dev(w.k_base), dev(w.v_base), dev(l), torch.tensor(lens, dtype=torch.int32, device=DEV), dev(w.block_table)]
+    cache = lra.make_cache(cache_t[0], cache_t[1], cache_t[2], cache_t[3], max(lens), cache_t[4], l_per_adapter=side == "own",
+                           seq_lens_host=host)
+    shape = lra.make_shape(q, hkv, r, 0.0, theta)
+    b_v, ids, start = dev(w.b_v), dev(w.query_adapter), dev(w.seq_query_start)
+    need = lra.lra_workspace_bytes(shape, cache, q.shape[0], agents)
+    out = torch.full_like(q, float("nan"))
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device=DEV)
+    lra.lra_attn_decode(shape, cache, b_k, b_v, w.n_adapters, q, ids, start, agents, out, ws)
+    torch.cuda.synchronize()
+    import oracle
+    got, ref = out.to(torch.float64).cpu().numpy(), np.empty(tuple(q.shape))
+    for i in range(q.shape[0]):  # one query at a time: its sequence's rows, its adapter's low-rank cache
+        t, a = i // agents, int(w.query_adapter[i])
+        table = w.block_table[t].numpy()
+        kb, vb = oracle.gather_paged(f(w.k_base), table, lens[t]), oracle.gather_paged(f(w.v_base), table, lens[t])
+        lr = oracle.lra_oracle.gather_paged_l(f(l[a] if side == "own" else l), table, lens[t])
+        bk = f(w.b_k[a]) if b_k is not None else np.zeros_like(f(w.b_k[a]))
+        ref[i] = oracle.prefill(f(w.q[i:i + 1]), kb, vb, lr, bk, f(w.b_v[a]), n=lens[t], scale=w.scale, key_rope_theta=theta)[0]
+    _gate(got, ref, label=f"{case} {mirror}")
+
+
 def test_uneven_queries_per_sequence(variant):
     """Sequences with 0, 1 and many queries in one call."""
     w = W.make_paged("uneven", seed=78, seq_lens=[300, 77, 129, 512], agents_per_seq=2, n_adapters=3,
