@@ -199,10 +199,11 @@ lra_status lra_attn_prefill(const lra_shape* shape, const lra_cache* cache, cons
   if (!plan_sizes_fit(shape, cache, n_new, 1)) return LRA_ERR_UNSUPPORTED;
   Tuning tune = resolve_tuning(tuning);
   Plan pl = make_plan(shape, cache, n_new, 1, true, tune, adapters->b_k != nullptr);
-  bool wave_rows = pl.wave_rows;
+  int wave_shares = pl.wave_rows ? 1 : pl.wave_shares;  // workgroups per 32 rows of prefill_rows_kernel, 0: another kernel
   if (pl.workspace_optional && (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) ||
                                 workspace_bytes < pl.bytes_without_kc)) {
     tune.prefill_splits = -1;
+    if (wave_shares > 1) wave_shares = 0;
     pl = make_plan(shape, cache, n_new, 1, true, tune, adapters->b_k != nullptr);
   }
   if (!pl.launchable) return LRA_ERR_UNSUPPORTED;
@@ -229,8 +230,8 @@ lra_status lra_attn_prefill(const lra_shape* shape, const lra_cache* cache, cons
   p.adapter_index = adapter_index;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool bf16 = shape->dtype == LRA_BF16;
-  if (shape->key_rope_theta > 0.f && adapters->b_k != nullptr && !keys_by_prepass) wave_rows = false;
-  if (pl.short_prefill && !wave_rows) {
+  if (shape->key_rope_theta > 0.f && adapters->b_k != nullptr && !keys_by_prepass) wave_shares = 0;
+  if (pl.short_prefill && wave_shares == 0) {
     if (launch_decode_mfma(p, pl.row_tiles, tune.variant != 2, tune.main_kernel_only, s) != hipSuccess) return LRA_ERR_HIP;
     if (tune.main_kernel_only) return LRA_OK;
     if (launch_merge(p, bf16, pl.rows, s) != hipSuccess) return LRA_ERR_HIP;
@@ -247,10 +248,13 @@ lra_status lra_attn_prefill(const lra_shape* shape, const lra_cache* cache, cons
       p.key_rope_theta = 0.f;
       p.keys_f16 = 1;
     }
-    if (wave_rows) {
+    if (wave_shares > 0) {
       p.tile_group = p.group;
       p.row_mul = (65535 + p.group) / p.group;
-      return launch_prefill_rows(p, s) == hipSuccess ? LRA_OK : LRA_ERR_HIP;
+      p.n_splits = wave_shares;
+      if (launch_prefill_rows(p, s) != hipSuccess) return LRA_ERR_HIP;
+      if (wave_shares > 1 && !tune.main_kernel_only && launch_merge(p, bf16, pl.rows, s) != hipSuccess) return LRA_ERR_HIP;
+      return LRA_OK;
     }
     if (launch_prefill_mfma(p, s) != hipSuccess) return LRA_ERR_HIP;
     if (pl.n_splits > 1 && !tune.main_kernel_only && launch_merge(p, bf16, pl.rows, s) != hipSuccess)

@@ -253,24 +253,9 @@ static int64_t rope_two_per_unit_keys(int max_seq_len, int64_t work, int tile, i
   return pays ? sk : 0;
 }
 
-// Whether a prefill runs on the kernel whose waves divide the keys of a workgroup's 32 rows (prefill_rows_kernel): one
-// kernel without a workspace, workgroups a quarter the size of a q tile.  It reads ranks up to 32, and a cache within
-// 32-bit byte offsets of one resource; the completed keys of a rotary call (`keys_ready`: the call has room for them).
-//
-// A workgroup has a compute unit to itself and takes 256 keys per 1.35 us (the way from L2 into LDS), about 7 us
-// outside its loop; the tile walk it replaces takes 15 to 20 us for anything that small but walks a long context with
-// fewer reads.  The line, from 1000 measured calls (8, 4 and 2 kv heads of group 4, 7 and 8, 32 of group 1, d = 64 and
-// 128, ranks 8 to 32, with and without pages; ratio of the times before / here):
-//   one round of the chip (w <= 256 workgroups): steps of 256 keys up to w / 8; 1.0 to 2.0, on the line itself 0.9 to
-//     1.1 (llama shape, 62 tokens on 525 keys 17.2 -> 9.9 us, 104 on 627 21.8 -> 10.7, 198 on 2199 31.4 -> 20.4; beyond
-//     the line 78 on 4395 0.82, 43 on 5802 0.80).  Above 16 kv heads the keys come from memory rather than from L2: w / 12.
-//   two rounds: from 3 steps on 1.0 to 1.8, with up to 8 steps whatever w, up to 20 with a second round half full (399
-//     tokens on 1270: 1.27; 264 on 3762 with 264 workgroups 0.89); at 512 keys and less 0.92 to 1.2, below 1 at rank 16
-//     under 320 workgroups.
-//   three rounds and more: 0.7 to 1.2, mostly below 1.
-//   calls of the size the split-KV path takes, two launches and 8.5 to 9.5 us of GPU time there: 512 keys 0.95 to 1.4,
-//     768 with two and three row tiles per kv head 1.0 to 1.3, 1024 from four on 1.07 to 1.4.
-static bool prefill_waves_divide_keys(const lra_shape* sh, const lra_cache* c, int tokens, bool split_kv_sized, bool keys_ready) {
+// What prefill_rows_kernel reads: ranks up to 32, and a cache within 32-bit byte offsets of one resource; the completed
+// keys of a rotary call (`keys_ready`: the call has room for them).
+static bool prefill_rows_reads(const lra_shape* sh, const lra_cache* c, bool split_kv_sized, bool keys_ready) {
   if (sh->rank > 32 || sh->rank % 8 != 0) return false;
   const bool rope = sh->key_rope_theta > 0.f;
   if (rope && (split_kv_sized || !keys_ready)) return false;
@@ -285,6 +270,27 @@ static bool prefill_waves_divide_keys(const lra_shape* sh, const lra_cache* c, i
         l_pitch > lim / (blocks * 16))
       return false;
   }
+  return true;
+}
+// Whether a prefill runs on the kernel whose waves divide the keys of a workgroup's 32 rows (prefill_rows_kernel): one
+// kernel without a workspace, workgroups a quarter the size of a q tile.
+//
+// A workgroup has a compute unit to itself and takes 256 keys per 1.35 us (the way from L2 into LDS), about 7 us
+// outside its loop; the tile walk it replaces takes 15 to 20 us for anything that small but walks a long context with
+// fewer reads.  The line, from 1000 measured calls (8, 4 and 2 kv heads of group 4, 7 and 8, 32 of group 1, d = 64 and
+// 128, ranks 8 to 32, with and without pages; ratio of the times before / here):
+//   one round of the chip (w <= 256 workgroups): steps of 256 keys up to w / 8; 1.0 to 2.0, on the line itself 0.9 to
+//     1.1 (llama shape, 62 tokens on 525 keys 17.2 -> 9.9 us, 104 on 627 21.8 -> 10.7, 198 on 2199 31.4 -> 20.4; beyond
+//     the line 78 on 4395 0.82, 43 on 5802 0.80).  Above 16 kv heads the keys come from memory rather than from L2: w / 12.
+//   two rounds: from 3 steps on 1.0 to 1.8, with up to 8 steps whatever w, up to 20 with a second round half full (399
+//     tokens on 1270: 1.27; 264 on 3762 with 264 workgroups 0.89); at 512 keys and less 0.92 to 1.2, below 1 at rank 16
+//     under 320 workgroups.
+//   three rounds and more: 0.7 to 1.2, mostly below 1.
+//   calls of the size the split-KV path takes, two launches and 8.5 to 9.5 us of GPU time there: 512 keys 0.95 to 1.4,
+//     768 with two and three row tiles per kv head 1.0 to 1.3, 1024 from four on 1.07 to 1.4.
+static bool prefill_waves_divide_keys(const lra_shape* sh, const lra_cache* c, int tokens, bool split_kv_sized,
+                                      bool keys_ready) {
+  if (!prefill_rows_reads(sh, c, split_kv_sized, keys_ready)) return false;
   const int64_t G = sh->n_q_heads / sh->n_kv_heads, tiles = (tokens * G + 31) / 32;
   const int64_t w = tiles * sh->n_kv_heads, steps = (static_cast<int64_t>(c->max_seq_len) + 255) / 256;
   if (split_kv_sized) return steps <= (tiles == 1 ? 2 : (tiles <= 3 ? 3 : 4)) && w <= kCUs;
@@ -292,6 +298,39 @@ static bool prefill_waves_divide_keys(const lra_shape* sh, const lra_cache* c, i
   if (w > 2 * kCUs) return false;
   if (steps <= 2) return w >= 320 || sh->rank > 16;
   return steps <= 8 || (w >= 384 && steps <= 20);
+}
+
+// Shares of the keys for prefill_rows_kernel where one workgroup per 32 rows leaves compute units idle (then the merge
+// kernel), 0 where another path stays: one workgroup per compute unit in all, at most 32 per row.  A share costs 10 us
+// with the merge and 1.33 us per 256 keys; its partial states are a quarter of those of 128-row tiles in number of rows.
+//
+// The line, from 5000 measured calls (the layer shapes of prefill_waves_divide_keys, 2 to 1000 tokens on 0.25 to 34
+// thousand keys); s = steps of 256 keys per share, T = workgroups per kv head and share.  Inside it 1.13 in the mean,
+// 0.95 at worst:
+//   fewer workgroup steps than compute units: 0.72 to 1.05.
+//   s < 1.4: 0.93 to 1.02 (8 kv heads, 10 tokens on 4568).
+//   T = 1, above 16 kv heads and with two row tiles of the split-KV kernel: shares of 512 keys, 1.02 to 1.2 to s = 8;
+//     with one row tile 0.87 to 1.0, with fewer kv heads 0.83 to 1.07 (8 kv heads, 8 tokens after 9001: 16.1 / 16.4 us).
+//   T = 2 to 4 on contiguous caches: 0.88 to 1.1 (10 tokens on 6644: 16.2 / 18.4 us; paged 1.06 in the mean, from 0.96).
+//   T > 1, up to the s where the 128 rows of the tile walk, which read the keys fewer times, catch up: 1.0 to 1.4 up to 6
+//     where T fills the last such tile, 7, 11 and 12 at T % 4 = 3, 2, 1; beyond 0.66 to 1.0 (107 after 30000 0.72).
+//     Above 16 kv heads, whose keys come from memory, to 4.
+static int plan_wave_shares(const lra_shape* sh, const lra_cache* c, int tokens, int room) {
+  const int64_t n = c->max_seq_len, G = sh->n_q_heads / sh->n_kv_heads;
+  const int64_t row_tiles = (tokens * G + 31) / 32, w = row_tiles * sh->n_kv_heads;
+  if (w > kCUs / 2 || w * n < int64_t{kCUs} * 256) return 0;
+  int64_t shares = kCUs / w < 32 ? kCUs / w : 32;
+  int64_t most;  // steps of a share
+  if (row_tiles == 1) {
+    if (tokens * (G <= 4 ? 4 : (G <= 8 ? 8 : 16)) <= 16 || sh->n_kv_heads <= 16) return 0;
+    if (shares > (n + 511) / 512) shares = (n + 511) / 512;
+    most = 8;
+  } else {
+    if (n < 360 * shares || (row_tiles < 5 && c->block_size == 0 && sh->n_kv_heads <= 16)) return 0;
+    most = sh->n_kv_heads > 16 ? 4 : (row_tiles % 4 == 1 ? 12 : (row_tiles == 2 || row_tiles % 4 == 0 ? 6 : (row_tiles % 4 == 2 ? 11 : 7)));
+  }
+  if (n > most * 256 * shares || shares > room || shares < 2) return 0;
+  return static_cast<int>(shares);
 }
 
 // Decode of a batch with the shares of all sequences in one row (decode_batch_kernel): two workgroups per compute unit
@@ -345,8 +384,8 @@ static void plan_batch(Plan& pl, const lra_shape* sh, const lra_cache* c, bool k
   pl.batch_splits = static_cast<int>(states < pl.n_splits ? states : pl.n_splits);
 }
 
-Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_queries_per_seq, bool prefill,
-               const Tuning& tune, bool key_adapter) {
+static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int max_queries_per_seq, bool prefill,
+                      const Tuning& tune, bool key_adapter) {
   Plan pl{};
   const int G = sh->n_q_heads / sh->n_kv_heads;
   pl.tile_group = G;
@@ -611,6 +650,19 @@ Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_quer
     pl.qt_bytes = decode_stream_qt_bytes(pl.group_pad, sh->rank, pl.row_tiles, pl.row_groups, sh->n_kv_heads);
   pl.bytes += align_up(pl.qt_bytes, 256);
   pl.bytes_without_kc = pl.bytes;
+  return pl;
+}
+
+Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_queries_per_seq, bool prefill,
+               const Tuning& tune, bool key_adapter) {
+  Plan pl = plan_call(sh, c, tokens, max_queries_per_seq, prefill, tune, key_adapter);
+  pl.wave_shares = 0;
+  if (prefill && pl.mfma && pl.n_splits > 1 && !pl.wave_rows && tune.variant == 0 && tune.prefill_splits == 0 && tune.short_prefill <= 32 &&
+      tune.split_keys <= 0) {
+    const bool split_kv_sized = tokens <= tune.short_prefill && static_cast<int64_t>(tokens) * 4 <= c->max_seq_len;
+    if (prefill_rows_reads(sh, c, split_kv_sized, pl.kc_bytes > 0))
+      pl.wave_shares = plan_wave_shares(sh, c, tokens, pl.n_splits);
+  }
   return pl;
 }
 

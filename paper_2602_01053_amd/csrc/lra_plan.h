@@ -35,6 +35,7 @@ struct Plan {
   int split_keys;  // keys per split
   int n_splits;    // splits per sequence at max_seq_len
   bool wave_rows;  // prefill: workgroups of 32 rows whose waves divide the keys (prefill_rows_kernel), whatever the rest says
+  int wave_shares;  // ... or, if not 0, that kernel with this many workgroups dividing the keys of 32 rows, then the merge kernel
   int tile_group;  // tile-walking prefill: q heads whose rows share a q tile (all of a kv head's, or one)
   int group_pad, row_tiles, row_groups;  // MFMA decode row packing
   int l_block;     // split-KV MFMA kernels with per-adapter low-rank caches: padded rank of one slot's column block, else 0

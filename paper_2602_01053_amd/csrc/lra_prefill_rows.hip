@@ -29,7 +29,7 @@ __device__ __forceinline__ void pr_fence() { __builtin_amdgcn_fence(__ATOMIC_SEQ
 
 enum PrKind { kPrQt = 0, kPrValueOnly = 1, kPrKeysF16 = 2 };  // key-side adapter on Qt; none; completed fp16 keys of the pre-pass
 
-template <int D, int RP, bool PAGED, int KIND>
+template <int D, int RP, bool PAGED, int KIND, bool SHARED>
 __global__ __launch_bounds__(512, 2) void prefill_rows_kernel(Params p) {
   static_assert(RP == 16 || RP == 32, "one 32-row block of Olr^T");
   constexpr bool HAS_BK = KIND == kPrQt, KF16 = KIND == kPrKeysF16;
@@ -59,8 +59,11 @@ __global__ __launch_bounds__(512, 2) void prefill_rows_kernel(Params p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, g2 = lane >> 5;
   const int Hq = p.n_q_heads, Hkv = p.n_kv_heads, r = p.rank, G = p.tile_group;
+  // Consecutive ids go to consecutive XCDs: a kv head stays on one, or the workgroups that read a key share of it do
+  const int n_shares = SHARED ? p.n_splits : 1;
   const int lin = blockIdx.x;
-  const int qt = lin / Hkv, hk = lin - qt * Hkv;  // consecutive ids go to consecutive XCDs: a kv head stays on one
+  const int qt = lin / (Hkv * n_shares), in_qt = lin - qt * (Hkv * n_shares);
+  const int share = SHARED ? in_qt / Hkv : 0, hk = in_qt - share * Hkv;
   const int t = p.seq_index, a_idx = p.adapter_index, n_new = p.n_new;
   const int32_t len_t = PF_CONST_I32(p.seq_lens)[t];  // (on its way while Q and B_K are asked for)
   const int n_rows = n_new * G, q0 = qt * BM;
@@ -103,7 +106,19 @@ __global__ __launch_bounds__(512, 2) void prefill_rows_kernel(Params p) {
   map_row(BM - 1, tok_last, gq_last);
   const int limit = base_vis + tok0 + tok_mine;  // last key the lane's row sees
   const int first_limit = base_vis + tok0;
-  const int n_tiles = (base_vis + tok0 + tok_last) / BK + 1;
+  const int all_tiles = (base_vis + tok0 + tok_last) / BK + 1;  // that the workgroup's rows see
+  const int tile0 = SHARED ? static_cast<int>(static_cast<int64_t>(all_tiles) * share / n_shares) : 0;
+  const int n_tiles = SHARED ? static_cast<int>(static_cast<int64_t>(all_tiles) * (share + 1) / n_shares) : all_tiles;
+  const int64_t out_row = row_base + static_cast<int64_t>(tok_mine) * Hq + gq_mine;
+  const int64_t slot = SHARED ? out_row * n_shares + share : 0;
+  if (SHARED && tile0 >= n_tiles) {  // fewer tiles than shares: no key, which the merge kernel reads off the row sum
+    pf_wait_vm0();
+    if (tid < BM && tid < live_rows) {
+      *reinterpret_cast<pf_f32x2*>(p.part_ml + slot * 2) = pf_f32x2{-INFINITY, 0.f};
+      if (share == 0) p.part_adapter[out_row] = a_idx;
+    }
+    return;
+  }
 
   // ---------------- requests: HBM -> LDS, no registers in between ----------------
   const uint32_t lds_w = lds0 + wave * WT;
@@ -131,7 +146,7 @@ __global__ __launch_bounds__(512, 2) void prefill_rows_kernel(Params p) {
   // Paged: lane l holds the id of block (l & 1) of this wave's tile number (l >> 1), all the tiles it can have
   const int nb_last = (n_t - 1) >> 4;
   int ids = 0;
-  if (PAGED) ids = p.block_table[static_cast<int64_t>(t) * p.max_blocks_per_seq + min(2 * (wave + NW * (lane >> 1)) + (lane & 1), nb_last)];
+  if (PAGED) ids = p.block_table[static_cast<int64_t>(t) * p.max_blocks_per_seq + min(2 * (tile0 + wave + NW * (lane >> 1)) + (lane & 1), nb_last)];
   // the wave's tile number `step`, which starts at key j
   auto issue_k = [&](int j, int step) __attribute__((always_inline)) {
 #pragma unroll
@@ -179,11 +194,11 @@ __global__ __launch_bounds__(512, 2) void prefill_rows_kernel(Params p) {
     }
   };
 
-  const bool has_tile = wave < n_tiles;
+  const bool has_tile = tile0 + wave < n_tiles;
   if (ONES_ROW && tid == 0) *reinterpret_cast<pf_u32x4*>(smem + ONES_AT) = pf_u32x4{0x00003f80u, 0u, 0u, 0u};
   if (has_tile) {
-    issue_k(wave * BK, 0);
-    issue_lv(wave * BK, 0);
+    issue_k((tile0 + wave) * BK, 0);
+    issue_lv((tile0 + wave) * BK, 0);
     pr_wait_vm<TL>();  // only the tile is outstanding: the Q and B_K rows have landed
   } else {
     pf_wait_vm0();
@@ -217,7 +232,7 @@ __global__ __launch_bounds__(512, 2) void prefill_rows_kernel(Params p) {
     }
   }
 
-  const bool has_bv = p.b_v != nullptr;
+  const bool has_bv = !SHARED && p.b_v != nullptr;  // (with shares the merge kernel applies B_V)
   if (has_bv) {
     if constexpr (HAS_BK) {
       pr_reads_done();
@@ -254,7 +269,7 @@ __global__ __launch_bounds__(512, 2) void prefill_rows_kernel(Params p) {
   const float sc = p.scale * 1.44269504088896340736f;
 
   int step = 0;
-  for (int tile = wave; tile < n_tiles; tile += NW, ++step) {
+  for (int tile = tile0 + wave; tile < n_tiles; tile += NW, ++step) {
     const int j = tile * BK;
     const bool more = tile + NW < n_tiles;
     pr_wait_vm<KVL>();  // K and L rows have landed
@@ -347,7 +362,7 @@ lr_acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[h2], lr_acc, 0, 0, 0);
   } else {
     l_run += pf_partner32(l_run);
   }
-  const int n_active = min(NW, n_tiles);  // waves that have seen keys
+  const int n_active = min(NW, n_tiles - tile0);  // waves that have seen keys
   auto quad = [](const pf_f32x16& v, int q) __attribute__((always_inline)) { return pf_f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]}; };
   auto slot_of = [&](int w) __attribute__((always_inline)) { return smem + (w < DB ? w * SLOT_SHORT : DB * SLOT_SHORT + (w - DB) * SLOT); };
   // block b of wave w's state: registers 4q..4q+3 of a lane are columns 8q + 4 g2 .. + 3 of row l32
@@ -417,7 +432,23 @@ lr_acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[h2], lr_acc, 0, 0, 0);
     }
   }
   const bool live = l32 < live_rows;
-  const int64_t out_row = row_base + static_cast<int64_t>(tok_mine) * Hq + gq_mine;
+  if constexpr (SHARED) {
+    // the share's state for the merge kernel: m in natural-log units, l, O and Olr as fp32 rows
+    if (!live) return;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      *reinterpret_cast<pf_f32x4*>(p.part_o + slot * D + 32 * wave + 8 * q + 4 * g2) = quad(o, q);
+    if (wave == 0) {
+#pragma unroll
+      for (int q = 0; q < RP / 8; ++q)
+        if (8 * q < r) *reinterpret_cast<pf_f32x4*>(p.part_lr + slot * r + 8 * q + 4 * g2) = quad(lr, q);
+      if (g2 == 0) {
+        *reinterpret_cast<pf_f32x2*>(p.part_ml + slot * 2) = pf_f32x2{m_all * 0.69314718055994530942f, l_all};
+        if (share == 0) p.part_adapter[out_row] = a_idx;
+      }
+    }
+    return;
+  }
   if (has_bv) {
     // O^T += B_V^T Olr^T, Olr as two bf16 terms (see prefill_mfma_kernel)
 #pragma unroll
@@ -445,23 +476,26 @@ lr_acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[h2], lr_acc, 0, 0, 0);
     *reinterpret_cast<uint2*>(dst + 8 * q) = make_uint2(pf_pack2(o[4 * q] * inv, o[4 * q + 1] * inv), pf_pack2(o[4 * q + 2] * inv, o[4 * q + 3] * inv));
 }
 
-template <int D, int RP, bool PAGED>
+template <int D, int RP, bool PAGED, bool SHARED>
 static hipError_t launch_rows3(const Params& p, dim3 grid, hipStream_t s) {
-  if (p.keys_f16) hipLaunchKernelGGL((prefill_rows_kernel<D, RP, PAGED, kPrKeysF16>), grid, dim3(512), 0, s, p);
-  else if (p.b_k != nullptr) hipLaunchKernelGGL((prefill_rows_kernel<D, RP, PAGED, kPrQt>), grid, dim3(512), 0, s, p);
-  else hipLaunchKernelGGL((prefill_rows_kernel<D, RP, PAGED, kPrValueOnly>), grid, dim3(512), 0, s, p);
+  if (p.keys_f16) hipLaunchKernelGGL((prefill_rows_kernel<D, RP, PAGED, kPrKeysF16, SHARED>), grid, dim3(512), 0, s, p);
+  else if (p.b_k != nullptr) hipLaunchKernelGGL((prefill_rows_kernel<D, RP, PAGED, kPrQt, SHARED>), grid, dim3(512), 0, s, p);
+  else hipLaunchKernelGGL((prefill_rows_kernel<D, RP, PAGED, kPrValueOnly, SHARED>), grid, dim3(512), 0, s, p);
   return hipGetLastError();
 }
 
 template <int D, int RP>
 static hipError_t launch_rows2(const Params& p, dim3 grid, hipStream_t s) {
-  return p.block_size != 0 ? launch_rows3<D, RP, true>(p, grid, s) : launch_rows3<D, RP, false>(p, grid, s);
+  if (p.n_splits > 1) return p.block_size != 0 ? launch_rows3<D, RP, true, true>(p, grid, s) : launch_rows3<D, RP, false, true>(p, grid, s);
+  return p.block_size != 0 ? launch_rows3<D, RP, true, false>(p, grid, s) : launch_rows3<D, RP, false, false>(p, grid, s);
 }
 
+// p.n_splits workgroups divide the keys of 32 rows (1: none of the partial-state fields is used)
 hipError_t launch_prefill_rows(const Params& p, hipStream_t s) {
-  if (p.max_seq_len > 32 * 256 && p.block_size != 0) return hipErrorInvalidValue;  // (a wave's block ids lie in one register)
-  if (p.rank > 32 || (p.block_size != 0 && !prefill_pool_fits(p))) return hipErrorInvalidValue;
-  const dim3 grid((p.n_new * p.tile_group + 31) / 32 * p.n_kv_heads);
+  // (a wave's block ids lie in one register: 32 tiles per wave, 256 per share)
+  if ((p.max_seq_len + 31) / 32 > 256 * p.n_splits && p.block_size != 0) return hipErrorInvalidValue;
+  if (p.n_splits < 1 || p.n_splits > 64 || p.rank > 32 || (p.block_size != 0 && !prefill_pool_fits(p))) return hipErrorInvalidValue;
+  const dim3 grid((p.n_new * p.tile_group + 31) / 32 * p.n_kv_heads * p.n_splits);
   if (p.head_dim == 128) return p.rank <= 16 ? launch_rows2<128, 16>(p, grid, s) : launch_rows2<128, 32>(p, grid, s);
   return p.rank <= 16 ? launch_rows2<64, 16>(p, grid, s) : launch_rows2<64, 32>(p, grid, s);
 }

@@ -110,6 +110,15 @@ int main(int argc, char** argv) {
         if (c.block_size == 0) CHECK(int64_t{c.max_seq_len} * c.kv_token_stride * 2 <= top && int64_t{c.max_seq_len} * pitch * 2 <= top);
         else CHECK(c.max_seq_len <= 8192 && int64_t{c.num_blocks} * c.kv_block_stride * 2 <= top && int64_t{c.num_blocks} * 16 * pitch * 2 <= top);
       }
+      if (pl.wave_shares) {  // that kernel with shares: one workgroup per compute unit, states inside the plan's slots, a wave's block ids in one register
+        CHECK(prefill && pl.mfma && !pl.wave_rows && sh.rank <= 32 && pl.wave_shares >= 2 && pl.wave_shares <= 32 && pl.wave_shares <= pl.n_splits);
+        CHECK((tokens * G + 31) / 32 * sh.n_kv_heads * pl.wave_shares <= 256 && (int64_t{c.max_seq_len} + 31) / 32 <= 256 * pl.wave_shares);
+        CHECK(!(sh.key_rope_theta > 0.f) || pl.kc_bytes > 0);
+        CHECK(tune.variant == 0 && tune.prefill_splits == 0 && tune.split_keys == 0);
+        const int64_t pitch = c.l_row_stride ? c.l_row_stride : sh.rank, top = 0x7ffff000;
+        if (c.block_size == 0) CHECK(int64_t{c.max_seq_len} * c.kv_token_stride * 2 <= top && int64_t{c.max_seq_len} * pitch * 2 <= top);
+        else CHECK(int64_t{c.num_blocks} * c.kv_block_stride * 2 <= top && int64_t{c.num_blocks} * 16 * pitch * 2 <= top);
+      }
       if (pl.batch_wgs) {  // a batch's shares in one row: a place for every sequence, every state inside the workspace's slots
         CHECK(!prefill && pl.mfma && c.block_size != 0 && c.n_seqs > 1 && c.n_seqs <= 64 && pl.batch_wgs >= c.n_seqs);
         CHECK(static_cast<int64_t>(pl.batch_wgs) * sh.n_kv_heads * pl.row_groups <= 512);
@@ -348,6 +357,30 @@ int main(int argc, char** argv) {
     lra_tuning forced{};
     forced.kernel_variant = 2;
     CHECK(!make_plan(&sh, &c, t.n_new, 1, true, resolve_tuning(&forced)).wave_rows);
+  }
+  // ... with shares: either side of the measured lines
+  struct WaveShareCase { int hkv, G, d, rank, n_new, n, shares; float theta; };
+  const WaveShareCase wave_share_cases[] = {
+      {8, 4, 128, 16, 8, 9009, 0, 0.f},    {32, 1, 128, 16, 16, 9009, 8, 0.f},  {32, 1, 128, 16, 4, 9009, 0, 0.f},    {32, 1, 128, 16, 5, 2047, 0, 0.f},
+      {32, 1, 128, 16, 5, 16385, 0, 0.f},  {8, 4, 128, 16, 48, 1800, 5, 0.f},   {8, 4, 128, 16, 48, 1799, 0, 0.f},   {8, 4, 128, 16, 32, 2880, 0, 0.f},    {8, 4, 128, 16, 64, 2880, 4, 0.f},
+      {8, 4, 128, 16, 64, 6144, 4, 0.f},   {8, 4, 128, 16, 64, 6145, 0, 0.f},   {8, 4, 128, 32, 33, 18432, 6, 0.f},   {8, 4, 128, 32, 33, 18433, 0, 0.f},
+      {8, 4, 128, 64, 64, 2880, 0, 0.f},   {8, 4, 128, 16, 129, 5000, 0, 0.f},  {32, 1, 128, 16, 64, 4096, 4, 0.f},   {32, 1, 128, 16, 64, 4097, 0, 0.f},
+      {8, 4, 128, 16, 33, 4000, 6, 1e4f},  {8, 4, 128, 16, 16, 9000, 0, 1e4f}};
+  for (int it = 0; it < static_cast<int>(sizeof(wave_share_cases) / sizeof(wave_share_cases[0])); ++it) {
+    const WaveShareCase& t = wave_share_cases[it];
+    lra_shape sh{};
+    sh.n_kv_heads = t.hkv;
+    sh.n_q_heads = t.hkv * t.G;
+    sh.head_dim = t.d;
+    sh.rank = t.rank;
+    sh.key_rope_theta = t.theta;
+    lra_cache c{};
+    c.n_seqs = 1;
+    c.max_seq_len = t.n;
+    c.kv_token_stride = t.hkv * t.d;
+    c.kv_head_stride = t.d;
+    const Plan pl = make_plan(&sh, &c, t.n_new, 1, true, resolve_tuning(nullptr));
+    CHECK(pl.wave_shares == t.shares);
   }
   // the split of lra_cache_append over d_model
   for (int it = 0; it < cases; ++it) {

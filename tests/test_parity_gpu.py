@@ -300,6 +300,68 @@ def test_prefill_whose_waves_divide_the_keys(case):
         _gate(out.to(torch.float64).cpu().numpy(), ref, label=str(case))
 
 
+WAVE_SHARE_CASES = [
+    # n, n_new, Hq, Hkv, d, r, paged, key side, longest: the keys of 32 rows divided among workgroups
+    (2100, 9, 32, 32, 128, 16, False, "bk", 2100),     # 5 shares of one row tile, nine live rows
+    (2880, 64, 32, 8, 128, 16, False, "bk", 2880),     # 4 shares of eight row tiles
+    (6144, 61, 32, 8, 64, 32, True, "none", 6144),     # the longest share of full 128-row tiles
+    (18432, 33, 32, 8, 128, 24, True, "bk", 18432),    # the longest share of all, four live rows in the fifth tile
+    (11521, 7, 28, 4, 128, 8, True, "bk", 11521),      # group of 7, 32 shares
+    (11777, 15, 16, 2, 64, 16, True, "bk", 11777),     # group of 8, 32 shares
+    (4096, 64, 32, 32, 128, 32, False, "none", 4096),  # group of 1
+    (2200, 33, 32, 8, 128, 8, False, "rotary", 2200),
+    (4401, 40, 16, 4, 64, 16, True, "rotary", 4401),
+    (100, 64, 32, 8, 128, 16, True, "bk", 2880),       # shorter than the longest it was planned for: 2 to 4 tiles,
+    (40, 40, 16, 4, 128, 32, False, "bk", 4400),       # so shares without a key, and (here) rows without one in theirs
+]
+
+
+@pytest.mark.parametrize("case", WAVE_SHARE_CASES, ids=lambda c: "n%d_new%d_hq%d_hkv%d_d%d_r%d_paged%d_%s_of%d" % c)
+def test_prefill_whose_waves_divide_the_keys_of_a_share(case):
+    """Against the oracle, twice with the same bits, on a workspace of NaN bytes; variant 2 passes the same bar."""
+    n, n_new, hq, hkv, d, r, paged, side, longest = case
+    theta = 500000.0 if side == "rotary" else 0.0
+    w = W.make_contiguous("wave_shares", "prefill", seed=4800 + n + n_new, n_agents=1, n_q_heads=hq, n_kv_heads=hkv,
+                          head_dim=d, rank=r, n=n, n_new=n_new, d_model=None, b_std=0.05)
+    blocks = (longest + 15) // 16
+    order = torch.randperm(blocks, generator=torch.Generator().manual_seed(n))
+    def store(t, lead):  # rows past the sequence's end hold NaN
+        pad = torch.full((blocks * 16, *t.shape[1:]), float("nan"), dtype=t.dtype)
+        pad[:n] = t
+        if not paged:
+            return pad[:longest].to(DEV)
+        out = torch.empty((blocks, 16, *t.shape[1:]), dtype=t.dtype)
+        out[order] = pad.view(blocks, 16, *t.shape[1:])
+        return (out.transpose(1, 2).contiguous() if lead else out).to(DEV)
+    k, v, l = store(w.k_base, True), store(w.v_base, True), store(w.l, False)
+    table = order.to(torch.int32).view(1, -1).to(DEV) if paged else None
+    lens = torch.tensor([n], dtype=torch.int32, device=DEV)
+    cache = lra.make_cache(k, v, l, lens, longest, table)
+    q = w.q.to(DEV)
+    shape = lra.make_shape(q, hkv, r, 0.0, theta)
+    b_k = None if side == "none" else w.b_k.to(DEV)
+    b_v = w.b_v.to(DEV)
+    outs = []
+    for variant in (0, 0, 2):
+        old = lra.lra_set_kernel_variant(variant)
+        try:
+            need = lra.lra_workspace_bytes(shape, cache, 1, 1, n_new)
+            ws = torch.full((need,), 0xff, dtype=torch.uint8, device=DEV)
+            out = torch.full_like(q, float("nan"))
+            lra.lra_attn_prefill(shape, cache, b_k, b_v, w.n_adapters, q, 0, 0, out, ws)
+            torch.cuda.synchronize()
+            outs.append(out)
+        finally:
+            lra.lra_set_kernel_variant(old)
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+    import oracle
+    f = lambda t: t.to(torch.float64).numpy()
+    bk0 = np.zeros_like(f(w.b_k[0])) if side == "none" else f(w.b_k[0])
+    ref = oracle.prefill(f(w.q), f(w.k_base), f(w.v_base), f(w.l), bk0, f(w.b_v[0]), n=n, scale=w.scale, key_rope_theta=theta)
+    for out in outs[1:]:
+        _gate(out.to(torch.float64).cpu().numpy(), ref, label=str(case))
+
+
 @pytest.mark.parametrize("n,n_new", [(417, 84), (1023, 300)])
 def test_short_sequence_prefill_with_and_without_a_workspace(n, n_new):
     w = W.make_contiguous("short_sequence", "prefill", seed=4700 + n, n_agents=1, n_q_heads=8, n_kv_heads=2,
