@@ -143,6 +143,6 @@ struct AppendParams {
   int k_splits, split_bt;
   float* split_ws;
 };
-hipError_t launch_append(const AppendParams& p, hipStream_t s);
+hipError_t launch_append(const AppendParams& p, bool quarter_tiles, hipStream_t s);
 
 }  // namespace lra

@@ -394,6 +394,11 @@ int main(int argc, char** argv) {
     t.append_tile = static_cast<int32_t>(pick({0, 0, 0, 64, 128}));
     t.append_stages = static_cast<int32_t>(pick({0, 0, 0, 3}));
     const Tuning tune = resolve_tuning(&t);
+    if (append_quarter_tiles(static_cast<int>(n_new), hkv, d, r, dm, tune)) {  // one round, whole steps, a place for every L block
+      const int64_t ft = 2LL * hkv * d / 64, tiles = (n_new + 63) / 64 * ft;
+      CHECK(n_new > tune.append_skinny && tiles <= 256 && dm % 128 == 0 && ft >= 4 * ((r + 15) / 16));
+      CHECK(tune.append_tile == 0 && tune.append_stages == 0 && tune.append_k_splits <= 1);
+    }
     const AppendSplit sp = plan_append_split(static_cast<int>(n_new), hkv, d, r, dm, tune);
     CHECK(sp.k_splits >= 1 && sp.k_splits <= 16 && (sp.bt == 64 || sp.bt == 128));
     CHECK((sp.k_splits == 1) == (sp.bytes == 0));
@@ -407,6 +412,15 @@ int main(int argc, char** argv) {
         CHECK(tiles * sp.k_splits <= kCUs && dm / 64 / sp.k_splits >= 4 && n_new > 32 && sp.bt == 64);
       }
     }
+  }
+  // 64 x 64 tiles: either side of the measured lines (kv heads, d, rank, d_model, new tokens)
+  const struct { int hkv, d, r, dm, n_new; bool quarter; } quarter_cases[] = {
+      {8, 128, 16, 4096, 321, true}, {8, 128, 16, 4096, 320, false}, {8, 128, 16, 4096, 512, true}, {8, 128, 16, 4096, 513, false},
+      {8, 64, 64, 2048, 321, true},  {8, 64, 64, 2048, 320, false},  {2, 128, 32, 2048, 1728, true}, {2, 128, 32, 2048, 1729, false},
+      {2, 128, 40, 2048, 1000, false}, {4, 64, 16, 1088, 700, false}, {4, 64, 16, 1024, 65, false}, {8, 128, 16, 256, 64, false}, {8, 128, 16, 256, 65, true}};
+  for (int it = 0; it < static_cast<int>(sizeof(quarter_cases) / sizeof(quarter_cases[0])); ++it) {
+    const auto& t = quarter_cases[it];
+    CHECK(append_quarter_tiles(t.n_new, t.hkv, t.d, t.r, t.dm, resolve_tuning(nullptr)) == t.quarter);
   }
   std::printf("plan_fuzz: %d cases, %d accepted by the argument checks, all plans consistent\n", cases, accepted);
   return accepted > cases / 10 ? 0 : 2;

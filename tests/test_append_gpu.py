@@ -431,3 +431,47 @@ def test_append_writes_nothing_when_the_device_length_exceeds_the_bound(n_new):
     torch.cuda.synchronize()
     for name, t in (("K", k), ("V", v), ("L", l)):
         assert bool((t == SENTINEL).all()), f"{name} rows were overwritten"
+
+
+QUARTER_CASES = [
+    # n, n_new, d_model, Hkv, d, r, theta, paged: 64 x 64 tiles
+    (66, 65, 128, 2, 64, 8, 10000.0, False),          # one step; one token in the second tile; L on every feature tile
+    (700, 128, 256, 2, 128, 32, 500000.0, True),      # two steps, both L blocks, no remainder
+    (400, 250, 384, 4, 64, 24, 500000.0, False),      # three steps; half of the second L block; six tokens short
+    (70000, 161, 640, 3, 128, 16, 500000.0, False),   # five steps, one more than the ring holds; far positions
+    (900, 320, 1024, 8, 128, 64, 0.0, True),          # four L blocks, unrotated keys
+    (2000, 511, 4096, 8, 128, 16, 500000.0, False),   # a full round of the chip
+    (1500, 1025, 128, 1, 128, 16, 10000.0, True),     # four feature tiles, all with L blocks
+]
+
+
+@pytest.mark.parametrize("case", QUARTER_CASES, ids=lambda c: "n%d_new%d_dm%d_hkv%d_d%d_r%d_th%g_paged%d" % c)
+def test_append_quarter_tiles(case):
+    """Against the oracle, all other cache elements keep their value, and an offered workspace is left alone (the
+    parts of a divided d_model would be in it)."""
+    n, n_new, d_model, hkv, d, r, theta, paged = case
+    x, w = _inputs(7300 + n, n_new, d_model, hkv, d, r)
+    blocks = (n + 15) // 16
+    order = torch.randperm(blocks, generator=torch.Generator().manual_seed(n))
+    if paged:
+        k = torch.full((blocks, hkv, 16, d), SENTINEL, dtype=torch.bfloat16, device=DEV)
+        l = torch.full((blocks, 16, r), SENTINEL, dtype=torch.bfloat16, device=DEV)
+    else:
+        k = torch.full((n, hkv, d), SENTINEL, dtype=torch.bfloat16, device=DEV)
+        l = torch.full((n, r), SENTINEL, dtype=torch.bfloat16, device=DEV)
+    v = k.clone()
+    lens = torch.tensor([n], dtype=torch.int32, device=DEV)
+    table = order.to(torch.int32).view(1, -1).to(DEV) if paged else None  # (the cache holds addresses only)
+    cache = lra.make_cache(k, v, l, lens, n, table)
+    shape = lra.make_shape(torch.empty(1, hkv, d, dtype=torch.bfloat16, device=DEV), hkv, r, 0.0)
+    ws = torch.full((8 << 20,), 0xA5, dtype=torch.uint8, device=DEV)
+    lra.lra_cache_append(shape, cache, w.to(DEV), theta, x.to(DEV), 0, workspace=ws)
+    torch.cuda.synchronize()
+    assert bool((ws == 0xA5).all())
+    rows = lambda t, lead: (t.transpose(1, 2) if lead else t)[order.to(DEV)].flatten(0, 1) if paged else t
+    f = lambda t: t.to(torch.float64).cpu().numpy()
+    refs = oracle.project_new_tokens(f(x), f(w), hkv, d, r, np.arange(n - n_new, n), theta)
+    for name, t, lead, ref in zip("KVL", (k, v, l), (True, True, False), refs):
+        t = rows(t, lead)
+        _gate(f(t[n - n_new:n]), ref, f"{case} {name}")
+        assert bool((t[:n - n_new] == SENTINEL).all()) and bool((t[n:] == SENTINEL).all())
