@@ -9,6 +9,10 @@
 // tiles w, w + 8, ..., and the eight states meet in LDS: four times the workgroups, an eighth of the steps, one kernel.
 // 62 new tokens on 525 keys, 8 kv heads of group 4: 17.2 -> 9.9 us; 198 on 2199, rank 32: 31.4 -> 20.4 us.
 //
+// SHARED: p.n_splits workgroups divide the keys of the 32 rows as well (even stretches of 32-key tiles), each leaves one
+// state per live row in the workspace and the merge kernel finishes.  For calls of about ten to a hundred tokens on long
+// contexts, where one workgroup per 32 rows leaves units idle: 40 after 9000 21.9 -> 17.9 us (see plan_wave_shares).
+//
 // A wave owns its tiles, so nothing in its loop waits for another wave.  K, L and V have one place each per wave: the
 // next K rows are requested when the scores have been taken, the next L and V rows behind the second product, and the
 // other wave of the SIMD computes meanwhile.  What bounds the loop is the way from L2 into LDS: 136 KB per 256 keys at
@@ -291,7 +295,7 @@ __global__ __launch_bounds__(512, 2) void prefill_rows_kernel(Params p) {
         const uint2 lo = *reinterpret_cast<const uint2*>(tile_lds + l_rd[ks][0]);
         const uint2 hi = *reinterpret_cast<const uint2*>(tile_lds + l_rd[ks][1]);
         const pf_bf16x8 a = pf_as_bf16x8(make_uint4(lo.x, lo.y, hi.x, hi.y));
-s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qtb[ks], s, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qtb[ks], s, 0, 0, 0);
       }
     }
     pr_reads_done();
@@ -339,7 +343,7 @@ s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qtb[ks], s, 0, 0, 0);
       for (int b = 0; b < DB; ++b) {
         const unsigned char* src = tile_lds + (v_pre ^ (b << 6)) + 16 * h2 * (D * 2);
         const pf_bf16x8 a = pf_join(pf_read_tr16(src), pf_read_tr16(src + 8 * (D * 2)));
-o_acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[h2], o_acc[b], 0, 0, 0);
+        o_acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[h2], o_acc[b], 0, 0, 0);
       }
       const unsigned char* src0 = tile_lds + lt_rd[0] + 16 * h2 * (RP * 2);
       const unsigned char* src1 = tile_lds + lt_rd[1] + 16 * h2 * (RP * 2);
@@ -348,7 +352,7 @@ o_acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[h2], o_acc[b], 0, 0, 0)
         src1 = ones_lane ? smem + ONES_AT : src1;
       }
       const pf_bf16x8 a = pf_join(pf_read_tr16(src0), pf_read_tr16(src1));
-lr_acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[h2], lr_acc, 0, 0, 0);
+      lr_acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[h2], lr_acc, 0, 0, 0);
     }
     pr_reads_done();
     if (more) issue_lv(j + NW * BK, step + 1);
