@@ -29,9 +29,53 @@
 // and never synchronise inside the loop; their states are merged through LDS at
 // the end (flash-decoding rule) and one partial (m, l, O, O_lr) per workgroup
 // goes to the workspace.
-#include "lra_decode_mfma_body.h"
+#include "lra_common.h"
+#include "lra_decode_util.h"
+#include "lra_plan.h"
+#include "lra_prefill_util.h"
 
 namespace lra {
+
+// HAS_BK = false is the value-only setting (b_k == NULL, keys fully shared): no Qt, no
+// adapter lookup on the key side, no L term in the scores; L is still streamed for P.L.
+// CAUSAL = true serves lra_attn_prefill with a handful of new tokens: the new tokens of the
+// one sequence take the place of the agents (same adapter for all), and row i only sees the
+// keys up to n - n_new + i (the mask of Alg. 1); a long context is then split over the whole chip
+// like any decode call instead of being walked by one workgroup per q head.
+//
+// RPE > 0 is the rotary key side, K_j = K_base,j + RoPE_j(L_j B_K) (what App. D.1 leaves to the
+// key cache because the rotation stands between L_j and B_K): the L.Qt term of the scores is
+// replaced, per 16-key tile and agent slot, by
+//   E^T[f][key]   = B_K^T[f][:] . L^T[:][key]                 (MFMA, C layout: lane = key)
+//   rotate the pairs (f, f + D/2) of E^T by the key's angle   (registers, sine/cosine shared by the slots)
+//   S^T[key][row] += rot(E)[key][f] . Q[row][f]                (MFMA; the C layout of E^T is the
+//                                                              A layout of this product)
+// with Q masked to the rows of the slot.  The B_K^T operands of NS agent slots stay in
+// registers (RPE = padded rank of that product: 16, 32 or 64, for 4, 2 or 4 slots per tile - at
+// 64 the LDS leaves room for one workgroup per CU only, whose waves then have 512 registers);
+// in the causal form all rows belong to the one adapter of the call.
+//
+// PA = true is the decode form for one low-rank cache per adapter (BaseShared, Sec. 3.2) outside the rotary key
+// side: the L tile is a row of column blocks [agent slot][32 keys][l_block ranks], block s requested from the cache
+// of the adapter of agent slot s; Qt of a row stands in the block of its slot and is zero elsewhere, so the same
+// products give Qt_a . L_a^T and P . L_a per agent, and a row keeps only its own block of O_lr.  K_base and V_base are
+// then read once for all agents of a tile, and no zero padding is streamed.
+// The body as a function of its own, for the forms whose registers come out better behind that boundary (us at the text /
+// at the function): rotary on paged caches, rank 8, one agent on 9001 tokens, 4 kv heads 22.2 / 19.1, 4 agents, 8 kv heads
+// 32.7 / 28.3, rank 64 36.8 / 35.1; rotary up to rank 16 with several row groups, 8 agents on 30000 71.6 / 66.3; value-only
+// adapters with their own low-rank caches on pages, d = 64, 20.0 / 19.7.  The other forms stand at the text: rotary above rank
+// 32 on contiguous caches, 4 agents on 2000, 4 kv heads 17.5 / 18.2 (14 to 16 registers in scratch memory against 32).
+template <bool PAGED, bool HAS_BK, int RPE, bool PA, bool RGI>
+constexpr bool kDecodeByFunction = (RPE > 0 && (PAGED || (RPE == 16 && RGI))) || (PA && PAGED && !HAS_BK);
+template <int D, int RT, int RP, bool PAGED, bool HAS_BK, bool CAUSAL, int RPE, bool PA>
+__device__ __forceinline__ void decode_mfma_keys(const Params& p, const int h, const int t, const int rg, const int split,
+                                                 const int j0, const int keys) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr bool LAST = false, last_of_seq = false;
+  constexpr int first_query = 0, end_query = 0;
+#include "lra_decode_mfma_body.h"
+}
 
 // RGI = false leaves out the grid layout for several row groups (below).  The rotary forms sit at the edge of their
 // register file, and the few instructions of that layout at the top of the kernel were enough to move their
@@ -39,6 +83,8 @@ namespace lra {
 // layout only when a call has several row groups.
 template <int D, int RT, int RP, bool PAGED, bool HAS_BK, bool CAUSAL, int RPE = 0, bool PA = false, bool RGI = true>
 __global__ __launch_bounds__(256, RPE == 64 ? 1 : 2) void decode_mfma_kernel(Params p) {
+  [[maybe_unused]] const int lane = threadIdx.x & 63;
+  [[maybe_unused]] const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // kv head is the fastest grid index: workgroups go round-robin over the XCDs, so with 8 kv
   // heads all workgroups of a head run on one XCD and share Q and B_K in its L2
   const int h = blockIdx.x;
@@ -59,7 +105,14 @@ __global__ __launch_bounds__(256, RPE == 64 ? 1 : 2) void decode_mfma_kernel(Par
     t = CAUSAL ? p.seq_index : blockIdx.z;
     if (split >= p.n_splits) return;
   }
-  decode_mfma_keys<D, RT, RP, PAGED, HAS_BK, CAUSAL, RPE, PA>(p, h, t, rg, split, split * p.split_keys, p.split_keys);
+  if constexpr (kDecodeByFunction<PAGED, HAS_BK, RPE, PA, RGI>) {
+    decode_mfma_keys<D, RT, RP, PAGED, HAS_BK, CAUSAL, RPE, PA>(p, h, t, rg, split, split * p.split_keys, p.split_keys);
+  } else {
+    constexpr bool LAST = false, last_of_seq = false;
+    constexpr int first_query = 0, end_query = 0;
+    const int j0 = split * p.split_keys, keys = p.split_keys;
+#include "lra_decode_mfma_body.h"
+  }
 }
 
 template <int D, int RT, int RP, bool CAUSAL>

@@ -1,50 +1,13 @@
-// Body of the split-KV MFMA decode kernels (lra_decode_mfma.hip, lra_decode_batch.hip): one key range of one
-// (sequence, kv head, row group).
-#pragma once
-#include <type_traits>
-
-#include "lra_common.h"
-#include "lra_decode_util.h"
-#include "lra_plan.h"
-#include "lra_prefill_util.h"
-
-namespace lra {
-
-// Agent slots per tile of the rotary form at ranks above 32: that kernel has a CU to itself
-// (its LDS leaves no room for a second workgroup), hence 512 registers per wave.
-constexpr int kRopeSlots64 = 4;
-
-// HAS_BK = false is the value-only setting (b_k == NULL, keys fully shared): no Qt, no
-// adapter lookup on the key side, no L term in the scores; L is still streamed for P.L.
-// CAUSAL = true serves lra_attn_prefill with a handful of new tokens: the new tokens of the
-// one sequence take the place of the agents (same adapter for all), and row i only sees the
-// keys up to n - n_new + i (the mask of Alg. 1); a long context is then split over the whole chip
-// like any decode call instead of being walked by one workgroup per q head.
-//
-// RPE > 0 is the rotary key side, K_j = K_base,j + RoPE_j(L_j B_K) (what App. D.1 leaves to the
-// key cache because the rotation stands between L_j and B_K): the L.Qt term of the scores is
-// replaced, per 16-key tile and agent slot, by
-//   E^T[f][key]   = B_K^T[f][:] . L^T[:][key]                 (MFMA, C layout: lane = key)
-//   rotate the pairs (f, f + D/2) of E^T by the key's angle   (registers, sine/cosine shared by the slots)
-//   S^T[key][row] += rot(E)[key][f] . Q[row][f]                (MFMA; the C layout of E^T is the
-//                                                              A layout of this product)
-// with Q masked to the rows of the slot.  The B_K^T operands of NS agent slots stay in
-// registers (RPE = padded rank of that product: 16, 32 or 64, for 4, 2 or 4 slots per tile - at
-// 64 the LDS leaves room for one workgroup per CU only, whose waves then have 512 registers);
-// in the causal form all rows belong to the one adapter of the call.
-//
-// PA = true is the decode form for one low-rank cache per adapter (BaseShared, Sec. 3.2) outside the rotary key
-// side: the L tile is a row of column blocks [agent slot][32 keys][l_block ranks], block s requested from the cache
-// of the adapter of agent slot s; Qt of a row stands in the block of its slot and is zero elsewhere, so the same
-// products give Qt_a . L_a^T and P . L_a per agent, and a row keeps only its own block of O_lr.  K_base and V_base are
-// then read once for all agents of a tile, and no zero padding is streamed.
-// slot: place of the partial state among the p.n_splits of each row.  keys: a multiple of 128; a wave takes a quarter.
-// LAST = true (the shares of a batch in one row, lra_decode_batch.hip): the sequence's queries are given, and where
-// last_of_seq is set the slots behind this one are left as empty states.
-template <int D, int RT, int RP, bool PAGED, bool HAS_BK, bool CAUSAL, int RPE, bool PA, bool LAST = false>
-__device__ __forceinline__ void decode_mfma_keys(const Params& p, const int h, const int t, const int rg, const int split, const int j0,
-                                                 const int keys, const bool last_of_seq = false, const int first_query = 0,
-                                                 const int end_query = 0) {
+// Body of the split-KV MFMA decode kernels, included inside each of them (lra_decode_mfma.hip, lra_decode_batch.hip) with
+// the template parameters in scope, and with
+//   lane, wave    of the thread, the wave uniform
+//   h, t, rg      kv head, sequence, row group of the workgroup
+//   split         place of its partial state among the p.n_splits of each row
+//   j0, keys      its first key and their number, a multiple of 128 of which a wave takes a quarter
+//   LAST          true for the shares of a batch in one row: the sequence's queries are first_query .. end_query - 1, and
+//                 where last_of_seq is set the slots behind this one are left as empty states.
+// Text, so that each kernel has it where its registers come out best: in the kernel itself or in a function (see
+// kDecodeByFunction).
   constexpr int NW = 4;
   constexpr bool ROPE = RPE > 0;
   static_assert(!PA || (!ROPE && !CAUSAL && RT == 1), "per-adapter low-rank caches: plain decode form, one row tile");
@@ -86,8 +49,6 @@ __device__ __forceinline__ void decode_mfma_keys(const Params& p, const int h, c
   __shared__ __align__(16) float rope_tab[ROPE_FLOATS];
   unsigned char* qt_lds = ALIAS ? smem : extra_lds;
 
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ln = lane & 15, lg = lane >> 4;
   LRA_STAMP_DECL;
   LRA_STAMP(0);
@@ -930,6 +891,3 @@ __device__ __forceinline__ void decode_mfma_keys(const Params& p, const int h, c
   for (int rt = 0; rt < RT; ++rt) asm volatile("" ::"v"(warm[rt][0]), "v"(warm[rt][1]));
   LRA_STAMP(8);
   LRA_STAMP_FLUSH();
-}
-
-}  // namespace lra

@@ -16,6 +16,10 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
+// Agent slots per tile of the split-KV rotary form at ranks above 32: that kernel has a CU to itself
+// (its LDS leaves no room for a second workgroup), hence 512 registers per wave.
+constexpr int kRopeSlots64 = 4;
+
 #ifdef LRA_TIMING
 // Build-time instrumentation (never part of the shipped library): wall-clock stamps (100 MHz) of
 // the phases of every wave, written to a buffer the test build passes in.

@@ -55,9 +55,13 @@ SCRATCH_ALLOWED = [
     (r"prefill_mfma_kernelILi\d+ELi\d+ELb[01]ELb0ELb1ELb1ELb0E", 192),
     # rank 64 with a Qt term on paged caches: a few registers over 256
     (r"prefill_mfma_kernelILi128ELi64ELb1ELb1ELb[01]ELb0ELb0E", 16),
-    # rotary decode at d = 128, ranks up to 16 and 33..64: a few registers over the file (B_K^T operands of four agent
-    # slots stay in registers); up to nine values spilled, five reloads per 32-key step
-    (r"decode_mfma_kernelILi128ELi1ELi(32|64)ELb[01]ELb1ELb0ELi(16|64)E", 160),
+    # rotary decode at d = 128 (B_K^T operands of four agent slots stay in registers), the caps what the build reaches:
+    # ranks up to 16 eight to ten values spilled
+    (r"decode_mfma_kernelILi128ELi1ELi32ELb0ELb1ELb0ELi16E", 40),
+    (r"decode_mfma_kernelILi128ELi1ELi32ELb1ELb1ELb0ELi16E", 44),
+    # ranks 33 to 64: 14 to 16 values on contiguous caches, 32 on paged ones
+    (r"decode_mfma_kernelILi128ELi1ELi64ELb0ELb1ELb0ELi64E", 68),
+    (r"decode_mfma_kernelILi128ELi1ELi64ELb1ELb1ELb0ELi64E", 132),
 ]
 
 
