@@ -174,10 +174,18 @@ typedef struct {
                                   believes seq_lens holds.  Read during the call, never after it
                                   returns, and used for launch planning only: the decode of a
                                   batch sizes its key shares so that the workgroups that find
-                                  keys fill the compute units once (or, beyond 64 sequences of
-                                  ragged lengths, just under twice); without it the shares of
-                                  up to 64 sequences are sized on the device, and a larger batch
-                                  is taken to be half as long on average as max_seq_len.
+                                  keys fill the compute units once (sequences of about equal
+                                  length) or just under twice (ragged lengths).  Paged batches of
+                                  up to 64 sequences have the shares of all of them in one row
+                                  instead, two per compute unit, where that evens out what the
+                                  plain grid does not: not where a grid is in place at once, not
+                                  where one share size for all would leave some share far above
+                                  the mean (one long sequence among many, hardly more places than
+                                  sequences), and not with a rotary key side at head dimension
+                                  128 and ranks up to 16 or above 32.  Without the lengths the
+                                  shares of a row are sized on the device, if it has two places
+                                  or more per sequence; any other batch is taken to be half as
+                                  long on average as max_seq_len.
                                   The results do
                                   not depend on it; entries outside [0, max_seq_len] are clamped.
                                   Key shares only grow with it, so a workspace sized with NULL

@@ -350,54 +350,70 @@ static int plan_wave_shares(const lra_shape* sh, const lra_cache* c, int tokens,
 }
 
 // Decode of a batch with the shares of all sequences in one row (decode_batch_kernel): two workgroups per compute unit
-// (one in the rotary form above rank 32), or the grid of decode_mfma_kernel where that already gives every place at most
-// one live workgroup.  Measured on 38 batches of 2 to 16 sequences, 2 k to 65 k tokens (us before / here): 16 of 4 k to 64 k,
-// 4 kv heads 176 / 162; 10 of 1 k to 6 k 41.9 / 30.0; 10 of 6 k to 8 k with a low-rank cache per adapter, two row groups
-// 67.7 / 45.6; 9 of 1 k to 4 k 30.7 / 25.1; the slowest, 4 of 4 k to 7 k with 650 workgroups before, 18.0 / 19.1.  With
-// equal lengths and 512 live workgroups the other grid is up to 4 % ahead (8 of 18 k to 21 k: 113.7 / 116.4), with several
-// row groups this one.  The rotary forms, whose steps are long against everything else, gain from three tiles on (13 of
-// 0.6 k to 2.7 k: 38.3 / 31.6) and lose up to 8 % at two.
+// (one in the rotary form above rank 32), or the grid of decode_mfma_kernel where that serves as well or the row cannot
+// balance it.  All sequences have one share size, the smallest with which the shares fit the places, so a sequence of n
+// tiles wastes part of a share, and with hardly more places than sequences a long one is not divided at all (one of 65536
+// among 63 of 500, 8 kv heads: 265 us on the grid, 951 in a row).  Measured over 690 batches of 2 to 64 sequences,
+// 0.3 k to 65 k tokens; ratio of the times grid / row:
+//   a grid that is in place at once, or nearly.  One row group: 0.96 to 1.0 where no more than 512 workgroups find keys (8 of
+//     18 k to 21 k: 113.7 / 116.4 us), without lengths 0.95 to 1.1 up to 576 in all (3 of 2.8 k: 11.0 / 11.6).  Several: 0.96
+//     to 1.03 up to 320, at d = 64, where a unit holds more than two, up to 512.
+//   known lengths, share size times places over all tiles: to 1.35 1.0 to 1.45 with one row group (16 of 4 k to 64 k, 4 kv
+//     heads 177 / 162), from there 0.86 to 1.24, 0.28 to 0.4 beyond 8; with several row groups, whose keys the row's layout
+//     reads once, 1.08 to 1.7 to a factor of 2 (10 of 6 k to 8 k, own low-rank caches 67.7 / 45.6), 0.36 at 16.  Shares no
+//     longer than the grid's are taken whatever the factor: 0.98 to 1.9.
+//   unknown lengths: from two places per sequence on 0.98 to 1.7, one long sequence among many short ones with it 1.0 to 2.6
+//     (0.93 at worst: 40000 among 25 of 4000, 117.6 / 126.2), below that 0.74 to 1.1 (62 of 0.1 k to 7.7 k: 96 / 130).
+// The rotary forms, whose steps are long against everything else, gain from three tiles on (13 of 0.6 k to 2.7 k: 38.3 /
+// 31.6) and lose up to 8 % at two.
 static void plan_batch(Plan& pl, const lra_shape* sh, const lra_cache* c, bool key_adapter) {
-  if (c->n_seqs > 64) return;
-  const bool rope = sh->key_rope_theta > 0.f && key_adapter;
+  constexpr int kMost = 64;  // sequences: one per lane
+  if (c->n_seqs > kMost) return;
+  const bool rope = sh->key_rope_theta > 0.f && key_adapter, one = pl.row_groups == 1;
   if (rope && sh->head_dim == 128 && (sh->rank <= 16 || sh->rank > 32)) return;  // (built without: its registers go to scratch memory)
   const int64_t units = static_cast<int64_t>(sh->n_kv_heads) * pl.row_groups;
   const int64_t places = (rope && sh->rank > 32 ? kCUs : 2 * kCUs) / units;
   if (places < c->n_seqs) return;
-  const int64_t longest = (static_cast<int64_t>(c->max_seq_len) + 127) / 128;
-  const int64_t least = (longest + pl.n_splits - 1) / pl.n_splits;
+  const int longest = (c->max_seq_len + 127) / 128, grid_tiles = pl.split_keys / 128;
+  const int least = (longest + pl.n_splits - 1) / pl.n_splits;
+  int tiles[kMost];  // of each sequence (at most 2^23)
   int64_t total = 0, live = 0;
-  auto length = [&](int t) {
-    int64_t len = c->seq_lens_host[t];
-    len = len < 0 ? 0 : (len > c->max_seq_len ? c->max_seq_len : len);
-    return len;
-  };
   if (c->seq_lens_host != nullptr)
     for (int t = 0; t < c->n_seqs; ++t) {
-      total += (length(t) + 127) / 128;
-      live += (length(t) + pl.split_keys - 1) / pl.split_keys;
+      const int32_t len = c->seq_lens_host[t];
+      tiles[t] = len < 0 ? 0 : ((len > c->max_seq_len ? c->max_seq_len : len) + 127) / 128;
+      total += tiles[t];
+      live += (tiles[t] + grid_tiles - 1) / grid_tiles;
     }
-  int64_t size = 0;
+  const int64_t grid = c->n_seqs * pl.n_splits * units;
+  if (one ? (total > 0 ? live * units <= 2 * kCUs : grid <= 576) : grid <= (sh->head_dim == 64 ? 512 : 320)) return;
+  int size = 0;
   if (total > 0) {
-    if (pl.row_groups == 1 && live * units <= 2 * kCUs) return;
-    size = (total + places - 1) / places;
-    size = size < least ? least : size;
-    auto shares = [&]() {
+    auto fits = [&](int share) {
       int64_t n = 0;
-      for (int t = 0; t < c->n_seqs; ++t) {
-        const int64_t tiles = (length(t) + 127) / 128;
-        n += tiles > 0 ? (tiles + size - 1) / size : 1;
-      }
-      return n;
+      for (int t = 0; t < c->n_seqs; ++t) n += tiles[t] > share ? (tiles[t] + share - 1) / share : 1;
+      return n <= places;
     };
-    while (shares() > places) ++size;  // (at most n_seqs <= places shares with size = longest)
+    const int64_t even = (total + places - 1) / places, balanced = (total * (one ? 27 : 40) + places * 20 - 1) / (places * 20);
+    int lo = static_cast<int>(even > least ? even : least);
+    int hi = static_cast<int>(balanced > grid_tiles ? balanced : grid_tiles);  // the largest share that is worth it
+    hi = hi > longest ? longest : hi;
+    if (!fits(hi)) return;
+    while (lo < hi) {  // the smallest that fits
+      const int mid = lo + (hi - lo) / 2;
+      if (fits(mid)) hi = mid;
+      else lo = mid + 1;
+    }
+    size = hi;
+  } else if (places < 2 * c->n_seqs) {
+    return;
   }
-  if (rope && (total > 0 ? size : longest * c->n_seqs / (2 * places)) < 3) return;
+  if (rope && (total > 0 ? size : static_cast<int64_t>(longest) * c->n_seqs / (2 * places)) < 3) return;
   pl.batch_wgs = static_cast<int>(places);
-  pl.batch_tiles = static_cast<int>(size);
-  pl.batch_min_tiles = static_cast<int>(least);
-  const int64_t states = size > 0 ? (longest + size - 1) / size : pl.n_splits;
-  pl.batch_splits = static_cast<int>(states < pl.n_splits ? states : pl.n_splits);
+  pl.batch_tiles = size;
+  pl.batch_min_tiles = least;
+  const int states = size > 0 ? (longest + size - 1) / size : pl.n_splits;
+  pl.batch_splits = states < pl.n_splits ? states : pl.n_splits;
 }
 
 static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int max_queries_per_seq, bool prefill,
@@ -571,7 +587,8 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
   if (split_keys > (1 << 30)) split_keys = 1 << 30;  // (a tuning value; max_seq_len itself is capped there)
   split_keys = (split_keys + tile - 1) / tile * tile;
   if (tune.split_keys <= 0 && pl.mfma && !prefill && c->n_seqs > 1 && c->seq_lens_host != nullptr && c->n_seqs <= 16384) {
-    // The lengths are known.  A batch of sequences of about the same length runs best when the workgroups that find
+    // The lengths are known (what follows is the grid of decode_mfma_kernel, which plan_batch may replace by a row of
+    // shares).  A batch of sequences of about the same length runs best when the workgroups that find
     // keys are all resident at once, two per compute unit, and equal in size (measured on MI355X, 16 sequences of
     // 32768 tokens: 5.7 TB/s at 512 workgroups, 5.0 at 2048, 4.9 at 704): the smallest share size that keeps them
     // within that; never smaller than the choice above, so the workspace of a call without the lengths is large

@@ -293,11 +293,32 @@ int main(int argc, char** argv) {
     const Plan pl = make_plan(&sh, &c, t.n_new, 1, true, Tuning{});
     CHECK(!pl.short_prefill && pl.n_splits >= t.least && pl.n_splits <= t.most);
   }
-  // batches with known lengths: shares in one row unless the other grid has a live workgroup per place
-  struct BatchCase { std::vector<int32_t> lens; int hkv, G, queries; bool row; float theta; };
-  const BatchCase batch_cases[] = {{{65536, 4096, 30000, 9000}, 4, 7, 4, true, 0.f},  {{20000, 20000, 20000, 20000}, 8, 4, 4, false, 0.f},
-                                   {{7000, 3000, 5000, 2000}, 8, 4, 4, true, 0.f},     {{900, 300}, 8, 4, 1, false, 0.f},
-                                   {{2048, 1100, 700}, 8, 4, 4, false, 1e4f},          {{20480, 11000, 7000}, 8, 4, 4, true, 1e4f}};
+  // batches: shares in one row where that balances what the other grid does not (row: with the lengths known, blind: without)
+  auto many = [](int first, int n, int rest) {
+    std::vector<int32_t> v(static_cast<size_t>(n), rest);
+    v[0] = first;
+    return v;
+  };
+  auto spread = [](int n, int lo, int hi) {
+    std::vector<int32_t> v;
+    for (int i = 0; i < n; ++i) v.push_back(lo + static_cast<int>(static_cast<int64_t>(hi - lo) * ((i * 37) % n) / (n - 1)));
+    return v;
+  };
+  struct BatchCase { std::vector<int32_t> lens; int hkv, G, queries; bool row, blind; float theta; };
+  const BatchCase batch_cases[] = {
+      {{65536, 4096, 30000, 9000}, 4, 7, 4, true, true, 0.f}, {{20000, 20000, 20000, 20000}, 8, 4, 4, false, true, 0.f},
+      {{7000, 3000, 5000, 2000}, 8, 4, 4, true, true, 0.f},   {{900, 300}, 8, 4, 1, false, false, 0.f},
+      {{2048, 1100, 700}, 8, 4, 4, false, false, 1e4f},       {{20480, 11000, 7000}, 8, 4, 4, true, true, 1e4f},
+      // one long sequence among many: a common share size would leave it whole
+      {many(65536, 16, 2000), 32, 1, 2, false, false, 0.f},   {many(65536, 64, 500), 8, 4, 2, false, false, 0.f},
+      {many(65536, 32, 2000), 8, 4, 16, false, false, 0.f},   {many(65536, 64, 500), 4, 7, 8, false, false, 0.f},
+      {many(20000, 32, 2000), 8, 4, 4, false, false, 1e4f},   {many(40000, 32, 300), 8, 4, 2, false, true, 0.f},
+      // hardly more places than sequences, several per sequence
+      {spread(56, 2000, 20000), 8, 4, 4, false, false, 0.f},  {spread(64, 2000, 20000), 8, 4, 1, false, false, 0.f},
+      {spread(24, 2000, 36000), 8, 4, 4, true, true, 0.f},    {spread(64, 2000, 20000), 2, 8, 4, true, true, 0.f},
+      {spread(12, 2000, 40000), 32, 1, 4, false, false, 0.f}, {spread(12, 2000, 40000), 8, 4, 16, true, true, 0.f},
+      // in place at once
+      {{670, 500, 520, 530}, 2, 8, 9, false, false, 0.f},     {{6000, 5600, 5700}, 2, 8, 9, true, true, 0.f}};
   for (int it = 0; it < static_cast<int>(sizeof(batch_cases) / sizeof(batch_cases[0])); ++it) {
     const BatchCase& t = batch_cases[it];
     lra_shape sh{};
@@ -317,6 +338,9 @@ int main(int argc, char** argv) {
     c.num_blocks = c.max_blocks_per_seq = (c.max_seq_len + 15) / 16;
     const Plan pl = make_plan(&sh, &c, t.queries * c.n_seqs, t.queries, false, Tuning{});
     CHECK((pl.batch_wgs > 0) == t.row);
+    c.seq_lens_host = nullptr;
+    const Plan blind = make_plan(&sh, &c, t.queries * c.n_seqs, t.queries, false, Tuning{});
+    CHECK((blind.batch_wgs > 0) == t.blind && blind.batch_tiles == 0 && blind.bytes >= pl.bytes);
     if (!t.row) continue;
     int64_t shares = 0, fewer = 0;
     for (int32_t n : t.lens) {
@@ -324,9 +348,6 @@ int main(int argc, char** argv) {
       if (pl.batch_tiles > 1) fewer += ((n + 127) / 128 + pl.batch_tiles - 2) / (pl.batch_tiles - 1);
     }
     CHECK(shares <= pl.batch_wgs && (fewer == 0 || fewer > pl.batch_wgs || pl.batch_tiles == pl.batch_min_tiles));
-    c.seq_lens_host = nullptr;
-    const Plan blind = make_plan(&sh, &c, t.queries * c.n_seqs, t.queries, false, Tuning{});
-    CHECK(blind.batch_tiles == 0 && blind.bytes >= pl.bytes);
     Tuning other;
     other.variant = 2;
     CHECK(make_plan(&sh, &c, t.queries * c.n_seqs, t.queries, false, other).batch_wgs == 0);
