@@ -358,12 +358,12 @@ static int plan_wave_shares(const lra_shape* sh, const lra_cache* c, int tokens,
 //   a grid that is in place at once, or nearly.  One row group: 0.96 to 1.0 where no more than 512 workgroups find keys (8 of
 //     18 k to 21 k: 113.7 / 116.4 us), without lengths 0.95 to 1.1 up to 576 in all (3 of 2.8 k: 11.0 / 11.6).  Several: 0.96
 //     to 1.03 up to 320, at d = 64, where a unit holds more than two, up to 512.
-//   known lengths, share size times places over all tiles: to 1.35 1.0 to 1.45 with one row group (16 of 4 k to 64 k, 4 kv
-//     heads 177 / 162), from there 0.86 to 1.24, 0.28 to 0.4 beyond 8; with several row groups, whose keys the row's layout
+//   known lengths, share size times places over all tiles: to 1.35 0.97 to 1.45 with one row group (16 of 4 k to 64 k, 4 kv
+//     heads 177 / 162), from there 0.86 to 1.26, 0.28 to 0.4 beyond 8; with several row groups, whose keys the row's layout
 //     reads once, 1.08 to 1.7 to a factor of 2 (10 of 6 k to 8 k, own low-rank caches 67.7 / 45.6), 0.36 at 16.  Shares no
 //     longer than the grid's are taken whatever the factor: 0.98 to 1.9.
 //   unknown lengths: from two places per sequence on 0.98 to 1.7, one long sequence among many short ones with it 1.0 to 2.6
-//     (0.93 at worst: 40000 among 25 of 4000, 117.6 / 126.2), below that 0.74 to 1.1 (62 of 0.1 k to 7.7 k: 96 / 130).
+//     (0.93 at worst: 40000 among 25 of 4000, 117.6 / 126.2), below that 0.74 to 1.5 (62 of 0.1 k to 7.7 k: 96 / 130).
 // The rotary forms, whose steps are long against everything else, gain from three tiles on (13 of 0.6 k to 2.7 k: 38.3 /
 // 31.6) and lose up to 8 % at two.
 static void plan_batch(Plan& pl, const lra_shape* sh, const lra_cache* c, bool key_adapter) {
@@ -473,6 +473,7 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
     if (kc_span > (int64_t{1} << 31)) kc_span = -1;
   }
   const bool split_kv_sized = tokens <= tune.short_prefill && static_cast<int64_t>(tokens) * 4 <= c->max_seq_len;
+  pl.split_kv_sized = prefill && split_kv_sized;
   // (The rest of the plan is that of the kernel which would run without it: a call needs the same workspace either way.)
   pl.wave_rows = prefill && pl.mfma && tune.variant == 0 && tune.prefill_splits == 0 && tune.short_prefill <= 32 &&
                  prefill_waves_divide_keys(sh, c, tokens, split_kv_sized, kc_span >= 0);
@@ -692,8 +693,7 @@ Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_quer
   pl.wave_shares = 0;
   if (prefill && pl.mfma && pl.n_splits > 1 && !pl.wave_rows && tune.variant == 0 && tune.prefill_splits == 0 && tune.short_prefill <= 32 &&
       tune.split_keys <= 0) {
-    const bool split_kv_sized = tokens <= tune.short_prefill && static_cast<int64_t>(tokens) * 4 <= c->max_seq_len;
-    if (prefill_rows_reads(sh, c, split_kv_sized, pl.kc_bytes > 0))
+    if (prefill_rows_reads(sh, c, pl.split_kv_sized, pl.kc_bytes > 0))
       pl.wave_shares = plan_wave_shares(sh, c, tokens, pl.n_splits);
   }
   return pl;
