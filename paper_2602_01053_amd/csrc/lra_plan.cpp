@@ -298,22 +298,35 @@ static bool prefill_rows_reads(const lra_shape* sh, const lra_cache* c, bool spl
 //   one round of the chip (w <= 256 workgroups): steps of 256 keys up to w / 8; 1.0 to 2.0, on the line itself 0.9 to
 //     1.1 (llama shape, 62 tokens on 525 keys 17.2 -> 9.9 us, 104 on 627 21.8 -> 10.7, 198 on 2199 31.4 -> 20.4; beyond
 //     the line 78 on 4395 0.82, 43 on 5802 0.80).  Above 16 kv heads the keys come from memory rather than from L2: w / 12.
-//   two rounds: from 3 steps on 1.0 to 1.8, with up to 8 steps whatever w, up to 20 with a second round half full (399
-//     tokens on 1270: 1.27; 264 on 3762 with 264 workgroups 0.89); at 512 keys and less 0.92 to 1.2, below 1 at rank 16
-//     under 320 workgroups.
+//   two rounds, from 950 more: 3 to 6 steps 1.0 to 1.7; 7 and 8 at ranks up to 16 under 320 workgroups 0.96 to 1.2, else 1.0
+//     to 1.5; 9 to 13 with a second round half full 1.0 to 1.4; 14 and more on the edge of that, 384 workgroups, 0.85 to 1.0,
+//     at ranks up to 16 beyond it 14 1.0, 15 to 20 0.92 to 1.2, at the higher ones to 20 0.99 to 1.25 (399 tokens on 1270: 1.27;
+//     378 on 5006 54.5 / 64.3 us).  At 512 keys and less 0.94 to 0.97 at ranks up to 16 under 448 workgroups, 1.0 to 1.2 from
+//     there, at the higher ones 1.0 to 1.2 (0.94 at one of ten).
 //   three rounds and more: 0.7 to 1.2, mostly below 1.
-//   calls of the size the split-KV path takes, two launches and 8.5 to 9.5 us of GPU time there: 512 keys 0.95 to 1.4,
-//     768 with two and three row tiles per kv head 1.0 to 1.3, 1024 from four on 1.07 to 1.4.
+//   calls of the size the split-KV path takes, two launches and 8.5 to 9.5 us of GPU time there, from 520 more.  From 8 kv heads
+//     on: one row tile per kv head 1.0 to 1.4 up to 384 keys, 0.93 to 1.1 to 512 (above 16 kv heads 1.01 to 1.2 from 7
+//     tokens on, 0.89 to 0.97 below); two 1.0 to 1.2 up to 640, 0.93 to 1.0 beyond 700; three 1.1 to 1.25 up to 768; more 1.02
+//     to 1.5 up to 1024.  Fewer kv heads: up to three 1.02 to 1.3 up to 512 and 0.89 to 1.06 to 768, four to six 1.03 to 1.2 up
+//     to 768 and 0.91 to 1.1 to 1024, more 1.01 to 1.2 (5 tokens on 697 keys on pages, 4 kv heads 9.8 / 11.0 us; 24 on 982, 2
+//     kv heads 11.4 / 12.5).
 static bool prefill_waves_divide_keys(const lra_shape* sh, const lra_cache* c, int tokens, bool split_kv_sized,
                                       bool keys_ready) {
   if (!prefill_rows_reads(sh, c, split_kv_sized, keys_ready)) return false;
   const int64_t G = sh->n_q_heads / sh->n_kv_heads, tiles = (tokens * G + 31) / 32;
-  const int64_t w = tiles * sh->n_kv_heads, steps = (static_cast<int64_t>(c->max_seq_len) + 255) / 256;
-  if (split_kv_sized) return steps <= (tiles == 1 ? 2 : (tiles <= 3 ? 3 : 4)) && w <= kCUs;
+  const int64_t w = tiles * sh->n_kv_heads, n = c->max_seq_len, steps = (n + 255) / 256;
+  if (split_kv_sized) {
+    if (w > kCUs) return false;
+    if (tiles == 1) return n <= (sh->n_kv_heads > 16 && tokens > 6 ? 512 : 384);
+    if (sh->n_kv_heads >= 8) return n <= (tiles == 2 ? 640 : (tiles == 3 ? 768 : 1024));
+    return n <= (tiles <= 3 ? 512 : (tiles <= 6 ? 768 : 1024));
+  }
   if (w <= kCUs) return steps <= 4 || steps * (sh->n_kv_heads > 16 ? 12 : 8) <= w;
   if (w > 2 * kCUs) return false;
-  if (steps <= 2) return w >= 320 || sh->rank > 16;
-  return steps <= 8 || (w >= 384 && steps <= 20);
+  const bool wide = sh->rank > 16;
+  if (steps <= 2) return wide || w >= 448;
+  if (steps <= 8) return steps <= 6 || wide || w >= 320;
+  return w >= 384 && steps <= (w < 400 ? 13 : (wide ? 20 : 14));
 }
 
 // Shares of the keys for prefill_rows_kernel where one workgroup per 32 rows leaves compute units idle (then the merge

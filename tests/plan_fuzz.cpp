@@ -356,11 +356,19 @@ int main(int argc, char** argv) {
   struct WaveCase { int hkv, G, rank, n_new, n; bool waves; float theta; };
   const WaveCase wave_cases[] = {
       {8, 4, 16, 62, 525, true, 0.f},    {8, 4, 16, 64, 2048, true, 0.f},   {8, 4, 16, 64, 2049, false, 0.f}, {8, 4, 16, 256, 8192, true, 0.f},
-      {8, 4, 16, 256, 8193, false, 0.f}, {8, 4, 16, 257, 512, false, 0.f},  {8, 4, 24, 257, 512, true, 0.f},  {8, 4, 16, 257, 2048, true, 0.f},
-      {8, 4, 16, 257, 2049, false, 0.f}, {8, 4, 16, 512, 5120, true, 0.f},  {8, 4, 16, 513, 2000, false, 0.f}, {8, 4, 16, 8, 512, true, 0.f},
-      {8, 4, 16, 8, 513, false, 0.f},    {8, 4, 16, 9, 768, true, 0.f},     {8, 4, 16, 32, 1024, true, 0.f},  {8, 4, 16, 32, 1025, false, 0.f},
-      {8, 4, 64, 62, 525, false, 0.f},   {8, 4, 16, 62, 525, true, 1e4f},   {8, 4, 16, 8, 512, false, 1e4f},  {32, 1, 16, 64, 1280, true, 0.f},
-      {32, 1, 16, 64, 1281, false, 0.f}};
+      {8, 4, 16, 256, 8193, false, 0.f}, {8, 4, 16, 257, 512, false, 0.f},  {8, 4, 24, 257, 512, true, 0.f},  {8, 4, 24, 257, 2048, true, 0.f},
+      {8, 4, 24, 257, 2049, false, 0.f}, {8, 4, 24, 512, 5120, true, 0.f},  {8, 4, 16, 513, 2000, false, 0.f}, {8, 4, 64, 62, 525, false, 0.f},
+      {8, 4, 16, 62, 525, true, 1e4f},   {8, 4, 16, 8, 384, false, 1e4f},   {32, 1, 16, 64, 1280, true, 0.f}, {32, 1, 16, 64, 1281, false, 0.f},
+      // two rounds at ranks up to 16
+      {8, 4, 16, 433, 512, false, 0.f},  {8, 4, 16, 448, 512, true, 0.f},   {8, 4, 16, 257, 1536, true, 0.f}, {8, 4, 16, 257, 1537, false, 0.f},
+      {8, 4, 16, 320, 2048, true, 0.f},  {8, 4, 16, 312, 2048, false, 0.f}, {8, 4, 16, 384, 3328, true, 0.f}, {8, 4, 24, 384, 3329, false, 0.f},
+      {8, 4, 16, 512, 3584, true, 0.f},  {8, 4, 16, 512, 3585, false, 0.f},
+      // the split-KV path's sizes
+      {8, 4, 16, 8, 384, true, 0.f},     {8, 4, 16, 8, 385, false, 0.f},    {32, 1, 16, 8, 512, true, 0.f},   {32, 1, 16, 8, 513, false, 0.f},
+      {32, 1, 16, 6, 384, true, 0.f},    {32, 1, 16, 6, 385, false, 0.f},
+      {8, 4, 16, 9, 640, true, 0.f},     {8, 4, 16, 9, 641, false, 0.f},    {8, 4, 16, 17, 768, true, 0.f},   {8, 4, 16, 17, 769, false, 0.f},
+      {8, 4, 16, 32, 1024, true, 0.f},   {8, 4, 16, 32, 1025, false, 0.f},  {4, 7, 16, 5, 512, true, 0.f},    {4, 7, 16, 5, 513, false, 0.f},
+      {2, 8, 16, 24, 768, true, 0.f},    {2, 8, 16, 24, 769, false, 0.f},   {2, 8, 16, 32, 1024, true, 0.f},  {2, 8, 16, 32, 1025, false, 0.f}};
   for (int it = 0; it < static_cast<int>(sizeof(wave_cases) / sizeof(wave_cases[0])); ++it) {
     const WaveCase& t = wave_cases[it];
     lra_shape sh{};
