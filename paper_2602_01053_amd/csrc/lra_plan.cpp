@@ -38,7 +38,8 @@ bool plan_sizes_fit(const lra_shape* sh, const lra_cache* c, int32_t tokens, int
 // before / with these tiles): Llama-3-8B projection, 193 to 256 tokens (128 to 159 tiles) 14.1 / 14.6, 321 to 384 15.6 /
 // 15.2, 449 to 512 19.6 / 16.3, 513 to 576 (a second round) 20.1 / 27.7; 4 kv heads on 3584, 449 to 576 13.9 / 13.9, 833 to 958
 // 17.3 / 15.1; 8 of 64 on 2048, 321 to 448 9.9 / 9.3, 833 to 960 12.7 / 10.1; 12 on 2048, 257 to 320 12.9 / 9.8; 32 on 4096, 65 to
-// 128 20.1 / 16.5.  With eight feature tiles or fewer, most of which then carry L features, nothing is left of it in a full
+// 128 20.1 / 16.5.  On the line itself a second token tile that is mostly empty is not worth it: 12 on 2048, 65 to 80 tokens
+// 8.5 / 8.8, 96 8.9 / 8.8, 128 9.5 / 9.1.  With eight feature tiles or fewer, most of which then carry L features, nothing is left of it in a full
 // round (2 kv heads on 2048, 1473 to 1726 tokens 12.5 / 11.6, 1731 to 1980 12.3 / 12.5).
 bool append_quarter_tiles(int n_new, int n_kv_heads, int head_dim, int rank, int d_model, const Tuning& tune) {
   if (tune.append_k_splits > 1 || tune.append_tile != 0 || tune.append_stages != 0) return false;
@@ -46,6 +47,7 @@ bool append_quarter_tiles(int n_new, int n_kv_heads, int head_dim, int rank, int
   const int64_t feature_tiles = 2 * static_cast<int64_t>(n_kv_heads) * head_dim / 64;
   if (feature_tiles < 4 * ((rank + 15) / 16)) return false;  // (tiles that the L features ride on)
   const int64_t tiles = (static_cast<int64_t>(n_new) + 63) / 64 * feature_tiles;
+  if (n_new < 96 && tiles * 64 < 4 * static_cast<int64_t>(d_model)) return false;
   return tiles * 64 >= 3 * static_cast<int64_t>(d_model) && tiles <= (feature_tiles <= 8 ? 216 : kCUs);
 }
 

@@ -446,7 +446,8 @@ int main(int argc, char** argv) {
   const struct { int hkv, d, r, dm, n_new; bool quarter; } quarter_cases[] = {
       {8, 128, 16, 4096, 321, true}, {8, 128, 16, 4096, 320, false}, {8, 128, 16, 4096, 512, true}, {8, 128, 16, 4096, 513, false},
       {8, 64, 64, 2048, 321, true},  {8, 64, 64, 2048, 320, false},  {2, 128, 32, 2048, 1728, true}, {2, 128, 32, 2048, 1729, false},
-      {2, 128, 40, 2048, 1000, false}, {4, 64, 16, 1088, 700, false}, {4, 64, 16, 1024, 65, false}, {8, 128, 16, 256, 64, false}, {8, 128, 16, 256, 65, true}};
+      {2, 128, 40, 2048, 1000, false}, {4, 64, 16, 1088, 700, false}, {4, 64, 16, 1024, 65, false}, {8, 128, 16, 256, 64, false}, {8, 128, 16, 256, 65, true},
+      {12, 128, 16, 2048, 95, false}, {12, 128, 16, 2048, 96, true}, {32, 128, 16, 4096, 65, true}};
   for (int it = 0; it < static_cast<int>(sizeof(quarter_cases) / sizeof(quarter_cases[0])); ++it) {
     const auto& t = quarter_cases[it];
     CHECK(append_quarter_tiles(t.n_new, t.hkv, t.d, t.r, t.dm, resolve_tuning(nullptr)) == t.quarter);
