@@ -218,20 +218,24 @@ typedef struct {
  *   kernel_variant     0 automatic (MFMA kernels for bf16, vector-ALU kernels for fp32; among the
  *                      MFMA kernels, decode calls on a contiguous cache that give every compute
  *                      unit at most one workgroup take the form with two tile stages per wave and
- *                      separate prologue waves, and prefills that leave most of the chip idle the
- *                      kernel whose waves divide the keys of 32 rows); 1 vector-ALU kernels for
- *                      every dtype; 2 automatic without those two
- *   decode_split_keys  keys per workgroup in decode (the flash-decoding split size), rounded up
- *                      to the kernel's key tile; 0 automatic
+ *                      separate prologue waves, paged batches of up to 64 sequences the kernel
+ *                      that deals the key shares of all of them in one row where that balances
+ *                      them, and prefills that leave most of the chip idle the kernel whose waves
+ *                      divide the keys of 32 rows, with or without key shares); 1 vector-ALU
+ *                      kernels for every dtype; 2 automatic without those three
+ *   decode_split_keys  keys per workgroup in decode and in prefills on the split-KV kernels (the
+ *                      flash-decoding split size), rounded up to the kernel's key tile; keeps
+ *                      batches off the row of shares and prefills off the kernel whose waves
+ *                      divide the keys; 0 automatic
  *   short_prefill      bf16 prefill calls with at most this many new tokens (and a context at
  *                      least four times as long) run on the split-KV decode kernels, the new
  *                      tokens standing in for the agents, where their sizes make that the
- *                      faster path; 0 automatic (32), above 32: whatever the sizes,
- *                      negative: never
+ *                      faster path; 0 automatic (32), above 32: whatever the sizes, and no
+ *                      prefill on the kernel whose waves divide the keys; negative: never
  *   prefill_splits     workgroups that share the key tiles of one q tile in the tile-walking
  *                      prefill kernel (1..32; more than one ends with the merge kernel);
  *                      0 automatic (an even division over the chip, or the smallest estimated
- *                      time where that is clearly below)
+ *                      time where that is clearly below; or the kernel whose waves divide the keys)
  *   rope_key_prepass   prefill calls of the tile-walking kernel with the rotary key side
  *                      (key_rope_theta > 0 and a b_k): 0 automatic (the completed keys
  *                      K_base + RoPE(L B_K) of the call's adapter and sequence are written once

@@ -491,7 +491,7 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
   pl.split_kv_sized = prefill && split_kv_sized;
   // (The rest of the plan is that of the kernel which would run without it: a call needs the same workspace either way.)
   pl.wave_rows = prefill && pl.mfma && tune.variant == 0 && tune.prefill_splits == 0 && tune.short_prefill <= 32 &&
-                 prefill_waves_divide_keys(sh, c, tokens, split_kv_sized, kc_span >= 0);
+                 tune.split_keys <= 0 && prefill_waves_divide_keys(sh, c, tokens, split_kv_sized, kc_span >= 0);
   const bool rope_split = rope && pl.mfma && (!prefill || pl.short_prefill);  // rotary form of the split-KV kernel
   if (prefill && pl.mfma && !pl.short_prefill) {
     // Tile-walking kernel: one workgroup per q tile (see plan_prefill_tiles).  Where those do not fill the chip the

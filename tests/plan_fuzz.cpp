@@ -386,6 +386,13 @@ int main(int argc, char** argv) {
     lra_tuning forced{};
     forced.kernel_variant = 2;
     CHECK(!make_plan(&sh, &c, t.n_new, 1, true, resolve_tuning(&forced)).wave_rows);
+    lra_tuning keys{};  // key shares asked for: the path that takes them
+    keys.decode_split_keys = 128;
+    const Plan split = make_plan(&sh, &c, t.n_new, 1, true, resolve_tuning(&keys));
+    CHECK(!split.wave_rows && split.wave_shares == 0 && (!split.short_prefill || split.split_keys == 128));
+    lra_tuning many{};
+    many.short_prefill = 64;
+    CHECK(!make_plan(&sh, &c, t.n_new, 1, true, resolve_tuning(&many)).wave_rows);
   }
   // ... with shares: either side of the measured lines
   struct WaveShareCase { int hkv, G, d, rank, n_new, n, shares; float theta; };
