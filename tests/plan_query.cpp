@@ -1,0 +1,26 @@
+// What the launch planner answers for one call, for tests that name the kernel they run (tests/test_gpu_cases_plan_cpu.py).
+#include "lra_plan.h"
+
+extern "C" void plan_query(const lra_shape* sh, const lra_cache* c, int tokens, int max_queries_per_seq, int prefill,
+                           int key_adapter, const lra_tuning* tuning, int32_t* out) {
+  const lra::Plan pl = lra::make_plan(sh, c, tokens, max_queries_per_seq, prefill != 0, lra::resolve_tuning(tuning), key_adapter != 0);
+  out[0] = pl.mfma;
+  out[1] = pl.short_prefill;
+  out[2] = pl.wave_rows;
+  out[3] = pl.wave_shares;
+  out[4] = pl.n_splits;
+  out[5] = pl.tile_group;
+  out[6] = pl.batch_wgs;
+  out[7] = pl.batch_tiles;
+  out[8] = pl.row_tiles;
+  out[9] = pl.row_groups;
+  out[10] = pl.l_block;
+  out[11] = pl.workspace_optional;
+  out[12] = pl.group_pad;
+}
+
+extern "C" int append_query(int n_new, int n_kv_heads, int head_dim, int rank, int d_model, const lra_tuning* tuning) {
+  const lra::Tuning t = lra::resolve_tuning(tuning);
+  if (lra::append_quarter_tiles(n_new, n_kv_heads, head_dim, rank, d_model, t)) return -1;
+  return lra::plan_append_split(n_new, n_kv_heads, head_dim, rank, d_model, t).k_splits;
+}

@@ -199,7 +199,9 @@ SPLIT_CASES = [
     (513, 257, 4096, 8, 128, 64, 0.0, 2),           # Llama-3-8B projection shape, r = 64, unrotated keys
     (1000, 512, 1024, 4, 128, 32, 500000.0, 2),
     (4300, 100, 4096, 8, 128, 16, 500000.0, 4),     # Llama-3-8B shape, a trace-sized chunk
-    (40000, 400, 4096, 8, 128, 16, 500000.0, 2),    # ... and about the largest chunk that still divides
+    (40000, 400, 4096, 8, 128, 16, 500000.0, 2),    # ... a chunk that asks for the parts and runs on 64 x 64 tiles, as the row above
+    (40000, 320, 4096, 8, 128, 16, 500000.0, 2),    # ... the largest that still divides
+    (1000, 128, 1024, 4, 128, 32, 500000.0, 4),
     (40000, 1000, 4096, 8, 128, 16, 500000.0, 0),   # more than half a chip of tiles: one kernel
     (2048, 2048, 4096, 8, 128, 16, 500000.0, 0),    # enough tiles for the chip: one kernel
     (31, 16, 4096, 8, 128, 16, 500000.0, 0),        # few tokens: the weight-streaming kernel

@@ -1,0 +1,98 @@
+"""The GPU tests name the kernels their cases run on; this asks the launch planner, compiled for the CPU
+(tests/plan_query.cpp), whether the calls still get there."""
+from __future__ import annotations
+
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2602_01053_amd.binding import LraCache, LraShape, LraTuning
+from tests import test_append_gpu as A
+from tests import test_parity_gpu as P
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+FIELDS = ("mfma", "short_prefill", "wave_rows", "wave_shares", "n_splits", "tile_group", "batch_wgs", "batch_tiles", "row_tiles",
+          "row_groups", "l_block", "workspace_optional", "group_pad")
+
+
+@pytest.fixture(scope="module")
+def planner(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host C++ compiler")
+    lib = str(tmp_path_factory.mktemp("plan") / "plan_query.so")
+    csrc = os.path.join(ROOT, "paper_2602_01053_amd", "csrc")
+    subprocess.run([gxx, "-std=c++17", "-O1", "-shared", "-fPIC", "-I", os.path.join(ROOT, "include"), "-I", csrc,
+                    os.path.join(csrc, "lra_plan.cpp"), os.path.join(ROOT, "tests", "plan_query.cpp"), "-o", lib], check=True)
+    return ctypes.CDLL(lib)
+
+
+def _plan(planner, hq, hkv, d, r, lens, *, longest=None, agents=0, n_new=0, paged, side="bk", host=None, variant=0):
+    n = longest or max(lens)
+    shape = LraShape(hq, hkv, d, r, 0, 0.0, 500000.0 if side == "rotary" else 0.0)
+    cache = LraCache(n_seqs=len(lens), max_seq_len=n, l_row_stride=r)
+    if paged:
+        blocks = sum((x + 15) // 16 for x in lens) if longest is None else (n + 15) // 16
+        cache.block_size, cache.num_blocks, cache.max_blocks_per_seq = 16, blocks, (n + 15) // 16
+        cache.kv_token_stride, cache.kv_head_stride, cache.kv_block_stride = d, 16 * d, 16 * d * hkv
+        if side in ("own", "own_none"):
+            cache.l_adapter_stride = blocks * 16 * r
+    else:
+        cache.kv_token_stride, cache.kv_head_stride = hkv * d, d
+    if host is not None:
+        mirror = (ctypes.c_int32 * len(host))(*host)
+        cache.seq_lens_host = ctypes.cast(mirror, ctypes.c_void_p)
+    out = (ctypes.c_int32 * len(FIELDS))()
+    planner.plan_query(ctypes.byref(shape), ctypes.byref(cache), n_new or agents * len(lens), max(agents, 1), int(n_new > 0),
+                       int(side not in ("none", "own_none")), ctypes.byref(LraTuning(kernel_variant=variant)), out)
+    return dict(zip(FIELDS, out))
+
+
+def test_batches_in_one_row(planner):
+    seen = set()
+    for lens, agents, hq, hkv, d, r, side in P.BATCH_ROW_CASES:
+        for host in (lens, None):
+            pl = _plan(planner, hq, hkv, d, r, lens, agents=agents, paged=True, side=side, host=host)
+            assert pl["batch_wgs"] >= len(lens) and (pl["batch_tiles"] > 0) == (host is not None), (lens, agents, hq, hkv, d, r, side)
+        tile_rank = 16 // pl["group_pad"] * pl["l_block"] if pl["l_block"] else r
+        rotary = (16 if r <= 16 else 32 if r <= 32 else 64) if side == "rotary" else 0
+        seen.add((d, pl["row_tiles"], 32 if tile_rank <= 32 else 64, side in ("bk", "own", "rotary"), rotary, pl["l_block"] > 0))
+    assert len(seen) == 28  # the instantiations of decode_batch_kernel
+    # ... of the shared list, the ones below, whatever the host believes
+    rows = [i for i, (lens, agents, hq, hkv, d, r, side) in enumerate(P.BATCH_CASES)
+            if all(_plan(planner, hq, hkv, d, r, lens, agents=agents, paged=True, side=side, host=h)["batch_wgs"]
+                   for h in (lens, None, [2 * n for n in lens]))]
+    assert rows == [1, 4, 7]
+
+
+def test_prefills_whose_waves_divide_the_keys(planner):
+    for n, n_new, hq, hkv, d, r, paged, side in P.WAVE_CASES:
+        assert _plan(planner, hq, hkv, d, r, [n], n_new=n_new, paged=paged, side=side)["wave_rows"], (n, n_new)
+    shares = {}
+    for n, n_new, hq, hkv, d, r, paged, side, longest in P.WAVE_SHARE_CASES:
+        pl = _plan(planner, hq, hkv, d, r, [n], longest=longest, n_new=n_new, paged=paged, side=side)
+        assert not pl["wave_rows"]
+        shares[n, n_new] = pl["wave_shares"]
+    assert shares == {(2100, 9): 5, (2880, 64): 4, (6144, 61): 4, (18432, 33): 6, (11521, 7): 0, (11777, 15): 0, (14001, 9): 32,
+                      (16000, 8): 32, (20000, 8): 32, (4096, 64): 4, (2200, 33): 6, (4401, 40): 12, (100, 64): 4, (40, 40): 12}
+
+
+def test_prefills_on_the_tile_walk(planner):
+    groups = set()
+    for n, n_new, hq, hkv, d, r in P.TILE_CASES:
+        pl = _plan(planner, hq, hkv, d, r, [n], n_new=n_new, paged=False, variant=2)
+        assert not (pl["wave_rows"] or pl["wave_shares"] or pl["short_prefill"])
+        groups.add((pl["tile_group"] == 1, pl["n_splits"] > 1))
+    assert groups >= {(True, True), (False, True), (True, False)}
+    for n, n_new in ((417, 84), (1023, 300)):  # without room for its shares, one per q tile
+        pl = _plan(planner, 8, 2, 128, 16, [n], n_new=n_new, paged=False, variant=2)
+        assert pl["workspace_optional"] and pl["n_splits"] > 1 and not pl["wave_rows"]
+
+
+def test_appends_that_divide_d_model(planner):
+    tiles_of_64 = {(129, 256), (512, 1024), (400, 4096)}  # (a size is told for the last two, and not used)
+    for n, n_new, d_model, hkv, d, r, theta, parts in A.SPLIT_CASES:
+        assert planner.append_query(n_new, hkv, d, r, d_model, None) == (-1 if (n_new, d_model) in tiles_of_64 else max(parts, 1))

@@ -39,7 +39,8 @@ def _args(name: str):
 
 def test_every_kernel_is_listed(table):
     names = " ".join(table)
-    for kernel in ("decode_stream_kernel", "decode_mfma_kernel", "decode_qt_prepass_kernel", "prefill_mfma_kernel", "prefill_pool_kernel",
+    for kernel in ("decode_stream_kernel", "decode_mfma_kernel", "decode_batch_kernel", "decode_qt_prepass_kernel", "prefill_mfma_kernel",
+                   "prefill_pool_kernel", "prefill_rows_kernel", "append_quarter_kernel",
                    "complete_rope_keys_kernel", "merge_rows_kernel", "merge_wave_kernel", "merge_kernel",
                    "generic_partial_kernel", "generic_partial_rope_kernel", "append_kernel", "append_finish_kernel",
                    "append_wide_kernel", "append_skinny_kernel", "append_gemv_kernel"):
@@ -96,12 +97,19 @@ def test_headline_kernels(table):
         if "append_wide_kernel" in name:  # one workgroup of eight waves per compute unit
             assert row[SCRATCH] == 0 and row[OCC] >= 2 and row[LDS] <= 160 * 1024, (name, row)
             seen.add("wide")
+        if "append_quarter_kernel" in name or "prefill_rows_kernel" in name:  # ... as here
+            assert row[SCRATCH] == 0 and row[OCC] >= 2 and row[LDS] <= 160 * 1024, (name, row)
+            seen.add("quarter" if "append" in name else "rows")
+        if "decode_batch_kernel" in name:  # two workgroups of four waves per compute unit, one in the rotary form above rank 32
+            two = _args(name)[4] != 64
+            assert row[SCRATCH] == 0 and row[OCC] >= (2 if two else 1) and row[LDS] <= (80 if two else 160) * 1024, (name, row)
+            seen.add("batch")
         if "generic_partial_kernel" in name:  # three workgroups per compute unit
             assert row[SCRATCH] == 0 and row[OCC] >= 3 and row[LDS] <= 160 * 1024 // 3, (name, row)
             seen.add("valu")
         if re.search(r"append_kernelILi128ELb0E", name) or "append_gemv_kernel" in name or "append_finish_kernel" in name:
             assert row[SCRATCH] == 0, name
-    assert seen == {"cfg2", "cfg3", "pool", "wide", "valu"}
+    assert seen == {"cfg2", "cfg3", "pool", "wide", "quarter", "rows", "batch", "valu"}
 
 
 def test_prefill_at_d64_rank64_reads_its_operands_ahead(table):

@@ -227,12 +227,19 @@ TILE_CASES = [
 ]
 
 
+@pytest.mark.parametrize("kernels", [0, 2], ids=["auto", "tile_walk"])
 @pytest.mark.parametrize("case", TILE_CASES, ids=lambda c: "n%d_new%d_hq%d_hkv%d_d%d_r%d" % c)
-def test_prefill_tiles_of_one_head_or_of_a_group(case):
+def test_prefill_tiles_of_one_head_or_of_a_group(case, kernels):
+    """(Variant 2: at ranks up to 32 the automatic choice is the kernel whose waves divide the keys.)"""
     n, n_new, hq, hkv, d, r = case
     w = W.make_contiguous("head_tiles", "prefill", seed=4600 + n + n_new, n_agents=1, n_q_heads=hq, n_kv_heads=hkv,
                           head_dim=d, rank=r, n=n, n_new=n_new, d_model=None, b_std=0.05)
-    _gate(run_prefill(w, DEV), oracle_prefill(w), label=str(case))
+    old = lra.lra_set_kernel_variant(kernels)
+    try:
+        got = run_prefill(w, DEV)
+    finally:
+        lra.lra_set_kernel_variant(old)
+    _gate(got, oracle_prefill(w), label=str(case))
 
 
 WAVE_CASES = [
@@ -306,8 +313,11 @@ WAVE_SHARE_CASES = [
     (2880, 64, 32, 8, 128, 16, False, "bk", 2880),     # 4 shares of eight row tiles
     (6144, 61, 32, 8, 64, 32, True, "none", 6144),     # the longest share of full 128-row tiles
     (18432, 33, 32, 8, 128, 24, True, "bk", 18432),    # the longest share of all, four live rows in the fifth tile
-    (11521, 7, 28, 4, 128, 8, True, "bk", 11521),      # group of 7, 32 shares
-    (11777, 15, 16, 2, 64, 16, True, "bk", 11777),     # group of 8, 32 shares
+    (11521, 7, 28, 4, 128, 8, True, "bk", 11521),      # group of 7, and no room for its 32 shares: the tile walk
+    (11777, 15, 16, 2, 64, 16, True, "bk", 11777),     # ... of 8
+    (14001, 9, 28, 4, 128, 8, True, "bk", 14001),      # 32 shares of two row tiles, group of 7
+    (16000, 8, 32, 4, 128, 24, True, "none", 16000),   # ... of 8
+    (20000, 8, 16, 1, 64, 32, True, "bk", 20000),      # 32 shares of four row tiles
     (4096, 64, 32, 32, 128, 32, False, "none", 4096),  # group of 1
     (2200, 33, 32, 8, 128, 8, False, "rotary", 2200),
     (4401, 40, 16, 4, 64, 16, True, "rotary", 4401),
@@ -381,20 +391,26 @@ def test_few_token_prefill_is_no_further_off_than_the_split_kv_path(n, n_new, hq
     assert err[0] <= 1.015 * err[1]
 
 
+@pytest.mark.parametrize("kernels", [0, 2], ids=["auto", "tile_walk"])
 @pytest.mark.parametrize("n,n_new", [(417, 84), (1023, 300)])
-def test_short_sequence_prefill_with_and_without_a_workspace(n, n_new):
+def test_short_sequence_prefill_with_and_without_a_workspace(n, n_new, kernels):
+    """(Variant 2: the tile walk, with key shares and, where it has no room for them, without.)"""
     w = W.make_contiguous("short_sequence", "prefill", seed=4700 + n, n_agents=1, n_q_heads=8, n_kv_heads=2,
                           head_dim=128, rank=16, n=n, n_new=n_new, d_model=None, b_std=0.05)
     ref = oracle_prefill(w)
-    for with_workspace in (True, False):
-        dw = DeviceWorkload(w, DEV)
-        assert dw.alloc_workspace() > 0
-        if not with_workspace:
-            dw.workspace = None
-        dw.out.fill_(float("nan"))
-        dw.prefill()
-        torch.cuda.synchronize()
-        _gate(dw.out.to(torch.float64).cpu().numpy(), ref, label=f"workspace {with_workspace}")
+    old = lra.lra_set_kernel_variant(kernels)
+    try:
+        for with_workspace in (True, False):
+            dw = DeviceWorkload(w, DEV)
+            assert dw.alloc_workspace() > 0
+            if not with_workspace:
+                dw.workspace = None
+            dw.out.fill_(float("nan"))
+            dw.prefill()
+            torch.cuda.synchronize()
+            _gate(dw.out.to(torch.float64).cpu().numpy(), ref, label=f"workspace {with_workspace}")
+    finally:
+        lra.lra_set_kernel_variant(old)
 
 
 @pytest.mark.parametrize("splits", [1, 3])
@@ -584,7 +600,8 @@ def test_one_long_sequence_in_a_paged_cache():
 
 
 BATCH_CASES = [
-    # lengths, agents, Hq, Hkv, d, r, side: the key shares of all sequences in one row, dealt to 512 workgroups
+    # lengths, agents, Hq, Hkv, d, r, side: about half of them small enough for the grid of equal shares, the others with the
+    # key shares of all sequences in one row, dealt to 512 workgroups
     ([3000, 129, 128, 1, 2500], 2, 8, 2, 128, 16, "bk"),        # a tile and a key, a tile, one key; up to 24 shares
     ([6000, 700], 5, 28, 4, 128, 32, "bk"),                     # group of 7: 40 rows, two row groups of two row tiles
     ([5000, 40, 1900], 3, 8, 8, 64, 24, "none"),
@@ -594,10 +611,27 @@ BATCH_CASES = [
     ([7000, 900], 2, 8, 4, 64, 64, "rotary"),                   # one workgroup per compute unit
     ([40 * (i + 3) for i in range(64)], 1, 4, 1, 64, 8, "bk"),  # a sequence in every lane
 ]
+_A, _B, _C = [4000, 1501, 3000, 700], [5200, 900, 2600], [2817, 3000, 129, 1, 2500]
+BATCH_ROW_CASES = [
+    # ... in one row with the lengths known and without, one case and more for every instantiation of that kernel
+    (_C, 2, 32, 8, 128, 16, "bk"), (_A, 3, 32, 8, 128, 24, "none"), (_A, 1, 32, 8, 128, 40, "bk"), (_A, 4, 32, 8, 128, 64, "none"),
+    (_A, 7, 32, 8, 128, 8, "bk"), (_A, 5, 32, 8, 128, 32, "none"), (_B, 6, 32, 8, 128, 64, "bk"), (_B, 8, 32, 8, 128, 40, "none"),
+    (_C, 2, 32, 8, 64, 16, "none"), (_A, 3, 32, 8, 64, 32, "bk"), (_A, 1, 32, 8, 64, 64, "none"), (_A, 4, 32, 8, 64, 40, "bk"),
+    (_A, 7, 32, 8, 64, 24, "none"), (_A, 5, 32, 8, 64, 8, "bk"), (_B, 6, 32, 8, 64, 40, "none"), (_B, 8, 32, 8, 64, 64, "bk"),
+    # a low-rank cache per adapter, two row groups at a group of 7
+    (_B, 3, 28, 4, 128, 16, "own"), (_A, 2, 32, 8, 128, 16, "own"), (_B, 3, 28, 4, 64, 16, "own"), (_A, 3, 32, 8, 64, 8, "own"),
+    (_B, 3, 28, 4, 128, 16, "own_none"), (_A, 2, 32, 8, 128, 16, "own_none"), (_B, 3, 28, 4, 64, 16, "own_none"), (_A, 3, 32, 8, 64, 8, "own_none"),
+    # rotary: three and five row groups, one workgroup per compute unit at rank 40
+    ([9000, 2000, 5000, 7000, 6100, 8000], 5, 28, 4, 64, 16, "rotary"), ([20000, 9000, 16000], 2, 32, 8, 64, 24, "rotary"),
+    ([9000, 3000, 6100, 2000], 3, 16, 8, 64, 40, "rotary"), ([9000, 2000, 5000], 9, 28, 4, 128, 24, "rotary"),
+    # batches of some tens of sequences, two row groups in the second
+    ([300 + 141 * (7 * i % 20) for i in range(20)], 2, 16, 4, 128, 16, "bk"), ([1200 + 90 * (11 * i % 48) for i in range(48)], 6, 14, 2, 64, 32, "none"),
+]
 
 
-@pytest.mark.parametrize("mirror", ["exact", "none", "half", "double"])
-@pytest.mark.parametrize("case", BATCH_CASES, ids=lambda c: "s%d_a%d_hq%d_hkv%d_d%d_r%d_%s" % (len(c[0]), *c[1:]))
+@pytest.mark.parametrize("case,mirror", [(c, m) for c in BATCH_CASES for m in ("exact", "none", "half", "double")] +
+                         [(c, m) for c in BATCH_ROW_CASES for m in ("exact", "none")],
+                         ids=lambda v: v if isinstance(v, str) else "s%d_a%d_hq%d_hkv%d_d%d_r%d_%s" % (len(v[0]), *v[1:]))
 def test_batch_whose_shares_stand_in_one_row(case, mirror):
     """Ragged batches against the oracle, with the right lengths on the host, with none, and with wrong ones (shares that
     do not fit their places are enlarged on the device); NaN in the workspace, so that a state nobody wrote would show."""
@@ -608,13 +642,14 @@ def test_batch_whose_shares_stand_in_one_row(case, mirror):
     dev = lambda t: t.to(DEV)
     f = lambda t: t.to(torch.float64).numpy()
     l = w.l
-    if side == "own":  # adapter a attends over a low-rank cache of its own
+    own = side in ("own", "own_none")
+    if own:  # adapter a attends over a low-rank cache of its own
         l = torch.stack([w.l.roll(a, dims=-1) * (1 + a) for a in range(w.n_adapters)])
     q = dev(w.q)
-    b_k = None if side == "none" else dev(w.b_k)
+    b_k = None if side in ("none", "own_none") else dev(w.b_k)
     host = {"exact": lens, "none": None, "half": [n // 2 for n in lens], "double": [2 * n for n in lens]}[mirror]
     cache_t = [dev(w.k_base), dev(w.v_base), dev(l), torch.tensor(lens, dtype=torch.int32, device=DEV), dev(w.block_table)]
-    cache = lra.make_cache(cache_t[0], cache_t[1], cache_t[2], cache_t[3], max(lens), cache_t[4], l_per_adapter=side == "own",
+    cache = lra.make_cache(cache_t[0], cache_t[1], cache_t[2], cache_t[3], max(lens), cache_t[4], l_per_adapter=own,
                            seq_lens_host=host)
     shape = lra.make_shape(q, hkv, r, 0.0, theta)
     b_v, ids, start = dev(w.b_v), dev(w.query_adapter), dev(w.seq_query_start)
@@ -625,13 +660,13 @@ def test_batch_whose_shares_stand_in_one_row(case, mirror):
     torch.cuda.synchronize()
     import oracle
     got, ref = out.to(torch.float64).cpu().numpy(), np.empty(tuple(q.shape))
+    qf, kf, vf, lf, bk, bv = f(w.q), f(w.k_base), f(w.v_base), f(l), f(w.b_k) * (b_k is not None), f(w.b_v)
     for i in range(q.shape[0]):  # one query at a time: its sequence's rows, its adapter's low-rank cache
         t, a = i // agents, int(w.query_adapter[i])
         table = w.block_table[t].numpy()
-        kb, vb = oracle.gather_paged(f(w.k_base), table, lens[t]), oracle.gather_paged(f(w.v_base), table, lens[t])
-        lr = oracle.lra_oracle.gather_paged_l(f(l[a] if side == "own" else l), table, lens[t])
-        bk = f(w.b_k[a]) if b_k is not None else np.zeros_like(f(w.b_k[a]))
-        ref[i] = oracle.prefill(f(w.q[i:i + 1]), kb, vb, lr, bk, f(w.b_v[a]), n=lens[t], scale=w.scale, key_rope_theta=theta)[0]
+        kb, vb = oracle.gather_paged(kf, table, lens[t]), oracle.gather_paged(vf, table, lens[t])
+        lr = oracle.lra_oracle.gather_paged_l(lf[a] if own else lf, table, lens[t])
+        ref[i] = oracle.prefill(qf[i:i + 1], kb, vb, lr, bk[a], bv[a], n=lens[t], scale=w.scale, key_rope_theta=theta)[0]
     _gate(got, ref, label=f"{case} {mirror}")
 
 
