@@ -59,6 +59,24 @@ def test_ragged_paged_batch_stays_inside_its_buffers(variant):
     assert rel <= REL_L2_TOL and mx <= MAX_ABS_TOL
 
 
+@pytest.mark.parametrize("believed", [1.0, 0.9], ids=["right_lengths", "short_lengths"])
+def test_batch_in_one_row_stays_inside_its_buffers(believed):
+    """... whose shares the device enlarges where the host believed the sequences shorter than they are."""
+    lens = [4000, 1501, 3000, 700]
+    w = W.make_paged("canary_row", seed=617, seq_lens=lens, agents_per_seq=2, n_adapters=2, n_q_heads=32, n_kv_heads=8,
+                     head_dim=128, rank=24, d_model=None, b_std=0.05)
+    dw = DeviceWorkload(w, DEV)
+    dw.cache = lra.make_cache(dw.k_base, dw.v_base, dw.l, dw.seq_lens, max(lens), dw.block_table,
+                              seq_lens_host=[int(n * believed) for n in lens])
+    need = dw.alloc_workspace()
+    ws_whole, dw.workspace, ws_start = _guarded(need)
+    dw.decode()
+    torch.cuda.synchronize()
+    assert _margins_intact(ws_whole, ws_start, need), "write outside the workspace"
+    rel, mx = errors(dw.out.to(torch.float64).cpu().numpy(), oracle_decode(w))
+    assert rel <= REL_L2_TOL and mx <= MAX_ABS_TOL
+
+
 @pytest.mark.parametrize("case", [
     # n, n_new, Hq, Hkv, d, r
     (4099, 7, 32, 8, 128, 16),     # a few new tokens: split-KV path, ragged last row tile

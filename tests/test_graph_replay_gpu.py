@@ -82,6 +82,23 @@ def test_decode_paged_batch_replays():
     _decode_case(w)
 
 
+@pytest.mark.parametrize("known", [True, False], ids=["lengths_known", "lengths_unknown"])
+def test_decode_batch_in_one_row_replays(known):
+    """The key shares of all sequences in one row, sized on the device: the sequences grow and shrink between the replays,
+    away from the lengths the host gave when the call was captured."""
+    lens = [[4000, 1501, 3000, 700], [1, 3900, 3999, 4000], [4000, 4000, 4000, 2500]]
+    w = W.make_paged("graph_row", seed=406, seq_lens=[4000] * 4, agents_per_seq=2, n_adapters=2, n_q_heads=32, n_kv_heads=8,
+                     head_dim=128, rank=16, d_model=None)
+    dw = DeviceWorkload(w, DEV, host_lens=False)
+    dw.alloc_workspace()
+    dw.cache = lra.make_cache(dw.k_base, dw.v_base, dw.l, dw.seq_lens, 4000, dw.block_table, seq_lens_host=lens[0] if known else None)
+    last = _replay_against_eager(lambda st: dw.decode(st), lambda i: dw.seq_lens.copy_(torch.tensor(lens[i], dtype=torch.int32)),
+                                 lambda: [dw.out])
+    w.seq_lens = lens[2]
+    rel, mx = errors(_f64(last[0].cpu()), oracle_decode(w))
+    assert rel <= REL_L2_TOL and mx <= MAX_ABS_TOL
+
+
 def test_decode_static_workspace_replays():
     w = W.make_contiguous("graph_static", "decode", seed=404, n_agents=4, n_q_heads=32, n_kv_heads=8, head_dim=128, rank=16,
                           n=1500, n_new=1, d_model=None)
