@@ -252,8 +252,7 @@ lra_status lra_attn_prefill(const lra_shape* shape, const lra_cache* cache, cons
       p.tile_group = p.group;
       p.row_mul = (65535 + p.group) / p.group;
       p.n_splits = wave_shares;
-      p.own_references = pl.split_kv_sized && wave_shares == 1;
-      if (launch_prefill_rows(p, s) != hipSuccess) return LRA_ERR_HIP;
+      if (launch_prefill_rows(p, pl.split_kv_sized && wave_shares == 1, s) != hipSuccess) return LRA_ERR_HIP;
       if (wave_shares > 1 && !tune.main_kernel_only && launch_merge(p, bf16, pl.rows, s) != hipSuccess) return LRA_ERR_HIP;
       return LRA_OK;
     }

@@ -55,7 +55,6 @@ struct Params {
   int32_t tile_group, tile_heads, tiles_per_round, row_mul;
   // decode_batch_kernel: workgroups per (kv head, row group), 128-key tiles of a share (0: from the lengths), their least
   int32_t batch_wgs, batch_tiles, batch_min_tiles;
-  int32_t own_references;  // prefill_rows_kernel: every key tile's probabilities against its own maximum
 #ifdef LRA_TIMING
   unsigned long long* timing;  // instrumented test build only: per-wave phase stamps
 #endif
@@ -119,7 +118,8 @@ hipError_t launch_decode_batch(const Params& p, int row_tiles, hipStream_t s);
 bool decode_stream_applies(const Params& p, int row_tiles, int n_cus);
 hipError_t launch_decode_stream(const Params& p, int row_tiles, bool main_kernel_only, hipStream_t s);
 hipError_t launch_prefill_mfma(const Params& p, hipStream_t s);
-hipError_t launch_prefill_rows(const Params& p, hipStream_t s);
+// own_references: every key tile's probabilities against its own maximum
+hipError_t launch_prefill_rows(const Params& p, bool own_references, hipStream_t s);
 // rotary key side, contiguous cache: the completed keys of the call's adapter, in K_base's layout, into kc
 hipError_t launch_complete_rope_keys(const Params& p, void* kc, hipStream_t s);
 

@@ -16,8 +16,9 @@
 // The softmax reference is raised lazily (kSlack), which leaves the largest probability of a tile anywhere in eight octaves
 // and rounds it to bf16; over many tiles, and in the walk of 128 rows, that is no loss.  Calls of the split-KV path's sizes come
 // from kernels that took the maximum of about every 32 keys, so that it is exact; where a wave sees a few tiles their
-// error against float64 was 1.02 to 1.17 times as large (31 tokens on 846 2.15e-3 -> 2.40e-3).  They take every tile's own maximum here (own_references, at most kReach
-// below the largest so far, which keeps the sums in range): 0.93 to 1.0 times, at 0.1 us per 256 keys.
+// error against float64 was 1.02 to 1.17 times as large (31 tokens on 846 2.15e-3 -> 2.40e-3).  They take every tile's own
+// maximum here (kPrOwn, at most 2^kReach below the largest so far, which keeps the sums in range): 0.93 to 1.0 times, at
+// 0.1 us per 256 keys.  (As an argument of the call rather than a form of its own it cost the other calls 0.8 %.)
 //
 // A wave owns its tiles, so nothing in its loop waits for another wave.  K, L and V have one place each per wave: the
 // next K rows are requested when the scores have been taken, the next L and V rows behind the second product, and the
@@ -38,11 +39,12 @@ __device__ __forceinline__ void pr_reads_done() {
 __device__ __forceinline__ void pr_fence() { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront"); }
 
 enum PrKind { kPrQt = 0, kPrValueOnly = 1, kPrKeysF16 = 2 };  // key-side adapter on Qt; none; completed fp16 keys of the pre-pass
+enum PrMode { kPrWhole = 0, kPrShared = 1, kPrOwn = 2 };  // all keys of the 32 rows; a share of them; all, and own references
 
-template <int D, int RP, bool PAGED, int KIND, bool SHARED>
+template <int D, int RP, bool PAGED, int KIND, int MODE>
 __global__ __launch_bounds__(512, 2) void prefill_rows_kernel(Params p) {
   static_assert(RP == 16 || RP == 32, "one 32-row block of Olr^T");
-  constexpr bool HAS_BK = KIND == kPrQt, KF16 = KIND == kPrKeysF16;
+  constexpr bool HAS_BK = KIND == kPrQt, KF16 = KIND == kPrKeysF16, SHARED = MODE == kPrShared, OWN = MODE == kPrOwn;
   constexpr int NW = 8, BK = 32, BM = 32;
   constexpr int KS = D / 16, RKS = RP / 16, DB = D / 32;
   constexpr int KCH = D / 8, LCH = RP / 8;
@@ -269,8 +271,8 @@ __global__ __launch_bounds__(512, 2) void prefill_rows_kernel(Params p) {
 
   // ---------------- main loop ----------------
   pf_f32x16 o_acc[DB], lr_acc;
-  float m_run = -INFINITY, m_top = -INFINITY, l_run = 0.f;  // reference, largest score so far, row sum
-  const bool own_ref = p.own_references != 0;
+  float m_run = -INFINITY, l_run = 0.f;
+  [[maybe_unused]] float m_top = -INFINITY;
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     lr_acc[i] = 0.f;
@@ -319,9 +321,9 @@ __global__ __launch_bounds__(512, 2) void prefill_rows_kernel(Params p) {
 #pragma unroll
       for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
       mx = fmaxf(mx, pf_partner32(mx)) * sc;
-      if (own_ref || __builtin_amdgcn_ballot_w64(mx > m_run + kSlack) != 0) {
-        m_top = fmaxf(m_top, mx);
-        const float m_new = own_ref ? fmaxf(mx, m_top - kReach) : m_top;
+      if (OWN || __builtin_amdgcn_ballot_w64(mx > m_run + kSlack) != 0) {
+        if (OWN) m_top = fmaxf(m_top, mx);
+        const float m_new = OWN ? fmaxf(mx, m_top - kReach) : fmaxf(m_run, mx);
         const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);  // (a row that has seen nothing yet)
         m_run = m_new;
         l_run *= alpha;
@@ -488,28 +490,38 @@ __global__ __launch_bounds__(512, 2) void prefill_rows_kernel(Params p) {
     *reinterpret_cast<uint2*>(dst + 8 * q) = make_uint2(pf_pack2(o[4 * q] * inv, o[4 * q + 1] * inv), pf_pack2(o[4 * q + 2] * inv, o[4 * q + 3] * inv));
 }
 
-template <int D, int RP, bool PAGED, bool SHARED>
+template <int D, int RP, bool PAGED, int MODE>
 static hipError_t launch_rows3(const Params& p, dim3 grid, hipStream_t s) {
-  if (p.keys_f16) hipLaunchKernelGGL((prefill_rows_kernel<D, RP, PAGED, kPrKeysF16, SHARED>), grid, dim3(512), 0, s, p);
-  else if (p.b_k != nullptr) hipLaunchKernelGGL((prefill_rows_kernel<D, RP, PAGED, kPrQt, SHARED>), grid, dim3(512), 0, s, p);
-  else hipLaunchKernelGGL((prefill_rows_kernel<D, RP, PAGED, kPrValueOnly, SHARED>), grid, dim3(512), 0, s, p);
+  if (p.keys_f16) {  // (rotary calls of the split-KV path's sizes do not come here)
+    if constexpr (MODE == kPrOwn) return hipErrorInvalidValue;
+    else hipLaunchKernelGGL((prefill_rows_kernel<D, RP, PAGED, kPrKeysF16, MODE>), grid, dim3(512), 0, s, p);
+  } else if (p.b_k != nullptr) {
+    hipLaunchKernelGGL((prefill_rows_kernel<D, RP, PAGED, kPrQt, MODE>), grid, dim3(512), 0, s, p);
+  } else {
+    hipLaunchKernelGGL((prefill_rows_kernel<D, RP, PAGED, kPrValueOnly, MODE>), grid, dim3(512), 0, s, p);
+  }
   return hipGetLastError();
 }
 
-template <int D, int RP>
+template <int D, int RP, int MODE>
 static hipError_t launch_rows2(const Params& p, dim3 grid, hipStream_t s) {
-  if (p.n_splits > 1) return p.block_size != 0 ? launch_rows3<D, RP, true, true>(p, grid, s) : launch_rows3<D, RP, false, true>(p, grid, s);
-  return p.block_size != 0 ? launch_rows3<D, RP, true, false>(p, grid, s) : launch_rows3<D, RP, false, false>(p, grid, s);
+  return p.block_size != 0 ? launch_rows3<D, RP, true, MODE>(p, grid, s) : launch_rows3<D, RP, false, MODE>(p, grid, s);
+}
+
+template <int D, int RP>
+static hipError_t launch_rows1(const Params& p, bool own_references, dim3 grid, hipStream_t s) {
+  if (p.n_splits > 1) return launch_rows2<D, RP, kPrShared>(p, grid, s);
+  return own_references ? launch_rows2<D, RP, kPrOwn>(p, grid, s) : launch_rows2<D, RP, kPrWhole>(p, grid, s);
 }
 
 // p.n_splits workgroups divide the keys of 32 rows (1: none of the partial-state fields is used)
-hipError_t launch_prefill_rows(const Params& p, hipStream_t s) {
+hipError_t launch_prefill_rows(const Params& p, bool own_references, hipStream_t s) {
   // (a wave's block ids lie in one register: 32 tiles per wave, 256 per share)
   if ((p.max_seq_len + 31) / 32 > 256 * p.n_splits && p.block_size != 0) return hipErrorInvalidValue;
   if (p.n_splits < 1 || p.n_splits > 64 || p.rank > 32 || (p.block_size != 0 && !prefill_pool_fits(p))) return hipErrorInvalidValue;
   const dim3 grid((p.n_new * p.tile_group + 31) / 32 * p.n_kv_heads * p.n_splits);
-  if (p.head_dim == 128) return p.rank <= 16 ? launch_rows2<128, 16>(p, grid, s) : launch_rows2<128, 32>(p, grid, s);
-  return p.rank <= 16 ? launch_rows2<64, 16>(p, grid, s) : launch_rows2<64, 32>(p, grid, s);
+  if (p.head_dim == 128) return p.rank <= 16 ? launch_rows1<128, 16>(p, own_references, grid, s) : launch_rows1<128, 32>(p, own_references, grid, s);
+  return p.rank <= 16 ? launch_rows1<64, 16>(p, own_references, grid, s) : launch_rows1<64, 32>(p, own_references, grid, s);
 }
 
 }  // namespace lra
