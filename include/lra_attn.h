@@ -184,8 +184,9 @@ typedef struct {
                                   sequences), and not with a rotary key side at head dimension
                                   128 and ranks up to 16 or above 32.  Without the lengths the
                                   shares of a row are sized on the device, if it has two places
-                                  or more per sequence; any other batch is taken to be half as
-                                  long on average as max_seq_len.
+                                  or more per sequence (five with a rotary key side of rank 32
+                                  or less and several row groups); any other batch is taken to
+                                  be half as long on average as max_seq_len.
                                   The results do
                                   not depend on it; entries outside [0, max_seq_len] are clamped.
                                   Key shares only grow with it, so a workspace sized with NULL

@@ -375,12 +375,17 @@ static int plan_wave_shares(const lra_shape* sh, const lra_cache* c, int tokens,
 //     to 1.03 up to 320, at d = 64, where a unit holds more than two, up to 512.
 //   known lengths, share size times places over all tiles: to 1.35 0.97 to 1.45 with one row group (16 of 4 k to 64 k, 4 kv
 //     heads 177 / 162), from there 0.86 to 1.26, 0.28 to 0.4 beyond 8; with several row groups, whose keys the row's layout
-//     reads once, 1.08 to 1.7 to a factor of 2 (10 of 6 k to 8 k, own low-rank caches 67.7 / 45.6), 0.36 at 16.  Shares no
+//     reads once, 0.93 to 1.8 to a factor of 2 (10 of 6 k to 8 k, own low-rank caches 67.7 / 45.6), 0.36 at 16.  Shares no
 //     longer than the grid's are taken whatever the factor: 0.98 to 1.9.
 //   unknown lengths: from two places per sequence on 0.98 to 1.7, one long sequence among many short ones with it 1.0 to 2.6
 //     (0.93 at worst: 40000 among 25 of 4000, 117.6 / 126.2), below that 0.74 to 1.5 (62 of 0.1 k to 7.7 k: 96 / 130).
 // The rotary forms, whose steps are long against everything else, gain from three tiles on (13 of 0.6 k to 2.7 k: 38.3 /
-// 31.6) and lose up to 8 % at two.
+// 31.6) and lose up to 8 % at two.  What bounds them is the vector unit and not the keys, so that with several row groups only
+// the balance counts (560 batches, several row groups).  Known lengths, to 1.35: 1.15 in the mean, 8 of 200 below 0.96, most
+// of them with five row groups (0.78 at one, 8 of 31 k to 39 k above rank 32); beyond 0.75 to 1.6 (11 of 4 k to 33 k, rank 24, four
+// row groups 516 / 690).  Unknown ones, up to rank 32: from five places per sequence on 1.1 in the mean, 0.87 to 0.94 at 4 of 54,
+// below that 0.82 to 1.33, worst where the sequences are long and even, since the grid then has four rounds of equal workgroups
+// (10 of 32 k to 38 k 304 / 365); above rank 32, one workgroup per unit, 1.0 to 1.7.
 static void plan_batch(Plan& pl, const lra_shape* sh, const lra_cache* c, bool key_adapter) {
   constexpr int kMost = 64;  // sequences: one per lane
   if (c->n_seqs > kMost) return;
@@ -409,7 +414,7 @@ static void plan_batch(Plan& pl, const lra_shape* sh, const lra_cache* c, bool k
       for (int t = 0; t < c->n_seqs; ++t) n += tiles[t] > share ? (tiles[t] + share - 1) / share : 1;
       return n <= places;
     };
-    const int64_t even = (total + places - 1) / places, balanced = (total * (one ? 27 : 40) + places * 20 - 1) / (places * 20);
+    const int64_t even = (total + places - 1) / places, balanced = (total * (one || rope ? 27 : 40) + places * 20 - 1) / (places * 20);
     int lo = static_cast<int>(even > least ? even : least);
     int hi = static_cast<int>(balanced > grid_tiles ? balanced : grid_tiles);  // the largest share that is worth it
     hi = hi > longest ? longest : hi;
@@ -420,7 +425,7 @@ static void plan_batch(Plan& pl, const lra_shape* sh, const lra_cache* c, bool k
       else lo = mid + 1;
     }
     size = hi;
-  } else if (places < 2 * c->n_seqs) {
+  } else if (places < (rope && !one && sh->rank <= 32 ? 5 : 2) * c->n_seqs) {
     return;
   }
   if (rope && (total > 0 ? size : static_cast<int64_t>(longest) * c->n_seqs / (2 * places)) < 3) return;

@@ -317,6 +317,9 @@ int main(int argc, char** argv) {
       {spread(56, 2000, 20000), 8, 4, 4, false, false, 0.f},  {spread(64, 2000, 20000), 8, 4, 1, false, false, 0.f},
       {spread(24, 2000, 36000), 8, 4, 4, true, true, 0.f},    {spread(64, 2000, 20000), 2, 8, 4, true, true, 0.f},
       {spread(12, 2000, 40000), 32, 1, 4, false, false, 0.f}, {spread(12, 2000, 40000), 8, 4, 16, true, true, 0.f},
+      // rotary, several row groups: four, uneven; three, even; three with places enough
+      {spread(11, 4000, 33000), 8, 4, 8, false, false, 1e4f}, {spread(10, 32000, 38000), 8, 4, 6, true, false, 1e4f},
+      {spread(4, 3000, 17000), 8, 4, 6, true, true, 1e4f},
       // in place at once
       {{670, 500, 520, 530}, 2, 8, 9, false, false, 0.f},     {{6000, 5600, 5700}, 2, 8, 9, true, true, 0.f}};
   for (int it = 0; it < static_cast<int>(sizeof(batch_cases) / sizeof(batch_cases[0])); ++it) {
