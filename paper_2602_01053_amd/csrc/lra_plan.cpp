@@ -39,8 +39,9 @@ bool plan_sizes_fit(const lra_shape* sh, const lra_cache* c, int32_t tokens, int
 // 15.2, 449 to 512 19.6 / 16.3, 513 to 576 (a second round) 20.1 / 27.7; 4 kv heads on 3584, 449 to 576 13.9 / 13.9, 833 to 958
 // 17.3 / 15.1; 8 of 64 on 2048, 321 to 448 9.9 / 9.3, 833 to 960 12.7 / 10.1; 12 on 2048, 257 to 320 12.9 / 9.8; 32 on 4096, 65 to
 // 128 20.1 / 16.5.  On the line itself a second token tile that is mostly empty is not worth it: 12 on 2048, 65 to 80 tokens
-// 8.5 / 8.8, 96 8.9 / 8.8, 128 9.5 / 9.1.  With eight feature tiles or fewer, most of which then carry L features, nothing is left of it in a full
-// round (2 kv heads on 2048, 1473 to 1726 tokens 12.5 / 11.6, 1731 to 1980 12.3 / 12.5).
+// 8.5 / 8.8, 96 8.9 / 8.8, 128 9.5 / 9.1.  With eight feature tiles or fewer, most of which then carry L features, to 216
+// tiles: 2 kv heads on 2048, 1473 to 1726 tokens 12.9 / 8.8, 1624 to 1728, where d_model is not divided, 10.1 / 8.9 (beyond 216 the
+// kernel was not faster when it still read x from beyond L2 there, 12.3 / 12.5, and has not been measured since).
 bool append_quarter_tiles(int n_new, int n_kv_heads, int head_dim, int rank, int d_model, const Tuning& tune) {
   if (tune.append_k_splits > 1 || tune.append_tile != 0 || tune.append_stages != 0) return false;
   if (n_new < 1 || n_new <= tune.append_skinny || n_new > (1 << 20) || d_model % 128 != 0) return false;

@@ -443,7 +443,8 @@ QUARTER_CASES = [
     (70000, 161, 640, 3, 128, 16, 500000.0, False),   # five steps, one more than the ring holds; far positions
     (900, 320, 1024, 8, 128, 64, 0.0, True),          # four L blocks, unrotated keys
     (2000, 511, 4096, 8, 128, 16, 500000.0, False),   # a full round of the chip
-    (1500, 1025, 128, 1, 128, 16, 10000.0, True),     # four feature tiles, all with L blocks
+    (1500, 1025, 128, 1, 128, 16, 10000.0, True),     # four feature tiles, all with L blocks; more tokens than features: an XCD's stretch by tokens
+    (900, 833, 256, 3, 64, 16, 500000.0, False),      # ... 84 tiles on 8 XCDs, the last stretch four short
 ]
 
 
