@@ -305,7 +305,8 @@ static bool prefill_rows_reads(const lra_shape* sh, const lra_cache* c, bool spl
 //     to 1.5; 9 to 13 with a second round half full 1.0 to 1.4; 14 and more on the edge of that, 384 workgroups, 0.85 to 1.0,
 //     at ranks up to 16 beyond it 14 1.0, 15 to 20 0.92 to 1.2, at the higher ones to 20 0.99 to 1.25 (399 tokens on 1270: 1.27;
 //     378 on 5006 54.5 / 64.3 us).  At 512 keys and less 0.94 to 0.97 at ranks up to 16 under 448 workgroups, 1.0 to 1.2 from
-//     there, at the higher ones 1.0 to 1.2 (0.94 at one of ten).
+//     there (rotary, with the pre-pass in front of either: 0.91 to 0.96 at 4 of 5, 248 on 360 18.0 / 19.8), at the higher ones 1.0
+//     to 1.2 (0.94 at one of ten).
 //   three rounds and more: 0.7 to 1.2, mostly below 1.
 //   calls of the size the split-KV path takes, two launches and 8.5 to 9.5 us of GPU time there, from 520 more.  From 8 kv heads
 //     on: one row tile per kv head 1.0 to 1.4 up to 384 keys, 0.93 to 1.1 to 512 (above 16 kv heads 1.01 to 1.2 from 7
@@ -327,7 +328,7 @@ static bool prefill_waves_divide_keys(const lra_shape* sh, const lra_cache* c, i
   if (w <= kCUs) return steps <= 4 || steps * (sh->n_kv_heads > 16 ? 12 : 8) <= w;
   if (w > 2 * kCUs) return false;
   const bool wide = sh->rank > 16;
-  if (steps <= 2) return wide || w >= 448;
+  if (steps <= 2) return wide || (w >= 448 && sh->key_rope_theta <= 0.f);
   if (steps <= 8) return steps <= 6 || wide || w >= 320;
   return w >= 384 && steps <= (w < 400 ? 13 : (wide ? 20 : 14));
 }

@@ -366,6 +366,7 @@ int main(int argc, char** argv) {
       {8, 4, 16, 433, 512, false, 0.f},  {8, 4, 16, 448, 512, true, 0.f},   {8, 4, 16, 257, 1536, true, 0.f}, {8, 4, 16, 257, 1537, false, 0.f},
       {8, 4, 16, 320, 2048, true, 0.f},  {8, 4, 16, 312, 2048, false, 0.f}, {8, 4, 16, 384, 3328, true, 0.f}, {8, 4, 24, 384, 3329, false, 0.f},
       {8, 4, 16, 512, 3584, true, 0.f},  {8, 4, 16, 512, 3585, false, 0.f},
+      {8, 8, 8, 248, 360, true, 0.f},    {8, 8, 8, 248, 360, false, 1e4f},  {8, 8, 24, 248, 360, true, 1e4f},
       // the split-KV path's sizes
       {8, 4, 16, 8, 384, true, 0.f},     {8, 4, 16, 8, 385, false, 0.f},    {32, 1, 16, 8, 512, true, 0.f},   {32, 1, 16, 8, 513, false, 0.f},
       {32, 1, 16, 6, 384, true, 0.f},    {32, 1, 16, 6, 385, false, 0.f},
