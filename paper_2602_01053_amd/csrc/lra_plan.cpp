@@ -362,6 +362,7 @@ static int plan_wave_shares(const lra_shape* sh, const lra_cache* c, int tokens,
     if (n < 360 * shares || (row_tiles < 5 && c->block_size == 0 && sh->n_kv_heads <= 16)) return 0;
     most = sh->n_kv_heads > 16 ? 4 : (row_tiles % 4 == 1 ? 12 : (row_tiles == 2 || row_tiles % 4 == 0 ? 6 : (row_tiles % 4 == 2 ? 11 : 7)));
   }
+  // (room: the partial states per row that the path it replaces keeps, which is what callers' workspaces are sized for)
   if (n > most * 256 * shares || shares > room || shares < 2) return 0;
   return static_cast<int>(shares);
 }
@@ -379,14 +380,15 @@ static int plan_wave_shares(const lra_shape* sh, const lra_cache* c, int tokens,
 //     heads 177 / 162), from there 0.86 to 1.26, 0.28 to 0.4 beyond 8; with several row groups, whose keys the row's layout
 //     reads once, 0.93 to 1.8 to a factor of 2 (10 of 6 k to 8 k, own low-rank caches 67.7 / 45.6), 0.36 at 16.  Shares no
 //     longer than the grid's are taken whatever the factor: 0.98 to 1.9.
-//   unknown lengths: from two places per sequence on 0.98 to 1.7, one long sequence among many short ones with it 1.0 to 2.6
-//     (0.93 at worst: 40000 among 25 of 4000, 117.6 / 126.2), below that 0.74 to 1.5 (62 of 0.1 k to 7.7 k: 96 / 130).
+//   unknown lengths: from two places per sequence on 0.97 to 1.7, one long sequence among many short ones with it 1.0 to 2.6
+//     (below that 4 of 400: 40000 among 25 of 4000 117.6 / 126.2, 10 of 9 k to 18 k, three row groups 55.1 / 63.3); with fewer
+//     places 0.74 to 1.5 (62 of 0.1 k to 7.7 k: 96 / 130).
 // The rotary forms, whose steps are long against everything else, gain from three tiles on (13 of 0.6 k to 2.7 k: 38.3 /
 // 31.6) and lose up to 8 % at two.  What bounds them is the vector unit and not the keys, so that with several row groups only
-// the balance counts (560 batches, several row groups).  Known lengths, to 1.35: 1.15 in the mean, 8 of 200 below 0.96, most
+// the balance counts (560 batches, several row groups).  Known lengths, to 1.35: 1.18 in the mean, 7 of 202 below 0.96, most
 // of them with five row groups (0.78 at one, 8 of 31 k to 39 k above rank 32); beyond 0.75 to 1.6 (11 of 4 k to 33 k, rank 24, four
-// row groups 516 / 690).  Unknown ones, up to rank 32: from five places per sequence on 1.1 in the mean, 0.87 to 0.94 at 4 of 54,
-// below that 0.82 to 1.33, worst where the sequences are long and even, since the grid then has four rounds of equal workgroups
+// row groups 516 / 690).  Unknown ones, up to rank 32: from five places per sequence on 1.1 to 1.2 in the mean, 0.87 to 0.94 at 4 of
+// 80, below that 0.82 to 1.33, worst where the sequences are long and even, since the grid then has four rounds of equal workgroups
 // (10 of 32 k to 38 k 304 / 365); above rank 32, one workgroup per unit, 1.0 to 1.7.
 static void plan_batch(Plan& pl, const lra_shape* sh, const lra_cache* c, bool key_adapter) {
   constexpr int kMost = 64;  // sequences: one per lane
