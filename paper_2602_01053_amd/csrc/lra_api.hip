@@ -57,6 +57,7 @@ static void fill_params(Params& p, const lra_shape* sh, const lra_cache* c, cons
   p.row_groups = pl.row_groups;
   p.split_keys = pl.split_keys;
   p.n_splits = pl.n_splits;
+  p.split_more = pl.split_more;
   p.scale = sh->scale > 0.f ? sh->scale : 1.0f / std::sqrt(static_cast<float>(sh->head_dim));
   p.key_rope_theta = sh->key_rope_theta;
 #ifdef LRA_TIMING

@@ -55,6 +55,7 @@ struct Params {
   int32_t tile_group, tile_heads, tiles_per_round, row_mul;
   // decode_batch_kernel: workgroups per (kv head, row group), 128-key tiles of a share (0: from the lengths), their least
   int32_t batch_wgs, batch_tiles, batch_min_tiles;
+  int32_t split_more;  // rotary form of decode_mfma_kernel: 0, or the splits that hold split_keys, those behind them 128 keys less
 #ifdef LRA_TIMING
   unsigned long long* timing;  // instrumented test build only: per-wave phase stamps
 #endif

@@ -13,6 +13,7 @@
 // begins; batch_min_tiles keeps the longest sequence within p.n_splits partial states.  A sequence's last workgroup
 // leaves the states behind its own empty.
 #include "lra_common.h"
+#include "lra_decode_rope.h"
 #include "lra_decode_util.h"
 #include "lra_plan.h"
 #include "lra_prefill_util.h"
@@ -32,7 +33,7 @@ __device__ __forceinline__ int scan_lanes(int v) {
 
 // One share.  (A function of its own: with the body's text in the kernel itself a step took 1.5 % longer, 32 sequences of
 // 300 to 40000 tokens 91.7 and 93.4 us.)
-template <int D, int RT, int RP, bool HAS_BK, int RPE, bool PA>
+template <int D, int RT, int RP, bool HAS_BK, bool PA>
 __device__ __forceinline__ void decode_share(const Params& p, const int h, const int t, const int rg, const int split, const int j0,
                                              const int keys, const bool last_of_seq, const int first_query, const int end_query) {
   constexpr bool PAGED = true, CAUSAL = false, LAST = true;
@@ -70,9 +71,10 @@ __global__ __launch_bounds__(256, RPE == 64 ? 1 : 2) void decode_batch_kernel(Pa
   const int t = __builtin_popcountll(__builtin_amdgcn_ballot_w64(end <= w) & (p.n_seqs == 64 ? ~0ull : (1ull << p.n_seqs) - 1));
   const int n = __builtin_amdgcn_readlane(shares, t), idx = w - (__builtin_amdgcn_readlane(end, t) - n);
   const int all = __builtin_amdgcn_readlane(tiles, t), len = all / n, more = all - len * n;  // the first `more` shares hold a tile more
-  decode_share<D, RT, RP, HAS_BK, RPE, PA>(p, h, t, rg, idx, (idx * len + min(idx, more)) * 128, (len + (idx < more ? 1 : 0)) * 128, idx == n - 1,
-                                           t > 0 ? __builtin_amdgcn_readlane(q_start, t) : 0,
-                                           t + 1 < p.n_seqs ? __builtin_amdgcn_readlane(q_next, t) : p.n_queries);
+  const int j0 = (idx * len + min(idx, more)) * 128, keys = (len + (idx < more ? 1 : 0)) * 128;
+  const int first = t > 0 ? __builtin_amdgcn_readlane(q_start, t) : 0, last = t + 1 < p.n_seqs ? __builtin_amdgcn_readlane(q_next, t) : p.n_queries;
+  if constexpr (RPE > 0) decode_rope_share<D, RPE, true, false, true>(p, h, t, rg, idx, j0, keys, idx == n - 1, first, last);
+  else decode_share<D, RT, RP, HAS_BK, PA>(p, h, t, rg, idx, j0, keys, idx == n - 1, first, last);
 }
 
 template <int D, int RT, int RP>
@@ -89,12 +91,13 @@ static void launch_batch2(const Params& p, dim3 grid, hipStream_t s) {
   }
 }
 
-// (at d = 128 the tiles of four agents' B_K^T operands, ranks up to 16 and above 32, leave no registers for this form)
+// (at d = 128 the B_K^T operands of ranks above 32 leave no registers for this form)
 static hipError_t launch_batch_rope(const Params& p, dim3 grid, hipStream_t s) {
   const dim3 block(256);
   if (p.head_dim == 128) {
-    if (p.rank <= 16 || p.rank > 32) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((decode_batch_kernel<128, 1, 32, true, 32, false>), grid, block, 0, s, p);
+    if (p.rank > 32) return hipErrorInvalidValue;
+    if (p.rank <= 16) hipLaunchKernelGGL((decode_batch_kernel<128, 1, 32, true, 16, false>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((decode_batch_kernel<128, 1, 32, true, 32, false>), grid, block, 0, s, p);
   } else if (p.rank <= 16) {
     hipLaunchKernelGGL((decode_batch_kernel<64, 1, 32, true, 16, false>), grid, block, 0, s, p);
   } else if (p.rank <= 32) {

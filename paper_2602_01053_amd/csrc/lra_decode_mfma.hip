@@ -30,6 +30,7 @@
 // the end (flash-decoding rule) and one partial (m, l, O, O_lr) per workgroup
 // goes to the workspace.
 #include "lra_common.h"
+#include "lra_decode_rope.h"
 #include "lra_decode_util.h"
 #include "lra_plan.h"
 #include "lra_prefill_util.h"
@@ -43,31 +44,19 @@ namespace lra {
 // keys up to n - n_new + i (the mask of Alg. 1); a long context is then split over the whole chip
 // like any decode call instead of being walked by one workgroup per q head.
 //
-// RPE > 0 is the rotary key side, K_j = K_base,j + RoPE_j(L_j B_K) (what App. D.1 leaves to the
-// key cache because the rotation stands between L_j and B_K): the L.Qt term of the scores is
-// replaced, per 16-key tile and agent slot, by
-//   E^T[f][key]   = B_K^T[f][:] . L^T[:][key]                 (MFMA, C layout: lane = key)
-//   rotate the pairs (f, f + D/2) of E^T by the key's angle   (registers, sine/cosine shared by the slots)
-//   S^T[key][row] += rot(E)[key][f] . Q[row][f]                (MFMA; the C layout of E^T is the
-//                                                              A layout of this product)
-// with Q masked to the rows of the slot.  The B_K^T operands of NS agent slots stay in
-// registers (RPE = padded rank of that product: 16, 32 or 64, for 4, 2 or 4 slots per tile - at
-// 64 the LDS leaves room for one workgroup per CU only, whose waves then have 512 registers);
-// in the causal form all rows belong to the one adapter of the call.
+// RPE > 0 is the rotary key side (lra_decode_rope.h): 16, 32 or 64, the padded rank of its E product, for 4, 2 or 4 agent slots
+// per tile with operands in registers; at 64 one workgroup fills a compute unit and its waves have 512 registers.
 //
 // PA = true is the decode form for one low-rank cache per adapter (BaseShared, Sec. 3.2) outside the rotary key
 // side: the L tile is a row of column blocks [agent slot][32 keys][l_block ranks], block s requested from the cache
 // of the adapter of agent slot s; Qt of a row stands in the block of its slot and is zero elsewhere, so the same
 // products give Qt_a . L_a^T and P . L_a per agent, and a row keeps only its own block of O_lr.  K_base and V_base are
 // then read once for all agents of a tile, and no zero padding is streamed.
-// The body as a function of its own, for the forms whose registers come out better behind that boundary (us at the text /
-// at the function): rotary on paged caches, rank 8, one agent on 9001 tokens, 4 kv heads 22.2 / 19.1, 4 agents, 8 kv heads
-// 32.7 / 28.3, rank 64 36.8 / 35.1; rotary up to rank 16 with several row groups, 8 agents on 30000 71.6 / 66.3; value-only
-// adapters with their own low-rank caches on pages, d = 64, 20.0 / 19.7.  The other forms stand at the text: rotary above rank
-// 32 on contiguous caches, 4 agents on 2000, 4 kv heads 17.5 / 18.2 (14 to 16 registers in scratch memory against 32).
-template <bool PAGED, bool HAS_BK, int RPE, bool PA, bool RGI>
-constexpr bool kDecodeByFunction = (RPE > 0 && (PAGED || (RPE == 16 && RGI))) || (PA && PAGED && !HAS_BK);
-template <int D, int RT, int RP, bool PAGED, bool HAS_BK, bool CAUSAL, int RPE, bool PA>
+// The body as a function of its own, for the form whose registers come out better behind that boundary: value-only adapters
+// with their own low-rank caches on pages, d = 64, 20.0 us at the text, 19.7 at the function.
+template <bool PAGED, bool HAS_BK, bool PA>
+constexpr bool kDecodeByFunction = PA && PAGED && !HAS_BK;
+template <int D, int RT, int RP, bool PAGED, bool HAS_BK, bool CAUSAL, bool PA>
 __device__ __forceinline__ void decode_mfma_keys(const Params& p, const int h, const int t, const int rg, const int split,
                                                  const int j0, const int keys) {
   const int lane = threadIdx.x & 63;
@@ -77,11 +66,7 @@ __device__ __forceinline__ void decode_mfma_keys(const Params& p, const int h, c
 #include "lra_decode_mfma_body.h"
 }
 
-// RGI = false leaves out the grid layout for several row groups (below).  The rotary forms sit at the edge of their
-// register file, and the few instructions of that layout at the top of the kernel were enough to move their
-// allocation (config 2 with the rotary key side: 21.9 -> 23.3 us per call): they are built both ways and take the
-// layout only when a call has several row groups.
-template <int D, int RT, int RP, bool PAGED, bool HAS_BK, bool CAUSAL, int RPE = 0, bool PA = false, bool RGI = true>
+template <int D, int RT, int RP, bool PAGED, bool HAS_BK, bool CAUSAL, int RPE = 0, bool PA = false>
 __global__ __launch_bounds__(256, RPE == 64 ? 1 : 2) void decode_mfma_kernel(Params p) {
   [[maybe_unused]] const int lane = threadIdx.x & 63;
   [[maybe_unused]] const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -91,7 +76,7 @@ __global__ __launch_bounds__(256, RPE == 64 ? 1 : 2) void decode_mfma_kernel(Par
   int split = blockIdx.y;
   int t = CAUSAL ? p.seq_index : blockIdx.z / p.row_groups;
   int rg = CAUSAL ? blockIdx.z : blockIdx.z - t * p.row_groups;
-  if constexpr (RGI) if (p.rg_interleave > 0) {
+  if (p.rg_interleave > 0) {
     // Several row groups share the keys of a (sequence, kv head, key share): only the first to ask reads them from
     // HBM if the others ask the same L2 soon after.  Workgroups go round-robin over the 8 XCDs in the order of
     // their linear index x + Hkv * y, so with m = lcm(8, Hkv) / Hkv and y = (share mod m) + m * (row group +
@@ -105,8 +90,15 @@ __global__ __launch_bounds__(256, RPE == 64 ? 1 : 2) void decode_mfma_kernel(Par
     t = CAUSAL ? p.seq_index : blockIdx.z;
     if (split >= p.n_splits) return;
   }
-  if constexpr (kDecodeByFunction<PAGED, HAS_BK, RPE, PA, RGI>) {
-    decode_mfma_keys<D, RT, RP, PAGED, HAS_BK, CAUSAL, RPE, PA>(p, h, t, rg, split, split * p.split_keys, p.split_keys);
+  if constexpr (RPE > 0) {
+    int j0 = split * p.split_keys, keys = p.split_keys;
+    if (p.split_more > 0 && split >= p.split_more) {
+      j0 -= (split - p.split_more) * 128;
+      keys -= 128;
+    }
+    decode_rope_share<D, RPE, PAGED, CAUSAL, false>(p, h, t, rg, split, j0, keys, false, 0, 0);
+  } else if constexpr (kDecodeByFunction<PAGED, HAS_BK, PA>) {
+    decode_mfma_keys<D, RT, RP, PAGED, HAS_BK, CAUSAL, PA>(p, h, t, rg, split, split * p.split_keys, p.split_keys);
   } else {
     constexpr bool LAST = false, last_of_seq = false;
     constexpr int first_query = 0, end_query = 0;
@@ -151,15 +143,11 @@ template <int D, int RP, int RPE>
 static hipError_t launch_rope(const Params& p, dim3 grid, hipStream_t s) {
   const bool paged = p.block_size != 0;
   if (p.is_prefill) {
-    // (launch_decode_mfma keeps the plain grid for these)
-    if (paged) hipLaunchKernelGGL((decode_mfma_kernel<D, 1, RP, true, true, true, RPE, false, false>), grid, dim3(256), 0, s, p);
-    else hipLaunchKernelGGL((decode_mfma_kernel<D, 1, RP, false, true, true, RPE, false, false>), grid, dim3(256), 0, s, p);
-  } else if (p.rg_interleave > 0) {
-    if (paged) hipLaunchKernelGGL((decode_mfma_kernel<D, 1, RP, true, true, false, RPE, false, true>), grid, dim3(256), 0, s, p);
-    else hipLaunchKernelGGL((decode_mfma_kernel<D, 1, RP, false, true, false, RPE, false, true>), grid, dim3(256), 0, s, p);
+    if (paged) hipLaunchKernelGGL((decode_mfma_kernel<D, 1, RP, true, true, true, RPE>), grid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((decode_mfma_kernel<D, 1, RP, false, true, true, RPE>), grid, dim3(256), 0, s, p);
   } else {
-    if (paged) hipLaunchKernelGGL((decode_mfma_kernel<D, 1, RP, true, true, false, RPE, false, false>), grid, dim3(256), 0, s, p);
-    else hipLaunchKernelGGL((decode_mfma_kernel<D, 1, RP, false, true, false, RPE, false, false>), grid, dim3(256), 0, s, p);
+    if (paged) hipLaunchKernelGGL((decode_mfma_kernel<D, 1, RP, true, true, false, RPE>), grid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((decode_mfma_kernel<D, 1, RP, false, true, false, RPE>), grid, dim3(256), 0, s, p);
   }
   return hipGetLastError();
 }
@@ -172,8 +160,7 @@ hipError_t launch_decode_mfma(const Params& p, int row_tiles, bool allow_stream_
   dim3 grid(p.n_kv_heads, p.n_splits, (p.is_prefill ? 1 : p.n_seqs) * p.row_groups);
   Params pi = p;
   pi.rg_interleave = 0;
-  const bool rope_prefill = p.is_prefill && p.key_rope_theta > 0.f && p.b_k != nullptr;  // (built without that layout)
-  if (p.row_groups > 1 && !rope_prefill) {
+  if (p.row_groups > 1) {
     // (see the kernel: row groups of a key share next to each other on one XCD)
     int g = p.n_kv_heads, e = 8;
     while (e) { const int tmp = g % e; g = e; e = tmp; }  // g = gcd(Hkv, 8)

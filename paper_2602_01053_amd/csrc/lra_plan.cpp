@@ -243,33 +243,27 @@ static bool short_prefill_walks_tiles(const lra_shape* sh, const lra_cache* c, i
   return tokens * G <= 96 || (walk < 8 ? units >= 12 && n >= 8192 : n >= 4096);
 }
 
-// Keys per share where one sequence in the rotary form of the split-KV kernel runs with two workgroups per compute
-// unit rather than one, else 0: its steps are a chain of dependent products and rotations that only a second wave per
-// SIMD covers, but the partial states double.  Measured on MI355X over 1500 decode calls, the ratio of the times with
-// one and with two: up to 64 shares (which one merge kernel takes) 1.0 to 1.5 with shares of 384 keys and more (0.92
-// for 72 rows of a kv head on 50000); with 256 at ranks up to 16 1.04 to 1.26 where one per unit has 512, 0.94 to
-// 1.08 where it has 384, at rank 32 0.92 to 1.01; with 128 at least 1.01 up to 2048 (row, share) states; beyond 64
-// shares 0.71 to 1.08 with 128 and 256 keys, at least 1.02 with 384 where one workgroup per unit makes more than 64
-// too, and where it does not 0.94 to 1.22 with 512 (rank 32 the lower) and at least 1.0 with 640.  Prefills of a few
-// tokens gain 1.03 to 1.6 from shares of 384 keys on (8 kv heads, 16 after 9000: 30.1 -> 26.2 us; 0.94 to 0.97 at
-// three of 720 calls) and lose up to 13 % below (4 kv heads, 4 after 16000: 18.5 and 21.3 us).
-// at_once: where units x shares, rounded up, pass two per compute unit the share grows by key tiles until they fit
-// (24 units, rank 32, us with 21 shares of 13009 keys 28.7, with 22 of 13463 38.6 and with one workgroup per unit
-// 35.7; 1440 calls 1.06 in the mean, up to 1.69).  Not in decode at d = 64, where units hold more than two: 0.91 to 1.
-static int64_t rope_two_per_unit_keys(int max_seq_len, int64_t work, int tile, int64_t rows, int rank, bool prefill,
-                                      bool at_once) {
-  auto share_keys = [&](int64_t wgs) {  // as the plan rounds them
-    const int64_t sk = (work * max_seq_len + wgs - 1) / wgs;
-    return work >= 2 * wgs || sk > max_seq_len ? (max_seq_len + int64_t{tile} - 1) / tile * tile : (sk + tile - 1) / tile * tile;
-  };
-  const int64_t one = (max_seq_len + share_keys(kCUs) - 1) / share_keys(kCUs);
-  int64_t sk = share_keys(2 * kCUs);
-  while (at_once && sk < max_seq_len && work * ((max_seq_len + sk - 1) / sk) > 2 * kCUs) sk += tile;
-  const int64_t two = (max_seq_len + sk - 1) / sk;
-  bool pays = sk >= 384 || (sk >= 256 ? rank <= 16 && share_keys(kCUs) >= 512 : rows * two <= 2048);
-  if (two > 64) pays = sk >= (one > 64 ? 384 : (rank <= 16 ? 512 : 640));
-  if (prefill) pays = sk >= 384 && two <= 64;
-  return pays ? sk : 0;
+// The shares of one sequence in the rotary form of the split-KV kernel at ranks up to 32, two workgroups per compute unit
+// (n = 0: one workgroup per unit).  Its steps are long and a unit takes as long as its two workgroups together, the first
+// and the 257th to start, so what counts is the load of a unit in key tiles: the least one there is, halved between the
+// two, an odd tile in the first.  Where that is the load of one workgroup per unit as well, two still cover each other's
+// dependent steps, and the partial states double.
+// us with one workgroup per unit / two, shares of one size / two, divided like this (8 kv heads of 128, rank 16, 4 agents on
+// 9000 keys, 3 tiles a unit: 24 shares 20.3, 64 20.3, 40 18.9; on 20011: 32 29.6, 53 31.0, 63 27.6; on 60000: 32 70.1, 59 64.5, 64
+// 59.9; 8 agents, two row groups, on 5000: 16 21.3, 24 18.6; on 33000: 16 74.4, 32 58.5; rank 32, 2 agents on 9000: 18.1,
+// 40 16.9).  Not beyond 64 shares, which one merge kernel takes (4 kv heads on 60000: 64 shares 29.2, 128 35.0), and 128 keys
+// only for up to 2048 (row, share) states; prefills of a few tokens from 384 keys on.
+struct RopeShares {
+  int keys, n, more;  // keys of the largest, shares, how many are of that size where the rest hold 128 less (0: all)
+};
+static RopeShares rope_two_per_unit(int max_seq_len, int64_t work, int64_t rows, bool prefill) {
+  const int64_t tiles = (static_cast<int64_t>(max_seq_len) + 127) / 128, units = work > 0 ? kCUs / work : 0;
+  const int64_t load = units > 0 ? (tiles + units - 1) / units : 0, first = (load + 1) / 2;
+  const bool odd = (load & 1) != 0;
+  if (load < 2) return {0, 0, 0};
+  const int64_t n = odd ? units + (tiles - units * first + first - 2) / (first - 1) : (tiles + first - 1) / first;
+  if (n > 64 || (prefill ? first < 3 : first < 2 && rows * n > 2048)) return {0, 0, 0};
+  return {static_cast<int>(first * 128), static_cast<int>(n), odd ? static_cast<int>(units) : 0};
 }
 
 // What prefill_rows_kernel reads: ranks up to 32, and a cache within 32-bit byte offsets of one resource; the completed
@@ -394,7 +388,7 @@ static void plan_batch(Plan& pl, const lra_shape* sh, const lra_cache* c, bool k
   constexpr int kMost = 64;  // sequences: one per lane
   if (c->n_seqs > kMost) return;
   const bool rope = sh->key_rope_theta > 0.f && key_adapter, one = pl.row_groups == 1;
-  if (rope && sh->head_dim == 128 && (sh->rank <= 16 || sh->rank > 32)) return;  // (built without: its registers go to scratch memory)
+  if (rope && sh->head_dim == 128 && sh->rank > 32) return;  // (built without: its registers go to scratch memory)
   const int64_t units = static_cast<int64_t>(sh->n_kv_heads) * pl.row_groups;
   const int64_t places = (rope && sh->rank > 32 ? kCUs : 2 * kCUs) / units;
   if (places < c->n_seqs) return;
@@ -577,6 +571,7 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
     want = rope && key_adapter ? kCUs * 8 : kCUs * 3;
   }
   int split_keys = tune.split_keys;
+  RopeShares two{0, 0, 0};
   if (split_keys <= 0 && pl.mfma) {
     // Measured on MI355X: one sequence runs best with about one workgroup per CU (the
     // per-workgroup prologue is not amortised otherwise); a ragged batch wants about four
@@ -588,14 +583,11 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
     // as long as a share then still has 512 keys (32768 tokens x 8 kv heads: 35.7 against 38.6 us, 65536: 49.2
     // against 53.7; at 256 keys per share the doubling loses)
     if (!batch && !prefill && c->block_size != 0 && !rope && work * c->max_seq_len >= int64_t{2} * kCUs * 512) wgs = 2 * kCUs;
-    // ... and one sequence in the rotary form at ranks up to 32 likewise (see rope_two_per_unit_keys).  Above rank 32 a
-    // unit holds one workgroup.  Nor without a B_K: nothing is rotated then, and one workgroup per unit keeps the
-    // streaming form.
-    const int64_t two_per_unit = !batch && rope_split && key_adapter && sh->rank <= 32
-                                     ? rope_two_per_unit_keys(c->max_seq_len, work, tile, pl.rows, sh->rank, prefill,
-                                                              prefill || sh->head_dim == 128) : 0;
-    if (two_per_unit > 0) {
-      split_keys = static_cast<int>(two_per_unit < c->max_seq_len ? two_per_unit : c->max_seq_len);
+    // ... and one sequence in the rotary form at ranks up to 32 likewise.  Above rank 32 a unit holds one workgroup.  Nor
+    // without a B_K: nothing is rotated then, and one workgroup per unit keeps the streaming form.
+    if (!batch && rope_split && key_adapter && sh->rank <= 32) two = rope_two_per_unit(c->max_seq_len, work, pl.rows, prefill);
+    if (two.n > 0) {
+      split_keys = two.keys < c->max_seq_len ? two.keys : c->max_seq_len;
     } else if (work >= 2 * wgs) {
       split_keys = c->max_seq_len;  // more units than workgroups wanted: one share per sequence
     } else {
@@ -689,6 +681,10 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
   if (!pl.mfma) pl.l_block = 0;
   pl.split_keys = split_keys;
   pl.n_splits = static_cast<int>((static_cast<int64_t>(c->max_seq_len) + split_keys - 1) / split_keys);
+  if (pl.mfma && two.n > 0 && split_keys == two.keys) {
+    pl.n_splits = two.n;
+    pl.split_more = two.more;
+  }
   if (pl.mfma && !prefill && c->block_size != 0 && c->n_seqs > 1 && tune.variant == 0 && tune.split_keys <= 0)
     plan_batch(pl, sh, c, key_adapter);
   // grids: (kv head, share, sequence x row group) for the MFMA kernels, (row, share) otherwise

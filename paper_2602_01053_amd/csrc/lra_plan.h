@@ -34,6 +34,7 @@ struct Plan {
   int rows;        // query rows = (queries | new tokens) x Hq
   int split_keys;  // keys per split
   int n_splits;    // splits per sequence at max_seq_len
+  int split_more;  // 0: all splits alike; else only the first so many hold split_keys, those behind them 128 keys less
   bool split_kv_sized;  // prefill: few new tokens behind a context, the sizes the split-KV path is for (whatever path it takes)
   bool wave_rows;  // prefill: workgroups of 32 rows whose waves divide the keys (prefill_rows_kernel), whatever the rest says
   int wave_shares;  // ... or, if not 0, that kernel with this many workgroups dividing the keys of 32 rows, then the merge kernel
