@@ -1,5 +1,5 @@
 // Split-KV decode kernel for calls that give every compute unit at most one workgroup
-// (bf16, gfx950): one sequence in a contiguous cache, no rotary key side.
+// (bf16, gfx950): one sequence, contiguous or paged, no rotary key side.
 //
 // Same arithmetic and data layout as decode_mfma_kernel (the inner loop of Alg. 1 with the
 // App. D.1 key-side reordering, scores computed transposed, all agents x GQA rows of a kv
@@ -54,9 +54,9 @@ namespace lra {
 // LDS bytes of one workgroup of decode_stream_kernel<D, RT, RP>: the tile stages and nothing else.
 constexpr int decode_stream_lds_bytes(int D, int RP) { return 4 * 2 * (2 * 32 * D * 2 + 32 * RP * 2); }
 
-template <int D, int RT, int RP, bool HAS_BK, bool CAUSAL, bool PA, bool SI = false>
-__global__ __launch_bounds__(512, 2) void decode_stream_kernel(Params p) {
-  static_assert(!PA || (!CAUSAL && RT == 1), "per-adapter low-rank caches: decode form, one row tile");
+template <int D, int RT, int RP, bool HAS_BK, bool CAUSAL, bool PA, bool SI, bool PAGED>
+__device__ __forceinline__ void decode_stream(const Params& p) {
+  static_assert(!PA || (!CAUSAL && RT == 1 && !PAGED), "per-adapter low-rank caches: decode form, one row tile, contiguous");
   constexpr int NW = 4;            // streaming waves; waves NW .. 2 NW - 1 are the prologue waves
   constexpr int KS = D / 32;       // MFMA k-steps over the head dimension
   constexpr int RKS = RP / 32;     // MFMA k-steps over the (padded) rank
@@ -127,8 +127,27 @@ __global__ __launch_bounds__(512, 2) void decode_stream_kernel(Params p) {
   const int split = p.share_major ? by * 8 + (bx & 7) : by;
   const int rg = blockIdx.z;
   if (split >= p.n_splits) return;  // (share_major pads the key shares to a multiple of 8)
-  const int t = CAUSAL ? p.seq_index : 0;                      // contiguous caches hold one sequence
+  const int t = CAUSAL ? p.seq_index : 0;                      // (decode: one sequence)
   const int32_t len_t = CONST_I32(p.seq_lens)[t];
+  const int j0 = split * p.split_keys;
+  const int kpw = p.split_keys / NW;  // keys per wave, a multiple of 32
+  // Paged cache: the physical blocks of a tile, two of 16 keys.  Those of this wave's first two tiles (a prologue wave: of the
+  // streaming wave it serves) are asked for with the lengths, at clamped places of the sequence's row of the table (what a
+  // place behind the sequence's end names is never read), later ones a tile ahead of their requests.
+  const const_i32_ptr bt = CONST_I32(p.block_table) + static_cast<int64_t>(t) * p.max_blocks_per_seq;
+  struct TileBlocks {
+    int b0, b1;
+  };
+  auto blocks_of = [&](int j) __attribute__((always_inline)) {
+    const int last = p.max_blocks_per_seq - 1;
+    return TileBlocks{bt[min(j >> 4, last)], bt[min((j >> 4) + 1, last)]};
+  };
+  TileBlocks first = {0, 0}, second = {0, 0};
+  if constexpr (PAGED) {
+    const int j = j0 + (wave & (NW - 1)) * kpw;
+    first = blocks_of(j);
+    second = blocks_of(j + 32);
+  }
   const int n_q = CAUSAL ? p.n_new : p.n_queries;
   const int GP = p.group_pad, G = p.group, r = p.rank;
   const int gps = __builtin_ctz(GP);                           // GP is 4, 8 or 16
@@ -158,7 +177,6 @@ __global__ __launch_bounds__(512, 2) void decode_stream_kernel(Params p) {
     return si == 0 ? a_slot[rt][0] : (si == 1 ? a_slot[rt][1] : (si == 2 ? a_slot[rt][2] : a_slot[rt][3]));
   };
   const int n_t = min(len_t, p.max_seq_len);
-  const int j0 = split * p.split_keys;
   // output row (query x Hq + q head) this lane stands for in row tile rt (-1: padding row);
   // its workspace slot is row * n_splits + split
   auto row_index = [&](int rt) -> int {
@@ -187,7 +205,6 @@ __global__ __launch_bounds__(512, 2) void decode_stream_kernel(Params p) {
 
   // ===================== tile requests (of streaming wave sw) =====================
   const int j1 = min(j0 + p.split_keys, n_t);
-  const int kpw = p.split_keys / NW;  // multiple of 32
   const uint32_t ts2 = static_cast<uint32_t>(p.kv_token_stride) * 2u;  // token stride in bytes
   const uint32_t r2 = static_cast<uint32_t>(r) * 2u;                     // L row in bytes
   const uint32_t lp2 = static_cast<uint32_t>(p.l_row_stride) * 2u;       // bytes between L rows
@@ -219,6 +236,7 @@ __global__ __launch_bounds__(512, 2) void decode_stream_kernel(Params p) {
     uint32_t k_voff[KPER], v_voff[VPER], l_voff;
     u32x4 rs_k, rs_v, rs_l[LL];  // one resource per wave covering exactly its keys; one L resource per request: the requests of a block read that block's adapter
     uint32_t l_soff[LL];        // first row of the request inside its block, in bytes of the source
+    const bf16_t* l_adapter;    // (paged) the pool of L rows
   };
   auto tile_requests = [&](int sw) __attribute__((always_inline)) {
     TileRequests q;
@@ -236,6 +254,10 @@ __global__ __launch_bounds__(512, 2) void decode_stream_kernel(Params p) {
       q.l_voff = (lch * 8 < r) ? static_cast<uint32_t>(lrow) * lp2 + (lch << 4) : kOob;
     }
     const int nk = q.jw1 - q.jw0;
+    if constexpr (PAGED) {
+      q.l_adapter = static_cast<const bf16_t*>(p.l) + (CAUSAL ? static_cast<int64_t>(p.adapter_index) * p.l_adapter_stride : 0);
+      return q;
+    }
     const int64_t base = static_cast<int64_t>(h) * p.kv_head_stride + static_cast<int64_t>(q.jw0) * p.kv_token_stride;
     const uint32_t bytes = nk > 0 ? static_cast<uint32_t>(nk - 1) * ts2 + D * 2 : 0u;
     q.rs_k = make_rsrc_words(static_cast<const bf16_t*>(p.k_base) + base, bytes);
@@ -264,10 +286,46 @@ __global__ __launch_bounds__(512, 2) void decode_stream_kernel(Params p) {
   // HBM -> LDS for the 32-key step starting at token j of the sequence, into stage st of the
   // wave: K rows, then L rows, then V rows
   // (parts: 1 = the K rows, 2 = the L and V rows, 3 = all, always in this order)
-  auto issue_tile_of = [&](const TileRequests& q, int j, int st, int parts) __attribute__((always_inline)) {
+  auto issue_tile_of = [&](const TileRequests& q, int j, int st, int parts, TileBlocks tb) __attribute__((always_inline)) {
     unsigned char* ks = q.wave_lds + st * STAGE_BYTES;
     unsigned char* vs = ks + KV_BYTES;
     unsigned char* ls = vs + KV_BYTES;
+    if constexpr (PAGED) {
+      // a resource per block, over the rows of it inside the wave's range (the rest read as zeros)
+      const int64_t hoff = static_cast<int64_t>(h) * p.kv_head_stride;
+      int64_t at[2];
+      uint32_t rows[2];
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {
+        at[half] = static_cast<int64_t>(half == 0 ? tb.b0 : tb.b1);
+        rows[half] = static_cast<uint32_t>(max(0, min(16, q.jw1 - j - 16 * half)));
+      }
+      auto kv_rows = [&](const void* pool, unsigned char* lds, const uint32_t* voff, int per) __attribute__((always_inline)) {
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          const u32x4 rs = make_rsrc_words(static_cast<const bf16_t*>(pool) + at[half] * p.kv_block_stride + hoff,
+                                           rows[half] > 0 ? (rows[half] - 1) * ts2 + D * 2 : 0u);
+          if (stream_kv) {
+#pragma unroll
+            for (int i = 0; i < KVL / 2; ++i) buf_load16_to_lds<true>(rs, lds + (half * (KVL / 2) + i) * 1024, voff[(half * (KVL / 2) + i) % per], i * KROWS * ts2);
+          } else {
+#pragma unroll
+            for (int i = 0; i < KVL / 2; ++i) buf_load16_to_lds<false>(rs, lds + (half * (KVL / 2) + i) * 1024, voff[(half * (KVL / 2) + i) % per], i * KROWS * ts2);
+          }
+        }
+      };
+      if (parts & 1) kv_rows(p.k_base, ks, q.k_voff, KPER);
+      if (parts & 2) {
+#pragma unroll
+        for (int i = 0; i < LL; ++i) {
+          const int half = i / (LL / 2);
+          const u32x4 rs = make_rsrc_words(q.l_adapter + at[half] * 16 * p.l_row_stride, rows[half] > 0 ? (rows[half] - 1) * lp2 + r2 : 0u);
+          buf_load16_to_lds(rs, ls + i * 1024, q.l_voff, (i % (LL / 2)) * LROWS * lp2);
+        }
+        kv_rows(p.v_base, vs, q.v_voff, VPER);
+      }
+      return;
+    }
     const uint32_t s0 = static_cast<uint32_t>(j - q.jw0);
     if (parts & 1) {
       if (stream_kv) {
@@ -341,7 +399,7 @@ __global__ __launch_bounds__(512, 2) void decode_stream_kernel(Params p) {
       // Item idx = hw + it*NW of row tile rt is (agent slot si, rho block cb); this lane holds row
       // rho = 16cb + ln of B_K^a, columns h*D + 32ks + 8lg ..: the A operand of Qt^T.  Rows beyond
       // the rank and the rows of empty slots lie outside the resource and arrive as zeros.
-      const int S = 16 >> gps;         // agent slots per 16-row tile
+      const int S = CAUSAL ? 1 : 16 >> gps;  // agent slots per 16-row tile (a prefill has one adapter: one product for all rows)
       const int ncb = (r + 15) >> 4;   // rho blocks: 1 .. RP/16
       const int n_items = S * ncb;
       // idx -> (slot, rho block): idx / ncb without a division (idx < 16, ncb <= 4)
@@ -384,7 +442,7 @@ __global__ __launch_bounds__(512, 2) void decode_stream_kernel(Params p) {
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
               acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(bt4[rt][it][ks]), qb[rt][ks], acc, 0, 0, 0);
-            if ((ln >> gps) == si) {
+            if (CAUSAL || (ln >> gps) == si) {
               const int kb = si * lb16 + cb;  // 16-rank block along the L tile's columns
               unsigned char* dst = qt_lds + ((rt * RKS + (kb >> 1)) * 64 + lane) * 16;
               *reinterpret_cast<uint2*>(dst + (kb & 1) * 8) = make_uint2(pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3]));
@@ -432,7 +490,7 @@ __global__ __launch_bounds__(512, 2) void decode_stream_kernel(Params p) {
       // their own requests have been taken, and need Q and Qt only when their tile has landed.)
       warm_b_v();
       const TileRequests q = tile_requests(hw);
-      if (q.jw0 + 32 < q.jw1) issue_tile_of(q, q.jw0 + 32, 1, 3);
+      if (q.jw0 + 32 < q.jw1) issue_tile_of(q, q.jw0 + 32, 1, 3, second);
       __syncthreads();  // Q and Qt are in LDS
       // Requests retire in order: with at most the KVL requests of the V rows outstanding (anything
       // issued after them only makes this later), the K and L rows of the tile have landed.
@@ -459,7 +517,11 @@ __global__ __launch_bounds__(512, 2) void decode_stream_kernel(Params p) {
   const TileRequests treq = tile_requests(wave);
   const int jw0 = treq.jw0, jw1 = treq.jw1;
   unsigned char* wave_lds = treq.wave_lds;
-  auto issue_tile = [&](int j, int st) __attribute__((always_inline)) { issue_tile_of(treq, j, st, 3); };
+  TileBlocks next = first;  // of the tile that is requested next
+  auto issue_tile = [&](int j, int st) __attribute__((always_inline)) {
+    issue_tile_of(treq, j, st, 3, next);
+    if constexpr (PAGED) next = j == jw0 ? second : blocks_of(j + 32);
+  };
   // (Letting the K rows of the first tile leave before this barrier starts the stream 0.3 us earlier
   // and makes the call slower: Q and B_K then queue behind 32 KB and Qt is late.)
   __builtin_amdgcn_s_barrier();  // the prologue waves' loads have left: theirs go first
@@ -743,6 +805,18 @@ __global__ __launch_bounds__(512, 2) void decode_stream_kernel(Params p) {
   LRA_STAMP_FLUSH();
 }
 
+template <int D, int RT, int RP, bool HAS_BK, bool CAUSAL, bool PA, bool SI = false>
+__global__ __launch_bounds__(512, 2) void decode_stream_kernel(Params p) {
+  decode_stream<D, RT, RP, HAS_BK, CAUSAL, PA, SI, false>(p);
+}
+// One sequence of a paged cache.  us of a call on decode_mfma_kernel, which holds one tile per wave, / here (8 kv heads, rank
+// 16, 4 agents on 700 tokens 10.4 / 9.3, on 8000 15.5 / 13.2, on 30000 33.1 / 28.3; rank 64, 8 agents on 16000 34.1 / 26.9; 4 kv
+// heads of group 7 on 8000 16.3 / 13.1; 32 of group 1, 2 agents on 60000, at the copy rate, 155.3 / 154.4).
+template <int D, int RT, int RP, bool HAS_BK, bool CAUSAL, bool SI>
+__global__ __launch_bounds__(512, 2) void decode_stream_paged_kernel(Params p) {
+  decode_stream<D, RT, RP, HAS_BK, CAUSAL, false, SI, true>(p);
+}
+
 // Qt = Q B_K^T for every row of a decode call, once per call instead of once per workgroup of
 // the streaming kernel (App. D.1: the query-side projection of the key-side reordering).  With
 // many agents and a large rank every key share of a kv head would otherwise reload the B_K rows of
@@ -750,7 +824,7 @@ __global__ __launch_bounds__(512, 2) void decode_stream_kernel(Params p) {
 // One workgroup per (kv head, row tile, agent slot); wave = rho block.  Output: the operand-ready
 // layout the streaming kernel keeps in LDS, [row group][kv head][row tile][k-step][lane] 16 bytes,
 // elements e -> rho = 32ks' + 16(e/4) + 4lg + e%4.
-template <int D, int RP, bool CAUSAL>
+template <int D, int RP>
 __global__ __launch_bounds__(256) void decode_qt_prepass_kernel(Params p, int row_tiles) {
   constexpr int KS = D / 32, RKS = RP / 32, ROW_BYTES = D * 2;
   const int lane = threadIdx.x & 63;
@@ -759,11 +833,11 @@ __global__ __launch_bounds__(256) void decode_qt_prepass_kernel(Params p, int ro
   // (the parameter block in one round trip; row_tiles is 1 or 2: no division)
   asm volatile("" ::"s"(p.q), "s"(p.b_k), "s"(p.query_adapter), "s"(p.qt_ws));
   asm volatile("" ::"s"(p.n_q_heads), "s"(p.n_kv_heads), "s"(p.group), "s"(p.rank), "s"(p.group_pad), "s"(p.n_queries),
-               "s"(p.n_new), "s"(p.n_adapters), "s"(p.adapter_index), "s"(row_tiles));
+               "s"(p.n_adapters), "s"(row_tiles));
   const int h = blockIdx.x, si = blockIdx.z;
   const int by = blockIdx.y;
   const int rg = row_tiles == 2 ? by >> 1 : by, rt = row_tiles == 2 ? by & 1 : 0;
-  const int n_q = CAUSAL ? p.n_new : p.n_queries;
+  const int n_q = p.n_queries;
   const int GP = p.group_pad, G = p.group, r = p.rank;
   const int gps = __builtin_ctz(GP);
   const int ncb = (r + 15) >> 4;
@@ -771,7 +845,7 @@ __global__ __launch_bounds__(256) void decode_qt_prepass_kernel(Params p, int ro
   const int slot = (tile_row0 >> gps) + si;
   if (si >= (16 >> gps) || cb >= ncb) return;
   int a = -1;
-  if (slot < n_q) a = min(max(CAUSAL ? p.adapter_index : CONST_I32(p.query_adapter)[slot], 0), p.n_adapters - 1);
+  if (slot < n_q) a = min(max(CONST_I32(p.query_adapter)[slot], 0), p.n_adapters - 1);
   const bool live = a >= 0;
   const int64_t ldb = static_cast<int64_t>(p.n_kv_heads) * D;
   const __amdgpu_buffer_rsrc_t rs_q = make_rsrc(p.q, static_cast<uint32_t>(n_q) * p.n_q_heads * D * 2);
@@ -805,40 +879,46 @@ __global__ __launch_bounds__(256) void decode_qt_prepass_kernel(Params p, int ro
 template <int D, int RP>
 static void launch_prepass2(const Params& p, int row_tiles, hipStream_t s) {
   const dim3 grid(p.n_kv_heads, p.row_groups * row_tiles, 16 / p.group_pad), block(256);
-  if (p.is_prefill) hipLaunchKernelGGL((decode_qt_prepass_kernel<D, RP, true>), grid, block, 0, s, p, row_tiles);
-  else hipLaunchKernelGGL((decode_qt_prepass_kernel<D, RP, false>), grid, block, 0, s, p, row_tiles);
+  hipLaunchKernelGGL((decode_qt_prepass_kernel<D, RP>), grid, block, 0, s, p, row_tiles);
 }
 
-// Whether a decode launch can take decode_stream_kernel: contiguous cache, no rotary key side, at
-// most one workgroup per compute unit.
+// Whether a decode launch can take decode_stream_kernel: one sequence (in a paged cache with one low-rank cache for all
+// adapters), no rotary key side, at most one workgroup per compute unit.
 bool decode_stream_applies(const Params& p, int row_tiles, int n_cus) {
-  if (p.block_size != 0 || (p.key_rope_theta > 0.f && p.b_k != nullptr)) return false;
+  if (p.key_rope_theta > 0.f && p.b_k != nullptr) return false;
+  if (p.block_size != 0 && !p.is_prefill && (p.n_seqs != 1 || p.l_adapter_stride != 0)) return false;
   if (row_tiles < 1 || row_tiles > 2) return false;
   const int64_t wgs = static_cast<int64_t>(p.n_kv_heads) * p.n_splits * p.row_groups;
   return wgs <= n_cus;
 }
 
+#define LRA_STREAM_LAUNCH(...) hipLaunchKernelGGL((__VA_ARGS__), grid, dim3(512), 0, s, p)
 template <int D, int RT, int RP, bool SI>
 static hipError_t launch_stream3(const Params& p, dim3 grid, hipStream_t s) {
-  const dim3 block(512);
   const bool has_bk = p.b_k != nullptr;
-  if (p.is_prefill) {
-    if (has_bk) hipLaunchKernelGGL((decode_stream_kernel<D, RT, RP, true, true, false, SI>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((decode_stream_kernel<D, RT, RP, false, true, false, SI>), grid, block, 0, s, p);
-  } else if (p.l_block != 0) {
-    // per-adapter low-rank caches: one column block of the L tile per agent slot (one row tile only)
-    if constexpr (RT == 1) {
-      if (has_bk) hipLaunchKernelGGL((decode_stream_kernel<D, 1, RP, true, false, true, SI>), grid, block, 0, s, p);
-      else hipLaunchKernelGGL((decode_stream_kernel<D, 1, RP, false, false, true, SI>), grid, block, 0, s, p);
-    } else {
-      return hipErrorInvalidValue;
-    }
-  } else {
-    if (has_bk) hipLaunchKernelGGL((decode_stream_kernel<D, RT, RP, true, false, false, SI>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((decode_stream_kernel<D, RT, RP, false, false, false, SI>), grid, block, 0, s, p);
+  if (p.block_size != 0) {
+    if (p.is_prefill && has_bk) LRA_STREAM_LAUNCH(decode_stream_paged_kernel<D, RT, RP, true, true, SI>);
+    else if (p.is_prefill) LRA_STREAM_LAUNCH(decode_stream_paged_kernel<D, RT, RP, false, true, SI>);
+    else if (has_bk) LRA_STREAM_LAUNCH(decode_stream_paged_kernel<D, RT, RP, true, false, SI>);
+    else LRA_STREAM_LAUNCH(decode_stream_paged_kernel<D, RT, RP, false, false, SI>);
+    return hipGetLastError();
   }
-  return hipGetLastError();
+  if (p.is_prefill || p.l_block == 0) {
+    if (p.is_prefill && has_bk) LRA_STREAM_LAUNCH(decode_stream_kernel<D, RT, RP, true, true, false, SI>);
+    else if (p.is_prefill) LRA_STREAM_LAUNCH(decode_stream_kernel<D, RT, RP, false, true, false, SI>);
+    else if (has_bk) LRA_STREAM_LAUNCH(decode_stream_kernel<D, RT, RP, true, false, false, SI>);
+    else LRA_STREAM_LAUNCH(decode_stream_kernel<D, RT, RP, false, false, false, SI>);
+    return hipGetLastError();
+  }
+  // per-adapter low-rank caches: one column block of the L tile per agent slot (one row tile only)
+  if constexpr (RT == 1) {
+    if (has_bk) LRA_STREAM_LAUNCH(decode_stream_kernel<D, 1, RP, true, false, true, SI>);
+    else LRA_STREAM_LAUNCH(decode_stream_kernel<D, 1, RP, false, false, true, SI>);
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
 }
+#undef LRA_STREAM_LAUNCH
 
 // Key ranges of at most two 32-key tiles per streaming wave take the split-issue form (where the
 // LDS has room for the hand-over area next to the tile stages).

@@ -93,8 +93,9 @@ int decode_mfma_row_tiles(int rows_needed) { return rows_needed <= 16 ? 1 : 2; }
 // again above, where the kernel has a compute unit to itself)
 int decode_mfma_rope_slots(int rank) { return rank <= 16 ? 4 : (rank <= 32 ? 2 : 4); }
 
-// The pre-pass pays (one more launch) once a workgroup of the streaming kernel would have to load
-// more than eight 16-row blocks of B_K.
+// The pre-pass pays (one more launch) once a workgroup of the streaming kernel would have to load more than eight 16-row
+// blocks of B_K.  (Not in a prefill, whose rows share one adapter: rank 64, 2 new tokens of group 4 on 500 keys 14.1 us with
+// the pre-pass.)
 size_t decode_stream_qt_bytes(int group_pad, int rank, int row_tiles, int row_groups, int n_kv_heads) {
   const int slots = 16 / group_pad, ncb = (rank + 15) / 16;
   if (slots * ncb * row_tiles <= 8) return 0;
@@ -570,6 +571,8 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
     // with 63 shares, 24.2 with 21)
     want = rope && key_adapter ? kCUs * 8 : kCUs * 3;
   }
+  // (the streaming kernel reads one sequence's blocks too, with one low-rank cache for the call)
+  const bool paged_stream = c->block_size != 0 && n_seqs_eff == 1 && tune.variant != 2 && (prefill || c->l_adapter_stride == 0);
   int split_keys = tune.split_keys;
   RopeShares two{0, 0, 0};
   if (split_keys <= 0 && pl.mfma) {
@@ -579,10 +582,10 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
     // half as long on average as its longest sequence.
     const bool batch = n_seqs_eff > 1;
     int64_t wgs = batch ? kCUs * 4 : kCUs;
-    // ... and one long sequence in a paged cache (the split-KV kernel, two workgroups per compute unit) with two,
-    // as long as a share then still has 512 keys (32768 tokens x 8 kv heads: 35.7 against 38.6 us, 65536: 49.2
+    // ... and one long sequence in a paged cache with two, where it takes the split-KV kernel, two workgroups per compute
+    // unit, as long as a share then still has 512 keys (32768 tokens x 8 kv heads: 35.7 against 38.6 us, 65536: 49.2
     // against 53.7; at 256 keys per share the doubling loses)
-    if (!batch && !prefill && c->block_size != 0 && !rope && work * c->max_seq_len >= int64_t{2} * kCUs * 512) wgs = 2 * kCUs;
+    if (!batch && !prefill && !paged_stream && c->block_size != 0 && !rope && work * c->max_seq_len >= int64_t{2} * kCUs * 512) wgs = 2 * kCUs;
     // ... and one sequence in the rotary form at ranks up to 32 likewise.  Above rank 32 a unit holds one workgroup.  Nor
     // without a B_K: nothing is rotated then, and one workgroup per unit keeps the streaming form.
     if (!batch && rope_split && key_adapter && sh->rank <= 32) two = rope_two_per_unit(c->max_seq_len, work, pl.rows, prefill);
@@ -700,7 +703,7 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
   // otherwise reload many B_K rows per workgroup (reserved whether or not the call has a B_K)
   pl.off_qt = pl.bytes;
   pl.qt_bytes = 0;
-  if (pl.mfma && c->block_size == 0 && !rope_split && tune.variant != 2 && pl.l_block == 0)
+  if (pl.mfma && !prefill && (c->block_size == 0 || paged_stream) && !rope_split && tune.variant != 2 && pl.l_block == 0)
     pl.qt_bytes = decode_stream_qt_bytes(pl.group_pad, sh->rank, pl.row_tiles, pl.row_groups, sh->n_kv_heads);
   pl.bytes += align_up(pl.qt_bytes, 256);
   pl.bytes_without_kc = pl.bytes;
