@@ -8,6 +8,8 @@
 //     m, l = online softmax statistics,  O += p_j V_base[j],  O_lr += p_j L[j]
 // The epilogue O += O_lr B_V and the division by l (the last two steps of Alg. 1) happen in
 // the merge kernel, after the per-split states are combined.
+#include <type_traits>
+
 #include "lra_common.h"
 
 namespace lra {
@@ -386,6 +388,11 @@ constexpr int kMergeUnroll = 8;  // splits per thread and pass
 // Rows from which the wave-per-row form of the merge runs (measured on MI355X: 1792 rows of config
 // 5 take 12.7 us against 20.5 us; 256 rows of config 4 take 10.4 us against 9.3 us).
 constexpr int kMergeWaveRows = 1024;
+// Rows from which the form with four rows per wave runs on a prefill, nine waves of it per compute unit: 9324 rows gain 2 %
+// at rank 16 and 6 % at 32, 22400 rows up to 5 %, 16384 rows at rank 64 7 to 11 %; 6400 rows come out even, 240 rows lose a third
+// to the chain of four rows per wave.  Plans of that many rows hold a handful of shares.
+constexpr int kMergeTokenRows = 9216;
+constexpr int kMergeTokenShares = 16;
 
 #ifdef LRA_TIMING
 #define LRA_MSTAMP(k) do { unsigned long long t_; asm volatile("s_waitcnt lgkmcnt(0)\n\ts_memrealtime %0\n\ts_waitcnt lgkmcnt(0)" : "=s"(t_)); mt[k] = t_; } while (0)
@@ -743,6 +750,189 @@ __global__ __launch_bounds__(256) void merge_wave_kernel(Params p) {
   for (int k = 0; k < CPL; ++k) out[k] = from_f32<T>(o[k] / ell);
 }
 
+// The same merge for the rows of a long prefill, which share one adapter: a wave takes four rows of a kv head, reads a
+// piece of 16 bytes per lane, two rows (d = 64: four) with one load, and the B_V slice once for its rows.  Statistics: the
+// sixteen lanes of a DPP row hold sixteen shares of the row that their loads belong to, and hand a weight round by a DPP
+// broadcast.  What bounds it is the states' bytes, which the caches behind the L2s hand over at about 3.5 TB/s (333 tokens of
+// 32 q heads, 5 shares, rank 16: 31 MB in 10.2 us, 10.6 with a wave per row); with a wave per row the loads of B_V, one per
+// rank and row, came on top (rank 64: 512 tokens on 8000 keys in 119 us in place of 128).
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
+}
+template <typename F>
+__device__ __forceinline__ float over_16_lanes(float v, F op) {
+  v = op(v, dpp_f32<0x128>(v));  // row_ror:8, 4, 2, 1
+  v = op(v, dpp_f32<0x124>(v));
+  v = op(v, dpp_f32<0x122>(v));
+  return op(v, dpp_f32<0x121>(v));
+}
+
+template <int D>
+__global__ __launch_bounds__(256) void merge_tokens_kernel(Params p) {
+  constexpr int RPL = 256 / D;        // rows of one load
+  constexpr int NL = 4 / RPL;         // loads that cover the wave's four rows
+  constexpr int LPR = 64 / RPL;       // lanes per row
+  constexpr int YN = 64 / LPR;        // loads that cover 64 ranks
+  constexpr int U = 8;                // shares in flight
+  constexpr int kShares = kMergeTokenShares;
+  __shared__ __align__(16) float olr_sh[4][4][64];
+  asm volatile("" ::"s"(p.part_ml), "s"(p.part_o), "s"(p.part_lr), "s"(p.b_v), "s"(p.out));
+  asm volatile("" ::"s"(p.n_q_heads), "s"(p.n_kv_heads), "s"(p.group), "s"(p.rank), "s"(p.n_splits), "s"(p.n_new), "s"(p.adapter_index));
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int sub = lane / LPR, c = lane % LPR, l16 = lane & 15;
+  const int h = blockIdx.x, G = p.group, r = p.rank, ns = p.n_splits;
+  const int n_rows = p.n_new * G;  // of this kv head: (new token, q head), the q head fastest
+  const int i0 = (static_cast<int>(blockIdx.y) * 4 + wave) * 4;
+  if (i0 >= n_rows) return;
+  int row[NL];
+  bool live_row[NL];
+  float2 st[NL][kShares / 16];
+#pragma unroll
+  for (int k = 0; k < NL; ++k) {
+    const int i = i0 + k * RPL + sub;
+    live_row[k] = i < n_rows;
+    const int ic = min(i, n_rows - 1), tok = ic / G;
+    row[k] = tok * p.n_q_heads + h * G + (ic - tok * G);
+    const float2* ml = reinterpret_cast<const float2*>(p.part_ml) + static_cast<int64_t>(row[k]) * ns;
+#pragma unroll
+    for (int j = 0; j < kShares / 16; ++j) st[k][j] = ml[min(16 * j + l16, ns - 1)];
+  }
+  // the first sixteen rows of B_V (the next ones, at larger ranks, follow the sums)
+  const int64_t ld = static_cast<int64_t>(p.n_kv_heads) * D;
+  const bf16_t* bv = static_cast<const bf16_t*>(p.b_v) + static_cast<int64_t>(p.adapter_index) * r * ld + h * D + 4 * c;
+  uint2 b[16];
+  auto fetch_bv = [&](int r0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      b[i] = *reinterpret_cast<const uint2*>(bv + min(r0 + i, r - 1) * ld);
+      if (r0 + i >= r) b[i] = make_uint2(0u, 0u);  // (fetched again, and no rank)
+    }
+  };
+  if (p.b_v != nullptr) fetch_bv(0);
+
+  // ---- weights of the shares ----
+  float w[NL][kShares / 16], ell[NL];
+#pragma unroll
+  for (int k = 0; k < NL; ++k) {
+    float big = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < kShares / 16; ++j) {
+      // (a share without a visible key left a zero row sum; its rows were never written)
+      if (!(16 * j + l16 < ns && st[k][j].y > 0.f)) st[k][j] = make_float2(-INFINITY, 0.f);
+      big = fmaxf(big, st[k][j].x);
+    }
+    big = over_16_lanes(big, [](float a, float x) { return fmaxf(a, x); });
+    float sum = 0.f;
+#pragma unroll
+    for (int j = 0; j < kShares / 16; ++j) {
+      w[k][j] = st[k][j].y > 0.f ? expf(st[k][j].x - big) : 0.f;
+      sum = fmaf(w[k][j], st[k][j].y, sum);
+    }
+    ell[k] = over_16_lanes(sum, [](float a, float x) { return a + x; });
+  }
+
+  // ---- weighted sums, shares in index order ----
+  float4 o[NL];
+  float olr[NL][YN];
+#pragma unroll
+  for (int k = 0; k < NL; ++k) {
+    o[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int y = 0; y < YN; ++y) olr[k][y] = 0.f;
+  }
+  auto shares = [&](auto s0_c) __attribute__((always_inline)) {
+    constexpr int S0 = decltype(s0_c)::value;
+    if (S0 >= ns) return;
+    float4 x[NL][U];
+    float y[NL][U][YN];
+#pragma unroll
+    for (int k = 0; k < NL; ++k)
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t slot = static_cast<int64_t>(row[k]) * ns + min(S0 + u, ns - 1);
+        x[k][u] = *reinterpret_cast<const float4*>(p.part_o + slot * D + 4 * c);
+#pragma unroll
+        for (int q = 0; q < YN; ++q)
+          if (q * LPR < r) y[k][u][q] = p.part_lr[slot * r + min(q * LPR + c, r - 1)];
+      }
+    __builtin_amdgcn_sched_barrier(0);
+    auto add = [&](int k, int u, float wu) __attribute__((always_inline)) {
+      // (weight zero: whatever an unwritten row holds stays out of the sums)
+      const bool in = wu > 0.f;
+      o[k].x = fmaf(wu, in ? x[k][u].x : 0.f, o[k].x);
+      o[k].y = fmaf(wu, in ? x[k][u].y : 0.f, o[k].y);
+      o[k].z = fmaf(wu, in ? x[k][u].z : 0.f, o[k].z);
+      o[k].w = fmaf(wu, in ? x[k][u].w : 0.f, o[k].w);
+#pragma unroll
+      for (int q = 0; q < YN; ++q)
+        if (q * LPR < r) olr[k][q] = fmaf(wu, in ? y[k][u][q] : 0.f, olr[k][q]);
+    };
+    constexpr int J = S0 / 16, B = 0x150 + (S0 & 15);  // row_newbcast of the share's lane
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+      add(k, 0, dpp_f32<B + 0>(w[k][J]));
+      add(k, 1, dpp_f32<B + 1>(w[k][J]));
+      add(k, 2, dpp_f32<B + 2>(w[k][J]));
+      add(k, 3, dpp_f32<B + 3>(w[k][J]));
+      add(k, 4, dpp_f32<B + 4>(w[k][J]));
+      add(k, 5, dpp_f32<B + 5>(w[k][J]));
+      add(k, 6, dpp_f32<B + 6>(w[k][J]));
+      add(k, 7, dpp_f32<B + 7>(w[k][J]));
+    }
+  };
+  // (shares behind the last have weight zero: lanes that hold none)
+  shares(std::integral_constant<int, 0>{});
+  shares(std::integral_constant<int, 8>{});
+
+  // ---- O += O_lr B_V ----
+  if (p.b_v != nullptr) {
+#pragma unroll
+    for (int k = 0; k < NL; ++k)
+#pragma unroll
+      for (int q = 0; q < YN; ++q) olr_sh[wave][k * RPL + sub][q * LPR + c] = q * LPR + c < r ? olr[k][q] : 0.f;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    for (int r0 = 0; r0 < r; r0 += 16) {
+      if (r0 > 0) fetch_bv(r0);
+#pragma unroll
+      for (int k = 0; k < NL; ++k)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float4 l4 = *reinterpret_cast<const float4*>(&olr_sh[wave][k * RPL + sub][r0 + 4 * q]);
+          const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const uint2 w = b[4 * q + e];
+            o[k].x = fmaf(lv[e], __uint_as_float(w.x << 16), o[k].x);
+            o[k].y = fmaf(lv[e], __uint_as_float(w.x & 0xffff0000u), o[k].y);
+            o[k].z = fmaf(lv[e], __uint_as_float(w.y << 16), o[k].z);
+            o[k].w = fmaf(lv[e], __uint_as_float(w.y & 0xffff0000u), o[k].w);
+          }
+        }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < NL; ++k)
+    if (live_row[k]) {
+      bf16_t* out = static_cast<bf16_t*>(p.out) + static_cast<int64_t>(row[k]) * D + 4 * c;
+      const bf16_t v[4] = {from_f32<bf16_t>(o[k].x / ell[k]), from_f32<bf16_t>(o[k].y / ell[k]), from_f32<bf16_t>(o[k].z / ell[k]),
+                           from_f32<bf16_t>(o[k].w / ell[k])};
+      *reinterpret_cast<uint2*>(out) = make_uint2(v[0] | static_cast<uint32_t>(v[1]) << 16, v[2] | static_cast<uint32_t>(v[3]) << 16);
+    }
+}
+
+static bool launch_merge_tokens(const Params& p, int rows, hipStream_t s) {
+  if (!p.is_prefill || rows < kMergeTokenRows || p.n_splits > kMergeTokenShares || (p.head_dim != 64 && p.head_dim != 128)) return false;
+  const int64_t blocks = (static_cast<int64_t>(p.n_new) * p.group + 15) / 16;
+  if (blocks > 65535) return false;
+  const dim3 grid(p.n_kv_heads, static_cast<unsigned>(blocks));
+  if (p.head_dim == 128) hipLaunchKernelGGL((merge_tokens_kernel<128>), grid, dim3(256), 0, s, p);
+  else hipLaunchKernelGGL((merge_tokens_kernel<64>), grid, dim3(256), 0, s, p);
+  return true;
+}
+
 template <typename T>
 static bool launch_merge_wave(const Params& p, int rows, hipStream_t s) {
   // worth it from a few hundred rows on; the statistics need one lane per split
@@ -800,6 +990,7 @@ static void launch_merge_t(const Params& p, int rows, hipStream_t s) {
 }
 
 hipError_t launch_merge(const Params& p, bool is_bf16, int rows, hipStream_t s) {
+  if (is_bf16 && launch_merge_tokens(p, rows, s)) return hipGetLastError();
   if (is_bf16)
     launch_merge_t<bf16_t>(p, rows, s);
   else
