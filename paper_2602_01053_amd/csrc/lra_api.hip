@@ -329,8 +329,8 @@ lra_status lra_cache_append(const lra_shape* shape, const lra_cache* cache, cons
   // the split over d_model, where the sizes ask for it and the caller brought room for its parts
   const AppendSplit sp = plan_append_split(n_new, shape->n_kv_heads, shape->head_dim, shape->rank, proj->d_model, tune);
   const bool quarter = append_quarter_tiles(n_new, shape->n_kv_heads, shape->head_dim, shape->rank, proj->d_model, tune);
-  const bool split = !quarter && sp.k_splits > 1 && workspace != nullptr && !(reinterpret_cast<uintptr_t>(workspace) & 255) &&
-                     workspace_bytes >= sp.bytes;
+  const bool split = !quarter && sp.k_splits > 1 && !append_streams(n_new, shape->n_kv_heads, shape->head_dim, proj->d_model, tune) &&
+                     workspace != nullptr && !(reinterpret_cast<uintptr_t>(workspace) & 255) && workspace_bytes >= sp.bytes;
   p.k_splits = split ? sp.k_splits : 1;
   p.split_bt = sp.bt;
   p.split_ws = split ? static_cast<float*>(workspace) : nullptr;

@@ -7,7 +7,7 @@
 // ones, App. D.1) and writes the rows into K_base, V_base and L, contiguous or paged.
 //
 // Five kernels, chosen by the number of new tokens (launch_append at the end of the file): a
-// matrix-vector kernel (1-2 tokens), a weight-streaming MFMA kernel (up to 64), and three tiled
+// matrix-vector kernel (1 token), a weight-streaming MFMA kernel (up to 64), and three tiled
 // GEMM kernels (128 features x 128 or 64 tokens per workgroup; 256 x 256 for large chunks,
 // see wide_tiles_pay; 64 x 64 where those fill the chip once, see append_quarter_tiles).
 //
@@ -718,149 +718,168 @@ __global__ __launch_bounds__(512, 2) void append_wide_kernel(AppendParams p) {
 }
 
 // ---------------------------------------------------------------------------------------
-// Few new tokens (a decode step appends one): the projection is one pass over the weights,
-// bound by HBM, and a 128 x 128 tile grid would put a handful of workgroups on the chip.
-// Here a workgroup owns 16 output features and 16 * NT tokens; its 8 waves split d_model
-// (wave w takes the 64-wide steps w, w+8, ...), feed v_mfma_f32_16x16x32_bf16 straight from
-// global loads (every weight element is used once: nothing to stage) and add their partial
-// tiles through LDS.  The 16 features are 8 + the 8 half a head further on, so the rotary
-// pairs meet in one thread of the epilogue.  blockIdx.y walks chunks of 16 * NT tokens.
+// Few new tokens: one pass over the weights with every compute unit on it.  A workgroup owns PP rotary pairs of features
+// (of K, then of V, numbered through) and, the first `rank` workgroups, one L feature; its 8 waves take every eighth 64-wide piece
+// of d_model.  Each copies its pieces of the rows and of the tokens into a ring of its own in LDS, eight rows of 128 bytes
+// per request, and reads the MFMA operands from there: no barrier before the partial tiles meet.
+// What bounds it: up to 16 tokens HBM and the latency of one round (llama-3-8B projection, 17 MB: 6.0 us, 2.8 TB/s), beyond
+// that x, which every workgroup reads through its compute unit's one path to L2 (0.1 us per token at d_model 4096).  Operands
+// straight from global memory, sixteen features per workgroup, as it was before: sixteen rows per request of 16 lanes pass that
+// path at a quarter of its width, and half of the units had no workgroup.  us before and now at 3, 16 and 32 tokens:
+// 8.5 / 10.4 / 14.2 and 6.0 / 7.3 / 9.0; 4 kv heads on 3584 8.6 / 9.6 / 12.2 and 4.4 / 4.6 / 5.9; 32 kv heads
+// 19.0 / 25.5 / 35.0 and 14.1 / 18.5 / 26.0; 4 of 64 on 256, where all of it is latency, 8 tokens 2.7 and 2.85.
+// The ring takes half of a unit's LDS or less (two workgroups, and the next call's can begin): with all of it 3 tokens 6.4.
 // ---------------------------------------------------------------------------------------
-template <int D, int NT, bool PAGED>
-__global__ __launch_bounds__(512) void append_skinny_kernel(AppendParams p) {
-  constexpr int NW = 8;
-  __shared__ __align__(16) float red[NW][NT][256];
+template <int D, int WI, int XI, bool PAGED>  // requests of eight rows per piece: weights (2 PP + 1 <= 8 WI), tokens
+__global__ __launch_bounds__(512, 2) void append_skinny_kernel(AppendParams p, int pp) {
+  constexpr int NW = 8, NT = (XI + 1) / 2, INS = WI + XI, DEPTH = INS <= 5 ? 10 / INS : 2;
+  constexpr int SLOT = INS * 1024, RING = DEPTH * SLOT;
+  static_assert(RING >= NT * 1024, "a wave's partial tiles fit into its ring");
+  __shared__ __align__(16) unsigned char smem[NW * RING];
 
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
+  // (the parameter block in one round trip, the sequence length first and by hand: only the last step needs it)
+  asm volatile("" ::"s"(p.w), "s"(p.x), "s"(p.seq_lens), "s"(p.k_base), "s"(p.v_base), "s"(p.l));
+  asm volatile("" ::"s"(p.d_model), "s"(p.n_kv_heads), "s"(p.rank), "s"(p.n_new), "s"(p.seq_index), "s"(p.max_seq_len),
+               "s"(p.rope_theta), "s"(p.kv_token_stride), "s"(p.kv_head_stride), "s"(p.l_row_stride));
+  int len_raw;
+  asm volatile("s_load_dword %0, %1, 0x0" : "=s"(len_raw) : "s"(p.seq_lens + p.seq_index));
+  const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g4 = lane >> 4;
-  const int HD = p.n_kv_heads * D;
-  const int groups_kv = HD / 16;  // feature groups of the K (and of the V) region
-  const int fg = blockIdx.x;
-  const int kind = fg < groups_kv ? 0 : (fg < 2 * groups_kv ? 1 : 2);
-  const int fg_in = kind == 0 ? fg : (kind == 1 ? fg - groups_kv : fg - 2 * groups_kv);
-  const int head = fg_in / (D / 16), sub = fg_in - head * (D / 16);
-  // feature (inside its region) of tile row i: K/V  head*D + 8 sub + i  (i < 8),  + d/2 - 8 beyond;  L  16 fg_in + i
-  auto feature_of = [&](int i) __attribute__((always_inline)) {
-    return kind == 2 ? 16 * fg_in + i : head * D + 8 * sub + (i < 8 ? i : i - 8 + D / 2);
-  };
-  const int n_new = p.n_new;
-  const int tok0 = blockIdx.y * (16 * NT);
-  const int n_t = append_length(PF_CONST_I32(p.seq_lens)[p.seq_index], p.max_seq_len);
-  const int pos0 = n_t - n_new;
+  const int HD = p.n_kv_heads * D, n_new = p.n_new, bx = blockIdx.x;
+  const int tok0 = blockIdx.y * (8 * XI);
+  // first feature of pair P (its partner lies D / 2 on), counted through K and V
+  auto feature = [&](int pair) __attribute__((always_inline)) { return pair / (D / 2) * D + pair % (D / 2); };
 
-  // operand rows of this lane (clamped into the tensors; what a clamped row produces is never stored)
-  const int w_row = (kind == 0 ? 0 : (kind == 1 ? HD : 2 * HD)) +
-                    (kind == 2 ? min(feature_of(l16), p.rank - 1) : feature_of(l16));
-  const int64_t ld = p.d_model;
-  const bf16_t* wp = static_cast<const bf16_t*>(p.w) + static_cast<int64_t>(w_row) * ld + 8 * g4;
-  const bf16_t* xp[NT];
+  const uint32_t ld2 = static_cast<uint32_t>(p.d_model) * 2u;
+  const pf_u32x4 rs_w = pf_rsrc(p.w, static_cast<uint32_t>(2 * HD + p.rank) * ld2);
+  const pf_u32x4 rs_x = pf_rsrc(p.x, static_cast<uint32_t>(n_new) * ld2);
+  const uint32_t ring = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(PF_LDS_AS(unsigned char, smem))) + wave * RING;
+  // A piece's row is 128 bytes, 16-byte chunk c of row R at place c ^ (R / 2) % 8: sixteen lanes that read one chunk of
+  // sixteen rows then meet every bank once.
+  const int dma_row = lane >> 3;
+  uint32_t w_off[WI], x_off[XI];
 #pragma unroll
-  for (int t = 0; t < NT; ++t)
-    xp[t] = static_cast<const bf16_t*>(p.x) + static_cast<int64_t>(min(tok0 + 16 * t + l16, n_new - 1)) * ld + 8 * g4;
+  for (int i = 0; i < WI; ++i) {
+    const int R = 8 * i + dma_row;  // rows: first features, partners, the L feature; rows behind them are fetched again
+    const int pair = min(bx * pp + (R < pp ? R : (R < 2 * pp ? R - pp : 0)), HD - 1);
+    int row = feature(pair) + (R >= pp && R < 2 * pp ? D / 2 : 0);
+    if (R == 2 * pp && bx < p.rank) row = 2 * HD + bx;
+    w_off[i] = static_cast<uint32_t>(row) * ld2 + (((lane & 7) ^ ((R >> 1) & 7)) << 4);
+  }
+#pragma unroll
+  for (int i = 0; i < XI; ++i) {
+    const int R = 8 * i + dma_row;
+    x_off[i] = static_cast<uint32_t>(min(tok0 + R, n_new - 1)) * ld2 + (((lane & 7) ^ ((R >> 1) & 7)) << 4);
+  }
+  // (The workgroups of an XCD, which run together, start on different pieces, so that x comes from different channels of its L2:
+  // 4 kv heads on 3584, 64 tokens 8.7 -> 8.4 us.  With fewer than eight pieces the first waves go without, to work out the rates.)
+  const int n_pieces = p.d_model / 64;
+  const int first = n_pieces >= NW ? (wave + (bx >> 3)) & (NW - 1) : NW - 1 - wave, n = (n_pieces - first + NW - 1) / NW;
+  auto request = [&](int i, int slot) __attribute__((always_inline)) {
+    const uint32_t k2 = static_cast<uint32_t>(first + NW * i) * 128u, dst = ring + slot * SLOT;
+#pragma unroll
+    for (int q = 0; q < WI; ++q) pf_load16_to_lds(rs_w, dst + q * 1024, w_off[q], k2);
+#pragma unroll
+    for (int q = 0; q < XI; ++q) pf_load16_to_lds(rs_x, dst + (WI + q) * 1024, x_off[q], k2);
+  };
+#pragma unroll
+  for (int i = 0; i < DEPTH; ++i)
+    if (i < n) request(i, i);
+
+  // thread (pair q or, behind the pairs, the L feature; token): its rotation rate, worked out under the requests
+  const int item = tid >> 4, q = item / NT, t_sum = item % NT, tk = l16;
+  const int pair = bx * pp + q;
+  double rate = 0.0;
+  if (q < pp && pair < HD / 2 && p.rope_theta > 0.f) {
+    rate = rope_rate_rev(pair % (D / 2), D, p.rope_theta);
+    asm volatile("" ::"v"(rate));
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(len_raw));
 
   pf_f32x4 acc[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) acc[t] = pf_f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // A step covers 64 values of d_model with two MFMAs: lane (l16, g4) holds k = 64 s + 16 g4 .. + 16
-  // of its W row (A) and of its token (B), the first eight for one MFMA, the rest for the other
-  // (any assignment of k to lanes is right as long as A and B share it); four lanes read one
-  // 128-byte line of a row.
-  const int n_steps = p.d_model / 64;
-  constexpr int U = 8 / NT;  // steps in flight per wave (64 operand registers of x)
-  const bf16_t* wq = wp + 8 * g4;  // wp and xp already carry 8 g4
-  int s = wave;
-  for (; s + (U - 1) * NW < n_steps; s += U * NW) {
-    pf_u32x4 a[U][2], b[U][NT][2];
+  // operand rows: weights, tokens (16 t on); of eight rows the upper lanes take the same again, for products nobody reads
+  auto chunk = [&](int row) __attribute__((always_inline)) { return row * 128 + ((g4 ^ ((row >> 1) & 7)) << 4); };
+  const int a_off = chunk(WI == 1 ? l16 & 7 : l16);
+  int b_off[NT];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      a[u][0] = *reinterpret_cast<const pf_u32x4*>(wq + (s + u * NW) * 64);
-      a[u][1] = *reinterpret_cast<const pf_u32x4*>(wq + (s + u * NW) * 64 + 8);
+  for (int t = 0; t < NT; ++t) b_off[t] = WI * 1024 + t * 2048 + chunk(2 * t + 2 > XI ? l16 & 7 : l16);
+  int slot = 0;
+  for (int i = 0; i < n; ++i) {
+    // piece i is there: at most the pieces behind it are under way
+    const int behind = min(DEPTH, n - i) - 1;
+    static_assert(DEPTH >= 2 && DEPTH <= 10, "the waits below");
+#define LRA_WAIT(B) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(DEPTH > B ? B * INS : 0) : "memory")
+    if (behind >= 9) LRA_WAIT(9);
+    else if (behind == 8) LRA_WAIT(8);
+    else if (behind == 7) LRA_WAIT(7);
+    else if (behind == 6) LRA_WAIT(6);
+    else if (behind == 5) LRA_WAIT(5);
+    else if (behind == 4) LRA_WAIT(4);
+    else if (behind == 3) LRA_WAIT(3);
+    else if (behind == 2) LRA_WAIT(2);
+    else if (behind == 1) LRA_WAIT(1);
+    else LRA_WAIT(0);
+#undef LRA_WAIT
+    const unsigned char* st = smem + wave * RING + slot * SLOT;
+    pf_bf16x8 a[2], b[NT][2];
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        b[u][t][0] = *reinterpret_cast<const pf_u32x4*>(xp[t] + 8 * g4 + (s + u * NW) * 64);
-        b[u][t][1] = *reinterpret_cast<const pf_u32x4*>(xp[t] + 8 * g4 + (s + u * NW) * 64 + 8);
-      }
+    for (int m = 0; m < 2; ++m) {
+      a[m] = pf_as_bf16x8(*reinterpret_cast<const uint4*>(st + (a_off ^ (m << 6))));
+#pragma unroll
+      for (int t = 0; t < NT; ++t) b[t][m] = pf_as_bf16x8(*reinterpret_cast<const uint4*>(st + (b_off[t] ^ (m << 6))));
     }
-    // every request of the batch is out before the first result is used (left alone the
-    // compiler recycles a few registers and the loads trickle out a handful at a time)
-    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (read, before the slot is filled again)
+    if (i + DEPTH < n) request(i + DEPTH, slot);
+    slot = slot + 1 == DEPTH ? 0 : slot + 1;
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+    for (int m = 0; m < 2; ++m)
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(pf_bf16x8, a[u][0]), __builtin_bit_cast(pf_bf16x8, b[u][t][0]), acc[t], 0, 0, 0);
-        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(pf_bf16x8, a[u][1]), __builtin_bit_cast(pf_bf16x8, b[u][t][1]), acc[t], 0, 0, 0);
-      }
+      for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], b[t][m], acc[t], 0, 0, 0);
   }
-  for (; s < n_steps; s += NW) {
-    const uint4 a0 = *reinterpret_cast<const uint4*>(wq + s * 64);
-    const uint4 a1 = *reinterpret_cast<const uint4*>(wq + s * 64 + 8);
+  // acc[t], register e, lane (l16, g4): row 4 g4 + e, token 16 t + l16; every wave's partial tiles to the start of its ring
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const uint4 b0 = *reinterpret_cast<const uint4*>(xp[t] + 8 * g4 + s * 64);
-      const uint4 b1 = *reinterpret_cast<const uint4*>(xp[t] + 8 * g4 + s * 64 + 8);
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pf_as_bf16x8(a0), pf_as_bf16x8(b0), acc[t], 0, 0, 0);
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pf_as_bf16x8(a1), pf_as_bf16x8(b1), acc[t], 0, 0, 0);
-    }
-  }
-  // acc[t], register e, lane (l16, g4): tile row (feature) 4 g4 + e, token 16 t + l16
-#pragma unroll
-  for (int t = 0; t < NT; ++t) *reinterpret_cast<pf_f32x4*>(&red[wave][t][lane * 4]) = acc[t];
+  for (int t = 0; t < NT; ++t) *reinterpret_cast<pf_f32x4*>(smem + wave * RING + (t * 256 + lane * 4) * 4) = acc[t];
   __syncthreads();
 
-  // thread (t, i < 8, token): sums the 8 partial tiles for rows i and i + 8, rotates, stores
-  if (tid >= NT * 128) return;
-  const int t = tid >> 7, i = (tid >> 4) & 7, tk = tid & 15;
-  const int tok = tok0 + 16 * t + tk;
-  if (tok >= n_new || pos0 + tok < 0) return;
-  const int at_lo = (tk + 16 * (i >> 2)) * 4 + (i & 3);  // row i      -> lane tk + 16 (i/4), register i%4
-  const int at_hi = at_lo + 128;                         // row i + 8  -> two lane groups further
+  const bool is_l = q == pp;
+  if (q > pp || (is_l ? bx >= p.rank : pair >= HD)) return;
+  const int tok = tok0 + 16 * t_sum + tk, j = append_length(len_raw, p.max_seq_len) - n_new + tok;
+  if (16 * t_sum + tk >= 8 * XI || tok >= n_new || j < 0) return;
+  const int r_lo = is_l ? 2 * pp : q, r_hi = is_l ? 2 * pp : pp + q;  // tile row -> lane tk + 16 (row / 4), register row % 4
+  const float* from = reinterpret_cast<const float*>(smem) + t_sum * 256 + 4 * tk;
   float lo = 0.f, hi = 0.f;
 #pragma unroll
   for (int w = 0; w < NW; ++w) {
-    lo += red[w][t][at_lo];
-    hi += red[w][t][at_hi];
+    lo += from[w * (RING / 4) + 64 * (r_lo >> 2) + (r_lo & 3)];
+    hi += from[w * (RING / 4) + 64 * (r_hi >> 2) + (r_hi & 3)];
   }
-  const int j = pos0 + tok;
-  if (kind == 2) {
-    int64_t row_off;
-    if (PAGED) {
-      const int blk = p.block_table[static_cast<int64_t>(p.seq_index) * p.max_blocks_per_seq + (j >> 4)];
-      row_off = (static_cast<int64_t>(blk) * 16 + (j & 15)) * p.l_row_stride;
-    } else {
-      row_off = static_cast<int64_t>(j) * p.l_row_stride;
-    }
-    bf16_t* lrow = static_cast<bf16_t*>(p.l) + row_off;
-    const int f = 16 * fg_in + i;
-    if (f < p.rank) lrow[f] = f32_to_bf16(lo);
-    if (f + 8 < p.rank) lrow[f + 8] = f32_to_bf16(hi);
+  int64_t blk = 0;
+  if (PAGED) blk = p.block_table[static_cast<int64_t>(p.seq_index) * p.max_blocks_per_seq + (j >> 4)];
+  if (is_l) {
+    const int64_t row = PAGED ? blk * 16 + (j & 15) : j;
+    static_cast<bf16_t*>(p.l)[row * p.l_row_stride + bx] = f32_to_bf16(lo);
     return;
   }
-  const int dd = 8 * sub + i;  // < d/2
-  if (kind == 0 && p.rope_theta > 0.f) {
+  const bool is_k = pair < HD / 2;
+  if (is_k && p.rope_theta > 0.f) {
     float sn, cs;
-    rope_sincos(rope_rate_rev(dd, D, p.rope_theta), j, sn, cs);
-    const float a = lo, b = hi;
-    lo = a * cs - b * sn;
-    hi = b * cs + a * sn;
+    rope_sincos(rate, j, sn, cs);
+    const float x = lo, y = hi;
+    lo = x * cs - y * sn;
+    hi = y * cs + x * sn;
   }
-  int64_t row_off;
-  if (PAGED) {
-    const int blk = p.block_table[static_cast<int64_t>(p.seq_index) * p.max_blocks_per_seq + (j >> 4)];
-    row_off = static_cast<int64_t>(blk) * p.kv_block_stride + static_cast<int64_t>(j & 15) * p.kv_token_stride;
-  } else {
-    row_off = static_cast<int64_t>(j) * p.kv_token_stride;
-  }
-  bf16_t* dst = static_cast<bf16_t*>(kind == 0 ? p.k_base : p.v_base) + row_off + static_cast<int64_t>(head) * p.kv_head_stride + dd;
+  const int f = feature(is_k ? pair : pair - HD / 2), head = f / D;
+  const int64_t row_off = PAGED ? blk * p.kv_block_stride + static_cast<int64_t>(j & 15) * p.kv_token_stride : static_cast<int64_t>(j) * p.kv_token_stride;
+  bf16_t* dst = static_cast<bf16_t*>(is_k ? p.k_base : p.v_base) + row_off + static_cast<int64_t>(head) * p.kv_head_stride + (f - head * D);
   dst[0] = f32_to_bf16(lo);
   dst[D / 2] = f32_to_bf16(hi);
 }
 
 // ---------------------------------------------------------------------------------------
-// One or two new tokens (every decode step appends one): a matrix-vector product.  One wave
+// One new token (every decode step appends one): a matrix-vector product.  One wave
 // per weight row reads it in fully coalesced 1 KB pieces, all in flight at once, and forms
 // the dot products with v_dot2c_f32_bf16; the 2 * Hkv * d + r rows make several hundred
 // workgroups, enough outstanding loads to run at HBM speed.  A workgroup's four rows are two
@@ -868,9 +887,9 @@ __global__ __launch_bounds__(512) void append_skinny_kernel(AppendParams p) {
 // ---------------------------------------------------------------------------------------
 typedef __bf16 ap_bf16x2 __attribute__((ext_vector_type(2)));
 
-template <int D, int NT, bool PAGED>
+template <int D, bool PAGED>
 __global__ __launch_bounds__(256) void append_gemv_kernel(AppendParams p) {
-  __shared__ float red[4][NT];
+  __shared__ float red[4];
   // A call of this kernel is one round of requests and a handful of dependent latencies; each is
   // kept off the others' path: the parameter block comes in one round trip, the sequence length
   // (needed only by the last step) is requested first and by hand, the weight requests (the bytes
@@ -879,7 +898,7 @@ __global__ __launch_bounds__(256) void append_gemv_kernel(AppendParams p) {
   // compiler wait for earlier loads on the spot), and the rotation rate of the pair (double
   // precision exp2 and log2) is worked out while the requests are in flight.
   asm volatile("" ::"s"(p.w), "s"(p.x), "s"(p.seq_lens), "s"(p.k_base), "s"(p.v_base), "s"(p.l));
-  asm volatile("" ::"s"(p.d_model), "s"(p.n_kv_heads), "s"(p.rank), "s"(p.n_new), "s"(p.seq_index), "s"(p.max_seq_len),
+  asm volatile("" ::"s"(p.d_model), "s"(p.n_kv_heads), "s"(p.rank), "s"(p.seq_index), "s"(p.max_seq_len),
                "s"(p.rope_theta), "s"(p.kv_token_stride), "s"(p.kv_head_stride), "s"(p.l_row_stride));
   int len_raw;
   asm volatile("s_load_dword %0, %1, 0x0" : "=s"(len_raw) : "s"(p.seq_lens + p.seq_index));
@@ -896,17 +915,11 @@ __global__ __launch_bounds__(256) void append_gemv_kernel(AppendParams p) {
   // row of this wave: K/V  head*D + 2 sub + pr (+ d/2 for the second half);  L  4 fg_in + pr + 2 half
   const int feat = kind == 2 ? 4 * fg_in + pr + 2 * half : head * D + 2 * sub + pr + half * (D / 2);
   const int w_row = kind == 2 ? 2 * HD + min(feat, p.rank - 1) : (kind == 1 ? HD : 0) + feat;
-  const int n_new = p.n_new;
   const int64_t ld = p.d_model;
   const uint4* wp = reinterpret_cast<const uint4*>(static_cast<const bf16_t*>(p.w) + static_cast<int64_t>(w_row) * ld);
-  const uint4* xp[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-    xp[t] = reinterpret_cast<const uint4*>(static_cast<const bf16_t*>(p.x) + static_cast<int64_t>(min(t, n_new - 1)) * ld);
+  const uint4* xp = static_cast<const uint4*>(p.x);
 
-  float acc[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) acc[t] = 0.f;
+  float acc = 0.f;
   const int n_chunks = p.d_model / 8;  // 16-byte pieces of a row; lane l takes l, l + 64, ...
   constexpr int U = 8;
   double rate = 0.0;  // revolutions per position of this thread's rotary pair (threads of the last step)
@@ -921,46 +934,36 @@ __global__ __launch_bounds__(256) void append_gemv_kernel(AppendParams p) {
     // all weight requests out before anything else.  (The operands stay HIP's uint4 structs on purpose:
     // with native 4-vectors this compiler selected element 0 for all four dot products.)
     __builtin_amdgcn_sched_barrier(0);
-    uint4 xv[NT][U];
+    uint4 xv[U];
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-      for (int u = 0; u < U; ++u) xv[t][u] = xp[t][min(c0 + 64 * u, n_chunks - 1)];
+    for (int u = 0; u < U; ++u) xv[u] = xp[min(c0 + 64 * u, n_chunks - 1)];
     __builtin_amdgcn_sched_barrier(0);
-    if (c0 == lane && tid < 2 * NT && kind == 0 && p.rope_theta > 0.f) {
+    if (c0 == lane && tid < 2 && kind == 0 && p.rope_theta > 0.f) {
       rate = rope_rate_rev(2 * sub + (tid & 1), D, p.rope_theta);
       asm volatile("" ::"v"(rate));  // (here, under the requests, not after the reduction)
     }
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        uint4 x4 = xv[t][u];
-        if (c0 + 64 * u >= n_chunks) x4 = make_uint4(0u, 0u, 0u, 0u);  // (a piece beyond the row)
-        acc[t] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(ap_bf16x2, wv[u].x), __builtin_bit_cast(ap_bf16x2, x4.x), acc[t], false);
-        acc[t] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(ap_bf16x2, wv[u].y), __builtin_bit_cast(ap_bf16x2, x4.y), acc[t], false);
-        acc[t] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(ap_bf16x2, wv[u].z), __builtin_bit_cast(ap_bf16x2, x4.z), acc[t], false);
-        acc[t] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(ap_bf16x2, wv[u].w), __builtin_bit_cast(ap_bf16x2, x4.w), acc[t], false);
-      }
+    for (int u = 0; u < U; ++u) {
+      uint4 x4 = xv[u];
+      if (c0 + 64 * u >= n_chunks) x4 = make_uint4(0u, 0u, 0u, 0u);  // (a piece beyond the row)
+      acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(ap_bf16x2, wv[u].x), __builtin_bit_cast(ap_bf16x2, x4.x), acc, false);
+      acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(ap_bf16x2, wv[u].y), __builtin_bit_cast(ap_bf16x2, x4.y), acc, false);
+      acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(ap_bf16x2, wv[u].z), __builtin_bit_cast(ap_bf16x2, x4.z), acc, false);
+      acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(ap_bf16x2, wv[u].w), __builtin_bit_cast(ap_bf16x2, x4.w), acc, false);
     }
   }
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    float v = acc[t];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    if (lane == 0) red[wave][t] = v;
-  }
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+  if (lane == 0) red[wave] = acc;
   __syncthreads();
 
-  // thread (pair, token): both halves of a rotary pair (K), two independent features (V, L)
-  if (tid >= 2 * NT) return;
-  const int q = tid & 1, t = tid >> 1;
+  // thread = pair: both halves of a rotary pair (K), two independent features (V, L)
+  if (tid >= 2) return;
+  const int q = tid;
   asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(len_raw));
-  const int n_t = append_length(len_raw, p.max_seq_len);
-  const int j = n_t - n_new + t;
-  if (t >= n_new || j < 0) return;
-  float lo = red[q][t], hi = red[2 + q][t];
+  const int j = append_length(len_raw, p.max_seq_len) - 1;
+  if (j < 0) return;
+  float lo = red[q], hi = red[2 + q];
   if (kind == 2) {
     int64_t row_off;
     if (PAGED) {
@@ -1090,20 +1093,42 @@ __global__ __launch_bounds__(256) void append_finish_kernel(AppendParams p) {
   }
 }
 
-template <int D, int NT>
+template <int D>
 static void launch_gemv(const AppendParams& p, hipStream_t s) {
   const int hd = p.n_kv_heads * p.head_dim;
   dim3 grid(2 * (hd / 4) + (p.rank + 3) / 4);
-  if (p.block_size != 0) hipLaunchKernelGGL((append_gemv_kernel<D, NT, true>), grid, dim3(256), 0, s, p);
-  else hipLaunchKernelGGL((append_gemv_kernel<D, NT, false>), grid, dim3(256), 0, s, p);
+  if (p.block_size != 0) hipLaunchKernelGGL((append_gemv_kernel<D, true>), grid, dim3(256), 0, s, p);
+  else hipLaunchKernelGGL((append_gemv_kernel<D, false>), grid, dim3(256), 0, s, p);
 }
 
-template <int D, int NT>
-static void launch_skinny(const AppendParams& p, hipStream_t s) {
-  const int hd = p.n_kv_heads * p.head_dim;
-  dim3 grid(2 * (hd / 16) + (p.rank + 15) / 16, (p.n_new + 16 * NT - 1) / (16 * NT));
-  if (p.block_size != 0) hipLaunchKernelGGL((append_skinny_kernel<D, NT, true>), grid, dim3(512), 0, s, p);
-  else hipLaunchKernelGGL((append_skinny_kernel<D, NT, false>), grid, dim3(512), 0, s, p);
+template <int D, int WI, int XI>
+static void launch_skinny(const AppendParams& p, int pp, hipStream_t s) {
+  const dim3 grid((p.n_kv_heads * D + pp - 1) / pp, (p.n_new + 8 * XI - 1) / (8 * XI));
+  if (p.block_size != 0) hipLaunchKernelGGL((append_skinny_kernel<D, WI, XI, true>), grid, dim3(512), 0, s, p, pp);
+  else hipLaunchKernelGGL((append_skinny_kernel<D, WI, XI, false>), grid, dim3(512), 0, s, p, pp);
+}
+
+// Pairs per workgroup: one workgroup per compute unit while its rows fit the 16 of a product (up to 1792 K features), else two (16
+// kv heads on 4096, 8 tokens: 9.9 us with 4 pairs, 11.2 with 7), and beyond 3072 six pairs (32 kv heads: 15.3 with 6, 15.7 with
+// 7, 16.2 with 4).  Two per unit on smaller layers read x twice as often (8 kv heads on 4096, 3 tokens: 6.0 and 7.3).
+// There are 64 workgroups or more, a workgroup for every L feature.
+template <int D>
+static void launch_skinny_tokens(const AppendParams& p, hipStream_t s) {
+  const int hd = p.n_kv_heads * D;
+  const int pp = hd <= 1792 ? (hd + 255) / 256 : (hd <= 3072 ? (hd + 511) / 512 : 6);
+#define LRA_SKINNY(XI)                                                    \
+  (pp <= 3 ? launch_skinny<D, 1, XI>(p, pp, s) : launch_skinny<D, 2, XI>(p, pp, s))
+  switch ((p.n_new + 7) / 8) {
+    case 1: return LRA_SKINNY(1);
+    case 2: return LRA_SKINNY(2);
+    case 3: return LRA_SKINNY(3);
+    case 4: return LRA_SKINNY(4);
+    case 5: return LRA_SKINNY(5);
+    case 6: return LRA_SKINNY(6);
+    case 7: return LRA_SKINNY(7);
+    default: return LRA_SKINNY(8);
+  }
+#undef LRA_SKINNY
 }
 
 // Whether the 256 x 256 tiles, one workgroup per compute unit, are faster than the 128 x 128 tiles with two.  An XCD
@@ -1154,27 +1179,9 @@ hipError_t launch_append(const AppendParams& p, bool quarter_tiles, hipStream_t 
 #undef LRA_APPEND_SPLIT
     return hipGetLastError();
   }
-  if (p.n_new <= 2 && p.n_new <= p.skinny_max) {
-    if (p.head_dim == 128) {
-      if (p.n_new == 1) launch_gemv<128, 1>(p, s);
-      else launch_gemv<128, 2>(p, s);
-    } else {
-      if (p.n_new == 1) launch_gemv<64, 1>(p, s);
-      else launch_gemv<64, 2>(p, s);
-    }
-    return hipGetLastError();
-  }
   if (p.n_new <= p.skinny_max) {
-    const int nt = p.n_new <= 16 ? 1 : (p.n_new <= 32 ? 2 : 4);
-    if (p.head_dim == 128) {
-      if (nt == 1) launch_skinny<128, 1>(p, s);
-      else if (nt == 2) launch_skinny<128, 2>(p, s);
-      else launch_skinny<128, 4>(p, s);
-    } else {
-      if (nt == 1) launch_skinny<64, 1>(p, s);
-      else if (nt == 2) launch_skinny<64, 2>(p, s);
-      else launch_skinny<64, 4>(p, s);
-    }
+    if (p.head_dim == 128) p.n_new == 1 ? launch_gemv<128>(p, s) : launch_skinny_tokens<128>(p, s);
+    else p.n_new == 1 ? launch_gemv<64>(p, s) : launch_skinny_tokens<64>(p, s);
     return hipGetLastError();
   }
   if (quarter_tiles) {

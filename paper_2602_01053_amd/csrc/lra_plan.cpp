@@ -52,11 +52,20 @@ bool append_quarter_tiles(int n_new, int n_kv_heads, int head_dim, int rank, int
   return tiles * 64 >= 3 * static_cast<int64_t>(d_model) && tiles <= (feature_tiles <= 8 ? 216 : kCUs);
 }
 
+// Chunks whose division of d_model below is set aside for the weight-streaming kernel, one launch: while x, which each of its
+// workgroups reads, is at most 416 KB and the layer's rows fit one workgroup per compute unit (us streamed and divided:
+// Llama-3-8B projection 33 tokens 9.4 / 11.5, 48 11.2 / 12.0, 64 12.8 / 12.1; 4 kv heads on 3584, 33 tokens 6.2 / 8.0,
+// 64 8.4 / 9.2; 12 on 2048, 64 9.2 / 10.6; 8 on 8192, 33 15.9 / 15.1; 16 on 4096, 33 18.7 / 15.1).
+bool append_streams(int n_new, int n_kv_heads, int head_dim, int d_model, const Tuning& tune) {
+  return tune.append_k_splits == 0 && n_new <= tune.append_skinny && n_new <= 64 && n_kv_heads * static_cast<int64_t>(head_dim) <= 1792 &&
+         static_cast<int64_t>(n_new) * d_model <= 208 * 1024;
+}
+
 // A chunk whose output tiles of 128 features x 64 tokens occupy about half of the chip or less walks all of d_model
 // in each of them, one 64-wide step after the other, at what one compute unit can pull from L2.  Such chunks divide
 // d_model among several workgroups per tile (a power of two of parts, at least four steps each, about one workgroup
 // per compute unit in all) and add the parts in a second kernel.  Measured on the Llama-3-8B projection: 64 tokens 10
-// against 18 us, 160 tokens 12 against 19 us; up to 32 tokens the weight-streaming kernel is as fast and stays.  Chunks
+// against 18 us, 160 tokens 12 against 19 us; up to 32 tokens the weight-streaming kernel is faster and stays.  Chunks
 // of more than 100 tiles of 128 tokens fill the chip with tiles of 64 in one round, unsplit (8 kv heads of 64 on 2048,
 // 1500 new tokens: 13 us, divided in two 19).  Forced tile or stage choices keep the unsplit kernels.
 AppendSplit plan_append_split(int n_new, int n_kv_heads, int head_dim, int rank, int d_model, const Tuning& tune) {

@@ -69,6 +69,8 @@ struct AppendSplit {
 // Whether tiles of 64 features x 64 tokens run instead (append_quarter_kernel); such a call is not split, whatever the
 // split's plan says (what a call is told to bring as workspace does not depend on it).
 bool append_quarter_tiles(int n_new, int n_kv_heads, int head_dim, int rank, int d_model, const Tuning& tune);
+// Whether the weight-streaming kernel runs in place of the divided GEMM (as above: whatever the split's plan says).
+bool append_streams(int n_new, int n_kv_heads, int head_dim, int d_model, const Tuning& tune);
 AppendSplit plan_append_split(int n_new, int n_kv_heads, int head_dim, int rank, int d_model, const Tuning& tune);
 
 // Row tiles per workgroup the split-KV MFMA kernels are built for.
