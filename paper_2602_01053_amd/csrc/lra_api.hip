@@ -37,8 +37,11 @@ static void fill_params(Params& p, const lra_shape* sh, const lra_cache* c, cons
   p.l_row_stride = c->l_row_stride ? c->l_row_stride : sh->rank;
   p.l_adapter_stride = c->l_adapter_stride;
   p.l_block = pl.l_block;
-  // wide L rows (64 bytes per token and more, or one low-rank cache per adapter): the kv heads of a key share on one XCD
-  p.share_major = (sh->rank >= 32 || pl.l_block != 0) ? 1 : 0;
+  // wide L rows (64 bytes per token and more, or one low-rank cache per adapter): the kv heads of a key share on one XCD, where no
+  // XCD then gets more workgroups than it has compute units (key share s runs on XCD s mod 8; 8 agents with caches of their own at
+  // rank 64 on 30000 keys, four shares of 64 workgroups: 153 us so, on four XCDs in two rounds, 84 with the kv heads over the XCDs;
+  // 6 agents at rank 32, ten shares of 24: 73 and 44)
+  p.share_major = (sh->rank >= 32 || pl.l_block != 0) && (pl.n_splits + 7) / 8 * sh->n_kv_heads * pl.row_groups <= kCUs / 8 ? 1 : 0;
   p.n_q_heads = sh->n_q_heads;
   p.n_kv_heads = sh->n_kv_heads;
   p.group = sh->n_q_heads / sh->n_kv_heads;
