@@ -604,7 +604,14 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
       split_keys = c->max_seq_len;  // more units than workgroups wanted: one share per sequence
     } else {
       const int64_t key_heads = work * c->max_seq_len / (batch ? 2 : 1);
-      const int64_t sk = (key_heads + wgs - 1) / wgs;
+      int64_t sk = (key_heads + wgs - 1) / wgs;
+      // One sequence: never a few more workgroups than that, for a second round, where the units do not divide them.  (us before
+      // and now: 12 kv heads, 12 agents in two row groups, rank 32, 20000 keys, eleven shares and ten 45 / 38; paged, 8 kv heads,
+      // 6 agents with low-rank caches of their own at rank 32, 30000 keys, 22 shares and 21 64 / 44)
+      if (!batch && !rope && work <= wgs) {
+        const int64_t least = (c->max_seq_len + wgs / work - 1) / (wgs / work);
+        sk = sk > least ? sk : least;
+      }
       split_keys = sk > c->max_seq_len ? c->max_seq_len : static_cast<int>(sk);
     }
   } else if (split_keys <= 0) {
