@@ -605,12 +605,17 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
     } else {
       const int64_t key_heads = work * c->max_seq_len / (batch ? 2 : 1);
       int64_t sk = (key_heads + wgs - 1) / wgs;
-      // One sequence: never a few more workgroups than that, for a second round, where the units do not divide them.  (us before
+      // One sequence: no last share more than fit, for a second round, where the units do not divide the workgroups.  (us before
       // and now: 12 kv heads, 12 agents in two row groups, rank 32, 20000 keys, eleven shares and ten 45 / 38; paged, 8 kv heads,
-      // 6 agents with low-rank caches of their own at rank 32, 30000 keys, 22 shares and 21 64 / 44)
-      if (!batch && !rope && work <= wgs) {
-        const int64_t least = (c->max_seq_len + wgs / work - 1) / (wgs / work);
-        sk = sk > least ? sk : least;
+      // 6 agents with low-rank caches of their own at rank 32, 30000 keys, 22 shares and 21 64 / 44; rotary, 4 kv heads, 5 agents
+      // of 7 heads at rank 64, 30000 keys, 22 and 20 77 / 56.)  In the rotary form, whose tiles take longest, a last share may stay
+      // that is no longer than what the others would grow by: 24 units, 9000 keys, ten shares of seven tiles and one of one 48 us,
+      // nine of eight 53.
+      if (!batch && work <= wgs) {
+        const int64_t shares = wgs / work, least = (c->max_seq_len + shares - 1) / shares;
+        const int64_t t = (sk + tile - 1) / tile, t_least = (least + tile - 1) / tile, all = (static_cast<int64_t>(c->max_seq_len) + tile - 1) / tile;
+        const int64_t last = all - (all - 1) / t * t;
+        if ((all + t - 1) / t > shares && (!rope || t + last > t_least)) sk = sk > least ? sk : least;
       }
       split_keys = sk > c->max_seq_len ? c->max_seq_len : static_cast<int>(sk);
     }
