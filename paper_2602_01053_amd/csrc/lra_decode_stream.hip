@@ -34,6 +34,7 @@
 //     flash-decoding weights, in wave order).
 #include "lra_common.h"
 #include "lra_decode_util.h"
+#include "lra_plan.h"
 
 namespace lra {
 
@@ -933,13 +934,7 @@ static hipError_t launch_stream2(const Params& p, dim3 grid, hipStream_t s) {
 
 // main_kernel_only (measurement): the streaming kernel alone, on whatever Qt an earlier call left
 hipError_t launch_decode_stream(const Params& p, int row_tiles, bool main_kernel_only, hipStream_t s) {
-  // Several row groups read the same keys: their workgroups of one share had better meet on one XCD, so the workgroups of a row
-  // group are filled up to a multiple of eight (those without a share end at once), unless an XCD then had more than its 32 compute
-  // units (4 kv heads of group 7, 37000 keys, rank 16: 29 shares, two row groups of 7 agents 34.8 us without the three, 28.6
-  // with them; 21 shares, three row groups 36 without the one, 53 with it, 33 workgroups on four XCDs).
-  int shares = p.n_splits;
-  if (p.row_groups > 1 && (p.n_kv_heads * shares + 7) / 8 * p.row_groups <= 32)
-    while (shares * p.n_kv_heads % 8 != 0) ++shares;
+  const int shares = stream_grid_shares(p.n_kv_heads, p.n_splits, p.row_groups);
   const dim3 grid = p.share_major ? dim3(8 * p.n_kv_heads, (p.n_splits + 7) / 8, p.row_groups)
                                   : dim3(p.n_kv_heads, shares, p.row_groups);  // (see the index layouts in the kernel)
   if (p.qt_ws != nullptr && !main_kernel_only) {

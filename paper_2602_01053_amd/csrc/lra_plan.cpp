@@ -96,6 +96,18 @@ AppendSplit plan_append_split(int n_new, int n_kv_heads, int head_dim, int rank,
   return sp;
 }
 
+// Several row groups read the same keys: their workgroups of one share had better meet on one XCD, so the workgroups of a row
+// group are filled up to a multiple of eight (those without a share end at once), unless an XCD then had more workgroups than its
+// 32 compute units, the empty ones counted: they hold a unit of their own for a moment, and what is behind them starts a second
+// round (us without the fill and with it; 4 kv heads of group 7, 37000 keys, rank 16, 29 shares, two row groups of 7 agents 34.8 and 28.6;
+// 21 shares, three row groups 36 and 53; 12 kv heads, 3 shares, six row groups of 41 agents on 44401 keys, 30 workgroups with keys
+// and 6 without on an XCD, 165 and 316; 6 kv heads, 13 shares, three row groups on 6635 keys 24.2 and 31.6).
+int stream_grid_shares(int n_kv_heads, int n_splits, int row_groups) {
+  int shares = n_splits;
+  while (shares * n_kv_heads % 8 != 0) ++shares;
+  return row_groups > 1 && shares * n_kv_heads / 8 * row_groups <= kCUs / 8 ? shares : n_splits;
+}
+
 int decode_mfma_row_tiles(int rows_needed) { return rows_needed <= 16 ? 1 : 2; }
 
 // (the B_K^T operands of a tile's slots stay in registers: 4 slots at ranks up to 16, 2 up to 32, 4

@@ -73,6 +73,9 @@ bool append_quarter_tiles(int n_new, int n_kv_heads, int head_dim, int rank, int
 bool append_streams(int n_new, int n_kv_heads, int head_dim, int d_model, const Tuning& tune);
 AppendSplit plan_append_split(int n_new, int n_kv_heads, int head_dim, int rank, int d_model, const Tuning& tune);
 
+// Key shares of the streaming kernel's grid where the kv head is its fastest index: the call's, or more, which end at once.
+int stream_grid_shares(int n_kv_heads, int n_splits, int row_groups);
+
 // Row tiles per workgroup the split-KV MFMA kernels are built for.
 int decode_mfma_row_tiles(int rows_needed);
 // Agent slots a 16-row tile may hold in the rotary form of the split-KV kernel.

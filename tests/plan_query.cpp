@@ -19,6 +19,8 @@ extern "C" void plan_query(const lra_shape* sh, const lra_cache* c, int tokens, 
   out[12] = pl.group_pad;
 }
 
+extern "C" int stream_grid_query(int n_kv_heads, int n_splits, int row_groups) { return lra::stream_grid_shares(n_kv_heads, n_splits, row_groups); }
+
 extern "C" int append_query(int n_new, int n_kv_heads, int head_dim, int rank, int d_model, const lra_tuning* tuning) {
   const lra::Tuning t = lra::resolve_tuning(tuning);
   if (lra::append_quarter_tiles(n_new, n_kv_heads, head_dim, rank, d_model, t)) return -1;
