@@ -160,16 +160,12 @@ hipError_t launch_decode_mfma(const Params& p, int row_tiles, bool allow_stream_
   dim3 grid(p.n_kv_heads, p.n_splits, (p.is_prefill ? 1 : p.n_seqs) * p.row_groups);
   Params pi = p;
   pi.rg_interleave = 0;
-  if (p.row_groups > 1) {
+  const int n_seqs = p.is_prefill ? 1 : p.n_seqs;
+  const int m = mfma_interleave(p.n_kv_heads, p.n_splits, p.row_groups, n_seqs, p.key_rope_theta > 0.f && p.b_k != nullptr, p.rank);
+  if (m > 0) {
     // (see the kernel: row groups of a key share next to each other on one XCD)
-    int g = p.n_kv_heads, e = 8;
-    while (e) { const int tmp = g % e; g = e; e = tmp; }  // g = gcd(Hkv, 8)
-    const int m = 8 / g;
-    const int64_t gy = static_cast<int64_t>((p.n_splits + m - 1) / m) * m * p.row_groups;
-    if (gy <= 65535) {
-      pi.rg_interleave = m;
-      grid = dim3(p.n_kv_heads, static_cast<unsigned>(gy), p.is_prefill ? 1 : p.n_seqs);
-    }
+    pi.rg_interleave = m;
+    grid = dim3(p.n_kv_heads, static_cast<unsigned>((p.n_splits + m - 1) / m * m * p.row_groups), n_seqs);
   }
   return launch_decode_mfma_grid(pi, row_tiles, grid, s);
 }

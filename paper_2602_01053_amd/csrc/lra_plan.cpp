@@ -108,6 +108,27 @@ int stream_grid_shares(int n_kv_heads, int n_splits, int row_groups) {
   return row_groups > 1 && shares * n_kv_heads / 8 * row_groups <= kCUs / 8 ? shares : n_splits;
 }
 
+// lcm(8, Hkv) / Hkv: key shares after which the kv heads of a share are on the XCDs of the first again.
+static int interleave_step(int n_kv_heads) {
+  int m = 8;
+  while (m > 1 && n_kv_heads * (m / 2) % 8 == 0) m /= 2;
+  return m;
+}
+
+// The rotary forms, which the vector unit bounds, take the interleaved grid, and the workgroups without keys that pad it, only where
+// a call whose workgroups are all resident at once does not come to another workgroup per compute unit (ranks up to 32 hold two,
+// above one; us interleaved / not: 5 kv heads, rank 64, 12 tokens after 21466, 255 workgroups and 360 padded 65.8 / 39.7, 16 tokens
+// 87.3 / 48.3; 12 kv heads, rank 48, 16 after 607 18.0 / 12.6; 5 kv heads, 4 agents on 41459, rank 32, 500 and 560 52.4 / 46.7).
+int mfma_interleave(int n_kv_heads, int n_splits, int row_groups, int n_seqs, bool rotary, int rank) {
+  if (row_groups <= 1) return 0;
+  const int m = interleave_step(n_kv_heads);
+  const int64_t shares = (static_cast<int64_t>(n_splits) + m - 1) / m * m;
+  if (shares * row_groups > 65535) return 0;
+  const int64_t units = static_cast<int64_t>(n_kv_heads) * row_groups * n_seqs;
+  if (rotary && units * n_splits <= (rank > 32 ? kCUs : 2 * kCUs) && (units * shares + kCUs - 1) / kCUs > (units * n_splits + kCUs - 1) / kCUs) return 0;
+  return m;
+}
+
 int decode_mfma_row_tiles(int rows_needed) { return rows_needed <= 16 ? 1 : 2; }
 
 // (the B_K^T operands of a tile's slots stay in registers: 4 slots at ranks up to 16, 2 up to 32, 4
