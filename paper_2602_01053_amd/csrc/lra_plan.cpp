@@ -115,6 +115,12 @@ static int interleave_step(int n_kv_heads) {
   return m;
 }
 
+// The key shares that fit, or up to a sixteenth less where the row groups of each share then meet on one XCD.
+static int64_t meeting_shares(int64_t fit, int n_kv_heads, int row_groups) {
+  const int m = row_groups > 1 ? interleave_step(n_kv_heads) : 1;
+  return fit / m * m * 16 >= fit * 15 ? fit / m * m : fit;
+}
+
 // The rotary forms, which the vector unit bounds, take the interleaved grid, and the workgroups without keys that pad it, only where
 // a call whose workgroups are all resident at once does not come to another workgroup per compute unit (ranks up to 32 hold two,
 // above one; us interleaved / not: 5 kv heads, rank 64, 12 tokens after 21466, 255 workgroups and 360 padded 65.8 / 39.7, 16 tokens
@@ -641,11 +647,15 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
       // One sequence: no last share more than fit, for a second round, where the units do not divide the workgroups.  (us before
       // and now: 12 kv heads, 12 agents in two row groups, rank 32, 20000 keys, eleven shares and ten 45 / 38; paged, 8 kv heads,
       // 6 agents with low-rank caches of their own at rank 32, 30000 keys, 22 shares and 21 64 / 44; rotary, 4 kv heads, 5 agents
-      // of 7 heads at rank 64, 30000 keys, 22 and 20 77 / 56.)  In the rotary form, whose tiles take longest, a last share may stay
-      // that is no longer than what the others would grow by: 24 units, 9000 keys, ten shares of seven tiles and one of one 48 us,
-      // nine of eight 53.
-      if (!batch && work <= wgs) {
-        const int64_t shares = wgs / work, least = (c->max_seq_len + shares - 1) / shares;
+      // of 7 heads at rank 64, 30000 keys, 22 and 20 77 / 56.)  Not where less than three quarters of the places are taken then (12 kv
+      // heads, 96 agents in twelve row groups, rank 32, 13895 keys, two shares 125 and one 156; 160 units of 256 0.90 to 1.12 of 32
+      // calls, 192 and more 1.0 to 1.4 of 140), nor on the split-KV kernel while it has places left, two per unit (paged, 16 kv
+      // heads, 6 agents with low-rank caches of their own at rank 32, 1304 keys, six shares 13.1, four 14.8).  In the rotary form, whose tiles take longest, a last share may stay that is no longer than what the others would grow by: 24
+      // units, 9000 keys, ten shares of seven tiles and one of one 48 us, nine of eight 53.
+      const bool streams = !rope && tune.variant != 2 && (c->block_size == 0 || paged_stream);
+      if (!batch && work <= wgs && (rope || wgs > kCUs || (streams && wgs / work * work * 4 >= 3 * wgs))) {
+        const int64_t shares = streams ? meeting_shares(wgs / work, sh->n_kv_heads, pl.row_groups) : wgs / work;
+        const int64_t least = (c->max_seq_len + shares - 1) / shares;
         const int64_t t = (sk + tile - 1) / tile, t_least = (least + tile - 1) / tile, all = (static_cast<int64_t>(c->max_seq_len) + tile - 1) / tile;
         const int64_t last = all - (all - 1) / t * t;
         if ((all + t - 1) / t > shares && (!rope || t + last > t_least)) sk = sk > least ? sk : least;

@@ -15,7 +15,27 @@ def test_one_round(planner, paged, side):  # noqa: F811
                         pl = _plan(planner, hkv * group, hkv, 128, r, [n], agents=agents, paged=paged, side=side)
                         units = hkv * pl["row_groups"]
                         # the split-KV kernel, two workgroups per unit, reads caches of blocks with low-rank rows per adapter
-                        room = 512 if paged and side == "own" and units * n >= 512 * 512 else 256
+                        room = 512 if paged and side == "own" else 256
                         if pl["mfma"] and units <= room:
                             short = 1 if side == "rotary" else 0  # (a last, short share may begin a second one)
                             assert units * (pl["n_splits"] - short) <= room, (hkv, group, agents, r, n, units, pl["n_splits"])
+
+
+def test_one_round_fills_the_chip(planner):  # noqa: F811
+    """The shares are cut down to one round only where that leaves three quarters of the places taken, and with several row groups
+    to a count whose workgroups meet on one XCD where there is one within a sixteenth."""
+    def splits(hkv, group, agents, n, r=16, paged=False, side="bk"):
+        pl = _plan(planner, hkv * group, hkv, 128, r, [n], agents=agents, paged=paged, side=side)
+        return hkv * pl["row_groups"], pl["n_splits"]
+
+    assert splits(24, 1, 45, 4465) == (144, 2)    # 144 of 256 in one round: two
+    assert splits(32, 1, 35, 22237) == (160, 2)
+    assert splits(32, 1, 41, 8000) == (192, 1)    # 192: one
+    assert splits(12, 2, 38, 5918) == (60, 4)
+    assert splits(5, 4, 10, 55301) == (10, 23)    # 25 fit; 24 meet, 23 of 19 tiles are enough
+    assert splits(6, 4, 10, 34074) == (12, 20)    # 21 fit; 20 meet
+    assert splits(8, 4, 12, 20000)[1] == 16
+    # low-rank caches per adapter on pages: the split-KV kernel, two workgroups per unit
+    assert splits(16, 2, 6, 1304, r=32, paged=True, side="own") == (48, 6)
+    assert splits(8, 8, 10, 2353, r=32, paged=True, side="own") == (40, 7)
+    assert splits(8, 4, 6, 30000, r=32, paged=True, side="own") == (24, 20)
