@@ -619,8 +619,14 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
     // with 63 shares, 24.2 with 21)
     want = rope && key_adapter ? kCUs * 8 : kCUs * 3;
   }
-  // (the streaming kernel reads one sequence's blocks too, with one low-rank cache for the call)
-  const bool paged_stream = c->block_size != 0 && n_seqs_eff == 1 && tune.variant != 2 && (prefill || c->l_adapter_stride == 0);
+  // The streaming kernel reads one sequence's blocks too, with one low-rank cache for the call; but not where several row groups
+  // read keys enough for two workgroups per unit of the split-KV kernel (units x keys of 2^18 and more): ratio of the times there
+  // and streaming, three row groups and more 0.59 to 1.5 (32 kv heads of 64, 39 agents on 6572 keys 35.5 / 59.7; 4 kv heads of
+  // group 7, 33 agents on 42376 64.6 / 83.9), two row groups at d = 64 0.87 to 1.05.  Streaming stays for two at d = 128 (0.93 to
+  // 1.44, 1.09 in the mean of 35), one row group (1.0 to 1.3) and fewer keys (0.92 to 1.4, 1.14 in the mean of 600).
+  const bool long_row = n_seqs_eff == 1 && !prefill && pl.mfma && work * c->max_seq_len >= int64_t{2} * kCUs * 512;
+  const bool paged_stream = c->block_size != 0 && n_seqs_eff == 1 && tune.variant != 2 && (prefill || c->l_adapter_stride == 0) &&
+                            !(long_row && (pl.row_groups > 2 || (pl.row_groups == 2 && sh->head_dim == 64)));
   int split_keys = tune.split_keys;
   RopeShares two{0, 0, 0};
   if (split_keys <= 0 && pl.mfma) {
@@ -631,9 +637,9 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
     const bool batch = n_seqs_eff > 1;
     int64_t wgs = batch ? kCUs * 4 : kCUs;
     // ... and one long sequence in a paged cache with two, where it takes the split-KV kernel, two workgroups per compute
-    // unit, as long as a share then still has 512 keys (32768 tokens x 8 kv heads: 35.7 against 38.6 us, 65536: 49.2
-    // against 53.7; at 256 keys per share the doubling loses)
-    if (!batch && !prefill && !paged_stream && c->block_size != 0 && !rope && work * c->max_seq_len >= int64_t{2} * kCUs * 512) wgs = 2 * kCUs;
+    // unit, as long as a share then still has 512 keys (on that kernel, 32768 tokens x 8 kv heads: 35.7 against 38.6 us, 65536:
+    // 49.2 against 53.7; at 256 keys per share the doubling loses)
+    if (long_row && c->block_size != 0 && !paged_stream && !rope) wgs = 2 * kCUs;
     // ... and one sequence in the rotary form at ranks up to 32 likewise.  Above rank 32 a unit holds one workgroup.  Nor
     // without a B_K: nothing is rotated then, and one workgroup per unit keeps the streaming form.
     if (!batch && rope_split && key_adapter && sh->rank <= 32) two = rope_two_per_unit(c->max_seq_len, work, pl.rows, prefill);
@@ -650,10 +656,12 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
       // of 7 heads at rank 64, 30000 keys, 22 and 20 77 / 56.)  Not where less than three quarters of the places are taken then (12 kv
       // heads, 96 agents in twelve row groups, rank 32, 13895 keys, two shares 125 and one 156; 160 units of 256 0.90 to 1.12 of 32
       // calls, 192 and more 1.0 to 1.4 of 140), nor on the split-KV kernel while it has places left, two per unit (paged, 16 kv
-      // heads, 6 agents with low-rank caches of their own at rank 32, 1304 keys, six shares 13.1, four 14.8).  In the rotary form, whose tiles take longest, a last share may stay that is no longer than what the others would grow by: 24
-      // units, 9000 keys, ten shares of seven tiles and one of one 48 us, nine of eight 53.
+      // heads, 6 agents with low-rank caches of their own at rank 32, 1304 keys, six shares 13.1, four 14.8; with one cache for the
+      // call, five shares of 96 units in place of six lose 3 %).  In the rotary form, whose tiles take longest, a last share may
+      // stay that is no longer than what the others would grow by: 24 units, 9000 keys, ten shares of seven tiles and one of one
+      // 48 us, nine of eight 53.
       const bool streams = !rope && tune.variant != 2 && (c->block_size == 0 || paged_stream);
-      if (!batch && work <= wgs && (rope || wgs > kCUs || (streams && wgs / work * work * 4 >= 3 * wgs))) {
+      if (!batch && work <= wgs && (rope || (wgs > kCUs && pl.l_block != 0) || (streams && wgs / work * work * 4 >= 3 * wgs))) {
         const int64_t shares = streams ? meeting_shares(wgs / work, sh->n_kv_heads, pl.row_groups) : wgs / work;
         const int64_t least = (c->max_seq_len + shares - 1) / shares;
         const int64_t t = (sk + tile - 1) / tile, t_least = (least + tile - 1) / tile, all = (static_cast<int64_t>(c->max_seq_len) + tile - 1) / tile;
