@@ -771,11 +771,11 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
   pl.off_lr = pl.off_o + align_up(slots * sh->head_dim * sizeof(float), 256);
   pl.off_adapter = pl.off_lr + align_up(slots * sh->rank * sizeof(float), 256);
   pl.bytes = pl.off_adapter + align_up(static_cast<size_t>(pl.rows) * sizeof(int32_t), 256);
-  // room for Qt of the whole call where the streaming form of the split-KV kernel would
-  // otherwise reload many B_K rows per workgroup (reserved whether or not the call has a B_K)
+  // room for Qt of the whole call where the streaming form of the split-KV kernel, which takes at most one workgroup per
+  // compute unit, would otherwise reload many B_K rows per workgroup (reserved whether or not the call has a B_K)
   pl.off_qt = pl.bytes;
   pl.qt_bytes = 0;
-  if (pl.mfma && !prefill && (c->block_size == 0 || paged_stream) && !rope_split && tune.variant != 2 && pl.l_block == 0)
+  if (pl.mfma && !prefill && (c->block_size == 0 || paged_stream) && work * pl.n_splits <= kCUs && !rope_split && tune.variant != 2 && pl.l_block == 0)
     pl.qt_bytes = decode_stream_qt_bytes(pl.group_pad, sh->rank, pl.row_tiles, pl.row_groups, sh->n_kv_heads);
   pl.bytes += align_up(pl.qt_bytes, 256);
   pl.bytes_without_kc = pl.bytes;

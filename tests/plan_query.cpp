@@ -17,6 +17,10 @@ extern "C" void plan_query(const lra_shape* sh, const lra_cache* c, int tokens, 
   out[10] = pl.l_block;
   out[11] = pl.workspace_optional;
   out[12] = pl.group_pad;
+  out[13] = pl.split_keys;
+  out[14] = pl.split_more;
+  out[15] = static_cast<int32_t>(pl.qt_bytes);
+  out[16] = static_cast<int32_t>(pl.bytes >> 8);
 }
 
 extern "C" int stream_grid_query(int n_kv_heads, int n_splits, int row_groups) { return lra::stream_grid_shares(n_kv_heads, n_splits, row_groups); }

@@ -15,7 +15,7 @@ from tests import test_parity_gpu as P
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 FIELDS = ("mfma", "short_prefill", "wave_rows", "wave_shares", "n_splits", "tile_group", "batch_wgs", "batch_tiles", "row_tiles",
-          "row_groups", "l_block", "workspace_optional", "group_pad")
+          "row_groups", "l_block", "workspace_optional", "group_pad", "split_keys", "split_more", "qt_bytes", "pages")
 
 
 @pytest.fixture(scope="module")

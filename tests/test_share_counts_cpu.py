@@ -56,3 +56,13 @@ def test_long_paged_sequences_of_several_row_groups(planner):  # noqa: F811
     assert workgroups(8, 4, 128, 17, 10922)[1] <= 256 < workgroups(8, 4, 128, 17, 10923)[1]  # 24 units
     assert workgroups(32, 1, 64, 14, 13256) == (2, 512) and workgroups(32, 1, 128, 14, 13256) == (2, 256)
     assert workgroups(8, 4, 128, 8, 65536) == (1, 256)
+
+
+def test_no_room_for_a_pre_pass_that_does_not_run(planner):  # noqa: F811
+    """Room for Qt only where the streaming kernel can run: without it a decode of many agents stays within the 64 MiB of the
+    library's own workspace."""
+    for paged in (False, True):
+        pl = _plan(planner, 256, 32, 128, 64, [9300], agents=289, paged=paged)
+        assert pl["row_groups"] * 32 > 256 and pl["qt_bytes"] == 0 and pl["pages"] * 256 <= 64 << 20
+        pl = _plan(planner, 32, 8, 128, 64, [9300], agents=8, paged=paged)
+        assert pl["row_groups"] * 8 * pl["n_splits"] <= 256 and pl["qt_bytes"] > 0
