@@ -826,23 +826,23 @@ __global__ __launch_bounds__(512, 2) void decode_stream_paged_kernel(Params p) {
 // layout the streaming kernel keeps in LDS, [row group][kv head][row tile][k-step][lane] 16 bytes,
 // elements e -> rho = 32ks' + 16(e/4) + 4lg + e%4.
 template <int D, int RP>
-__global__ __launch_bounds__(256) void decode_qt_prepass_kernel(Params p, int row_tiles) {
+__global__ __launch_bounds__(256) void decode_qt_prepass_kernel(Params p) {
   constexpr int KS = D / 32, RKS = RP / 32, ROW_BYTES = D * 2;
   const int lane = threadIdx.x & 63;
   const int cb = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // rho block of this wave
   const int ln = lane & 15, lg = lane >> 4;
-  // (the parameter block in one round trip; row_tiles is 1 or 2: no division)
+  // (the parameter block in one round trip)
   asm volatile("" ::"s"(p.q), "s"(p.b_k), "s"(p.query_adapter), "s"(p.qt_ws));
   asm volatile("" ::"s"(p.n_q_heads), "s"(p.n_kv_heads), "s"(p.group), "s"(p.rank), "s"(p.group_pad), "s"(p.n_queries),
-               "s"(p.n_adapters), "s"(row_tiles));
+               "s"(p.n_adapters));
   const int h = blockIdx.x, si = blockIdx.z;
   const int by = blockIdx.y;
-  const int rg = row_tiles == 2 ? by >> 1 : by, rt = row_tiles == 2 ? by & 1 : 0;
+  const int rg = by >> 1, rt = by & 1;  // (calls of two row tiles only)
   const int n_q = p.n_queries;
   const int GP = p.group_pad, G = p.group, r = p.rank;
   const int gps = __builtin_ctz(GP);
   const int ncb = (r + 15) >> 4;
-  const int tile_row0 = (rg * row_tiles + rt) * 16;
+  const int tile_row0 = (rg * 2 + rt) * 16;
   const int slot = (tile_row0 >> gps) + si;
   if (si >= (16 >> gps) || cb >= ncb) return;
   int a = -1;
@@ -868,7 +868,7 @@ __global__ __launch_bounds__(256) void decode_qt_prepass_kernel(Params p, int ro
   for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv[ks], qv[ks], acc, 0, 0, 0);
   if ((ln >> gps) == si) {
     unsigned char* dst = static_cast<unsigned char*>(p.qt_ws) +
-                         ((((static_cast<size_t>(rg) * p.n_kv_heads + h) * row_tiles + rt) * RKS + (cb >> 1)) * 64 + lane) * 16;
+                         ((((static_cast<size_t>(rg) * p.n_kv_heads + h) * 2 + rt) * RKS + (cb >> 1)) * 64 + lane) * 16;
     const uint2 pk = make_uint2(pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3]));
     if (!(cb & 1) && cb + 1 >= ncb)  // the odd block next to it lies beyond the rank: zeros
       *reinterpret_cast<uint4*>(dst) = make_uint4(pk.x, pk.y, 0u, 0u);
@@ -878,9 +878,9 @@ __global__ __launch_bounds__(256) void decode_qt_prepass_kernel(Params p, int ro
 }
 
 template <int D, int RP>
-static void launch_prepass2(const Params& p, int row_tiles, hipStream_t s) {
-  const dim3 grid(p.n_kv_heads, p.row_groups * row_tiles, 16 / p.group_pad), block(256);
-  hipLaunchKernelGGL((decode_qt_prepass_kernel<D, RP>), grid, block, 0, s, p, row_tiles);
+static void launch_prepass2(const Params& p, hipStream_t s) {
+  const dim3 grid(p.n_kv_heads, p.row_groups * 2, 16 / p.group_pad), block(256);
+  hipLaunchKernelGGL((decode_qt_prepass_kernel<D, RP>), grid, block, 0, s, p);
 }
 
 // Whether a decode launch can take decode_stream_kernel: one sequence (in a paged cache with one low-rank cache for all
@@ -938,8 +938,8 @@ hipError_t launch_decode_stream(const Params& p, int row_tiles, bool main_kernel
   const dim3 grid = p.share_major ? dim3(8 * p.n_kv_heads, (p.n_splits + 7) / 8, p.row_groups)
                                   : dim3(p.n_kv_heads, shares, p.row_groups);  // (see the index layouts in the kernel)
   if (p.qt_ws != nullptr && !main_kernel_only) {
-    if (p.head_dim == 128) { if (p.rank > 32) launch_prepass2<128, 64>(p, row_tiles, s); else launch_prepass2<128, 32>(p, row_tiles, s); }
-    else { if (p.rank > 32) launch_prepass2<64, 64>(p, row_tiles, s); else launch_prepass2<64, 32>(p, row_tiles, s); }
+    if (p.head_dim == 128) { if (p.rank > 32) launch_prepass2<128, 64>(p, s); else launch_prepass2<128, 32>(p, s); }
+    else { if (p.rank > 32) launch_prepass2<64, 64>(p, s); else launch_prepass2<64, 32>(p, s); }
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
   }
   // columns of the L tile: the rank, or with per-adapter low-rank caches one block per agent slot of a row tile

@@ -66,3 +66,12 @@ def test_no_room_for_a_pre_pass_that_does_not_run(planner):  # noqa: F811
         assert pl["row_groups"] * 32 > 256 and pl["qt_bytes"] == 0 and pl["pages"] * 256 <= 64 << 20
         pl = _plan(planner, 32, 8, 128, 64, [9300], agents=8, paged=paged)
         assert pl["row_groups"] * 8 * pl["n_splits"] <= 256 and pl["qt_bytes"] > 0
+
+
+def test_the_pre_pass_runs_for_two_row_tiles(planner):  # noqa: F811
+    for paged in (False, True):
+        for agents in (1, 2, 3, 4):
+            pl = _plan(planner, 32, 8, 128, 64, [3000], agents=agents, paged=paged)
+            assert pl["row_tiles"] == 1 and pl["qt_bytes"] == 0
+        assert _plan(planner, 32, 8, 128, 64, [3000], agents=5, paged=paged)["qt_bytes"] > 0
+        assert _plan(planner, 28, 4, 128, 64, [3000], agents=2, paged=paged)["qt_bytes"] == 0

@@ -22,7 +22,9 @@ CASES = [
     (4113, 4, 8, 8, 64, 8, False, 900),      # group of one; two thirds of the shares find nothing
     (9001, 2, 32, 8, 128, 64, True, 1),      # more than two tiles per wave, hand-over in a stage
     (8193, 8, 32, 8, 128, 64, True, 0),      # ... with Qt from the pre-pass
-    (5003, 3, 16, 1, 64, 48, True, 0),       # group of 16: three row groups
+    (1100, 4, 32, 8, 128, 64, True, 0),      # one row tile of four slots: sixteen blocks of B_K in the prologue
+    (500, 3, 16, 4, 64, 40, True, 2),        # ... one slot empty, the last block half beyond the rank
+    (5003, 3, 16, 1, 64, 48, True, 0),       # group of 16: two row groups, the second with a row tile of no agent
 ]
 
 
