@@ -304,14 +304,20 @@ static bool short_prefill_walks_tiles(const lra_shape* sh, const lra_cache* c, i
 // 59.9; 8 agents, two row groups, on 5000: 16 21.3, 24 18.6; on 33000: 16 74.4, 32 58.5; rank 32, 2 agents on 9000: 18.1,
 // 40 16.9).  Not beyond 64 shares, which one merge kernel takes (4 kv heads on 60000: 64 shares 29.2, 128 35.0), and 128 keys
 // only for up to 2048 (row, share) states; prefills of a few tokens from 384 keys on.
+// Where the units do not divide 256 shares of one size in all 512 places can be shorter than half of that load, and are taken then
+// (24 kv heads, 11 agents of 1 head, rank 32, 144 units, 6250 keys: two shares 99.7, three 75.2; 96 units, 8 agents on 40888, four
+// 304 and five 256).  With several row groups the counts are those whose workgroups meet on one XCD, a sixteenth less at most (5 kv
+// heads, 8 agents in two row groups on 35089, 25 shares for 24, 58.5 / 47.1 in all).
 struct RopeShares {
   int keys, n, more;  // keys of the largest, shares, how many are of that size where the rest hold 128 less (0: all)
 };
-static RopeShares rope_two_per_unit(int max_seq_len, int64_t work, int64_t rows, bool prefill) {
-  const int64_t tiles = (static_cast<int64_t>(max_seq_len) + 127) / 128, units = work > 0 ? kCUs / work : 0;
-  const int64_t load = units > 0 ? (tiles + units - 1) / units : 0, first = (load + 1) / 2;
-  const bool odd = (load & 1) != 0;
+static RopeShares rope_two_per_unit(int max_seq_len, int n_kv_heads, int row_groups, int64_t rows, bool prefill) {
+  const int64_t tiles = (static_cast<int64_t>(max_seq_len) + 127) / 128, work = static_cast<int64_t>(n_kv_heads) * row_groups;
+  const int64_t units = meeting_shares(kCUs / work, n_kv_heads, row_groups), load = units > 0 ? (tiles + units - 1) / units : 0;
   if (load < 2) return {0, 0, 0};
+  const int64_t places = meeting_shares(2 * kCUs / work, n_kv_heads, row_groups), level = (tiles + places - 1) / places;
+  const bool alike = 2 * level < load, odd = !alike && (load & 1) != 0;
+  const int64_t first = alike ? level : (load + 1) / 2;
   const int64_t n = odd ? units + (tiles - units * first + first - 2) / (first - 1) : (tiles + first - 1) / first;
   if (n > 64 || (prefill ? first < 3 : first < 2 && rows * n > 2048)) return {0, 0, 0};
   return {static_cast<int>(first * 128), static_cast<int>(n), odd ? static_cast<int>(units) : 0};
@@ -644,7 +650,7 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
     if (long_row && c->block_size != 0 && !paged_stream && !rope) wgs = 2 * kCUs;
     // ... and one sequence in the rotary form at ranks up to 32 likewise.  Above rank 32 a unit holds one workgroup.  Nor
     // without a B_K: nothing is rotated then, and one workgroup per unit keeps the streaming form.
-    if (!batch && rope_split && key_adapter && sh->rank <= 32) two = rope_two_per_unit(c->max_seq_len, work, pl.rows, prefill);
+    if (!batch && rope_split && key_adapter && sh->rank <= 32) two = rope_two_per_unit(c->max_seq_len, sh->n_kv_heads, pl.row_groups, pl.rows, prefill);
     if (two.n > 0) {
       split_keys = two.keys < c->max_seq_len ? two.keys : c->max_seq_len;
     } else if (work >= 2 * wgs) {

@@ -75,3 +75,19 @@ def test_the_pre_pass_runs_for_two_row_tiles(planner):  # noqa: F811
             assert pl["row_tiles"] == 1 and pl["qt_bytes"] == 0
         assert _plan(planner, 32, 8, 128, 64, [3000], agents=5, paged=paged)["qt_bytes"] > 0
         assert _plan(planner, 28, 4, 128, 64, [3000], agents=2, paged=paged)["qt_bytes"] == 0
+
+
+def test_two_workgroups_per_unit_in_the_rotary_form(planner):  # noqa: F811
+    """One size for all shares where the units do not divide the chip and that makes the longest load shorter; else the first ones a
+    tile longer; with several row groups counts that meet on one XCD."""
+    def shares(hkv, group, agents, n, r):
+        pl = _plan(planner, hkv * group, hkv, 128, r, [n], agents=agents, paged=False, side="rotary")
+        return hkv * pl["row_groups"], pl["n_splits"], pl["split_keys"], pl["split_more"]
+
+    assert shares(24, 1, 11, 6250, 32) == (144, 3, 17 * 128, 0)
+    assert shares(24, 1, 8, 40888, 32) == (96, 5, 64 * 128, 0)
+    assert shares(32, 1, 5, 8187, 24) == (96, 5, 13 * 128, 0)
+    assert shares(8, 4, 4, 9000, 16) == (8, 39, 2 * 128, 32)      # 71 tiles on 32 units: loads of three
+    assert shares(5, 4, 4, 41459, 32) == (10, 47, 7 * 128, 0)     # 25 units fit, 24 meet: loads of 14
+    assert shares(5, 4, 8, 35089, 8)[:2] == (10, 46)
+    assert shares(2, 8, 11, 38848, 16)[:2] == (12, 38)
