@@ -132,23 +132,6 @@ __device__ __forceinline__ void decode_stream(const Params& p) {
   const int32_t len_t = CONST_I32(p.seq_lens)[t];
   const int j0 = split * p.split_keys;
   const int kpw = p.split_keys / NW;  // keys per wave, a multiple of 32
-  // Paged cache: the physical blocks of a tile, two of 16 keys.  Those of this wave's first two tiles (a prologue wave: of the
-  // streaming wave it serves) are asked for with the lengths, at clamped places of the sequence's row of the table (what a
-  // place behind the sequence's end names is never read), later ones a tile ahead of their requests.
-  const const_i32_ptr bt = CONST_I32(p.block_table) + static_cast<int64_t>(t) * p.max_blocks_per_seq;
-  struct TileBlocks {
-    int b0, b1;
-  };
-  auto blocks_of = [&](int j) __attribute__((always_inline)) {
-    const int last = p.max_blocks_per_seq - 1;
-    return TileBlocks{bt[min(j >> 4, last)], bt[min((j >> 4) + 1, last)]};
-  };
-  TileBlocks first = {0, 0}, second = {0, 0};
-  if constexpr (PAGED) {
-    const int j = j0 + (wave & (NW - 1)) * kpw;
-    first = blocks_of(j);
-    second = blocks_of(j + 32);
-  }
   const int n_q = CAUSAL ? p.n_new : p.n_queries;
   const int GP = p.group_pad, G = p.group, r = p.rank;
   const int gps = __builtin_ctz(GP);                           // GP is 4, 8 or 16
@@ -203,6 +186,23 @@ __device__ __forceinline__ void decode_stream(const Params& p) {
     return;
   }
   LRA_STAMP(1);
+  // Paged cache: the physical blocks of a tile, two of 16 keys.  Those of this wave's first two tiles (a prologue wave: of the
+  // streaming wave it serves) are asked for as soon as the length is there, later ones a tile ahead of their requests; places of
+  // the table behind the sequence's last block are not read.
+  const const_i32_ptr bt = CONST_I32(p.block_table) + static_cast<int64_t>(t) * p.max_blocks_per_seq;
+  struct TileBlocks {
+    int b0, b1;
+  };
+  auto blocks_of = [&](int j) __attribute__((always_inline)) {
+    const int last = (n_t - 1) >> 4;
+    return TileBlocks{bt[min(j >> 4, last)], bt[min((j >> 4) + 1, last)]};
+  };
+  TileBlocks first = {0, 0}, second = {0, 0};
+  if constexpr (PAGED) {
+    const int j = j0 + (wave & (NW - 1)) * kpw;
+    first = blocks_of(j);
+    second = blocks_of(j + 32);
+  }
 
   // ===================== tile requests (of streaming wave sw) =====================
   const int j1 = min(j0 + p.split_keys, n_t);
