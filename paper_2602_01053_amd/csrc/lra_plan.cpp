@@ -667,14 +667,16 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
       // heads, 6 agents with low-rank caches of their own at rank 32, 1304 keys, six shares 13.1, four 14.8; with one cache for the
       // call, five shares of 96 units in place of six lose 3 %).  In the rotary form, whose tiles take longest, a last share may
       // stay that is no longer than what the others would grow by: 24 units, 9000 keys, ten shares of seven tiles and one of one
-      // 48 us, nine of eight 53.
-      const bool streams = !rope && tune.variant != 2 && (c->block_size == 0 || paged_stream);
-      if (!batch && work <= wgs && (rope || (wgs > kCUs && pl.l_block != 0) || (streams && wgs / work * work * 4 >= 3 * wgs))) {
+      // 48 us, nine of eight 53.  (Without a B_K
+      // nothing is rotated, and the call streams where one round fills the chip.)
+      const bool full = wgs / work * work * 4 >= 3 * wgs, rotates = rope && (key_adapter || !full);
+      const bool streams = !rotates && tune.variant != 2 && (c->block_size == 0 || paged_stream);
+      if (!batch && work <= wgs && (rope || (wgs > kCUs && pl.l_block != 0) || (streams && full))) {
         const int64_t shares = streams ? meeting_shares(wgs / work, sh->n_kv_heads, pl.row_groups) : wgs / work;
         const int64_t least = (c->max_seq_len + shares - 1) / shares;
         const int64_t t = (sk + tile - 1) / tile, t_least = (least + tile - 1) / tile, all = (static_cast<int64_t>(c->max_seq_len) + tile - 1) / tile;
         const int64_t last = all - (all - 1) / t * t;
-        if ((all + t - 1) / t > shares && (!rope || t + last > t_least)) sk = sk > least ? sk : least;
+        if ((all + t - 1) / t > shares && (!rotates || t + last > t_least)) sk = sk > least ? sk : least;
       }
       split_keys = sk > c->max_seq_len ? c->max_seq_len : static_cast<int>(sk);
     }

@@ -32,7 +32,7 @@ def planner(tmp_path_factory):
 
 def _plan(planner, hq, hkv, d, r, lens, *, longest=None, agents=0, n_new=0, paged, side="bk", host=None, variant=0):
     n = longest or max(lens)
-    shape = LraShape(hq, hkv, d, r, 0, 0.0, 500000.0 if side == "rotary" else 0.0)
+    shape = LraShape(hq, hkv, d, r, 0, 0.0, 500000.0 if side.startswith("rotary") else 0.0)
     cache = LraCache(n_seqs=len(lens), max_seq_len=n, l_row_stride=r)
     if paged:
         blocks = sum((x + 15) // 16 for x in lens) if longest is None else (n + 15) // 16
@@ -47,7 +47,7 @@ def _plan(planner, hq, hkv, d, r, lens, *, longest=None, agents=0, n_new=0, page
         cache.seq_lens_host = ctypes.cast(mirror, ctypes.c_void_p)
     out = (ctypes.c_int32 * len(FIELDS))()
     planner.plan_query(ctypes.byref(shape), ctypes.byref(cache), n_new or agents * len(lens), max(agents, 1), int(n_new > 0),
-                       int(side not in ("none", "own_none")), ctypes.byref(LraTuning(kernel_variant=variant)), out)
+                       int(side not in ("none", "own_none", "rotary_none")), ctypes.byref(LraTuning(kernel_variant=variant)), out)
     return dict(zip(FIELDS, out))
 
 

@@ -91,3 +91,12 @@ def test_two_workgroups_per_unit_in_the_rotary_form(planner):  # noqa: F811
     assert shares(5, 4, 4, 41459, 32) == (10, 47, 7 * 128, 0)     # 25 units fit, 24 meet: loads of 14
     assert shares(5, 4, 8, 35089, 8)[:2] == (10, 46)
     assert shares(2, 8, 11, 38848, 16)[:2] == (12, 38)
+
+
+def test_rotary_shapes_without_a_key_adapter_keep_one_round(planner):  # noqa: F811
+    """Nothing is rotated without a B_K: the call runs on the streaming kernel, which has no second round."""
+    for paged in (False, True):
+        for hkv, agents, n, r in ((24, 1, 9000, 16), (12, 8, 9000, 16), (24, 2, 9000, 64), (5, 4, 20000, 48)):
+            pl = _plan(planner, 4 * hkv, hkv, 128, r, [n], agents=agents, paged=paged, side="rotary_none")
+            units = hkv * pl["row_groups"]
+            assert units * 2 <= 256 and 192 <= units * pl["n_splits"] <= 256, (hkv, agents, n, r, pl["n_splits"])
