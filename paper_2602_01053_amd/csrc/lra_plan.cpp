@@ -630,11 +630,15 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
   // The streaming kernel reads one sequence's blocks too, with one low-rank cache for the call; but not where several row groups
   // read keys enough for two workgroups per unit of the split-KV kernel (units x keys of 2^18 and more): ratio of the times there
   // and streaming, three row groups and more 0.59 to 1.5 (32 kv heads of 64, 39 agents on 6572 keys 35.5 / 59.7; 4 kv heads of
-  // group 7, 33 agents on 42376 64.6 / 83.9), two row groups at d = 64 0.87 to 1.05.  Streaming stays for two at d = 128 (0.93 to
-  // 1.44, 1.09 in the mean of 35), one row group (1.0 to 1.3) and fewer keys (0.92 to 1.4, 1.14 in the mean of 600).
-  const bool long_row = n_seqs_eff == 1 && !prefill && pl.mfma && work * c->max_seq_len >= int64_t{2} * kCUs * 512;
+  // group 7, 33 agents on 42376 64.6 / 83.9), two row groups at d = 64 0.87 to 1.05.  Two at d = 128 stream below 2^19 (split-KV /
+  // streaming 0.95 to 1.3), above rank 32 (0.93 to 1.3) and from 5 x 2^18 on, where the two are level; between, with shares that
+  // meet and fit, split-KV takes 0.89 to 0.98 (16 kv heads, 11 agents on 23854 44.6 / 48.4; 24, 9 on 17550 50.6 / 56.9).  Streaming
+  // stays for one row group (1.0 to 1.3) and fewer keys (0.92 to 1.4, 1.14 in the mean of 600).
+  const int64_t reads = n_seqs_eff == 1 && !prefill && pl.mfma ? work * c->max_seq_len : 0;
+  const bool long_row = reads >= int64_t{2} * kCUs * 512;
+  const bool long_pair = pl.row_groups == 2 && sh->head_dim == 128 && sh->rank <= 32 && reads >= int64_t{1} << 19 && reads < int64_t{5} << 18;
   const bool paged_stream = c->block_size != 0 && n_seqs_eff == 1 && tune.variant != 2 && (prefill || c->l_adapter_stride == 0) &&
-                            !(long_row && (pl.row_groups > 2 || (pl.row_groups == 2 && sh->head_dim == 64)));
+                            !(long_row && (pl.row_groups > 2 || (pl.row_groups == 2 && sh->head_dim == 64) || long_pair));
   int split_keys = tune.split_keys;
   RopeShares two{0, 0, 0};
   if (split_keys <= 0 && pl.mfma) {
@@ -671,8 +675,8 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
       // nothing is rotated, and the call streams where one round fills the chip.)
       const bool full = wgs / work * work * 4 >= 3 * wgs, rotates = rope && (key_adapter || !full);
       const bool streams = !rotates && tune.variant != 2 && (c->block_size == 0 || paged_stream);
-      if (!batch && work <= wgs && (rope || (wgs > kCUs && pl.l_block != 0) || (streams && full))) {
-        const int64_t shares = streams ? meeting_shares(wgs / work, sh->n_kv_heads, pl.row_groups) : wgs / work;
+      if (!batch && work <= wgs && (rope || (wgs > kCUs && (pl.l_block != 0 || long_pair)) || (streams && full))) {
+        const int64_t shares = streams || (long_pair && pl.l_block == 0 && !rope) ? meeting_shares(wgs / work, sh->n_kv_heads, pl.row_groups) : wgs / work;
         const int64_t least = (c->max_seq_len + shares - 1) / shares;
         const int64_t t = (sk + tile - 1) / tile, t_least = (least + tile - 1) / tile, all = (static_cast<int64_t>(c->max_seq_len) + tile - 1) / tile;
         const int64_t last = all - (all - 1) / t * t;

@@ -20,6 +20,9 @@ def test_one_round(planner, paged, side):  # noqa: F811
                         if paged and side == "bk" and pl["row_groups"] > 2 and units * n >= 512 * 512:
                             assert units * (pl["n_splits"] - 1) <= 512 or pl["n_splits"] == 1
                             continue
+                        # ... or two, between 2^19 and 5 x 2^18, at ranks up to 32
+                        if paged and side == "bk" and pl["row_groups"] == 2 and r <= 32 and 1 << 19 <= units * n < 5 << 18:
+                            room = 512
                         if pl["mfma"] and units <= room:
                             short = 1 if side == "rotary" else 0  # (a last, short share may begin a second one)
                             assert units * (pl["n_splits"] - short) <= room, (hkv, group, agents, r, n, units, pl["n_splits"])
@@ -54,7 +57,11 @@ def test_long_paged_sequences_of_several_row_groups(planner):  # noqa: F811
     assert workgroups(32, 1, 64, 39, 6572) == (5, 640)
     assert workgroups(4, 7, 128, 33, 42376)[1] > 460
     assert workgroups(8, 4, 128, 17, 10922)[1] <= 256 < workgroups(8, 4, 128, 17, 10923)[1]  # 24 units
-    assert workgroups(32, 1, 64, 14, 13256) == (2, 512) and workgroups(32, 1, 128, 14, 13256) == (2, 256)
+    assert workgroups(32, 1, 64, 14, 13256) == (2, 512) and workgroups(32, 1, 128, 14, 4700) == (2, 256)
+    # two row groups at d = 128: between 2^19 and 5 x 2^18, shares that meet on an XCD
+    assert workgroups(32, 1, 128, 14, 8191) == (2, 256) and workgroups(32, 1, 128, 14, 8192) == (2, 512)
+    assert workgroups(32, 1, 128, 14, 20479) == (2, 512) and workgroups(32, 1, 128, 14, 20480) == (2, 256)
+    assert workgroups(12, 2, 128, 10, 40000) == (2, 480) and workgroups(5, 4, 128, 9, 55000)[1] <= 480
     assert workgroups(8, 4, 128, 8, 65536) == (1, 256)
 
 
