@@ -40,6 +40,9 @@ __device__ __forceinline__ void decode_rope_share(const Params& p, const int h, 
   constexpr int RP = RPE;                                                  // ranks of an L row in LDS
   constexpr int NS = RPE == 16 ? 4 : (RPE == 32 ? 2 : kRopeSlots64);        // agent slots with operands in registers
   constexpr int NSL = CAUSAL ? 1 : NS;                                     // (causal: one adapter for all rows)
+  // (causal: no slots to choose between, and registers to spare for Q; 24 kv heads of group 1, 23 tokens after 13163, rank 8, 103 us
+  // with Q read from LDS each step, 98.7 so; 300 calls 1.01 in the mean)
+  constexpr bool HOLD_Q = CAUSAL;
   constexpr int EK = RPE / 16;     // 16-wide k-steps of the E product
   constexpr int KS = D / 32;       // k-steps of K_base Q^T
   constexpr int DB = D / 16;       // 16-wide output blocks over d; 16-wide k-steps of rot(E) Q
@@ -334,6 +337,11 @@ __device__ __forceinline__ void decode_rope_share(const Params& p, const int h, 
 #pragma unroll
   for (int b = 0; b < RB; ++b) lt_rd[b] = ka * (2 * RP) + (((2 * b + ((ln & 3) >> 1)) ^ swz_l(ka)) << 4) + (ln & 1) * 8;
   const int q_mine = (ln + 16 * g2) * QOP_STRIDE;
+  bf16x8 q_held[HOLD_Q ? DB : 1];
+  if constexpr (HOLD_Q) {
+#pragma unroll
+    for (int kk = 0; kk < DB; ++kk) q_held[kk] = as_bf16x8(lds_read16(q_op + q_mine + kk * 16));
+  }
   f32x4 o_acc[DB], lr_acc[RB];
   float m_run = -INFINITY, l_run = 0.f;  // m_run in base-2 units of the scaled score
   [[maybe_unused]] float m_top = -INFINITY;
@@ -403,7 +411,7 @@ __device__ __forceinline__ void decode_rope_share(const Params& p, const int h, 
 #pragma unroll
       for (int si = 0; si < NSL; ++si) {
         if (si > 0 && si >= n_live) continue;
-        const int q_at = CAUSAL || ((ln >> gps) == si) ? q_mine : 32 * QOP_STRIDE;
+        [[maybe_unused]] const int q_at = (ln >> gps) == si ? q_mine : 32 * QOP_STRIDE;
         pf_f32x16 e_lo, e_hi;
 #pragma unroll
         for (int i = 0; i < 16; ++i) e_lo[i] = e_hi[i] = 0.f;
@@ -422,8 +430,14 @@ __device__ __forceinline__ void decode_rope_share(const Params& p, const int h, 
             lo[x] = pack_bf16x2(e_lo[i] * cs[i] - e_hi[i] * sn[i], e_lo[i + 1] * cs[i + 1] - e_hi[i + 1] * sn[i + 1]);
             hi[x] = pack_bf16x2(e_hi[i] * cs[i] + e_lo[i] * sn[i], e_hi[i + 1] * cs[i + 1] + e_lo[i + 1] * sn[i + 1]);
           }
-          const bf16x8 q_lo = as_bf16x8(lds_read16(q_op + q_at + (pb * 4 + q) * 16));
-          const bf16x8 q_hi = as_bf16x8(lds_read16(q_op + q_at + (pb * 4 + 2 + q) * 16));
+          bf16x8 q_lo, q_hi;
+          if constexpr (HOLD_Q) {
+            q_lo = q_held[pb * 4 + q];
+            q_hi = q_held[pb * 4 + 2 + q];
+          } else {
+            q_lo = as_bf16x8(lds_read16(q_op + q_at + (pb * 4 + q) * 16));
+            q_hi = as_bf16x8(lds_read16(q_op + q_at + (pb * 4 + 2 + q) * 16));
+          }
           s_rot = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(make_uint4(lo[0], lo[1], lo[2], lo[3])), q_lo, s_rot, 0, 0, 0);
           s_rot = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(make_uint4(hi[0], hi[1], hi[2], hi[3])), q_hi, s_rot, 0, 0, 0);
         }
