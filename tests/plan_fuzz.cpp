@@ -31,10 +31,18 @@ static int64_t pick(std::initializer_list<int64_t> v) { return *(v.begin() + rnd
     }                                                                                   \
   } while (0)
 
+// Every key is in a share and no share is empty; those behind the first split_more hold 128 keys less.
+static bool shares_cover(const Plan& pl, int64_t keys) {
+  if (pl.split_more < 0 || pl.split_more >= pl.n_splits || (pl.split_more > 0 && pl.split_keys < 256)) return false;
+  const int64_t large = pl.split_more > 0 ? pl.split_more : pl.n_splits, last = pl.split_keys - (pl.split_more > 0 ? 128 : 0);
+  const int64_t all = large * pl.split_keys + (pl.n_splits - large) * last;
+  return all >= keys && all - last < keys;
+}
+
 int main(int argc, char** argv) {
   const int cases = argc > 1 ? std::atoi(argv[1]) : 200000;
   static char dummy[64];
-  int accepted = 0;
+  int accepted = 0, uneven = 0;
   for (int it = 0; it < cases; ++it) {
     // every field: usually from the values the library supports, now and then a bad one
     auto pv = [&](std::initializer_list<int64_t> good, std::initializer_list<int64_t> bad) { return rnd() % 12 ? pick(good) : pick(bad); };
@@ -84,7 +92,8 @@ int main(int argc, char** argv) {
       const Plan pl = make_plan(&sh, &c, static_cast<int>(tokens), static_cast<int>(mq), prefill != 0, tune);
       CHECK(pl.rows == tokens * sh.n_q_heads);
       CHECK(pl.n_splits >= 1 && pl.split_keys >= 1);
-      CHECK(static_cast<int64_t>(pl.n_splits) * pl.split_keys >= c.max_seq_len || (prefill && pl.mfma && !pl.short_prefill));
+      CHECK(pl.split_more == 0 || !prefill || pl.short_prefill);
+      CHECK((prefill && pl.mfma && !pl.short_prefill) || shares_cover(pl, c.max_seq_len));
       CHECK(pl.off_ml % 256 == 0 && pl.off_o % 256 == 0 && pl.off_lr % 256 == 0 && pl.off_adapter % 256 == 0 && pl.off_qt % 256 == 0);
       CHECK(pl.bytes % 256 == 0);
       CHECK(pl.bytes == pl.bytes_without_kc + pl.kc_bytes && pl.off_kc % 256 == 0 && pl.kc_bytes % 256 == 0);
@@ -201,6 +210,8 @@ int main(int argc, char** argv) {
     c.kv_head_stride = sh.head_dim;
     const int agents = static_cast<int>(pick({1, 2, 4, 8, 16}));
     const Plan two = make_plan(&sh, &c, agents, agents, false, Tuning{}), one = make_plan(&sh, &c, agents, agents, false, Tuning{}, false);
+    CHECK(!two.mfma || shares_cover(two, c.max_seq_len));
+    uneven += two.split_more > 0;
     // (with a B_K one workgroup per unit may leave a short last share, the first of a second round, which without one it may not)
     if (two.split_keys == one.split_keys || (two.n_splits - 1) * sh.n_kv_heads * two.row_groups <= 256) continue;
     CHECK(sh.rank <= 32 && two.split_keys < one.split_keys);
@@ -224,6 +235,8 @@ int main(int argc, char** argv) {
     c.kv_head_stride = sh.head_dim;
     const int n_new = static_cast<int>(pick({1, 4, 8, 16, 31, 32}));
     const Plan two = make_plan(&sh, &c, n_new, 1, true, Tuning{}), one = make_plan(&sh, &c, n_new, 1, true, Tuning{}, false);
+    CHECK((two.mfma && !two.short_prefill) || shares_cover(two, c.max_seq_len));
+    uneven += two.split_more > 0;
     // (with a B_K one workgroup per unit may leave a short last share, the first of a second round, which without one it may not)
     if (two.split_keys == one.split_keys || (two.n_splits - 1) * sh.n_kv_heads * two.row_groups <= 256) continue;
     CHECK(two.short_prefill && two.split_keys >= 384 && two.n_splits <= 64);
@@ -464,6 +477,10 @@ int main(int argc, char** argv) {
   for (int it = 0; it < static_cast<int>(sizeof(quarter_cases) / sizeof(quarter_cases[0])); ++it) {
     const auto& t = quarter_cases[it];
     CHECK(append_quarter_tiles(t.n_new, t.hkv, t.d, t.r, t.dm, resolve_tuning(nullptr)) == t.quarter);
+  }
+  if (uneven < cases / 100) {
+    std::fprintf(stderr, "plan_fuzz: %d plans with shares of two sizes\n", uneven);
+    return 1;
   }
   std::printf("plan_fuzz: %d cases, %d accepted by the argument checks, all plans consistent\n", cases, accepted);
   return accepted > cases / 10 ? 0 : 2;

@@ -32,5 +32,6 @@ extern "C" int interleave_query(int n_kv_heads, int n_splits, int row_groups, in
 extern "C" int append_query(int n_new, int n_kv_heads, int head_dim, int rank, int d_model, const lra_tuning* tuning) {
   const lra::Tuning t = lra::resolve_tuning(tuning);
   if (lra::append_quarter_tiles(n_new, n_kv_heads, head_dim, rank, d_model, t)) return -1;
-  return lra::plan_append_split(n_new, n_kv_heads, head_dim, rank, d_model, t).k_splits;
+  const int parts = lra::plan_append_split(n_new, n_kv_heads, head_dim, rank, d_model, t).k_splits;
+  return parts > 1 && lra::append_streams(n_new, n_kv_heads, head_dim, d_model, t) ? -2 : parts;
 }

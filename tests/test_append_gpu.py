@@ -42,17 +42,21 @@ CASES = [
 SMALL = [
     (1, 1, 64, 1, 64, 8, 10000.0),
     (4097, 1, 4096, 8, 128, 16, 500000.0),     # a decode step at the Llama-3-8B shape
-    (9, 2, 192, 2, 64, 8, 10000.0),            # matrix-vector kernel, d_model/8 = 24 pieces: lanes without one
-    (31, 3, 1088, 2, 128, 24, 500000.0),       # three tokens on the four-token instantiation; 136 pieces: a ragged second round
+    (9, 2, 192, 2, 64, 8, 10000.0),
+    (9, 1, 192, 2, 64, 8, 10000.0),            # matrix-vector kernel, d_model/8 = 24 pieces: lanes without one
+    (19, 1, 1088, 2, 128, 24, 500000.0),       # ... 136 pieces: a third piece on some lanes
+    (300, 1, 4160, 3, 128, 16, 10000.0),       # ... 520 pieces: a second round of eight per lane, of one
+    (20, 1, 128, 2, 64, 8, 0.0),               # ... unrotated keys
+    (31, 3, 1088, 2, 128, 24, 500000.0),
     (40000, 4, 4096, 8, 128, 16, 500000.0),
-    (50, 7, 320, 2, 64, 24, 10000.0),          # d_model/32 = 10 steps over 8 waves; rank 24: a partly filled L group
+    (50, 7, 320, 2, 64, 24, 10000.0),          # five pieces of d_model over 8 waves
     (100, 16, 512, 2, 128, 16, 500000.0),
     (100, 17, 512, 2, 128, 40, 500000.0),
     (65000, 33, 1024, 4, 128, 16, 500000.0),
     (64, 64, 768, 3, 64, 64, 10000.0),
     (300, 150, 512, 2, 128, 16, 500000.0),     # beyond the default limit: runs streamed only when the limit is raised
-    (20, 3, 128, 2, 64, 8, 0.0),               # unrotated keys on the matrix-vector kernel
-    (40, 12, 256, 2, 128, 16, 0.0),            # and on the weight-streaming one
+    (20, 3, 128, 2, 64, 8, 0.0),               # unrotated keys
+    (40, 12, 256, 2, 128, 16, 0.0),
 ]
 
 
@@ -191,9 +195,14 @@ def _append_contiguous(case, with_workspace):
 SPLIT_CASES = [
     # n, n_new, d_model, Hkv, d, r, theta, parts the automatic choice takes (0: it keeps one kernel)
     (100, 17, 512, 2, 128, 16, 500000.0, 0),        # up to 32 tokens: the weight-streaming kernel
-    (200, 40, 512, 2, 128, 16, 500000.0, 2),        # 8 steps of d_model: two parts of four
-    (65000, 33, 1024, 4, 128, 16, 500000.0, 4),
-    (64, 64, 768, 3, 64, 64, 10000.0, 2),           # 12 steps: two parts of six
+    (200, 40, 512, 2, 128, 16, 500000.0, 2),        # told a size, and streamed: x is small
+    (65000, 33, 1024, 4, 128, 16, 500000.0, 4),     # ... likewise
+    (64, 64, 768, 3, 64, 64, 10000.0, 2),           # ... likewise
+    (200, 65, 512, 2, 128, 16, 500000.0, 2),        # 8 steps of d_model: two parts of four
+    (200, 65, 768, 3, 64, 64, 10000.0, 2),          # 12 steps: two parts of six; 64 wide
+    (90, 90, 1280, 5, 64, 24, 500000.0, 4),         # 20 steps: four parts of five
+    (300, 64, 4096, 2, 64, 8, 0.0, 16),             # x beyond 416 KB: sixteen parts of four
+    (70, 33, 2048, 15, 128, 16, 10000.0, 8),        # more features than one workgroup per unit has
     (200, 129, 256, 2, 128, 16, 500000.0, 0),       # 4 steps: too short to divide
     (700, 300, 704, 3, 64, 24, 10000.0, 0),         # 11 steps: no part count divides them
     (513, 257, 4096, 8, 128, 64, 0.0, 2),           # Llama-3-8B projection shape, r = 64, unrotated keys

@@ -11,7 +11,9 @@ import pytest
 
 from paper_2602_01053_amd.binding import LraCache, LraShape, LraTuning
 from tests import test_append_gpu as A
+from tests import test_merge_tokens_gpu as M
 from tests import test_parity_gpu as P
+from tests import test_rope_shares_gpu as R
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 FIELDS = ("mfma", "short_prefill", "wave_rows", "wave_shares", "n_splits", "tile_group", "batch_wgs", "batch_tiles", "row_tiles",
@@ -60,7 +62,7 @@ def test_batches_in_one_row(planner):
         tile_rank = 16 // pl["group_pad"] * pl["l_block"] if pl["l_block"] else r
         rotary = (16 if r <= 16 else 32 if r <= 32 else 64) if side == "rotary" else 0
         seen.add((d, pl["row_tiles"], 32 if tile_rank <= 32 else 64, side in ("bk", "own", "rotary"), rotary, pl["l_block"] > 0))
-    assert len(seen) == 28  # the instantiations of decode_batch_kernel
+    assert len(seen) == 29  # the instantiations of decode_batch_kernel
     # ... of the shared list, the ones below, whatever the host believes
     rows = [i for i, (lens, agents, hq, hkv, d, r, side) in enumerate(P.BATCH_CASES)
             if all(_plan(planner, hq, hkv, d, r, lens, agents=agents, paged=True, side=side, host=h)["batch_wgs"]
@@ -92,7 +94,27 @@ def test_prefills_on_the_tile_walk(planner):
         assert pl["workspace_optional"] and pl["n_splits"] > 1 and not pl["wave_rows"]
 
 
+def test_long_prefills_that_merge(planner):
+    for n_new, n, hq, hkv, d, r, _ in M.CASES:
+        pl = _plan(planner, hq, hkv, d, r, [n], n_new=n_new, paged=True)
+        assert n_new * hq >= 9216 and not pl["wave_rows"] and not pl["short_prefill"], (n_new, n)
+        assert 2 <= pl["n_splits"] <= 16 if pl["mfma"] else (pl["n_splits"] == 1 and r % 8), (n_new, n)
+
+
+def test_rotary_calls_with_shares_of_two_sizes(planner):
+    for n, n_new, hq, hkv, d, r in R.PREFILL_CASES:
+        for paged in (False, True):
+            pl = _plan(planner, hq, hkv, d, r, [n], n_new=n_new, paged=paged, side="rotary")
+            assert pl["short_prefill"] and 0 < pl["split_more"] < pl["n_splits"], (n, n_new)
+    for host in (R.ROW_LENS, None):
+        pl = _plan(planner, 32, 8, 128, 16, R.ROW_LENS, agents=3, paged=True, side="rotary", host=host)
+        assert pl["batch_wgs"] >= len(R.ROW_LENS) and (pl["batch_tiles"] > 0) == (host is not None)
+
+
 def test_appends_that_divide_d_model(planner):
+    """-1: 64 x 64 tiles, -2: the weight-streaming kernel where d_model would be divided; else the parts."""
     tiles_of_64 = {(129, 256), (512, 1024), (400, 4096)}  # (a size is told for the last two, and not used)
+    streamed = {(40, 512), (33, 1024), (64, 768)}         # (here too)
     for n, n_new, d_model, hkv, d, r, theta, parts in A.SPLIT_CASES:
-        assert planner.append_query(n_new, hkv, d, r, d_model, None) == (-1 if (n_new, d_model) in tiles_of_64 else max(parts, 1))
+        expect = -1 if (n_new, d_model) in tiles_of_64 else (-2 if (n_new, d_model) in streamed else max(parts, 1))
+        assert planner.append_query(n_new, hkv, d, r, d_model, None) == expect, (n_new, d_model)

@@ -16,10 +16,11 @@ DEV = "cuda:0"
 CASES = [
     # new tokens, keys, Hq, Hkv, d, r, value side
     (331, 3000, 28, 4, 128, 24, True),   # 2317 rows of a kv head: a wave with one row
-    (577, 1200, 16, 2, 128, 8, True),    # most of the keys are the new tokens' own
+    (577, 2400, 16, 2, 128, 8, True),    # group of 8
     (293, 2500, 32, 8, 64, 64, True),
     (289, 2049, 32, 8, 64, 8, False),
     (384, 4000, 24, 2, 128, 40, True),   # 9216 rows, the first size
+    (297, 1100, 32, 8, 128, 20, True),   # a rank that is no multiple of eight: the vector kernel's states, one share
 ]
 
 
@@ -29,7 +30,7 @@ def test_prefill(n_new, n, hq, hkv, d, r, value_side):
                      d_model=None, b_std=0.1)
     dw = DeviceWorkload(w, DEV)
     shares = lra.lra_workspace_bytes(dw.shape, dw.cache, 1, 1, n_new) // (n_new * hq * (d + r) * 4)
-    assert 2 <= shares <= 16
+    assert 2 <= shares <= 16 or (shares == 1 and r % 8)
     q = torch.randn(n_new, hq, d, generator=torch.Generator().manual_seed(n)).to(torch.bfloat16)
     out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device=DEV)
     ws = torch.empty(lra.lra_workspace_bytes(dw.shape, dw.cache, 1, 1, n_new), dtype=torch.uint8, device=DEV)

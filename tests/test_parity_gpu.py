@@ -624,6 +624,7 @@ BATCH_ROW_CASES = [
     # rotary: three and five row groups, one workgroup per compute unit at rank 40
     ([9000, 2000, 5000, 7000, 6100, 8000], 5, 28, 4, 64, 16, "rotary"), ([20000, 9000, 16000], 2, 32, 8, 64, 24, "rotary"),
     ([9000, 3000, 6100, 2000], 3, 16, 8, 64, 40, "rotary"), ([9000, 2000, 5000], 9, 28, 4, 128, 24, "rotary"),
+    ([20000, 3000, 9000, 1000], 3, 32, 8, 128, 16, "rotary"),
     # batches of some tens of sequences, two row groups in the second
     ([300 + 141 * (7 * i % 20) for i in range(20)], 2, 16, 4, 128, 16, "bk"), ([1200 + 90 * (11 * i % 48) for i in range(48)], 6, 14, 2, 64, 32, "none"),
 ]

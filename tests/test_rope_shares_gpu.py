@@ -52,9 +52,12 @@ def test_decode(case):
     assert rel <= REL_L2_TOL and mx <= MAX_ABS_TOL
 
 
+ROW_LENS = [9000, 8700, 129, 1, 2500, 4000]
+
+
 def test_batch_in_one_row_at_rank_16():
     """128 wide, ranks up to 16, the shares of all sequences in one row."""
-    w = W.make_paged("rope", seed=5, seq_lens=[2817, 3000, 129, 1, 2500], agents_per_seq=3, n_adapters=3, n_q_heads=32, n_kv_heads=8,
+    w = W.make_paged("rope", seed=5, seq_lens=ROW_LENS, agents_per_seq=3, n_adapters=3, n_q_heads=32, n_kv_heads=8,
                      head_dim=128, rank=16, d_model=None, b_std=0.1)
     ref = oracle.decode(_f64(w.q), _f64(w.k_base), _f64(w.v_base), _f64(w.l), _f64(w.b_k), _f64(w.b_v), w.query_adapter.numpy(),
                         w.seq_query_start.numpy(), w.seq_lens, w.scale, block_size=w.block_size, block_table=w.block_table.numpy(),
@@ -67,3 +70,37 @@ def test_batch_in_one_row_at_rank_16():
         torch.cuda.synchronize()
         rel, mx = errors(dw.out.to(torch.float64).cpu().numpy(), ref)
         assert rel <= REL_L2_TOL and mx <= MAX_ABS_TOL
+
+
+PREFILL_CASES = [
+    # keys, new tokens, Hq, Hkv, d, r: the first shares a tile longer than the rest
+    (9000, 8, 32, 8, 128, 8),       # 71 tiles, 16 shares of three and 12 of two; two row groups
+    (9089, 5, 32, 8, 128, 16),      # 72 tiles, the last of one key; a row group of one token
+    (12417, 6, 32, 8, 128, 24),
+    (10348, 25, 12, 12, 128, 16),   # seven row groups, six shares
+    (16584, 27, 16, 16, 64, 16),
+]
+
+
+@pytest.mark.parametrize("paged", [False, True], ids=["contiguous", "paged"])
+@pytest.mark.parametrize("case", PREFILL_CASES, ids=[f"n{c[0]}_new{c[1]}_{c[2]}over{c[3]}_d{c[4]}_r{c[5]}" for c in PREFILL_CASES])
+def test_prefill_of_a_few_tokens(case, paged):
+    n, n_new, hq, hkv, d, r = case
+    w = W.make_paged("rope", seed=n, seq_lens=[n], agents_per_seq=1, n_adapters=2, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, rank=r,
+                     d_model=None, b_std=0.1)
+    j = torch.arange(n)
+    blk = w.block_table[0, j // 16].long()
+    k, v, l = w.k_base[blk, :, j % 16], w.v_base[blk, :, j % 16], w.l[blk, j % 16]
+    dw = DeviceWorkload(w, "cuda:0", key_rope_theta=THETA)
+    held = [t.contiguous().to("cuda:0") for t in (k, v, l)]  # (the cache holds addresses only)
+    cache = dw.cache if paged else lra.make_cache(*held, dw.seq_lens, n, None)
+    q = torch.randn(n_new, hq, d, generator=torch.Generator().manual_seed(n)).to(torch.bfloat16)
+    out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    ws = torch.full((lra.lra_workspace_bytes(dw.shape, cache, 1, 1, n_new),), 0xFF, dtype=torch.uint8, device="cuda:0")
+    qd = q.to("cuda:0")
+    lra.lra_attn_prefill(dw.shape, cache, dw.b_k, dw.b_v, 2, qd, 0, 1, out, ws)
+    torch.cuda.synchronize()
+    ref = oracle.prefill(_f64(q), _f64(k), _f64(v), _f64(l), _f64(w.b_k[1]), _f64(w.b_v[1]), n=n, scale=w.scale, key_rope_theta=THETA)
+    rel, mx = errors(out.to(torch.float64).cpu().numpy(), ref)
+    print(f"relL2={rel:.3e} maxabs={mx:.3e}", flush=True)
+    assert rel <= REL_L2_TOL and mx <= MAX_ABS_TOL
