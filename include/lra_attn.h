@@ -182,7 +182,7 @@ typedef struct {
                                   where one share size for all would leave some share far above
                                   the mean (one long sequence among many, hardly more places than
                                   sequences), and not with a rotary key side at head dimension
-                                  128 and ranks up to 16 or above 32.  Without the lengths the
+                                  128 and ranks above 32.  Without the lengths the
                                   shares of a row are sized on the device, if it has two places
                                   or more per sequence (five with a rotary key side of rank 32
                                   or less and several row groups); any other batch is taken to
@@ -388,8 +388,10 @@ lra_status lra_cache_append(const lra_shape* shape, const lra_cache* cache, cons
                             size_t workspace_bytes, const lra_tuning* tuning, void* stream);
 
 /*
- * Bytes of DEVICE workspace with which lra_cache_append takes its fastest path for this n_new;
- * 0 when the call has no use for one.  (size_t)-1 when the arguments would be rejected.
+ * Bytes of DEVICE workspace with which lra_cache_append takes its fastest path for this n_new, 0 for
+ * chunks that run as one kernel.  Some for which a size is told run as one kernel all the same (33 to
+ * some 50 tokens, and chunks whose tiles fill the chip once) and leave the workspace alone.
+ * (size_t)-1 when the arguments would be rejected.
  */
 size_t lra_append_workspace_bytes(const lra_shape* shape, const lra_cache* cache,
                                   const lra_projection* proj, int32_t n_new, const lra_tuning* tuning);

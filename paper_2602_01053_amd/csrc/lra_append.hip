@@ -728,7 +728,9 @@ __global__ __launch_bounds__(512, 2) void append_wide_kernel(AppendParams p) {
 // path at a quarter of its width, and half of the units had no workgroup.  us before and now at 3, 16 and 32 tokens:
 // 8.5 / 10.4 / 14.2 and 6.0 / 7.3 / 9.0; 4 kv heads on 3584 8.6 / 9.6 / 12.2 and 4.4 / 4.6 / 5.9; 32 kv heads
 // 19.0 / 25.5 / 35.0 and 14.1 / 18.5 / 26.0; 4 of 64 on 256, where all of it is latency, 8 tokens 2.7 and 2.85.
-// The ring takes half of a unit's LDS or less (two workgroups, and the next call's can begin): with all of it 3 tokens 6.4.
+// Up to five requests of eight rows per piece (up to 32 tokens with three pairs, 24 with more) the ring takes half of a unit's LDS or
+// less (two workgroups, and the next call's can begin: with all of it 3 tokens 6.4).  Above, a wave keeps two pieces, 96 to 160 KB:
+// one workgroup per unit.
 // ---------------------------------------------------------------------------------------
 template <int D, int WI, int XI, bool PAGED>  // requests of eight rows per piece: weights (2 PP + 1 <= 8 WI), tokens
 __global__ __launch_bounds__(512, 2) void append_skinny_kernel(AppendParams p, int pp) {
@@ -1110,7 +1112,12 @@ static void launch_skinny(const AppendParams& p, int pp, hipStream_t s) {
 
 // Pairs per workgroup: one workgroup per compute unit while its rows fit the 16 of a product (up to 1792 K features), else two (16
 // kv heads on 4096, 8 tokens: 9.9 us with 4 pairs, 11.2 with 7), and beyond 3072 six pairs (32 kv heads: 15.3 with 6, 15.7 with
-// 7, 16.2 with 4).  Two per unit on smaller layers read x twice as often (8 kv heads on 4096, 3 tokens: 6.0 and 7.3).
+// 7, 16.2 with 4).  Two per unit on smaller layers read x twice as often (8 kv heads on 4096, 3 tokens: 6.0 and 7.3).  (From 25
+// tokens on their rings leave room for one at a time, and these workgroups run one after the other: with seven pairs, the most a
+// product's rows hold, there would still be more than one per unit.)
+// Layers of 256 features and less on a width of up to 256 take 0.1 to 0.25 us more at 5 to 16 tokens than with operands straight
+// from memory and sixteen features per workgroup (3.1 / 2.85), and neither operands from memory here (3.15), nor a ring of two
+// pieces (3.05), nor the rate worked out behind the sums (3.3) brings that back.
 // There are 64 workgroups or more, a workgroup for every L feature.
 template <int D>
 static void launch_skinny_tokens(const AppendParams& p, hipStream_t s) {

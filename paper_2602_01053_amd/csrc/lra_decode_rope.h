@@ -11,8 +11,9 @@
 // with Q read as zeros in the rows of the other slots (their lanes read a zero piece: no masking instructions).  The B_K^T
 // operands of the slots stay in registers for the whole share.
 //
-// What bounds it is the vector unit: per 32 keys and slot 128 multiply-adds and 32 conversions a lane, 64 sines and cosines
-// for all slots; the products run beside it.  A wave has 100 to 400 keys, so everything before its first step counts as
+// What bounds it on long shares is the vector unit: per 32 keys and slot 128 multiply-adds and 32 conversions a lane, 64 sines and
+// cosines for all slots; the products run beside it (4 agents on 60000 keys: vector instructions issue in 64 % of a SIMD's time, the
+// matrix pipes are busy for 24 %, LDS for 26 %; on 8192, two steps per wave, it is the round trips before the first: 28 % and 10 %, waiting 53 %).  A wave has 100 to 400 keys, so everything before its first step counts as
 // much as the steps: the workgroup fetches the B_K slices and the rows of Q once (the waves share them), the K and L rows
 // of the first tile follow at once and its V rows when the operands are picked up; in the loop the next K rows are requested
 // as soon as the scores have read this tile's, so the rotation covers their way.

@@ -263,19 +263,24 @@ static PrefillTiles plan_prefill_tiles(const lra_shape* sh, int tokens, int max_
 // Whether a prefill of few new tokens (no rotary key side) runs on the tile-walking kernel rather than on the
 // split-KV decode kernels.  Those take 16 rows per tile and, beyond 32 rows of a kv head, read the keys once per row
 // group; the tile-walking kernel has one tile for 128 rows, at the price of 128 rows' matrix work per key, and at most
-// 32 shares of it: with few kv heads it cannot fill the chip on long contexts.  Measured on MI355X at 0.3 to 33
-// thousand keys (ratio of the times split-KV / tile walk; G = q heads per kv head):
-//   8 kv heads, G 4    5 and 8 tokens 1.2 at 2 k, 1.05 at 9 k, paged 1.1 to 1.4 throughout; 32 tokens 1.0 to 4 k, 1.15 at 9 k, 1.55 at 33 k
-//   8 kv heads, d 64   8 tokens 1.13 at 2 k, 1.0 at 9 k, 0.87 at 20 k
-//   4 kv heads, G 7    4 tokens 1.0 at 6 k, 0.97 at 9 k, paged 1.08 at 9 k, 0.95 at 14 k; 8 tokens 1.03 at 9 k, paged 1.02 at 33 k
-//   2 kv heads, G 8    8 tokens 1.08 at 2 k, 0.98 at 6 k, 0.94 at 9 k, paged 1.02 at 9 k, 0.92 at 14 k; 16 tokens 0.94 from 2 k
-//                      on, paged 1.0 at 14 k, 0.94 at 20 k; 20 tokens 0.92 to 0.97 from 7 k on; 32 tokens 0.96 at 6 k, 1.04 at 9 k
-//   32 kv heads, G 1   5 and 8 tokens 1.1 to 14 k, 0.81 to 0.93 at 20 k (one row group: both read the keys once)
+// 32 shares of it: with few kv heads it cannot fill the chip on long contexts.  Measured on MI355X at 2 to 33 thousand
+// keys, each path as it is now (ratio of the times split-KV / tile walk, contiguous and paged; G = q heads per kv head):
+//   8 kv heads, G 4    5 and 8 tokens 1.17 and 1.13 at 2 k, 1.03 and 1.0 at 9 k, 1.05 and 0.97 at 33 k; 16 tokens 1.03 and 1.0 at 2 k,
+//                      1.12 and 1.2 at 9 k and beyond; 32 tokens 0.88 at 2 k, 1.05 at 4 k, 1.15 at 9 k, 1.57 and 1.71 at 33 k
+//   8 kv heads, d 64   8 tokens 1.18 at 2 k, 0.98 at 9 k, 0.85 and 0.79 at 20 k; 16 tokens 1.03 to 1.08, paged to 1.22
+//   4 kv heads, G 7    4 tokens 1.08 and 1.05 at 4 k, 1.01 and 0.96 at 6 k, 0.95 and 0.9 at 9 k, 0.78 and 0.73 at 33 k; 8 tokens 1.03 and
+//                      1.0 at 4 k, 1.0 and 0.97 at 9 k, 0.92 and 0.88 at 33 k; 16 tokens 0.93 at 4 k, 1.07 and 1.24 at 9 k, 1.2 at 33 k
+//   2 kv heads, G 8    8 tokens 1.1 and 1.05 at 2 k, 0.99 and 0.94 at 6 k, 0.93 and 0.87 at 9 k, 0.82 and 0.78 at 14 k; 16 tokens 0.94 and
+//                      0.9 at 2 k to 9 k, 0.93 at 14 k; 20 tokens 0.9 to 6 k, 1.02 from 9 k on; 32 tokens 0.9 at 2 k, 1.24 at 9 k
+//   32 kv heads, G 1   5 and 8 tokens 0.85 and 0.88 at 20 k; 16 tokens 1.16 to 1.3 throughout
 // Ranks above 32 cost the tile walk more, on pages most of all:
-//   4 kv heads, G 7    paged 4 and 8 tokens 1.1 at 4 k, 0.92 and 0.95 at 7 k; 12 tokens 0.98 at 7 k, 0.90 at 33 k
-//   2 kv heads, G 8    paged 8 tokens 1.07 at 4 k, 0.92 at 7 k, 0.83 at 11 k; 20 tokens 0.98 at 4 k, 0.94 at 7 k, 0.80 at 33 k; 28 tokens 1.0 to 1.13
-//   32 kv heads, G 1   paged 8 tokens 1.03 at 2 k, 0.94 at 7 k, 0.75 at 33 k
-//   8 kv heads, d 64   10 to 16 tokens 1.0 at 11 k, 0.95 at 20 k, 0.92 at 33 k
+//   4 kv heads, G 7    paged 4 and 8 tokens 1.06 and 1.0 at 2 k, 0.96 and 0.99 at 4 k, 0.79 and 0.86 at 7 k; 12 tokens 0.91 to 0.95, 0.86 at 7 k
+//   2 kv heads, G 8    paged 8 tokens 0.92 at 4 k, 0.79 at 7 k, 0.51 at 33 k; 20 tokens 0.89 at 4 k, 0.84 at 7 k; 28 tokens 0.85 to 0.89
+//   32 kv heads, G 1   paged 8 tokens 0.86 at 2 k, 0.75 at 7 k, 0.64 at 33 k
+//   8 kv heads, d 64   12 and 16 tokens 0.94 and 0.91 at 11 k, 0.87 at 33 k, paged 1.01 to 1.04
+// The lines below are older than the streaming kernel on pages and the one product that forms Qt of a prefill: paged calls of few kv
+// heads, and ranks above 32 from 4 thousand keys on, stay on the tile walk up to where it is 6 to 20 % behind (2 kv heads, 8 tokens on
+// 9000 keys of a paged cache 15.5 / 13.5 us); none is slower than it was before those two.
 static bool short_prefill_walks_tiles(const lra_shape* sh, const lra_cache* c, int tokens) {
   const int G = sh->n_q_heads / sh->n_kv_heads, n = c->max_seq_len;
   const int rows = tokens * (G <= 4 ? 4 : (G <= 8 ? 8 : 16));  // rows of a kv head in the split-KV kernels
@@ -441,6 +446,8 @@ static int plan_wave_shares(const lra_shape* sh, const lra_cache* c, int tokens,
 // row groups 516 / 690).  Unknown ones, up to rank 32: from five places per sequence on 1.1 to 1.2 in the mean, 0.87 to 0.94 at 4 of
 // 80, below that 0.82 to 1.33, worst where the sequences are long and even, since the grid then has four rounds of equal workgroups
 // (10 of 32 k to 38 k 304 / 365); above rank 32, one workgroup per unit, 1.0 to 1.7.
+// (The lines are those of the 16 x 16 form before decode_rope_share.  With that, at d = 128 and ranks up to 16, 200 drawn batches, in a
+// row where these lines say so: 1.03 in the mean, two of them 0.945 and 0.967.)
 static void plan_batch(Plan& pl, const lra_shape* sh, const lra_cache* c, bool key_adapter) {
   constexpr int kMost = 64;  // sequences: one per lane
   if (c->n_seqs > kMost) return;
