@@ -215,11 +215,13 @@ __device__ __forceinline__ void decode_rope_share(const Params& p, const int h, 
                              nv > 0 ? static_cast<uint32_t>(nv - 1) * ts2 + D * 2 : 0u);
         s0 = 0;
       }
+      constexpr int N = KVL / 2;
+      if (stream_kv) {
 #pragma unroll
-      for (int i = 0; i < KVL / 2; ++i) {
-        const int ii = half * (KVL / 2) + i;
-        if (stream_kv) buf_load16_to_lds<true>(rs, lds + ii * 1024, voff[ii % per], (s0 + i * KROWS) * ts2);
-        else buf_load16_to_lds<false>(rs, lds + ii * 1024, voff[ii % per], (s0 + i * KROWS) * ts2);
+        for (int i = 0; i < N; ++i) buf_load16_to_lds<true>(rs, lds + (half * N + i) * 1024, voff[(half * N + i) % per], (s0 + i * KROWS) * ts2);
+      } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) buf_load16_to_lds<false>(rs, lds + (half * N + i) * 1024, voff[(half * N + i) % per], (s0 + i * KROWS) * ts2);
       }
     }
   };
