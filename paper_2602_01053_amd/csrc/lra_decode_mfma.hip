@@ -81,12 +81,21 @@ __global__ __launch_bounds__(256, RPE == 64 ? 1 : 2) void decode_mfma_kernel(Par
     // HBM if the others ask the same L2 soon after.  Workgroups go round-robin over the 8 XCDs in the order of
     // their linear index x + Hkv * y, so with m = lcm(8, Hkv) / Hkv and y = (share mod m) + m * (row group +
     // row_groups * (share / m)) the row groups of a share are lcm(8, Hkv) workgroups apart: the same XCD, the next
-    // round of the dispatcher.  (Key shares are padded to a multiple of m; z is the sequence.)
+    // round of the dispatcher.  (z is the sequence.)  Key shares are padded to a multiple of m; in the rotary form, where a
+    // workgroup without keys can push another into the next round, those behind the last multiple stand in the order of
+    // the plain grid.
     const int m = p.rg_interleave, y = blockIdx.y;
-    const int hi = y >> __builtin_ctz(m);
-    const int q = hi / p.row_groups;
-    rg = hi - q * p.row_groups;
-    split = (y & (m - 1)) + m * q;
+    const int whole = RPE > 0 ? p.n_splits & ~(m - 1) : p.n_splits;
+    if (RPE > 0 && y >= whole * p.row_groups) {
+      const int rest = p.n_splits - whole, at = y - whole * p.row_groups;
+      rg = at / rest;
+      split = whole + at - rg * rest;
+    } else {
+      const int hi = y >> __builtin_ctz(m);
+      const int q = hi / p.row_groups;
+      rg = hi - q * p.row_groups;
+      split = (y & (m - 1)) + m * q;
+    }
     t = CAUSAL ? p.seq_index : blockIdx.z;
     if (split >= p.n_splits) return;
   }
@@ -161,11 +170,13 @@ hipError_t launch_decode_mfma(const Params& p, int row_tiles, bool allow_stream_
   Params pi = p;
   pi.rg_interleave = 0;
   const int n_seqs = p.is_prefill ? 1 : p.n_seqs;
-  const int m = mfma_interleave(p.n_kv_heads, p.n_splits, p.row_groups, n_seqs, p.key_rope_theta > 0.f && p.b_k != nullptr, p.rank);
+  const bool rotary = p.key_rope_theta > 0.f && p.b_k != nullptr;
+  const int m = mfma_interleave(p.n_kv_heads, p.n_splits, p.row_groups, rotary);
   if (m > 0) {
     // (see the kernel: row groups of a key share next to each other on one XCD)
     pi.rg_interleave = m;
-    grid = dim3(p.n_kv_heads, static_cast<unsigned>((p.n_splits + m - 1) / m * m * p.row_groups), n_seqs);
+    const int shares = rotary ? p.n_splits : (p.n_splits + m - 1) / m * m;
+    grid = dim3(p.n_kv_heads, static_cast<unsigned>(shares * p.row_groups), n_seqs);
   }
   return launch_decode_mfma_grid(pi, row_tiles, grid, s);
 }

@@ -121,18 +121,15 @@ static int64_t meeting_shares(int64_t fit, int n_kv_heads, int row_groups) {
   return fit / m * m * 16 >= fit * 15 ? fit / m * m : fit;
 }
 
-// The rotary forms, which the vector unit bounds, take the interleaved grid, and the workgroups without keys that pad it, only where
-// a call whose workgroups are all resident at once does not come to another workgroup per compute unit (ranks up to 32 hold two,
-// above one; us interleaved / not: 5 kv heads, rank 64, 12 tokens after 21466, 255 workgroups and 360 padded 65.8 / 39.7, 16 tokens
-// 87.3 / 48.3; 12 kv heads, rank 48, 16 after 607 18.0 / 12.6; 5 kv heads, 4 agents on 41459, rank 32, 500 and 560 52.4 / 46.7).
-int mfma_interleave(int n_kv_heads, int n_splits, int row_groups, int n_seqs, bool rotary, int rank) {
+// The rotary forms are not padded (the shares behind the last multiple of m stand in the order of the plain grid): calls that are
+// resident at once would get workgroups for another round, and on the plain grid every row group reads the keys from beyond L2
+// (us padded / plain / so: 5 kv heads, rank 64, 12 tokens after 21466, 255 workgroups and 360 padded, 66 / 37.0 / 34.2; 12 kv heads,
+// rank 32, 24 after 33421, 504 and 576 183 / 145 / 111; of 500 calls 1.001 in the mean, one at 0.92).
+int mfma_interleave(int n_kv_heads, int n_splits, int row_groups, bool rotary) {
   if (row_groups <= 1) return 0;
   const int m = interleave_step(n_kv_heads);
-  const int64_t shares = (static_cast<int64_t>(n_splits) + m - 1) / m * m;
-  if (shares * row_groups > 65535) return 0;
-  const int64_t units = static_cast<int64_t>(n_kv_heads) * row_groups * n_seqs;
-  if (rotary && units * n_splits <= (rank > 32 ? kCUs : 2 * kCUs) && (units * shares + kCUs - 1) / kCUs > (units * n_splits + kCUs - 1) / kCUs) return 0;
-  return m;
+  const int64_t shares = rotary ? n_splits : (static_cast<int64_t>(n_splits) + m - 1) / m * m;
+  return shares * row_groups > 65535 ? 0 : m;
 }
 
 int decode_mfma_row_tiles(int rows_needed) { return rows_needed <= 16 ? 1 : 2; }

@@ -76,7 +76,7 @@ AppendSplit plan_append_split(int n_new, int n_kv_heads, int head_dim, int rank,
 // Key shares of the streaming kernel's grid where the kv head is its fastest index: the call's, or more, which end at once.
 int stream_grid_shares(int n_kv_heads, int n_splits, int row_groups);
 // rg_interleave of the split-KV kernel's grid (see there), 0: kv head, key share, (sequence, row group).
-int mfma_interleave(int n_kv_heads, int n_splits, int row_groups, int n_seqs, bool rotary, int rank);
+int mfma_interleave(int n_kv_heads, int n_splits, int row_groups, bool rotary);
 
 // Row tiles per workgroup the split-KV MFMA kernels are built for.
 int decode_mfma_row_tiles(int rows_needed);

@@ -25,8 +25,8 @@ extern "C" void plan_query(const lra_shape* sh, const lra_cache* c, int tokens, 
 
 extern "C" int stream_grid_query(int n_kv_heads, int n_splits, int row_groups) { return lra::stream_grid_shares(n_kv_heads, n_splits, row_groups); }
 
-extern "C" int interleave_query(int n_kv_heads, int n_splits, int row_groups, int n_seqs, int rotary, int rank) {
-  return lra::mfma_interleave(n_kv_heads, n_splits, row_groups, n_seqs, rotary != 0, rank);
+extern "C" int interleave_query(int n_kv_heads, int n_splits, int row_groups, int rotary) {
+  return lra::mfma_interleave(n_kv_heads, n_splits, row_groups, rotary != 0);
 }
 
 extern "C" int append_query(int n_new, int n_kv_heads, int head_dim, int rank, int d_model, const lra_tuning* tuning) {

@@ -106,6 +106,13 @@ def test_rotary_calls_with_shares_of_two_sizes(planner):
         for paged in (False, True):
             pl = _plan(planner, hq, hkv, d, r, [n], n_new=n_new, paged=paged, side="rotary")
             assert pl["short_prefill"] and 0 < pl["split_more"] < pl["n_splits"], (n, n_new)
+    rests = []
+    for n, n_new, hq, hkv, d, r in R.REST_CASES:
+        pl = _plan(planner, hq, hkv, d, r, [n], n_new=n_new, paged=True, side="rotary")
+        m = planner.interleave_query(hkv, pl["n_splits"], pl["row_groups"], 1)
+        assert pl["short_prefill"]
+        rests.append((m, pl["n_splits"]))
+    assert rests == [(8, 12), (2, 7), (8, 6)]
     for host in (R.ROW_LENS, None):
         pl = _plan(planner, 32, 8, 128, 16, R.ROW_LENS, agents=3, paged=True, side="rotary", host=host)
         assert pl["batch_wgs"] >= len(R.ROW_LENS) and (pl["batch_tiles"] > 0) == (host is not None)

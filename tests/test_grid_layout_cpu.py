@@ -22,22 +22,30 @@ def test_streaming_grids_fit_one_round(planner):  # noqa: F811
 
 
 def test_interleaved_grids_of_rotary_calls(planner):  # noqa: F811
-    """The padding of an interleaved grid does not cost a rotary call that is resident at once another workgroup per compute unit;
-    where it is taken the row groups of a share are on one XCD."""
-    taken = refused = 0
+    """The kernel's walk of its grid: every (share, row group) once, nothing beyond them, and the row groups of every share in a
+    whole block of m on one XCD."""
+    met = 0
     for hkv in (1, 2, 3, 4, 5, 6, 7, 8, 12, 24, 32, 40):
         for row_groups in range(2, 12):
-            for rank, room in ((16, 512), (32, 512), (40, 256), (64, 256)):
-                for splits in range(1, room // (hkv * row_groups) + 1):
-                    m = planner.interleave_query(hkv, splits, row_groups, 1, 1, rank)
-                    if m == 0:
-                        refused += 1
-                        continue
-                    taken += 1
-                    padded = -(-splits // m) * m
-                    assert hkv * m % 8 == 0 and hkv * row_groups * padded <= room
-                    assert -(-hkv * row_groups * padded // 256) == -(-hkv * row_groups * splits // 256)
-    assert taken > 100 and refused > 100
-    assert planner.interleave_query(5, 17, 3, 1, 1, 64) == 0 and planner.interleave_query(5, 50, 2, 1, 1, 32) == 0
-    assert planner.interleave_query(5, 48, 2, 1, 1, 32) == 8 and planner.interleave_query(8, 31, 2, 1, 1, 16) == 1
-    assert planner.interleave_query(5, 17, 3, 1, 0, 64) == 8  # no rotation: as ever
+            for splits in range(1, 512 // (hkv * row_groups) + 1):
+                m = planner.interleave_query(hkv, splits, row_groups, 1)
+                assert m in (1, 2, 4, 8) and hkv * m % 8 == 0
+                whole = splits & ~(m - 1)
+                seen = {}
+                for y in range(splits * row_groups):
+                    if y >= whole * row_groups:
+                        rest, at = splits - whole, y - whole * row_groups
+                        rg, split = at // rest, whole + at % rest
+                    else:
+                        hi = y // m
+                        rg, split = hi % row_groups, y % m + m * (hi // row_groups)
+                    assert (split, rg) not in seen and split < splits and rg < row_groups
+                    seen[split, rg] = y
+                assert len(seen) == splits * row_groups
+                for split in range(whole):
+                    for x in (0, hkv - 1):
+                        assert len({(x + hkv * seen[split, rg]) % 8 for rg in range(row_groups)}) == 1
+                        met += 1
+    assert met > 1000
+    assert planner.interleave_query(5, 17, 1, 1) == 0 and planner.interleave_query(5, 17, 3, 0) == 8
+    assert planner.interleave_query(5, 65530, 2, 0) == 0  # (131072 in the grid's second dimension)

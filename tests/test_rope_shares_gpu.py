@@ -26,6 +26,8 @@ CASES = [
     (129, 4, 8, 2, 128, 8, True, 0),        # a tile and a key
     (17, 2, 8, 2, 64, 40, True, 0),         # one workgroup, three waves without keys
     (3001, 4, 16, 1, 128, 64, True, 0),     # group of 16: a slot fills the tile
+    (2500, 9, 20, 5, 64, 40, True, 0),      # three row groups, ten shares of which eight meet on an XCD
+    (3001, 7, 20, 5, 128, 24, False, 0),    # four, twelve of which eight
 ]
 
 
@@ -80,10 +82,16 @@ PREFILL_CASES = [
     (10348, 25, 12, 12, 128, 16),   # seven row groups, six shares
     (16584, 27, 16, 16, 64, 16),
 ]
+REST_CASES = [
+    # ... and as many shares as do not all meet on an XCD: whole blocks of eight, eight and two, none, with a rest
+    (3001, 12, 20, 5, 128, 24),     # twelve shares, three row groups
+    (4000, 21, 12, 12, 128, 32),    # seven, six row groups
+    (700, 10, 20, 5, 128, 48),      # six
+]
 
 
 @pytest.mark.parametrize("paged", [False, True], ids=["contiguous", "paged"])
-@pytest.mark.parametrize("case", PREFILL_CASES, ids=[f"n{c[0]}_new{c[1]}_{c[2]}over{c[3]}_d{c[4]}_r{c[5]}" for c in PREFILL_CASES])
+@pytest.mark.parametrize("case", PREFILL_CASES + REST_CASES, ids=lambda c: f"n{c[0]}_new{c[1]}_{c[2]}over{c[3]}_d{c[4]}_r{c[5]}")
 def test_prefill_of_a_few_tokens(case, paged):
     n, n_new, hq, hkv, d, r = case
     w = W.make_paged("rope", seed=n, seq_lens=[n], agents_per_seq=1, n_adapters=2, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, rank=r,
