@@ -1,24 +1,32 @@
-"""Where the workgroups of several row groups run: workgroup i goes to XCD i mod 8, each of 32 compute units."""
+"""Where the workgroups of several row groups run: workgroup i goes to XCD i mod 8 and, of its four shader engines of eight
+compute units, to the one that i mod 32 stands for."""
 from collections import Counter
 
 from tests.test_gpu_cases_plan_cpu import planner  # noqa: F401 (a fixture)
 
 
 def test_streaming_grids_fit_one_round(planner):  # noqa: F811
-    """A grid filled up so that the row groups of a key share meet on one XCD does not give an XCD more workgroups, empty ones
-    among them, than it has compute units."""
-    filled = 0
+    """A grid filled up so that the row groups of a key share meet on one XCD does not give a shader engine more workgroups with keys
+    than it has compute units; one that is left as it is would."""
+    filled = left = 0
     for hkv in range(1, 41):
         for row_groups in range(1, 12):
             for splits in range(1, 256 // (hkv * row_groups) + 1):
                 shares = planner.stream_grid_query(hkv, splits, row_groups)
-                assert splits <= shares < splits + 8
-                if shares == splits:
+                full = next(n for n in range(splits, splits + 8) if n * hkv % 8 == 0)
+                assert shares in (splits, full)
+                if row_groups == 1 or full == splits:
+                    assert shares == splits
                     continue
-                filled += 1
-                where = [Counter((x + hkv * y + hkv * shares * rg) % 8 for y in range(shares) for x in range(hkv)) for rg in range(row_groups)]
-                assert all(w == where[0] for w in where) and max(where[0].values()) * row_groups <= 32, (hkv, splits, row_groups)
-    assert filled > 100
+                where = [[x + hkv * y + hkv * full * rg for y in range(splits) for x in range(hkv)] for rg in range(row_groups)]
+                most = max(Counter(i % 32 for w in where for i in w).values())
+                assert (shares == full) == (most <= 8), (hkv, splits, row_groups)
+                filled, left = filled + (shares == full), left + (shares != full)
+                if shares == full:
+                    on = [Counter(i % 8 for i in w) for w in where]
+                    assert all(c == on[0] for c in on)
+    assert filled > 100 and left > 100
+    assert planner.stream_grid_query(4, 29, 2) == 30 and planner.stream_grid_query(5, 12, 4) == 16 and planner.stream_grid_query(12, 3, 6) == 3
 
 
 def test_interleaved_grids_of_rotary_calls(planner):  # noqa: F811
