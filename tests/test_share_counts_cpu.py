@@ -63,6 +63,9 @@ def test_long_paged_sequences_of_several_row_groups(planner):  # noqa: F811
     assert workgroups(32, 1, 128, 14, 20479) == (2, 512) and workgroups(32, 1, 128, 14, 20480) == (2, 256)
     assert workgroups(12, 2, 128, 10, 40000) == (2, 480) and workgroups(5, 4, 128, 9, 55000)[1] <= 480
     assert workgroups(8, 4, 128, 8, 65536) == (1, 256)
+    # shares that fit two workgroups per unit, or up to a fifth less where they then meet on an XCD
+    assert workgroups(4, 7, 128, 50, 10232) == (13, 416) and workgroups(8, 8, 128, 83, 10908) == (21, 504)
+    assert workgroups(12, 2, 128, 31, 42330) == (4, 480) and workgroups(7, 2, 128, 26, 33554) == (4, 448)  # (18 fit, 16 meet)
 
 
 def test_no_room_for_a_pre_pass_that_does_not_run(planner):  # noqa: F811
