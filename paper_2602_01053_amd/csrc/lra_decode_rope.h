@@ -44,6 +44,10 @@ __device__ __forceinline__ void decode_rope_share(const Params& p, const int h, 
   // (causal: no slots to choose between, and registers to spare for Q; 24 kv heads of group 1, 23 tokens after 13163, rank 8, 103 us
   // with Q read from LDS each step, 98.7 so; 300 calls 1.01 in the mean)
   constexpr bool HOLD_Q = CAUSAL;
+  // (the non-temporal hint chosen once per sixteen rows: decodes 1.017, batches 1.021, prefills of a few tokens 1.025 in the mean against
+  // a choice per request, which spreads them; contiguous decode at ranks up to 16 has calls either way, 4 agents on 20011 keys, rank 8,
+  // 26.0 us with a choice per request and 26.8 with one per sixteen rows, 2 agents of 7 heads on 53104 29.4 and 27.5, and keeps the first)
+  constexpr bool ONE_CHOICE = CAUSAL || LAST || PAGED || RPE != 16;
   constexpr int EK = RPE / 16;     // 16-wide k-steps of the E product
   constexpr int KS = D / 32;       // k-steps of K_base Q^T
   constexpr int DB = D / 16;       // 16-wide output blocks over d; 16-wide k-steps of rot(E) Q
@@ -216,7 +220,13 @@ __device__ __forceinline__ void decode_rope_share(const Params& p, const int h, 
         s0 = 0;
       }
       constexpr int N = KVL / 2;
-      if (stream_kv) {
+      if constexpr (!ONE_CHOICE) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+          if (stream_kv) buf_load16_to_lds<true>(rs, lds + (half * N + i) * 1024, voff[(half * N + i) % per], (s0 + i * KROWS) * ts2);
+          else buf_load16_to_lds<false>(rs, lds + (half * N + i) * 1024, voff[(half * N + i) % per], (s0 + i * KROWS) * ts2);
+        }
+      } else if (stream_kv) {
 #pragma unroll
         for (int i = 0; i < N; ++i) buf_load16_to_lds<true>(rs, lds + (half * N + i) * 1024, voff[(half * N + i) % per], (s0 + i * KROWS) * ts2);
       } else {
