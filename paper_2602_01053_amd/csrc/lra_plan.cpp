@@ -330,10 +330,12 @@ static RopeShares rope_two_per_unit(int max_seq_len, int n_kv_heads, int row_gro
   const int64_t units = meeting_shares(kCUs / work, n_kv_heads, row_groups), load = units > 0 ? (tiles + units - 1) / units : 0;
   if (load < 2) return {0, 0, 0};
   const int64_t places = meeting_shares(2 * kCUs / work, n_kv_heads, row_groups), level = (tiles + places - 1) / places;
-  const bool alike = 2 * level < load, odd = !alike && (load & 1) != 0;
+  const int64_t n_alike = (tiles + level - 1) / level;
+  auto held = [&](int64_t largest, int64_t n) { return n <= 64 && (prefill ? largest >= 3 : largest >= 2 || rows * n <= 2048); };
+  const bool alike = 2 * level < load && held(level, n_alike), odd = !alike && (load & 1) != 0;
   const int64_t first = alike ? level : (load + 1) / 2;
   const int64_t n = odd ? units + (tiles - units * first + first - 2) / (first - 1) : (tiles + first - 1) / first;
-  if (n > 64 || (prefill ? first < 3 : first < 2 && rows * n > 2048)) return {0, 0, 0};
+  if (!held(first, n)) return {0, 0, 0};
   return {static_cast<int>(first * 128), static_cast<int>(n), odd ? static_cast<int>(units) : 0};
 }
 

@@ -101,6 +101,11 @@ def test_two_workgroups_per_unit_in_the_rotary_form(planner):  # noqa: F811
     assert shares(5, 4, 4, 41459, 32) == (10, 47, 7 * 128, 0)     # 25 units fit, 24 meet: loads of 14
     assert shares(5, 4, 8, 35089, 8)[:2] == (10, 46)
     assert shares(2, 8, 11, 38848, 16)[:2] == (12, 38)
+    # a prefill of a few tokens keeps 384 keys and more per share: 14 tiles on three units of 72, shares of three and two
+    pl = _plan(planner, 24, 24, 128, 8, [1686], n_new=10, paged=False, side="rotary")
+    assert (pl["n_splits"], pl["split_keys"], pl["split_more"]) == (6, 384, 3)
+    pl = _plan(planner, 32, 8, 64, 16, [2621], agents=12, paged=False, side="rotary")  # (one tile for all: too many states)
+    assert (pl["n_splits"], pl["split_keys"], pl["split_more"]) == (11, 256, 10)
 
 
 def test_rotary_shapes_without_a_key_adapter_keep_one_round(planner):  # noqa: F811
