@@ -693,12 +693,13 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
       // nothing is rotated, and the call streams where one round fills the chip.)
       const bool full = wgs / work * work * 4 >= 3 * wgs, rotates = rope && (key_adapter || !full);
       const bool streams = !rotates && tune.variant != 2 && (c->block_size == 0 || paged_stream);
-      // (two workgroups per unit, several row groups at d = 128: the shares that fit, or up to a fifth less where they then meet; without
+      // (two workgroups per unit, several row groups: the shares that fit, or up to a fifth less where they then meet; without
       // that the padded grid has another round.  28 q heads over 4, 50 agents on 10232 paged keys, rank 24 56.6 / 45; 64 over 8, 83 agents
       // on 10908, rank 64 105.7 / 94.7; 500 calls of 9 to 60 agents 1.08 in the mean, two of them 0.94 and 0.97.  At d = 64, where a
-      // unit holds three, 0.94 to 1.0.)
+      // unit holds three, 0.94 to 1.0, and only kv heads that are no multiple of eight, whose grid is padded: 1.04 in the mean of 250,
+      // 0.94 at worst.)
       const int64_t fit = wgs / work, block = interleave_step(sh->n_kv_heads), meets = fit / block * block;
-      const bool pair_rows = wgs > kCUs && pl.row_groups > 1 && sh->head_dim == 128 && pl.l_block == 0 && !rope && meets * 5 >= fit * 4 && meets > 0;
+      const bool pair_rows = wgs > kCUs && pl.row_groups > 1 && (sh->head_dim == 128 || block > 1) && pl.l_block == 0 && !rope && meets * 5 >= fit * 4 && meets > 0;
       if (!batch && work <= wgs && (rope || pair_rows || (wgs > kCUs && pl.l_block != 0) || (streams && full))) {
         const int64_t shares = pair_rows ? meets : (streams ? meeting_shares(fit, sh->n_kv_heads, pl.row_groups) : fit);
         const int64_t least = (c->max_seq_len + shares - 1) / shares;
