@@ -11,6 +11,7 @@
 #include <type_traits>
 
 #include "lra_common.h"
+#include "lra_decode_util.h"
 
 namespace lra {
 
@@ -385,13 +386,7 @@ __global__ __launch_bounds__(kWave) void generic_partial_rope_kernel(Params p) {
 // order: the result does not depend on which workgroup of the first kernel
 // finished first.
 constexpr int kMergeUnroll = 8;  // splits per thread and pass
-// Rows from which the wave-per-row form of the merge runs (measured on MI355X: 1792 rows of config
-// 5 take 12.7 us against 20.5 us; 256 rows of config 4 take 10.4 us against 9.3 us).
-constexpr int kMergeWaveRows = 1024;
-// Rows from which the form with four rows per wave runs on a prefill, nine waves of it per compute unit: 9324 rows gain 2 %
-// at rank 16 and 6 % at 32, 22400 rows up to 5 %, 16384 rows at rank 64 7 to 11 %; 6400 rows come out even, 240 rows lose a third
-// to the chain of four rows per wave.  Plans of that many rows hold a handful of shares.
-constexpr int kMergeTokenRows = 9216;
+// Shares that merge_tokens_kernel has room for.
 constexpr int kMergeTokenShares = 16;
 
 #ifdef LRA_TIMING
@@ -529,132 +524,168 @@ __global__ __launch_bounds__(128 * kMergeGroups) void merge_kernel(Params p) {
 #endif
 }
 
-// The same merge with wide loads, for the common case (head dimension 64 or 128, rank a multiple of
-// 4, at most 64 splits): one workgroup of 256 threads per query row.
-//   - lane = split for the statistics: every wave forms the flash-decoding weights w_s on its own
-//     (one 8-byte load per lane), so no barrier stands before the partial rows can be weighted;
-//   - O rows as float4: thread (split group sg, column quad cq) sums splits sg, sg + SG, ...;
-//   - O_lr rows as float4: thread (split group of 16, quad q < r/4);
-//   - the B_V slice of the row's adapter and kv head ([r][d] elements) travels to LDS in 16-byte
-//     pieces; the epilogue O += O_lr B_V reads it from there.
-// Three barriers; every sum runs in a fixed order (splits ascending inside a thread, groups
-// ascending across threads), so the result does not depend on which workgroup of the first
-// kernel finished first.  All loads of a thread are issued before the first is consumed.
-template <typename T, int D>
+// Lane exchanges on the vector unit: an LDS permute (__shfl) costs its round trip through LDS at every step of a chain.
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
+}
+template <typename F>
+__device__ __forceinline__ float over_16_lanes(float v, F op) {
+  v = op(v, dpp_f32<0x128>(v));  // row_ror:8, 4, 2, 1
+  v = op(v, dpp_f32<0x124>(v));
+  v = op(v, dpp_f32<0x122>(v));
+  return op(v, dpp_f32<0x121>(v));
+}
+__device__ __forceinline__ float from_lane(float v, int lane) {  // (lane: uniform)
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+}
+// op over the first N lanes' rows of sixteen (N = 16, 32 or 64), in every lane
+template <int N, typename F>
+__device__ __forceinline__ float over_lanes(float v, F op) {
+  v = over_16_lanes(v, op);
+  float x = from_lane(v, 0);
+#pragma unroll
+  for (int i = 16; i < N; i += 16) x = op(x, from_lane(v, i));
+  return x;
+}
+
+// The same merge for the common case (head dimension 64 or 128, rank a multiple of 4, at most 64 splits): one workgroup
+// of four waves per query row.  The launch is a chain of latencies (parameter block, the row's adapter id, the loads, one
+// barrier), so nothing may stand between them:
+//   - the parameter block is fetched in one round trip (left alone the compiler fetches it piece by piece behind each
+//     use), the grid is (kv head, q head of the group, query) so that no index needs a division, and every load is
+//     unconditional from a clamped index (a load under a condition, with zero as the other value, makes the compiler
+//     wait for it on the spot); what a clamped index fetched in vain gets weight zero;
+//   - wave w sums the splits w, w + 4, ...: addresses and weights are scalars (v_readlane), lane = column (pair at d = 128);
+//   - lane = split for the statistics, every wave forms the weights w_s on its own by DPP, without LDS;
+//   - the waves' sums meet in LDS behind the only barrier; then a wave finishes a quarter of the columns, sixteen lanes of
+//     which each take a quarter of the ranks, with their B_V elements in registers since before the barrier.
+// With weights by ds_bpermute (24 dependent ones), a branch per split and three barriers the launch took 3.57 us behind the
+// headline decode's first kernel, 2.40 so (3.09 and 2.11 behind the fp32 one); a launch that only adds the same parts takes 2.2.
+// NS, RB: bounds of splits and rank (16, 32 or 64).  Every sum runs in a fixed order, so the result does not depend on
+// which workgroup of the first kernel finished first.
+template <typename T, int D, int NS, int RB>
 __global__ __launch_bounds__(256) void merge_rows_kernel(Params p) {
-  constexpr int CQ = D / 4;        // column quads of an O row
-  constexpr int SG = 256 / CQ;     // split groups for the O rows
-  constexpr int OP = 64 / SG;      // passes over at most 64 splits
-  constexpr int BV_PIECES = 64 * D * static_cast<int>(sizeof(T)) / 16 / 256;  // 16-byte pieces of B_V per thread at r = 64
-  // This kernel is a chain of latencies (launch, parameter block, the row's adapter id, the loads,
-  // two barriers), so nothing may stand between them: the parameter block is fetched in one round
-  // trip (left alone the compiler fetches it piece by piece behind each use), the grid is (kv head,
-  // q head of the group, query) so that no index needs a division, and every load is unconditional
-  // from a clamped index (a load under a condition, with zero as the other value, makes the compiler
-  // wait for it on the spot: both write the same register); what a clamped index fetched in vain
-  // gets weight zero below.
+  constexpr int CPL = D / 64;  // columns per lane
+  constexpr int OPW = NS / 4;  // splits per wave
+  constexpr int RPT = RB / 4;  // ranks per thread of the epilogue
   asm volatile("" ::"s"(p.part_adapter), "s"(p.part_ml), "s"(p.part_o), "s"(p.part_lr), "s"(p.b_v), "s"(p.out));
   asm volatile("" ::"s"(p.n_q_heads), "s"(p.n_kv_heads), "s"(p.group), "s"(p.head_dim), "s"(p.rank), "s"(p.n_splits),
                "s"(p.n_adapters));
   const int Hq = p.n_q_heads, r = p.rank, ns = p.n_splits;
   const int h = blockIdx.x;
   const int row = static_cast<int>(blockIdx.z) * Hq + h * p.group + static_cast<int>(blockIdx.y);
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t slot0 = static_cast<int64_t>(row) * ns;
 
-  __shared__ __align__(16) float o_sh[SG][D];
-  __shared__ __align__(16) float lr_sh[16][64];
-  __shared__ __align__(16) float olr_tot[64];
-  __shared__ __align__(16) unsigned char bv_sh[64 * D * sizeof(T)];
+  __shared__ __align__(16) float o_sh[4][D];
+  __shared__ __align__(16) float lr_sh[64][4];  // [rank][wave]
 
-  // the row's adapter first: the B_V rows depend on it (clamped: whatever the workspace holds, the
-  // B_V rows read below exist)
-  // (requested here by hand and waited for where the B_V addresses are formed: left to the compiler
-  // the request sinks below the vector loads, and its round trip is then paid after theirs)
+  // the row's adapter first: the B_V rows depend on it (requested here by hand and waited for where the B_V addresses are
+  // formed: left to the compiler the request sinks below the vector loads, and its round trip is then paid after theirs)
   int a_raw;
   asm volatile("s_load_dword %0, %1, 0x0" : "=s"(a_raw) : "s"(p.part_adapter + row));
 
   // ---- issue everything ----
   const float2 st_raw = reinterpret_cast<const float2*>(p.part_ml)[slot0 + min(lane, ns - 1)];
-  const int sg = tid / CQ, cq = tid % CQ;
-  float4 xo[OP];
+  float xo[OPW][CPL], xl[OPW];
 #pragma unroll
-  for (int k = 0; k < OP; ++k)
-    xo[k] = *reinterpret_cast<const float4*>(p.part_o + (slot0 + min(sg + SG * k, ns - 1)) * D + cq * 4);
-  const int lg16 = tid >> 4, q = tid & 15;
-  const bool q_live = q * 4 < r;
-  float4 xl[4];
+  for (int k = 0; k < OPW; ++k) {
+    const float* po = p.part_o + (slot0 + min(wave + 4 * k, ns - 1)) * D;
+    if constexpr (CPL == 2) {
+      const float2 v = reinterpret_cast<const float2*>(po)[lane];
+      xo[k][0] = v.x;
+      xo[k][CPL - 1] = v.y;
+    } else {
+      xo[k][0] = po[lane];
+    }
+  }
+  const int rl = min(lane, r - 1);  // (lanes beyond the rank: sums that are never read)
 #pragma unroll
-  for (int k = 0; k < 4; ++k)
-    xl[k] = *reinterpret_cast<const float4*>(p.part_lr + (slot0 + min(lg16 + 16 * k, ns - 1)) * r + (q_live ? q * 4 : 0));
-  constexpr int ROW_PIECES = D * static_cast<int>(sizeof(T)) / 16;  // 16-byte pieces per B_V row of one kv head
-  uint4 bvp[BV_PIECES];
+  for (int k = 0; k < OPW; ++k) xl[k] = (p.part_lr + (slot0 + min(wave + 4 * k, ns - 1)) * r)[rl];
+  // epilogue: columns c .. c + CPL - 1 of this wave's quarter, ranks rq, rq + 4, ...
+  const int c = wave * (D / 4) + (lane & 15) * CPL, rq = lane >> 4;
   asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(a_raw));
-  const int a = min(max(a_raw, 0), p.n_adapters - 1);
+  const int a = min(max(a_raw, 0), p.n_adapters - 1);  // (clamped: whatever the workspace holds, the rows read below exist)
+  typedef typename std::conditional<sizeof(T) * CPL == 8, float2, typename std::conditional<sizeof(T) * CPL == 4, uint32_t, T>::type>::type BvPiece;
+  BvPiece bvp[RPT];
   // (Requesting the slices of all adapters of a small table next to the partial rows, to pick the row's
   // own when its id arrives, takes one dependent round trip off the path and was measured 0.8 us slower.)
-  if (p.b_v != nullptr) {  // (uniform)
+  const bool has_bv = p.b_v != nullptr;  // (uniform)
+  if (has_bv) {
     const int64_t ld = static_cast<int64_t>(p.n_kv_heads) * D;
     const T* bv = static_cast<const T*>(p.b_v) + static_cast<int64_t>(a) * r * ld + h * D;
+    const uint32_t ldb = static_cast<uint32_t>(ld);
 #pragma unroll
-    for (int k = 0; k < BV_PIECES; ++k) {
-      const int e = tid + 256 * k;
-      const int rho = min(e / ROW_PIECES, r - 1), pc = e % ROW_PIECES;  // (rows beyond the rank: fetched again, never read)
-      bvp[k] = *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned char*>(bv + rho * ld) + pc * 16);
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < BV_PIECES; ++k) bvp[k] = make_uint4(0u, 0u, 0u, 0u);
+    for (int i = 0; i < RPT; ++i)  // (ranks beyond the last: fetched again, left out below)
+      bvp[i] = *reinterpret_cast<const BvPiece*>(bv + (static_cast<uint32_t>(min(4 * i + rq, r - 1)) * ldb + static_cast<uint32_t>(c)));
   }
-  const float2 st = lane < ns ? st_raw : make_float2(0.f, 0.f);
 
   // ---- weights (per wave, lane = split) ----
-  const bool live = st.y > 0.f;  // a share without a visible key left a zero row sum; its rows were never written
-  const float big = wave_max(live ? st.x : -INFINITY);
-  const float w = live ? expf(st.x - big) : 0.f;
-  const float ell = wave_sum(w * st.y);
+  // (a share without a visible key left a zero row sum; its rows were never written)
+  const bool live = lane < ns && st_raw.y > 0.f;
+  const float big = over_lanes<NS>(live ? st_raw.x : -INFINITY, [](float x, float y) { return fmaxf(x, y); });
+  const float w = live ? expf(st_raw.x - big) : 0.f;
+  const float ell = over_lanes<NS>(live ? w * st_raw.y : 0.f, [](float x, float y) { return x + y; });
 
-  // ---- weighted sums of this thread's splits ----
-  float4 o = make_float4(0.f, 0.f, 0.f, 0.f), olr = o;
+  // ---- weighted sums of this wave's splits ----
+  float o[CPL], olr = 0.f;
 #pragma unroll
-  for (int k = 0; k < OP; ++k) {
-    const float wk = __shfl(w, min(sg + SG * k, 63), kWave);
-    if (sg + SG * k < ns && wk > 0.f) {  // also keeps whatever an unwritten row holds out of the sums
-      o.x = fmaf(wk, xo[k].x, o.x);
-      o.y = fmaf(wk, xo[k].y, o.y);
-      o.z = fmaf(wk, xo[k].z, o.z);
-      o.w = fmaf(wk, xo[k].w, o.w);
+  for (int e = 0; e < CPL; ++e) o[e] = 0.f;
+#pragma unroll
+  for (int k = 0; k < OPW; ++k) {
+    const float wk = from_lane(w, wave + 4 * k);
+    const bool in = wk > 0.f;  // also keeps whatever an unwritten row holds out of the sums
+#pragma unroll
+    for (int e = 0; e < CPL; ++e) o[e] = fmaf(wk, in ? xo[k][e] : 0.f, o[e]);
+    olr = fmaf(wk, in ? xl[k] : 0.f, olr);
+  }
+#pragma unroll
+  for (int e = 0; e < CPL; ++e) o_sh[wave][lane * CPL + e] = o[e];
+  lr_sh[lane][wave] = lane < r ? olr : 0.f;
+  __syncthreads();
+
+  // ---- O += O_lr B_V, division, store ----
+  float x[CPL];
+#pragma unroll
+  for (int e = 0; e < CPL; ++e) x[e] = o_sh[rq][c + e];  // (each quarter of the lanes brings one wave's sums)
+  if (has_bv) {
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      if (4 * i >= r) break;  // (uniform; a fetched-again row of infinities stays out)
+      const float4 l4 = *reinterpret_cast<const float4*>(lr_sh[4 * i + rq]);
+      const float lv = (l4.x + l4.y) + (l4.z + l4.w);
+      if constexpr (sizeof(T) * CPL == 8) {
+        x[0] = fmaf(lv, bvp[i].x, x[0]);
+        x[CPL - 1] = fmaf(lv, bvp[i].y, x[CPL - 1]);
+      } else if constexpr (sizeof(T) == 2 && CPL == 2) {
+        x[0] = fmaf(lv, __uint_as_float(bvp[i] << 16), x[0]);
+        x[CPL - 1] = fmaf(lv, __uint_as_float(bvp[i] & 0xffff0000u), x[CPL - 1]);
+      } else if constexpr (sizeof(T) == 2) {
+        x[0] = fmaf(lv, bf16_to_f32(static_cast<bf16_t>(bvp[i])), x[0]);
+      } else {
+        x[0] = fmaf(lv, __builtin_bit_cast(float, bvp[i]), x[0]);
+      }
     }
   }
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const float wk = __shfl(w, lg16 + 16 * k, kWave);
-    if (lg16 + 16 * k < ns && wk > 0.f && q_live) {
-      olr.x = fmaf(wk, xl[k].x, olr.x);
-      olr.y = fmaf(wk, xl[k].y, olr.y);
-      olr.z = fmaf(wk, xl[k].z, olr.z);
-      olr.w = fmaf(wk, xl[k].w, olr.w);
+  for (int e = 0; e < CPL; ++e) {
+    float lo = x[e], hi = x[e];
+    permlane16_swap(lo, hi);
+    lo += hi;
+    hi = lo;
+    permlane32_swap(lo, hi);
+    x[e] = (lo + hi) / ell;
+  }
+  if (rq == 0) {
+    T* out = static_cast<T*>(p.out) + static_cast<int64_t>(row) * D + c;
+    if constexpr (sizeof(T) == 2 && CPL == 2) {
+      *reinterpret_cast<uint32_t*>(out) = pack_bf16x2(x[0], x[CPL - 1]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < CPL; ++e) out[e] = from_f32<T>(x[e]);
     }
-  }
-  *reinterpret_cast<float4*>(&o_sh[sg][cq * 4]) = o;
-  *reinterpret_cast<float4*>(&lr_sh[lg16][q * 4]) = olr;
-#pragma unroll
-  for (int k = 0; k < BV_PIECES; ++k) *reinterpret_cast<uint4*>(bv_sh + (tid + 256 * k) * 16) = bvp[k];
-  __syncthreads();
-  if (tid < 64) {
-    float x = 0.f;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) x += lr_sh[k][tid];
-    olr_tot[tid] = x;
-  }
-  __syncthreads();
-  if (tid < D) {
-    float x = 0.f;
-#pragma unroll
-    for (int k = 0; k < SG; ++k) x += o_sh[k][tid];
-    const T* bcol = reinterpret_cast<const T*>(bv_sh) + tid;
-    for (int rho = 0; rho < r; ++rho) x = fmaf(olr_tot[rho], to_f32<T>(bcol[rho * D]), x);
-    static_cast<T*>(p.out)[static_cast<int64_t>(row) * D + tid] = from_f32<T>(x / ell);
   }
 }
 
@@ -662,10 +693,12 @@ __global__ __launch_bounds__(256) void merge_rows_kernel(Params p) {
 // head, per workgroup), no LDS and no barrier, so that a CU holds twenty rows' worth of loads
 // in flight instead of four.  Lane = split for the statistics (at most 64 splits), lane =
 // column (pair of columns at d = 128) for the rows; the weight of a split and the entries of
-// O_lr travel by v_readlane.  Splits are added in index order.
-template <typename T, int D>
+// O_lr travel by v_readlane.  Splits are added in index order, eight requested at a time, up to the last
+// one that holds a visible key (in a ragged batch most rows have fewer shares than the grid).
+template <typename T, int D, int RB, int U>
 __global__ __launch_bounds__(256) void merge_wave_kernel(Params p) {
-  constexpr int CPL = D / 64;  // columns per lane: c = CPL * lane + k
+  constexpr int CPL = D / 64;   // columns per lane: c = CPL * lane + k
+  constexpr int SPL = 64 / RB;  // splits whose O_lr entries one load brings
   // (as in merge_rows_kernel: the parameter block in one round trip, a grid (kv head, group of four q
   // heads, query) without divisions, the adapter id requested by hand ahead of the vector loads, and
   // unconditional loads from clamped indices)
@@ -683,71 +716,105 @@ __global__ __launch_bounds__(256) void merge_wave_kernel(Params p) {
   const int64_t slot0 = static_cast<int64_t>(row) * ns;
   int a_raw;
   asm volatile("s_load_dword %0, %1, 0x0" : "=s"(a_raw) : "s"(p.part_adapter + row));
-
   const float2 st_raw = reinterpret_cast<const float2*>(p.part_ml)[slot0 + min(lane, ns - 1)];
-  const float2 st = lane < ns ? st_raw : make_float2(0.f, 0.f);
-  const bool live = st.y > 0.f;  // a share without a visible key left a zero row sum; its rows were never written
-  const float big = wave_max(live ? st.x : -INFINITY);
-  const float w = live ? expf(st.x - big) : 0.f;
-  const float ell = wave_sum(w * st.y);
 
-  const float* po = p.part_o + slot0 * D + CPL * lane;
-  const float* pl = p.part_lr + slot0 * r + (lane < r ? lane : 0);
-  float o[CPL], olr = 0.f;
-#pragma unroll
-  for (int k = 0; k < CPL; ++k) o[k] = 0.f;
-  constexpr int U = 8;
-  for (int s0 = 0; s0 < ns; s0 += U) {
-    float x[U][CPL], y[U];
+  const float* po = p.part_o + slot0 * D;
+  const float* pl = p.part_lr + slot0 * r + min(lane % RB, r - 1);  // (lanes beyond the rank: sums that are never read)
+  const int y_split = lane / RB;
+  float x[U][CPL], y[U / SPL];
+  auto request = [&](int s0) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int sidx = min(s0 + u, ns - 1);
-      if (CPL == 2) {
-        const float2 v = *reinterpret_cast<const float2*>(po + static_cast<int64_t>(sidx) * D);
+      if constexpr (CPL == 2) {
+        const float2 v = reinterpret_cast<const float2*>(po + sidx * D)[lane];
         x[u][0] = v.x;
         x[u][CPL - 1] = v.y;
       } else {
-        x[u][0] = po[static_cast<int64_t>(sidx) * D];
+        x[u][0] = (po + sidx * D)[lane];
       }
-      y[u] = pl[static_cast<int64_t>(sidx) * r];  // (lanes beyond the rank read column 0; their sums are never used)
+    }
+#pragma unroll
+    for (int k = 0; k < U / SPL; ++k) y[k] = pl[min(s0 + k * SPL + y_split, ns - 1) * r];
+  };
+  request(0);
+  // this wave's column pairs of B_V, requested behind the first partial rows
+  typedef typename std::conditional<sizeof(T) * CPL == 8, float2, typename std::conditional<sizeof(T) * CPL == 4, uint32_t, T>::type>::type BvPiece;
+  constexpr int BN = RB < 32 ? RB : 32;  // rows at a time
+  BvPiece bvp[BN];
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(a_raw));
+  const int a = min(max(a_raw, 0), p.n_adapters - 1);
+  const bool has_bv = p.b_v != nullptr;  // (uniform)
+  const int64_t ld = static_cast<int64_t>(p.n_kv_heads) * D;
+  const T* bv = static_cast<const T*>(p.b_v) + static_cast<int64_t>(a) * r * ld + h * D;
+  auto request_bv = [&](int r0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < BN; ++i)  // (ranks beyond the last: fetched again, left out below)
+      bvp[i] = reinterpret_cast<const BvPiece*>(bv + min(r0 + i, r - 1) * ld)[lane];
+  };
+  if (has_bv) request_bv(0);
+
+  // (a share without a visible key left a zero row sum; its rows were never written)
+  const bool live = lane < ns && st_raw.y > 0.f;
+  const float big = over_lanes<64>(live ? st_raw.x : -INFINITY, [](float u, float v) { return fmaxf(u, v); });
+  const float w = live ? expf(st_raw.x - big) : 0.f;
+  const float ell = over_lanes<64>(live ? w * st_raw.y : 0.f, [](float u, float v) { return u + v; });
+  const uint64_t live_mask = __ballot(w > 0.f);
+  const int ns_live = 64 - __builtin_clzll(live_mask | 1);
+
+  float o[CPL], olr = 0.f;
+#pragma unroll
+  for (int k = 0; k < CPL; ++k) o[k] = 0.f;
+  for (int s0 = 0; s0 < ns_live; s0 += U) {
+    if (s0 > 0) request(s0);
+#pragma unroll
+    for (int k = 0; k < U / SPL; ++k) {
+      const int s = s0 + k * SPL;
+      const float wy = SPL == 1 ? from_lane(w, s & 63) : __shfl(w, (s + y_split) & 63, kWave);
+      olr = fmaf(wy, wy > 0.f ? y[k] : 0.f, olr);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const float wu = (s0 + u < ns) ? __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w), (s0 + u) & 63)) : 0.f;
-      if (wu > 0.f) {  // wave-uniform; also keeps whatever an unwritten row holds out of the sums
+      const float wu = from_lane(w, (s0 + u) & 63);  // (splits beyond the last: lanes without a weight)
+      const bool in = wu > 0.f;                      // keeps whatever an unwritten row holds out of the sums
 #pragma unroll
-        for (int k = 0; k < CPL; ++k) o[k] = fmaf(wu, x[u][k], o[k]);
-        olr = fmaf(wu, y[u], olr);
-      }
+      for (int k = 0; k < CPL; ++k) o[k] = fmaf(wu, in ? x[u][k] : 0.f, o[k]);
     }
   }
-  // epilogue O += O_lr B_V, sixteen B_V rows requested at a time
-  asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(a_raw));
-  const int a = min(max(a_raw, 0), p.n_adapters - 1);
-  if (p.b_v != nullptr) {
-    const int64_t ld = static_cast<int64_t>(p.n_kv_heads) * D;
-    const T* bv = static_cast<const T*>(p.b_v) + static_cast<int64_t>(a) * r * ld + h * D + CPL * lane;
-    for (int r0 = 0; r0 < r; r0 += 16) {
-      float b[16][CPL];
+  if constexpr (SPL == 4) olr = sum_over_lane_groups(olr);
+  if constexpr (SPL == 2) {
+    float other = olr;
+    permlane32_swap(olr, other);
+    olr += other;
+  }
+  // epilogue O += O_lr B_V
+  if (has_bv) {
+    for (int r0 = 0; r0 < r; r0 += BN) {
+      if (r0 > 0) request_bv(r0);
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int rho = min(r0 + i, r - 1);
-#pragma unroll
-        for (int k = 0; k < CPL; ++k) b[i][k] = to_f32<T>(bv[rho * ld + k]);
-      }
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        if (r0 + i < r) {
-          const float xr = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, olr), (r0 + i) & 63));
-#pragma unroll
-          for (int k = 0; k < CPL; ++k) o[k] = fmaf(xr, b[i][k], o[k]);
+      for (int i = 0; i < BN; ++i) {
+        if (r0 + i < r) {  // (uniform)
+          const float xr = from_lane(olr, r0 + i);
+          if constexpr (sizeof(T) * CPL == 8) {
+            o[0] = fmaf(xr, bvp[i].x, o[0]);
+            o[CPL - 1] = fmaf(xr, bvp[i].y, o[CPL - 1]);
+          } else if constexpr (sizeof(T) == 2 && CPL == 2) {
+            o[0] = fmaf(xr, __uint_as_float(bvp[i] << 16), o[0]);
+            o[CPL - 1] = fmaf(xr, __uint_as_float(bvp[i] & 0xffff0000u), o[CPL - 1]);
+          } else {
+            o[0] = fmaf(xr, to_f32<T>(__builtin_bit_cast(T, bvp[i])), o[0]);
+          }
         }
       }
     }
   }
   T* out = static_cast<T*>(p.out) + static_cast<int64_t>(row) * D + CPL * lane;
+  if constexpr (sizeof(T) == 2 && CPL == 2) {
+    *reinterpret_cast<uint32_t*>(out) = pack_bf16x2(o[0] / ell, o[CPL - 1] / ell);
+  } else {
 #pragma unroll
-  for (int k = 0; k < CPL; ++k) out[k] = from_f32<T>(o[k] / ell);
+    for (int k = 0; k < CPL; ++k) out[k] = from_f32<T>(o[k] / ell);
+  }
 }
 
 // The same merge for the rows of a long prefill, which share one adapter: a wave takes four rows of a kv head, reads a
@@ -756,18 +823,6 @@ __global__ __launch_bounds__(256) void merge_wave_kernel(Params p) {
 // broadcast.  What bounds it is the states' bytes, which the caches behind the L2s hand over at about 3.5 TB/s (333 tokens of
 // 32 q heads, 5 shares, rank 16: 31 MB in 10.2 us, 10.6 with a wave per row); with a wave per row the loads of B_V, one per
 // rank and row, came on top (rank 64: 512 tokens on 8000 keys in 119 us in place of 128).
-template <int CTRL>
-__device__ __forceinline__ float dpp_f32(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
-}
-template <typename F>
-__device__ __forceinline__ float over_16_lanes(float v, F op) {
-  v = op(v, dpp_f32<0x128>(v));  // row_ror:8, 4, 2, 1
-  v = op(v, dpp_f32<0x124>(v));
-  v = op(v, dpp_f32<0x122>(v));
-  return op(v, dpp_f32<0x121>(v));
-}
-
 template <int D>
 __global__ __launch_bounds__(256) void merge_tokens_kernel(Params p) {
   constexpr int RPL = 256 / D;        // rows of one load
@@ -923,26 +978,47 @@ __global__ __launch_bounds__(256) void merge_tokens_kernel(Params p) {
     }
 }
 
-static bool launch_merge_tokens(const Params& p, int rows, hipStream_t s) {
-  if (!p.is_prefill || rows < kMergeTokenRows || p.n_splits > kMergeTokenShares || (p.head_dim != 64 && p.head_dim != 128)) return false;
-  const int64_t blocks = (static_cast<int64_t>(p.n_new) * p.group + 15) / 16;
-  if (blocks > 65535) return false;
-  const dim3 grid(p.n_kv_heads, static_cast<unsigned>(blocks));
+static void launch_merge_tokens(const Params& p, hipStream_t s) {
+  const dim3 grid(p.n_kv_heads, static_cast<unsigned>((static_cast<int64_t>(p.n_new) * p.group + 15) / 16));
   if (p.head_dim == 128) hipLaunchKernelGGL((merge_tokens_kernel<128>), grid, dim3(256), 0, s, p);
   else hipLaunchKernelGGL((merge_tokens_kernel<64>), grid, dim3(256), 0, s, p);
-  return true;
 }
 
 template <typename T>
-static bool launch_merge_wave(const Params& p, int rows, hipStream_t s) {
-  // worth it from a few hundred rows on; the statistics need one lane per split
-  if (rows < kMergeWaveRows || p.n_splits > 64 || (p.head_dim != 64 && p.head_dim != 128)) return false;
-  const int tokens = rows / p.n_q_heads;
-  if (tokens > 65535) return false;  // (the query index is the grid's z)
-  dim3 grid(p.n_kv_heads, (p.group + 3) / 4, tokens);
-  if (p.head_dim == 128) hipLaunchKernelGGL((merge_wave_kernel<T, 128>), grid, dim3(256), 0, s, p);
-  else hipLaunchKernelGGL((merge_wave_kernel<T, 64>), grid, dim3(256), 0, s, p);
-  return true;
+static void launch_merge_wave(const Params& p, int rows, hipStream_t s) {
+  const dim3 grid(p.n_kv_heads, (p.group + 3) / 4, rows / p.n_q_heads);
+  auto launch = [&](auto rb_c, auto u_c) {
+    constexpr int RB = decltype(rb_c)::value, U = decltype(u_c)::value;
+    if (p.head_dim == 128) hipLaunchKernelGGL((merge_wave_kernel<T, 128, RB, U>), grid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((merge_wave_kernel<T, 64, RB, U>), grid, dim3(256), 0, s, p);
+  };
+  auto by_rank = [&](auto u_c) {
+    if (p.rank <= 16) launch(std::integral_constant<int, 16>{}, u_c);
+    else if (p.rank <= 32) launch(std::integral_constant<int, 32>{}, u_c);
+    else launch(std::integral_constant<int, 64>{}, u_c);
+  };
+  if (p.n_splits <= 4) by_rank(std::integral_constant<int, 4>{});
+  else by_rank(std::integral_constant<int, 8>{});
+}
+
+template <typename T>
+static void launch_merge_rows(const Params& p, int rows, hipStream_t s) {
+  // (kv head, q head of the group, query): workgroups go round-robin over the XCDs, so with 8 kv heads
+  // the rows of a head are merged on one XCD
+  const dim3 grid(p.n_kv_heads, p.group, rows / p.n_q_heads);
+  auto launch = [&](auto ns_c, auto rb_c) {
+    constexpr int NS = decltype(ns_c)::value, RB = decltype(rb_c)::value;
+    if (p.head_dim == 128) hipLaunchKernelGGL((merge_rows_kernel<T, 128, NS, RB>), grid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((merge_rows_kernel<T, 64, NS, RB>), grid, dim3(256), 0, s, p);
+  };
+  auto by_rank = [&](auto ns_c) {
+    if (p.rank <= 16) launch(ns_c, std::integral_constant<int, 16>{});
+    else if (p.rank <= 32) launch(ns_c, std::integral_constant<int, 32>{});
+    else launch(ns_c, std::integral_constant<int, 64>{});
+  };
+  if (p.n_splits <= 16) by_rank(std::integral_constant<int, 16>{});
+  else if (p.n_splits <= 32) by_rank(std::integral_constant<int, 32>{});
+  else by_rank(std::integral_constant<int, 64>{});
 }
 
 hipError_t launch_generic_partials(const Params& p, bool is_bf16, int rows, hipStream_t s) {
@@ -965,16 +1041,40 @@ hipError_t launch_generic_partials(const Params& p, bool is_bf16, int rows, hipS
   return hipGetLastError();
 }
 
+// Which form merges, by rows, splits and rank (us of a launch, captured, 32 q heads over 8 of 128; T: four rows per wave, W: one
+// row per wave, R: one per workgroup):
+//   rows   r 16, 5 splits   r 16, 16 splits   r 32, 5 splits   r 32, 16 splits   r 64, 5 splits   r 64, 16 splits
+//          R    W    T      R    W    T       R    W    T      R    W    T       R    T           R    T
+//   512    3.6  3.9  5.9    3.5  4.3  7.4     3.7  4.8  6.8    3.7  5.2  8.2     4.3  8.6         4.2  10.0
+//   1792   4.9  4.5  6.0    4.9  5.1  7.5     5.4  5.6  6.8    5.5  6.3  8.4     6.7  8.7         6.7  10.2
+//   3072   6.3  5.2  6.1    6.4  5.9  7.7     7.3  6.7  7.0    7.5  7.8  9.3     9.1  8.8         10.1 14.0
+//   6144   9.9  6.9  7.1    11.1 11.0 13.3    11.5 9.6  8.1    12.5 13.3 15.1    15.1 11.1        16.3 19.0
+//   10240  14.6 9.3  9.3    16.0 16.3 18.8    17.2 13.6 10.8   18.2 18.9 21.4    23.2 15.3        23.8 26.9
+// W reads no further than a row's last share with a key, the others read every slot: with a third of 32 shares live, 3072 rows,
+// 11.3 (R) and 6.4 (W) at rank 16, 12.5 and 8.2 at rank 32.  So a batch, whose sequences may leave shares empty, takes W wherever the
+// two come near each other, and a prefill, whose shares are all live, R.
+enum class MergeForm { kColumns, kRows, kWave, kTokens };
+static MergeForm merge_form(const Params& p, bool is_bf16, int rows) {
+  const int r = p.rank, ns = p.n_splits;
+  // (statistics in one wave's lanes, the query index in the grid's z)
+  if (ns > 64 || (p.head_dim != 64 && p.head_dim != 128) || rows / p.n_q_heads > 65535) return MergeForm::kColumns;
+  if (r % 4 != 0) return rows >= 1024 ? MergeForm::kWave : MergeForm::kColumns;
+  if (rows < (r <= 16 || (r <= 32 && !p.is_prefill && ns > 16) ? 1024 : 2560)) return MergeForm::kRows;
+  if (p.is_prefill) {
+    if (is_bf16 && ns <= 10 && (r > 32 || (r > 16 && rows >= 5120)) && (static_cast<int64_t>(p.n_new) * p.group + 15) / 16 <= 65535)
+      return MergeForm::kTokens;
+    if (r > 32 || (ns > 8 && rows < 2560)) return MergeForm::kRows;
+  }
+  return MergeForm::kWave;
+}
+
 template <typename T>
-static void launch_merge_t(const Params& p, int rows, hipStream_t s) {
-  if (launch_merge_wave<T>(p, rows, s)) return;
-  if (p.rank % 4 == 0 && p.n_splits <= 64 && (p.head_dim == 64 || p.head_dim == 128) && rows / p.n_q_heads <= 65535) {
-    // (kv head, q head of the group, query): workgroups go round-robin over the XCDs, so with 8 kv heads
-    // the rows of a head are merged on one XCD
-    const dim3 grid(p.n_kv_heads, p.group, rows / p.n_q_heads);
-    if (p.head_dim == 128) hipLaunchKernelGGL((merge_rows_kernel<T, 128>), grid, dim3(256), 0, s, p);
-    else hipLaunchKernelGGL((merge_rows_kernel<T, 64>), grid, dim3(256), 0, s, p);
-    return;
+static void launch_merge_t(const Params& p, bool is_bf16, int rows, hipStream_t s) {
+  switch (merge_form(p, is_bf16, rows)) {
+    case MergeForm::kRows: return launch_merge_rows<T>(p, rows, s);
+    case MergeForm::kWave: return launch_merge_wave<T>(p, rows, s);
+    case MergeForm::kTokens: return launch_merge_tokens(p, s);
+    case MergeForm::kColumns: break;
   }
   // enough 128-thread groups that one pass of kMergeUnroll splits per thread covers the splits
   const int groups = (p.n_splits + kMergeUnroll - 1) / kMergeUnroll;
@@ -990,11 +1090,10 @@ static void launch_merge_t(const Params& p, int rows, hipStream_t s) {
 }
 
 hipError_t launch_merge(const Params& p, bool is_bf16, int rows, hipStream_t s) {
-  if (is_bf16 && launch_merge_tokens(p, rows, s)) return hipGetLastError();
   if (is_bf16)
-    launch_merge_t<bf16_t>(p, rows, s);
+    launch_merge_t<bf16_t>(p, true, rows, s);
   else
-    launch_merge_t<float>(p, rows, s);
+    launch_merge_t<float>(p, false, rows, s);
   return hipGetLastError();
 }
 
