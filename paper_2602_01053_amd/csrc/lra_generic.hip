@@ -62,24 +62,100 @@ __device__ __forceinline__ void unpack_piece(uint4 v, float (&x)[E]) {
   }
 }
 
-// One workgroup of four waves per (query row, share of the keys), 64 keys per step.  Calls of this kernel (fp32, odd
-// ranks) cost round trips, not bytes, so a step is one round of requests: four lanes share a K row (16-byte pieces
-// dealt round robin) and reduce by two exchanges, a thread takes a column piece of V for PK keys and an eighth to a
-// sixteenth of the keys.  The K and L rows of a step are requested under the sums of the one before, its V rows as
-// soon as those of the one before are used up, so that three workgroups fit the registers of a compute unit (fp32,
-// d = 128: 168; with V a whole step ahead 216 and two).  One wave per share, one key per lane and a load per
-// dot-product step, takes a round trip per step instead: two agents on 512 keys in fp32 17.6 us per call, 9.8 us so;
-// 1024 new tokens in fp32 at 32 heads of 128 1602 us, 1562 us so.  Every wave forms the softmax of the 64 scores by
-// itself (lane = key), which leaves one barrier between the scores and the sums.
+// Lane exchanges on the vector unit: an LDS permute (__shfl) costs its round trip through LDS at every step of a chain.
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
+}
+template <typename F>
+__device__ __forceinline__ float over_16_lanes(float v, F op) {
+  v = op(v, dpp_f32<0x128>(v));  // row_ror:8, 4, 2, 1
+  v = op(v, dpp_f32<0x124>(v));
+  v = op(v, dpp_f32<0x122>(v));
+  return op(v, dpp_f32<0x121>(v));
+}
+__device__ __forceinline__ float from_lane(float v, int lane) {  // (lane: uniform)
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+}
+// op over the first N lanes' rows of sixteen (N = 16, 32 or 64), in every lane
+template <int N, typename F>
+__device__ __forceinline__ float over_lanes(float v, F op) {
+  v = over_16_lanes(v, op);
+  float x = from_lane(v, 0);
+#pragma unroll
+  for (int i = 16; i < N; i += 16) x = op(x, from_lane(v, i));
+  return x;
+}
+
+// sum over a quad of lanes, in each of them
+__device__ __forceinline__ float sum_quad(float v) {
+  v += dpp_f32<0xb1>(v);         // quad_perm [1,0,3,2]
+  return v + dpp_f32<0x4e>(v);   // quad_perm [2,3,0,1]
+}
+
+// kv_offset / l_offset with the layout known
+template <bool PAGED>
+__device__ __forceinline__ int64_t kv_row(const Params& p, int t, int j, int h) {
+  if constexpr (PAGED) {
+    const int blk = p.block_table[static_cast<int64_t>(t) * p.max_blocks_per_seq + (j >> 4)];
+    return static_cast<int64_t>(blk) * p.kv_block_stride + static_cast<int64_t>(h) * p.kv_head_stride +
+           static_cast<int64_t>(j & 15) * p.kv_token_stride;
+  } else {
+    return static_cast<int64_t>(j) * p.kv_token_stride + static_cast<int64_t>(h) * p.kv_head_stride;
+  }
+}
+template <bool PAGED>
+__device__ __forceinline__ int64_t l_row(const Params& p, int t, int j, int a) {
+  const int64_t base = static_cast<int64_t>(a) * p.l_adapter_stride;
+  if constexpr (PAGED) {
+    const int blk = p.block_table[static_cast<int64_t>(t) * p.max_blocks_per_seq + (j >> 4)];
+    return base + (static_cast<int64_t>(blk) * 16 + (j & 15)) * p.l_row_stride;
+  } else {
+    return base + static_cast<int64_t>(j) * p.l_row_stride;
+  }
+}
+
+// idx / n for rows of any plan: below 2^23 (and n of at most 4096 heads) a short division
+__device__ __forceinline__ int row_div(int idx, int n) {
+  if (__builtin_expect(idx >= (1 << 23), 0)) return idx / n;
+  return static_cast<int>((static_cast<uint32_t>(idx) & 0x7fffffu) / (static_cast<uint32_t>(n) & 0x1fffu));
+}
+
+// (a grid dimension holds fewer than 2^32 threads: rows beyond 2^23 go on in z)
+constexpr int kGenericRowBits = 23;
+
+// One workgroup of four waves per (query row, share of the keys), 64 keys per step, sixteen to a wave.  Calls of this
+// kernel (fp32, odd ranks) cost round trips and chains of instructions, not bytes.  A wave is on its own from the first
+// key to the last: four lanes share a K row (16-byte pieces dealt round robin) and add up by DPP, the wave keeps its own
+// softmax reference, a lane sums a column piece of V over every KGW-th of the wave's keys and the ranks of its own L
+// pieces over its own key, and only behind the last step do lanes, then waves (in LDS, one barrier) meet.  One barrier
+// before the loop hands Qt = q B_K^T round.  The K and L rows of a step are requested under the sums of the one before,
+// its V rows as soon as those of the one before are used up, so that three workgroups fit the registers of a compute unit.
+// Parameter block, adapter id and length come in one round trip each, the layout and the rank's bound are template
+// arguments (13 KB of code otherwise, of which a small call executes a third).  With scores, weights and L rows through LDS
+// (two barriers a step, 18 dependent LDS permutes) two agents on 512 fp32 keys took 6.23 us in this kernel, 3.82 so; 1024 new
+// fp32 tokens at 32 heads of 128 1353, 739; 8192 fp32 keys, 4 agents, 91, 59; 700 new bf16 tokens of rank 12 578, 294.
 // K and V rows are 16-byte aligned (bases and strides are checked); L rows of a rank that is no multiple of four
-// are not, and go through LDS element by element.
-template <typename T, int D>
-__global__ __launch_bounds__(256, sizeof(T) == 4 || D == 64 ? 3 : 1) void generic_partial_kernel(Params p) {
+// are not, and are read element by element.
+template <typename T, int D, bool PAGED, int RB>
+__global__ __launch_bounds__(256, 3) void generic_partial_kernel(Params p) {
   constexpr int E = 16 / static_cast<int>(sizeof(T));  // elements per piece
   constexpr int CG = D / E;                            // pieces per row
-  constexpr int PK = CG / 4;                           // pieces of a K row per thread; V rows per thread and step
-  constexpr int KG = 256 / CG;                         // key groups of the V sums
-  constexpr bool LANE_SUMS = sizeof(T) == 2;
+  constexpr int PK = CG / 4;                           // pieces of a K row per lane; V rows per lane and step
+  constexpr int KGW = 64 / CG;                         // V rows of one request of a wave
+  constexpr bool Q_IN_REGS = D == 64;
+  constexpr bool L_EARLY = RB == 16;  // (L rows of a step under the sums of the one before; at higher ranks behind them, for the registers)
+  constexpr int LN = RB / 4;  // L elements per lane
+  // (the large forms: the scheduler kept to one part at a time, or it asks for more registers than three workgroups leave)
+  auto part_end = []() __attribute__((always_inline)) {
+    if constexpr (RB > 16 && D == 128) __builtin_amdgcn_sched_barrier(0);
+  };
+  // the parameter block in one round trip (left alone the compiler fetches it piece by piece behind each use)
+  asm volatile("" ::"s"(p.q), "s"(p.k_base), "s"(p.v_base), "s"(p.l), "s"(p.b_k), "s"(p.seq_lens), "s"(p.query_adapter));
+  asm volatile("" ::"s"(p.kv_token_stride), "s"(p.kv_head_stride), "s"(p.l_row_stride), "s"(p.l_adapter_stride), "s"(p.part_ml), "s"(p.part_o),
+               "s"(p.part_lr), "s"(p.part_adapter));
+  asm volatile("" ::"s"(p.n_q_heads), "s"(p.n_kv_heads), "s"(p.group), "s"(p.rank), "s"(p.max_seq_len), "s"(p.n_seqs), "s"(p.n_queries),
+               "s"(p.n_adapters), "s"(p.n_new), "s"(p.is_prefill), "s"(p.split_keys), "s"(p.n_splits), "s"(p.scale));
   const int split = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -87,158 +163,236 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 || D == 64 ? 3 : 1) void generi
   // workgroup -> row: the kv head runs fastest, so that with 8 kv heads an XCD takes the rows of one (200 new tokens
   // on 1200 fp32 keys: 1206 -> 966 us); the longest rows of a prefill come first, so that no long one is left for
   // the end (1024 new tokens, bf16, rank 12: 1140 -> 1103 us)
-  const int idx = static_cast<int>(blockIdx.z) * static_cast<int>(gridDim.x) + static_cast<int>(blockIdx.x);
+  const int idx = (static_cast<int>(blockIdx.z) << kGenericRowBits) + static_cast<int>(blockIdx.x);
   if (idx >= (p.is_prefill ? p.n_new : p.n_queries) * Hq) return;
-  const int rest = idx / p.n_kv_heads, h = idx - rest * p.n_kv_heads;
-  const int tok_up = rest / p.group, tok = p.is_prefill ? p.n_new - 1 - tok_up : tok_up;
+  const int rest = row_div(idx, p.n_kv_heads), h = idx - rest * p.n_kv_heads;
+  const int tok_up = row_div(rest, p.group), tok = p.is_prefill ? p.n_new - 1 - tok_up : tok_up;
   const int row = tok * Hq + h * p.group + (rest - tok_up * p.group);
 
+  // (scalar loads, both requested before either is waited for)
   int t, a, n_vis;
   if (p.is_prefill) {
     t = p.seq_index;
     a = p.adapter_index;
-    const int n_t = min(p.seq_lens[t], p.max_seq_len);
-    n_vis = n_t - p.n_new + tok + 1;
+    n_vis = min(CONST_I32(p.seq_lens)[t], p.max_seq_len) - p.n_new + tok + 1;
   } else {
-    t = sequence_of_query(p, tok);
-    a = min(max(p.query_adapter[tok], 0), p.n_adapters - 1);  // ids are device data: kept inside the table
-    n_vis = min(p.seq_lens[t], p.max_seq_len);
+    t = p.n_seqs > 1 ? sequence_of_query(p, tok) : 0;
+    const int a_raw = CONST_I32(p.query_adapter)[tok], n_t = CONST_I32(p.seq_lens)[t];
+    a = min(max(a_raw, 0), p.n_adapters - 1);  // ids are device data: kept inside the table
+    n_vis = min(n_t, p.max_seq_len);
   }
+  const int64_t slot = static_cast<int64_t>(row) * p.n_splits + split;
   const int j0 = split * p.split_keys;
   const int j1 = min(j0 + p.split_keys, n_vis);
+  if (j0 >= j1) {  // nothing visible: (-inf, 0), rows that the merge does not read
+    if (tid == 0) {
+      p.part_ml[slot * 2 + 0] = -INFINITY;
+      p.part_ml[slot * 2 + 1] = 0.f;
+      if (split == 0) p.part_adapter[row] = a;
+    }
+    return;
+  }
 
-  __shared__ float q_s[D];
+  __shared__ __align__(16) T q_s[Q_IN_REGS ? 1 : D];
   __shared__ float qt_s[64];
-  __shared__ float s_s[64];
-  __shared__ float l_s[64 * 65];  // [key of the step][rho], rows padded to 65 floats
-  __shared__ float o_s[KG * D];
-  __shared__ float olr_s[4 * 64];
+  __shared__ __align__(16) float o_s[4][D];
+  __shared__ float olr_s[4][64];
+  __shared__ float m_s[4], ell_s[4];
 
   const T* kb = static_cast<const T*>(p.k_base);
   const T* vb = static_cast<const T*>(p.v_base);
   const T* lr = static_cast<const T*>(p.l);
-  const int quarter = tid & 3, key_k = tid >> 2;  // score part: this thread's K row of the step, and its quarter
-  const int cg = tid % CG, kg = tid / CG;         // sum part: column piece, first of its keys (kg, kg + KG, ...)
+  const int quarter = lane & 3, key_k = 16 * wave + (lane >> 2);  // score part: this lane's K row of the step, and its quarter
+  const int cg = lane % CG, kg = lane / CG;                       // sum part: column piece, first of the wave's keys (kg, kg + KGW, ...)
 
   uint4 kp[PK], vp[PK];
-  T lv[16];
+  T lv[LN];
   // (rows past the end: the last one again, weighted zero)
   auto request_v = [&](int jb) __attribute__((always_inline)) {
+    int jk = jb + 16 * wave + kg;
+    if constexpr (RB > 16) asm volatile("" : "+v"(jk));  // (row numbers formed again in each step, not held in registers)
 #pragma unroll
     for (int i = 0; i < PK; ++i)
-      vp[i] = reinterpret_cast<const uint4*>(vb + kv_offset(p, t, min(jb + kg + KG * i, j1 - 1), h))[cg];
+      vp[i] = reinterpret_cast<const uint4*>(vb + kv_row<PAGED>(p, t, min(jk + KGW * i, j1 - 1), h))[cg];
   };
-  auto request = [&](int jb) __attribute__((always_inline)) {
-    const uint4* krow = reinterpret_cast<const uint4*>(kb + kv_offset(p, t, min(jb + key_k, j1 - 1), h));
+  auto request_k = [&](int jb) __attribute__((always_inline)) {
+    const uint4* krow = reinterpret_cast<const uint4*>(kb + kv_row<PAGED>(p, t, min(jb + key_k, j1 - 1), h));
 #pragma unroll
     for (int i = 0; i < PK; ++i) kp[i] = krow[quarter + 4 * i];
-    const T* lrow = lr + l_offset(p, t, min(jb + key_k, j1 - 1), a);
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-      if (4 * i < r) lv[i] = lrow[min(4 * i + quarter, r - 1)];  // (uniform)
   };
-  if (j0 < j1) {
-    request(j0);
-    request_v(j0);
-  }
-
-  const T* q = static_cast<const T*>(p.q) + static_cast<int64_t>(row) * D;
-  uint4 bp[PK];
-  const bool has_bk = p.b_k != nullptr;
-  if (has_bk) {  // row key_k of B_K for this kv head, a quarter of it
-    const uint4* brow = reinterpret_cast<const uint4*>(static_cast<const T*>(p.b_k) +
-        (static_cast<int64_t>(a) * r + min(key_k, r - 1)) * (static_cast<int64_t>(p.n_kv_heads) * D) + h * D);
+  auto request_l = [&](int jb) __attribute__((always_inline)) {
+    const T* lrow = lr + l_row<PAGED>(p, t, min(jb + key_k, j1 - 1), a);
+    int q4 = quarter;
+    if constexpr (!L_EARLY) asm volatile("" : "+v"(q4));  // (sixteen offsets formed again in each step, not held in registers)
 #pragma unroll
-    for (int i = 0; i < PK; ++i) bp[i] = brow[quarter + 4 * i];
+    for (int i = 0; i < LN; ++i) {
+      lv[i] = lrow[min(4 * i + q4, r - 1)];  // (ranks beyond the last: zeroed below)
+      if ((i & 3) == 3) part_end();
+    }
+  };
+  const uint4* qrow = reinterpret_cast<const uint4*>(static_cast<const T*>(p.q) + static_cast<int64_t>(row) * D);
+  uint4 qp[PK];
+#pragma unroll
+  for (int i = 0; i < PK; ++i) qp[i] = qrow[quarter + 4 * i];
+  uint4 bp[PK];
+  request_k(j0);
+  part_end();
+  request_l(j0);
+  // row key_k of B_K for this kv head, a quarter of it (without a key-side adapter: q again, times zero below)
+  const bool has_bk = p.b_k != nullptr;
+  {
+    const T* base = has_bk ? static_cast<const T*>(p.b_k) + (static_cast<int64_t>(a) * r * p.n_kv_heads + h) * D : reinterpret_cast<const T*>(qrow);
+    int64_t ld = has_bk ? static_cast<int64_t>(p.n_kv_heads) * D : 0;
+    asm volatile("" : "+s"(base), "+s"(ld));  // (otherwise the loads of the two cases are told apart, under a branch and with waits)
+    const auto* brow = (const __attribute__((address_space(1))) u32x4*)(base + min(key_k, r - 1) * ld);
+#pragma unroll
+    for (int i = 0; i < PK; ++i) bp[i] = __builtin_bit_cast(uint4, u32x4(brow[quarter + 4 * i]));
   }
-  if (tid < D) q_s[tid] = to_f32<T>(q[tid]);
-  __syncthreads();
-  auto dot_pieces = [&](const uint4 (&pc)[PK]) __attribute__((always_inline)) -> float {
+  request_v(j0);
+  part_end();
+  auto dot_pieces = [&](const uint4 (&pc)[PK], auto q_piece) __attribute__((always_inline)) -> float {
     float acc = 0.f;
 #pragma unroll
     for (int i = 0; i < PK; ++i) {
-      float x[E];
+      float x[E], y[E];
       unpack_piece<T, E>(pc[i], x);
+      unpack_piece<T, E>(q_piece(i), y);
 #pragma unroll
-      for (int e = 0; e < E; ++e) acc = fmaf(x[e], q_s[(quarter + 4 * i) * E + e], acc);
+      for (int e = 0; e < E; ++e) acc = fmaf(x[e], y[e], acc);
+      if ((i & 3) == 3) part_end();
     }
     return acc;
   };
-  auto sum4 = [&](float v) __attribute__((always_inline)) -> float {
-    v += __shfl_xor(v, 1, kWave);
-    return v + __shfl_xor(v, 2, kWave);
-  };
+  if constexpr (!Q_IN_REGS) {
+    if (tid < 4) {
+#pragma unroll
+      for (int i = 0; i < PK; ++i) reinterpret_cast<uint4*>(q_s)[quarter + 4 * i] = qp[i];
+    }
+  }
   {
-    const float qt = has_bk ? sum4(dot_pieces(bp)) : 0.f;
-    if (quarter == 0) qt_s[key_k] = key_k < r ? qt : 0.f;
+    const float qt = sum_quad(dot_pieces(bp, [&](int i) { return qp[i]; }));
+    if (quarter == 0) qt_s[key_k] = has_bk && key_k < r ? qt : 0.f;
   }
   __syncthreads();
 
-  float m = -INFINITY, ell = 0.f, olr = 0.f, o[E];
+  float m = -INFINITY, ell = 0.f, o[E], olr[LN];  // (ell, o, olr: this lane's part)
 #pragma unroll
   for (int e = 0; e < E; ++e) o[e] = 0.f;
-  for (int jb = j0; jb < j1; jb += kWave) {
-    const int cnt = min(kWave, j1 - jb);
-    float part = dot_pieces(kp);
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
-      if (4 * i < r) {  // (uniform)
-        const int rho = 4 * i + quarter;
-        const float x = rho < r && key_k < cnt ? to_f32<T>(lv[i]) : 0.f;
-        l_s[key_k * 65 + rho] = x;
-        part = fmaf(x, qt_s[rho], part);
-      }
-    part = p.scale * sum4(part);
-    if (quarter == 0) s_s[key_k] = key_k < cnt ? part : -INFINITY;
-    __syncthreads();
-    if (jb + kWave < j1) request(jb + kWave);
-    const float s = s_s[lane];
-    const float m_new = fmaxf(m, wave_max(s));  // finite: key 0 of the step is always valid
+  for (int i = 0; i < LN; ++i) olr[i] = 0.f;
+  for (int jb = j0; jb < j1; jb += kWave) {
+    const int cnt = j1 - jb - 16 * wave;  // this wave's keys of the step (sixteen and more: all)
+    if (cnt <= 0) break;
+    const bool mine = (lane >> 2) < cnt;
+    int q4 = quarter;
+    if constexpr (RB > 16) asm volatile("" : "+v"(q4));  // (q and Qt read from LDS in each step, not held in registers)
+    float part = dot_pieces(kp, [&](int i) {
+      if constexpr (Q_IN_REGS) return qp[i];
+      else return reinterpret_cast<const uint4*>(q_s)[q4 + 4 * i];
+    });
+    T x[LN];  // this lane's L elements, zero past the end and past the rank (the next rows take lv under the sums)
+#pragma unroll
+    for (int i = 0; i < LN; ++i) {
+      if (!(4 * i + q4 < r && mine)) lv[i] = T(0);
+      if constexpr (L_EARLY) x[i] = lv[i];
+      part = fmaf(to_f32<T>(lv[i]), qt_s[4 * i + q4], part);
+    }
+    part = p.scale * sum_quad(part);
+    asm volatile("" : "+v"(part));  // (or the whole product moves under a branch on the lanes whose key exists)
+    part_end();
+    const float s = mine ? part : -INFINITY;
+    const bool more = jb + kWave < j1;
+    if (more) request_k(jb + kWave);
+    if (more && L_EARLY) request_l(jb + kWave);
+    part_end();
+    const float m_new = fmaxf(m, over_lanes<64>(s, [](float u, float v) { return fmaxf(u, v); }));  // finite: the wave's first key is valid
     const float alpha = (m == -INFINITY) ? 0.f : expf(m - m_new);
-    const float pj = lane < cnt ? expf(s - m_new) : 0.f;
-    // (bf16: the sum of this lane's keys, added up after the last step; in fp32 it is the register too many)
-    ell = fmaf(alpha, ell, LANE_SUMS ? pj : wave_sum(pj));
-    olr *= alpha;
+    const float pj = expf(s - m_new);  // (past the end: zero)
+    ell = fmaf(alpha, ell, quarter == 0 ? pj : 0.f);
 #pragma unroll
     for (int e = 0; e < E; ++e) o[e] *= alpha;
+    if (cnt < 16) {  // (a row requested again stays out of the sums, whatever it holds)
+#pragma unroll
+      for (int i = 0; i < PK; ++i)
+        if (kg >= cnt - KGW * i) vp[i] = make_uint4(0u, 0u, 0u, 0u);
+    }
 #pragma unroll
     for (int i = 0; i < PK; ++i) {
-      const int key = kg + KG * i;
-      const float pk = __shfl(pj, key, kWave);
-      if (key < cnt) {
-        float x[E];
-        unpack_piece<T, E>(vp[i], x);
+      const float pk = __shfl(pj, 4 * (kg + KGW * i), kWave);
+      float v[E];
+      unpack_piece<T, E>(vp[i], v);
 #pragma unroll
-        for (int e = 0; e < E; ++e) o[e] = fmaf(pk, x[e], o[e]);
-      }
+      for (int e = 0; e < E; ++e) o[e] = fmaf(pk, v[e], o[e]);
     }
-    if (jb + kWave < j1) request_v(jb + kWave);
-    // O_lr: lane = rho, wave w the keys 16 w .. 16 w + 15
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const float pk = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, pj), 16 * wave + i));
-      if (lane < r) olr = fmaf(pk, l_s[(16 * wave + i) * 65 + lane], olr);
-    }
+    for (int e = 0; e < E; ++e) asm volatile("" : "+v"(o[e]));  // (or the sums sink behind the requests, with a copy of every row)
+    part_end();
+    if (more) request_v(jb + kWave);
+    part_end();
+#pragma unroll
+    for (int i = 0; i < LN; ++i) olr[i] = fmaf(alpha, olr[i], pj * to_f32<T>(L_EARLY ? x[i] : lv[i]));
+    if (more && !L_EARLY) request_l(jb + kWave);
+    part_end();
     m = m_new;
-    __syncthreads();  // before the next step overwrites the scores and the L rows
   }
 
+  // ---- lanes of a wave, then the waves ----
+  auto over_rows = [&](float v) __attribute__((always_inline)) -> float {  // over the lanes with the same index mod 16
+    return sum_over_lane_groups(v);
+  };
 #pragma unroll
-  for (int e = 0; e < E; ++e) o_s[kg * D + cg * E + e] = o[e];
-  olr_s[wave * 64 + lane] = olr;
-  if (LANE_SUMS) ell = wave_sum(ell);
+  for (int e = 0; e < E; ++e) {
+    if constexpr (CG == 8) o[e] += dpp_f32<0x128>(o[e]);  // row_ror:8
+    if constexpr (CG <= 16) o[e] = over_rows(o[e]);
+    else {
+      float other = o[e];
+      permlane32_swap(o[e], other);
+      o[e] += other;
+    }
+  }
+  part_end();
+  if (lane < CG) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) o_s[wave][cg * E + e] = o[e];
+  }
+#pragma unroll
+  for (int i = 0; i < LN; ++i)
+    if (RB == 16 || 4 * i < r) {  // (uniform)
+      float v = olr[i];
+      v += dpp_f32<0x124>(v);  // row_ror:4, 8: the keys of a row of sixteen lanes
+      v += dpp_f32<0x128>(v);
+      v = over_rows(v);
+      if (lane < 4) olr_s[wave][4 * i + lane] = v;
+    }
+  ell = over_lanes<64>(ell, [](float u, float v) { return u + v; });
+  if (lane == 0) {
+    m_s[wave] = m;
+    ell_s[wave] = ell;
+  }
   __syncthreads();
-  const int64_t slot = static_cast<int64_t>(row) * p.n_splits + split;
+  const float m_all = fmaxf(fmaxf(m_s[0], m_s[1]), fmaxf(m_s[2], m_s[3]));
+  float f[4];
+#pragma unroll
+  for (int w = 0; w < 4; ++w) f[w] = m_s[w] == -INFINITY ? 0.f : expf(m_s[w] - m_all);
   if (tid < D) {
     float v = 0.f;
 #pragma unroll
-    for (int k = 0; k < KG; ++k) v += o_s[k * D + tid];
+    for (int w = 0; w < 4; ++w) v = fmaf(f[w], o_s[w][tid], v);
     p.part_o[slot * D + tid] = v;
   }
-  if (tid < r) p.part_lr[slot * r + tid] = (olr_s[tid] + olr_s[64 + tid]) + (olr_s[128 + tid] + olr_s[192 + tid]);
-  if (tid == 0) {
-    p.part_ml[slot * 2 + 0] = m;  // a split past the row's last visible key leaves (-inf, 0)
-    p.part_ml[slot * 2 + 1] = ell;
+  const int rho = tid - (256 - 64);  // (the last wave, which has no columns at d = 128)
+  if (rho >= 0 && rho < r) {
+    float v = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) v = fmaf(f[w], olr_s[w][rho], v);
+    p.part_lr[slot * r + rho] = v;
+  }
+  if (tid == 128) {
+    float l_all = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) l_all = fmaf(f[w], ell_s[w], l_all);
+    p.part_ml[slot * 2 + 0] = m_all;
+    p.part_ml[slot * 2 + 1] = l_all;
     if (split == 0) p.part_adapter[row] = a;
   }
 }
@@ -522,31 +676,6 @@ __global__ __launch_bounds__(128 * kMergeGroups) void merge_kernel(Params p) {
     for (int i_ = 0; i_ < 6; ++i_) o_[i_] = mt[i_];
   }
 #endif
-}
-
-// Lane exchanges on the vector unit: an LDS permute (__shfl) costs its round trip through LDS at every step of a chain.
-template <int CTRL>
-__device__ __forceinline__ float dpp_f32(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
-}
-template <typename F>
-__device__ __forceinline__ float over_16_lanes(float v, F op) {
-  v = op(v, dpp_f32<0x128>(v));  // row_ror:8, 4, 2, 1
-  v = op(v, dpp_f32<0x124>(v));
-  v = op(v, dpp_f32<0x122>(v));
-  return op(v, dpp_f32<0x121>(v));
-}
-__device__ __forceinline__ float from_lane(float v, int lane) {  // (lane: uniform)
-  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
-}
-// op over the first N lanes' rows of sixteen (N = 16, 32 or 64), in every lane
-template <int N, typename F>
-__device__ __forceinline__ float over_lanes(float v, F op) {
-  v = over_16_lanes(v, op);
-  float x = from_lane(v, 0);
-#pragma unroll
-  for (int i = 16; i < N; i += 16) x = op(x, from_lane(v, i));
-  return x;
 }
 
 // The same merge for the common case (head dimension 64 or 128, rank a multiple of 4, at most 64 splits): one workgroup
@@ -1028,16 +1157,25 @@ hipError_t launch_generic_partials(const Params& p, bool is_bf16, int rows, hipS
     else hipLaunchKernelGGL(generic_partial_rope_kernel<float>, grid, block, 0, s, p);
     return hipGetLastError();
   }
-  // (a grid dimension holds fewer than 2^32 threads: rows beyond 2^23 go on in z)
-  const int x = rows < (1 << 23) ? rows : (1 << 23);
+  const int x = rows < (1 << kGenericRowBits) ? rows : (1 << kGenericRowBits);
   const dim3 rgrid(x, p.n_splits, (rows + x - 1) / x);
-  if (p.head_dim == 128) {
-    if (is_bf16) hipLaunchKernelGGL((generic_partial_kernel<bf16_t, 128>), rgrid, dim3(256), 0, s, p);
-    else hipLaunchKernelGGL((generic_partial_kernel<float, 128>), rgrid, dim3(256), 0, s, p);
-  } else {
-    if (is_bf16) hipLaunchKernelGGL((generic_partial_kernel<bf16_t, 64>), rgrid, dim3(256), 0, s, p);
-    else hipLaunchKernelGGL((generic_partial_kernel<float, 64>), rgrid, dim3(256), 0, s, p);
-  }
+  auto launch = [&](auto paged_c, auto rb_c) {
+    constexpr bool PAGED = decltype(paged_c)::value;
+    constexpr int RB = decltype(rb_c)::value;
+    if (p.head_dim == 128) {
+      if (is_bf16) hipLaunchKernelGGL((generic_partial_kernel<bf16_t, 128, PAGED, RB>), rgrid, dim3(256), 0, s, p);
+      else hipLaunchKernelGGL((generic_partial_kernel<float, 128, PAGED, RB>), rgrid, dim3(256), 0, s, p);
+    } else {
+      if (is_bf16) hipLaunchKernelGGL((generic_partial_kernel<bf16_t, 64, PAGED, RB>), rgrid, dim3(256), 0, s, p);
+      else hipLaunchKernelGGL((generic_partial_kernel<float, 64, PAGED, RB>), rgrid, dim3(256), 0, s, p);
+    }
+  };
+  auto by_rank = [&](auto paged_c) {
+    if (p.rank <= 16) launch(paged_c, std::integral_constant<int, 16>{});
+    else launch(paged_c, std::integral_constant<int, 64>{});
+  };
+  if (p.block_size != 0) by_rank(std::true_type{});
+  else by_rank(std::false_type{});
   return hipGetLastError();
 }
 
