@@ -1,4 +1,5 @@
-"""Thin ctypes binding over liblra_attn.so: argument marshalling only.
+"""Thin binding over liblra_attn.so (ctypes; the three per-layer entry points through a CPython module of
+their own, csrc/lra_pycall.cpp): argument marshalling only.
 
 Every step of the attention path runs inside the library's HIP kernels.  There is
 no CPU or PyTorch fallback: if the shared library is missing the first call
@@ -12,7 +13,7 @@ from typing import Optional
 
 import torch
 
-from .build import LIB_PATH
+from .build import LIB_PATH, PYCALL_PATH
 
 LRA_OK = 0
 LRA_BF16, LRA_F32 = 0, 1
@@ -71,11 +72,18 @@ class LraError(RuntimeError):
 
 
 _lib = None
+_calls = None   # the CPython module, bound to _lib
+
+
+# The raw handle of the current stream, without the Stream object torch.cuda.current_stream() builds around it: a
+# call's time on the host is what a decode step of a short context waits for (see lra_attn_decode).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda device: torch.cuda.current_stream().cuda_stream)
+_current_device = getattr(torch._C, "_cuda_getDevice", None) or (lambda: 0)
 
 
 def load_library() -> ctypes.CDLL:
     """dlopen the in-tree library.  Raises if it has not been built."""
-    global _lib
+    global _lib, _calls
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -104,8 +112,19 @@ def load_library() -> ctypes.CDLL:
     lib.lra_probe_stream_read.argtypes = [vp, ctypes.c_size_t, vp, vp]
     lib.lra_probe_mfma_bf16.restype = ctypes.c_int
     lib.lra_probe_mfma_bf16.argtypes = [i32, i32, ctypes.POINTER(ctypes.c_int64), vp, vp]
+    if not os.path.exists(PYCALL_PATH):
+        raise RuntimeError(f"{PYCALL_PATH} is missing: build it with `python -m paper_2602_01053_amd.build`")
+    from . import _lra_pycall
+    entry = [ctypes.cast(f, vp).value for f in (lib.lra_attn_decode, lib.lra_attn_prefill, lib.lra_cache_append)]
+    _lra_pycall.bind(*entry, ctypes.addressof(_tuning), LraShape, LraCache, _current_device, _raw_stream, torch.cuda.is_initialized)
+    _calls = _lra_pycall
     _lib = lib
     return lib
+
+
+def _entry_points():
+    load_library()
+    return _calls
 
 
 def lra_status_string(status: int) -> str:
@@ -119,12 +138,7 @@ def lra_cache_append(shape: LraShape, cache: LraCache, w: torch.Tensor, rope_the
     (optional, lra_append_workspace_bytes bytes) lets mid-sized chunks split d_model over the chip."""
     if not (x.is_contiguous() and w.is_contiguous()) or x.size(1) != w.size(1):
         raise LraError(2, "x and w must be dense and share d_model")
-    proj = LraProjection(w.data_ptr(), w.size(1), float(rope_theta))
-    ws_ptr, ws_bytes = (None, 0) if workspace is None else (workspace.data_ptr(), workspace.nbytes)
-    byref = ctypes.byref
-    status = (_lib or load_library()).lra_cache_append(
-        byref(shape), byref(cache), byref(proj), _ptr(x), int(seq_index), x.size(0), ws_ptr, ws_bytes, _tuning_ref,
-        _stream_ptr(stream))
+    status = (_calls or _entry_points()).append(shape, cache, w, float(rope_theta), x, seq_index, workspace, stream)
     if status:
         _check(status)
 
@@ -282,15 +296,9 @@ def lra_workspace_bytes(shape: LraShape, cache: LraCache, n_queries: int,
     return int(n)
 
 
-# The raw handle of the current stream, without the Stream object torch.cuda.current_stream() builds around it: a
-# call's time on the host is what a decode step of a short context waits for (see lra_attn_decode).
-_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-_current_device = getattr(torch._C, "_cuda_getDevice", None)
-
-
 def _stream_ptr(stream) -> Optional[int]:
     if stream is None:
-        if _raw_stream is not None and _current_device is not None and torch.cuda.is_initialized():
+        if torch.cuda.is_initialized():
             return _raw_stream(_current_device()) or None
         stream = torch.cuda.current_stream()
     return stream.cuda_stream or None
@@ -306,14 +314,10 @@ def lra_attn_decode(shape: LraShape, cache: LraCache, b_k: Optional[torch.Tensor
                     query_adapter: torch.Tensor, seq_query_start: torch.Tensor,
                     max_queries_per_seq: int, out: torch.Tensor, workspace: Optional[torch.Tensor],
                     stream=None) -> None:
-    # (marshalling is kept short: small calls issued one by one take as long on the host as on the GPU; a decode of a
-    # short context with two launches 10.0 us, with shape tuples, a stream object and the tuning reference made anew in each call 11.8)
-    ad = LraAdapters(_ptr(b_k), _ptr(b_v), int(n_adapters))
-    ws_ptr, ws_bytes = (None, 0) if workspace is None else (workspace.data_ptr(), workspace.nbytes)
-    byref = ctypes.byref
-    status = (_lib or load_library()).lra_attn_decode(
-        byref(shape), byref(cache), byref(ad), _ptr(q), _ptr(query_adapter), _ptr(seq_query_start), q.size(0),
-        int(max_queries_per_seq), _ptr(out), ws_ptr, ws_bytes, _tuning_ref, _stream_ptr(stream))
+    # (small calls issued one by one take as long on the host as on the GPU: a decode of a short context with two
+    # launches 6.9 us, 9.6 with ctypes arguments)
+    status = (_calls or _entry_points()).decode(shape, cache, b_k, b_v, n_adapters, q, query_adapter, seq_query_start,
+                                                max_queries_per_seq, out, workspace, stream)
     if status:
         _check(status)
 
@@ -334,11 +338,7 @@ def lra_attn_prefill(shape: LraShape, cache: LraCache, b_k: Optional[torch.Tenso
                      b_v: Optional[torch.Tensor], n_adapters: int, q: torch.Tensor, seq_index: int,
                      adapter_index: int, out: torch.Tensor, workspace: Optional[torch.Tensor],
                      stream=None) -> None:
-    ad = LraAdapters(_ptr(b_k), _ptr(b_v), int(n_adapters))
-    ws_ptr, ws_bytes = (None, 0) if workspace is None else (workspace.data_ptr(), workspace.nbytes)
-    byref = ctypes.byref
-    status = (_lib or load_library()).lra_attn_prefill(
-        byref(shape), byref(cache), byref(ad), _ptr(q), int(seq_index), int(adapter_index), q.size(0), _ptr(out),
-        ws_ptr, ws_bytes, _tuning_ref, _stream_ptr(stream))
+    status = (_calls or _entry_points()).prefill(shape, cache, b_k, b_v, n_adapters, q, seq_index, adapter_index, out, workspace,
+                                                 stream)
     if status:
         _check(status)

@@ -9,6 +9,8 @@ PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG_DIR)
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "liblra_attn.so")
+PYCALL_SOURCE = "lra_pycall.cpp"   # CPython module over the C ABI, on its own: it links neither the library nor torch
+PYCALL_PATH = os.path.join(PKG_DIR, "_lra_pycall.so")
 # what the compiler reports per kernel (registers, scratch, LDS, occupancy), written by every build
 RESOURCES_PATH = os.path.join(PKG_DIR, "kernel_resources.json")
 
@@ -84,7 +86,8 @@ def _run(cmd, verbose):
 
 
 def build_library(verbose: bool = False) -> str:
-    """Compile every source to an object file (in parallel, under _build/) and link the shared library."""
+    """Compile every source to an object file (in parallel, under _build/), link the shared library, and build the
+    CPython module that calls it."""
     from concurrent.futures import ThreadPoolExecutor
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     obj_dir = os.path.join(ROOT, "_build")
@@ -103,6 +106,9 @@ def build_library(verbose: bool = False) -> str:
     with ThreadPoolExecutor(max_workers=min(len(jobs), os.cpu_count() or 1)) as pool:
         tables = list(pool.map(lambda j: _run(j[0], verbose), jobs))
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *[o for _, o in jobs], "-o", LIB_PATH], verbose)
+    import sysconfig
+    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-I", sysconfig.get_paths()["include"], *inc,
+          os.path.join(CSRC, PYCALL_SOURCE), "-o", PYCALL_PATH], verbose)
     import json
     resources = {}
     for (cmd, _), table in zip(jobs, tables):
