@@ -15,7 +15,7 @@
 //     so the scores and the softmax of a tile run while its V rows are still on their way.
 //   - Waves 4-7 are the prologue: they load Q and the B_K rows of the workgroup's agents
 //     into registers with ordinary loads (their own request counters: nothing of theirs
-//     queues in front of a tile), form Qt = Q B_K^T by MFMA and leave Q and Qt in LDS in
+//     queues in front of a tile; each only what it has a use for), form Qt = Q B_K^T by MFMA and leave Q and Qt in LDS in
 //     operand-ready order - in a hand-over area of their own where the LDS has room for one
 //     next to the tile stages, else (head dimension 128 with 64 ranks) in the second stage of
 //     the last streaming wave, which that wave fills only after everybody has picked them up.
@@ -23,15 +23,15 @@
 //     the two): the memory path of a compute unit serves requests in order, so a load issued
 //     behind 80 KB of tile requests comes back after them.  With many agent slots and large
 //     ranks Qt comes from a pre-pass kernel instead and is only copied.  The prologue waves
-//     then touch the B_V rows the merge kernel will need and wait at the final barrier.
+//     then touch the B_V rows the merge kernel will need and wait for the streaming waves, to merge with them.
 //   - With one low-rank cache per adapter (BaseShared) the L tile is a row of column blocks,
 //     one per agent slot of the row tile, each requested from that slot's cache; Qt of a row
 //     is zero outside the block of its slot, so the products are unchanged (template form PA).
 //   - All divisions by the row padding (a power of two) are shifts; the addresses of the
 //     LDS reads are formed after the requests have left.
-//   - The four streaming waves merge their states with one barrier (each deposits its
-//     unscaled state and its maxima, then sums a quarter of the blocks with the
-//     flash-decoding weights, in wave order).
+//   - The states of the four streaming waves meet behind one barrier (each deposits its unscaled
+//     state and its maxima; all eight waves then sum the blocks with the flash-decoding weights,
+//     in wave order).
 #include "lra_common.h"
 #include "lra_decode_util.h"
 #include "lra_plan.h"
@@ -75,7 +75,6 @@ __device__ __forceinline__ void decode_stream(const Params& p) {
   constexpr int STAGE_BYTES = 2 * KV_BYTES + L_BYTES;
   constexpr int WAVE_BYTES = 2 * STAGE_BYTES;
   constexpr int ROW_BYTES = D * 2;
-  constexpr int MAXIT = RP / 16;               // Qt items per prologue wave and row tile: 4 slots x RP/16 rho blocks over 4 waves
   constexpr int Q_BYTES = RT * KS * 1024;      // Q as B operands: 16 bytes per lane, k-step and row tile
   constexpr int QT_BYTES = RT * RKS * 1024;
   constexpr int NBLK = DB + RB;                                // f32x4 blocks per lane and row tile
@@ -108,6 +107,8 @@ __device__ __forceinline__ void decode_stream(const Params& p) {
   const bool helper = wave >= NW;
   LRA_STAMP_DECL;
   LRA_STAMP(0);
+  // (the prologue waves come first wherever the eight compete: the others wait for their loads, and for Q and Qt)
+  if (helper) __builtin_amdgcn_s_setprio(3);
   // Everything of the parameter block that stands before the first request is asked for at once:
   // left to itself the compiler fetches it piece by piece, each piece a round trip of its own
   // behind the branch that needs it.
@@ -131,7 +132,10 @@ __device__ __forceinline__ void decode_stream(const Params& p) {
   const int t = CAUSAL ? p.seq_index : 0;                      // (decode: one sequence)
   const int32_t len_t = CONST_I32(p.seq_lens)[t];
   const int j0 = split * p.split_keys;
-  const int kpw = p.split_keys / NW;  // keys per wave, a multiple of 32
+  // The 32-key tiles of a share are divided among the streaming waves as they come, in order: the first `tiles mod 4` waves
+  // take one more than the others.
+  const int wave_tiles = p.split_keys >> 7, more_tiles = (p.split_keys >> 5) & (NW - 1);
+  auto wave_start = [&](int sw) { return j0 + (sw * wave_tiles + min(sw, more_tiles)) * 32; };
   const int n_q = CAUSAL ? p.n_new : p.n_queries;
   const int GP = p.group_pad, G = p.group, r = p.rank;
   const int gps = __builtin_ctz(GP);                           // GP is 4, 8 or 16
@@ -199,7 +203,7 @@ __device__ __forceinline__ void decode_stream(const Params& p) {
   };
   TileBlocks first = {0, 0}, second = {0, 0};
   if constexpr (PAGED) {
-    const int j = j0 + (wave & (NW - 1)) * kpw;
+    const int j = wave_start(wave & (NW - 1));
     first = blocks_of(j);
     second = blocks_of(j + 32);
   }
@@ -241,8 +245,8 @@ __device__ __forceinline__ void decode_stream(const Params& p) {
   };
   auto tile_requests = [&](int sw) __attribute__((always_inline)) {
     TileRequests q;
-    q.jw0 = j0 + sw * kpw;
-    q.jw1 = max(q.jw0, min(q.jw0 + kpw, j1));  // == jw0 for a wave without keys
+    q.jw0 = wave_start(sw);
+    q.jw1 = max(q.jw0, min(q.jw0 + (sw < more_tiles ? wave_tiles + 1 : wave_tiles) * 32, j1));  // == jw0 for a wave without keys
     q.wave_lds = smem + sw * WAVE_BYTES;
     const int rr = lane / KCH, pc = lane % KCH;
 #pragma unroll
@@ -350,25 +354,41 @@ __device__ __forceinline__ void decode_stream(const Params& p) {
     }
   };
 
+  int out_row[RT];
   if (helper) {
     // ===================== prologue waves: Q operands and Qt = Q B_K^T =====================
     const int hw = wave - NW;
-    // qb[rt][ks]: lane (row ln of tile rt, k = 32ks + 8lg + e), e = 0..7: the B operand of S^T
+    const bool qt_ready = HAS_BK && p.qt_ws != nullptr;  // a pre-pass has formed Qt for the whole call
+    // Qt^T blocks to form per row tile: agent slots (a prefill has one adapter: one B_K for all rows) x rho blocks (1 .. RP/16)
+    const int S = CAUSAL ? 1 : 16 >> gps;
+    const int ncb = (r + 15) >> 4;
+    const int n_items = HAS_BK && !qt_ready ? S * ncb : 0;
+    // The streaming waves wait until every load of these waves has left, and a load of sixteen rows takes the memory path of the
+    // unit sixteen cycles and more: no wave asks for what it has no use for.  Two row tiles are two waves' each (each wave then
+    // holds the Q rows of its own tile only), except in a prefill with a B_K, whose one product serves both tiles; Q goes to the
+    // first wave of a tile and to those with a Qt block to form, B_K rows to the latter.  (24 loads per wave at two row tiles of
+    // rank 16 before, 8 or 12 now, 12 and 8 at one: 8 agents on 1500 keys 10.5 -> 9.95 us a call, 4 on 8192 11.15 -> 10.3; the
+    // waves' priority, which ends where their Q is handed over, for another 0.15 to 0.25.)
+    constexpr bool BY_TILE = RT == 2 && !(CAUSAL && HAS_BK);
+    constexpr int NQ = BY_TILE ? 1 : RT;        // row tiles whose Q a wave holds
+    constexpr int IW = BY_TILE ? NW / 2 : NW;   // waves that share the items of a row tile
+    constexpr int MAXIT = CAUSAL ? 1 : RP / 4 / IW;  // items per wave: at most 4 slots x RP/16 rho blocks per row tile
+    const int iw = BY_TILE ? hw & 1 : hw, rt0 = BY_TILE ? hw >> 1 : 0;
+    // qb[q][ks]: lane (row ln of tile rt0 + q, k = 32ks + 8lg + e), e = 0..7: the B operand of S^T
     // and of Qt^T = B_K Q^T
-    bf16x8 qb[RT][KS];
-    {
+    bf16x8 qb[NQ][KS];
+    if (iw == 0 || iw < n_items) {
       const __amdgpu_buffer_rsrc_t rs_q = make_rsrc(p.q, static_cast<uint32_t>(n_q) * p.n_q_heads * D * 2);
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        const int R = row0 + rt * 16 + ln;
+      for (int q = 0; q < NQ; ++q) {
+        const int R = row0 + (rt0 + q) * 16 + ln;
         const int slot = R >> gps, gg = R & (GP - 1);
         const bool valid = slot < n_q && gg < G;
         const uint32_t off = valid ? static_cast<uint32_t>((slot * p.n_q_heads + h * G + gg) * ROW_BYTES + lg * 16) : kOob;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) qb[rt][ks] = as_bf16x8(buf_load16(rs_q, off, ks * 64));
+        for (int ks = 0; ks < KS; ++ks) qb[q][ks] = as_bf16x8(buf_load16(rs_q, off, ks * 64));
       }
     }
-    const bool qt_ready = HAS_BK && p.qt_ws != nullptr;  // a pre-pass has formed Qt for the whole call
     if (qt_ready) {
       // operand-ready Qt of this (kv head, row group): RT*RKS pieces of 1 KB; prologue wave hw copies
       // pieces hw, hw + NW, ...
@@ -397,32 +417,28 @@ __device__ __forceinline__ void decode_stream(const Params& p) {
         if (idx < RT * RKS) *reinterpret_cast<uint4*>(qt_lds + (idx * 64 + lane) * 16) = make_uint4(0u, 0u, 0u, 0u);
       }
       __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): written before the barrier below lets the products follow
-      // Item idx = hw + it*NW of row tile rt is (agent slot si, rho block cb); this lane holds row
+      // Item idx = iw + it*IW of a row tile is (agent slot si, rho block cb); this lane holds row
       // rho = 16cb + ln of B_K^a, columns h*D + 32ks + 8lg ..: the A operand of Qt^T.  Rows beyond
       // the rank and the rows of empty slots lie outside the resource and arrive as zeros.
-      const int S = CAUSAL ? 1 : 16 >> gps;  // agent slots per 16-row tile (a prefill has one adapter: one product for all rows)
-      const int ncb = (r + 15) >> 4;   // rho blocks: 1 .. RP/16
-      const int n_items = S * ncb;
       // idx -> (slot, rho block): idx / ncb without a division (idx < 16, ncb <= 4)
       const int inv_ncb = ncb == 1 ? 257 : (ncb == 2 ? 129 : (ncb == 3 ? 86 : 65));  // 256 / ncb + 1
       auto item_slot = [&](int idx) { return (idx * inv_ncb) >> 8; };
       const int64_t ldb = static_cast<int64_t>(p.n_kv_heads) * D;
       const bf16_t* bkg = static_cast<const bf16_t*>(p.b_k);
-      uint4 bt4[RT][MAXIT][KS];
+      bf16x8 bt[MAXIT][KS];
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-        for (int it = 0; it < MAXIT; ++it) {
-          const int idx = hw + it * NW;
+      for (int it = 0; it < MAXIT; ++it) {
+        const int idx = iw + it * IW;
+        if (idx < n_items) {
           const int si = item_slot(idx), cb = idx - si * ncb;
-          const int a = slot_adapter(rt, si);
-          const bool live = idx < n_items && a >= 0;
-          const uint32_t bytes = live ? static_cast<uint32_t>((r - 1) * ldb + D) * 2u : 0u;
-          const __amdgpu_buffer_rsrc_t rs_b = make_rsrc(bkg + static_cast<int64_t>(live ? a : 0) * r * ldb + h * D, bytes);
+          const int a = rt0 == 0 ? slot_adapter(0, si) : slot_adapter(RT - 1, si);
+          const uint32_t bytes = a >= 0 ? static_cast<uint32_t>((r - 1) * ldb + D) * 2u : 0u;
+          const __amdgpu_buffer_rsrc_t rs_b = make_rsrc(bkg + static_cast<int64_t>(max(a, 0)) * r * ldb + h * D, bytes);
           const uint32_t off = static_cast<uint32_t>((cb * 16 + ln) * ldb * 2 + lg * 16);
 #pragma unroll
-          for (int ks = 0; ks < KS; ++ks) bt4[rt][it][ks] = buf_load16(rs_b, off, ks * 64);
+          for (int ks = 0; ks < KS; ++ks) bt[it][ks] = as_bf16x8(buf_load16(rs_b, off, ks * 64));
         }
+      }
       // The streaming waves hold their requests back until these loads have left: the memory
       // path of a CU takes requests in order, and behind 144 KB of tile requests Q and B_K would
       // arrive last.  (A bare barrier: nothing is exchanged yet, it only orders the issue.)
@@ -433,32 +449,33 @@ __device__ __forceinline__ void decode_stream(const Params& p) {
       // at ((rt*RKS + ks')*64 + l)*16, elements e -> rho = 32ks' + 16(e/4) + 4lg + e%4 (the L
       // operand of the loop uses the same order).
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt)
+      for (int it = 0; it < MAXIT; ++it) {
+        const int idx = iw + it * IW;
+        if (idx < n_items) {
+          const int si = item_slot(idx), cb = idx - si * ncb;
 #pragma unroll
-        for (int it = 0; it < MAXIT; ++it) {
-          const int idx = hw + it * NW;
-          if (idx < n_items) {
-            const int si = item_slot(idx), cb = idx - si * ncb;
+          for (int q = 0; q < NQ; ++q) {
             f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-              acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(bt4[rt][it][ks]), qb[rt][ks], acc, 0, 0, 0);
+            for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bt[it][ks], qb[q][ks], acc, 0, 0, 0);
             if (CAUSAL || (ln >> gps) == si) {
               const int kb = si * lb16 + cb;  // 16-rank block along the L tile's columns
-              unsigned char* dst = qt_lds + ((rt * RKS + (kb >> 1)) * 64 + lane) * 16;
+              unsigned char* dst = qt_lds + (((rt0 + q) * RKS + (kb >> 1)) * 64 + lane) * 16;
               *reinterpret_cast<uint2*>(dst + (kb & 1) * 8) = make_uint2(pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3]));
             }
           }
         }
+      }
     }
     if constexpr (!HAS_BK) __builtin_amdgcn_s_barrier();  // the Q loads have left (see above)
-    if (hw == 0) {
+    if (iw == 0) {
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt)
+      for (int q = 0; q < NQ; ++q)
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
-          *reinterpret_cast<uint4*>(q_lds + ((rt * KS + ks) * 64 + lane) * 16) = __builtin_bit_cast(uint4, qb[rt][ks]);
+          *reinterpret_cast<uint4*>(q_lds + (((rt0 + q) * KS + ks) * 64 + lane) * 16) = __builtin_bit_cast(uint4, qb[q][ks]);
     }
+    __builtin_amdgcn_s_setprio(0);
     LRA_STAMP(2);
     // One workgroup per (kv head, row group) touches the B_V rows the merge kernel will need
     // (one 4-byte read per 128-byte line), so that they wait in this XCD's L2 instead of in
@@ -508,12 +525,9 @@ __device__ __forceinline__ void decode_stream(const Params& p) {
     }
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) asm volatile("" ::"v"(warm[rt]));
-    __syncthreads();  // the streaming waves' merge barrier
-    LRA_STAMP(11);
-    LRA_STAMP_FLUSH();
-    return;
-  }
-
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) out_row[rt] = row_index(rt);
+  } else {
   // ===================== streaming waves =====================
   const TileRequests treq = tile_requests(wave);
   const int jw0 = treq.jw0, jw1 = treq.jw1;
@@ -560,7 +574,6 @@ __device__ __forceinline__ void decode_stream(const Params& p) {
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) lim[rt] = n_t - n_q + min((row0 + rt * 16 + ln) >> gps, n_q - 1);
   const int lim_first = n_t - n_q + (row0 >> gps);  // the smallest of them in this workgroup
-  int out_row[RT];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) out_row[rt] = row_index(rt);
 
@@ -735,10 +748,11 @@ __device__ __forceinline__ void decode_stream(const Params& p) {
   LRA_STAMP(5);
 
   // ===================== merge the streaming waves (one barrier) =====================
-  // Every wave deposits its state as it stands - blocks as 16 bytes per lane, then (m, l) per
-  // lane - in its own tile region (nothing of its own is outstanding any more); after the
-  // barrier wave w sums blocks w, w + 4, ... of all four states with the weights
-  // 2^(m_w' - max m), in wave order, and stores them.
+  // Every streaming wave deposits its state as it stands - blocks as 16 bytes per lane, then (m, l)
+  // per lane - in its own tile region (nothing of its own is outstanding any more); after the
+  // barrier the eight waves of the workgroup sum a block of all four states each in turn, with the
+  // weights 2^(m_w' - max m), in the order of the states, and store it.  (Reads of LDS and stores bound
+  // this: with the prologue waves idle 0.6 and 1.1 us at one and two row tiles, 0.15 and 0.4 less so.)
   {
     unsigned char* mine = wave_lds;
 #pragma unroll
@@ -752,6 +766,7 @@ __device__ __forceinline__ void decode_stream(const Params& p) {
       *reinterpret_cast<f32x2*>(base + NBLK * 1024 + lane * 8) = f32x2{m_run[rt], lsum};
     }
   }
+  }  // (streaming waves)
   __syncthreads();
   LRA_STAMP(6);
 #pragma unroll
@@ -773,7 +788,7 @@ __device__ __forceinline__ void decode_stream(const Params& p) {
     const int64_t slot = static_cast<int64_t>(out_row[rt]) * p.n_splits + split;
 #pragma unroll
     for (int x = 0; x < NBLK; ++x) {
-      if ((x & (NW - 1)) != wave) continue;  // wave-uniform
+      if (((rt * NBLK + x) & (2 * NW - 1)) != wave) continue;  // wave-uniform
       f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int w = 0; w < NW; ++w) {
@@ -796,7 +811,7 @@ __device__ __forceinline__ void decode_stream(const Params& p) {
         if (mine && rho < r) *reinterpret_cast<f32x4*>(p.part_lr + slot * r + rho) = v;
       }
     }
-    if (wave == NW - 1 && lg == 0) {
+    if (wave == 2 * NW - 1 && lg == 0) {
       p.part_ml[slot * 2 + 0] = m_all * 0.69314718055994530942f;  // natural-log units
       p.part_ml[slot * 2 + 1] = l_all;
       if (split == 0) p.part_adapter[out_row[rt]] = max(slot_adapter(rt, ln >> gps), 0);
