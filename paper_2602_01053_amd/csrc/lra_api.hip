@@ -130,8 +130,8 @@ static lra_status decode_call(const lra_shape* shape, const lra_cache* cache, co
        reinterpret_cast<uintptr_t>(adapters->b_k) | reinterpret_cast<uintptr_t>(adapters->b_v)) & 15)
     return LRA_ERR_SHAPE;
   if (!plan_sizes_fit(shape, cache, n_queries, max_queries_per_seq)) return LRA_ERR_UNSUPPORTED;
-  const Tuning tune = resolve_tuning(tuning);
-  const Plan pl = make_plan(shape, cache, n_queries, max_queries_per_seq, false, tune, adapters->b_k != nullptr);
+  Tuning tune = resolve_tuning(tuning);
+  Plan pl = make_plan(shape, cache, n_queries, max_queries_per_seq, false, tune, adapters->b_k != nullptr);
   if (!pl.launchable) return LRA_ERR_UNSUPPORTED;
   if (use_static) {
     if (pl.bytes > LRA_STATIC_WORKSPACE_BYTES) return LRA_ERR_WORKSPACE;
@@ -139,8 +139,13 @@ static lra_status decode_call(const lra_shape* shape, const lra_cache* cache, co
     if (st != LRA_OK) return st;
     workspace_bytes = LRA_STATIC_WORKSPACE_BYTES;
   }
+  if (pl.stream_keys > 0 && check_workspace(pl, workspace, workspace_bytes) != LRA_OK) {  // enough without those shares, perhaps
+    tune.stream_shares = false;
+    pl = make_plan(shape, cache, n_queries, max_queries_per_seq, false, tune, adapters->b_k != nullptr);
+  }
   st = check_workspace(pl, workspace, workspace_bytes);
   if (st != LRA_OK) return st;
+  pl = as_run(pl);
 
   Params p{};
   fill_params(p, shape, cache, adapters, pl, workspace);
@@ -211,6 +216,15 @@ lra_status lra_attn_prefill(const lra_shape* shape, const lra_cache* cache, cons
     pl = make_plan(shape, cache, n_new, 1, true, tune, adapters->b_k != nullptr);
   }
   if (!pl.launchable) return LRA_ERR_UNSUPPORTED;
+  if (pl.stream_keys > 0) {
+    if (check_workspace(pl, workspace, workspace_bytes) == LRA_OK) {
+      pl = as_run(pl);
+      wave_shares = 0;
+    } else {  // enough without, perhaps
+      tune.stream_shares = false;
+      pl = make_plan(shape, cache, n_new, 1, true, tune, adapters->b_k != nullptr);
+    }
+  }
   // Rotary key side: the completed keys go to the workspace when the call has a key-side adapter and
   // the workspace has room for them; otherwise the kernel completes every key tile itself.
   bool keys_by_prepass = pl.kc_bytes > 0 && adapters->b_k != nullptr;

@@ -821,6 +821,84 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
   return pl;
 }
 
+// Whether a prefill of few new tokens that the lines above give to the tile walk, or the shares of prefill_rows_kernel, runs on the
+// streaming kernel.  Four to eight kv heads of 128, ranks up to 32, up to three row groups; ratio of the times there / streaming:
+//   8 kv heads, G 4    5 to 8 tokens 0.92 to 0.99 at 1 and 2 k, 0.97 to 1.03 at 3 and 4.5 k, 1.0 to 1.14 beyond (8 after 9001 15.7 / 13.6 us),
+//                      rank 32 from 6 k on; paged 0.97 at 1 k, 1.04 to 1.2 from 2 k on, 8 at rank 32 0.95 at 4.5 k. 9 to 16 tokens at
+//                      ranks up to 16 1.01 to 1.12 from 2 to 5 k, 0.95 to 1.1 to 7.5 k and 0.9 to 0.96 beyond, paged 1.02 to 1.15 to 3 k, 0.95
+//                      to 1.02 at 4 k and 0.8 to 0.98 beyond; at rank 32 0.94 to 1.05.  24 tokens 1.03 to 1.15 to 2 k, at rank 32 to
+//                      7.5 k, paged 1.0 to 1.2 to 3 k
+//   4 kv heads, G 7    3 and 4 tokens 0.95 at 1 and 2 k, 1.03 to 1.08 from 3 k on; paged 0.97 at 1 k, 1.1 to 1.3 from 3 k on.  6 and 8 0.98 at 1
+//                      k, 1.02 to 1.16 beyond, paged 1.02 to 1.2 throughout.  9 to 12 1.0 to 1.15, paged 1.08 to 1.2 to 4.5 k, beyond
+//                      0.96 (9 tokens) and 1.0 to 1.1 (12), paged 0.97 and 1.08 to 11 k, 0.96 beyond
+// (Two row groups on the pages of fewer than six kv heads beyond 14 k keep the shares of prefill_rows_kernel: group 7 would gain 1.15,
+// group 8 has not been measured.)
+static bool few_tokens_stream(const lra_shape* sh, const lra_cache* c, int tokens, int row_groups) {
+  if (sh->head_dim != 128 || sh->rank > 32 || sh->n_kv_heads < 4 || sh->n_kv_heads > 8 || row_groups > 3) return false;
+  const int rows = tokens * (sh->n_q_heads / sh->n_kv_heads), n = c->max_seq_len;
+  const bool pages = c->block_size != 0, wide = sh->rank > 16, few = sh->n_kv_heads < 6;
+  if (row_groups == 1) return n > (wide && !few && (!pages || rows > 24) ? 5120 : (pages ? 1536 : 2560));
+  if (n <= (row_groups == 2 && !pages ? (few ? 1536 : 1280) : 900)) return false;
+  if (few) return row_groups == 2 ? !pages || n <= 14336 : n <= 5120 || (!pages && rows >= 84);
+  if (row_groups == 2) return !wide && n <= (pages ? 3584 : 5120);
+  return n <= (pages ? 3072 : (wide ? 8192 : 2560));
+}
+
+// What the streaming kernel does with a call: key shares of any number of 32-key tiles, which its waves divide as they come.  Shares of
+// 129 to 1024 keys (pages: 768; two row tiles or several row groups: 512) are as long as the places ask for, not the next multiple of
+// 128.  us with multiples of 128 / so, 8 kv heads of group 4, rank 16: 4 agents on 4500 keys 10.1 / 9.1, on 9009 12.6 / 12.1, on 15000
+// 16.1 / 15.2, on 25500 22.4 / 22.0; rank 64, 2 agents on 6000 12.5 / 11.9, on 22000 22.5 / 22.1; low-rank caches per adapter on 6000
+// 12.0 / 11.4; d = 64 on 22000 13.8 / 13.2; 4 kv heads of group 7, two row tiles, on 10500 12.2 / 11.3; 8 tokens after 9001 14.9 / 14.0.
+// Beyond, and where a pre-pass forms Qt, 0.97 to 1.02 (paged, 4 agents on 26576 20.9 / 21.2); below, a share more per row costs what the
+// shorter ones save (4500 keys on 4 kv heads 0.98 to 1.03).
+static void plan_stream(Plan& pl, const lra_shape* sh, const lra_cache* c, int tokens, int max_queries_per_seq, bool prefill,
+                        const Tuning& tune, bool key_adapter) {
+  if (sh->key_rope_theta > 0.f || (!prefill && c->n_seqs != 1)) return;
+  Plan st = pl;
+  if (prefill && (!pl.short_prefill || pl.wave_shares > 0)) {
+    // (a call that needs no workspace goes on without one)
+    if (tune.short_prefill != 32 || tune.prefill_splits != 0 || !pl.split_kv_sized || pl.bytes == 0) return;
+    const int G = sh->n_q_heads / sh->n_kv_heads, rows = tokens * (G <= 4 ? 4 : (G <= 8 ? 8 : 16));
+    if (!few_tokens_stream(sh, c, tokens, (rows + 31) / 32)) return;
+    Tuning forced = tune;
+    forced.short_prefill = 33;
+    if (!pl.short_prefill) st = plan_call(sh, c, tokens, max_queries_per_seq, true, forced, key_adapter);
+    if (!st.mfma || !st.short_prefill) return;
+  }
+  // as in plan_call: the call streams (a paged decode of low-rank caches per adapter does not, nor one that it gives two workgroups
+  // per unit), and one round of its shares fills the chip
+  const int64_t work = static_cast<int64_t>(sh->n_kv_heads) * st.row_groups, n = c->max_seq_len;
+  if (work * st.n_splits > kCUs || (c->block_size != 0 && !prefill && c->l_adapter_stride != 0)) return;
+  const bool finer = kCUs / work * work * 4 >= 3 * kCUs && (prefill || st.qt_bytes == 0);
+  int64_t keys = st.split_keys;
+  if (finer) {
+    const int64_t fit = kCUs / work, even = (n * work + kCUs - 1) / kCUs;
+    const int64_t most = st.row_tiles > 1 || st.row_groups > 1 ? 512 : (c->block_size != 0 ? 768 : 1024);
+    if (even > 128 && even <= most) {
+      const int64_t shares = meeting_shares(fit, sh->n_kv_heads, st.row_groups);
+      const int64_t least = ((n + shares - 1) / shares + 31) / 32 * 32;
+      keys = least < keys ? least : keys;
+    }
+  }
+  if (keys == st.split_keys && st.short_prefill == pl.short_prefill && pl.wave_shares == 0) return;
+  pl.stream_keys = static_cast<int>(keys);
+  pl.stream_splits = static_cast<int>((n + keys - 1) / keys);
+  pl.stream_pad = st.group_pad;
+  pl.stream_row_tiles = st.row_tiles;
+  pl.stream_row_groups = st.row_groups;
+  pl.stream_prefill = prefill;
+  if (pl.stream_splits > pl.n_splits) {  // room for either
+    const size_t slots = static_cast<size_t>(pl.rows) * pl.stream_splits;
+    pl.off_ml = 0;
+    pl.off_o = align_up(slots * 2 * sizeof(float), 256);
+    pl.off_lr = pl.off_o + align_up(slots * sh->head_dim * sizeof(float), 256);
+    pl.off_adapter = pl.off_lr + align_up(slots * sh->rank * sizeof(float), 256);
+    pl.off_qt = pl.off_adapter + align_up(static_cast<size_t>(pl.rows) * sizeof(int32_t), 256);
+    pl.bytes = pl.off_qt + align_up(pl.qt_bytes, 256);
+    pl.bytes_without_kc = pl.bytes;
+  }
+}
+
 Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_queries_per_seq, bool prefill,
                const Tuning& tune, bool key_adapter) {
   Plan pl = plan_call(sh, c, tokens, max_queries_per_seq, prefill, tune, key_adapter);
@@ -830,6 +908,21 @@ Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_quer
     if (prefill_rows_reads(sh, c, pl.split_kv_sized, pl.kc_bytes > 0))
       pl.wave_shares = plan_wave_shares(sh, c, tokens, pl.n_splits);
   }
+  if (pl.mfma && !pl.wave_rows && pl.launchable && tune.variant == 0 && tune.split_keys <= 0 && tune.stream_shares)
+    plan_stream(pl, sh, c, tokens, max_queries_per_seq, prefill, tune, key_adapter);
+  return pl;
+}
+
+Plan as_run(const Plan& plan) {
+  Plan pl = plan;
+  if (pl.stream_keys == 0) return pl;
+  pl.split_keys = pl.stream_keys;
+  pl.n_splits = pl.stream_splits;
+  pl.group_pad = pl.stream_pad;
+  pl.row_tiles = pl.stream_row_tiles;
+  pl.row_groups = pl.stream_row_groups;
+  pl.short_prefill = pl.stream_prefill;
+  pl.wave_shares = 0;
   return pl;
 }
 

@@ -24,6 +24,7 @@ struct Tuning {
   int append_stages = 0;    // LDS stages of the tiled append GEMM, 0 = chosen from the grid
   int append_tile = 0;      // output tile of the append GEMM, 0 = chosen from the grid
   int append_k_splits = 0;  // parts of d_model in the append GEMM: 0 = chosen from the grid, 1 = never split
+  bool stream_shares = true;      // shares and calls of the streaming kernel beside the rest of a plan (false: a workspace without room for them)
   bool main_kernel_only = false;  // measurement: enqueue only the dominant kernel of a call
 };
 Tuning resolve_tuning(const lra_tuning* t);
@@ -38,6 +39,11 @@ struct Plan {
   bool split_kv_sized;  // prefill: few new tokens behind a context, the sizes the split-KV path is for (whatever path it takes)
   bool wave_rows;  // prefill: workgroups of 32 rows whose waves divide the keys (prefill_rows_kernel), whatever the rest says
   int wave_shares;  // ... or, if not 0, that kernel with this many workgroups dividing the keys of 32 rows, then the merge kernel
+  // The streaming kernel (stream_keys > 0; nothing is rotated then, one sequence, at most one workgroup per unit) with other key shares
+  // than the rest says, or in place of the kernel that the rest is for: keys of a share (a multiple of 32), shares, row packing.  The
+  // workspace has room for either; as_run() is the plan of what runs.
+  int stream_keys, stream_splits, stream_pad, stream_row_tiles, stream_row_groups;
+  bool stream_prefill;
   int tile_group;  // tile-walking prefill: q heads whose rows share a q tile (all of a kv head's, or one)
   int group_pad, row_tiles, row_groups;  // MFMA decode row packing
   int l_block;     // split-KV MFMA kernels with per-adapter low-rank caches: padded rank of one slot's column block, else 0
@@ -59,6 +65,9 @@ bool plan_sizes_fit(const lra_shape* sh, const lra_cache* c, int32_t tokens, int
 // never needs more workspace.
 Plan make_plan(const lra_shape* sh, const lra_cache* c, int tokens, int max_queries_per_seq, bool prefill,
                const Tuning& tune, bool key_adapter = true);
+
+// The plan with its key shares, row packing and path those of the streaming kernel where that runs.
+Plan as_run(const Plan& pl);
 
 // lra_cache_append: parts of d_model the tiled GEMM is divided into (1: none), the token side of its
 // tile, and the fp32 workspace the parts need.
