@@ -822,35 +822,34 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
 }
 
 // Whether a prefill of few new tokens that the lines above give to the tile walk, or the shares of prefill_rows_kernel, runs on the
-// streaming kernel.  Four to eight kv heads of 128, ranks up to 32, up to three row groups; ratio of the times there / streaming:
-//   8 kv heads, G 4    5 to 8 tokens 0.92 to 0.99 at 1 and 2 k, 0.97 to 1.03 at 3 and 4.5 k, 1.0 to 1.14 beyond (8 after 9001 15.7 / 13.6 us),
-//                      rank 32 from 6 k on; paged 0.97 at 1 k, 1.04 to 1.2 from 2 k on, 8 at rank 32 0.95 at 4.5 k. 9 to 16 tokens at
-//                      ranks up to 16 1.01 to 1.12 from 2 to 5 k, 0.95 to 1.1 to 7.5 k and 0.9 to 0.96 beyond, paged 1.02 to 1.15 to 3 k, 0.95
-//                      to 1.02 at 4 k and 0.8 to 0.98 beyond; at rank 32 0.94 to 1.05.  24 tokens 1.03 to 1.15 to 2 k, at rank 32 to
-//                      7.5 k, paged 1.0 to 1.2 to 3 k
-//   4 kv heads, G 7    3 and 4 tokens 0.95 at 1 and 2 k, 1.03 to 1.08 from 3 k on; paged 0.97 at 1 k, 1.1 to 1.3 from 3 k on.  6 and 8 0.98 at 1
-//                      k, 1.02 to 1.16 beyond, paged 1.02 to 1.2 throughout.  9 to 12 1.0 to 1.15, paged 1.08 to 1.2 to 4.5 k, beyond
-//                      0.96 (9 tokens) and 1.0 to 1.1 (12), paged 0.97 and 1.08 to 11 k, 0.96 beyond
-// (Two row groups on the pages of fewer than six kv heads beyond 14 k keep the shares of prefill_rows_kernel: group 7 would gain 1.15,
+// streaming kernel.  Four to eight kv heads of 128, ranks up to 32, up to three row groups; ratio of the times there / streaming, three
+// sets of tensors taken in turn, ranks 16 / 32 where they differ, at 1, 2, 3, 4.5, 6, 9 and 13 thousand keys:
+//   8 kv heads, G 4    8 tokens 0.97 1.11 1.10 1.01 1.03 0.96 0.97 / 0.94 1.04 1.00 0.95 0.99 0.95 1.0, paged 0.98 1.11 1.12 1.03 1.02 0.97 0.97 /
+//                      0.95 1.07 1.05 0.97 1.01 0.99 1.0; 16 tokens 1.06 1.09 1.09 0.99 1.04 0.89 0.94 / 1.02 1.11 1.09 1.02 1.05 0.98 0.99, paged
+//                      1.10 1.11 1.07 0.99 0.95 0.88 0.85 / 1.03 1.14 1.10 1.04 0.98 0.90 0.88; 24 tokens 1.16 1.15 1.06 1.04 0.97 0.89 0.83, paged
+//                      1.21 1.14 1.05 0.90 0.85 0.77 0.70
+//   4 kv heads, G 7    3 and 4 tokens 0.92 0.96 1.03 1.08 1.07 1.02 1.0, paged 0.96 0.98 1.07 1.13 1.13 1.15 0.99; 6 and 8 1.02 1.06 1.10 1.08 1.08
+//                      1.05 0.99, paged 1.07 1.09 1.13 1.10 1.10 1.09 1.13; 12 1.11 1.18 1.10 1.15 1.05 1.05 1.0, paged 1.15 1.20 1.12 1.17 1.05 1.0
+//                      0.95 (9 tokens 0.96 to 0.97 at 5.8 k)
+// (Two row groups on the pages of fewer than six kv heads beyond 14 k keep the shares of prefill_rows_kernel: group 7 would gain,
 // group 8 has not been measured.)
 static bool few_tokens_stream(const lra_shape* sh, const lra_cache* c, int tokens, int row_groups) {
   if (sh->head_dim != 128 || sh->rank > 32 || sh->n_kv_heads < 4 || sh->n_kv_heads > 8 || row_groups > 3) return false;
   const int rows = tokens * (sh->n_q_heads / sh->n_kv_heads), n = c->max_seq_len;
   const bool pages = c->block_size != 0, wide = sh->rank > 16, few = sh->n_kv_heads < 6;
-  if (row_groups == 1) return n > (wide && !few && (!pages || rows > 24) ? 5120 : (pages ? 1536 : 2560));
-  if (n <= (row_groups == 2 && !pages ? (few ? 1536 : 1280) : 900)) return false;
+  if (row_groups == 1) return few ? n > (pages ? 2304 : 2560) : n > 1536 && n <= (wide ? 3328 : 7168);
+  if (n <= 900) return false;
   if (few) return row_groups == 2 ? !pages || n <= 14336 : n <= 5120 || (!pages && rows >= 84);
-  if (row_groups == 2) return !wide && n <= (pages ? 3584 : 5120);
-  return n <= (pages ? 3072 : (wide ? 8192 : 2560));
+  return n <= (row_groups == 2 ? (wide ? (pages ? 4608 : 6144) : 3584) : (pages ? 3584 : 5120));
 }
 
 // What the streaming kernel does with a call: key shares of any number of 32-key tiles, which its waves divide as they come.  Shares of
-// 129 to 1024 keys (pages: 768; two row tiles or several row groups: 512) are as long as the places ask for, not the next multiple of
-// 128.  us with multiples of 128 / so, 8 kv heads of group 4, rank 16: 4 agents on 4500 keys 10.1 / 9.1, on 9009 12.6 / 12.1, on 15000
-// 16.1 / 15.2, on 25500 22.4 / 22.0; rank 64, 2 agents on 6000 12.5 / 11.9, on 22000 22.5 / 22.1; low-rank caches per adapter on 6000
-// 12.0 / 11.4; d = 64 on 22000 13.8 / 13.2; 4 kv heads of group 7, two row tiles, on 10500 12.2 / 11.3; 8 tokens after 9001 14.9 / 14.0.
-// Beyond, and where a pre-pass forms Qt, 0.97 to 1.02 (paged, 4 agents on 26576 20.9 / 21.2); below, a share more per row costs what the
-// shorter ones save (4500 keys on 4 kv heads 0.98 to 1.03).
+// 129 to 1024 keys (two row tiles or several row groups: 384; pages: 256) are as long as the places ask for, not the next multiple of
+// 128.  Ratio of the times with multiples of 128 / so, three sets of tensors in turn, rank 16: 8 kv heads of group 4, 1 and 4 agents on
+// 4300 keys 1.07 to 1.12, 5000 1.05 to 1.07 (paged 1.03), 5700 1.04, 9009 to 13000 1.01 to 1.03 (paged 0.98 to 1.01), beyond 1.0 to 1.01 (paged
+// 0.98 to 1.0); 8 agents, two row tiles, 1.07, 1.02, 1.04, 1.0 to 1.04 on 9009 to 11200, 0.99 on 13000 and 15000 (paged 0.97 on 9009); 4 kv
+// heads of group 7, twice as many shares, on 9009 1.05 to 1.08, 10000 1.03 to 1.07, 11200 1.01 to 1.04.  Where a pre-pass forms Qt 0.97 to
+// 1.02; shares below 128 add one more per row and cost what the shorter ones save.
 static void plan_stream(Plan& pl, const lra_shape* sh, const lra_cache* c, int tokens, int max_queries_per_seq, bool prefill,
                         const Tuning& tune, bool key_adapter) {
   if (sh->key_rope_theta > 0.f || (!prefill && c->n_seqs != 1)) return;
@@ -873,7 +872,7 @@ static void plan_stream(Plan& pl, const lra_shape* sh, const lra_cache* c, int t
   int64_t keys = st.split_keys;
   if (finer) {
     const int64_t fit = kCUs / work, even = (n * work + kCUs - 1) / kCUs;
-    const int64_t most = st.row_tiles > 1 || st.row_groups > 1 ? 512 : (c->block_size != 0 ? 768 : 1024);
+    const int64_t most = c->block_size != 0 ? 256 : (st.row_tiles > 1 || st.row_groups > 1 ? 384 : 1024);
     if (even > 128 && even <= most) {
       const int64_t shares = meeting_shares(fit, sh->n_kv_heads, st.row_groups);
       const int64_t least = ((n + shares - 1) / shares + 31) / 32 * 32;

@@ -69,10 +69,11 @@ def test_only_calls_that_stream(planner, runs):  # noqa: F811
 
 def test_which_few_token_prefills_stream(runs):
     for hkv, group, n_new, n, paged, r, streams in [
-            (8, 4, 8, 9009, False, 16, True), (8, 4, 8, 2560, False, 16, False), (8, 4, 8, 2561, False, 16, True), (8, 4, 8, 5000, False, 32, False),
-            (8, 4, 6, 2000, True, 32, True), (8, 4, 8, 2000, True, 32, False), (4, 7, 4, 6004, False, 16, True), (4, 7, 8, 14000, True, 24, True),
-            (8, 4, 16, 4000, False, 8, True), (8, 4, 16, 6000, False, 8, False), (8, 4, 16, 4000, True, 8, False), (8, 4, 16, 3000, True, 8, True),
-            (8, 4, 24, 2000, False, 16, True), (8, 4, 24, 3000, False, 16, False), (8, 4, 24, 8000, False, 32, True), (4, 7, 12, 6000, True, 16, False)]:
+            (8, 4, 8, 9009, False, 16, False), (8, 4, 8, 1536, False, 16, False), (8, 4, 8, 1537, False, 16, True), (8, 4, 8, 7168, False, 16, True),
+            (8, 4, 8, 5000, False, 32, False), (8, 4, 6, 2000, True, 32, True), (4, 7, 4, 6004, False, 16, True), (4, 7, 4, 2200, True, 16, False),
+            (4, 7, 8, 14000, True, 24, True), (4, 7, 8, 14400, True, 24, False), (8, 4, 16, 3500, False, 8, True), (8, 4, 16, 6000, False, 8, False),
+            (8, 4, 16, 6000, False, 32, True), (8, 4, 16, 4000, True, 8, False), (8, 4, 24, 5000, False, 16, True), (8, 4, 24, 4000, True, 16, False),
+            (4, 7, 12, 6000, True, 16, False), (4, 7, 12, 6000, False, 16, True), (4, 7, 9, 6000, False, 16, False)]:
         assert _plan(runs, hkv * group, hkv, 128, r, [n], n_new=n_new, paged=paged)["short_prefill"] == streams, (hkv, n_new, n, paged, r)
 
 

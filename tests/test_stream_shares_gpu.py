@@ -19,8 +19,8 @@ DEV = "cuda:0"
 CASES = [
     # keys, longest of the plan, agents, Hq, Hkv, d, r, paged, key share
     (4100, 4100, 4, 32, 8, 128, 16, False, 160), (4100, 5200, 4, 32, 8, 128, 16, True, 192), (6400, 6400, 8, 32, 8, 128, 16, False, 224),
-    (9009, 9009, 4, 32, 8, 128, 24, True, 288), (10000, 10300, 2, 32, 8, 128, 64, False, 352), (3001, 3001, 3, 32, 32, 128, 8, False, 384),
-    (13000, 13000, 4, 8, 8, 64, 16, True, 416), (9009, 9009, 3, 28, 4, 128, 16, False, 160),
+    (9009, 9009, 4, 32, 8, 128, 24, False, 288), (10000, 10300, 2, 32, 8, 128, 64, False, 352), (3001, 3001, 3, 32, 32, 128, 8, False, 384),
+    (13000, 13000, 4, 8, 8, 64, 16, False, 416), (9009, 9009, 3, 28, 4, 128, 16, True, 160),
 ]
 
 
@@ -71,7 +71,7 @@ def test_low_rank_cache_per_adapter():
     _check(out.to(torch.float64).cpu().numpy(), ref)
 
 
-@pytest.mark.parametrize("n_new,n,hq,hkv,r", [(8, 9009, 32, 8, 16), (3, 10000, 28, 4, 24), (12, 4000, 32, 8, 8)])
+@pytest.mark.parametrize("n_new,n,hq,hkv,r", [(8, 6001, 32, 8, 16), (3, 10000, 28, 4, 24), (12, 3500, 32, 8, 8)])
 def test_few_new_tokens(runs, n_new, n, hq, hkv, r):  # noqa: F811
     pl = _plan(runs, hq, hkv, 128, r, [n], n_new=n_new, paged=False)
     assert pl["short_prefill"] and pl["wave_shares"] == 0 and not pl["wave_rows"] and pl["split_keys"] % 32 == 0
