@@ -358,7 +358,8 @@ __device__ __forceinline__ void decode_stream(const Params& p) {
   if (helper) {
     // ===================== prologue waves: Q operands and Qt = Q B_K^T =====================
     const int hw = wave - NW;
-    const bool qt_ready = HAS_BK && p.qt_ws != nullptr;  // a pre-pass has formed Qt for the whole call
+    // a pre-pass has formed Qt for the whole call (sixteen blocks of B_K for each of two row tiles)
+    const bool qt_ready = HAS_BK && RT == 2 && RP == 64 && !CAUSAL && p.qt_ws != nullptr;
     // Qt^T blocks to form per row tile: agent slots (a prefill has one adapter: one B_K for all rows) x rho blocks (1 .. RP/16)
     const int S = CAUSAL ? 1 : 16 >> gps;
     const int ncb = (r + 15) >> 4;
@@ -839,10 +840,11 @@ __global__ __launch_bounds__(512, 2) void decode_stream_paged_kernel(Params p) {
 // all its agents (config "8 agents, r = 64": 128 KB per workgroup, 32 workgroups per head).
 // One workgroup per (kv head, row tile, agent slot); wave = rho block.  Output: the operand-ready
 // layout the streaming kernel keeps in LDS, [row group][kv head][row tile][k-step][lane] 16 bytes,
-// elements e -> rho = 32ks' + 16(e/4) + 4lg + e%4.
-template <int D, int RP>
+// elements e -> rho = 32ks' + 16(e/4) + 4lg + e%4.  Taken for four slots at ranks above 48 (four rho
+// blocks), where it costs 3 us and loading B_K in the streaming kernel 3.3; with fewer blocks that is ahead.
+template <int D>
 __global__ __launch_bounds__(256) void decode_qt_prepass_kernel(Params p) {
-  constexpr int KS = D / 32, RKS = RP / 32, ROW_BYTES = D * 2;
+  constexpr int KS = D / 32, RKS = 2, ROW_BYTES = D * 2;
   const int lane = threadIdx.x & 63;
   const int cb = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // rho block of this wave
   const int ln = lane & 15, lg = lane >> 4;
@@ -856,10 +858,8 @@ __global__ __launch_bounds__(256) void decode_qt_prepass_kernel(Params p) {
   const int n_q = p.n_queries;
   const int GP = p.group_pad, G = p.group, r = p.rank;
   const int gps = __builtin_ctz(GP);
-  const int ncb = (r + 15) >> 4;
   const int tile_row0 = (rg * 2 + rt) * 16;
   const int slot = (tile_row0 >> gps) + si;
-  if (si >= (16 >> gps) || cb >= ncb) return;
   int a = -1;
   if (slot < n_q) a = min(max(CONST_I32(p.query_adapter)[slot], 0), p.n_adapters - 1);
   const bool live = a >= 0;
@@ -885,17 +885,14 @@ __global__ __launch_bounds__(256) void decode_qt_prepass_kernel(Params p) {
     unsigned char* dst = static_cast<unsigned char*>(p.qt_ws) +
                          ((((static_cast<size_t>(rg) * p.n_kv_heads + h) * 2 + rt) * RKS + (cb >> 1)) * 64 + lane) * 16;
     const uint2 pk = make_uint2(pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3]));
-    if (!(cb & 1) && cb + 1 >= ncb)  // the odd block next to it lies beyond the rank: zeros
-      *reinterpret_cast<uint4*>(dst) = make_uint4(pk.x, pk.y, 0u, 0u);
-    else
-      *reinterpret_cast<uint2*>(dst + (cb & 1) * 8) = pk;
+    *reinterpret_cast<uint2*>(dst + (cb & 1) * 8) = pk;
   }
 }
 
-template <int D, int RP>
-static void launch_prepass2(const Params& p, hipStream_t s) {
+template <int D>
+static void launch_prepass(const Params& p, hipStream_t s) {
   const dim3 grid(p.n_kv_heads, p.row_groups * 2, 16 / p.group_pad), block(256);
-  hipLaunchKernelGGL((decode_qt_prepass_kernel<D, RP>), grid, block, 0, s, p);
+  hipLaunchKernelGGL((decode_qt_prepass_kernel<D>), grid, block, 0, s, p);
 }
 
 // Whether a decode launch can take decode_stream_kernel: one sequence (in a paged cache with one low-rank cache for all
@@ -953,8 +950,8 @@ hipError_t launch_decode_stream(const Params& p, int row_tiles, bool main_kernel
   const dim3 grid = p.share_major ? dim3(8 * p.n_kv_heads, (p.n_splits + 7) / 8, p.row_groups)
                                   : dim3(p.n_kv_heads, shares, p.row_groups);  // (see the index layouts in the kernel)
   if (p.qt_ws != nullptr && !main_kernel_only) {
-    if (p.head_dim == 128) { if (p.rank > 32) launch_prepass2<128, 64>(p, s); else launch_prepass2<128, 32>(p, s); }
-    else { if (p.rank > 32) launch_prepass2<64, 64>(p, s); else launch_prepass2<64, 32>(p, s); }
+    if (p.head_dim == 128) launch_prepass<128>(p, s);
+    else launch_prepass<64>(p, s);
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
   }
   // columns of the L tile: the rank, or with per-adapter low-rank caches one block per agent slot of a row tile

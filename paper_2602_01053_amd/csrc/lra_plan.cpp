@@ -150,16 +150,16 @@ int decode_mfma_row_tiles(int rows_needed) { return rows_needed <= 16 ? 1 : 2; }
 // again above, where the kernel has a compute unit to itself)
 int decode_mfma_rope_slots(int rank) { return rank <= 16 ? 4 : (rank <= 32 ? 2 : 4); }
 
-// The pre-pass pays (one more launch) once a workgroup of the streaming kernel would have to load more than eight 16-row
-// blocks of B_K for two row tiles.  One row tile has sixteen at most, many of them empty slots' (8 kv heads of group 4, paged, rank
-// 48, us with the pre-pass and without: 1 agent on 275 keys 12.0 / 10.2, 3 on 298 12.1 / 10.8, 4 on 469 12.3 / 11.1; 300 calls at
-// ranks 40 to 64 1.06 in the mean; two row tiles of 5 agents, fifteen blocks, 15.3 / 16.2).  (Not in a prefill, whose rows share one
-// adapter: rank 64, 2 new tokens of group 4 on 500 keys 14.1 us with the pre-pass.)
+// The pre-pass pays (one more launch) once a workgroup of the streaming kernel would have to load sixteen 16-row blocks of B_K for
+// each of two row tiles: four agent slots at ranks above 48.  us with the pre-pass / with Qt formed per workgroup, three sets of tensors in
+// turn: rank 24, 8 agents on 1500 keys 11.5 / 10.2, on 15000 22.2 / 20.8; rank 32 12.0 / 11.3, 22.7 / 21.7; rank 64, groups of seven, 4
+// agents, 13.2 / 12.2, 19.7 / 18.3; rank 48, twelve blocks, 13.8 / 13.7, 24.3 / 23.9; rank 64, sixteen, 14.5 / 14.8, 25.2 / 25.4, 16
+// agents in two row groups 14.9 / 16.1, 28.5 / 29.1.  One row tile has sixteen at most, many of them empty slots' (8 kv heads of
+// group 4, paged, rank 48, 1 agent on 275 keys 12.0 / 10.2, 4 on 469 12.3 / 11.1).  Not in a prefill, whose rows share one adapter.
 size_t decode_stream_qt_bytes(int group_pad, int rank, int row_tiles, int row_groups, int n_kv_heads) {
   const int slots = 16 / group_pad, ncb = (rank + 15) / 16;
-  if (row_tiles == 1 || slots * ncb * row_tiles <= 8) return 0;
-  const int rks = rank > 32 ? 2 : 1;
-  return static_cast<size_t>(row_groups) * n_kv_heads * row_tiles * rks * 1024;
+  if (row_tiles == 1 || slots * ncb < 16) return 0;
+  return static_cast<size_t>(row_groups) * n_kv_heads * row_tiles * 2 * 1024;
 }
 
 lra_status check_common(const lra_shape* sh, const lra_cache* c) {
