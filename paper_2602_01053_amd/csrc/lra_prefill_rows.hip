@@ -54,12 +54,13 @@ __global__ __launch_bounds__(512, 2) void prefill_rows_kernel(Params p) {
   constexpr int KV_BYTES = BK * D * 2, L_BYTES = BK * RP * 2, WT = 2 * KV_BYTES + L_BYTES;
   constexpr bool ONES_ROW = RP == 16;  // idle rows of Olr^T take the softmax row sums
   constexpr int Q_AT = NW * WT, Q_BYTES = BM * D * 2;
-  // merging: per wave the state of the 32 rows, [O block][row][32 columns] (waves below DB keep the block they finish in
-  // registers), [row][rho], then (m, l) per row
-  constexpr int BLK = 32 * 32 * 4, LR_BYTES = 32 * RP * 4;
-  constexpr int SLOT = DB * BLK + LR_BYTES + 256, SLOT_SHORT = SLOT - BLK;
-  constexpr int STATES = DB * SLOT_SHORT + (NW - DB) * SLOT;
-  constexpr int B_AT = Q_AT + Q_BYTES > STATES ? Q_AT + Q_BYTES : STATES, B_BYTES = RP * D * 2;  // rows of B_K, then of B_V
+  // merging: per wave the state of the 32 rows, [half O block][row][16 columns] (waves below 2 DB keep the one they finish in
+  // registers), [row][rho], then (m, l) per row; behind the states the sum of Olr
+  constexpr int HALF = 32 * 16 * 4, LR_BYTES = 32 * RP * 4;
+  constexpr int SLOT = 2 * DB * HALF + LR_BYTES + 256, SLOT_SHORT = SLOT - HALF;
+  constexpr int STATES = 2 * DB * SLOT_SHORT + (NW - 2 * DB) * SLOT;
+  constexpr int LR_SUM_AT = STATES;
+  constexpr int B_AT = Q_AT + Q_BYTES > STATES + LR_BYTES ? Q_AT + Q_BYTES : STATES + LR_BYTES, B_BYTES = RP * D * 2;  // rows of B_K, then of B_V
   constexpr int ONES_AT = B_AT + B_BYTES;
   constexpr int SMEM = ONES_AT + (ONES_ROW ? 16 : 0);
   static_assert(SMEM <= 160 * 1024, "LDS of one compute unit");
@@ -378,116 +379,161 @@ __global__ __launch_bounds__(512, 2) void prefill_rows_kernel(Params p) {
   }
   const int n_active = min(NW, n_tiles - tile0);  // waves that have seen keys
   auto quad = [](const pf_f32x16& v, int q) __attribute__((always_inline)) { return pf_f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]}; };
-  auto slot_of = [&](int w) __attribute__((always_inline)) { return smem + (w < DB ? w * SLOT_SHORT : DB * SLOT_SHORT + (w - DB) * SLOT); };
-  // block b of wave w's state: registers 4q..4q+3 of a lane are columns 8q + 4 g2 .. + 3 of row l32
-  auto o_at = [&](int w, int b, int q) __attribute__((always_inline)) {
-    return reinterpret_cast<pf_f32x4*>(slot_of(w) + (b - (w < DB && b > w)) * BLK + l32 * 128 + (((2 * q + g2) ^ (l32 & 7)) << 4));
+  auto slot_of = [&](int w) __attribute__((always_inline)) { return smem + (w < 2 * DB ? w * SLOT_SHORT : 2 * DB * SLOT_SHORT + (w - 2 * DB) * SLOT); };
+  // half block b of wave w's state, columns 16b .. 16b + 15: registers 4q..4q+3 of a lane, q = 2 (b & 1) + i, are columns
+  // 16b + 8i + 4 g2 .. + 3 of row l32 (sixteen lanes of a write or read cover 256 bytes)
+  auto o_at = [&](int w, int b, int i) __attribute__((always_inline)) {
+    return reinterpret_cast<pf_f32x4*>(slot_of(w) + (b - (w < 2 * DB && b > w)) * HALF + l32 * 64 + (((2 * i + g2) ^ ((l32 >> 2) & 3)) << 4));
   };
   auto lr_at = [&](int w, int q) __attribute__((always_inline)) {
-    return reinterpret_cast<pf_f32x4*>(slot_of(w) + (w < DB ? DB - 1 : DB) * BLK + l32 * (RP * 4) + (((2 * q + g2) ^ (l32 & (RP / 4 - 1))) << 4));
+    return reinterpret_cast<pf_f32x4*>(slot_of(w) + (w < 2 * DB ? 2 * DB - 1 : 2 * DB) * HALF + l32 * (RP * 4) + (((2 * q + g2) ^ (RP == 16 ? (l32 >> 2) & 3 : (l32 >> 1) & 7)) << 4));
   };
   auto ml_at = [&](int w) __attribute__((always_inline)) {
-    return reinterpret_cast<pf_f32x2*>(slot_of(w) + (w < DB ? DB - 1 : DB) * BLK + LR_BYTES + l32 * 8);
+    return reinterpret_cast<pf_f32x2*>(slot_of(w) + (w < 2 * DB ? 2 * DB - 1 : 2 * DB) * HALF + LR_BYTES + l32 * 8);
   };
   __syncthreads();  // every wave is done with its tiles
   if (wave < n_active) {
 #pragma unroll
-    for (int b = 0; b < DB; ++b)
+    for (int b = 0; b < 2 * DB; ++b)
       if (b != wave) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) *o_at(wave, b, q) = quad(o_acc[b], q);
+        for (int i = 0; i < 2; ++i) *o_at(wave, b, i) = quad(o_acc[b >> 1], 2 * (b & 1) + i);
       }
 #pragma unroll
     for (int q = 0; q < RP / 8; ++q) *lr_at(wave, q) = quad(lr_acc, q);
     if (g2 == 0) *ml_at(wave) = pf_f32x2{m_run, l_run};
   }
   __syncthreads();
-  if (wave >= DB) return;
-  // wave w finishes columns 32w .. 32w + 31
+  // Wave w finishes columns 16w .. 16w + 15.  Olr is summed by the last waves, a part each, and handed round behind another
+  // barrier; at up to 16 ranks with all keys every wave sums it for itself (that is shorter than the barrier).  All reads leave
+  // before the first is used.  The time is that of the bytes through LDS, whose rows have to be spread over all banks.  (With four
+  // waves, each with a whole block and all of Olr, and lanes of the same bank: 1.65 us of a call's 9.7 here.  Now rank 24, 106 tokens
+  // on 1106 keys 12.7 -> 12.4 us, 24 on 6905 in shares 15.5 -> 14.7; rank 16, 45 on 478 keys 9.47 -> 9.40, 10 on 506 paged 9.64 -> 9.45.)
+  const bool finishes = wave < 2 * DB;
+  constexpr bool EACH_LR = RP == 16 && !SHARED;
+  constexpr int LQ = EACH_LR ? RP / 8 : 1;  // parts of Olr, 8 ranks each, that a wave sums, from lr_q on
+  const int lr_q = EACH_LR ? 0 : NW - 1 - wave;
+  const bool sums_lr = EACH_LR ? finishes && has_bv : lr_q < RP / 8 && (SHARED || has_bv);
   float m_all = -INFINITY, l_all = 0.f;
   pf_f32x2 ml[NW];
+  pf_f32x4 v_o[NW][2], v_lr[NW][LQ];
+#pragma unroll
+  for (int w = 0; w < NW; ++w) ml[w] = *ml_at(w);
+  if (finishes) {
+#pragma unroll
+    for (int w = 0; w < NW; ++w)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) v_o[w][i] = *o_at(w, wave, i);  // (its own, and those beyond n_active, are not used)
+  }
+  if (sums_lr) {
+#pragma unroll
+    for (int w = 0; w < NW; ++w)
+#pragma unroll
+      for (int q = 0; q < LQ; ++q) v_lr[w][q] = *lr_at(w, lr_q + q);
+  }
 #pragma unroll
   for (int w = 0; w < NW; ++w) {
-    ml[w] = pf_f32x2{-INFINITY, 0.f};
-    if (w < n_active) ml[w] = *ml_at(w);
+    if (w >= n_active) ml[w] = pf_f32x2{-INFINITY, 0.f};
     m_all = fmaxf(m_all, ml[w][0]);
   }
-  pf_f32x16 o, lr;
+  pf_f32x4 o[2], lr[LQ];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    o[i] = 0.f;
-    lr[i] = 0.f;
+  for (int q = 0; q < LQ; ++q) lr[q] = pf_f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int b = 0; b < DB; ++b)
-      if (b == wave) o[i] = o_acc[b][i];
+  for (int i = 0; i < 2; ++i) {
+    o[i] = pf_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int b = 0; b < 2 * DB; ++b)
+      if (b == wave) o[i] = quad(o_acc[b >> 1], 2 * (b & 1) + i);
   }
   {
     const float own = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_all);
-    o *= own;
+    o[0] *= own;
+    o[1] *= own;
   }
 #pragma unroll
   for (int w = 0; w < NW; ++w) {
     if (w >= n_active) break;
     const float wgt = ml[w][0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[w][0] - m_all);
     l_all = fmaf(wgt, ml[w][1], l_all);
-    if (w != wave) {
+    if (finishes && w != wave) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const pf_f32x4 v = *o_at(w, wave, q);
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) o[4 * q + i] = fmaf(wgt, v[i], o[4 * q + i]);
-      }
+        for (int e = 0; e < 4; ++e) o[i][e] = fmaf(wgt, v_o[w][i][e], o[i][e]);
     }
+    if (sums_lr) {
 #pragma unroll
-    for (int q = 0; q < RP / 8; ++q) {
-      const pf_f32x4 v = *lr_at(w, q);
+      for (int q = 0; q < LQ; ++q)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) lr[4 * q + i] = fmaf(wgt, v[i], lr[4 * q + i]);
+        for (int e = 0; e < 4; ++e) lr[q][e] = fmaf(wgt, v_lr[w][q][e], lr[q][e]);
     }
   }
   const bool live = l32 < live_rows;
+  const int col = 16 * wave + 4 * g2;
   if constexpr (SHARED) {
     // the share's state for the merge kernel: m in natural-log units, l, O and Olr as fp32 rows
     if (!live) return;
+    if (finishes) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      *reinterpret_cast<pf_f32x4*>(p.part_o + slot * D + 32 * wave + 8 * q + 4 * g2) = quad(o, q);
-    if (wave == 0) {
-#pragma unroll
-      for (int q = 0; q < RP / 8; ++q)
-        if (8 * q < r) *reinterpret_cast<pf_f32x4*>(p.part_lr + slot * r + 8 * q + 4 * g2) = quad(lr, q);
-      if (g2 == 0) {
-        *reinterpret_cast<pf_f32x2*>(p.part_ml + slot * 2) = pf_f32x2{m_all * 0.69314718055994530942f, l_all};
-        if (share == 0) p.part_adapter[out_row] = a_idx;
-      }
+      for (int i = 0; i < 2; ++i) *reinterpret_cast<pf_f32x4*>(p.part_o + slot * D + col + 8 * i) = o[i];
+    }
+    if (sums_lr && 8 * lr_q < r) *reinterpret_cast<pf_f32x4*>(p.part_lr + slot * r + 8 * lr_q + 4 * g2) = lr[0];
+    if (wave == 0 && g2 == 0) {
+      *reinterpret_cast<pf_f32x2*>(p.part_ml + slot * 2) = pf_f32x2{m_all * 0.69314718055994530942f, l_all};
+      if (share == 0) p.part_adapter[out_row] = a_idx;
     }
     return;
   }
   if (has_bv) {
-    // O^T += B_V^T Olr^T, Olr as two bf16 terms (see prefill_mfma_kernel)
+    auto sum_at = [&](int q) __attribute__((always_inline)) { return reinterpret_cast<pf_f32x4*>(smem + LR_SUM_AT + q * 1024 + lane * 16); };
+    if constexpr (!EACH_LR) {
+      if (sums_lr) *sum_at(lr_q) = lr[0];
+      __syncthreads();
+    }
+    if (!finishes) return;
+    // O^T += B_V^T Olr^T, Olr as two bf16 terms (see prefill_mfma_kernel); the product is that of the 32 columns that the half
+    // block lies in
+    pf_f32x16 acc;
+    const bool upper = (wave & 1) != 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      acc[i] = upper ? 0.f : o[i >> 2][i & 3];
+      acc[8 + i] = upper ? o[i >> 2][i & 3] : 0.f;
+    }
 #pragma unroll
     for (int ks = 0; ks < RKS; ++ks) {
+      pf_f32x4 x[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        if constexpr (EACH_LR) x[i] = lr[2 * ks + i];
+        else x[i] = *sum_at(2 * ks + i);
+      }
       uint32_t w2[2][4];
 #pragma unroll
       for (int e2 = 0; e2 < 4; ++e2) {
-        const float x0 = lr[8 * ks + 2 * e2], x1 = lr[8 * ks + 2 * e2 + 1];
+        const float x0 = x[e2 >> 1][2 * (e2 & 1)], x1 = x[e2 >> 1][2 * (e2 & 1) + 1];
         w2[0][e2] = pf_pack2(x0, x1);
         const float r0 = x0 - __uint_as_float(w2[0][e2] << 16), r1 = x1 - __uint_as_float(w2[0][e2] & 0xffff0000u);
         w2[1][e2] = pf_pack2(__builtin_isfinite(r0) ? r0 : 0.f, __builtin_isfinite(r1) ? r1 : 0.f);
       }
-      const unsigned char* src = smem + B_AT - KV_BYTES + (v_pre ^ (wave << 6)) + 16 * ks * (D * 2);
+      const unsigned char* src = smem + B_AT - KV_BYTES + (v_pre ^ ((wave >> 1) << 6)) + 16 * ks * (D * 2);
       const pf_bf16x8 a = pf_join(pf_read_tr16(src), pf_read_tr16(src + 8 * (D * 2)));
 #pragma unroll
       for (int term = 1; term >= 0; --term)
-        o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf_as_bf16x8(make_uint4(w2[term][0], w2[term][1], w2[term][2], w2[term][3])), o, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf_as_bf16x8(make_uint4(w2[term][0], w2[term][1], w2[term][2], w2[term][3])), acc, 0, 0, 0);
     }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) o[i >> 2][i & 3] = upper ? acc[8 + i] : acc[i];
+  } else if (!finishes) {
+    return;
   }
   if (!live) return;
   const float inv = 1.0f / l_all;
-  bf16_t* dst = static_cast<bf16_t*>(p.out) + out_row * D + 32 * wave + 4 * g2;
+  bf16_t* dst = static_cast<bf16_t*>(p.out) + out_row * D + col;
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
-    *reinterpret_cast<uint2*>(dst + 8 * q) = make_uint2(pf_pack2(o[4 * q] * inv, o[4 * q + 1] * inv), pf_pack2(o[4 * q + 2] * inv, o[4 * q + 3] * inv));
+  for (int i = 0; i < 2; ++i)
+    *reinterpret_cast<uint2*>(dst + 8 * i) = make_uint2(pf_pack2(o[i][0] * inv, o[i][1] * inv), pf_pack2(o[i][2] * inv, o[i][3] * inv));
 }
 
 template <int D, int RP, bool PAGED, int MODE>
