@@ -24,7 +24,7 @@
 // next K rows are requested when the scores have been taken, the next L and V rows behind the second product, and the
 // other wave of the SIMD computes meanwhile.  What bounds the loop is the way from L2 into LDS: 136 KB per 256 keys at
 // about 100 GB/s per compute unit, 1.35 us (a wave with 64 rows, which halves that, holds 2 x 80 accumulators and has
-// to read Q from LDS in every step: 2.3 us).  Outside the loop 7 us: launch, two round trips to memory, the exchange.
+// to read Q from LDS in every step: 2.3 us).  Outside the loop 6.5 us: launch, two round trips to memory, the exchange.
 #include "lra_prefill_util.h"
 
 namespace lra {
