@@ -305,9 +305,10 @@ __global__ __launch_bounds__(256, 3) void generic_partial_kernel(Params p) {
     if (more) request_k(jb + kWave);
     if (more && L_EARLY) request_l(jb + kWave);
     part_end();
-    const float m_new = fmaxf(m, over_lanes<64>(s, [](float u, float v) { return fmaxf(u, v); }));  // finite: the wave's first key is valid
+    const float m_new = fmaxf(m, over_lanes<64>(s, [](float u, float v) { return fmaxf(u, v); }));
     const float alpha = (m == -INFINITY) ? 0.f : expf(m - m_new);
-    const float pj = expf(s - m_new);  // (past the end: zero)
+    // past the end: zero; a score of minus infinity likewise, also where all sixteen are and m_new with them (NaN stays NaN)
+    const float pj = s == -INFINITY ? 0.f : expf(s - m_new);
     ell = fmaf(alpha, ell, quarter == 0 ? pj : 0.f);
 #pragma unroll
     for (int e = 0; e < E; ++e) o[e] *= alpha;
