@@ -757,7 +757,7 @@ __global__ __launch_bounds__(256) void merge_rows_kernel(Params p) {
   const bool live = lane < ns && st_raw.y > 0.f;
   const float big = over_lanes<NS>(live ? st_raw.x : -INFINITY, [](float x, float y) { return fmaxf(x, y); });
   const float w = live ? expf(st_raw.x - big) : 0.f;
-  const float ell = over_lanes<NS>(live ? w * st_raw.y : 0.f, [](float x, float y) { return x + y; });
+  const float ell = over_lanes<NS>(lane < ns ? w * st_raw.y : 0.f, [](float x, float y) { return x + y; });  // (a share's NaN is the row's)
 
   // ---- weighted sums of this wave's splits ----
   float o[CPL], olr = 0.f;
@@ -888,7 +888,7 @@ __global__ __launch_bounds__(256) void merge_wave_kernel(Params p) {
   const bool live = lane < ns && st_raw.y > 0.f;
   const float big = over_lanes<64>(live ? st_raw.x : -INFINITY, [](float u, float v) { return fmaxf(u, v); });
   const float w = live ? expf(st_raw.x - big) : 0.f;
-  const float ell = over_lanes<64>(live ? w * st_raw.y : 0.f, [](float u, float v) { return u + v; });
+  const float ell = over_lanes<64>(lane < ns ? w * st_raw.y : 0.f, [](float u, float v) { return u + v; });  // (a share's NaN is the row's)
   const uint64_t live_mask = __ballot(w > 0.f);
   const int ns_live = 64 - __builtin_clzll(live_mask | 1);
 
@@ -1004,16 +1004,16 @@ __global__ __launch_bounds__(256) void merge_tokens_kernel(Params p) {
     float big = -INFINITY;
 #pragma unroll
     for (int j = 0; j < kShares / 16; ++j) {
+      if (16 * j + l16 >= ns) st[k][j] = make_float2(-INFINITY, 0.f);
       // (a share without a visible key left a zero row sum; its rows were never written)
-      if (!(16 * j + l16 < ns && st[k][j].y > 0.f)) st[k][j] = make_float2(-INFINITY, 0.f);
-      big = fmaxf(big, st[k][j].x);
+      big = fmaxf(big, st[k][j].y > 0.f ? st[k][j].x : -INFINITY);
     }
     big = over_16_lanes(big, [](float a, float x) { return fmaxf(a, x); });
     float sum = 0.f;
 #pragma unroll
     for (int j = 0; j < kShares / 16; ++j) {
       w[k][j] = st[k][j].y > 0.f ? expf(st[k][j].x - big) : 0.f;
-      sum = fmaf(w[k][j], st[k][j].y, sum);
+      sum = fmaf(w[k][j], st[k][j].y, sum);  // (a share's NaN is the row's)
     }
     ell[k] = over_16_lanes(sum, [](float a, float x) { return a + x; });
   }
