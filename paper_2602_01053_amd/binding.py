@@ -77,8 +77,16 @@ _calls = None   # the CPython module, bound to _lib
 
 # The raw handle of the current stream, without the Stream object torch.cuda.current_stream() builds around it: a
 # call's time on the host is what a decode step of a short context waits for (see lra_attn_decode).
-_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda device: torch.cuda.current_stream().cuda_stream)
-_current_device = getattr(torch._C, "_cuda_getDevice", None) or (lambda: 0)
+def _stream_hooks(c):
+    """(raw stream of a device, current device) of torch's C module: both, or the public way for the pair, since a raw
+    stream is that of the device it is asked for."""
+    raw, device = getattr(c, "_cuda_getCurrentRawStream", None), getattr(c, "_cuda_getDevice", None)
+    if raw is None or device is None:
+        return lambda _: torch.cuda.current_stream().cuda_stream, lambda: None
+    return raw, device
+
+
+_raw_stream, _current_device = _stream_hooks(torch._C)
 
 
 def load_library() -> ctypes.CDLL:

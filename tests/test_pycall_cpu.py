@@ -98,3 +98,15 @@ def test_missing_module_is_told(monkeypatch):
     monkeypatch.setattr(B, "PYCALL_PATH", "/nonexistent/_lra_pycall.so")
     with pytest.raises(RuntimeError, match="missing"):
         lra.load_library()
+
+
+def test_stream_hooks_come_as_a_pair(monkeypatch):
+    """Without the current device the raw stream of some device would be another stream than the caller's."""
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("S", (), {"cuda_stream": 99})())
+    both = type("C", (), {"_cuda_getCurrentRawStream": staticmethod(lambda d: 10 + d), "_cuda_getDevice": staticmethod(lambda: 3)})
+    raw, device = B._stream_hooks(both)
+    assert raw(device()) == 13
+    for missing in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        one = type("C", (), {k: staticmethod(getattr(both, k)) for k in ("_cuda_getCurrentRawStream", "_cuda_getDevice") if k != missing})
+        raw, device = B._stream_hooks(one)
+        assert raw(device()) == 99
