@@ -1,16 +1,18 @@
-"""Compile the HIP library (and nothing else) for gfx950, in-tree."""
+"""Compile the HIP library for gfx950 and the CPython module that calls it, in-tree."""
 from __future__ import annotations
 
 import os
 import re
 import subprocess
+import sysconfig
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG_DIR)
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "liblra_attn.so")
 PYCALL_SOURCE = "lra_pycall.cpp"   # CPython module over the C ABI, on its own: it links neither the library nor torch
-PYCALL_PATH = os.path.join(PKG_DIR, "_lra_pycall.so")
+# (named for the interpreter that it is compiled for: it uses more than the stable ABI, and no other one may load it)
+PYCALL_PATH = os.path.join(PKG_DIR, "_lra_pycall" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 # what the compiler reports per kernel (registers, scratch, LDS, occupancy), written by every build
 RESOURCES_PATH = os.path.join(PKG_DIR, "kernel_resources.json")
 
@@ -106,7 +108,6 @@ def build_library(verbose: bool = False) -> str:
     with ThreadPoolExecutor(max_workers=min(len(jobs), os.cpu_count() or 1)) as pool:
         tables = list(pool.map(lambda j: _run(j[0], verbose), jobs))
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *[o for _, o in jobs], "-o", LIB_PATH], verbose)
-    import sysconfig
     _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-I", sysconfig.get_paths()["include"], *inc,
           os.path.join(CSRC, PYCALL_SOURCE), "-o", PYCALL_PATH], verbose)
     import json

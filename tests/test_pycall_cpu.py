@@ -2,6 +2,8 @@
 views, numbers of other types; what is no descriptor is refused; an error of a tensor comes through.  The C functions are
 replaced by callbacks that note what they get."""
 import ctypes
+import os
+import sysconfig
 
 import numpy as np
 import pytest
@@ -110,3 +112,10 @@ def test_stream_hooks_come_as_a_pair(monkeypatch):
         one = type("C", (), {k: staticmethod(getattr(both, k)) for k in ("_cuda_getCurrentRawStream", "_cuda_getDevice") if k != missing})
         raw, device = B._stream_hooks(one)
         assert raw(device()) == 99
+
+
+def test_module_is_this_interpreters():
+    """Its name carries the interpreter's ABI, so that another one finds no module rather than a foreign binary."""
+    lra.load_library()
+    assert B.PYCALL_PATH.endswith(sysconfig.get_config_var("EXT_SUFFIX")) and len(sysconfig.get_config_var("EXT_SUFFIX")) > len(".so")
+    assert os.path.realpath(B._entry_points().__file__) == os.path.realpath(B.PYCALL_PATH)
