@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import os
 import re
+import shutil
 import subprocess
 import sysconfig
 
@@ -81,7 +82,7 @@ def _run(cmd, verbose):
             rest.append(ln)
     err = "\n".join(rest)
     if res.returncode != 0:
-        raise RuntimeError(f"hipcc failed ({res.returncode}): {' '.join(cmd)}\n{err}")
+        raise RuntimeError(f"{os.path.basename(cmd[0])} failed ({res.returncode}): {' '.join(cmd)}\n{err}")
     if verbose and err.strip():
         print(err)
     return _parse_resource_remarks("\n".join(remarks))
@@ -89,7 +90,7 @@ def _run(cmd, verbose):
 
 def build_library(verbose: bool = False) -> str:
     """Compile every source to an object file (in parallel, under _build/), link the shared library, and build the
-    CPython module that calls it."""
+    CPython module that calls it (build_pycall)."""
     from concurrent.futures import ThreadPoolExecutor
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     obj_dir = os.path.join(ROOT, "_build")
@@ -108,8 +109,6 @@ def build_library(verbose: bool = False) -> str:
     with ThreadPoolExecutor(max_workers=min(len(jobs), os.cpu_count() or 1)) as pool:
         tables = list(pool.map(lambda j: _run(j[0], verbose), jobs))
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *[o for _, o in jobs], "-o", LIB_PATH], verbose)
-    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-I", sysconfig.get_paths()["include"], *inc,
-          os.path.join(CSRC, PYCALL_SOURCE), "-o", PYCALL_PATH], verbose)
     import json
     resources = {}
     for (cmd, _), table in zip(jobs, tables):
@@ -117,7 +116,23 @@ def build_library(verbose: bool = False) -> str:
             resources[name] = dict(row, source=os.path.basename(cmd[-3]))
     with open(RESOURCES_PATH, "w") as f:
         json.dump({"source_fingerprint": source_fingerprint(), "kernels": resources}, f, indent=0, sort_keys=True)
+    build_pycall(hipcc, verbose)
     return LIB_PATH
+
+
+def build_pycall(hipcc: str, verbose: bool = False) -> bool:
+    """Compile the CPython module, with the host compiler or else with hipcc's.  Without the interpreter's headers there is
+    none, nor one left from an earlier build: the binding then makes its calls by ctypes."""
+    headers = sysconfig.get_paths()["include"]
+    if os.path.exists(PYCALL_PATH):
+        os.remove(PYCALL_PATH)
+    if not os.path.exists(os.path.join(headers, "Python.h")):
+        print(f"no Python.h under {headers}: calls go through ctypes", flush=True)
+        return False
+    cxx = os.environ.get("CXX") or shutil.which("g++") or hipcc
+    _run([cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-I", headers, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+          os.path.join(CSRC, PYCALL_SOURCE), "-o", PYCALL_PATH], verbose)
+    return True
 
 
 if __name__ == "__main__":

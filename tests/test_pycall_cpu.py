@@ -11,13 +11,14 @@ import torch
 
 import paper_2602_01053_amd as lra
 from paper_2602_01053_amd import binding as B
+from paper_2602_01053_amd import build
 
 vp, i32 = ctypes.c_void_p, ctypes.c_int32
 
 
-@pytest.fixture
-def noted(monkeypatch):
-    """The binding bound to callbacks: (list of calls, status to return)."""
+@pytest.fixture(params=["module", "ctypes"])
+def noted(request, monkeypatch):
+    """The binding bound to callbacks, through the CPython module and by ctypes: (list of calls, status to return)."""
     lib = lra.load_library()
     calls, status = [], [0]
 
@@ -34,6 +35,11 @@ def noted(monkeypatch):
                           vp, vp)(lambda sh, c, ad, *r: note("prefill")(sh[0].rank, c[0].max_seq_len, ad[0].b_k, ad[0].b_v, ad[0].n_adapters, *r))
     fa = ctypes.CFUNCTYPE(ctypes.c_int, P(B.LraShape), P(B.LraCache), P(B.LraProjection), vp, i32, i32, vp, ctypes.c_size_t, vp, vp)(
         lambda sh, c, pr, *r: note("append")(sh[0].rank, c[0].max_seq_len, pr[0].w, pr[0].d_model, pr[0].rope_theta, *r))
+    if request.param == "ctypes":
+        monkeypatch.setattr(B, "_calls", B._CtypesCalls(fd, fp, fa))
+        monkeypatch.setattr(B, "_stream_ptr", lambda s: 4003 if s is None else s.cuda_stream)
+        yield calls, status
+        return
     mod = B._entry_points()
     mod.bind(*[ctypes.cast(f, vp).value for f in (fd, fp, fa)], ctypes.addressof(B._tuning), B.LraShape, B.LraCache,
              lambda: 3, lambda dev: 4000 + dev, lambda: True)
@@ -85,7 +91,7 @@ def test_what_is_refused(noted):
                                ("q", 7, AttributeError), ("n_adapters", None, TypeError), ("workspace", 4096, AttributeError),
                                ("b_v", object(), AttributeError),
                                ("max_queries_per_seq", "x", ValueError)]:
-        with pytest.raises(error):
+        with pytest.raises((error, ctypes.ArgumentError)):
             lra.lra_attn_decode(**{**good, name: value})
     x = torch.zeros(4, 128)
     with pytest.raises(lra.LraError):
@@ -95,11 +101,22 @@ def test_what_is_refused(noted):
     assert not calls
 
 
-def test_missing_module_is_told(monkeypatch):
+def test_library_without_the_module(monkeypatch, tmp_path, capfd):
+    """No module for this interpreter: the library is loaded and called by ctypes; a build without its headers makes none
+    and leaves no stale one."""
+    lra.load_library()
     monkeypatch.setattr(B, "_lib", None)
-    monkeypatch.setattr(B, "PYCALL_PATH", "/nonexistent/_lra_pycall.so")
-    with pytest.raises(RuntimeError, match="missing"):
-        lra.load_library()
+    monkeypatch.setattr(B, "_calls", None)
+    monkeypatch.setattr(B, "PYCALL_PATH", str(tmp_path / "none.so"))
+    assert lra.lra_status_string(0) == "ok" and isinstance(B._entry_points(), B._CtypesCalls)
+    q, shape, cache, lens = _descriptors()
+    with pytest.raises(lra.LraError):  # (refused before any launch: no adapter)
+        lra.lra_attn_decode(shape, cache, None, None, 0, q, lens, lens, 1, q, None, stream=type("S", (), {"cuda_stream": 0})())
+    stale = tmp_path / "stale.so"
+    stale.write_bytes(b"x")
+    monkeypatch.setattr(build, "PYCALL_PATH", str(stale))
+    monkeypatch.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    assert not build.build_pycall("hipcc") and not stale.exists() and "ctypes" in capfd.readouterr().out
 
 
 def test_stream_hooks_come_as_a_pair(monkeypatch):
