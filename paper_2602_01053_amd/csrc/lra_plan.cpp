@@ -849,7 +849,11 @@ static bool few_tokens_stream(const lra_shape* sh, const lra_cache* c, int token
 // 4300 keys 1.07 to 1.12, 5000 1.05 to 1.07 (paged 1.03), 5700 1.04, 9009 to 13000 1.01 to 1.03 (paged 0.98 to 1.01), beyond 1.0 to 1.01 (paged
 // 0.98 to 1.0); 8 agents, two row tiles, 1.07, 1.02, 1.04, 1.0 to 1.04 on 9009 to 11200, 0.99 on 13000 and 15000 (paged 0.97 on 9009); 4 kv
 // heads of group 7, twice as many shares, on 9009 1.05 to 1.08, 10000 1.03 to 1.07, 11200 1.01 to 1.04.  Where a pre-pass forms Qt 0.97 to
-// 1.02; shares below 128 add one more per row and cost what the shorter ones save.
+// 1.02; shares below 128 add one more per row and cost what the shorter ones save.  By kv heads (groups of 4 and 8, ranks 16, 32 and
+// 64, 650 calls; n x kv heads / 256 = 140, 170, 200, 300, 420, 700): 4, 8, 12 ... 48 1.03 to 1.17, 1.0 to 1.1, 1.0 to 1.07, 1.0 to 1.06, 0.99 to 1.1,
+// 0.99 to 1.03; 5 and those above 8 that are no multiple of four 1.01 to 1.08, 0.97 to 1.05, 0.95 to 1.04, then 0.91 to 1.03; 6 and 7 0.91 to
+// 1.02 throughout; 1 to 3, whose more than 64 shares take the slow form of the merge, 0.7 to 0.99 (3 on 23037 at rank 64 0.70).
+// 64 wide with two row tiles at 140 0.95 to 1.0 up to 12 kv heads, from 170 on 0.98 to 1.05.
 static void plan_stream(Plan& pl, const lra_shape* sh, const lra_cache* c, int tokens, int max_queries_per_seq, bool prefill,
                         const Tuning& tune, bool key_adapter) {
   if (sh->key_rope_theta > 0.f || (!prefill && c->n_seqs != 1)) return;
@@ -872,8 +876,11 @@ static void plan_stream(Plan& pl, const lra_shape* sh, const lra_cache* c, int t
   int64_t keys = st.split_keys;
   if (finer) {
     const int64_t fit = kCUs / work, even = (n * work + kCUs - 1) / kCUs;
-    const int64_t most = c->block_size != 0 ? 256 : (st.row_tiles > 1 || st.row_groups > 1 ? 384 : 1024);
-    if (even > 128 && even <= most) {
+    const int hkv = sh->n_kv_heads;
+    const int64_t most = hkv % 4 != 0 ? (hkv == 5 || hkv > 8 ? 192 : 0)
+                                      : (c->block_size != 0 ? 256 : (st.row_tiles > 1 || st.row_groups > 1 ? 384 : 1024));
+    const int64_t from = sh->head_dim == 64 && st.row_tiles > 1 ? 160 : 128;
+    if (even > from && even <= most) {
       const int64_t shares = meeting_shares(fit, sh->n_kv_heads, st.row_groups);
       const int64_t least = ((n + shares - 1) / shares + 31) / 32 * 32;
       keys = least < keys ? least : keys;

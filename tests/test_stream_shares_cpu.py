@@ -82,3 +82,23 @@ def test_cases_of_the_kernel_whose_waves_divide_the_keys_keep_it(planner, runs):
         a = dict(longest=longest, n_new=n_new, paged=paged, side=side)
         shares = _plan(planner, hq, hkv, d, r, [n], **a)["wave_shares"]
         assert _plan(runs, hq, hkv, d, r, [n], **a)["wave_shares"] == shares, (n, n_new)
+
+
+def test_kv_heads_whose_calls_have_them(planner, runs):  # noqa: F811
+    """Key shares of any number of tiles by kv heads: 1 to 3, 6 and 7 keep multiples of 128, 5 and those above 8 that are no multiple of
+    four leave them only for shares of at most 192 keys."""
+    for hkv in (1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 14, 16, 20, 32):
+        for even in (140, 180, 201, 241, 300, 420, 700):
+            n = even * 256 // hkv
+            for r in (16, 64):
+                for paged in (False, True):
+                    a = (hkv * 4, hkv, 128, r, [n])
+                    pl, run = (_plan(x, *a, agents=2, paged=paged) for x in (planner, runs))
+                    most = (256 if paged else 1024) if hkv % 4 == 0 else (192 if hkv == 5 or hkv > 8 else 0)
+                    if even > most:
+                        assert run == pl, (hkv, even, r, paged)
+                    elif even < 241:  # (an even share close below a multiple of 128 is that multiple)
+                        assert run["split_keys"] < pl["split_keys"], (hkv, even, r, paged)
+    for hkv, n, own in ((8, 4500, False), (8, 5500, True)):  # 64 wide, two row tiles
+        pl, run = (_plan(x, hkv * 8, hkv, 64, 32, [n], agents=4, paged=True) for x in (planner, runs))
+        assert (run != pl) == own
