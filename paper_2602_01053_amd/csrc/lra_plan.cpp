@@ -831,16 +831,20 @@ static Plan plan_call(const lra_shape* sh, const lra_cache* c, int tokens, int m
 //   4 kv heads, G 7    3 and 4 tokens 0.92 0.96 1.03 1.08 1.07 1.02 1.0, paged 0.96 0.98 1.07 1.13 1.13 1.15 0.99; 6 and 8 1.02 1.06 1.10 1.08 1.08
 //                      1.05 0.99, paged 1.07 1.09 1.13 1.10 1.10 1.09 1.13; 12 1.11 1.18 1.10 1.15 1.05 1.05 1.0, paged 1.15 1.20 1.12 1.17 1.05 1.0
 //                      0.95 (9 tokens 0.96 to 0.97 at 5.8 k)
-// (Two row groups on the pages of fewer than six kv heads beyond 14 k keep the shares of prefill_rows_kernel: group 7 would gain,
-// group 8 has not been measured.)
+// (Two row groups on the pages of fewer than six kv heads beyond 14 k keep the shares of prefill_rows_kernel: not measured there.)
+// 5, 6 and 7 kv heads, groups of 1 to 16, value-side adapters only, 3300 more calls after the exchange of prefill_rows_kernel and the
+// merge got shorter: 1.07 in the mean, 0.96 at worst.  Groups of one and two q heads fill a quarter and a half of their padded rows: one
+// row group 0.92 to 0.97 to 1800 keys, several 1.0 to 1.15 to 2100 and 0.80 to 0.96 beyond, except with 4 and 5 kv heads (1.0 to 1.1); three of
+// group 1 0.80 to 0.96 from 1750 on.  6 kv heads: one row group 0.96 to 0.99 at 6 thousand (7: 1.0 to 1.04), three 0.89 to 0.97 from 3300 on.
 static bool few_tokens_stream(const lra_shape* sh, const lra_cache* c, int tokens, int row_groups) {
   if (sh->head_dim != 128 || sh->rank > 32 || sh->n_kv_heads < 4 || sh->n_kv_heads > 8 || row_groups > 3) return false;
-  const int rows = tokens * (sh->n_q_heads / sh->n_kv_heads), n = c->max_seq_len;
-  const bool pages = c->block_size != 0, wide = sh->rank > 16, few = sh->n_kv_heads < 6;
-  if (row_groups == 1) return few ? n > (pages ? 2304 : 2560) : n > 1536 && n <= (wide ? 3328 : 7168);
-  if (n <= 900) return false;
+  const int hkv = sh->n_kv_heads, G = sh->n_q_heads / hkv, rows = tokens * G, n = c->max_seq_len;
+  const bool pages = c->block_size != 0, wide = sh->rank > 16, few = hkv < 6;
+  if (row_groups == 1) return few ? n > (pages ? 2304 : 2560) : n > (G < 3 ? 1920 : 1536) && n <= (wide ? 3328 : (hkv == 6 ? 5120 : 7168));
+  if (n <= 900 || (G == 1 && row_groups == 3)) return false;
   if (few) return row_groups == 2 ? !pages || n <= 14336 : n <= 5120 || (!pages && rows >= 84);
-  return n <= (row_groups == 2 ? (wide ? (pages ? 4608 : 6144) : 3584) : (pages ? 3584 : 5120));
+  if (G < 3) return n <= 2304;
+  return n <= (row_groups == 2 ? (wide ? (pages ? 4608 : 6144) : 3584) : (hkv == 6 ? 3072 : (pages ? 3584 : 5120)));
 }
 
 // What the streaming kernel does with a call: key shares of any number of 32-key tiles, which its waves divide as they come.  Shares of

@@ -102,3 +102,14 @@ def test_kv_heads_whose_calls_have_them(planner, runs):  # noqa: F811
     for hkv, n, own in ((8, 4500, False), (8, 5500, True)):  # 64 wide, two row tiles
         pl, run = (_plan(x, hkv * 8, hkv, 64, 32, [n], agents=4, paged=True) for x in (planner, runs))
         assert (run != pl) == own
+
+
+def test_few_token_prefills_of_other_groups_and_heads(runs):
+    """Groups of one and two q heads, whose rows are padded to four, and 6 kv heads leave streaming earlier."""
+    for hkv, group, n_new, n, paged, r, streams in [
+            (8, 2, 8, 1800, False, 16, False), (8, 2, 8, 2000, False, 16, True), (8, 3, 8, 1800, False, 16, True),
+            (8, 2, 24, 2300, False, 16, True), (8, 2, 24, 2600, False, 16, False), (8, 2, 16, 3000, True, 32, False), (6, 1, 16, 2300, True, 16, True),
+            (6, 1, 16, 2600, True, 16, False), (8, 1, 24, 2000, False, 16, False), (4, 1, 24, 4500, False, 16, False), (4, 2, 24, 4500, False, 16, True),
+            (4, 1, 16, 4500, False, 16, True), (6, 4, 24, 3000, False, 16, True), (6, 4, 24, 3300, False, 16, False), (7, 4, 24, 4500, False, 16, True),
+            (6, 4, 8, 5000, False, 16, True), (6, 4, 8, 6000, False, 16, False), (7, 4, 8, 6000, False, 16, True)]:
+        assert _plan(runs, hkv * group, hkv, 128, r, [n], n_new=n_new, paged=paged)["short_prefill"] == streams, (hkv, group, n_new, n, paged, r)
