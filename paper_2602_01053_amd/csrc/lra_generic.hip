@@ -12,6 +12,7 @@
 
 #include "lra_common.h"
 #include "lra_decode_util.h"
+#include "lra_plan.h"
 
 namespace lra {
 
@@ -541,8 +542,6 @@ __global__ __launch_bounds__(kWave) void generic_partial_rope_kernel(Params p) {
 // order: the result does not depend on which workgroup of the first kernel
 // finished first.
 constexpr int kMergeUnroll = 8;  // splits per thread and pass
-// Shares that merge_tokens_kernel has room for.
-constexpr int kMergeTokenShares = 16;
 
 #ifdef LRA_TIMING
 #define LRA_MSTAMP(k) do { unsigned long long t_; asm volatile("s_waitcnt lgkmcnt(0)\n\ts_memrealtime %0\n\ts_waitcnt lgkmcnt(0)" : "=s"(t_)); mt[k] = t_; } while (0)
@@ -1180,36 +1179,9 @@ hipError_t launch_generic_partials(const Params& p, bool is_bf16, int rows, hipS
   return hipGetLastError();
 }
 
-// Which form merges, by rows, splits and rank (us of a launch, captured, 32 q heads over 8 of 128; T: four rows per wave, W: one
-// row per wave, R: one per workgroup):
-//   rows   r 16, 5 splits   r 16, 16 splits   r 32, 5 splits   r 32, 16 splits   r 64, 5 splits   r 64, 16 splits
-//          R    W    T      R    W    T       R    W    T      R    W    T       R    T           R    T
-//   512    3.6  3.9  5.9    3.5  4.3  7.4     3.7  4.8  6.8    3.7  5.2  8.2     4.3  8.6         4.2  10.0
-//   1792   4.9  4.5  6.0    4.9  5.1  7.5     5.4  5.6  6.8    5.5  6.3  8.4     6.7  8.7         6.7  10.2
-//   3072   6.3  5.2  6.1    6.4  5.9  7.7     7.3  6.7  7.0    7.5  7.8  9.3     9.1  8.8         10.1 14.0
-//   6144   9.9  6.9  7.1    11.1 11.0 13.3    11.5 9.6  8.1    12.5 13.3 15.1    15.1 11.1        16.3 19.0
-//   10240  14.6 9.3  9.3    16.0 16.3 18.8    17.2 13.6 10.8   18.2 18.9 21.4    23.2 15.3        23.8 26.9
-// W reads no further than a row's last share with a key, the others read every slot: with a third of 32 shares live, 3072 rows,
-// 11.3 (R) and 6.4 (W) at rank 16, 12.5 and 8.2 at rank 32.  So a batch, whose sequences may leave shares empty, takes W wherever the
-// two come near each other, and a prefill, whose shares are all live, R.
-enum class MergeForm { kColumns, kRows, kWave, kTokens };
-static MergeForm merge_form(const Params& p, bool is_bf16, int rows) {
-  const int r = p.rank, ns = p.n_splits;
-  // (statistics in one wave's lanes, the query index in the grid's z)
-  if (ns > 64 || (p.head_dim != 64 && p.head_dim != 128) || rows / p.n_q_heads > 65535) return MergeForm::kColumns;
-  if (r % 4 != 0) return rows >= 1024 ? MergeForm::kWave : MergeForm::kColumns;
-  if (rows < (r <= 16 || (r <= 32 && !p.is_prefill && ns > 16) ? 1024 : 2560)) return MergeForm::kRows;
-  if (p.is_prefill) {
-    if (is_bf16 && ns <= 10 && (r > 32 || (r > 16 && rows >= 5120)) && (static_cast<int64_t>(p.n_new) * p.group + 15) / 16 <= 65535)
-      return MergeForm::kTokens;
-    if (r > 32 || (ns > 8 && rows < 2560)) return MergeForm::kRows;
-  }
-  return MergeForm::kWave;
-}
-
 template <typename T>
 static void launch_merge_t(const Params& p, bool is_bf16, int rows, hipStream_t s) {
-  switch (merge_form(p, is_bf16, rows)) {
+  switch (merge_form(is_bf16, p.head_dim, p.rank, p.n_q_heads, p.n_kv_heads, p.n_splits, p.is_prefill != 0, rows)) {
     case MergeForm::kRows: return launch_merge_rows<T>(p, rows, s);
     case MergeForm::kWave: return launch_merge_wave<T>(p, rows, s);
     case MergeForm::kTokens: return launch_merge_tokens(p, s);

@@ -1,6 +1,7 @@
 // Launch planning (host only; see lra_plan.h).
 #include "lra_plan.h"
 
+#include <algorithm>
 #include <cmath>
 
 namespace lra {
@@ -149,6 +150,42 @@ int decode_mfma_row_tiles(int rows_needed) { return rows_needed <= 16 ? 1 : 2; }
 // (the B_K^T operands of a tile's slots stay in registers: 4 slots at ranks up to 16, 2 up to 32, 4
 // again above, where the kernel has a compute unit to itself)
 int decode_mfma_rope_slots(int rank) { return rank <= 16 ? 4 : (rank <= 32 ? 2 : 4); }
+
+// Which form merges, by rows, shares, rank and group.  9756 combinations behind a kernel that writes the states (bf16 and fp32, 64 and 128
+// wide, groups of 1, 2, 3, 4, 5, 7, 12 and 16, ranks 16, 32 and 64, 512 to 10240 rows, 3 to 48 shares, all live or a third): 1.02
+// of the best form's time in the mean.  Ratios W (a wave per row) / R (a workgroup per row) and T (four rows per wave) / R, bf16, 128 wide,
+// groups of 4, all shares live:
+//   rows    r 16, 3, 8, 16, 32 shares  r 32                   r 64                   T: r 16, 3, 8 shares  r 32         r 64
+//   1024    0.83 0.94 1.07 1.09        0.93 0.97 1.07 1.13    1.21 1.24 1.24 1.39    1.58 1.48             1.64 1.54    1.72 1.59
+//   2560    0.76 0.91 0.99 0.97        0.86 0.95 1.07 1.03    1.00 1.09 1.20 1.14    1.02 1.12             1.04 1.11    1.04 1.15
+//   3584    0.73 0.89 0.95 1.02        0.82 0.91 1.02 1.02    0.95 1.03 1.13 1.12    0.88 1.05             0.88 1.06    0.88 1.05
+//   6144    0.67 0.71 0.96 0.99        0.74 0.82 1.04 1.00    0.85 0.98 1.13 1.14    0.78 0.91             0.78 0.90    0.77 0.90
+//   10240   0.61 0.67 0.99 1.08        0.68 0.74 0.97 0.99    0.81 0.91 1.06 0.97    0.67 0.81             0.65 0.81    0.62 0.80
+// (fp32 within 0.05 of it; 64 wide 0.05 to 0.1 less for T, and for W up to rank 32.)  W reads no further than a row's last share
+// with a key, the others read every slot: with a third of 32 shares live 0.57 to 0.8 for W up to rank 32.  So a batch, whose
+// sequences may leave shares empty, takes W wherever the two come near each other, and a prefill, whose shares are all live, R.
+// A workgroup of W is four q heads of a kv head.  Groups of 1, 2 and 5 leave two waves and more of four idle: above rank 32 W / R
+// 1.04 to 1.5 (64 wide, group 5, 6144 rows, 16 shares 22.8 / 14.6 us), and T takes the longest prefills that W had (64 wide, rank 16, group
+// 5, 10240 rows, 3 shares, W 11.3, T 9.1 us).
+MergeForm merge_form(bool bf16, int head_dim, int r, int n_q_heads, int n_kv_heads, int ns, bool prefill, int rows) {
+  // (statistics in one wave's lanes, the query index in the grid's z)
+  if (ns > 64 || (head_dim != 64 && head_dim != 128) || rows / n_q_heads > 65535) return MergeForm::kColumns;
+  if (r % 4 != 0) return rows >= 1024 ? MergeForm::kWave : MergeForm::kColumns;
+  if (rows < (r <= 16 || (r <= 32 && !prefill && ns > 16) ? 1024 : 2560)) return MergeForm::kRows;
+  const int G = n_q_heads / n_kv_heads, waves = (G + 3) / 4 * 4;  // (of W's workgroups)
+  const bool wide = r > 32, narrow = head_dim == 64, most_rows = rows >= 9216, idle = (waves - G) * 4 > waves;
+  if (prefill && bf16 && (rows / n_kv_heads + 15) / 16 <= 65535) {
+    int most = 0;  // shares up to which T is ahead
+    if (wide) most = rows >= 5120 ? 10 : 5;
+    else if (r > 16 && rows >= 5120) most = narrow || (idle && most_rows) ? 10 : 5;
+    if (most_rows && waves > G) most = std::max(most, narrow ? (idle ? kMergeTokenShares : 8) : (idle ? 5 : 0));
+    if (ns <= most) return MergeForm::kTokens;
+  }
+  if (wide && (idle || rows < 5120 || ns > (!narrow && most_rows ? 8 : 5)) &&
+      (prefill || ns <= (narrow ? (idle ? 64 : 32) : (idle ? 32 : 16))))
+    return MergeForm::kRows;
+  return prefill && ns > 8 && rows < 2560 ? MergeForm::kRows : MergeForm::kWave;
+}
 
 // The pre-pass pays (one more launch) once a workgroup of the streaming kernel would have to load sixteen 16-row blocks of B_K for
 // each of two row tiles: four agent slots at ranks above 48.  us with the pre-pass / with Qt formed per workgroup, three sets of tensors in

@@ -87,6 +87,12 @@ int stream_grid_shares(int n_kv_heads, int n_splits, int row_groups);
 // rg_interleave of the split-KV kernel's grid (see there), 0: kv head, key share, (sequence, row group).
 int mfma_interleave(int n_kv_heads, int n_splits, int row_groups, bool rotary);
 
+// Kernel that merges the states of `shares` key shares per row: merge_kernel, merge_rows_kernel, merge_wave_kernel, merge_tokens_kernel
+// (which has room for kMergeTokenShares).
+enum class MergeForm { kColumns, kRows, kWave, kTokens };
+constexpr int kMergeTokenShares = 16;
+MergeForm merge_form(bool bf16, int head_dim, int rank, int n_q_heads, int n_kv_heads, int shares, bool prefill, int rows);
+
 // Row tiles per workgroup the split-KV MFMA kernels are built for.
 int decode_mfma_row_tiles(int rows_needed);
 // Agent slots a 16-row tile may hold in the rotary form of the split-KV kernel.

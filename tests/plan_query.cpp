@@ -23,6 +23,21 @@ extern "C" void plan_query(const lra_shape* sh, const lra_cache* c, int tokens, 
   out[16] = static_cast<int32_t>(pl.bytes >> 8);
 }
 
+// The merge kernel that a call ends with (0 merge_kernel, 1 merge_rows_kernel, 2 merge_wave_kernel, 3 merge_tokens_kernel; -1: none) and
+// the shares per row that it takes.
+extern "C" int merge_query(const lra_shape* sh, const lra_cache* c, int tokens, int max_queries_per_seq, int prefill, int key_adapter,
+                           const lra_tuning* tuning, int32_t* shares) {
+  const lra::Plan pl = lra::as_run(lra::make_plan(sh, c, tokens, max_queries_per_seq, prefill != 0, lra::resolve_tuning(tuning), key_adapter != 0));
+  *shares = pl.batch_wgs > 0 ? pl.batch_splits : pl.n_splits;
+  const int wave = pl.wave_rows ? 1 : pl.wave_shares;
+  if (prefill && pl.mfma && !(pl.short_prefill && wave == 0)) {
+    *shares = wave > 0 ? wave : pl.n_splits;
+    if (*shares == 1) return -1;
+  }
+  return static_cast<int>(lra::merge_form(sh->dtype == LRA_BF16, sh->head_dim, sh->rank, sh->n_q_heads, sh->n_kv_heads, *shares, prefill != 0,
+                                          tokens * sh->n_q_heads));
+}
+
 extern "C" int stream_grid_query(int n_kv_heads, int n_splits, int row_groups) { return lra::stream_grid_shares(n_kv_heads, n_splits, row_groups); }
 
 extern "C" int interleave_query(int n_kv_heads, int n_splits, int row_groups, int rotary) {

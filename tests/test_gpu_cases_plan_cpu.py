@@ -32,9 +32,10 @@ def planner(tmp_path_factory):
     return ctypes.CDLL(lib)
 
 
-def _plan(planner, hq, hkv, d, r, lens, *, longest=None, agents=0, n_new=0, paged, side="bk", host=None, variant=0):
+def _call(hq, hkv, d, r, lens, *, longest=None, agents=0, n_new=0, paged, side="bk", host=None, variant=0, fp32=False, split_keys=0, splits=0):
+    """The planner's arguments for a call."""
     n = longest or max(lens)
-    shape = LraShape(hq, hkv, d, r, 0, 0.0, 500000.0 if side.startswith("rotary") else 0.0)
+    shape = LraShape(hq, hkv, d, r, int(fp32), 0.0, 500000.0 if side.startswith("rotary") else 0.0)
     cache = LraCache(n_seqs=len(lens), max_seq_len=n, l_row_stride=r)
     if paged:
         blocks = sum((x + 15) // 16 for x in lens) if longest is None else (n + 15) // 16
@@ -47,10 +48,22 @@ def _plan(planner, hq, hkv, d, r, lens, *, longest=None, agents=0, n_new=0, page
     if host is not None:
         mirror = (ctypes.c_int32 * len(host))(*host)
         cache.seq_lens_host = ctypes.cast(mirror, ctypes.c_void_p)
+    return (ctypes.byref(shape), ctypes.byref(cache), n_new or agents * len(lens), max(agents, 1), int(n_new > 0),
+            int(side not in ("none", "own_none", "rotary_none")),
+            ctypes.byref(LraTuning(kernel_variant=variant, decode_split_keys=split_keys, prefill_splits=splits)))
+
+
+def _plan(planner, *call, **kw):
     out = (ctypes.c_int32 * len(FIELDS))()
-    planner.plan_query(ctypes.byref(shape), ctypes.byref(cache), n_new or agents * len(lens), max(agents, 1), int(n_new > 0),
-                       int(side not in ("none", "own_none", "rotary_none")), ctypes.byref(LraTuning(kernel_variant=variant)), out)
+    planner.plan_query(*_call(*call, **kw), out)
     return dict(zip(FIELDS, out))
+
+
+def _merge(planner, *call, **kw):
+    """The merge kernel that a call ends with, and its shares."""
+    shares = ctypes.c_int32()
+    form = planner.merge_query(*_call(*call, **kw), ctypes.byref(shares))
+    return (("columns", "rows", "wave", "tokens")[form] if form >= 0 else None), shares.value
 
 
 def test_batches_in_one_row(planner):
@@ -99,6 +112,32 @@ def test_long_prefills_that_merge(planner):
         pl = _plan(planner, hq, hkv, d, r, [n], n_new=n_new, paged=True)
         assert n_new * hq >= 9216 and not pl["wave_rows"] and not pl["short_prefill"], (n_new, n)
         assert 2 <= pl["n_splits"] <= 16 if pl["mfma"] else (pl["n_splits"] == 1 and r % 8), (n_new, n)
+
+
+def test_merge_lines(planner):
+    """Which form merges, on both sides of every line of the rule."""
+    def prefill(rows, shares, r, d=128, hq=32, hkv=8, **kw):
+        return _merge(planner, hq, hkv, d, r, [4 * rows], n_new=rows // hq, paged=False, splits=shares, **kw)[0]
+
+    def batch(rows, shares, r, d=128, hq=32, hkv=8):
+        return _merge(planner, hq, hkv, d, r, [128 * shares] * 8, agents=rows // hq // 8, paged=True, split_keys=128)[0]
+
+    for form, args in [
+            ("rows", (992, 5, 16)), ("wave", (1024, 5, 16)), ("rows", (2528, 9, 16)), ("wave", (2560, 9, 16)), ("rows", (2528, 5, 32)),
+            ("wave", (2560, 5, 32)), ("wave", (5088, 5, 32)), ("tokens", (5120, 5, 32)), ("wave", (5120, 6, 32)), ("tokens", (5120, 10, 32, 64)),
+            ("wave", (5120, 11, 32, 64)), ("rows", (2528, 5, 64)), ("tokens", (2560, 5, 64)), ("rows", (2560, 6, 64)), ("tokens", (5120, 10, 64)),
+            ("rows", (5120, 11, 64)), ("wave", (9216, 5, 16)), ("wave", (9216, 5, 16, 64)), ("tokens", (9240, 8, 16, 64, 28, 4)),
+            ("wave", (9240, 9, 16, 64, 28, 4)), ("tokens", (9240, 16, 16, 64, 40, 8)), ("wave", (9240, 17, 16, 64, 40, 8)),
+            ("tokens", (9240, 5, 16, 128, 40, 8)), ("wave", (9240, 6, 16, 128, 40, 8)), ("tokens", (9240, 10, 32, 128, 40, 8)),
+            ("wave", (9200, 5, 16, 64, 40, 8))]:
+        assert prefill(*args) == form, args
+    for form, args in [
+            ("rows", (768, 5, 16)), ("wave", (1024, 5, 16)), ("wave", (1024, 17, 32)), ("rows", (1024, 16, 32)), ("wave", (2560, 16, 32)),
+            ("rows", (2304, 5, 64)), ("rows", (5120 - 256, 5, 64)), ("wave", (5120, 5, 64)), ("rows", (5120, 6, 64)), ("rows", (9216 - 256, 8, 64)),
+            ("wave", (9216, 8, 64)), ("rows", (9216, 9, 64)), ("rows", (2560, 16, 64)), ("wave", (2560, 17, 64)), ("rows", (2560, 32, 64, 64)),
+            ("wave", (2560, 33, 64, 64)), ("rows", (5120, 5, 64, 128, 32, 32)), ("rows", (2560, 32, 64, 128, 32, 32)),
+            ("wave", (2560, 33, 64, 128, 32, 32)), ("rows", (2560, 64, 64, 64, 32, 32)), ("columns", (2560, 65, 64, 64))]:
+        assert batch(*args) == form, args
 
 
 def test_rotary_calls_with_shares_of_two_sizes(planner):
