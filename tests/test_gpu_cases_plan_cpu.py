@@ -11,6 +11,7 @@ import pytest
 
 from paper_2602_01053_amd.binding import LraCache, LraShape, LraTuning
 from tests import test_append_gpu as A
+from tests import test_merge_forms_gpu as F
 from tests import test_merge_tokens_gpu as M
 from tests import test_parity_gpu as P
 from tests import test_rope_shares_gpu as R
@@ -108,10 +109,35 @@ def test_prefills_on_the_tile_walk(planner):
 
 
 def test_long_prefills_that_merge(planner):
+    forms = []
     for n_new, n, hq, hkv, d, r, _ in M.CASES:
         pl = _plan(planner, hq, hkv, d, r, [n], n_new=n_new, paged=True)
         assert n_new * hq >= 9216 and not pl["wave_rows"] and not pl["short_prefill"], (n_new, n)
         assert 2 <= pl["n_splits"] <= 16 if pl["mfma"] else (pl["n_splits"] == 1 and r % 8), (n_new, n)
+        forms.append(_merge(planner, hq, hkv, d, r, [n], n_new=n_new, paged=True))
+    assert forms == [("tokens", 3), ("wave", 3), ("tokens", 3), ("wave", 3), ("tokens", 7), ("tokens", 1)]
+    reach = set()
+    for n_new, n, hq, hkv, d, r, value_side, shares in M.SHARE_CASES:
+        assert _merge(planner, hq, hkv, d, r, [n], n_new=n_new, paged=False, splits=shares) == ("tokens", shares), (n_new, n)
+        reach.add((d, value_side, shares > 8))
+    assert reach == {(128, True, True), (128, True, False), (128, False, False), (64, True, True), (64, False, True), (64, False, False)}
+
+
+def test_merges_of_many_rows(planner):
+    """A wave per row, in the instantiations that the cases stand for."""
+    def call(case, split, **kw):
+        seqs, agents, hq, hkv, d, r, longest = case
+        return _merge(planner, hq, hkv, d, r, [longest] * seqs, longest=longest, agents=agents, paged=True, split_keys=split, **kw)
+    reach = set()
+    for case in F.WAVE_CASES:
+        form, shares = call(case, 128)
+        assert form == "wave", case
+        reach.add((case[4], 16 if case[5] <= 16 else 32 if case[5] <= 32 else 64, shares <= 4))
+    assert reach >= {(128, 64, True), (128, 64, False), (64, 64, False), (64, 32, False), (128, 32, True)}
+    forms = [call((*c, 699), 128)[0] for c in P.test_many_rows_take_the_wave_per_row_merge.pytestmark[0].args[1]]
+    assert forms == ["wave", "rows", "rows", "wave"]
+    forms = [call(c, 64) for c in F.test_many_rows_of_ragged_batches.pytestmark[0].args[1]]
+    assert [f[0] for f in forms] == ["wave", "rows", "wave", "rows", "wave"]
 
 
 def test_merge_lines(planner):

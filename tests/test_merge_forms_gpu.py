@@ -56,6 +56,27 @@ def test_many_rows_of_ragged_batches(case):
         lra.lra_set_decode_split_keys(old)
 
 
+# sequences, agents, Hq, Hkv, d, r, longest (shares of 128 keys): a wave per row at ranks above 16, up to four shares and more (a second
+# request of B_V above rank 32), more than 16 and 32, groups of 16, 7 and 4
+WAVE_CASES = [
+    (40, 8, 16, 1, 128, 64, 500), (40, 8, 16, 1, 128, 36, 600), (20, 8, 16, 1, 128, 40, 2300), (20, 8, 32, 8, 64, 48, 4300),
+    (37, 5, 14, 2, 64, 24, 700), (21, 4, 32, 8, 128, 32, 450),
+]
+
+
+@pytest.mark.parametrize("case", WAVE_CASES, ids=lambda c: "q%dx%d_%dover%d_d%d_r%d_n%d" % c)
+def test_a_wave_per_row(case):
+    seqs, agents, hq, hkv, d, r, longest = case
+    lens = [longest] + [int(x) for x in np.random.default_rng(sum(case)).integers(1, longest, size=seqs - 1)]
+    w = W.make_paged("merge", seed=sum(case), seq_lens=lens, agents_per_seq=agents, n_adapters=3, n_q_heads=hq, n_kv_heads=hkv,
+                     head_dim=d, rank=r, d_model=None, b_std=0.05)
+    old = lra.lra_set_decode_split_keys(128)
+    try:
+        _check(run_decode(w, DEV), oracle_decode(w))
+    finally:
+        lra.lra_set_decode_split_keys(old)
+
+
 @pytest.mark.parametrize("case", [
     # new tokens, keys, Hq, Hkv, d, r, shares
     (70, 700, 32, 8, 128, 16, 4), (70, 1400, 32, 8, 128, 16, 9), (90, 1300, 32, 8, 64, 16, 11), (90, 700, 28, 4, 128, 24, 3),

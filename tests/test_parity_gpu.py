@@ -801,8 +801,9 @@ def test_machine_probes_run():
     (70, 3, 5, 5, 64, 8),       # 1050 rows, group of 1 (three of four waves idle)
 ], ids=lambda c: "s%d_a%d_hq%d_hkv%d_d%d_r%d" % c)
 def test_many_rows_take_the_wave_per_row_merge(case):
-    """Calls with 1024 rows or more end with the wave-per-row form of the merge kernel: ragged paged batches
-    with many short sequences (so that most key shares of most rows are empty), every group size class."""
+    """Ragged paged batches of 1024 rows and more with many short sequences (so that most key shares of most rows are
+    empty), every group size class: at ranks up to 16 the merge is a wave per row, at the two above a workgroup per row
+    (tests/test_merge_forms_gpu.py has the wave per row of those ranks, from 2560 rows on)."""
     n_seqs, agents, hq, hkv, d, r = case
     rng = np.random.default_rng(sum(case))
     lens = [int(x) for x in rng.integers(1, 700, size=n_seqs)]
