@@ -827,7 +827,8 @@ __global__ __launch_bounds__(256) void merge_rows_kernel(Params p) {
 template <typename T, int D, int RB, int U>
 __global__ __launch_bounds__(256) void merge_wave_kernel(Params p) {
   constexpr int CPL = D / 64;   // columns per lane: c = CPL * lane + k
-  constexpr int SPL = 64 / RB;  // splits whose O_lr entries one load brings
+  constexpr int SPL = 64 / RB;  // splits whose O_lr entries one load brings: four, or one above rank 16
+  static_assert(SPL == 4 || SPL == 1, "how their lanes are added up");
   // (as in merge_rows_kernel: the parameter block in one round trip, a grid (kv head, group of four q
   // heads, query) without divisions, the adapter id requested by hand ahead of the vector loads, and
   // unconditional loads from clamped indices)
@@ -911,11 +912,6 @@ __global__ __launch_bounds__(256) void merge_wave_kernel(Params p) {
     }
   }
   if constexpr (SPL == 4) olr = sum_over_lane_groups(olr);
-  if constexpr (SPL == 2) {
-    float other = olr;
-    permlane32_swap(olr, other);
-    olr += other;
-  }
   // epilogue O += O_lr B_V
   if (has_bv) {
     for (int r0 = 0; r0 < r; r0 += BN) {
@@ -1121,9 +1117,10 @@ static void launch_merge_wave(const Params& p, int rows, hipStream_t s) {
     if (p.head_dim == 128) hipLaunchKernelGGL((merge_wave_kernel<T, 128, RB, U>), grid, dim3(256), 0, s, p);
     else hipLaunchKernelGGL((merge_wave_kernel<T, 64, RB, U>), grid, dim3(256), 0, s, p);
   };
+  // (bound 64 for rank 16 1.02 to 1.27 times as long, a bound of 32 for ranks 17 to 32 0.99 to 1.02; eight shares requested at a time where
+  // there are three 1.03 to 1.07)
   auto by_rank = [&](auto u_c) {
     if (p.rank <= 16) launch(std::integral_constant<int, 16>{}, u_c);
-    else if (p.rank <= 32) launch(std::integral_constant<int, 32>{}, u_c);
     else launch(std::integral_constant<int, 64>{}, u_c);
   };
   if (p.n_splits <= 4) by_rank(std::integral_constant<int, 4>{});
@@ -1140,6 +1137,8 @@ static void launch_merge_rows(const Params& p, int rows, hipStream_t s) {
     if (p.head_dim == 128) hipLaunchKernelGGL((merge_rows_kernel<T, 128, NS, RB>), grid, dim3(256), 0, s, p);
     else hipLaunchKernelGGL((merge_rows_kernel<T, 64, NS, RB>), grid, dim3(256), 0, s, p);
   };
+  // (a bound of 64 for 3, 16 and 32 shares 1.24 to 1.45, 1.19 to 1.31 and 1.07 to 1.15 times as long, for ranks 16 and 32 1.04 to
+  // 1.09 and 1.03 to 1.05)
   auto by_rank = [&](auto ns_c) {
     if (p.rank <= 16) launch(ns_c, std::integral_constant<int, 16>{});
     else if (p.rank <= 32) launch(ns_c, std::integral_constant<int, 32>{});
