@@ -300,7 +300,9 @@ size_t lra_workspace_bytes(const lra_shape* shape, const lra_cache* cache, int32
  *   out              DEVICE [n_queries][Hq][d], same dtype as q
  *   workspace        DEVICE, 256-byte aligned, >= lra_workspace_bytes(...); contents
  *                    undefined afterwards.  Calls that overlap in time need
- *                    separate workspaces.
+ *                    separate workspaces.  (With less, calls that other key shares or another
+ *                    kernel can serve within it take those, at a cost in time; the others
+ *                    are refused with LRA_ERR_WORKSPACE.)
  */
 lra_status lra_attn_decode(const lra_shape* shape, const lra_cache* cache,
                            const lra_adapters* adapters, const void* q,

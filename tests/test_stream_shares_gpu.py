@@ -10,7 +10,7 @@ import paper_2602_01053_amd as lra
 from paper_2602_01053_amd import workloads as W
 from paper_2602_01053_amd.runner import DeviceWorkload
 from tests.harness import MAX_ABS_TOL, REL_L2_TOL, _f64, errors, oracle_decode, oracle_prefill, run_prefill
-from tests.test_gpu_cases_plan_cpu import _plan
+from tests.test_gpu_cases_plan_cpu import _plan, planner  # noqa: F401 (a fixture)
 from tests.test_stream_shares_cpu import runs  # noqa: F401 (a fixture)
 
 pytestmark = pytest.mark.gpu
@@ -96,3 +96,33 @@ def test_workspace_without_room_for_these_shares():
     dw.workspace = torch.empty(least - 256, dtype=torch.uint8, device=DEV)
     with pytest.raises(lra.LraError):
         dw.decode()
+
+
+def test_few_new_tokens_without_room_for_these_shares(runs, planner):  # noqa: F811
+    """A few-token prefill whose workspace has room for the shares of its other path only: that path runs, and below its need the
+    call is refused."""
+    n_new, n, hq, hkv, d, r = 8, 4500, 32, 8, 128, 16
+    a = (hq, hkv, d, r, [n])
+    other, run = (_plan(x, *a, n_new=n_new, paged=False) for x in (planner, runs))
+    assert run["short_prefill"] and not other["short_prefill"] and not other["wave_rows"]
+    align = lambda x: (x + 255) // 256 * 256
+    rows, shares = n_new * hq, other["n_splits"]
+    need = lambda k: align(rows * k * 8) + align(rows * k * d * 4) + align(rows * k * r * 4) + align(rows * 4)
+    assert need(shares) < need(run["n_splits"])
+    w = W.make_contiguous("shares", "prefill", seed=4, n_agents=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, rank=r, n=n, n_new=n_new, b_std=0.1)
+    ref = oracle_prefill(w)
+    dw = DeviceWorkload(w, DEV)
+    dw.alloc_workspace()
+    assert dw.workspace.numel() == need(run["n_splits"])
+    outs = []
+    for nbytes in (need(run["n_splits"]), need(run["n_splits"]) - 256, need(shares)):
+        dw.workspace = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
+        dw.out.fill_(float("nan"))
+        dw.prefill()
+        torch.cuda.synchronize()
+        outs.append(dw.out.to(torch.float64).cpu().numpy())
+        _check(outs[-1], ref)
+    assert (outs[1] == outs[2]).all() and (outs[0] != outs[1]).any()  # (one path with either of the smaller ones, another with the largest)
+    dw.workspace = torch.empty(need(shares) - 256, dtype=torch.uint8, device=DEV)
+    with pytest.raises(lra.LraError):
+        dw.prefill()
