@@ -33,7 +33,7 @@ def planner(tmp_path_factory):
     return ctypes.CDLL(lib)
 
 
-def _call(hq, hkv, d, r, lens, *, longest=None, agents=0, n_new=0, paged, side="bk", host=None, variant=0, fp32=False, split_keys=0, splits=0):
+def _call(hq, hkv, d, r, lens, *, longest=None, agents=0, n_new=0, paged, side="bk", host=None, variant=0, fp32=False, split_keys=0, splits=0, short_prefill=0):
     """The planner's arguments for a call."""
     n = longest or max(lens)
     shape = LraShape(hq, hkv, d, r, int(fp32), 0.0, 500000.0 if side.startswith("rotary") else 0.0)
@@ -51,7 +51,7 @@ def _call(hq, hkv, d, r, lens, *, longest=None, agents=0, n_new=0, paged, side="
         cache.seq_lens_host = ctypes.cast(mirror, ctypes.c_void_p)
     return (ctypes.byref(shape), ctypes.byref(cache), n_new or agents * len(lens), max(agents, 1), int(n_new > 0),
             int(side not in ("none", "own_none", "rotary_none")),
-            ctypes.byref(LraTuning(kernel_variant=variant, decode_split_keys=split_keys, prefill_splits=splits)))
+            ctypes.byref(LraTuning(kernel_variant=variant, decode_split_keys=split_keys, prefill_splits=splits, short_prefill=short_prefill)))
 
 
 def _plan(planner, *call, **kw):

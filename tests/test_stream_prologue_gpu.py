@@ -1,6 +1,7 @@
 """Streaming decode and few-token prefills where the prologue's division can go wrong: one and two row tiles, two waves to a tile, Qt
 blocks from one to sixteen per tile (empty agent slots, ranks that end inside a block, Qt from the pre-pass and without one), no
-key-side adapter, and streaming waves without a key, whose states the merge of the eight waves reads too.  Same gate as everywhere."""
+key-side adapter, and streaming waves without a key, whose states the merge of the eight waves reads too.  (That these calls stream is
+asked of the planner in tests/test_stream_shares_cpu.py.)  Same gate as everywhere."""
 import pytest
 import torch
 
@@ -24,6 +25,7 @@ CASES = [
     (31, 1, 8, 8, 64, 8, True), (97, 8, 32, 8, 128, 16, False), (300, 5, 32, 8, 128, 16, True), (700, 8, 32, 8, 64, 16, True),
     (1100, 3, 28, 4, 128, 16, True), (600, 4, 28, 4, 128, 32, True), (700, 2, 16, 1, 128, 64, True), (513, 2, 16, 1, 64, 48, True),
     (600, 7, 32, 8, 128, 24, True), (900, 2, 32, 8, 128, 64, True), (260, 6, 32, 8, 128, 40, False),
+    (900, 8, 32, 8, 128, 64, True), (1000, 7, 32, 8, 64, 56, True),  # (with the pre-pass)
 ]
 
 
@@ -57,8 +59,10 @@ def test_sixteen_blocks_of_each_of_two_row_tiles():
     _check(dw.out.to(torch.float64).cpu().numpy(), oracle_decode(w))
 
 
-@pytest.mark.parametrize("n_new,n,hq,hkv,d,r", [(1, 40, 8, 8, 64, 8), (7, 1000, 32, 8, 128, 16), (5, 900, 32, 8, 128, 64), (3, 700, 28, 4, 128, 24),
-                                                (13, 600, 8, 2, 128, 48)])
+PREFILL_CASES = [(1, 40, 8, 8, 64, 8), (7, 1000, 32, 8, 128, 16), (5, 900, 32, 8, 128, 64), (3, 700, 28, 4, 128, 24), (13, 600, 8, 2, 128, 48)]
+
+
+@pytest.mark.parametrize("n_new,n,hq,hkv,d,r", PREFILL_CASES)
 def test_few_new_tokens(n_new, n, hq, hkv, d, r):
     w = W.make_contiguous("prologue", "prefill", seed=n, n_agents=1, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, rank=r, n=n, n_new=n_new, b_std=0.1)
     old = lra.lra_set_short_prefill(33)  # (the split-KV path, whatever the sizes)

@@ -8,6 +8,7 @@ import subprocess
 import pytest
 
 from tests import test_parity_gpu as P
+from tests import test_stream_prologue_gpu as S
 from tests.test_gpu_cases_plan_cpu import ROOT, _plan, planner  # noqa: F401 (a fixture)
 
 
@@ -113,3 +114,21 @@ def test_few_token_prefills_of_other_groups_and_heads(runs):
             (4, 1, 16, 4500, False, 16, True), (6, 4, 24, 3000, False, 16, True), (6, 4, 24, 3300, False, 16, False), (7, 4, 24, 4500, False, 16, True),
             (6, 4, 8, 5000, False, 16, True), (6, 4, 8, 6000, False, 16, False), (7, 4, 8, 6000, False, 16, True)]:
         assert _plan(runs, hkv * group, hkv, 128, r, [n], n_new=n_new, paged=paged)["short_prefill"] == streams, (hkv, group, n_new, n, paged, r)
+
+
+def test_calls_of_the_prologue_tests_stream(runs):
+    seen = set()
+    for n, agents, hq, hkv, d, r, key_side in S.CASES:
+        pl = _plan(runs, hq, hkv, d, r, [n], agents=agents, paged=False, side="bk" if key_side else "none")
+        assert pl["mfma"] and hkv * pl["n_splits"] * pl["row_groups"] <= 256, (n, agents)
+        seen.add((pl["row_tiles"], d, pl["qt_bytes"] > 0, key_side))
+    assert seen >= {(1, 64, False, True), (1, 128, False, True), (2, 64, False, True), (2, 128, False, True), (2, 128, True, True), (2, 64, True, True),
+                    (2, 128, False, False)}
+    tiles = set()
+    for n_new, n, hq, hkv, d, r in S.PREFILL_CASES:
+        pl = _plan(runs, hq, hkv, d, r, [n], n_new=n_new, paged=False, short_prefill=33)
+        assert pl["short_prefill"] and not pl["wave_rows"] and hkv * pl["n_splits"] * pl["row_groups"] <= 256, (n_new, n)
+        tiles.add(pl["row_tiles"])
+    assert tiles == {1, 2}
+    pl = _plan(runs, 32, 8, 128, 64, [11000], agents=17, paged=True, split_keys=11000)  # (three row groups, one share)
+    assert pl["row_groups"] == 3 and pl["n_splits"] == 1 and pl["qt_bytes"] == 0 and pl["row_tiles"] == 2
