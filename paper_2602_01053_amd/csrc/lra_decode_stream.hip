@@ -582,7 +582,8 @@ __device__ __forceinline__ void decode_stream(const Params& p) {
   float m_run[RT], l_run[RT];  // m_run in base-2 units of the scaled score
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
-    m_run[rt] = -INFINITY;
+    // (the lowest finite number, not minus infinity: a wave's first tile may have no score above that, which then has weight zero)
+    m_run[rt] = -3.4028234663852886e38f;
     l_run[rt] = 0.f;
 #pragma unroll
     for (int b = 0; b < DB; ++b) o_acc[rt][b] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -669,8 +670,7 @@ __device__ __forceinline__ void decode_stream(const Params& p) {
       mx = max_over_lane_groups(mx) * sc;  // sc > 0
       if (__builtin_amdgcn_ballot_w64(mx > m_run[rt]) != 0) {
         const float m_new = fmaxf(m_run[rt], mx);
-        // causal form: a row may have seen no key yet (both maxima -inf)
-        const float alpha = (CAUSAL && m_new == -INFINITY) ? 1.f : fast_exp2(m_run[rt] - m_new);
+        const float alpha = fast_exp2(m_run[rt] - m_new);
         m_run[rt] = m_new;
         l_run[rt] *= alpha;
 #pragma unroll
@@ -678,7 +678,7 @@ __device__ __forceinline__ void decode_stream(const Params& p) {
 #pragma unroll
         for (int b = 0; b < RB; ++b) lr_acc[rt][b] *= alpha;
       }
-      const float nm = (CAUSAL && m_run[rt] == -INFINITY) ? 0.f : -m_run[rt];
+      const float nm = -m_run[rt];
       float pe[8];
       float sum = 0.f;
 #pragma unroll
@@ -779,10 +779,10 @@ __device__ __forceinline__ void decode_stream(const Params& p) {
       ml[w] = *reinterpret_cast<const f32x2*>(smem + w * WAVE_BYTES + rt * (NBLK * 1024 + 512) + NBLK * 1024 + lane * 8);
       m_all = fmaxf(m_all, ml[w][0]);
     }
-    // m_all is finite (wave 0 always owns a key) unless a causal row sees none of this split
+    // (a wave whose row has seen no key, or none with a score, left the lowest number, zero sums and a zero l)
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      wgt[w] = ml[w][0] == -INFINITY ? 0.f : fast_exp2(ml[w][0] - m_all);
+      wgt[w] = fast_exp2(ml[w][0] - m_all);
       l_all = fmaf(wgt[w], ml[w][1], l_all);
     }
     if (out_row[rt] < 0) continue;

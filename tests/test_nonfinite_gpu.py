@@ -113,3 +113,20 @@ def test_nan_of_one_share_of_a_prefill(d, r, shares):
     nan = np.zeros(got.shape[:2], bool)
     nan[:, 12:16] = True
     _nan_rows(got, ref, nan)
+
+
+@pytest.mark.parametrize("lo,hi", [(0, 32), (128, 160), (160, 192), (192, 224), (480, 512), (160, 320), (0, 480), (0, 4099)])
+@pytest.mark.parametrize("agents,prefill", [(2, False), (8, False), (1, True)])
+def test_streaming_kernel_with_keys_below_the_type(lo, hi, agents, prefill):
+    """Key shares of 160 keys, of which a wave of the streaming kernel has one 32-key tile or two: a tile, a share or several without
+    weight, where a wave or a share begins and elsewhere."""
+    n = 4100 if agents < 8 else 4500
+    if prefill:
+        n, hi = 4500, min(hi, 4492)
+    w = W.make_contiguous("mask", "prefill" if prefill else "decode", seed=lo + hi + agents, n_agents=agents, n_q_heads=32, n_kv_heads=8,
+                          head_dim=128, rank=16, n=n, n_new=8 if prefill else 1, b_std=0.1)
+    w.q.abs_().add_(0.5)
+    w.k_base[lo:hi] = torch.finfo(w.k_base.dtype).min
+    rel, mx = errors(_run(w, prefill), oracle_prefill(w) if prefill else oracle_decode(w))
+    print(f"relL2={rel:.3e} maxabs={mx:.3e}", flush=True)
+    assert rel <= REL_L2_TOL and mx <= MAX_ABS_TOL
