@@ -443,12 +443,16 @@ static bool prefill_waves_divide_keys(const lra_shape* sh, const lra_cache* c, i
 //
 // The line, from 5000 measured calls (the layer shapes of prefill_waves_divide_keys, 2 to 1000 tokens on 0.25 to 34
 // thousand keys); s = steps of 256 keys per share, T = workgroups per kv head and share.  Inside it 1.13 in the mean,
-// 0.95 at worst:
+// 0.95 at worst.  (Before the exchange of prefill_rows_kernel and the merge got shorter and few_tokens_stream came; outside it now,
+// ratio of the time as the lines are / on this path, 420 calls of 2, 4 and 8 kv heads: T = 1 with 8 kv heads 5 and 8 tokens on
+// 9009 1.0 to 1.05, paged 1.07 to 1.11, on 13000 1.05 to 1.13, 3 tokens 0.89 to 0.95; with 4 of group 7 5 and 8 tokens 0.84 to 0.95 to 9009,
+// 1.08 to 1.11 on 13000; T = 2 to 4 on contiguous caches, 8 kv heads, 12 to 32 tokens 1.05 to 1.27 from 6644 keys on, 4 kv heads 16 tokens 1.06
+// to 1.26, 2 kv heads 1.0 to 1.14.)
 //   fewer workgroup steps than compute units: 0.72 to 1.05.
 //   s < 1.4: 0.93 to 1.02 (8 kv heads, 10 tokens on 4568).
 //   T = 1, above 16 kv heads and with two row tiles of the split-KV kernel: shares of 512 keys, 1.02 to 1.2 to s = 8;
-//     with one row tile 0.87 to 1.0, with fewer kv heads 0.83 to 1.07 (8 kv heads, 8 tokens after 9001: 16.1 / 16.4 us).
-//   T = 2 to 4 on contiguous caches: 0.88 to 1.1 (10 tokens on 6644: 16.2 / 18.4 us; paged 1.06 in the mean, from 0.96).
+//     with one row tile 0.87 to 1.0, with fewer kv heads 0.83 to 1.07 (8 kv heads, 8 tokens after 9001: 16.1 / 16.4 us, 14.9 / 14.9 now).
+//   T = 2 to 4 on contiguous caches: 0.88 to 1.1 (10 tokens on 6644: 16.2 / 18.4 us; 12 14.8 / 14.0 now; paged 1.06 in the mean, from 0.96).
 //   T > 1, up to the s where the 128 rows of the tile walk, which read the keys fewer times, catch up: 1.0 to 1.4 up to 6
 //     where T fills the last such tile, 7, 11 and 12 at T % 4 = 3, 2, 1; beyond 0.66 to 1.0 (107 after 30000 0.72).
 //     Above 16 kv heads, whose keys come from memory, to 4.
