@@ -54,7 +54,7 @@ MIN_TIMED_SECONDS = 0.02      # a timed region is repeated until it is at least 
 
 def graph_seconds(torch, launch, n, min_seconds=MIN_TIMED_SECONDS, max_replays=2000):
     """Seconds per launch of `launch(i, stream)`, i = 0..n-1, enqueued back to back: the n calls are
-    captured into a HIP graph (so that no Python or ctypes time sits between two launches; a decode
+    captured into a HIP graph (so that no Python or binding time sits between two launches; a decode
     step is shorter than that overhead) and the graph is replayed between two HIP events on the
     stream it runs on, as often as it takes to fill min_seconds.  Returns (seconds per launch,
     launches timed).  A HIP event pair costs about 6 us here, which is why events bracket whole
@@ -642,7 +642,7 @@ def main():
                    "python_loop_ms_per_step": round(ksec["loop_cold"] * 1e3, 6),
                    "python_loop_GBps": round(alg_bytes / ksec["loop_cold"] / 1e9, 1),
                    "python_loop_note": "exactly K calls issued one by one from Python between two synchronisations: "
-                                       "includes the interpreter and ctypes time per call"},
+                                       "includes the interpreter and the binding per call"},
         "roofline": _traffic_fields({"bound": "hbm", "kernel": decode_kernel_label(w), "achieved": round(k_gbs, 1),
                                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(k_gbs / HBM_PEAK_GBS, 4),
                                      "kernel_us": round(ksec["cold"] * 1e6, 3)}, "decode_cfg2", ksec["cold"]),

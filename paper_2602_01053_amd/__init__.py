@@ -1,4 +1,4 @@
-"""Flash-LoRA-Attention for MI355X: ctypes binding over the in-tree HIP library."""
+"""Flash-LoRA-Attention for MI355X: binding over the in-tree HIP library."""
 from .binding import (  # noqa: F401
     LraAdapters, LraCache, LraError, LraProjection, LraShape, LraTuning, lra_attn_decode, lra_attn_decode_static, lra_attn_prefill,
     lra_append_workspace_bytes, lra_cache_append, lra_set_append_k_splits, lra_probe_mfma_bf16, lra_probe_stream_read, lra_set_append_skinny, lra_set_append_stages, lra_set_append_tile,

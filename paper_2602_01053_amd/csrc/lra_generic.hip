@@ -134,8 +134,9 @@ constexpr int kGenericRowBits = 23;
 // its V rows as soon as those of the one before are used up, so that three workgroups fit the registers of a compute unit.
 // Parameter block, adapter id and length come in one round trip each, the layout and the rank's bound are template
 // arguments (13 KB of code otherwise, of which a small call executes a third).  With scores, weights and L rows through LDS
-// (two barriers a step, 18 dependent LDS permutes) two agents on 512 fp32 keys took 6.23 us in this kernel, 3.82 so; 1024 new
-// fp32 tokens at 32 heads of 128 1353, 739; 8192 fp32 keys, 4 agents, 91, 59; 700 new bf16 tokens of rank 12 578, 294.
+// (two barriers a step, 18 dependent LDS permutes) two agents on 512 fp32 keys took 6.23 us in this kernel, 3.82 so
+// (a captured call less its merge; traced by itself 4.5); 1024 new fp32 tokens at 32 heads of 128 1353, 739; 8192 fp32
+// keys, 4 agents, 91, 59; 700 new bf16 tokens of rank 12 578, 294.
 // K and V rows are 16-byte aligned (bases and strides are checked); L rows of a rank that is no multiple of four
 // are not, and are read element by element.
 template <typename T, int D, bool PAGED, int RB>
@@ -690,7 +691,8 @@ __global__ __launch_bounds__(128 * kMergeGroups) void merge_kernel(Params p) {
 //   - the waves' sums meet in LDS behind the only barrier; then a wave finishes a quarter of the columns, sixteen lanes of
 //     which each take a quarter of the ranks, with their B_V elements in registers since before the barrier.
 // With weights by ds_bpermute (24 dependent ones), a branch per split and three barriers the launch took 3.57 us behind the
-// headline decode's first kernel, 2.40 so (3.09 and 2.11 behind the fp32 one); a launch that only adds the same parts takes 2.2.
+// headline decode's first kernel, 2.40 so (3.09 and 2.11 behind the fp32 one); a launch that only adds the same parts takes 2.2
+// (all of captured calls, with the merge less without; traced by itself the kernel takes 3.6 and 2.7, its start and end included).
 // NS, RB: bounds of splits and rank (16, 32 or 64).  Every sum runs in a fixed order, so the result does not depend on
 // which workgroup of the first kernel finished first.
 template <typename T, int D, int NS, int RB>
@@ -822,7 +824,7 @@ __global__ __launch_bounds__(256) void merge_rows_kernel(Params p) {
 // head, per workgroup), no LDS and no barrier, so that a CU holds twenty rows' worth of loads
 // in flight instead of four.  Lane = split for the statistics (at most 64 splits), lane =
 // column (pair of columns at d = 128) for the rows; the weight of a split and the entries of
-// O_lr travel by v_readlane.  Splits are added in index order, eight requested at a time, up to the last
+// O_lr travel by v_readlane.  Splits are added in index order, four or eight requested at a time, up to the last
 // one that holds a visible key (in a ragged batch most rows have fewer shares than the grid).
 template <typename T, int D, int RB, int U>
 __global__ __launch_bounds__(256) void merge_wave_kernel(Params p) {
@@ -945,9 +947,9 @@ __global__ __launch_bounds__(256) void merge_wave_kernel(Params p) {
 // The same merge for the rows of a long prefill, which share one adapter: a wave takes four rows of a kv head, reads a
 // piece of 16 bytes per lane, two rows (d = 64: four) with one load, and the B_V slice once for its rows.  Statistics: the
 // sixteen lanes of a DPP row hold sixteen shares of the row that their loads belong to, and hand a weight round by a DPP
-// broadcast.  What bounds it is the states' bytes, which the caches behind the L2s hand over at about 3.5 TB/s (333 tokens of
-// 32 q heads, 5 shares, rank 16: 31 MB in 10.2 us, 10.6 with a wave per row); with a wave per row the loads of B_V, one per
-// rank and row, came on top (rank 64: 512 tokens on 8000 keys in 119 us in place of 128).
+// broadcast.  What bounds it is the states' bytes, which the caches behind the L2s hand over at 2.5 to 2.7 TB/s, launch included (10240 rows of 32 q heads
+// over 8, 5 shares, rank 32: 33 MB in 12.1 us, 12.6 with a wave per row, 17.6 with a workgroup per row; rank 64: 39 MB in 15.6, 20.2
+// and 22.8: the other forms load B_V once per rank and row).
 template <int D>
 __global__ __launch_bounds__(256) void merge_tokens_kernel(Params p) {
   constexpr int RPL = 256 / D;        // rows of one load
